@@ -94,6 +94,13 @@ pq_epilogue epi_zero() {
   return e;
 }
 
+pq_ref_problem ref_problem(int form, int M, int N, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& e) {
+  pq_ref_problem p;
+  memset(&p, 0, sizeof(p));
+  p.form = form; p.M = M; p.N = N; p.K = K; p.A = A; p.B = B; p.epi = e;
+  return p;
+}
+
 // Buffer layout of one linear.  Sections are 256-byte aligned.
 struct lin_layout {
   // ctx (saved by forward for backward)
@@ -124,7 +131,7 @@ lin_layout make_layout(const pq_linear_desc& d) {
   const bool hp8 = d.hp_kind == PQ_HP_LOWRANK_INT8 && d.hp_rank > 0;
   // the dense-branch sections (H, dH, the rank-r GEMM plans) are sized for the dense branch only
   const size_t T = d.tokens, K = d.d_in, N = d.d_out, r = (routed || hp8) ? 0 : d.hp_rank, es = esize(d.io_dtype);
-  const int engine = d.io_dtype == PQ_BF16 ? 0 : 1;
+  const bool bf16 = d.io_dtype == PQ_BF16;   // fp32 I/O: reference-precision products, nothing is split
   cursor c;
   L.mulam = c.take(2 * sizeof(float));
   L.P = c.take(N * K / 8);
@@ -147,15 +154,15 @@ lin_layout make_layout(const pq_linear_desc& d) {
   cursor w;
   L.stat_partials = w.take(2 * sizeof(double) * 1024);
   const int Ti = d.tokens, Ki = d.d_in, Ni = d.d_out, ri = (int)r;
-  L.n_red_a = r ? pq_plan_gemm(engine, Ti, ri, Ni).red_blocks : 0;       // dH GEMM
+  L.n_red_a = r ? (bf16 ? pq_plan_gemm(Ti, ri, Ni).red_blocks : pq_ref_red_blocks(Ti, ri, Ni)) : 0;   // dH GEMM
   if (r && pq_skinny_blocks(Ti) > L.n_red_a) L.n_red_a = pq_skinny_blocks(Ti);   // room for the streaming rank-r kernel's partials
-  L.n_red_b = pq_plan_gemm(engine, Ni, Ki, Ti).red_blocks;                // dW GEMM
+  L.n_red_b = bf16 ? pq_plan_gemm(Ni, Ki, Ti).red_blocks : pq_ref_red_blocks(Ni, Ki, Ti);              // dW GEMM
   size_t sk = 0;
   const int shapes[8][3] = {{Ti, ri, Ki}, {Ti, Ni, ri}, {Ti, ri, Ni}, {Ti, Ki, Ni},
                             {Ti, Ki, ri}, {Ni, Ki, Ti}, {Ni, ri, Ti}, {ri, Ki, Ti}};
   for (const auto& sh : shapes) {
-    if (sh[0] <= 0 || sh[1] <= 0) continue;
-    const size_t b = pq_plan_gemm(engine, sh[0], sh[1], sh[2]).ws_bytes;
+    if (!bf16 || sh[0] <= 0 || sh[1] <= 0) continue;
+    const size_t b = pq_plan_gemm(sh[0], sh[1], sh[2]).ws_bytes;
     if (b > sk) sk = b;
   }
   if (routed) {
@@ -165,7 +172,7 @@ lin_layout make_layout(const pq_linear_desc& d) {
     if (pq_mode2_ws_bytes(Ni, (int)re, d.n_experts, (int)S) > sk) sk = pq_mode2_ws_bytes(Ni, (int)re, d.n_experts, (int)S);
     if (pq_mode2_ws_bytes((int)re, Ki, d.n_experts, (int)S) > sk) sk = pq_mode2_ws_bytes((int)re, Ki, d.n_experts, (int)S);
   }
-  if (hp8) L.n_red_a = pq_plan_gemm(0, Ti, d.hp_rank, Ni).red_blocks;      // the INT8 branch's dH GEMM leaves the partials of d alpha
+  if (hp8) L.n_red_a = pq_plan_gemm(Ti, d.hp_rank, Ni).red_blocks;      // the INT8 branch's dH GEMM leaves the partials of d alpha
   L.red_a = w.take(sizeof(double) * (size_t)(L.n_red_a > 0 ? L.n_red_a : 1));
   L.red_b = w.take(sizeof(double) * (size_t)L.n_red_b);
   L.dH = w.take(T * r * es);
@@ -174,7 +181,7 @@ lin_layout make_layout(const pq_linear_desc& d) {
   L.w_H = w.take(T * r * es);
   L.splitk = w.take(sk);
   // slabs of dA, which shares a launch with dB (whose slabs are in the region above)
-  L.splitk2 = w.take((ri > 0 && Ki > 0) ? pq_plan_gemm(engine, ri, Ki, Ti).ws_bytes : 0);
+  L.splitk2 = w.take((bf16 && ri > 0 && Ki > 0) ? pq_plan_gemm(ri, Ki, Ti).ws_bytes : 0);
   if (routed) {
     L.dYp = w.take(S * N * 2); L.rd = w.take(S * 4); L.dHs = w.take(S * re * 2); L.dXs = w.take(S * K * 2);
     L.dlogit = w.take(T * E * 4);
@@ -335,7 +342,7 @@ extern "C" int pq_onebit_acc(const int8_t* Xq, const uint32_t* packed, int32_t T
   pq_operand B{packed, K / 8, PQ_SRC_BITS8, nullptr};
   pq_epilogue e = epi_zero();
   e.C = acc; e.ldc = N; e.out_kind = PQ_OUT_I32;
-  return pq_launch_gemm(0, T, N, K, A, B, e, (hipStream_t)stream);
+  return pq_launch_gemm(T, N, K, A, B, e, (hipStream_t)stream);
 }
 
 extern "C" size_t pq_linear_ctx_bytes(const pq_linear_desc* d) {
@@ -378,7 +385,6 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
   char* ws = (char*)workspace;
   void* sk_ws = ws + L.splitk;
   const bool bf16 = d->io_dtype == PQ_BF16;
-  const int engine = bf16 ? 0 : 1;
   const int ok = out_kind_of(d->io_dtype);
 
   int8_t* Xq = (int8_t*)(ctx ? cx + L.Xq : ws + L.w_Xq);
@@ -396,20 +402,24 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
     H_skinny = pq_skinny_applies(T, r, K, A, B, e);
   }
   auto launch_H = [&](bool defer) -> int {
-    pq_operand A{X, K, bf16 ? PQ_SRC_KC16 : PQ_SRC_KC32, nullptr};
-    pq_operand B{hpA, K, bf16 ? PQ_SRC_KC16 : PQ_SRC_KC32, nullptr};
     pq_epilogue e = epi_zero();
     e.C = H; e.ldc = r; e.out_kind = ok; e.defer_reduce = defer ? 1 : 0;
+    if (!bf16) {
+      pq_ref_problem p = ref_problem(PQ_REF_CC, T, r, K, {X, K, PQ_SRC_KC32, nullptr}, {hpA, K, PQ_SRC_KC32, nullptr}, e);
+      return pq_launch_ref(&p, 1, nullptr, 0, s, PQP_GEMM_HP_H);
+    }
+    pq_operand A{X, K, PQ_SRC_KC16, nullptr};
+    pq_operand B{hpA, K, PQ_SRC_KC16, nullptr};
     if (H_skinny) return pq_launch_skinny(T, K, A, B, e, s, PQP_GEMM_HP_H);
-    return pq_launch_gemm(engine, T, r, K, A, B, e, s, PQP_GEMM_HP_H, sk_ws);
+    return pq_launch_gemm(T, r, K, A, B, e, s, PQP_GEMM_HP_H, sk_ws);
   };
   // The weight statistics' first stage and the activation quantiser share a launch (rows of up to 8192 elements stay
   // in registers); when H = X A^T splits its contraction it goes first and the sum of its slabs rides along too.
-  const bool combo = d->w_kind == PQ_W_MASTER && bf16 && !prequant && T > 0 && K <= 8192;
+  const bool combo = d->w_kind == PQ_W_MASTER && !prequant && T > 0 && K <= (bf16 ? 8192 : 4096);
   bool H_done = false;
   int H_splits = 0;
-  if (combo && r > 0) {
-    H_splits = H_skinny ? 1 : pq_plan_gemm(0, T, r, K).splits;
+  if (combo && bf16 && r > 0) {
+    H_splits = H_skinny ? 1 : pq_plan_gemm(T, r, K).splits;
     if (int e = launch_H(H_splits > 1)) return e;
     H_done = true;
   }
@@ -421,7 +431,7 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
     double* part = (double*)(ws + L.stat_partials);
     if (combo) {
       const bool sum = H_done && H_splits > 1;
-      if (int e = pq_launch_wstats_quant(W_or_packed, n, part, nb, X, T, K, Xq, gamma, Xt, s, sum ? (const float*)sk_ws : nullptr, H_splits,
+      if (int e = pq_launch_wstats_quant(W_or_packed, d->io_dtype, n, part, nb, X, T, K, Xq, gamma, Xt, s, sum ? (const float*)sk_ws : nullptr, H_splits,
                                          T, r, H, r)) return e;
       quant_done = true;
     } else if (int e = pq_launch_wstats_partial(W_or_packed, d->io_dtype, n, part, nb, s)) return e;
@@ -448,7 +458,7 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
   // (the fused form carries beta / alpha through the tile: only while that ratio stays far from the fp32 range, otherwise
   // the two branches are scaled separately as in the Sec. 3.2 sum)
   const bool fuse_hp = bf16 && r > 0 && d->alpha != 0.0f && fabsf(d->alpha) >= 9.5367431640625e-7f * fabsf(d->beta) &&
-                       pq_plan_gemm(0, T, N, K, true).splits == 1;
+                       pq_plan_gemm(T, N, K, true).splits == 1;
   if (r > 0 && !H_done)
     if (int err = launch_H(false)) return err;
   {  // 1-bit branch: Y = fl32(fl32(beta*lambda)/gamma_t) * acc   [+ alpha * H B^T when fused]
@@ -462,18 +472,23 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
       p2.B2 = pq_operand{hpB, r, PQ_SRC_KC16, nullptr};
       p2.K2 = r; p2.scale1 = d->beta / d->alpha; p2.dev_scale1 = mulam + 1; p2.row_div1 = gamma;
       e.scale = d->alpha;
-      if (int err = pq_launch_gemm(0, T, N, K, A, B, e, s, PQP_GEMM_ONEBIT, sk_ws, nullptr, &p2)) return err;
+      if (int err = pq_launch_gemm(T, N, K, A, B, e, s, PQP_GEMM_ONEBIT, sk_ws, nullptr, &p2)) return err;
     } else {
       e.scale = d->beta; e.dev_scale = mulam + 1; e.row_div = gamma;
-      if (int err = pq_launch_gemm(0, T, N, K, A, B, e, s, PQP_GEMM_ONEBIT, sk_ws)) return err;
+      if (int err = pq_launch_gemm(T, N, K, A, B, e, s, PQP_GEMM_ONEBIT, sk_ws)) return err;
     }
   }
   if (r > 0 && !fuse_hp && d->alpha != 0.0f) {  // Y += alpha * H B^T
-    pq_operand A{H, r, bf16 ? PQ_SRC_KC16 : PQ_SRC_KC32, nullptr};
-    pq_operand B{hpB, r, bf16 ? PQ_SRC_KC16 : PQ_SRC_KC32, nullptr};
     pq_epilogue e = epi_zero();
     e.C = Y; e.ldc = N; e.out_kind = ok; e.accumulate = 1; e.scale = d->alpha;
-    if (int err = pq_launch_gemm(engine, T, N, r, A, B, e, s, PQP_GEMM_HP_Y, sk_ws)) return err;
+    if (bf16) {
+      pq_operand A{H, r, PQ_SRC_KC16, nullptr};
+      pq_operand B{hpB, r, PQ_SRC_KC16, nullptr};
+      if (int err = pq_launch_gemm(T, N, r, A, B, e, s, PQP_GEMM_HP_Y, sk_ws)) return err;
+    } else {
+      pq_ref_problem p = ref_problem(PQ_REF_CC, T, N, r, {H, r, PQ_SRC_KC32, nullptr}, {hpB, r, PQ_SRC_KC32, nullptr}, e);
+      if (int err = pq_launch_ref(&p, 1, nullptr, 0, s, PQP_GEMM_HP_Y)) return err;
+    }
   }
   if (hp8)   // Y += alpha * B~ Q(A~ Q(x)) on the codes and gamma formed above
     return pq_hp_int8_fwd(Xq, gamma, hpA, hpB, PQ_BF16, T, K, N, d->hp_rank, d->alpha, Y, 1, cx + L.hp8, L.hp8_bytes,
@@ -496,7 +511,7 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
       pq_epilogue e = epi_zero();
       e.C = cx + L.Hs; e.ldc = re; e.out_kind = PQ_OUT_BF16;
       g1.b_stride = (long)re * K;
-      if (int err = pq_launch_gemm(0, S, re, K, A, B, e, s, PQP_GEMM_EXPERT, sk_ws, &g1)) return err;
+      if (int err = pq_launch_gemm(S, re, K, A, B, e, s, PQP_GEMM_EXPERT, sk_ws, &g1)) return err;
     }
     {
       pq_operand A{cx + L.Hs, re, PQ_SRC_KC16, nullptr};
@@ -504,7 +519,7 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
       pq_epilogue e = epi_zero();
       e.C = cx + L.Ys; e.ldc = N; e.out_kind = PQ_OUT_BF16;
       g1.b_stride = (long)N * re;
-      if (int err = pq_launch_gemm(0, S, N, re, A, B, e, s, PQP_GEMM_EXPERT, sk_ws, &g1)) return err;
+      if (int err = pq_launch_gemm(S, N, re, A, B, e, s, PQP_GEMM_EXPERT, sk_ws, &g1)) return err;
     }
     return pq_launch_combine_fwd(Y, cx + L.Ys, inv, gate, d->alpha, T, k, N, s);
   }
@@ -524,6 +539,51 @@ extern "C" int pq_linear_fwd(const pq_linear_desc* d, const void* X, const void*
 static int hp_int8_bwd_impl(const void* dY, const void* Xt, int32_t dtype, int32_t T, int32_t K, int32_t N, int32_t r, float alpha,
                             const void* ctx, size_t ctx_bytes, void* dX, int32_t accumulate_dX, float* dA, float* dB, void* workspace,
                             size_t workspace_bytes, void* stream, double* red_a);
+
+// fp32 I/O: the same products at reference precision.  What depends on nothing (dW, dH, dB) is one launch, what needs dH
+// (dX with dH A in the same sums, dA) and the two scalar reductions a second one: six products and a reduction in a row
+// left most of the chip idle at every size, and at 64 tokens their starts were most of the time.
+static int linear_bwd_f32(const pq_linear_desc* d, const lin_layout& L, const void* dY, const void* X, const void* W, const void* hpA,
+                          const void* hpB, const char* cx, void* dX, float* dW, float* dhpA, float* dhpB, float* dalpha_dbeta, char* ws,
+                          hipStream_t s) {
+  const int T = d->tokens, K = d->d_in, N = d->d_out, r = d->hp_rank;
+  const float* mulam = (const float*)(cx + L.mulam);
+  double* red_a = (double*)(ws + L.red_a);
+  double* red_b = (double*)(ws + L.red_b);
+  const void* H = cx + L.H;
+  void* dH = ws + L.dH;
+  pq_ref_problem p[PQ_REF_MAX];
+  int n = 0;
+  {  // dW = beta * dY^T (q / gamma)  [masked];  d beta = lambda * sum S .* (dY^T (q / gamma))
+    pq_epilogue e = epi_zero();
+    e.C = dW; e.ldc = K; e.scale = d->beta;
+    e.sign_bytes = (const uint8_t*)(cx + L.P); e.ld_sign = K / 8; e.partials = red_b;
+    if (d->ste_mode == PQ_STE_CLIP) { e.maskW = W; e.mu_dev = mulam; e.tau = d->ste_tau; }
+    p[n++] = ref_problem(PQ_REF_SS8, N, K, T, {dY, N, PQ_SRC_KS32, nullptr}, {cx + L.Xq, K, PQ_SRC_KS8, (const float*)(cx + L.gamma)}, e);
+  }
+  if (r > 0) {
+    pq_epilogue e = epi_zero();      // dB = alpha * dY^T H
+    e.C = dhpB; e.ldc = r; e.scale = d->alpha;
+    p[n++] = ref_problem(PQ_REF_SS, N, r, T, {dY, N, PQ_SRC_KS32, nullptr}, {H, r, PQ_SRC_KS32, nullptr}, e);
+    e = epi_zero();                  // dH = alpha * dY B ; d alpha = <H, dY B>
+    e.C = dH; e.ldc = r; e.scale = d->alpha; e.dot_comp = H; e.ld_comp = r; e.partials = red_a;
+    p[n++] = ref_problem(PQ_REF_CS, T, r, N, {dY, N, PQ_SRC_KC32, nullptr}, {hpB, r, PQ_SRC_KS32, nullptr}, e);
+  }
+  if (int err = pq_launch_ref(p, n, nullptr, 0, s, PQP_GEMM_DW)) return err;
+  const pq_reduce_job jobs[2] = {{red_a, (T > 0 && r > 0) ? pq_ref_red_blocks(T, r, N) : 0, 1.0f, nullptr, dalpha_dbeta},
+                                 {red_b, L.n_red_b, 1.0f, mulam + 1, dalpha_dbeta + 1}};
+  pq_epilogue e = epi_zero();        // dX = beta * lambda * dY S + dH A
+  e.C = dX; e.ldc = K;
+  p[0] = ref_problem(PQ_REF_CBITS, T, K, N, {dY, N, PQ_SRC_KC32, nullptr}, {cx + L.Pt, N / 8, PQ_SRC_BITSF, nullptr}, e);
+  p[0].scale1 = d->beta; p[0].dev_scale1 = mulam + 1;
+  n = 1;
+  if (r > 0) {
+    p[0].K2 = r; p[0].A2 = pq_operand{dH, r, PQ_SRC_KC32, nullptr}; p[0].B2 = pq_operand{hpA, K, PQ_SRC_KS32, nullptr};
+    e.C = dhpA; e.ldc = K;           // dA = dH^T X   (dH already carries alpha)
+    p[n++] = ref_problem(PQ_REF_SS, r, K, T, {dH, r, PQ_SRC_KS32, nullptr}, {X, K, PQ_SRC_KS32, nullptr}, e);
+  }
+  return pq_launch_ref(p, n, jobs, 2, s, PQP_GEMM_DX);
+}
 
 extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void* X, const void* W,
                              const void* hpA, const void* hpB, const void* Wr, const void* ctx, size_t ctx_bytes,
@@ -548,64 +608,61 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
   char* ws = (char*)workspace;
   void* sk_ws = ws + L.splitk;
   const bool bf16 = d->io_dtype == PQ_BF16;
-  const int engine = bf16 ? 0 : 1;
   const int ok = out_kind_of(d->io_dtype);
-  const int KC = bf16 ? PQ_SRC_KC16 : PQ_SRC_KC32, KS = bf16 ? PQ_SRC_KS16 : PQ_SRC_KS32;
   const float* mulam = (const float*)(cx + L.mulam);
-  const float* gamma = (const float*)(cx + L.gamma);
   const void* H = cx + L.H;
   void* dH = ws + L.dH;
   double* red_a = (double*)(ws + L.red_a);
   double* red_b = (double*)(ws + L.red_b);
-  int n_red_a = r > 0 ? pq_plan_gemm(engine, T, r, N).red_blocks : 0;   // partial sums of d alpha that the dH GEMM leaves
+  if (!bf16) return linear_bwd_f32(d, L, dY, X, W, hpA, hpB, cx, dX, dW, dhpA, dhpB, dalpha_dbeta, ws, s);
+  int n_red_a = r > 0 ? pq_plan_gemm(T, r, N).red_blocks : 0;   // partial sums of d alpha that the dH GEMM leaves
 
   if (T > 0 && r > 0) {  // dH = alpha * dY B ; d alpha = <H, dY B>
-    pq_operand A{dY, N, KC, nullptr};
-    pq_operand B{hpB, r, KS, nullptr};
+    pq_operand A{dY, N, PQ_SRC_KC16, nullptr};
+    pq_operand B{hpB, r, PQ_SRC_KS16, nullptr};
     pq_epilogue e = epi_zero();
     e.C = dH; e.ldc = r; e.out_kind = ok; e.scale = d->alpha;
     e.dot_comp = H; e.ld_comp = r; e.comp_kind = ok; e.partials = red_a;
-    if (engine == 0 && pq_skinny_applies(T, r, N, A, B, e)) {   // many tokens at rank 128: nothing to split or reduce
+    if (pq_skinny_applies(T, r, N, A, B, e)) {   // many tokens at rank 128: nothing to split or reduce
       n_red_a = pq_skinny_blocks(T);
       if (int err = pq_launch_skinny(T, N, A, B, e, s, PQP_GEMM_DH)) return err;
-    } else if (int err = pq_launch_gemm(engine, T, r, N, A, B, e, s, PQP_GEMM_DH, sk_ws)) return err;
+    } else if (int err = pq_launch_gemm(T, r, N, A, B, e, s, PQP_GEMM_DH, sk_ws)) return err;
   }
 
-  if (T > 0) {  // dX = beta*lambda * dY S  (+ dH A, fused into the same tile for bf16 I/O)
-    pq_operand A{dY, N, KC, nullptr};
-    pq_operand B{cx + L.Pt, N / 8, bf16 ? PQ_SRC_BITS16 : PQ_SRC_BITSF, nullptr};
+  if (T > 0) {  // dX = beta*lambda * dY S  (+ dH A, fused into the same tile)
+    pq_operand A{dY, N, PQ_SRC_KC16, nullptr};
+    pq_operand B{cx + L.Pt, N / 8, PQ_SRC_BITS16, nullptr};
     pq_epilogue e = epi_zero();
     e.C = dX; e.ldc = K; e.out_kind = ok;
-    const bool fuse = bf16 && r > 0 && pq_plan_gemm(0, T, K, N).splits == 1;
+    const bool fuse = r > 0 && pq_plan_gemm(T, K, N).splits == 1;
     if (fuse) {
       pq_phase2 p2;
       p2.A2 = pq_operand{dH, r, PQ_SRC_KC16, nullptr};
       p2.B2 = pq_operand{hpA, K, PQ_SRC_KS16, nullptr};
       p2.K2 = r; p2.scale1 = d->beta; p2.dev_scale1 = mulam + 1; p2.row_div1 = nullptr;
-      if (int err = pq_launch_gemm(0, T, K, N, A, B, e, s, PQP_GEMM_DX, sk_ws, nullptr, &p2)) return err;
+      if (int err = pq_launch_gemm(T, K, N, A, B, e, s, PQP_GEMM_DX, sk_ws, nullptr, &p2)) return err;
     } else {
       e.scale = d->beta; e.dev_scale = mulam + 1;
-      if (int err = pq_launch_gemm(engine, T, K, N, A, B, e, s, PQP_GEMM_DX, sk_ws)) return err;
+      if (int err = pq_launch_gemm(T, K, N, A, B, e, s, PQP_GEMM_DX, sk_ws)) return err;
       if (r > 0) {
-        pq_operand A2{dH, r, KC, nullptr};
-        pq_operand B2{hpA, K, KS, nullptr};
+        pq_operand A2{dH, r, PQ_SRC_KC16, nullptr};
+        pq_operand B2{hpA, K, PQ_SRC_KS16, nullptr};
         pq_epilogue e2 = epi_zero();
         e2.C = dX; e2.ldc = K; e2.out_kind = ok; e2.accumulate = 1;
-        if (int err = pq_launch_gemm(engine, T, K, r, A2, B2, e2, s, PQP_GEMM_DX_HP, sk_ws)) return err;
+        if (int err = pq_launch_gemm(T, K, r, A2, B2, e2, s, PQP_GEMM_DX_HP, sk_ws)) return err;
       }
     }
   }
   {  // dW = beta * (dY/gamma)^T q  [masked];  d beta = lambda * sum S .* (dY/gamma)^T q
-    pq_operand A{dY, N, KS, nullptr};
-    pq_operand B = bf16 ? pq_operand{cx + L.Xt, K, PQ_SRC_KS16, nullptr}
-                        : pq_operand{cx + L.Xq, K, PQ_SRC_KS8, gamma};
+    pq_operand A{dY, N, PQ_SRC_KS16, nullptr};
+    pq_operand B{cx + L.Xt, K, PQ_SRC_KS16, nullptr};
     pq_epilogue e = epi_zero();
     e.C = dW; e.ldc = K; e.out_kind = PQ_OUT_F32; e.scale = d->beta;
     e.sign_bytes = (const uint8_t*)(cx + L.P); e.ld_sign = K / 8; e.partials = red_b;
     if (d->ste_mode == PQ_STE_CLIP) {
       e.maskW = W; e.mask_kind = ok; e.mu_dev = mulam; e.tau = d->ste_tau;
     }
-    if (int err = pq_launch_gemm(engine, N, K, T, A, B, e, s, PQP_GEMM_DW, sk_ws)) return err;
+    if (int err = pq_launch_gemm(N, K, T, A, B, e, s, PQP_GEMM_DW, sk_ws)) return err;
   }
   if (routed) {
     // Sec. 3.3 backward: upstream of expert e's output for slot (t, j) is alpha gate_tj dY_t; the gate itself
@@ -629,7 +686,7 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
       pq_epilogue e = epi_zero();
       e.C = ws + L.dHs; e.ldc = re; e.out_kind = PQ_OUT_BF16;
       g1.b_stride = (long)N * re;
-      if (int err = pq_launch_gemm(0, S, re, N, A, B, e, s, PQP_GEMM_EXPERT, sk_ws, &g1)) return err;
+      if (int err = pq_launch_gemm(S, re, N, A, B, e, s, PQP_GEMM_EXPERT, sk_ws, &g1)) return err;
     }
     {  // per-expert weight gradients: the contraction runs over the expert's slots
       pq_operand A{ws + L.dYp, N, PQ_SRC_KS16, nullptr};
@@ -637,12 +694,12 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
       pq_epilogue e = epi_zero();
       e.C = dhpB; e.ldc = re; e.out_kind = PQ_OUT_F32;
       g2.c_stride = (long)N * re;
-      if (int err = pq_launch_gemm(0, N, re, S, A, B, e, s, PQP_GEMM_EXPERT, sk_ws, &g2)) return err;
+      if (int err = pq_launch_gemm(N, re, S, A, B, e, s, PQP_GEMM_EXPERT, sk_ws, &g2)) return err;
       pq_operand A2{ws + L.dHs, re, PQ_SRC_KS16, nullptr};
       pq_operand B2{cx + L.Xp, K, PQ_SRC_KS16, nullptr};
       e.C = dhpA; e.ldc = K;
       g2.c_stride = (long)re * K;
-      if (int err = pq_launch_gemm(0, re, K, S, A2, B2, e, s, PQP_GEMM_EXPERT, sk_ws, &g2)) return err;
+      if (int err = pq_launch_gemm(re, K, S, A2, B2, e, s, PQP_GEMM_EXPERT, sk_ws, &g2)) return err;
     }
     if (S > 0) {  // dXs = dH_e A_e (slot order), then scattered back with the router's share
       pq_operand A{ws + L.dHs, re, PQ_SRC_KC16, nullptr};
@@ -650,7 +707,7 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
       pq_epilogue e = epi_zero();
       e.C = ws + L.dXs; e.ldc = K; e.out_kind = PQ_OUT_BF16;
       g1.b_stride = (long)re * K;
-      if (int err = pq_launch_gemm(0, S, K, re, A, B, e, s, PQP_GEMM_EXPERT, sk_ws, &g1)) return err;
+      if (int err = pq_launch_gemm(S, K, re, A, B, e, s, PQP_GEMM_EXPERT, sk_ws, &g1)) return err;
     }
     float* dlogit = (float*)(ws + L.dlogit);
     if (int e = pq_launch_router_bwd(rd, inv, idx, (const float*)(cx + L.probs), d->alpha, T, k, E, dlogit, s)) return e;
@@ -658,7 +715,7 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
     if (int e = pq_launch_combine_bwd(dX, ws + L.dXs, inv, dlogit, Wr, T, k, K, E, s)) return e;
   }
   if (hp8) {   // STE backward of the INT8 branch on the de-quantised factors; its dH GEMM leaves the partials of d alpha
-    n_red_a = T > 0 ? pq_plan_gemm(0, T, d->hp_rank, N).red_blocks : 0;
+    n_red_a = T > 0 ? pq_plan_gemm(T, d->hp_rank, N).red_blocks : 0;
     if (int e = hp_int8_bwd_impl(dY, cx + L.Xt, PQ_BF16, T, K, N, d->hp_rank, d->alpha, cx + L.hp8, L.hp8_bytes, dX, 1, dhpA, dhpB,
                                  ws + L.hp8_ws, L.hp8_ws_bytes, stream, red_a)) return e;
   }
@@ -666,7 +723,7 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
   const pq_reduce_job jobs[2] = {{red_a, (T > 0 && (r > 0 || routed || hp8)) ? n_red_a : 0, 1.0f, nullptr, dalpha_dbeta},
                                  {red_b, L.n_red_b, 1.0f, mulam + 1, dalpha_dbeta + 1}};
   bool jobs_done = false;
-  if (r > 0 && bf16 && T > 0) {
+  if (r > 0 && T > 0) {
     // dB = alpha * dY^T H and dA = dH^T X (dH already carries alpha): two narrow GEMMs over the same contraction,
     // one launch when their plans agree; the two scalar reductions then ride along with their split reduction
     pq_operand A0{dY, N, PQ_SRC_KS16, nullptr}, B0{H, r, PQ_SRC_KS16, nullptr};
@@ -677,21 +734,14 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
   if (!jobs_done)
     if (int err = pq_launch_reduce_partials2(jobs[0].partials, jobs[0].n, 1.0f, nullptr, jobs[0].out, jobs[1].partials, jobs[1].n, 1.0f,
                                              jobs[1].dev_factor, jobs[1].out, s)) return err;
-  if (r > 0 && !(bf16 && T > 0)) {
-    {  // dB = alpha * dY^T H
-      pq_operand A{dY, N, KS, nullptr};
-      pq_operand B{H, r, KS, nullptr};
-      pq_epilogue e = epi_zero();
-      e.C = dhpB; e.ldc = r; e.out_kind = PQ_OUT_F32; e.scale = d->alpha;
-      if (int err = pq_launch_gemm(engine, N, r, T, A, B, e, s, PQP_GEMM_DB, sk_ws)) return err;
-    }
-    {  // dA = dH^T X   (dH already carries alpha)
-      pq_operand A{dH, r, KS, nullptr};
-      pq_operand B{X, K, KS, nullptr};
-      pq_epilogue e = epi_zero();
-      e.C = dhpA; e.ldc = K; e.out_kind = PQ_OUT_F32;
-      if (int err = pq_launch_gemm(engine, r, K, T, A, B, e, s, PQP_GEMM_DA, sk_ws)) return err;
-    }
+  if (r > 0 && T == 0) {   // no tokens: the factor gradients are the zeros an empty contraction leaves
+    pq_operand A{dY, N, PQ_SRC_KS16, nullptr}, B{H, r, PQ_SRC_KS16, nullptr};
+    pq_epilogue e = epi_zero();
+    e.C = dhpB; e.ldc = r; e.out_kind = PQ_OUT_F32; e.scale = d->alpha;
+    if (int err = pq_launch_gemm(N, r, T, A, B, e, s, PQP_GEMM_DB, sk_ws)) return err;
+    pq_operand A1{dH, r, PQ_SRC_KS16, nullptr}, B1{X, K, PQ_SRC_KS16, nullptr};
+    e.C = dhpA; e.ldc = K; e.scale = 1.0f;
+    if (int err = pq_launch_gemm(r, K, T, A1, B1, e, s, PQP_GEMM_DA, sk_ws)) return err;
   }
   return PQ_OK;
 }
@@ -802,15 +852,15 @@ hp8_layout make_hp8_layout(int T, int K, int N, int r) {
   const int shapes[4][3] = {{T, r, N}, {N, r, T}, {r, K, T}, {T, K, r}};
   for (const auto& sh : shapes) {
     if (sh[0] <= 0 || sh[1] <= 0) continue;
-    const size_t b = pq_plan_gemm(0, sh[0], sh[1], sh[2]).ws_bytes;
+    const size_t b = pq_plan_gemm(sh[0], sh[1], sh[2]).ws_bytes;
     if (b > sk) sk = b;
   }
   if (T > 0) {   // the int8 H product splits its contraction (int32 slabs)
-    const size_t b = pq_plan_gemm(0, T, r, K, true, true).ws_bytes;
+    const size_t b = pq_plan_gemm(T, r, K, true, true).ws_bytes;
     if (b > sk) sk = b;
   }
   L.splitk = w.take(sk);
-  L.splitk2 = w.take((r > 0 && K > 0) ? pq_plan_gemm(0, r, K, T).ws_bytes : 0);   // dA's slabs when dB and dA share a launch
+  L.splitk2 = w.take((r > 0 && K > 0) ? pq_plan_gemm(r, K, T).ws_bytes : 0);   // dA's slabs when dB and dA share a launch
   L.ws_total = w.off;
   return L;
 }
@@ -855,7 +905,7 @@ extern "C" int pq_hp_int8_fwd(const int8_t* Xq, const float* gamma_x, const void
     pq_epilogue e = epi_zero();
     e.C = cx + L.H; e.ldc = r; e.out_kind = PQ_OUT_BF16; e.row_div = gamma_x; e.col_div = (const float*)(cx + L.gA);
     e.split_int8 = 1;
-    if (int err = pq_launch_gemm(0, T, r, K, a, b, e, s, PQP_GEMM_HP_H, sk)) return err;
+    if (int err = pq_launch_gemm(T, r, K, a, b, e, s, PQP_GEMM_HP_H, sk)) return err;
   }
   if (int e = pq_launch_quant_act(cx + L.H, dtype, T, r, (int8_t*)(cx + L.Hq), (float*)(cx + L.gH), (uint16_t*)(cx + L.Ht), s)) return e;
   {  // Y (+)= alpha * (q_h q_b^T) / (gamma_h gamma_b)
@@ -864,7 +914,7 @@ extern "C" int pq_hp_int8_fwd(const int8_t* Xq, const float* gamma_x, const void
     pq_epilogue e = epi_zero();
     e.C = Y; e.ldc = N; e.out_kind = PQ_OUT_BF16; e.accumulate = accumulate ? 1 : 0; e.scale = alpha;
     e.row_div = (const float*)(cx + L.gH); e.col_div = (const float*)(cx + L.gB);
-    if (int err = pq_launch_gemm(0, T, N, r, a, b, e, s, PQP_GEMM_HP_Y, sk)) return err;
+    if (int err = pq_launch_gemm(T, N, r, a, b, e, s, PQP_GEMM_HP_Y, sk)) return err;
   }
   return PQ_OK;
 }
@@ -900,7 +950,7 @@ static int hp_int8_bwd_impl(const void* dY, const void* Xt, int32_t dtype, int32
     if (red_a) {   // sum H~ .* (dY B~) = <dY, H~ B~^T>: the gradient of alpha, one partial per workgroup
       e.dot_comp = cx + L.Ht; e.ld_comp = r; e.comp_kind = PQ_OUT_BF16; e.partials = red_a;
     }
-    if (int err = pq_launch_gemm(0, T, r, N, a, b, e, s, PQP_GEMM_DH, sk)) return err;
+    if (int err = pq_launch_gemm(T, r, N, a, b, e, s, PQP_GEMM_DH, sk)) return err;
   }
   {  // dB = alpha * dY^T H~ and dA = dH^T X~ (dH already carries alpha): one launch when their shapes allow it
     pq_operand a0{dY, N, PQ_SRC_KS16, nullptr}, b0{cx + L.Ht, r, PQ_SRC_KS16, nullptr};
@@ -913,7 +963,7 @@ static int hp_int8_bwd_impl(const void* dY, const void* Xt, int32_t dtype, int32
     pq_operand b{cx + L.At, K, PQ_SRC_KS16, nullptr};
     pq_epilogue e = epi_zero();
     e.C = dX; e.ldc = K; e.out_kind = PQ_OUT_BF16; e.accumulate = accumulate_dX ? 1 : 0;
-    if (int err = pq_launch_gemm(0, T, K, r, a, b, e, s, PQP_GEMM_DX_HP, sk)) return err;
+    if (int err = pq_launch_gemm(T, K, r, a, b, e, s, PQP_GEMM_DX_HP, sk)) return err;
   }
   return PQ_OK;
 }

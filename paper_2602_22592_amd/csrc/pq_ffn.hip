@@ -71,7 +71,7 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   cursor w;
   L.stat = w.take(2 * sizeof(double) * 1024);
   L.n_red_a = pq_rowdot_blocks((int)S);
-  L.n_red_b = pq_plan_gemm(0, (int)D, (int)F, (int)T).red_blocks;      // dW_down GEMM
+  L.n_red_b = pq_plan_gemm((int)D, (int)F, (int)T).red_blocks;      // dW_down GEMM
   L.red_a = w.take(sizeof(double) * (size_t)L.n_red_a);
   L.red_b = w.take(sizeof(double) * (size_t)L.n_red_b);
   size_t sk = 0;
@@ -82,7 +82,7 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
                              {Si, 2 * ri, Di}, {Si, ri, Di}, {Si, Di, 2 * ri}, {Si, Di, ri}, {Di, ri, Si}, {2 * ri, Di, Si}, {ri, Di, Si}};
   for (const auto& sh : shapes) {
     if (sh[0] <= 0 || sh[1] <= 0) continue;
-    const size_t b = pq_plan_gemm(0, sh[0], sh[1], sh[2]).ws_bytes;
+    const size_t b = pq_plan_gemm(sh[0], sh[1], sh[2]).ws_bytes;
     if (b > sk) sk = b;
   }
   // the expert up/gate projections and their input gradients split the contraction up to 8 ways: [8][S][r] fp32
@@ -187,7 +187,7 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
   if (combo) {
     const size_t n = (size_t)Fv * D;
     const int nb = pq_stats_blocks(n);
-    if (int e = pq_launch_wstats_quant(W_up, n, part, nb, X, T, D, Xq, gx, (uint16_t*)(cx + L.Xt), s)) return e;
+    if (int e = pq_launch_wstats_quant(W_up, PQ_BF16, n, part, nb, X, T, D, Xq, gx, (uint16_t*)(cx + L.Xt), s)) return e;
     if (int e = pq_launch_pack(W_up, PQ_BF16, Fv, D, part, nb, (uint32_t*)(cx + L.P_up), (uint32_t*)(cx + L.Pt_up),
                                (float*)(cx + L.ml_up), s)) return e;
   } else if (int e = pack_weight(W_up, Fv, D, cx, L.P_up, L.Pt_up, L.ml_up, part, s)) return e;
@@ -213,10 +213,10 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
     pq_operand Bu{cx + L.P_up, D / 8, PQ_SRC_BITS8, nullptr};
     pq_epilogue e = epi0();
     e.C = cx + L.U; e.ldc = F; e.out_kind = PQ_OUT_BF16; e.dev_scale = (const float*)(cx + L.ml_up) + 1; e.row_div = gx;
-    if (int err = pq_launch_gemm(0, T, F, D, A, Bu, e, s, PQP_GEMM_ONEBIT, sk)) return err;
+    if (int err = pq_launch_gemm(T, F, D, A, Bu, e, s, PQP_GEMM_ONEBIT, sk)) return err;
     pq_operand Bg{cx + L.P_gate, D / 8, PQ_SRC_BITS8, nullptr};
     e.C = cx + L.G; e.dev_scale = (const float*)(cx + L.ml_gate) + 1;
-    if (int err = pq_launch_gemm(0, T, F, D, A, Bg, e, s, PQP_GEMM_ONEBIT, sk)) return err;
+    if (int err = pq_launch_gemm(T, F, D, A, Bg, e, s, PQP_GEMM_ONEBIT, sk)) return err;
   }
   int8_t* Hq = (int8_t*)(cx + L.Hq);
   float* gh = (float*)(cx + L.gh);
@@ -226,7 +226,7 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
     pq_operand B{cx + L.P_down, F / 8, PQ_SRC_BITS8, nullptr};
     pq_epilogue e = epi0();
     e.C = Y; e.ldc = D; e.out_kind = PQ_OUT_BF16; e.scale = d->beta; e.dev_scale = (const float*)(cx + L.ml_down) + 1; e.row_div = gh;
-    if (int err = pq_launch_gemm(0, T, D, F, A, B, e, s, PQP_GEMM_ONEBIT, sk)) return err;
+    if (int err = pq_launch_gemm(T, D, F, A, B, e, s, PQP_GEMM_ONEBIT, sk)) return err;
   }
   // routed experts: router -> stable permutation by expert -> gather -> grouped GEMMs -> combine
   int* idx = (int*)(cx + L.idx);
@@ -262,7 +262,7 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
       pq_epilogue e = epi0();
       e.C = cx + L.ue; e.ldc = 2 * r; e.out_kind = PQ_OUT_BF16; e.row_div = gxp; e.col_div = (const float*)(cx + L.gUG);
       g1.b_stride = (long)2 * r * D; g1.coldiv_stride = 2 * r;
-      if (int err = pq_launch_gemm(0, S, 2 * r, D, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
+      if (int err = pq_launch_gemm(S, 2 * r, D, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
     }
     if (int e = pq_launch_expert_act(cx + L.ue, cx + L.ue + (size_t)r * 2, 2 * r, S, r, cx + L.a, s)) return e;
     if (int e = pq_launch_quant_act(cx + L.a, PQ_BF16, S, r, (int8_t*)(cx + L.aQ), (float*)(cx + L.gA), (uint16_t*)(cx + L.aT), s)) return e;
@@ -272,7 +272,7 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
       pq_epilogue e = epi0();
       e.C = cx + L.Ys; e.ldc = D; e.out_kind = PQ_OUT_BF16; e.row_div = (const float*)(cx + L.gA); e.col_div = (const float*)(cx + L.gDown);
       g1.b_stride = (long)D * r; g1.coldiv_stride = D;
-      if (int err = pq_launch_gemm(0, S, D, r, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
+      if (int err = pq_launch_gemm(S, D, r, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
     }
     return pq_launch_combine_fwd(Y, cx + L.Ys, inv, gate, d->alpha, T, k, D, s);
   }
@@ -287,7 +287,7 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
     pq_epilogue e = epi0();
     e.C = cx + L.ue; e.ldc = 2 * r; e.out_kind = PQ_OUT_BF16;
     g1.b_stride = (long)2 * r * D;
-    if (int err = pq_launch_gemm(0, S, 2 * r, D, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
+    if (int err = pq_launch_gemm(S, 2 * r, D, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
   }
   if (int e = pq_launch_expert_act(cx + L.ue, cx + L.ue + (size_t)r * 2, 2 * r, S, r, cx + L.a, s)) return e;
   {
@@ -296,7 +296,7 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
     pq_epilogue e = epi0();
     e.C = cx + L.Ys; e.ldc = D; e.out_kind = PQ_OUT_BF16;
     g1.b_stride = (long)D * r;
-    if (int err = pq_launch_gemm(0, S, D, r, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
+    if (int err = pq_launch_gemm(S, D, r, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
   }
   return pq_launch_combine_fwd(Y, cx + L.Ys, inv, gate, d->alpha, T, k, D, s);
 }
@@ -337,7 +337,7 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
     e.C = dW_down; e.ldc = Fv; e.out_kind = PQ_OUT_F32; e.scale = d->beta;
     if (Fv != F) e.n_limit = Fv;                     // the padded columns (zero: Ht is zero there) are not part of dW_down
     e.sign_bytes = (const uint8_t*)(cx + L.P_down); e.ld_sign = F / 8; e.partials = red_b;
-    if (int err = pq_launch_gemm(0, D, F, T, A, B, e, s, PQP_GEMM_DW, sk)) return err;
+    if (int err = pq_launch_gemm(D, F, T, A, B, e, s, PQP_GEMM_DW, sk)) return err;
   }
   if (T > 0) {
     {  // dHd = beta * lambda_d * dY S_d
@@ -345,7 +345,7 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
       pq_operand B{cx + L.Pt_down, D / 8, PQ_SRC_BITS16, nullptr};
       pq_epilogue e = epi0();
       e.C = ws + L.dHd; e.ldc = F; e.out_kind = PQ_OUT_BF16; e.scale = d->beta; e.dev_scale = ml_down + 1;
-      if (int err = pq_launch_gemm(0, T, F, D, A, B, e, s, PQP_GEMM_DX, sk)) return err;
+      if (int err = pq_launch_gemm(T, F, D, A, B, e, s, PQP_GEMM_DX, sk)) return err;
     }
     if (int err = pq_launch_swiglu_bwd(ws + L.dHd, cx + L.U, cx + L.G, T, F, Fv, ws + L.dU, ws + L.dG, s)) return err;
     {  // dX = lambda_u dU S_u + lambda_g dG S_g
@@ -353,11 +353,11 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
       pq_operand B{cx + L.Pt_up, F / 8, PQ_SRC_BITS16, nullptr};
       pq_epilogue e = epi0();
       e.C = dX; e.ldc = D; e.out_kind = PQ_OUT_BF16; e.dev_scale = ml_up + 1;
-      if (int err = pq_launch_gemm(0, T, D, F, A, B, e, s, PQP_GEMM_DX, sk)) return err;
+      if (int err = pq_launch_gemm(T, D, F, A, B, e, s, PQP_GEMM_DX, sk)) return err;
       pq_operand A2{ws + L.dG, F, PQ_SRC_KC16, nullptr};
       pq_operand B2{cx + L.Pt_gate, F / 8, PQ_SRC_BITS16, nullptr};
       e.accumulate = 1; e.dev_scale = ml_gate + 1;
-      if (int err = pq_launch_gemm(0, T, D, F, A2, B2, e, s, PQP_GEMM_DX, sk)) return err;
+      if (int err = pq_launch_gemm(T, D, F, A2, B2, e, s, PQP_GEMM_DX, sk)) return err;
     }
   }
   {  // dW_up = dU^T Xt, dW_gate = dG^T Xt
@@ -367,10 +367,10 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
     if (Fv != F) e.m_limit = Fv;                     // rows Fv.. of the padded product do not exist in dW_up / dW_gate
     pq_operand A{ws + L.dU, F, PQ_SRC_KS16, nullptr};
     e.C = dW_up;
-    if (int err = pq_launch_gemm(0, F, D, T, A, B, e, s, PQP_GEMM_DW, sk)) return err;
+    if (int err = pq_launch_gemm(F, D, T, A, B, e, s, PQP_GEMM_DW, sk)) return err;
     pq_operand A2{ws + L.dG, F, PQ_SRC_KS16, nullptr};
     e.C = dW_gate;
-    if (int err = pq_launch_gemm(0, F, D, T, A2, B, e, s, PQP_GEMM_DW, sk)) return err;
+    if (int err = pq_launch_gemm(F, D, T, A2, B, e, s, PQP_GEMM_DW, sk)) return err;
   }
   // experts
   const int* idx = (const int*)(cx + L.idx);
@@ -400,7 +400,7 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
     pq_epilogue e = epi0();
     e.C = ws + L.da; e.ldc = r; e.out_kind = PQ_OUT_BF16;
     g1.b_stride = (long)D * r;
-    if (int err = pq_launch_gemm(0, S, r, D, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
+    if (int err = pq_launch_gemm(S, r, D, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
   }
   // u | g and du | dg lie side by side in [S][2 r] matrices (Up and Gate are one weight matrix per expert, in both forms)
   if (int e = pq_launch_expert_act_bwd(ws + L.da, cx + L.ue, cx + L.ue + (size_t)r * 2, a_fwd, perm, gate, d->alpha, S, r, 2 * r,
@@ -411,13 +411,13 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
     pq_epilogue e = epi0();
     e.C = dDown; e.ldc = r; e.out_kind = PQ_OUT_F32;
     g2.c_stride = (long)D * r;
-    if (int err = pq_launch_gemm(0, D, r, S, A, B, e, s, PQP_GEMM_EXPERT, sk, pg2)) return err;
+    if (int err = pq_launch_gemm(D, r, S, A, B, e, s, PQP_GEMM_EXPERT, sk, pg2)) return err;
     pq_operand Bx{xp, D, PQ_SRC_KS16, nullptr};
     {   // d[Up_e; Gate_e] = [du | dg]^T Xp, then split into the caller's two gradients
       pq_operand Aug{ws + L.du, 2 * r, PQ_SRC_KS16, nullptr};
       e.C = ws + L.dUG; e.ldc = D;
       g2.c_stride = (long)2 * r * D;
-      if (int err = pq_launch_gemm(0, 2 * r, D, S, Aug, Bx, e, s, PQP_GEMM_EXPERT, sk, pg2)) return err;
+      if (int err = pq_launch_gemm(2 * r, D, S, Aug, Bx, e, s, PQP_GEMM_EXPERT, sk, pg2)) return err;
       if (int err = pq_launch_split_expert_rows((const float*)(ws + L.dUG), E, r, D, dUp, dGate, s)) return err;
     }
   }
@@ -427,7 +427,7 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
     pq_epilogue e = epi0();
     e.C = ws + L.dXs; e.ldc = D; e.out_kind = PQ_OUT_BF16;
     g1.b_stride = (long)2 * r * D;
-    if (int err = pq_launch_gemm(0, S, D, 2 * r, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
+    if (int err = pq_launch_gemm(S, D, 2 * r, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
   }
   float* dlogit = (float*)(ws + L.dlogit);
   if (one) {   // softmax over one logit is constant: no gradient reaches the router

@@ -1,5 +1,4 @@
-// Tiled MFMA GEMM for gfx950 with pluggable operand sources and epilogues, plus a
-// reference-precision engine (fp64 products and sums on the fp64 matrix instruction) used for fp32 I/O.
+// Tiled MFMA GEMM for gfx950 with pluggable operand sources and epilogues.
 //
 //   C[m][n] (+)= epilogue( sum_k A(m,k) * B(n,k) )
 //
@@ -237,7 +236,7 @@ struct tile_stage {
 };
 
 // ---------------------------------------------------------------------------------------------
-// Epilogue shared by both engines
+// Epilogue
 // ---------------------------------------------------------------------------------------------
 struct epi_state {
   float sc0;
@@ -253,33 +252,6 @@ __device__ __forceinline__ void epi_begin(const pq_epilogue& e, epi_state& st) {
 
 __device__ __forceinline__ float load_io(const void* p, int kind, size_t i) {
   return kind == PQ_OUT_BF16 ? bf16_to_f32(((const uint16_t*)p)[i]) : ((const float*)p)[i];
-}
-
-// acc_f: the accumulator as a real number; acc_i: as an integer (int8 engine / I32 output only)
-template <typename AccT>
-__device__ __forceinline__ void epi_elem(const pq_epilogue& e, epi_state& st, int m, int n, AccT acc, int acc_i) {
-  const size_t ci = (size_t)m * e.ldc + n;
-  if ((e.m_limit > 0 && m >= e.m_limit) || (e.n_limit > 0 && n >= e.n_limit)) return;
-  if (e.out_kind == PQ_OUT_I32) {
-    ((int*)e.C)[ci] = acc_i;
-    return;
-  }
-  if (e.dot_comp) st.psum += (double)load_io(e.dot_comp, e.comp_kind, (size_t)m * e.ld_comp + n) * (double)acc;
-  if (e.sign_bytes) {
-    const uint32_t bit = (e.sign_bytes[(size_t)m * e.ld_sign + (n >> 3)] >> (n & 7)) & 1u;
-    st.psum += bit ? (double)acc : -(double)acc;
-  }
-  float sc = st.sc0;
-  if (e.row_div) sc = sc / e.row_div[m];
-  AccT val = (AccT)sc * acc;
-  if (e.col_div) val = val / (AccT)e.col_div[n];
-  if (e.maskW) {
-    const double w = (double)load_io(e.maskW, e.mask_kind, ci);
-    if (fabs(w - (double)st.mu) > (double)e.tau) val = (AccT)0;
-  }
-  if (e.accumulate) val += (AccT)load_io(e.C, e.out_kind, ci);
-  if (e.out_kind == PQ_OUT_BF16) ((uint16_t*)e.C)[ci] = f32_to_bf16((float)val);
-  else ((float*)e.C)[ci] = (float)val;
 }
 
 template <int NT>
@@ -1347,143 +1319,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_pair_kernel(int splits, int
 }
 
 // ---------------------------------------------------------------------------------------------
-// Reference-precision engine (fp32 I/O): any source kind, products and sums in fp64 on the matrix pipe
-// (v_mfma_f64_16x16x4_f64).  A workgroup owns a 128x128 tile, a wavefront 64x64 of it; sixteen contraction
-// indices of both operands are converted to fp64 on the way into LDS ([k][row], row stride 129 doubles).
-// ---------------------------------------------------------------------------------------------
-template <int KIND>
-__device__ __forceinline__ double ref_elem(const pq_operand& op, int row, int k) {
-  if constexpr (KIND == PQ_SRC_KC32) return ((const float*)op.p)[(size_t)row * op.ld + k];
-  else if constexpr (KIND == PQ_SRC_KS32) return ((const float*)op.p)[(size_t)k * op.ld + row];
-  else if constexpr (KIND == PQ_SRC_KC16) return bf16_to_f32(((const uint16_t*)op.p)[(size_t)row * op.ld + k]);
-  else if constexpr (KIND == PQ_SRC_KS16) return bf16_to_f32(((const uint16_t*)op.p)[(size_t)k * op.ld + row]);
-  else if constexpr (KIND == PQ_SRC_KC8) return ((const int8_t*)op.p)[(size_t)row * op.ld + k];
-  else if constexpr (KIND == PQ_SRC_KS8) return ((const int8_t*)op.p)[(size_t)k * op.ld + row];
-  else {                                                // packed bits: one bit per weight, set = +1
-    const uint32_t byte = ((const uint8_t*)op.p)[(size_t)row * op.ld + (k >> 3)];
-    return ((byte >> (k & 7)) & 1u) ? 1.0 : -1.0;
-  }
-}
-
-constexpr int REF_KB = 16;
-// 128x128 tiles, or 64x64 when those would leave half of the compute units without one
-static int ref_tile(int M, int N) { return (long)((M + 127) / 128) * ((N + 127) / 128) < 128 ? 64 : 128; }
-
-// Sixteen contraction indices of TILE rows, fetched into registers (rows and indices past the end become zeros) and
-// later written to LDS as [k][row].  Sources whose rows are contiguous in memory are read with the row index fastest
-// over the lanes, the others with the contraction index.
-template <int TILE>
-struct ref_stage {
-  static constexpr int PER = TILE / 16, LD = TILE + 1;
-  double v[PER];
-  __device__ __forceinline__ static void where(bool rows_fastest, int j, int& kk, int& rl) {
-    const int tid = threadIdx.x;
-    kk = rows_fastest ? tid / TILE + (256 / TILE) * j : (tid & 15);
-    rl = rows_fastest ? tid % TILE : (tid >> 4) + 16 * j;
-  }
-  // All loads of a step are issued back to back (addresses clamped into the matrix, the kind decided once), so a
-  // step waits for one memory latency and not for one per element.
-  template <int KIND>
-  __device__ __forceinline__ void fetch_kind(const pq_operand& op, int row0, int rows, int k0, int K) {
-    constexpr bool rows_fastest = KIND == PQ_SRC_KS32 || KIND == PQ_SRC_KS16 || KIND == PQ_SRC_KS8;
-    double d[PER];
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      int kk, rl;
-      where(rows_fastest, j, kk, rl);
-      v[j] = ref_elem<KIND>(op, min(row0 + rl, rows - 1), min(k0 + kk, K - 1));
-      d[j] = op.kdiv ? (double)op.kdiv[min(k0 + kk, K - 1)] : 1.0;
-    }
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      int kk, rl;
-      where(rows_fastest, j, kk, rl);
-      if (op.kdiv) v[j] /= d[j];
-      if (row0 + rl >= rows || k0 + kk >= K) v[j] = 0.0;
-    }
-  }
-  __device__ __forceinline__ void fetch(const pq_operand& op, int row0, int rows, int k0, int K) {
-    switch (op.kind) {                                  // uniform
-      case PQ_SRC_KC32: fetch_kind<PQ_SRC_KC32>(op, row0, rows, k0, K); break;
-      case PQ_SRC_KS32: fetch_kind<PQ_SRC_KS32>(op, row0, rows, k0, K); break;
-      case PQ_SRC_KC16: fetch_kind<PQ_SRC_KC16>(op, row0, rows, k0, K); break;
-      case PQ_SRC_KS16: fetch_kind<PQ_SRC_KS16>(op, row0, rows, k0, K); break;
-      case PQ_SRC_KC8: fetch_kind<PQ_SRC_KC8>(op, row0, rows, k0, K); break;
-      case PQ_SRC_KS8: fetch_kind<PQ_SRC_KS8>(op, row0, rows, k0, K); break;
-      default: fetch_kind<PQ_SRC_BITSF>(op, row0, rows, k0, K);   // packed bits, whatever the engine they were declared for
-    }
-  }
-  __device__ __forceinline__ void store(const pq_operand& op, double* dst) const {
-    const bool rows_fastest = op.kind == PQ_SRC_KS32 || op.kind == PQ_SRC_KS16 || op.kind == PQ_SRC_KS8;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      int kk, rl;
-      where(rows_fastest, j, kk, rl);
-      dst[kk * LD + rl] = v[j];
-    }
-  }
-};
-
-template <int TILE>
-__global__ __launch_bounds__(256) void ref_gemm_kernel(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi) {
-  typedef double f64x4_t __attribute__((ext_vector_type(4)));
-  constexpr int LD = TILE + 1, WT = TILE / 2, NB = WT / 16;   // a wavefront owns WT x WT: NB x NB blocks of 16x16
-  __shared__ double As[REF_KB * LD], Bs[REF_KB * LD];
-  __shared__ double red[4];
-  const int m0 = blockIdx.y * TILE, n0 = blockIdx.x * TILE;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = (wave >> 1) * WT, wn = (wave & 1) * WT;
-  const int li = lane & 15, lk = lane >> 4;
-  f64x4_t acc[NB][NB];
-#pragma unroll
-  for (int i = 0; i < NB; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-  ref_stage<TILE> ra, rb;
-  if (K > 0) {
-    ra.fetch(A, m0, M, 0, K);
-    rb.fetch(B, n0, N, 0, K);
-  }
-  for (int k0 = 0; k0 < K; k0 += REF_KB) {
-    ra.store(A, As);
-    rb.store(B, Bs);
-    __syncthreads();
-    if (k0 + REF_KB < K) {                               // the next step's elements travel while this one multiplies
-      ra.fetch(A, m0, M, k0 + REF_KB, K);
-      rb.fetch(B, n0, N, k0 + REF_KB, K);
-    }
-#pragma unroll
-    for (int kk = 0; kk < REF_KB; kk += 4) {
-      // operand layout of the instruction: lane (li, lk) holds element (row li, contraction index lk) of either side
-      double a[NB], b[NB];
-#pragma unroll
-      for (int i = 0; i < NB; ++i) a[i] = As[(kk + lk) * LD + wm + 16 * i + li];
-#pragma unroll
-      for (int j = 0; j < NB; ++j) b[j] = Bs[(kk + lk) * LD + wn + 16 * j + li];
-#pragma unroll
-      for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-  epi_state st;
-  epi_begin(epi, st);
-  // result layout: register v of lane (li, lk) is element (row lk + 4 v, column li) of the 16x16 block
-#pragma unroll
-  for (int i = 0; i < NB; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int m = m0 + wm + 16 * i + lk + 4 * v, n = n0 + wn + 16 * j + li;
-        const double c = acc[i][j][v];
-        if (m < M && n < N) epi_elem<double>(epi, st, m, n, c, (int)c);
-      }
-  epi_end<256>(epi, st, red, blockIdx.y * gridDim.x + blockIdx.x);
-}
-
-// ---------------------------------------------------------------------------------------------
 // Weight-gradient GEMMs (both operands bf16 with the contraction index as rows: dW = dY^T X over the tokens):
 // a 256x256 tile on FOUR wavefronts.
 // ---------------------------------------------------------------------------------------------
@@ -2166,16 +2001,10 @@ int pq_launch_skinny(int M, int K, const pq_operand& A, const pq_operand& B, con
 // Tile shape and contraction split for one GEMM.  A 256x256 tile (8 wavefronts, 128x64 each) when
 // the output is large enough, else 128x128 (4 wavefronts); when the tiles alone cannot occupy the
 // 256 compute units the contraction is split and reduced in a second, fixed-order pass.
-pq_gemm_plan pq_plan_gemm(int engine, int M, int N, int K, bool int8, bool split_int8) {
+pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8, bool split_int8) {
   pq_gemm_plan pl;
   memset(&pl, 0, sizeof(pl));
   pl.splits = 1;
-  if (engine == 1) {
-    pl.bm = pl.bn = ref_tile(M, N);
-    pl.kchunk = K;
-    pl.red_blocks = ((M + pl.bm - 1) / pl.bm) * ((N + pl.bn - 1) / pl.bn);
-    return pl;
-  }
   const bool big = (M >= 256 && N >= 256);
   pl.bm = pl.bn = big ? 256 : 128;
   const long tiles = (long)((M + pl.bm - 1) / pl.bm) * ((N + pl.bn - 1) / pl.bn);
@@ -2204,7 +2033,7 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
   e0.C = C0; e0.ldc = ldc0; e0.out_kind = PQ_OUT_F32; e0.scale = scale0;
   pq_epilogue e1 = e0;
   e1.C = C1; e1.ldc = ldc1; e1.scale = scale1;
-  const pq_gemm_plan p0 = pq_plan_gemm(0, M0, N0, K), p1 = pq_plan_gemm(0, M1, N1, K);
+  const pq_gemm_plan p0 = pq_plan_gemm(M0, N0, K), p1 = pq_plan_gemm(M1, N1, K);
   {
     // rank 128 over many tokens: the streaming pair kernel (problem 1 runs transposed).  Four token ranges when that
     // already gives a workgroup per CU (fewer slabs to write and add), up to sixteen for small matrices, never
@@ -2243,8 +2072,8 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
                     p0.kchunk == p1.kchunk && nbm0 * nbn0 == nbm1 * nbn1 && A0.kind == PQ_SRC_KS16 && B0.kind == PQ_SRC_KS16 &&
                     A1.kind == PQ_SRC_KS16 && B1.kind == PQ_SRC_KS16 && (p0.splits == 1 || (splitk_ws0 && splitk_ws1));
   if (!same) {
-    if (int rc = pq_launch_gemm(0, M0, N0, K, A0, B0, e0, s, prof_label0, splitk_ws0)) return rc;
-    return pq_launch_gemm(0, M1, N1, K, A1, B1, e1, s, prof_label1, splitk_ws1);
+    if (int rc = pq_launch_gemm(M0, N0, K, A0, B0, e0, s, prof_label0, splitk_ws0)) return rc;
+    return pq_launch_gemm(M1, N1, K, A1, B1, e1, s, prof_label1, splitk_ws1);
   }
   pq_gemm_group grp;
   memset(&grp, 0, sizeof(grp));
@@ -2288,7 +2117,7 @@ size_t pq_mode2_ws_bytes(int M, int N, int n_groups, int total_k) {
   return sp > 1 ? (size_t)sp * n_groups * M * N * sizeof(float) : 0;
 }
 
-int pq_launch_gemm(int engine, int M, int N, int K, const pq_operand& A, const pq_operand& B,
+int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B,
                    const pq_epilogue& epi, hipStream_t s, int prof_label, void* splitk_ws,
                    const pq_gemm_group* group, const pq_phase2* phase2) {
   if (M <= 0 || N <= 0) return PQ_OK;
@@ -2298,26 +2127,16 @@ int pq_launch_gemm(int engine, int M, int N, int K, const pq_operand& A, const p
   pq_phase2 ph2;
   memset(&ph2, 0, sizeof(ph2));
   if (phase2) ph2 = *phase2;
-  if (ph2.K2 > 0 && (engine == 1 || grp.mode)) return pq_set_error(PQ_ERR_BAD_ARG, "a fused second contraction needs the plain MFMA engine");
+  if (ph2.K2 > 0 && grp.mode) return pq_set_error(PQ_ERR_BAD_ARG, "a fused second contraction needs the plain MFMA engine");
   if ((epi.n_limit > 0 || epi.m_limit > 0) && (epi.accumulate || epi.maskW || epi.dot_comp || epi.n_limit % 4 != 0))
     return pq_set_error(PQ_ERR_BAD_ARG, "store limits go with plain stores and a column limit that is a multiple of 4");
-  if (grp.mode && engine == 1) return pq_set_error(PQ_ERR_DTYPE, "grouped GEMMs run on the MFMA engine only (bf16 I/O)");
   // plain rank-128 products over many rows: the streaming kernel (callers that want per-block partial sums or the
   // slabs of a split contraction choose it themselves, since it changes how many of those there are)
-  if (engine == 0 && !grp.mode && ph2.K2 == 0 && !epi.partials && !epi.defer_reduce && pq_skinny_applies(M, N, K, A, B, epi))
+  if (!grp.mode && ph2.K2 == 0 && !epi.partials && !epi.defer_reduce && pq_skinny_applies(M, N, K, A, B, epi))
     return pq_launch_skinny(M, K, A, B, epi, s, prof_label);
-  if (engine == 1) {
-    pq_prof_scope prof(prof_label, s);
-    const int tile = ref_tile(M, N);
-    dim3 grid((N + tile - 1) / tile, (M + tile - 1) / tile), block(256);
-    if (tile == 64) ref_gemm_kernel<64><<<grid, block, 0, s>>>(M, N, K, A, B, epi);
-    else ref_gemm_kernel<128><<<grid, block, 0, s>>>(M, N, K, A, B, epi);
-    PQ_CHECK_LAUNCH("ref_gemm_kernel");
-    return PQ_OK;
-  }
   const int ak = A.kind, bk = B.kind;
   const bool int8 = (ak == PQ_SRC_KC8);
-  pq_gemm_plan pl = pq_plan_gemm(0, M, N, K, int8, epi.split_int8 != 0);
+  pq_gemm_plan pl = pq_plan_gemm(M, N, K, int8, epi.split_int8 != 0);
   if (grp.mode) {
     pl.splits = 1;
     pl.kchunk = K > 0 ? K : 1;

@@ -33,9 +33,9 @@ size_t pq_static_scratch_bytes();
 int pq_static_scratch(void** out);
 // Weight statistics, stage 1: per-block fp64 partial sums {sum W, sum |W|}.
 int pq_stats_blocks(size_t n_elems);
-// slabs != nullptr: `splits` fp32 slabs [M][N] of a deferred split contraction are summed in slab order into the bf16
+// dtype: of W and X.  slabs != nullptr: `splits` fp32 slabs [M][N] of a deferred split contraction are summed in slab order into the bf16
 // matrix C [M][ldc] by further workgroups of the same launch (N % 8 == 0)
-int pq_launch_wstats_quant(const void* W, size_t n_elems, double* partials, int nblocks, const void* X, int T, int K,
+int pq_launch_wstats_quant(const void* W, int dtype, size_t n_elems, double* partials, int nblocks, const void* X, int T, int K,
                            int8_t* Xq, float* gamma, uint16_t* Xt, hipStream_t s, const float* slabs = nullptr, int splits = 0,
                            int M = 0, int N = 0, void* C = nullptr, int ldc = 0);
 int pq_launch_wstats_partial(const void* W, int dtype, size_t n_elems, double* partials, int nblocks,
@@ -59,7 +59,7 @@ enum pq_src_kind {
   PQ_SRC_KC8 = 2,    // int8, contraction contiguous
   PQ_SRC_BITS8 = 3,  // +/-1 as int8 from packed bits, ld = bytes per row
   PQ_SRC_BITS16 = 4, // +/-1 as bf16 from packed bits, ld = bytes per row
-  // reference-precision engine only:
+  // fp32 I/O only (pq_ref.hip):
   PQ_SRC_KC32 = 5,   // fp32, contraction contiguous
   PQ_SRC_KS32 = 6,   // fp32, contraction strided
   PQ_SRC_KS8 = 7,    // int8, contraction strided
@@ -70,7 +70,7 @@ struct pq_operand {
   const void* p;
   long ld;             // leading dimension in elements (bytes per row for the BITS kinds)
   int kind;
-  const float* kdiv;   // optional: divide element by kdiv[k] (per contraction index); ref engine only
+  const float* kdiv;   // optional: divide element by kdiv[k] (per contraction index); fp32 I/O only
 };
 
 enum pq_out_kind { PQ_OUT_F32 = 0, PQ_OUT_BF16 = 1, PQ_OUT_I32 = 2 };
@@ -118,8 +118,7 @@ struct pq_phase2 {
   const float* row_div1;
 };
 
-// C[M][N] (+)= epilogue( sum_k A(m,k) * B(n,k) ).  `engine` 0 = MFMA (bf16 or int8 operands),
-// 1 = reference precision (fp64 products and sums on the fp64 MFMA, any operand kind).
+// C[M][N] (+)= epilogue( sum_k A(m,k) * B(n,k) ) on the MFMA engine (bf16 or int8 operands).
 // Grouped execution over expert segments (Sec. 3.3): `offsets` [n_groups+1] is a device array of
 // slot positions.  mode 1: rows [offsets[e], offsets[e+1]) of A and C belong to group e and use
 // B + e*b_stride (elements of B's type) -- the per-expert GEMMs of the forward pass;  mode 2: the
@@ -153,7 +152,7 @@ struct pq_gemm_plan {
   int red_blocks;    // number of per-block partial sums written when a reduction is requested
   size_t ws_bytes;   // scratch for the split slabs
 };
-pq_gemm_plan pq_plan_gemm(int engine, int M, int N, int K, bool int8 = false, bool split_int8 = false);
+pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8 = false, bool split_int8 = false);
 // Scratch a grouped launch over contraction ranges (mode 2; M x N per group, total_k indices over all groups) may use
 size_t pq_mode2_ws_bytes(int M, int N, int n_groups, int total_k);
 // Two bf16 GEMMs with contraction-strided operands on both sides (the rank-r weight gradients dA and dB) in one
@@ -172,10 +171,33 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
                              int M1, int N1, const pq_operand& A1, const pq_operand& B1, float* C1, int ldc1, float scale1,
                              hipStream_t s, int prof_label0, int prof_label1, void* splitk_ws0, void* splitk_ws1,
                              const pq_reduce_job* jobs = nullptr, bool* jobs_done = nullptr);   // jobs: two scalar reductions to ride along
-int pq_launch_gemm(int engine, int M, int N, int K, const pq_operand& A, const pq_operand& B,
+int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B,
                    const pq_epilogue& epi, hipStream_t s, int prof_label = PQP_GEMM_OTHER,
                    void* splitk_ws = nullptr, const pq_gemm_group* group = nullptr,
                    const pq_phase2* phase2 = nullptr);
+
+// ---- pq_ref.hip ---------------------------------------------------------------------------
+// Reference-precision products (fp32 I/O): fp64 products and sums, C fp32.  `form` names the operand kinds.
+enum pq_ref_form {
+  PQ_REF_CC = 0,      // A KC32, B KC32
+  PQ_REF_CS = 1,      // A KC32, B KS32
+  PQ_REF_CBITS = 2,   // A KC32, B packed signs; then, K2 > 0, a second contraction A2 (KC32) x B2 (KS32) into the same sums:
+                      // (scale1 [* *dev_scale1]) * sum_k A B + sum_k2 A2 B2
+  PQ_REF_SS8 = 3,     // A KS32, B KS8 divided by its kdiv
+  PQ_REF_SS = 4       // A KS32, B KS32
+};
+struct pq_ref_problem {
+  int form, M, N, K, K2, cfg;   // cfg is set by the launcher
+  pq_operand A, B, A2, B2;
+  float scale1;
+  const float* dev_scale1;
+  pq_epilogue epi;              // scale, dev_scale, accumulate, dot_comp, sign_bytes, partials and the clip mask; C is fp32
+};
+constexpr int PQ_REF_MAX = 3;
+int pq_ref_red_blocks(int M, int N, int K);   // partial sums one product leaves when its epilogue asks for them
+// Up to PQ_REF_MAX independent products in one launch per tile class (at most two launches); up to two scalar reductions of
+// partials that EARLIER launches left ride along.
+int pq_launch_ref(pq_ref_problem* p, int n, const pq_reduce_job* jobs, int njobs, hipStream_t s, int prof_label);
 
 // ---- pq_decode.hip ------------------------------------------------------------------------
 size_t pq_decode_ws_layout(const pq_decode_desc& d, size_t* off);

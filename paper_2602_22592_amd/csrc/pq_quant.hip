@@ -489,35 +489,43 @@ __global__ __launch_bounds__(256) void wstats_partial_kernel(const T* __restrict
 // The first stage of the weight statistics and the activation quantiser of one forward call are independent and
 // each too short to fill its own launch well: one launch, the first nw workgroups take the weights.
 struct slab_sum_job { const float* part; int splits, M, N; uint16_t* C; int ldc; };
-template <int NV>
-__global__ __launch_bounds__(256) void wstats_quant_kernel(const uint16_t* __restrict__ W, size_t nvec, double* __restrict__ partials,
-                                                           int nw, const uint16_t* __restrict__ X, int Tn, int K,
+template <typename T, int NV>
+__global__ __launch_bounds__(256) void wstats_quant_kernel(const T* __restrict__ W, size_t nvec, double* __restrict__ partials,
+                                                           int nw, const T* __restrict__ X, int Tn, int K,
                                                            int8_t* __restrict__ Xq, float* __restrict__ gamma,
                                                            uint16_t* __restrict__ Xt, int nq, slab_sum_job sj) {
   const int b = blockIdx.x;
-  if (b < nw) wstats_partial_body<uint16_t>(W, nvec, partials, b, nw);
-  else if (b < nw + nq) quant_act_body<uint16_t, NV>(X, Tn, K, Xq, gamma, Xt, b - nw);
+  if (b < nw) wstats_partial_body<T>(W, nvec, partials, b, nw);
+  else if (b < nw + nq) quant_act_body<T, NV>(X, Tn, K, Xq, gamma, Xt, b - nw);
   else pq_slab_sum_bf16_body(sj.part, sj.splits, sj.M, sj.N, sj.C, sj.ldc, (size_t)(b - nw - nq) * 256 + threadIdx.x);
 }
 
-// bf16 only; rows too long for the register-cached quantiser (more than 16 vectors per lane) take two launches
-int pq_launch_wstats_quant(const void* W, size_t n_elems, double* partials, int nblocks, const void* X, int T, int K,
-                           int8_t* Xq, float* gamma, uint16_t* Xt, hipStream_t s, const float* slabs, int splits, int M, int N,
-                           void* C, int ldc) {
-  const int per_lane = (K / 8 + 63) / 64;
-  if (T <= 0 || per_lane > 16) return pq_set_error(PQ_ERR_SHAPE, "combined statistics/quantiser launch: bad shape T=%d K=%d", T, K);
+// rows too long for the register-cached quantiser (more than 16 vectors per lane) take two launches
+template <typename T>
+static int launch_wstats_quant_t(const T* w, size_t n_elems, double* partials, int nblocks, const T* x, int Tn, int K, int8_t* Xq,
+                                 float* gamma, uint16_t* Xt, hipStream_t s, const slab_sum_job& sj) {
+  constexpr int V = vec16<T>::V;
+  const int per_lane = (K / V + 63) / 64;
+  if (Tn <= 0 || per_lane > 16) return pq_set_error(PQ_ERR_SHAPE, "combined statistics/quantiser launch: bad shape T=%d K=%d", Tn, K);
   pq_prof_scope prof(PQP_QUANT, s);
-  const int nq = (T + 3) / 4;
-  const int ns = slabs ? (int)(((size_t)M * (N / 8) + 255) / 256) : 0;
+  const int nq = (Tn + 3) / 4;
+  const int ns = sj.part ? (int)(((size_t)sj.M * (sj.N / 8) + 255) / 256) : 0;
   dim3 grid(nblocks + nq + ns), block(256);
-  const uint16_t* w = (const uint16_t*)W;
-  const uint16_t* x = (const uint16_t*)X;
-  const slab_sum_job sj{slabs, splits, M, N, (uint16_t*)C, ldc};
-  if (per_lane <= 4) wstats_quant_kernel<4><<<grid, block, 0, s>>>(w, n_elems / 8, partials, nblocks, x, T, K, Xq, gamma, Xt, nq, sj);
-  else if (per_lane <= 8) wstats_quant_kernel<8><<<grid, block, 0, s>>>(w, n_elems / 8, partials, nblocks, x, T, K, Xq, gamma, Xt, nq, sj);
-  else wstats_quant_kernel<16><<<grid, block, 0, s>>>(w, n_elems / 8, partials, nblocks, x, T, K, Xq, gamma, Xt, nq, sj);
+  const size_t nvec = n_elems / V;
+  if (per_lane <= 4) wstats_quant_kernel<T, 4><<<grid, block, 0, s>>>(w, nvec, partials, nblocks, x, Tn, K, Xq, gamma, Xt, nq, sj);
+  else if (per_lane <= 8) wstats_quant_kernel<T, 8><<<grid, block, 0, s>>>(w, nvec, partials, nblocks, x, Tn, K, Xq, gamma, Xt, nq, sj);
+  else wstats_quant_kernel<T, 16><<<grid, block, 0, s>>>(w, nvec, partials, nblocks, x, Tn, K, Xq, gamma, Xt, nq, sj);
   PQ_CHECK_LAUNCH("wstats_quant_kernel");
   return PQ_OK;
+}
+
+int pq_launch_wstats_quant(const void* W, int dtype, size_t n_elems, double* partials, int nblocks, const void* X, int T, int K,
+                           int8_t* Xq, float* gamma, uint16_t* Xt, hipStream_t s, const float* slabs, int splits, int M, int N,
+                           void* C, int ldc) {
+  const slab_sum_job sj{slabs, splits, M, N, (uint16_t*)C, ldc};
+  if (dtype == PQ_F32)
+    return launch_wstats_quant_t<float>((const float*)W, n_elems, partials, nblocks, (const float*)X, T, K, Xq, gamma, Xt, s, sj);
+  return launch_wstats_quant_t<uint16_t>((const uint16_t*)W, n_elems, partials, nblocks, (const uint16_t*)X, T, K, Xq, gamma, Xt, s, sj);
 }
 
 int pq_stats_blocks(size_t n_elems) {
