@@ -165,6 +165,11 @@ lin_layout make_layout(const pq_linear_desc& d) {
     const size_t b = pq_plan_gemm(sh[0], sh[1], sh[2]).ws_bytes;
     if (b > sk) sk = b;
   }
+  if (bf16) {   // the 1-bit forward and the paired factor gradients
+    const size_t f = pq_plan_gemm(Ti, Ni, Ki, true, true).ws_bytes;
+    if (Ti > 0 && f > sk) sk = f;
+    if (ri > 0 && pq_plan_pair(Ti, Ni, ri, ri, Ki).ws0 > sk) sk = pq_plan_pair(Ti, Ni, ri, ri, Ki).ws0;
+  }
   if (routed) {
     L.n_red_a = pq_rowdot_blocks((int)S);
     if (8 * S * re * sizeof(float) > sk) sk = 8 * S * re * sizeof(float);   // narrow grouped GEMMs split the contraction up to 8 ways
@@ -181,7 +186,8 @@ lin_layout make_layout(const pq_linear_desc& d) {
   L.w_H = w.take(T * r * es);
   L.splitk = w.take(sk);
   // slabs of dA, which shares a launch with dB (whose slabs are in the region above)
-  L.splitk2 = w.take((bf16 && ri > 0 && Ki > 0) ? pq_plan_gemm(ri, Ki, Ti).ws_bytes : 0);
+  const size_t sk2a = (bf16 && ri > 0) ? pq_plan_gemm(ri, Ki, Ti).ws_bytes : 0, sk2b = (bf16 && ri > 0) ? pq_plan_pair(Ti, Ni, ri, ri, Ki).ws1 : 0;
+  L.splitk2 = w.take(sk2a > sk2b ? sk2a : sk2b);
   if (routed) {
     L.dYp = w.take(S * N * 2); L.rd = w.take(S * 4); L.dHs = w.take(S * re * 2); L.dXs = w.take(S * K * 2);
     L.dlogit = w.take(T * E * 4);
@@ -458,14 +464,14 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
   // (the fused form carries beta / alpha through the tile: only while that ratio stays far from the fp32 range, otherwise
   // the two branches are scaled separately as in the Sec. 3.2 sum)
   const bool fuse_hp = bf16 && r > 0 && d->alpha != 0.0f && fabsf(d->alpha) >= 9.5367431640625e-7f * fabsf(d->beta) &&
-                       pq_plan_gemm(T, N, K, true).splits == 1;
+                       pq_plan_fuses(pq_plan_gemm(T, N, K, true, true));
   if (r > 0 && !H_done)
     if (int err = launch_H(false)) return err;
   {  // 1-bit branch: Y = fl32(fl32(beta*lambda)/gamma_t) * acc   [+ alpha * H B^T when fused]
     pq_operand A{Xq, K, PQ_SRC_KC8, nullptr};
     pq_operand B{P, K / 8, PQ_SRC_BITS8, nullptr};
     pq_epilogue e = epi_zero();
-    e.C = Y; e.ldc = N; e.out_kind = ok;
+    e.C = Y; e.ldc = N; e.out_kind = ok; e.split_int8 = bf16 ? 1 : 0;
     if (fuse_hp) {   // Y = alpha * ( (beta*lambda/alpha/gamma_t) * acc + H B^T )
       pq_phase2 p2;
       p2.A2 = pq_operand{H, r, PQ_SRC_KC16, nullptr};
@@ -634,7 +640,7 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
     pq_operand B{cx + L.Pt, N / 8, PQ_SRC_BITS16, nullptr};
     pq_epilogue e = epi_zero();
     e.C = dX; e.ldc = K; e.out_kind = ok;
-    const bool fuse = r > 0 && pq_plan_gemm(T, K, N).splits == 1;
+    const bool fuse = r > 0 && pq_plan_fuses(pq_plan_gemm(T, K, N));
     if (fuse) {
       pq_phase2 p2;
       p2.A2 = pq_operand{dH, r, PQ_SRC_KC16, nullptr};
@@ -859,8 +865,11 @@ hp8_layout make_hp8_layout(int T, int K, int N, int r) {
     const size_t b = pq_plan_gemm(T, r, K, true, true).ws_bytes;
     if (b > sk) sk = b;
   }
+  const pq_pair_plan pair = pq_plan_pair(T, N, r, r, K);
+  if (pair.ws0 > sk) sk = pair.ws0;
   L.splitk = w.take(sk);
-  L.splitk2 = w.take((r > 0 && K > 0) ? pq_plan_gemm(r, K, T).ws_bytes : 0);   // dA's slabs when dB and dA share a launch
+  const size_t alone = (r > 0 && K > 0) ? pq_plan_gemm(r, K, T).ws_bytes : 0;
+  L.splitk2 = w.take(pair.ws1 > alone ? pair.ws1 : alone);   // dA's slabs when dB and dA share a launch
   L.ws_total = w.off;
   return L;
 }

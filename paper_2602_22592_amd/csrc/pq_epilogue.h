@@ -1,0 +1,142 @@
+// Pieces shared by the MFMA GEMM kernels (pq_gemm.hip, pq_tile.hip): the epilogue over eight consecutive columns and the
+// expansion of packed signs into MFMA operands.
+#pragma once
+#include "pq_internal.h"
+
+typedef int pq_i32x2 __attribute__((ext_vector_type(2)));
+#define PQ_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
+
+namespace {
+
+// ---------------------------------------------------------------------------------------------
+// Epilogue
+// ---------------------------------------------------------------------------------------------
+struct epi_state {
+  float sc0;
+  float mu;
+  double psum;
+};
+
+__device__ __forceinline__ void epi_begin(const pq_epilogue& e, epi_state& st) {
+  st.sc0 = e.dev_scale ? __fmul_rn(e.scale, *e.dev_scale) : e.scale;
+  st.mu = e.mu_dev ? *e.mu_dev : 0.0f;
+  st.psum = 0.0;
+}
+
+__device__ __forceinline__ float load_io(const void* p, int kind, size_t i) {
+  return kind == PQ_OUT_BF16 ? bf16_to_f32(((const uint16_t*)p)[i]) : ((const float*)p)[i];
+}
+
+template <int NT>
+__device__ __forceinline__ void epi_end(const pq_epilogue& e, epi_state& st, double* red, int block_linear) {
+  if (e.partials) {
+    double t = block_sum_d<NT>(st.psum, red);
+    if (threadIdx.x == 0) e.partials[block_linear] = t;
+  }
+}
+
+// Eight consecutive columns of one output row (MFMA engine; widths and leading dimensions are
+// multiples of 8, so every group is either fully inside or fully outside the matrix).
+__device__ __forceinline__ void load_io8(const void* p, int kind, size_t i, float* f) {
+  if (kind == PQ_OUT_BF16) {
+    const uint4 u = *reinterpret_cast<const uint4*>((const uint16_t*)p + i);
+    f[0] = __uint_as_float(u.x << 16); f[1] = __uint_as_float(u.x & 0xFFFF0000u);
+    f[2] = __uint_as_float(u.y << 16); f[3] = __uint_as_float(u.y & 0xFFFF0000u);
+    f[4] = __uint_as_float(u.z << 16); f[5] = __uint_as_float(u.z & 0xFFFF0000u);
+    f[6] = __uint_as_float(u.w << 16); f[7] = __uint_as_float(u.w & 0xFFFF0000u);
+  } else {
+    const float4 a = *reinterpret_cast<const float4*>((const float*)p + i);
+    const float4 b = *reinterpret_cast<const float4*>((const float*)p + i + 4);
+    f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
+  }
+}
+
+template <bool INT8>
+// row_scale: sc0 / row_div[m] when the caller has it at hand (NaN = not given, it is formed here)
+__device__ __forceinline__ void epi_vec8(const pq_epilogue& e, epi_state& st, int m, int n, const uint4& r0,
+                                         const uint4& r1, float row_scale = __builtin_nanf("")) {
+  const size_t ci = (size_t)m * e.ldc + n;
+  if ((e.m_limit > 0 && m >= e.m_limit) || (e.n_limit > 0 && n >= e.n_limit)) return;
+  const bool half = e.n_limit > 0 && n + 8 > e.n_limit;   // only the first four columns exist
+  if (e.out_kind == PQ_OUT_I32) {
+    *reinterpret_cast<uint4*>((int*)e.C + ci) = r0;
+    if (!half) *reinterpret_cast<uint4*>((int*)e.C + ci + 4) = r1;
+    return;
+  }
+  float acc[8];
+  if constexpr (INT8) {
+    acc[0] = (float)(int)r0.x; acc[1] = (float)(int)r0.y; acc[2] = (float)(int)r0.z; acc[3] = (float)(int)r0.w;
+    acc[4] = (float)(int)r1.x; acc[5] = (float)(int)r1.y; acc[6] = (float)(int)r1.z; acc[7] = (float)(int)r1.w;
+  } else {
+    acc[0] = __uint_as_float(r0.x); acc[1] = __uint_as_float(r0.y); acc[2] = __uint_as_float(r0.z); acc[3] = __uint_as_float(r0.w);
+    acc[4] = __uint_as_float(r1.x); acc[5] = __uint_as_float(r1.y); acc[6] = __uint_as_float(r1.z); acc[7] = __uint_as_float(r1.w);
+  }
+  if (e.dot_comp) {
+    float c[8];
+    load_io8(e.dot_comp, e.comp_kind, (size_t)m * e.ld_comp + n, c);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) st.psum += (double)c[j] * (double)acc[j];
+  }
+  if (e.sign_bytes) {
+    const uint32_t byte = e.sign_bytes[(size_t)m * e.ld_sign + (n >> 3)];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) st.psum += ((byte >> j) & 1u) ? (double)acc[j] : -(double)acc[j];
+  }
+  float sc = st.sc0;
+  if (e.row_div) sc = (row_scale == row_scale) ? row_scale : sc / e.row_div[m];
+  float val[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) val[j] = __fmul_rn(sc, acc[j]);
+  if (e.col_div) {
+    const float4 c0 = *reinterpret_cast<const float4*>(e.col_div + n), c1 = *reinterpret_cast<const float4*>(e.col_div + n + 4);
+    const float cd[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) val[j] = val[j] / cd[j];
+  }
+  if (e.maskW) {
+    float w[8];
+    load_io8(e.maskW, e.mask_kind, ci, w);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (fabs((double)w[j] - (double)st.mu) > (double)e.tau) val[j] = 0.0f;
+  }
+  if (e.accumulate) {
+    float c[8];
+    load_io8(e.C, e.out_kind, ci, c);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) val[j] += c[j];
+  }
+  if (e.out_kind == PQ_OUT_BF16) {
+    if (half)
+      *reinterpret_cast<uint2*>((uint16_t*)e.C + ci) = make_uint2(pack_bf16x2(val[0], val[1]), pack_bf16x2(val[2], val[3]));
+    else
+      *reinterpret_cast<uint4*>((uint16_t*)e.C + ci) =
+          make_uint4(pack_bf16x2(val[0], val[1]), pack_bf16x2(val[2], val[3]), pack_bf16x2(val[4], val[5]),
+                     pack_bf16x2(val[6], val[7]));
+  } else {
+    *reinterpret_cast<float4*>((float*)e.C + ci) = make_float4(val[0], val[1], val[2], val[3]);
+    if (!half) *reinterpret_cast<float4*>((float*)e.C + ci + 4) = make_float4(val[4], val[5], val[6], val[7]);
+  }
+}
+
+// MFMA operand of +/-1 values from packed bits (bit i set = +1, clear = -1, Eq. 4): 8 bits -> 8 bf16 (bits
+// above the eighth are ignored), 16 bits -> 16 int8.
+__device__ __forceinline__ i32x4_t pq_bits_to_bf16(uint32_t b) {
+  const uint32_t nb = ~b;
+  i32x4_t o;
+#pragma unroll
+  for (int d = 0; d < 4; ++d)
+    o[d] = (int)(0x3F803F80u | ((nb << (15 - 2 * d)) & 0x00008000u) | ((nb << (30 - 2 * d)) & 0x80000000u));
+  return o;
+}
+__device__ __forceinline__ i32x4_t pq_bits_to_i8(uint32_t b) {
+  i32x4_t o;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const uint32_t m = __umul24((b >> (4 * d)) & 0xFu, 0x00204081u) & 0x01010101u;
+    o[d] = (int)__builtin_amdgcn_perm(0x000001FFu, 0x000001FFu, m);
+  }
+  return o;
+}
+
+}  // namespace

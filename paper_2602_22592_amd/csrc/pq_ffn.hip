@@ -7,6 +7,7 @@
 // GEMM epilogue, and the STE backward on the de-quantised factors.
 // This file sequences the kernels; all arithmetic lives in pq_gemm.hip / pq_quant.hip / pq_moe.hip.
 #include <string.h>
+#include <utility>
 #include "pq_internal.h"
 
 namespace {
@@ -83,6 +84,10 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   for (const auto& sh : shapes) {
     if (sh[0] <= 0 || sh[1] <= 0) continue;
     const size_t b = pq_plan_gemm(sh[0], sh[1], sh[2]).ws_bytes;
+    if (b > sk) sk = b;
+  }
+  for (const auto& sh : {std::pair<int, int>{Fi, Di}, std::pair<int, int>{Di, Fi}}) {   // the 1-bit forward products
+    const size_t b = Ti > 0 ? pq_plan_gemm(Ti, sh.first, sh.second, true, true).ws_bytes : 0;
     if (b > sk) sk = b;
   }
   // the expert up/gate projections and their input gradients split the contraction up to 8 ways: [8][S][r] fp32
@@ -212,7 +217,7 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
     pq_operand A{Xq, D, PQ_SRC_KC8, nullptr};
     pq_operand Bu{cx + L.P_up, D / 8, PQ_SRC_BITS8, nullptr};
     pq_epilogue e = epi0();
-    e.C = cx + L.U; e.ldc = F; e.out_kind = PQ_OUT_BF16; e.dev_scale = (const float*)(cx + L.ml_up) + 1; e.row_div = gx;
+    e.C = cx + L.U; e.ldc = F; e.out_kind = PQ_OUT_BF16; e.dev_scale = (const float*)(cx + L.ml_up) + 1; e.row_div = gx; e.split_int8 = 1;
     if (int err = pq_launch_gemm(T, F, D, A, Bu, e, s, PQP_GEMM_ONEBIT, sk)) return err;
     pq_operand Bg{cx + L.P_gate, D / 8, PQ_SRC_BITS8, nullptr};
     e.C = cx + L.G; e.dev_scale = (const float*)(cx + L.ml_gate) + 1;
@@ -225,7 +230,7 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
     pq_operand A{Hq, F, PQ_SRC_KC8, nullptr};
     pq_operand B{cx + L.P_down, F / 8, PQ_SRC_BITS8, nullptr};
     pq_epilogue e = epi0();
-    e.C = Y; e.ldc = D; e.out_kind = PQ_OUT_BF16; e.scale = d->beta; e.dev_scale = (const float*)(cx + L.ml_down) + 1; e.row_div = gh;
+    e.C = Y; e.ldc = D; e.out_kind = PQ_OUT_BF16; e.scale = d->beta; e.dev_scale = (const float*)(cx + L.ml_down) + 1; e.row_div = gh; e.split_int8 = 1;
     if (int err = pq_launch_gemm(T, D, F, A, B, e, s, PQP_GEMM_ONEBIT, sk)) return err;
   }
   // routed experts: router -> stable permutation by expert -> gather -> grouped GEMMs -> combine

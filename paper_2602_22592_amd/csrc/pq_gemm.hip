@@ -9,7 +9,7 @@
 // Two main loops share the kernel.  The streaming loop (256x256 tiles, whole contraction steps) sends operands from
 // global memory straight into LDS: KC tiles as ROWS x 128 bytes, KS16 tiles as they lie in memory (read back with the
 // transposing LDS read), and packed bits stay packed in LDS and are expanded in registers next to the MFMAs that consume
-// them.  The register-staged loop (ragged contraction steps, 128x128 tiles, grouped contraction ranges) stages every
+// them.  The register-staged loop (contractions of partial steps) stages every
 // operand as ROWS x 128 bytes with the contraction index contiguous: KS16 blocks are transposed in registers with byte
 // permutes, bits are expanded on the way into LDS.
 // A wavefront owns a (BM/WGM) x (BN/WGN) sub-tile as 32x32 MFMA blocks:
@@ -19,7 +19,7 @@
 #include <stdlib.h>
 #include <string.h>
 #include <type_traits>
-#include "pq_internal.h"
+#include "pq_epilogue.h"
 
 #ifdef PQ_TRACE
 // Instrumented builds only (never the shipped library): cycle stamps of two workgroups of the streaming loops, taken at
@@ -236,117 +236,6 @@ struct tile_stage {
 };
 
 // ---------------------------------------------------------------------------------------------
-// Epilogue
-// ---------------------------------------------------------------------------------------------
-struct epi_state {
-  float sc0;
-  float mu;
-  double psum;
-};
-
-__device__ __forceinline__ void epi_begin(const pq_epilogue& e, epi_state& st) {
-  st.sc0 = e.dev_scale ? __fmul_rn(e.scale, *e.dev_scale) : e.scale;
-  st.mu = e.mu_dev ? *e.mu_dev : 0.0f;
-  st.psum = 0.0;
-}
-
-__device__ __forceinline__ float load_io(const void* p, int kind, size_t i) {
-  return kind == PQ_OUT_BF16 ? bf16_to_f32(((const uint16_t*)p)[i]) : ((const float*)p)[i];
-}
-
-template <int NT>
-__device__ __forceinline__ void epi_end(const pq_epilogue& e, epi_state& st, double* red, int block_linear) {
-  if (e.partials) {
-    double t = block_sum_d<NT>(st.psum, red);
-    if (threadIdx.x == 0) e.partials[block_linear] = t;
-  }
-}
-
-// Eight consecutive columns of one output row (MFMA engine; widths and leading dimensions are
-// multiples of 8, so every group is either fully inside or fully outside the matrix).
-__device__ __forceinline__ void load_io8(const void* p, int kind, size_t i, float* f) {
-  if (kind == PQ_OUT_BF16) {
-    const uint4 u = *reinterpret_cast<const uint4*>((const uint16_t*)p + i);
-    f[0] = __uint_as_float(u.x << 16); f[1] = __uint_as_float(u.x & 0xFFFF0000u);
-    f[2] = __uint_as_float(u.y << 16); f[3] = __uint_as_float(u.y & 0xFFFF0000u);
-    f[4] = __uint_as_float(u.z << 16); f[5] = __uint_as_float(u.z & 0xFFFF0000u);
-    f[6] = __uint_as_float(u.w << 16); f[7] = __uint_as_float(u.w & 0xFFFF0000u);
-  } else {
-    const float4 a = *reinterpret_cast<const float4*>((const float*)p + i);
-    const float4 b = *reinterpret_cast<const float4*>((const float*)p + i + 4);
-    f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
-  }
-}
-
-template <bool INT8>
-// row_scale: sc0 / row_div[m] when the caller has it at hand (NaN = not given, it is formed here)
-__device__ __forceinline__ void epi_vec8(const pq_epilogue& e, epi_state& st, int m, int n, const uint4& r0,
-                                         const uint4& r1, float row_scale = __builtin_nanf("")) {
-  const size_t ci = (size_t)m * e.ldc + n;
-  if ((e.m_limit > 0 && m >= e.m_limit) || (e.n_limit > 0 && n >= e.n_limit)) return;
-  const bool half = e.n_limit > 0 && n + 8 > e.n_limit;   // only the first four columns exist
-  if (e.out_kind == PQ_OUT_I32) {
-    *reinterpret_cast<uint4*>((int*)e.C + ci) = r0;
-    if (!half) *reinterpret_cast<uint4*>((int*)e.C + ci + 4) = r1;
-    return;
-  }
-  float acc[8];
-  if constexpr (INT8) {
-    acc[0] = (float)(int)r0.x; acc[1] = (float)(int)r0.y; acc[2] = (float)(int)r0.z; acc[3] = (float)(int)r0.w;
-    acc[4] = (float)(int)r1.x; acc[5] = (float)(int)r1.y; acc[6] = (float)(int)r1.z; acc[7] = (float)(int)r1.w;
-  } else {
-    acc[0] = __uint_as_float(r0.x); acc[1] = __uint_as_float(r0.y); acc[2] = __uint_as_float(r0.z); acc[3] = __uint_as_float(r0.w);
-    acc[4] = __uint_as_float(r1.x); acc[5] = __uint_as_float(r1.y); acc[6] = __uint_as_float(r1.z); acc[7] = __uint_as_float(r1.w);
-  }
-  if (e.dot_comp) {
-    float c[8];
-    load_io8(e.dot_comp, e.comp_kind, (size_t)m * e.ld_comp + n, c);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) st.psum += (double)c[j] * (double)acc[j];
-  }
-  if (e.sign_bytes) {
-    const uint32_t byte = e.sign_bytes[(size_t)m * e.ld_sign + (n >> 3)];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) st.psum += ((byte >> j) & 1u) ? (double)acc[j] : -(double)acc[j];
-  }
-  float sc = st.sc0;
-  if (e.row_div) sc = (row_scale == row_scale) ? row_scale : sc / e.row_div[m];
-  float val[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) val[j] = __fmul_rn(sc, acc[j]);
-  if (e.col_div) {
-    const float4 c0 = *reinterpret_cast<const float4*>(e.col_div + n), c1 = *reinterpret_cast<const float4*>(e.col_div + n + 4);
-    const float cd[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
-#pragma unroll
-    for (int j = 0; j < 8; ++j) val[j] = val[j] / cd[j];
-  }
-  if (e.maskW) {
-    float w[8];
-    load_io8(e.maskW, e.mask_kind, ci, w);
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (fabs((double)w[j] - (double)st.mu) > (double)e.tau) val[j] = 0.0f;
-  }
-  if (e.accumulate) {
-    float c[8];
-    load_io8(e.C, e.out_kind, ci, c);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) val[j] += c[j];
-  }
-  if (e.out_kind == PQ_OUT_BF16) {
-    if (half)
-      *reinterpret_cast<uint2*>((uint16_t*)e.C + ci) = make_uint2(pack_bf16x2(val[0], val[1]), pack_bf16x2(val[2], val[3]));
-    else
-      *reinterpret_cast<uint4*>((uint16_t*)e.C + ci) =
-          make_uint4(pack_bf16x2(val[0], val[1]), pack_bf16x2(val[2], val[3]), pack_bf16x2(val[4], val[5]),
-                     pack_bf16x2(val[6], val[7]));
-  } else {
-    *reinterpret_cast<float4*>((float*)e.C + ci) = make_float4(val[0], val[1], val[2], val[3]);
-    if (!half) *reinterpret_cast<float4*>((float*)e.C + ci + 4) = make_float4(val[4], val[5], val[6], val[7]);
-  }
-}
-
-// ---------------------------------------------------------------------------------------------
 // Streaming main loop (DTL instantiations): operands go from global memory straight into LDS
 // (global_load_lds_dwordx4, no staging registers, no ds_write), and the contraction step is a fixed
 // instruction order written as volatile asm statements: the fragment reads of MFMA group g+1 are issued
@@ -366,8 +255,6 @@ __device__ __forceinline__ void epi_vec8(const pq_epilogue& e, epi_state& st, in
 //     behind each MFMA; with B that small the A operand gets a ring of four stages instead of two.
 // A wait on asm-issued reads names the registers it releases ("+v"), which orders their uses after it.
 // ---------------------------------------------------------------------------------------------
-typedef int pq_i32x2 __attribute__((ext_vector_type(2)));
-#define PQ_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 #define PQ_DS_READ128(dst, addr, off) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(off) : "memory")
 #define PQ_DS_READ64(dst, addr, off) asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(off) : "memory")
 #define PQ_DS_READ_TR(dst, addr, off) asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(off) : "memory")
@@ -381,26 +268,6 @@ typedef int pq_i32x2 __attribute__((ext_vector_type(2)));
 #define PQ_SETPRIO(n) asm volatile("s_setprio %0" ::"n"(n))
 #define PQ_MFMA_BF16(acc, a, b) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %2, %1, %0" : "+v"(acc) : "v"(a), "v"(b))
 #define PQ_MFMA_I8(acc, a, b) asm volatile("v_mfma_i32_32x32x32_i8 %0, %2, %1, %0" : "+v"(acc) : "v"(a), "v"(b))
-
-// MFMA operand of +/-1 values from packed bits (bit i set = +1, clear = -1, Eq. 4): 8 bits -> 8 bf16 (bits
-// above the eighth are ignored), 16 bits -> 16 int8.
-__device__ __forceinline__ i32x4_t pq_bits_to_bf16(uint32_t b) {
-  const uint32_t nb = ~b;
-  i32x4_t o;
-#pragma unroll
-  for (int d = 0; d < 4; ++d)
-    o[d] = (int)(0x3F803F80u | ((nb << (15 - 2 * d)) & 0x00008000u) | ((nb << (30 - 2 * d)) & 0x80000000u));
-  return o;
-}
-__device__ __forceinline__ i32x4_t pq_bits_to_i8(uint32_t b) {
-  i32x4_t o;
-#pragma unroll
-  for (int d = 0; d < 4; ++d) {
-    const uint32_t m = __umul24((b >> (4 * d)) & 0xFu, 0x00204081u) & 0x01010101u;
-    o[d] = (int)__builtin_amdgcn_perm(0x000001FFu, 0x000001FFu, m);
-  }
-  return o;
-}
 
 // One fragment set of a 128x64 wavefront tile: four A and two B operands of 16 bytes per lane.  Operands
 // read with ds_read_b128 are whole (q), transposing reads deliver 8-byte halves (h) that the register
@@ -474,15 +341,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
   // Work items are ordered (contraction split, tile row, tile column) and XCD c takes the c-th eighth of
   // that order: with a split contraction an XCD then works on one split and a band of tile rows, so the
   // operand panels it streams are shared by its workgroups instead of being fetched by every XCD.
-  // paired launches exist for the 128x128 kernel with contraction-strided operands only; elsewhere the test would
-  // only turn kernel arguments into run-time selections
-  if constexpr (BM == 128 && !DTL && AK == PQ_SRC_KS16 && BKIND == PQ_SRC_KS16 && AK2 < 0)
-  if (grp.mode == 3 && blockIdx.z == 1) {            // uniform: the second problem of a paired launch
-    A = grp.second.A; B = grp.second.B;
-    M = grp.second.M; N = grp.second.N; nbn = grp.second.nbn;
-    splitk_part = grp.second.part;
-    epi.C = grp.second.C; epi.ldc = grp.second.ldc; epi.scale = grp.second.scale;
-  }
   int pid = blockIdx.x, split = blockIdx.y;
   {
     const int nb = total_tiles * (int)gridDim.y;
@@ -496,10 +354,9 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
   const int bm = pid / nbn, bn = pid % nbn;
   int m0 = bm * BM;
   const int n0 = bn * BN;
-  int kb = split * kchunk;
-  int ke = min(K, kb + kchunk);
-  int Mtot = M;                 // rows of C (a split's slab has Mtot rows)
-  size_t slab_group = 0;        // offset of this group's rows in a slab (grouped contraction ranges)
+  const int kb = split * kchunk;
+  const int ke = min(K, kb + kchunk);
+  const int Mtot = M;           // rows of C (a split's slab has Mtot rows)
   if (grp.mode == 1) {          // rows of group z: [offsets[z], offsets[z+1]); row tiles are numbered group after group
     int t = bm, z = 0;
     for (; z < grp.n_groups; ++z) {
@@ -512,21 +369,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
     M = grp.offsets[z + 1];
     B.p = (const char*)B.p + (size_t)z * grp.b_stride * (BKIND == PQ_SRC_KC8 ? 1 : 2);
     if (epi.col_div) epi.col_div += (size_t)z * grp.coldiv_stride;
-  } else if (grp.mode == 2) {   // contraction range of group z, own output slab
-    const int z = blockIdx.z;
-    kb = grp.offsets[z];
-    ke = grp.offsets[z + 1];
-    if (gridDim.y > 1) {
-      // the group's range in gridDim.y pieces of whole 64-element steps (the last ones may be empty: they leave zeros);
-      // a slab holds the outputs of all groups, one under the other
-      int chunk = (ke - kb + (int)gridDim.y - 1) / (int)gridDim.y;
-      chunk = (chunk + 63) & ~63;
-      kb = min(ke, kb + split * chunk);
-      ke = min(ke, kb + chunk);
-      slab_group = (size_t)z * M * N;
-      Mtot = grp.n_groups * M;
-    }
-    epi.C = (char*)epi.C + (size_t)z * grp.c_stride * (epi.out_kind == PQ_OUT_BF16 ? 2 : 4);
   }
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1110,7 +952,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
   // the raw fp32 accumulators go to this split's slab instead; splitk_reduce_kernel finishes the job.
   epi_state st;
   epi_begin(epi, st);
-  float* slab = splitk_part ? splitk_part + (size_t)split * Mtot * N + slab_group : nullptr;
+  float* slab = splitk_part ? splitk_part + (size_t)split * Mtot * N : nullptr;
   const bool row_scaled = !slab && epi.row_div != nullptr;   // uniform
   if (row_scaled) {
     for (int r = tid; r < BM; r += NT) rowscale[r] = st.sc0 / epi.row_div[min(m0 + r, M - 1)];
@@ -1537,7 +1379,7 @@ int launch_mfma(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A
   const int nbm = grp.mode == 1 ? (grp.max_rows + BM - 1) / BM + grp.n_groups : (M + BM - 1) / BM;
   const int nbn = (N + BN - 1) / BN;
   const int tiles = nbm * nbn;
-  dim3 grid(tiles, pl.splits, grp.mode == 2 ? grp.n_groups : grp.mode == 3 ? 2 : 1), block(WGM * WGN * 64);
+  dim3 grid(tiles, pl.splits), block(WGM * WGN * 64);
   mfma_gemm_kernel<BM, BN, WGM, WGN, KB, FAST, INT8, AK, BKIND, AK2, BK2, DTL><<<grid, block, 0, s>>>(
       M, N, K, A, B, epi, nbn, tiles, pl.kchunk, pl.splits > 1 ? part : nullptr, grp, ph2);
   PQ_CHECK_LAUNCH("mfma_gemm_kernel");
@@ -1548,7 +1390,8 @@ template <bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1>
 int launch_mfma_cfg(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B,
                     const pq_epilogue& epi, hipStream_t s, float* part, const pq_gemm_group& grp, const pq_phase2& ph2) {
   constexpr int EPB = INT8 ? 128 : 64;
-  if (pl.bm == 256) {
+  if (pl.bm != 256) return pq_launch_tile(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+  {
     // whole tiles everywhere: the instantiation without validity masks
     const bool whole = grp.mode == 0 && M % 256 == 0 && N % 256 == 0 && K % EPB == 0 && pl.kchunk % EPB == 0 &&
                        ph2.K2 % 64 == 0;
@@ -1586,7 +1429,6 @@ int launch_mfma_cfg(const pq_gemm_plan& pl, int M, int N, int K, const pq_operan
     if (whole) return launch_mfma<256, 256, 2, 4, 128, true, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
     return launch_mfma<256, 256, 2, 4, 128, false, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
   }
-  return launch_mfma<128, 128, 2, 2, 128, false, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
 }
 
 }  // namespace
@@ -1998,30 +1840,84 @@ int pq_launch_skinny(int M, int K, const pq_operand& A, const pq_operand& B, con
   return PQ_OK;
 }
 
-// Tile shape and contraction split for one GEMM.  A 256x256 tile (8 wavefronts, 128x64 each) when
-// the output is large enough, else 128x128 (4 wavefronts); when the tiles alone cannot occupy the
-// 256 compute units the contraction is split and reduced in a second, fixed-order pass.
-pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8, bool split_int8) {
+// Tile shape and contraction split for one GEMM: the smallest of the times (us) that the kernels were measured to take, c the
+// workgroups a CU has to take one after the other:
+//   64x64:   4.5 + 0.25 c per 128-byte step (0.30 with int8) + 1 per further workgroup
+//   128x128: 7 + 0.85 per step alone on a CU (0.95), 0.72 c when two workgroups share it (0.75) + 2.5 per further workgroup
+//   256x256: c (12 + 1.5 per step (1.25), 2.0 (1.9) on the register-staged loop that takes contractions of partial steps);
+//            split only while the tiles are at most half of the CUs: beyond that more active CUs lower the clock instead
+//   a split's reduction: 2 + its slabs and the result at 7 TB/s, at least 4.7
+// (2048 x 2048 outputs over 2048 / 8192 tokens: 64x64 37 / 126, 128x128 35 / 109, 256x256 in four splits 43 / 82 with the
+// reduction; 765 x 672 over 672: 7, 13, 22.)
+static double est_tile(int bm, long wgs, long steps, bool int8, bool whole) {
+  const double c = (double)((wgs + 255) / 256);
+  if (bm == 64) return 4.5 + c * steps * (int8 ? 0.30 : 0.25) + (c - 1.0);
+  if (bm == 128) return 7.0 + (wgs <= 256 ? steps * (int8 ? 0.95 : 0.85) : c * steps * (int8 ? 0.75 : 0.72)) + 2.5 * (c - 1.0);
+  return c * (12.0 + steps * (int8 ? (whole ? 1.25 : 1.9) : (whole ? 1.5 : 2.0)));
+}
+static double est_reduce(int splits, double elems) {
+  if (splits <= 1) return 0.0;
+  const double t = 2.0 + (4.0 * splits + 3.0) * elems / 7.0e6;
+  return t > 4.7 ? t : 4.7;
+}
+
+static pq_gemm_plan pq_plan_gemm_impl(int M, int N, int K, bool int8, bool may_split) {
   pq_gemm_plan pl;
   memset(&pl, 0, sizeof(pl));
+  pl.bm = 64;
   pl.splits = 1;
-  const bool big = (M >= 256 && N >= 256);
-  pl.bm = pl.bn = big ? 256 : 128;
-  const long tiles = (long)((M + pl.bm - 1) / pl.bm) * ((N + pl.bn - 1) / pl.bn);
   pl.kchunk = K > 0 ? K : 1;
-  if ((!int8 || split_int8) && tiles > 0 && tiles <= 128 && K >= 512) {
-    long want = 256 / tiles;
-    if (want > 16) want = 16;
-    long chunk = (K + want - 1) / want;
-    chunk = (chunk + 255) / 256 * 256;          // whole 128-byte steps, at least four of them
-    pl.kchunk = (int)chunk;
-    pl.splits = (int)((K + chunk - 1) / chunk);
+  const int epb = int8 ? 128 : 64;
+  double best = 1e30;
+  for (int bm = 64; bm <= 256; bm *= 2) {
+    if (bm == 256 && !(M >= 256 && N >= 256)) continue;
+    const long tiles = (long)((M + bm - 1) / bm) * ((N + bm - 1) / bm);
+    const bool whole = K % epb == 0;
+    for (int want = 1; want <= 16; ++want) {
+      if (want > 1 && (!may_split || K / want < 256 || tiles * want > 1024 || (bm == 256 && (int8 || tiles > 128)))) break;
+      const int chunk = want == 1 ? (K > 0 ? K : 1) : ((K + want - 1) / want + 255) / 256 * 256;   // whole 128-byte steps, at least two
+      const int sp = want == 1 ? 1 : (K + chunk - 1) / chunk;
+      const double t = est_tile(bm, tiles * sp, (chunk + epb - 1) / epb, int8, whole) + est_reduce(sp, (double)M * N);
+      if (t < best) { best = t; pl.bm = bm; pl.splits = sp; pl.kchunk = chunk; }
+    }
   }
+  pl.bn = pl.bm;
+  const long tiles = (long)((M + pl.bm - 1) / pl.bm) * ((N + pl.bn - 1) / pl.bn);
   pl.red_blocks = pl.splits > 1 ? (int)(((size_t)M * (N / 8) + 255) / 256) : (int)tiles;
   pl.ws_bytes = pl.splits > 1 ? (size_t)pl.splits * M * N * sizeof(float) : 0;
   return pl;
 }
+pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8, bool split_int8) {
+  return pq_plan_gemm_impl(M, N, K, int8, !int8 || split_int8);
+}
 
+// Two narrow products over the same contraction in one launch (dB and dA of the rank-r branch).  tn: rank 128 over many
+// tokens, the streaming pair kernel (problem 1 runs transposed): four token ranges when that already gives a workgroup per
+// CU (fewer slabs to write and add), up to sixteen for small matrices, never shorter than 256 tokens.  Otherwise 64x64 tiles.
+pq_pair_plan pq_plan_pair(int K, int M0, int N0, int M1, int N1) {
+  pq_pair_plan p;
+  memset(&p, 0, sizeof(p));
+  int sp = 4;
+  while (sp < 16 && (M0 / 64 + N1 / 64) * sp < 256 && K % (sp * 2 * 64) == 0 && K / (sp * 2) >= 256) sp *= 2;
+  p.tn = N0 == SK_BN && M1 == SK_BN && M0 >= 64 && N1 >= 64 && M0 % 64 == 0 && N1 % 64 == 0 && K >= 2048 && K % (sp * 64) == 0;
+  p.splits = sp;
+  p.kchunk = K / sp;
+  if (!p.tn) {
+    const long tiles = (long)((M0 + 63) / 64) * ((N0 + 63) / 64) + (long)((M1 + 63) / 64) * ((N1 + 63) / 64);
+    const double elems = (double)M0 * N0 + (double)M1 * N1;
+    double best = 1e30;
+    for (int want = 1; want <= 16; ++want) {
+      if (want > 1 && (K / want < 256 || tiles * want > 1024)) break;
+      const int chunk = want == 1 ? (K > 0 ? K : 1) : ((K + want - 1) / want + 255) / 256 * 256;
+      const int n = want == 1 ? 1 : (K + chunk - 1) / chunk;
+      const double t = est_tile(64, tiles * n, (chunk + 63) / 64, false, true) + est_reduce(n, elems);
+      if (t < best) { best = t; p.splits = n; p.kchunk = chunk; }
+    }
+  }
+  p.ws0 = p.splits > 1 ? (size_t)p.splits * M0 * N0 * sizeof(float) : 0;
+  p.ws1 = p.splits > 1 ? (size_t)p.splits * M1 * N1 * sizeof(float) : 0;
+  return p;
+}
 
 int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const pq_operand& B0, float* C0, int ldc0, float scale0,
                              int M1, int N1, const pq_operand& A1, const pq_operand& B1, float* C1, int ldc1, float scale1,
@@ -2033,87 +1929,71 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
   e0.C = C0; e0.ldc = ldc0; e0.out_kind = PQ_OUT_F32; e0.scale = scale0;
   pq_epilogue e1 = e0;
   e1.C = C1; e1.ldc = ldc1; e1.scale = scale1;
-  const pq_gemm_plan p0 = pq_plan_gemm(M0, N0, K), p1 = pq_plan_gemm(M1, N1, K);
-  {
-    // rank 128 over many tokens: the streaming pair kernel (problem 1 runs transposed).  Four token ranges when that
-    // already gives a workgroup per CU (fewer slabs to write and add), up to sixteen for small matrices, never
-    // shorter than 256 tokens
-    auto al = [](const pq_operand& o) { return o.kind == PQ_SRC_KS16 && !o.kdiv && (o.ld * 2) % 16 == 0 && ((uintptr_t)o.p % 16) == 0; };
-    int splits = 4;
-    while (splits < 16 && (M0 / 64 + N1 / 64) * splits < 256 && K % (splits * 2 * 64) == 0 && K / (splits * 2) >= 256) splits *= 2;
-    const size_t need0 = (size_t)splits * M0 * N0 * sizeof(float), need1 = (size_t)splits * M1 * N1 * sizeof(float);
-    const bool tn = N0 == SK_BN && M1 == SK_BN && M0 >= 64 && N1 >= 64 && M0 % 64 == 0 && N1 % 64 == 0 && K >= 2048 &&
-                    K % (splits * 64) == 0 && al(A0) && al(B0) && al(A1) && al(B1) && A0.ld >= M0 && B0.ld >= N0 && A1.ld >= M1 &&
-                    B1.ld >= N1 && splitk_ws0 && splitk_ws1 && p0.ws_bytes >= need0 && p1.ws_bytes >= need1 &&
-                    ((uintptr_t)splitk_ws0 % 16) == 0 && ((uintptr_t)splitk_ws1 % 16) == 0;
-    if (tn) {
-      skt_problem q0{(const uint16_t*)A0.p, A0.ld, (const uint16_t*)B0.p, B0.ld, M0, 0, (float*)splitk_ws0};
-      skt_problem q1{(const uint16_t*)B1.p, B1.ld, (const uint16_t*)A1.p, A1.ld, N1, 1, (float*)splitk_ws1};
-      {
-        pq_prof_scope prof(prof_label0, s);
-        const dim3 grid((M0 > N1 ? M0 : N1) / 64, splits, 2);
-        skinny_tn_pair_kernel<<<grid, 256, 0, s>>>(q0, q1, K / splits);
-        PQ_CHECK_LAUNCH("skinny_tn_pair_kernel");
-      }
-      pq_prof_scope prof(PQP_SPLITK_REDUCE, s);
-      pq_reduce_job none;
-      memset(&none, 0, sizeof(none));
-      const int rb0 = (int)(((size_t)M0 * (N0 / 8) + 255) / 256), rb1 = (int)(((size_t)M1 * (N1 / 8) + 255) / 256);
-      splitk_reduce_pair_kernel<<<rb0 + rb1 + (jobs ? 2 : 0), 256, 0, s>>>(splits, rb0, rb1, M0, N0, (const float*)splitk_ws0, e0, M1, N1,
-                                                                          (const float*)splitk_ws1, e1, jobs ? jobs[0] : none,
-                                                                          jobs ? jobs[1] : none);
-      PQ_CHECK_LAUNCH("splitk_reduce_pair_kernel");
-      if (jobs && jobs_done) *jobs_done = true;
-      return PQ_OK;
-    }
-  }
-  const int nbm0 = (M0 + 127) / 128, nbn0 = (N0 + 127) / 128, nbm1 = (M1 + 127) / 128, nbn1 = (N1 + 127) / 128;
-  const bool same = M0 > 0 && N0 > 0 && M1 > 0 && N1 > 0 && K > 0 && p0.bm == 128 && p1.bm == 128 && p0.splits == p1.splits &&
-                    p0.kchunk == p1.kchunk && nbm0 * nbn0 == nbm1 * nbn1 && A0.kind == PQ_SRC_KS16 && B0.kind == PQ_SRC_KS16 &&
-                    A1.kind == PQ_SRC_KS16 && B1.kind == PQ_SRC_KS16 && (p0.splits == 1 || (splitk_ws0 && splitk_ws1));
-  if (!same) {
+  const pq_pair_plan pp = pq_plan_pair(K, M0, N0, M1, N1);
+  pq_reduce_job none;
+  memset(&none, 0, sizeof(none));
+  const int rb0 = (int)(((size_t)M0 * (N0 / 8) + 255) / 256), rb1 = (int)(((size_t)M1 * (N1 / 8) + 255) / 256);
+  auto al = [](const pq_operand& o) { return o.kind == PQ_SRC_KS16 && !o.kdiv && (o.ld * 2) % 16 == 0 && ((uintptr_t)o.p % 16) == 0; };
+  const bool one = M0 > 0 && N0 > 0 && M1 > 0 && N1 > 0 && K > 0 && al(A0) && al(B0) && al(A1) && al(B1) && A0.ld >= M0 && B0.ld >= N0 &&
+                   A1.ld >= M1 && B1.ld >= N1 &&
+                   (pp.splits == 1 || (splitk_ws0 && splitk_ws1 && ((uintptr_t)splitk_ws0 % 16) == 0 && ((uintptr_t)splitk_ws1 % 16) == 0));
+  if (!one) {
     if (int rc = pq_launch_gemm(M0, N0, K, A0, B0, e0, s, prof_label0, splitk_ws0)) return rc;
     return pq_launch_gemm(M1, N1, K, A1, B1, e1, s, prof_label1, splitk_ws1);
   }
-  pq_gemm_group grp;
-  memset(&grp, 0, sizeof(grp));
-  grp.mode = 3;
-  grp.second.A = A1; grp.second.B = B1; grp.second.C = C1; grp.second.ldc = ldc1; grp.second.scale = scale1;
-  grp.second.part = p0.splits > 1 ? (float*)splitk_ws1 : nullptr; grp.second.M = M1; grp.second.N = N1; grp.second.nbn = nbn1;
-  pq_phase2 ph2;
-  memset(&ph2, 0, sizeof(ph2));
   {
     pq_prof_scope prof(prof_label0, s);
-    if (int rc = launch_mfma<128, 128, 2, 2, 128, false, false, PQ_SRC_KS16, PQ_SRC_KS16>(p0, M0, N0, K, A0, B0, e0, s, (float*)splitk_ws0, grp, ph2))
-      return rc;
+    if (pp.tn) {
+      skt_problem q0{(const uint16_t*)A0.p, A0.ld, (const uint16_t*)B0.p, B0.ld, M0, 0, (float*)splitk_ws0};
+      skt_problem q1{(const uint16_t*)B1.p, B1.ld, (const uint16_t*)A1.p, A1.ld, N1, 1, (float*)splitk_ws1};
+      const dim3 grid((M0 > N1 ? M0 : N1) / 64, pp.splits, 2);
+      skinny_tn_pair_kernel<<<grid, 256, 0, s>>>(q0, q1, K / pp.splits);
+      PQ_CHECK_LAUNCH("skinny_tn_pair_kernel");
+    } else {
+      pq_gemm_plan pl;
+      memset(&pl, 0, sizeof(pl));
+      pl.bm = pl.bn = 64; pl.splits = pp.splits; pl.kchunk = pp.kchunk;
+      pq_gemm_group grp;
+      memset(&grp, 0, sizeof(grp));
+      grp.mode = 3;
+      grp.second.A = A1; grp.second.B = B1; grp.second.C = C1; grp.second.ldc = ldc1; grp.second.scale = scale1;
+      grp.second.part = pp.splits > 1 ? (float*)splitk_ws1 : nullptr; grp.second.M = M1; grp.second.N = N1; grp.second.nbn = (N1 + 63) / 64;
+      pq_phase2 ph2;
+      memset(&ph2, 0, sizeof(ph2));
+      if (int rc = pq_launch_tile(pl, M0, N0, K, A0, B0, e0, s, (float*)splitk_ws0, grp, ph2)) return rc;
+    }
   }
-  if (p0.splits > 1) {
+  if (pp.splits > 1) {
     pq_prof_scope prof(PQP_SPLITK_REDUCE, s);
-    pq_reduce_job none;
-    memset(&none, 0, sizeof(none));
-    const int extra = jobs ? 2 : 0;
-    splitk_reduce_pair_kernel<<<p0.red_blocks + p1.red_blocks + extra, 256, 0, s>>>(
-        p0.splits, p0.red_blocks, p1.red_blocks, M0, N0, (const float*)splitk_ws0, e0, M1, N1, (const float*)splitk_ws1, e1,
-        jobs ? jobs[0] : none, jobs ? jobs[1] : none);
+    splitk_reduce_pair_kernel<<<rb0 + rb1 + (jobs ? 2 : 0), 256, 0, s>>>(pp.splits, rb0, rb1, M0, N0, (const float*)splitk_ws0, e0, M1, N1,
+                                                                        (const float*)splitk_ws1, e1, jobs ? jobs[0] : none,
+                                                                        jobs ? jobs[1] : none);
     PQ_CHECK_LAUNCH("splitk_reduce_pair_kernel");
     if (jobs && jobs_done) *jobs_done = true;
   }
   return PQ_OK;
 }
 
-// Grouped contraction ranges (per-expert weight gradients): with few output tiles per group and few groups the launch is
-// far from a workgroup per CU, so every group's range is cut into up to 8 pieces whose slabs a second launch adds.
-int pq_mode2_splits(int M, int N, int n_groups, int total_k) {
-  if (M <= 0 || N <= 0 || n_groups <= 0) return 1;
-  const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128) * n_groups;
-  long want = 512 / tiles;
-  const long by_len = (long)total_k / n_groups / 256;   // pieces of about 256 contraction indices or more
-  if (want > by_len) want = by_len;
-  if (want > 8) want = 8;
-  return want > 1 ? (int)want : 1;
+// Grouped contraction ranges (per-expert weight gradients): tile and pieces of every group's range (up to 8, of about 256
+// indices or more, whose slabs a second launch adds), by the times above for segments of equal length.
+struct mode2_plan { int bm, splits; };
+static mode2_plan plan_mode2(int M, int N, int n_groups, int total_k) {
+  mode2_plan p{64, 1};
+  if (M <= 0 || N <= 0 || n_groups <= 0) return p;
+  const long len = (total_k + n_groups - 1) / n_groups;
+  double best = 1e30;
+  for (int bm = 64; bm <= 128; bm *= 2) {
+    const long tiles = (long)((M + bm - 1) / bm) * ((N + bm - 1) / bm) * n_groups;
+    for (int sp = 1; sp <= 8; ++sp) {
+      if (sp > 1 && (len / sp < 256 || tiles * sp > 1024)) break;
+      const double t = est_tile(bm, tiles * sp, (len / sp + 63) / 64, false, true) + est_reduce(sp, (double)n_groups * M * N);
+      if (t < best) { best = t; p.bm = bm; p.splits = sp; }
+    }
+  }
+  return p;
 }
 size_t pq_mode2_ws_bytes(int M, int N, int n_groups, int total_k) {
-  const int sp = pq_mode2_splits(M, N, n_groups, total_k);
+  const int sp = plan_mode2(M, N, n_groups, total_k).splits;
   return sp > 1 ? (size_t)sp * n_groups * M * N * sizeof(float) : 0;
 }
 
@@ -2140,37 +2020,40 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
   if (grp.mode) {
     pl.splits = 1;
     pl.kchunk = K > 0 ? K : 1;
-    pl.bm = pl.bn = 128;
-    // wide row groups (experts of several hundred hidden units, Table 1: r = 384): the 256x256 streaming instantiation,
-    // whose loaders clamp a group's last rows like any ragged edge
-    if (grp.mode == 1 && N >= 256 && grp.max_rows >= 256 && K % 64 == 0) pl.bm = pl.bn = 256;
-    // contraction ranges with a plain fp32 output whose groups lie one behind the other: cut the ranges (see above)
-    if (grp.mode == 2 && splitk_ws && epi.out_kind == PQ_OUT_F32 && epi.ldc == N && grp.c_stride == (long)M * N && N % 8 == 0 &&
-        !epi.partials && !epi.dot_comp && !epi.sign_bytes && !epi.maskW && !epi.accumulate && !epi.row_div && !epi.col_div &&
-        epi.m_limit == 0 && epi.n_limit == 0) {
-      const int sp = pq_mode2_splits(M, N, grp.n_groups, K);
-      if (sp > 1) {
-        pl.splits = sp;
+    pl.bm = pl.bn = 64;
+    // contraction ranges: pieces only for a plain fp32 output whose groups lie one behind the other
+    if (grp.mode == 2) {
+      const mode2_plan p2 = plan_mode2(M, N, grp.n_groups, K);
+      pl.bm = pl.bn = p2.bm;
+      if (p2.splits > 1 && splitk_ws && epi.out_kind == PQ_OUT_F32 && epi.ldc == N && grp.c_stride == (long)M * N && N % 8 == 0 &&
+          !epi.partials && !epi.dot_comp && !epi.sign_bytes && !epi.maskW && !epi.accumulate && !epi.row_div && !epi.col_div &&
+          epi.m_limit == 0 && epi.n_limit == 0) {
+        pl.splits = p2.splits;
         pl.red_blocks = (int)(((size_t)grp.n_groups * M * (N / 8) + 255) / 256);
         pl.ws_bytes = pq_mode2_ws_bytes(M, N, grp.n_groups, K);
       }
     }
-    // row groups with a narrow output and a long contraction (expert up/gate projections, their input
-    // gradients): too few tiles to fill the chip, so the contraction is split as for plain GEMMs
-    // (a per-group column divisor is applied in the GEMM's own epilogue only: such products are not split)
-    // (likewise experts of several hundred hidden units on the 256x256 tiles: Table 1's r = 384 gives 99 tiles at 8192 slots)
-    const bool wide_few = pl.bm == 256 && (long)((grp.max_rows + 255) / 256 + grp.n_groups) * ((N + 255) / 256) <= 128 && K % 512 == 0 &&
-                          epi.out_kind == PQ_OUT_BF16 && !epi.accumulate && !epi.row_div;
-    if (grp.mode == 1 && (N <= 128 || wide_few) && K >= 1024 && splitk_ws && !(epi.col_div && grp.coldiv_stride)) {
-      const long tiles = wide_few ? (long)((grp.max_rows + 255) / 256 + grp.n_groups) * ((N + 255) / 256)
-                                  : (long)((grp.max_rows + 127) / 128 + grp.n_groups) * ((N + 127) / 128);
-      long want = tiles > 0 ? 256 / tiles : 1;
-      if (want > 8) want = 8;
-      if (want > 1) {
-        long chunk = (K + want - 1) / want;
-        chunk = (chunk + 255) / 256 * 256;
-        pl.kchunk = (int)chunk;
-        pl.splits = (int)((K + chunk - 1) / chunk);
+    // row groups (expert segments): the tile by the same times (the streaming 256x256 form only on whole steps), the
+    // contraction of a product with few tiles split as for plain GEMMs.  A per-group column divisor is applied in the
+    // GEMM's own epilogue only, so such products are not split.
+    if (grp.mode == 1) {
+      const bool narrow = N <= 128, wide = N >= 256 && K % 512 == 0 && epi.out_kind == PQ_OUT_BF16 && !epi.accumulate && !epi.row_div;
+      // (N <= K: callers size the scratch for eight slabs as wide as the hidden states)
+      const bool may = (narrow || wide) && N <= K && K >= 1024 && splitk_ws && !(epi.col_div && grp.coldiv_stride);
+      const int epb = int8 ? 128 : 64;
+      double best = 1e30;
+      for (int bm = 64; bm <= 256; bm *= 2) {
+        if (bm == 256 && !(N >= 256 && grp.max_rows >= 256 && K % 64 == 0)) continue;
+        const long tiles = ((long)(grp.max_rows + bm - 1) / bm + (grp.n_groups + 1) / 2) * ((N + bm - 1) / bm);
+        for (int want = 1; want <= 8; ++want) {
+          if (want > 1 && (!may || tiles * want > 1024 || (bm == 256 && tiles > 128))) break;
+          const int chunk = want == 1 ? K : ((K + want - 1) / want + 255) / 256 * 256;
+          const int sp = (K + chunk - 1) / chunk;
+          const double t = est_tile(bm, tiles * sp, (chunk + epb - 1) / epb, int8, K % epb == 0) + est_reduce(sp, (double)grp.max_rows * N);
+          if (t < best) { best = t; pl.bm = pl.bn = bm; pl.splits = sp; pl.kchunk = chunk; }
+        }
+      }
+      if (pl.splits > 1) {
         pl.red_blocks = (int)(((size_t)M * (N / 8) + 255) / 256);
         pl.ws_bytes = (size_t)pl.splits * M * N * sizeof(float);
       }
@@ -2182,14 +2065,13 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
   {
     pq_prof_scope prof(prof_label, s);   // the MFMA kernel alone; a split's reduction is timed under its own label
     if (ph2.K2 > 0) {
-      if (pl.splits > 1) return pq_set_error(PQ_ERR_BAD_ARG, "a fused second contraction cannot be combined with a split contraction");
+      if (!pq_plan_fuses(pl)) return pq_set_error(PQ_ERR_BAD_ARG, "a fused second contraction cannot be combined with a split contraction of 256x256 tiles");
       if (ak == PQ_SRC_KC8 && bk == PQ_SRC_BITS8 && ph2.A2.kind == PQ_SRC_KC16 && ph2.B2.kind == PQ_SRC_KC16)
-        return launch_mfma_cfg<true, PQ_SRC_KC8, PQ_SRC_BITS8, PQ_SRC_KC16, PQ_SRC_KC16>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
-      if (ak == PQ_SRC_KC16 && bk == PQ_SRC_BITS16 && ph2.A2.kind == PQ_SRC_KC16 && ph2.B2.kind == PQ_SRC_KS16)
-        return launch_mfma_cfg<false, PQ_SRC_KC16, PQ_SRC_BITS16, PQ_SRC_KC16, PQ_SRC_KS16>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
-      return pq_set_error(PQ_ERR_BAD_ARG, "no fused MFMA kernel for these operand kinds");
-    }
-    if (ak == PQ_SRC_KC8 && bk == PQ_SRC_BITS8) rc = launch_mfma_cfg<true, PQ_SRC_KC8, PQ_SRC_BITS8>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+        rc = launch_mfma_cfg<true, PQ_SRC_KC8, PQ_SRC_BITS8, PQ_SRC_KC16, PQ_SRC_KC16>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+      else if (ak == PQ_SRC_KC16 && bk == PQ_SRC_BITS16 && ph2.A2.kind == PQ_SRC_KC16 && ph2.B2.kind == PQ_SRC_KS16)
+        rc = launch_mfma_cfg<false, PQ_SRC_KC16, PQ_SRC_BITS16, PQ_SRC_KC16, PQ_SRC_KS16>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+      else return pq_set_error(PQ_ERR_BAD_ARG, "no fused MFMA kernel for these operand kinds");
+    } else if (ak == PQ_SRC_KC8 && bk == PQ_SRC_BITS8) rc = launch_mfma_cfg<true, PQ_SRC_KC8, PQ_SRC_BITS8>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
     else if (ak == PQ_SRC_KC8 && bk == PQ_SRC_KC8) rc = launch_mfma_cfg<true, PQ_SRC_KC8, PQ_SRC_KC8>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
     else if (ak == PQ_SRC_KC16 && bk == PQ_SRC_KC16) rc = launch_mfma_cfg<false, PQ_SRC_KC16, PQ_SRC_KC16>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
     else if (ak == PQ_SRC_KC16 && bk == PQ_SRC_KS16) rc = launch_mfma_cfg<false, PQ_SRC_KC16, PQ_SRC_KS16>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
@@ -2201,7 +2083,8 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
   if (pl.splits > 1 && !epi.defer_reduce) {
     pq_prof_scope prof(PQP_SPLITK_REDUCE, s);
     const int Mred = grp.mode == 2 ? grp.n_groups * M : M;   // grouped ranges: the groups' outputs as one matrix
-    if (int8) splitk_reduce_kernel<true><<<pl.red_blocks, 256, 0, s>>>(Mred, N, pl.splits, part, epi);
+    // (with a second contraction the slabs are already floating-point numbers)
+    if (int8 && ph2.K2 == 0) splitk_reduce_kernel<true><<<pl.red_blocks, 256, 0, s>>>(Mred, N, pl.splits, part, epi);
     else splitk_reduce_kernel<false><<<pl.red_blocks, 256, 0, s>>>(Mred, N, pl.splits, part, epi);
     PQ_CHECK_LAUNCH("splitk_reduce_kernel");
   }

@@ -124,7 +124,7 @@ struct pq_phase2 {
 // B + e*b_stride (elements of B's type) -- the per-expert GEMMs of the forward pass;  mode 2: the
 // contraction index runs over [offsets[e], offsets[e+1]) and the result goes to C + e*c_stride
 // (elements of C's type) -- the per-expert weight gradients.  max_rows bounds a segment (launch size).
-// mode 3: two independent GEMMs of the same operand kinds, tile shape, tile count and contraction in one launch;
+// mode 3: two independent GEMMs of the same operand kinds, tile shape and contraction split in one launch;
 // workgroups with blockIdx.z == 1 work on `second` (plain epilogue: C = scale * acc, or raw slabs when split).
 struct pq_gemm_second {
   pq_operand A, B;
@@ -153,10 +153,14 @@ struct pq_gemm_plan {
   size_t ws_bytes;   // scratch for the split slabs
 };
 pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8 = false, bool split_int8 = false);
+// whether a second contraction (pq_phase2) can be fused into a GEMM of this plan
+inline bool pq_plan_fuses(const pq_gemm_plan& pl) { return pl.splits == 1 || pl.bm < 256; }
+struct pq_pair_plan { bool tn; int splits, kchunk; size_t ws0, ws1; };   // scratch of pq_launch_gemm_pair_ks16's two problems
+pq_pair_plan pq_plan_pair(int K, int M0, int N0, int M1, int N1);
 // Scratch a grouped launch over contraction ranges (mode 2; M x N per group, total_k indices over all groups) may use
 size_t pq_mode2_ws_bytes(int M, int N, int n_groups, int total_k);
 // Two bf16 GEMMs with contraction-strided operands on both sides (the rank-r weight gradients dA and dB) in one
-// launch when their plans agree (same tile shape, tile count and contraction split), else one after the other.
+// launch (pq_plan_pair).
 // Both have plain epilogues: C (fp32) = scale * acc.
 // C[M][128] = scale * A B^T for bf16 operands and many rows (the hidden state of the dense high-precision branch
 // and its gradient, Sec. 3.2): one workgroup per 64 rows runs the whole contraction through a six-stage ring of
@@ -171,6 +175,9 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
                              int M1, int N1, const pq_operand& A1, const pq_operand& B1, float* C1, int ldc1, float scale1,
                              hipStream_t s, int prof_label0, int prof_label1, void* splitk_ws0, void* splitk_ws1,
                              const pq_reduce_job* jobs = nullptr, bool* jobs_done = nullptr);   // jobs: two scalar reductions to ride along
+// ---- pq_tile.hip: the 64x64 and 128x128 streaming tiles (pl.bm; the contraction split is the caller's plan) ----
+int pq_launch_tile(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi, hipStream_t s,
+                   float* part, const pq_gemm_group& grp, const pq_phase2& ph2);
 int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B,
                    const pq_epilogue& epi, hipStream_t s, int prof_label = PQP_GEMM_OTHER,
                    void* splitk_ws = nullptr, const pq_gemm_group* group = nullptr,
