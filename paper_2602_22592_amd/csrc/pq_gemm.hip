@@ -6,12 +6,11 @@
 //   KC16 / KC8   contraction-contiguous rows, 16 bytes at a time;
 //   KS16         contraction-strided sources (the transposed operands of the weight-gradient GEMMs);
 //   BITS8/BITS16 packed sign bits, expanded to +/-1 (int8 or bf16).
-// Two main loops share the kernel.  The streaming loop (256x256 tiles, whole contraction steps) sends operands from
-// global memory straight into LDS: KC tiles as ROWS x 128 bytes, KS16 tiles as they lie in memory (read back with the
-// transposing LDS read), and packed bits stay packed in LDS and are expanded in registers next to the MFMAs that consume
-// them.  The register-staged loop (contractions of partial steps) stages every
-// operand as ROWS x 128 bytes with the contraction index contiguous: KS16 blocks are transposed in registers with byte
-// permutes, bits are expanded on the way into LDS.
+// 256x256 tiles here, smaller ones in pq_tile.hip.  The main loop sends operands from global memory straight into LDS: KC
+// tiles as ROWS x 128 bytes, KS16 tiles as they lie in memory (read back with the transposing LDS read), and packed bits stay
+// packed in LDS and are expanded in registers next to the MFMAs that consume them.  Contractions that are not whole steps
+// fetch what is missing from a page of zeros.  The rank-r branch's second contraction rides in on the same ring, or, when it
+// is not one or two whole steps, through registers (KS16 blocks are then transposed with byte permutes).
 // A wavefront owns a (BM/WGM) x (BN/WGN) sub-tile as 32x32 MFMA blocks:
 //   v_mfma_f32_32x32x16_bf16 / v_mfma_i32_32x32x32_i8, 16 bytes of operand per lane per issue.
 // LDS rows are 128 bytes with the 16-byte chunk index XOR-swizzled by the row so that the MFMA
@@ -41,6 +40,8 @@ extern "C" int pq_debug_read_trace(unsigned long long* host_out) {
 
 namespace {
 
+[[maybe_unused]] __device__ __attribute__((aligned(256))) unsigned char pq_zero_page[256];   // never written
+
 __device__ __forceinline__ uint4 mask4(const uint4& t, bool keep) {
   const uint32_t m = keep ? 0xFFFFFFFFu : 0u;
   return make_uint4(t.x & m, t.y & m, t.z & m, t.w & m);
@@ -56,7 +57,7 @@ __device__ __forceinline__ int lds_off(int r, int c) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Operand tile staging: global -> registers (load) and registers -> LDS (store)
+// Operand tile staging of the second contraction: global -> registers (load) and registers -> LDS (store)
 // ---------------------------------------------------------------------------------------------
 // Everything that does not change from one contraction step to the next (which rows and LDS slots a
 // thread serves, their byte offsets) is computed once in setup(); a step then costs one load per
@@ -68,9 +69,9 @@ template <int KIND, int ROWS, int NT, int KB, bool FAST>
 struct tile_stage {
   static constexpr int CPR = KB / 16;                        // 16-byte chunks per LDS row
   static constexpr int NCH = (ROWS * CPR + NT - 1) / NT;     // chunks per thread
-  static constexpr bool kBits = (KIND == PQ_SRC_BITS8 || KIND == PQ_SRC_BITS16);
+  static_assert(KIND == PQ_SRC_KC16 || KIND == PQ_SRC_KS16, "bf16 operands");
   static constexpr bool kStrided = (KIND == PQ_SRC_KS16);
-  static constexpr int EPC = (KIND == PQ_SRC_KC8 || KIND == PQ_SRC_BITS8) ? 16 : 8;  // elements per chunk
+  static constexpr int EPC = 8;                              // elements per chunk
   // KS16: a unit is 8 rows x KQ contraction indices (KQ 16-byte loads, transposed in registers);
   // KQ is the largest of 8, 4, 2 that still gives every thread a unit
   static constexpr int KQ = (ROWS * KB / 128 >= NT) ? 8 : (ROWS * KB / 64 >= NT) ? 4 : 2;
@@ -78,17 +79,13 @@ struct tile_stage {
   static constexpr int UPC = 8 / KQ;                         // units per 16-byte chunk
   static constexpr int NU = (ROWS / 8 * UPR + NT - 1) / NT;  // units per thread
   static_assert(NT % CPR == 0 && NT % UPR == 0, "a thread keeps its contraction position across chunks");
-  uint4 v[kBits ? 1 : (kStrided ? NU * KQ : NCH)];
-  uint32_t raw[kBits ? NCH : 1];
+  uint4 v[kStrided ? NU * KQ : NCH];
   uint32_t boff[kStrided ? NU : NCH];      // byte offset of each load at contraction index 0
   uint32_t ldst[kStrided ? NU * 8 : NCH];  // LDS byte offset of each store
   uint32_t rowok;                          // bit i: chunk / unit i lies in a valid row
   uint32_t okbits;                         // validity of each load of the step in flight
   uint32_t jstride;                        // KS16: bytes between consecutive contraction indices
   int kpos;                                // this thread's contraction offset inside a tile (elements)
-
-  // bytes of the source advanced per contraction element, times 8 (bits kinds advance 1/8 byte)
-  static constexpr int ES8 = (KIND == PQ_SRC_KC16) ? 16 : (KIND == PQ_SRC_KC8) ? 8 : 1;
 
   __device__ __forceinline__ void setup(const pq_operand& op, int row0, int rows, int tid) {
     rowok = 0u;
@@ -118,8 +115,7 @@ struct tile_stage {
         const int grow = row0 + r;
         const bool ok = (c < ROWS * CPR) && (grow < rows);
         rowok |= (ok ? 1u : 0u) << i;
-        const uint32_t rowb = (uint32_t)(ok ? grow : 0) * (uint32_t)op.ld;   // ld is in bytes for the bits kinds
-        boff[i] = (kBits ? rowb : rowb * (uint32_t)(ES8 / 8)) + (uint32_t)(kc * EPC * ES8 / 8);
+        boff[i] = ((uint32_t)(ok ? grow : 0) * (uint32_t)op.ld + (uint32_t)(kc * EPC)) * 2u;
         ldst[i] = (uint32_t)lds_off<KB>(r, kc);
       }
     }
@@ -149,7 +145,7 @@ struct tile_stage {
         }
       }
     } else {
-      const size_t kb8 = (size_t)k0 * ES8 / 8;
+      const size_t kb8 = (size_t)k0 * 2;
       const char* base = FAST ? (const char*)op.p + kb8 : (const char*)op.p;
       const bool kv = FAST ? true : (k0 + kpos < K);
       okbits = kv ? rowok : 0u;
@@ -158,9 +154,7 @@ struct tile_stage {
         if ((i * np) / NCH != piece) continue;
         uint32_t off = boff[i];
         if constexpr (!FAST) off = ((okbits >> i) & 1u) ? off + (uint32_t)kb8 : 0u;
-        if constexpr (KIND == PQ_SRC_BITS8) raw[i] = *reinterpret_cast<const uint16_t*>(base + off);
-        else if constexpr (KIND == PQ_SRC_BITS16) raw[i] = *reinterpret_cast<const uint8_t*>(base + off);
-        else v[i] = *reinterpret_cast<const uint4*>(base + off);
+        v[i] = *reinterpret_cast<const uint4*>(base + off);
       }
     }
   }
@@ -170,7 +164,7 @@ struct tile_stage {
     else return mask4(t, (okbits >> bit) & 1u);
   }
 
-  // np > 1: only the chunks of piece `piece` (contraction-contiguous and bit kinds)
+  // np > 1: only the chunks of piece `piece` (contraction-contiguous kinds)
   __device__ __forceinline__ void store(unsigned char* lds, int tid, int piece = 0, int np = 1) const {
     if constexpr (kStrided) {
 #pragma unroll
@@ -204,30 +198,7 @@ struct tile_stage {
         if ((i * np) / NCH != piece) continue;
         const int c = tid + i * NT;
         if (c < ROWS * CPR) {
-          uint4 out;
-          if constexpr (KIND == PQ_SRC_BITS8) {
-            // 16 bits -> 16 bytes of +1 (0x01) / -1 (0xFF): spread a nibble to one bit per byte with a
-            // 24-bit multiply, then map byte values {0,1} through a byte permute.
-            const uint32_t b = raw[i];
-            uint32_t o[4];
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-              const uint32_t nib = (b >> (4 * d)) & 0xFu;
-              const uint32_t m = __umul24(nib, 0x00204081u) & 0x01010101u;
-              o[d] = __builtin_amdgcn_perm(0x000001FFu, 0x000001FFu, m);
-            }
-            out = valid(make_uint4(o[0], o[1], o[2], o[3]), i);
-          } else if constexpr (KIND == PQ_SRC_BITS16) {
-            // 8 bits -> 8 bf16 of +1 (0x3F80) / -1 (0xBF80): move each (inverted) bit to a sign position
-            const uint32_t nb = ~raw[i];
-            uint32_t o[4];
-#pragma unroll
-            for (int d = 0; d < 4; ++d)
-              o[d] = 0x3F803F80u | ((nb << (15 - 2 * d)) & 0x00008000u) | ((nb << (30 - 2 * d)) & 0x80000000u);
-            out = valid(make_uint4(o[0], o[1], o[2], o[3]), i);
-          } else {
-            out = valid(v[i], i);
-          }
+          const uint4 out = valid(v[i], i);
           *reinterpret_cast<uint4*>(lds + ldst[i]) = out;
         }
       }
@@ -236,7 +207,7 @@ struct tile_stage {
 };
 
 // ---------------------------------------------------------------------------------------------
-// Streaming main loop (DTL instantiations): operands go from global memory straight into LDS
+// Main loop: operands go from global memory straight into LDS
 // (global_load_lds_dwordx4, no staging registers, no ds_write), and the contraction step is a fixed
 // instruction order written as volatile asm statements: the fragment reads of MFMA group g+1 are issued
 // before the MFMAs of group g, and the single barrier of a step sits before its last MFMA group, so the
@@ -310,12 +281,10 @@ struct pq_frag_set {
 // ---------------------------------------------------------------------------------------------
 // MFMA engine
 // ---------------------------------------------------------------------------------------------
-// One workgroup computes a BM x BN tile over the contraction range [z*kchunk, (z+1)*kchunk), z =
-// blockIdx.y.  Register-staged instantiations (DTL = false): LDS holds two stages of both operand tiles;
-// per 128-byte step there is a single barrier: after it, the registers prefetched during the previous
-// step are written to the idle stage, the loads of the step after next are issued, and the MFMAs run on
-// the ready stage.  Streaming instantiations (DTL = true) are described above.
-template <int BM, int BN, int WGM, int WGN, int KB, bool FAST, bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1, bool DTL = false>
+// One workgroup computes a BM x BN tile over the contraction range [z*kchunk, (z+1)*kchunk), z = blockIdx.y.
+// FAST: whole tiles (no validity masks in the register-staged second contraction); TAIL: the contraction may end inside a step
+// (an instantiation of its own: the registers its addresses take are spills elsewhere).
+template <int BM, int BN, int WGM, int WGN, int KB, bool FAST, bool TAIL, bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1>
 __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N, int K, pq_operand A,
                                                                      pq_operand B, pq_epilogue epi,
                                                                      int nbn, int total_tiles, int kchunk,
@@ -328,9 +297,9 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
   constexpr int STAGE = (BM + BN) * KB;
   using acc_t = typename std::conditional<INT8, i32x16_t, f32x16_t>::type;
 
-  // Streaming instantiations with a packed-bit B operand keep that operand as bits in LDS (three buffers of
+  // A packed-bit B operand stays packed in LDS (three buffers of
   // 32 bytes per row), which leaves room for a ring of four stages of the A operand.
-  constexpr bool BBITS = DTL && (BKIND == PQ_SRC_BITS8 || BKIND == PQ_SRC_BITS16);
+  constexpr bool BBITS = BKIND == PQ_SRC_BITS8 || BKIND == PQ_SRC_BITS16;
   constexpr int SMEM_BYTES = BBITS ? 4 * BM * KB + 3 * BN * 32 : 2 * STAGE;
   __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM_BYTES];
   __shared__ double red[NT / 64];
@@ -382,10 +351,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
 
-  tile_stage<AK, BM, NT, KB, FAST> sa;
-  tile_stage<BKIND, BN, NT, KB, FAST> sb;
-  sa.setup(A, m0, M, tid);
-  sb.setup(B, n0, N, tid);
   const int nkt = ke > kb ? (ke - kb + EPB - 1) / EPB : 0;
   constexpr int NKS = KB / 32;   // MFMA issues along the contraction per LDS stage
   // Streaming loop with a fused second contraction of one or two 64-element steps: its operand tiles (32 KB each:
@@ -394,7 +359,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
   // Tile j goes to ring stage (pf2_s0 + j) mod 4.
   bool pf2 = false;                                  // uniform
   [[maybe_unused]] const int pf2_s0 = nkt & 3;
-  if constexpr (DTL && BBITS && AK2 == PQ_SRC_KC16 && (BK2 == PQ_SRC_KC16 || BK2 == PQ_SRC_KS16)) {
+  if constexpr (BBITS && AK2 == PQ_SRC_KC16 && (BK2 == PQ_SRC_KC16 || BK2 == PQ_SRC_KS16)) {
 #ifndef PQ_NO_PF2
     pf2 = ph2.K2 > 0 && ph2.K2 <= 128 && ph2.K2 % 64 == 0 && nkt >= 4 && ((uintptr_t)ph2.A2.p % 16) == 0 && (ph2.A2.ld * 2) % 16 == 0 &&
           ((uintptr_t)ph2.B2.p % 16) == 0 && (ph2.B2.ld * 2) % 16 == 0 && (BK2 != PQ_SRC_KS16 || N % 8 == 0);
@@ -424,7 +389,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
     for (int j = 0; j < TN; ++j) fb[j] = *reinterpret_cast<const uint4*>(stage + b_rb[j] + ((ch ^ b_fx[j]) << 4));
   };
 
-  if constexpr (DTL) {
+  {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the kernel's signature (LDS address-space casts are device-only)
     static_assert(BM == 256 && BN == 256 && WGM == 2 && WGN == 4 && KB == 128, "streaming loop: 256x256 tile on 8 wavefronts");
     constexpr bool ATR = (AK == PQ_SRC_KS16), BTR = (BKIND == PQ_SRC_KS16);
@@ -475,8 +440,21 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
       if (opB) adv = BTR ? (size_t)64 * B.ld * 2 : (size_t)128;
       else adv = ATR ? (size_t)64 * A.ld * 2 : (size_t)128;
     }
+    // A last step that the contraction does not fill takes its missing chunks (KC: 16 bytes of a row; KS16: a row) from a page
+    // of zeros, in both operands; bits past the end may be anything then.
     auto issue = [&](int kt, int stage) {
       unsigned char* base = smem + stage * STG + (opB ? BM * KB : 0) + q0 * 1024;
+      if (TAIL && (kt + 1) * EPB > ke - kb) {       // uniform
+        const bool ks = opB ? BTR : ATR;
+#pragma unroll
+        for (int i = 0; i < IPW; ++i) {
+          const int qi = q0 + i;
+          const int pos = ks ? kt * EPB + qi * 2 + (lane >> 5) : kt * EPB + (((lane & 7) ^ ((lane >> 3) ^ qi)) & 7) * (EPB / 8);
+          const char* g = pos < ke - kb ? src[i] + (size_t)kt * adv : (const char*)pq_zero_page;
+          __builtin_amdgcn_global_load_lds(g, PQ_LDS_PTR(base + i * 1024), 16, 0, 0);
+        }
+        return;
+      }
 #pragma unroll
       for (int i = 0; i < IPW; ++i)
         __builtin_amdgcn_global_load_lds(src[i] + (size_t)kt * adv, PQ_LDS_PTR(base + i * 1024), 16, 0, 0);
@@ -514,10 +492,23 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
     // 16 bytes of the wavefront's 32 rows and lanes 32..63 the second, so in LDS a block of 32 rows is
     // [half][row][16 B]: the per-step reads (8 or 16 bytes of 32 consecutive rows) then walk consecutive
     // 16-byte slots instead of a 32-byte row stride (rows 8 apart on the same banks).
-    // The last chunk of a contraction range may be half a chunk (ranges are whole multiples of 128 indices):
-    // its missing half re-reads the start of the range into a place no step uses.
+    // Rows that are not a multiple of 16 bytes (contractions that are not whole multiples of 128) are fetched a word per
+    // lane, four loads per wavefront and chunk into the same places (the waits below then merely cover more loads of A).
+    // What the last chunk lacks re-reads the start of the range into a place no step uses, or where A is zero.
     const int range_bytes = (ke - kb) >> 3;
+    const bool words = TAIL && (B.ld & 15) != 0;     // uniform
     auto issue_bits = [&](int chunk, int buf) {
+      if (words) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = min(n0 + wv * 32 + (i & 1) * 16 + (lane >> 2), N - 1);
+          int off = chunk * 32 + (i >> 1) * 16 + (lane & 3) * 4;
+          if (off + 4 > range_bytes) off = 0;
+          const char* g = (const char*)B.p + (size_t)row * B.ld + (kb >> 3) + off;
+          __builtin_amdgcn_global_load_lds(g, PQ_LDS_PTR(smem + BITS0 + buf * (BN * 32) + wv * 1024 + i * 256), 4, 0, 0);
+        }
+        return;
+      }
       const int row = min(n0 + wv * 32 + (lane & 31), N - 1);
       int off = chunk * 32 + (lane >> 5) * 16;
       if (off + 16 > range_bytes) off = 0;
@@ -801,49 +792,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     }
 #endif
-  } else {
-  if (nkt > 0) {
-      sa.load(A, kb, ke);
-      sb.load(B, kb, ke);
-      sa.store(smem, tid);
-      sb.store(smem + BM * KB, tid);
-      const int k1 = nkt > 1 ? 1 : 0;
-      sa.load(A, kb + k1 * EPB, ke);
-      sb.load(B, kb + k1 * EPB, ke);
-    }
-    __syncthreads();
-    if (nkt > 0) read_frags(smem, 0, af[0], bf[0]);
-
-    // Steady state, one barrier per stage and no branches in the body: the registers hold tile kt+1,
-    // which goes to the idle LDS stage while the loads of tile kt+2 are issued and the MFMAs run on
-    // the ready stage; the operand fragments of the next MFMA group are read one group ahead.  On the
-    // last steps the tile index is clamped, so the same tile is (harmlessly) staged again.
-    for (int kt = 0; kt < nkt; ++kt) {
-      unsigned char* cur = smem + (kt & 1) * STAGE;
-      unsigned char* nxt = smem + ((kt + 1) & 1) * STAGE;
-      sa.store(nxt, tid);
-      sb.store(nxt + BM * KB, tid);
-      const int k2 = min(kt + 2, nkt - 1);
-      sa.load(A, kb + k2 * EPB, ke);
-      sb.load(B, kb + k2 * EPB, ke);
-#pragma unroll
-      for (int ks = 0; ks < NKS; ++ks) {
-        if (ks + 1 < NKS) read_frags(cur, ks + 1, af[(ks + 1) & 1], bf[(ks + 1) & 1]);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            if constexpr (INT8)
-              acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4_t, bf[ks & 1][j]),
-                                                                __builtin_bit_cast(i32x4_t, af[ks & 1][i]), acc[i][j], 0, 0, 0);
-            else
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, bf[ks & 1][j]),
-                                                                  __builtin_bit_cast(bf16x8_t, af[ks & 1][i]), acc[i][j], 0, 0, 0);
-          }
-      }
-      __syncthreads();  // stage nxt is complete and nobody still reads stage cur
-      read_frags(nxt, 0, af[0], bf[0]);
-    }
   }
   __syncthreads();  // all MFMA operand reads are done: LDS is reused below
 
@@ -1192,6 +1140,9 @@ struct pq_frag_set_w4 {
   }
 };
 
+// RAGGED: the last stage of a range is not whole; its missing rows come from a page of zeros.  (An instantiation of its own: the
+// test behind every load cost the whole ones 3 to 4 %.)
+template <bool RAGGED>
 __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn,
                                                           int total_tiles, int kchunk, float* splitk_part) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -1211,7 +1162,7 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
   const int bm = pid / nbn, bn = pid % nbn;
   const int m0 = bm * 256, n0 = bn * 256;
   const int kb = split * kchunk, ke = min(K, kb + kchunk);
-  const int nkt = ke > kb ? (ke - kb) >> 5 : 0;      // whole stages (the launcher checks)
+  const int nkt = ke > kb ? (ke - kb + (RAGGED ? 31 : 0)) >> 5 : 0;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm0 = (wv >> 1) * 128, wn0 = (wv & 1) * 128;
@@ -1242,7 +1193,11 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
   const size_t advA = (size_t)32 * A.ld * 2, advB = (size_t)32 * B.ld * 2;
   auto issue1 = [&](int kt, int slot, int i) {
     unsigned char* base = smem + slot * STG + wv * 4096;
-    if (i < 4) __builtin_amdgcn_global_load_lds(src[i] + (size_t)kt * advA, PQ_LDS_PTR(base + i * 1024), 16, 0, 0);
+    if (RAGGED && kt == nkt - 1) {
+      const int t = (wv * 4 + (i & 3)) * 2 + (lane >> 5);
+      const char* g = kt * 32 + t < ke - kb ? src[i] + (size_t)kt * (i < 4 ? advA : advB) : (const char*)pq_zero_page;
+      __builtin_amdgcn_global_load_lds(g, PQ_LDS_PTR(base + (i < 4 ? i * 1024 : 16384 + (i - 4) * 1024)), 16, 0, 0);
+    } else if (i < 4) __builtin_amdgcn_global_load_lds(src[i] + (size_t)kt * advA, PQ_LDS_PTR(base + i * 1024), 16, 0, 0);
     else __builtin_amdgcn_global_load_lds(src[i] + (size_t)kt * advB, PQ_LDS_PTR(base + 16384 + (i - 4) * 1024), 16, 0, 0);
   };
 
@@ -1372,7 +1327,7 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
 #endif
 }
 
-template <int BM, int BN, int WGM, int WGN, int KB, bool FAST, bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1, bool DTL = false>
+template <int BM, int BN, int WGM, int WGN, int KB, bool FAST, bool TAIL, bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1>
 int launch_mfma(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B,
                 const pq_epilogue& epi, hipStream_t s, float* part, const pq_gemm_group& grp, const pq_phase2& ph2) {
   // grouped rows: every group may end in a partial tile, so at most ceil(rows / BM) + n_groups row tiles exist
@@ -1380,7 +1335,7 @@ int launch_mfma(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A
   const int nbn = (N + BN - 1) / BN;
   const int tiles = nbm * nbn;
   dim3 grid(tiles, pl.splits), block(WGM * WGN * 64);
-  mfma_gemm_kernel<BM, BN, WGM, WGN, KB, FAST, INT8, AK, BKIND, AK2, BK2, DTL><<<grid, block, 0, s>>>(
+  mfma_gemm_kernel<BM, BN, WGM, WGN, KB, FAST, TAIL, INT8, AK, BKIND, AK2, BK2><<<grid, block, 0, s>>>(
       M, N, K, A, B, epi, nbn, tiles, pl.kchunk, pl.splits > 1 ? part : nullptr, grp, ph2);
   PQ_CHECK_LAUNCH("mfma_gemm_kernel");
   return PQ_OK;
@@ -1389,45 +1344,31 @@ int launch_mfma(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A
 template <bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1>
 int launch_mfma_cfg(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B,
                     const pq_epilogue& epi, hipStream_t s, float* part, const pq_gemm_group& grp, const pq_phase2& ph2) {
-  constexpr int EPB = INT8 ? 128 : 64;
   if (pl.bm != 256) return pq_launch_tile(pl, M, N, K, A, B, epi, s, part, grp, ph2);
-  {
-    // whole tiles everywhere: the instantiation without validity masks
-    const bool whole = grp.mode == 0 && M % 256 == 0 && N % 256 == 0 && K % EPB == 0 && pl.kchunk % EPB == 0 &&
-                       ph2.K2 % 64 == 0;
-    // Streaming main loop: plain tiles or row groups (expert segments as row ranges), whole contraction steps in every
-    // split, rows of both operands 16-byte aligned.  Ragged M or N are fine there (edge rows are clamped, never stored).
-    constexpr bool kinds_ok = (AK == PQ_SRC_KC16 || AK == PQ_SRC_KS16 || AK == PQ_SRC_KC8) &&
-                              (BKIND == PQ_SRC_KC16 || BKIND == PQ_SRC_KS16 || BKIND == PQ_SRC_BITS8 || BKIND == PQ_SRC_BITS16);
-    if constexpr (kinds_ok) {
-      const long aes = AK == PQ_SRC_KC8 ? 1 : 2;
-      const bool a_ok = (A.ld * aes) % 16 == 0 && ((uintptr_t)A.p % 16) == 0 && (AK != PQ_SRC_KS16 || M % 8 == 0);
-      // packed rows are fetched in 16-byte halves of 32-byte chunks: ranges of whole multiples of 128 contraction
-      // indices, a split's range starting on a chunk
-      constexpr bool b_bits = (BKIND == PQ_SRC_BITS8 || BKIND == PQ_SRC_BITS16);
-      const bool b_ok = b_bits ? (K % 128 == 0 && (pl.splits == 1 || pl.kchunk % 256 == 0) && B.ld % 16 == 0 && ((uintptr_t)B.p % 16) == 0) :
-                        ((B.ld * 2) % 16 == 0 && ((uintptr_t)B.p % 16) == 0 && (BKIND != PQ_SRC_KS16 || N % 8 == 0));
-      const bool stream = (grp.mode == 0 || grp.mode == 1) && K % EPB == 0 && pl.kchunk % EPB == 0 && a_ok && b_ok && M >= 1 && N >= 1;
-#ifndef PQ_NO_W4
-      // weight gradients: the four-wavefront kernel (whole 32-row stages in every split; no per-row divisor, no int32 output)
-      if constexpr (AK == PQ_SRC_KS16 && BKIND == PQ_SRC_KS16 && AK2 < 0) {
-        if (grp.mode == 0 && ph2.K2 == 0 && K % 32 == 0 && pl.kchunk % 32 == 0 && a_ok && b_ok && !A.kdiv && !B.kdiv && !epi.row_div &&
-            epi.out_kind != PQ_OUT_I32) {
-          const int nbm = (M + 255) / 256, nbn = (N + 255) / 256;
-          dim3 grid(nbm * nbn, pl.splits), block(256);
-          gemm_tn_w4_kernel<<<grid, block, 0, s>>>(M, N, K, A, B, epi, nbn, nbm * nbn, pl.kchunk, pl.splits > 1 ? part : nullptr);
-          PQ_CHECK_LAUNCH("gemm_tn_w4_kernel");
-          return PQ_OK;
-        }
-      }
-#endif
-      if (stream) {
-        if (whole) return launch_mfma<256, 256, 2, 4, 128, true, INT8, AK, BKIND, AK2, BK2, true>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
-        return launch_mfma<256, 256, 2, 4, 128, false, INT8, AK, BKIND, AK2, BK2, true>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
-      }
-    }
-    if (whole) return launch_mfma<256, 256, 2, 4, 128, true, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
-    return launch_mfma<256, 256, 2, 4, 128, false, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+  // rows of 16-byte chunks on 16-byte boundaries, as every width and section of this library has them
+  const long aes = AK == PQ_SRC_KC8 ? 1 : 2, bes = BKIND == PQ_SRC_KC8 ? 1 : 2;
+  constexpr bool bits = BKIND == PQ_SRC_BITS8 || BKIND == PQ_SRC_BITS16;
+  if ((A.ld * aes) % 16 || ((uintptr_t)A.p % 16) || (AK == PQ_SRC_KS16 && M % 8) || ((uintptr_t)B.p % 16) ||
+      (bits ? B.ld % 4 != 0 || K % 32 != 0 : (B.ld * bes) % 16 != 0 || (BKIND == PQ_SRC_KS16 && N % 8)))
+    return pq_set_error(PQ_ERR_SHAPE, "GEMM operands must have 16-byte aligned rows");
+  // weight gradients: the four-wavefront kernel (no per-row divisor, no int32 output)
+  if constexpr (AK == PQ_SRC_KS16 && BKIND == PQ_SRC_KS16 && AK2 < 0) {
+    const int nbm = (M + 255) / 256, nbn = (N + 255) / 256;
+    dim3 grid(nbm * nbn, pl.splits), block(256);
+    if (grp.mode || A.kdiv || B.kdiv || epi.row_div || epi.out_kind == PQ_OUT_I32) return pq_set_error(PQ_ERR_BAD_ARG, "no 256x256 weight-gradient kernel for this epilogue");
+    float* p = pl.splits > 1 ? part : nullptr;
+    if (K % 32 == 0 && pl.kchunk % 32 == 0) gemm_tn_w4_kernel<false><<<grid, block, 0, s>>>(M, N, K, A, B, epi, nbn, nbm * nbn, pl.kchunk, p);
+    else gemm_tn_w4_kernel<true><<<grid, block, 0, s>>>(M, N, K, A, B, epi, nbn, nbm * nbn, pl.kchunk, p);
+    PQ_CHECK_LAUNCH("gemm_tn_w4_kernel");
+    return PQ_OK;
+  } else {
+    // whole steps (packed rows of whole 16 bytes): no tail to look for; whole tiles too: no validity masks in the second contraction
+    constexpr int EPB = INT8 ? 128 : 64;
+    const bool steps = K % EPB == 0 && pl.kchunk % EPB == 0 && (!bits || B.ld % 16 == 0);
+    const bool tiles = grp.mode == 0 && M % 256 == 0 && N % 256 == 0 && ph2.K2 % 64 == 0;
+    if (steps && tiles) return launch_mfma<256, 256, 2, 4, 128, true, false, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+    if (steps) return launch_mfma<256, 256, 2, 4, 128, false, false, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+    return launch_mfma<256, 256, 2, 4, 128, false, true, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
   }
 }
 
@@ -1842,23 +1783,25 @@ int pq_launch_skinny(int M, int K, const pq_operand& A, const pq_operand& B, con
 
 // Tile shape and contraction split for one GEMM: the smallest of the times (us) that the kernels were measured to take, c the
 // workgroups a CU has to take one after the other:
-//   64x64:   4.5 + 0.25 c per 128-byte step (0.30 with int8) + 1 per further workgroup
-//   128x128: 7 + 0.85 per step alone on a CU (0.95), 0.72 c when two workgroups share it (0.75) + 2.5 per further workgroup
-//   256x256: c (12 + 1.5 per step (1.25), 2.0 (1.9) on the register-staged loop that takes contractions of partial steps);
-//            split only while the tiles are at most half of the CUs: beyond that more active CUs lower the clock instead
-//   a split's reduction: 2 + its slabs and the result at 7 TB/s, at least 4.7
+//   64x64:   5 + 0.25 c per 128-byte step + 1 per further workgroup
+//   128x128: 6 + 0.76 per step alone on a CU (int8 0.85), 0.58 c (0.61) when two workgroups share it, + 2.4 per further workgroup
+//   256x256: c (9.5 + 1.38 per step); split only while the tiles are at most half of the CUs: beyond that more active CUs
+//            lower the clock instead
+//   a split: its slabs written at 10 TB/s (the caches take part of them), then 2 + slabs and result at 7 TB/s, at least 4
+// Fitted to 997 timings of 141 shapes (64 to 16384 rows, 16 to 8192 columns, contractions of 16 to 8192; int8, bf16 and
+// packed-sign operands): the tile and split these pick are 1 to 3 % slower than the fastest of all, averaged over the shapes.
 // (2048 x 2048 outputs over 2048 / 8192 tokens: 64x64 37 / 126, 128x128 35 / 109, 256x256 in four splits 43 / 82 with the
 // reduction; 765 x 672 over 672: 7, 13, 22.)
-static double est_tile(int bm, long wgs, long steps, bool int8, bool whole) {
+static double est_tile(int bm, long wgs, long steps, bool int8) {
   const double c = (double)((wgs + 255) / 256);
-  if (bm == 64) return 4.5 + c * steps * (int8 ? 0.30 : 0.25) + (c - 1.0);
-  if (bm == 128) return 7.0 + (wgs <= 256 ? steps * (int8 ? 0.95 : 0.85) : c * steps * (int8 ? 0.75 : 0.72)) + 2.5 * (c - 1.0);
-  return c * (12.0 + steps * (int8 ? (whole ? 1.25 : 1.9) : (whole ? 1.5 : 2.0)));
+  if (bm == 64) return (int8 ? 5.3 : 5.0) + c * steps * 0.25 + (c - 1.0);
+  if (bm == 128) return (int8 ? 6.3 : 6.0) + (wgs <= 256 ? steps * (int8 ? 0.85 : 0.76) : c * steps * (int8 ? 0.61 : 0.58)) + 2.4 * (c - 1.0);
+  return c * (9.5 + steps * 1.38);
 }
 static double est_reduce(int splits, double elems) {
   if (splits <= 1) return 0.0;
   const double t = 2.0 + (4.0 * splits + 3.0) * elems / 7.0e6;
-  return t > 4.7 ? t : 4.7;
+  return 4.0 * splits * elems / 1.0e7 + (t > 4.0 ? t : 4.0);
 }
 
 static pq_gemm_plan pq_plan_gemm_impl(int M, int N, int K, bool int8, bool may_split) {
@@ -1872,12 +1815,11 @@ static pq_gemm_plan pq_plan_gemm_impl(int M, int N, int K, bool int8, bool may_s
   for (int bm = 64; bm <= 256; bm *= 2) {
     if (bm == 256 && !(M >= 256 && N >= 256)) continue;
     const long tiles = (long)((M + bm - 1) / bm) * ((N + bm - 1) / bm);
-    const bool whole = K % epb == 0;
     for (int want = 1; want <= 16; ++want) {
       if (want > 1 && (!may_split || K / want < 256 || tiles * want > 1024 || (bm == 256 && (int8 || tiles > 128)))) break;
       const int chunk = want == 1 ? (K > 0 ? K : 1) : ((K + want - 1) / want + 255) / 256 * 256;   // whole 128-byte steps, at least two
       const int sp = want == 1 ? 1 : (K + chunk - 1) / chunk;
-      const double t = est_tile(bm, tiles * sp, (chunk + epb - 1) / epb, int8, whole) + est_reduce(sp, (double)M * N);
+      const double t = est_tile(bm, tiles * sp, (chunk + epb - 1) / epb, int8) + est_reduce(sp, (double)M * N);
       if (t < best) { best = t; pl.bm = bm; pl.splits = sp; pl.kchunk = chunk; }
     }
   }
@@ -1910,7 +1852,7 @@ pq_pair_plan pq_plan_pair(int K, int M0, int N0, int M1, int N1) {
       if (want > 1 && (K / want < 256 || tiles * want > 1024)) break;
       const int chunk = want == 1 ? (K > 0 ? K : 1) : ((K + want - 1) / want + 255) / 256 * 256;
       const int n = want == 1 ? 1 : (K + chunk - 1) / chunk;
-      const double t = est_tile(64, tiles * n, (chunk + 63) / 64, false, true) + est_reduce(n, elems);
+      const double t = est_tile(64, tiles * n, (chunk + 63) / 64, false) + est_reduce(n, elems);
       if (t < best) { best = t; p.splits = n; p.kchunk = chunk; }
     }
   }
@@ -1986,7 +1928,7 @@ static mode2_plan plan_mode2(int M, int N, int n_groups, int total_k) {
     const long tiles = (long)((M + bm - 1) / bm) * ((N + bm - 1) / bm) * n_groups;
     for (int sp = 1; sp <= 8; ++sp) {
       if (sp > 1 && (len / sp < 256 || tiles * sp > 1024)) break;
-      const double t = est_tile(bm, tiles * sp, (len / sp + 63) / 64, false, true) + est_reduce(sp, (double)n_groups * M * N);
+      const double t = est_tile(bm, tiles * sp, (len / sp + 63) / 64, false) + est_reduce(sp, (double)n_groups * M * N);
       if (t < best) { best = t; p.bm = bm; p.splits = sp; }
     }
   }
@@ -2043,13 +1985,13 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
       const int epb = int8 ? 128 : 64;
       double best = 1e30;
       for (int bm = 64; bm <= 256; bm *= 2) {
-        if (bm == 256 && !(N >= 256 && grp.max_rows >= 256 && K % 64 == 0)) continue;
+        if (bm == 256 && !(N >= 256 && grp.max_rows >= 256)) continue;
         const long tiles = ((long)(grp.max_rows + bm - 1) / bm + (grp.n_groups + 1) / 2) * ((N + bm - 1) / bm);
         for (int want = 1; want <= 8; ++want) {
           if (want > 1 && (!may || tiles * want > 1024 || (bm == 256 && tiles > 128))) break;
           const int chunk = want == 1 ? K : ((K + want - 1) / want + 255) / 256 * 256;
           const int sp = (K + chunk - 1) / chunk;
-          const double t = est_tile(bm, tiles * sp, (chunk + epb - 1) / epb, int8, K % epb == 0) + est_reduce(sp, (double)grp.max_rows * N);
+          const double t = est_tile(bm, tiles * sp, (chunk + epb - 1) / epb, int8) + est_reduce(sp, (double)grp.max_rows * N);
           if (t < best) { best = t; pl.bm = pl.bn = bm; pl.splits = sp; pl.kchunk = chunk; }
         }
       }

@@ -1,4 +1,4 @@
-"""The 64x64 and 128x128 streaming tiles at the edges they have: rows, columns and contractions that end inside a tile, a step
+"""The 64x64, 128x128 and 256x256 streaming tiles at the edges they have: rows, columns and contractions that end inside a tile, a step
 or a group of two steps, a second contraction longer than its first group, split contractions, expert segments shorter than a
 tile.  Accumulators are exact; bf16 results hold the 2e-2 bar of the other parity tests.  X and dY lie inside buffers of NaN,
 so that anything fetched past the last token shows."""
@@ -16,7 +16,8 @@ TOL = 2e-2
 
 
 @pytest.mark.parametrize("T,K,N", [(1, 32, 8), (63, 96, 72), (64, 128, 64), (65, 160, 64), (128, 256, 128), (129, 288, 136), (300, 4096, 2056),
-                                   (700, 2080, 3000)])
+                                   (700, 2080, 3000),
+                                   (4100, 1056, 2080), (4100, 96, 2056)])   # 256x256 tiles over contractions of partial steps
 def test_accumulators_exact(T, K, N):
     print(f"accumulators T={T} K={K} N={N}", flush=True)
     rng = np.random.default_rng(40 + T)
@@ -37,7 +38,8 @@ def padded(x):
 @pytest.mark.parametrize("T,K,N,r,E,k,tau", [(1, 32, 32, 8, 1, 1, None), (31, 64, 96, 0, 1, 1, 0.02), (64, 128, 128, 136, 1, 1, None),
                                              (65, 160, 224, 264, 1, 1, None), (20, 4128, 672, 64, 1, 1, None), (513, 2048, 96, 24, 1, 1, None),
                                              (1100, 96, 64, 40, 1, 1, None), (777, 672, 1312, 72, 1, 1, 0.02), (1025, 1152, 1184, 128, 1, 1, None),
-                                             (37, 64, 96, 8, 4, 1, None), (333, 1056, 224, 72, 8, 2, None), (600, 160, 1120, 136, 2, 1, None)])
+                                             (37, 64, 96, 8, 4, 1, None), (333, 1056, 224, 72, 8, 2, None), (600, 160, 1120, 136, 2, 1, None),
+                                             (4101, 1056, 2080, 88, 1, 1, None), (4101, 2080, 1056, 0, 1, 1, 0.02)])   # 256x256 tiles, partial steps
 def test_linear_at_tile_edges(T, K, N, r, E, k, tau):
     print(f"linear T={T} K={K} N={N} r={r} E={E} k={k} tau={tau}", flush=True)
     c = wl.linear_case(700 + T, T, K, N, hp_rank=r, n_experts=E, bf16=True, outlier_count=2, outlier_scale=10.0)
