@@ -1246,7 +1246,10 @@ __global__ __launch_bounds__(256) void decode_gemm16_kernel(gemm16_params p) {
 // makes a round trip through a wave-private LDS patch: written as loaded, read back one word per tile
 // (word g of row 16 t + i, bank-conflict free).  Results leave through the same patch so that a token's
 // 64 outputs are stored as one 128-byte run.
-template <int TOKS, bool I8 = false>
+// SHARE: one group per workgroup, its contraction shared out over the four wavefronts (every fourth chunk each) and its four
+// 16-row tiles of the experts' part (one each); the exact partial sums meet in LDS.  For calls of few groups, where a
+// wavefront per group leaves most of the chip idle and each wavefront is one long chain of loads (rule and figures at launch_gemm16_tiled).
+template <int TOKS, bool I8 = false, bool SHARE = false>
 __global__ __launch_bounds__(256, 4) void decode_gemm16_tiled_kernel(gemm16_params p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char dsm[];
   // dsm: xq [TOKS][min(K, KC)] int8 (one block of the codes), then a region that first holds Hm [TOKS][E*r] bf16 (expert phase) and afterwards
@@ -1263,28 +1266,35 @@ __global__ __launch_bounds__(256, 4) void decode_gemm16_tiled_kernel(gemm16_para
   const int i = lane & 15, g = lane >> 4;
   const int il = i & (TOKS - 1);
   const int G = (p.N + 63) / 64;
-  const int grp = blockIdx.x * 4 + wave;
+  const int grp = SHARE ? blockIdx.x : blockIdx.x * 4 + wave;
   const int nq = K / 128;
   const uint4* __restrict__ Pg = reinterpret_cast<const uint4*>(p.P) + ((size_t)layer * G + (grp < G ? grp : G - 1)) * nq * 64 + lane;
   constexpr uint32_t SIGNS = 0x80808080u;             // weight bytes {0, -128}, see decode_gemm16_kernel
+
+  // the wavefront's n-th chunk, and how many it has
+  auto chunk_of = [&](int n) { return SHARE ? 4 * n + wave : n; };
+  const int nqw = SHARE ? (nq - wave + 3) >> 2 : nq;
+  constexpr int NW = (SHARE && TOKS == 16) ? 4 : 8;   // chunks in flight; a whole number of passes per block of codes
+  constexpr int TT = SHARE ? 1 : 4;                   // 16-row tiles of the experts' part
 
   i32x4_t acc[4][2];
 #pragma unroll
   for (int t = 0; t < 4; ++t) acc[t][0] = acc[t][1] = i32x4_t{0, 0, 0, 0};
 
-  // Eight chunks (8 KB per wavefront) are in flight at any time: as soon as a chunk has been written to the
-  // patch its registers receive the chunk eight positions ahead.
-  uint4 w[8];
+  // NW chunks (1 KB each) are in flight at any time: as soon as a chunk has been written to the
+  // patch its registers receive the chunk NW positions ahead.
+  uint4 w[NW];
+  const int last = nqw > 0 ? chunk_of(nqw - 1) : 0;
 #pragma unroll
-  for (int jj = 0; jj < 8; ++jj) w[jj] = nt_load16(Pg + (size_t)(jj < nq ? jj : nq - 1) * 64);
+  for (int jj = 0; jj < NW; ++jj) w[jj] = nt_load16(Pg + (size_t)(jj < nqw ? chunk_of(jj) : last) * 64);
   const int lx = p.xshare > 1 ? layer / p.xshare : layer;   // the token block this weight set reads
   const unsigned long long used = g16_stage_inputs<TOKS, I8>(p, lx, xs, hm, KCs);   // overlaps the first loads
   const bool active = grp < G;                        // idle wavefronts of the last workgroup still meet the barrier
 
   // experts selected by at least one token of the batch (dense-masked bf16 MFMA, 32 columns of r per issue)
-  f32x4_t accf[4];
+  f32x4_t accf[TT];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) accf[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < TT; ++t) accf[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   if constexpr (I8) {
     // INT8 experts: per selected expert an exact int8 MFMA product (64 columns of r per issue, lane (i, g) holds
     // bytes 16 g .. 16 g + 15 of row i resp. token i), then D[row 4 g + v][token i] is de-quantised with the
@@ -1294,35 +1304,35 @@ __global__ __launch_bounds__(256, 4) void decode_gemm16_tiled_kernel(gemm16_para
       const float* inv = reinterpret_cast<const float*>(hq + (size_t)TOKS * Er);
       const float* gts = inv + TOKS * p.E;
       const int nblk = p.r / 64;
-      size_t roff[4];
-      int rowg[4];
+      size_t roff[TT];
+      int rowg[TT];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int row = grp * 64 + 16 * t + i;
+      for (int t = 0; t < TT; ++t) {
+        const int row = grp * 64 + 16 * (SHARE ? wave : t) + i;
         roff[t] = (size_t)(row < p.N ? row : 0) * p.r + 16 * g;
-        const int r4 = grp * 64 + 16 * t + 4 * g;     // first of the four output rows this lane holds (N % 4 == 0)
+        const int r4 = grp * 64 + 16 * (SHARE ? wave : t) + 4 * g;     // first of the four output rows this lane holds (N % 4 == 0)
         rowg[t] = r4 < p.N ? r4 : 0;
       }
       for (int e = 0; e < p.E; ++e) {
         if (!((used >> e) & 1ull)) continue;
         const int8_t* Be = (const int8_t*)p.hpB + ((size_t)layer * p.E + e) * p.N * p.r;
-        i32x4_t ai[4];
+        i32x4_t ai[TT];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) ai[t] = i32x4_t{0, 0, 0, 0};
+        for (int t = 0; t < TT; ++t) ai[t] = i32x4_t{0, 0, 0, 0};
         for (int blk = 0; blk < nblk; ++blk) {
-          uint4 a[4];
+          uint4 a[TT];
 #pragma unroll
-          for (int t = 0; t < 4; ++t) a[t] = nt_load16(reinterpret_cast<const uint4*>(Be + roff[t] + 64 * blk));
+          for (int t = 0; t < TT; ++t) a[t] = nt_load16(reinterpret_cast<const uint4*>(Be + roff[t] + 64 * blk));
           const int chunk = (e * p.r + 64 * blk) / 16 + g;
           const uint4 b = *reinterpret_cast<const uint4*>(hq + (size_t)il * Er + ((chunk ^ (il & 7)) << 4));
 #pragma unroll
-          for (int t = 0; t < 4; ++t)
+          for (int t = 0; t < TT; ++t)
             ai[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4_t, a[t]), __builtin_bit_cast(i32x4_t, b), ai[t], 0, 0, 0);
         }
         const float ig = inv[il * p.E + e], gt = gts[il * p.E + e];
         const float* gbe = p.gB + ((size_t)layer * p.E + e) * p.N;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
+        for (int t = 0; t < TT; ++t) {
           // the row gammas come off through the hardware reciprocal (1 ulp): sixteen IEEE divisions per expert and
           // lane would cost as many instructions as the whole packed product
           const float4 gb = *reinterpret_cast<const float4*>(gbe + rowg[t]);
@@ -1335,10 +1345,10 @@ __global__ __launch_bounds__(256, 4) void decode_gemm16_tiled_kernel(gemm16_para
     }
   } else if (p.r > 0 && active) {
     const int nhf = p.r / 32;
-    size_t roff[4];
+    size_t roff[TT];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int row = grp * 64 + 16 * t + i;
+    for (int t = 0; t < TT; ++t) {
+      const int row = grp * 64 + 16 * (SHARE ? wave : t) + i;
       roff[t] = (size_t)(row < p.N ? row : 0) * p.r + 8 * g;
     }
     for (int e = 0; e < p.E; ++e) {
@@ -1346,9 +1356,9 @@ __global__ __launch_bounds__(256, 4) void decode_gemm16_tiled_kernel(gemm16_para
       const uint16_t* Be = p.hpB + ((size_t)layer * p.E + e) * p.N * p.r;
       for (int hf = 0; hf < nhf; hf += 2) {
         const bool two = hf + 1 < nhf;
-        uint4 a0[4], a1[4];
+        uint4 a0[TT], a1[TT];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
+        for (int t = 0; t < TT; ++t) {
           // plain loads: the two instructions take the two halves of the same 128-byte lines (16 rows x 64 B each), and
           // with the non-temporal hint the second half was fetched from memory again (1.15 x the algorithmic bytes)
           a0[t] = *reinterpret_cast<const uint4*>(Be + roff[t] + 32 * hf);
@@ -1358,7 +1368,7 @@ __global__ __launch_bounds__(256, 4) void decode_gemm16_tiled_kernel(gemm16_para
         const uint4 b0 = *reinterpret_cast<const uint4*>(hm + (size_t)il * Er + (((col >> 3) ^ (il & 7)) << 3));
         const uint4 b1 = *reinterpret_cast<const uint4*>(hm + (size_t)il * Er + ((((col + (two ? 32 : 0)) >> 3) ^ (il & 7)) << 3));
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
+        for (int t = 0; t < TT; ++t) {
           accf[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a0[t]), __builtin_bit_cast(bf16x8_t, b0),
                                                             accf[t], 0, 0, 0);
           if (two)
@@ -1371,21 +1381,21 @@ __global__ __launch_bounds__(256, 4) void decode_gemm16_tiled_kernel(gemm16_para
 
   __syncthreads();                                    // Hm is dead: its LDS becomes the patches
 
-  // Passes of 8 chunks; whole passes carry no condition (one basic block: the accumulators stay put and
+  // Passes of NW chunks; whole passes carry no condition (one basic block: the accumulators stay put and
   // the MFMAs of one chunk overlap the LDS round trip of the next), the ragged last pass checks each chunk.
   int qb = 0;                                         // first 128-column chunk of the staged block
-  auto pass = [&](const int q0, auto full_tag) {
+  auto pass = [&](const int n0, auto full_tag) {
     constexpr bool FULL = decltype(full_tag)::value;
 #pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
-      if (FULL || q0 + jj < nq) {                     // block-uniform
+    for (int jj = 0; jj < NW; ++jj) {
+      if (FULL || n0 + jj < nqw) {                    // wavefront-uniform
         uint32_t* buf = patch + (jj & 1) * 256;
         *reinterpret_cast<uint4*>(buf + 4 * lane) = w[jj];
-        const int qn = q0 + 8 + jj;
-        w[jj] = nt_load16(Pg + (size_t)(qn < nq ? qn : nq - 1) * 64);
+        const int nn = n0 + NW + jj;
+        w[jj] = nt_load16(Pg + (size_t)(nn < nqw ? chunk_of(nn) : last) * 64);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        const int chunk = 8 * (q0 - qb + jj) + 2 * g; // 16-column chunk of the staged part of the activation row
+        const int chunk = 8 * (chunk_of(n0 + jj) - qb) + 2 * g; // 16-column chunk of the staged part of the activation row
         const uint4 act0 = *reinterpret_cast<const uint4*>(xs + (size_t)il * KCs + ((chunk ^ (il & 7)) << 4));
         const uint4 act1 = *reinterpret_cast<const uint4*>(xs + (size_t)il * KCs + (((chunk + 1) ^ (il & 7)) << 4));
 #pragma unroll
@@ -1410,14 +1420,51 @@ __global__ __launch_bounds__(256, 4) void decode_gemm16_tiled_kernel(gemm16_para
       __syncthreads();
     }
     if (active) {
-      const int qe = nq < qb + QPC ? nq : qb + QPC;
-      int q0 = qb;
-      for (; q0 + 8 <= qe; q0 += 8) pass(q0, std::true_type{});
-      if (q0 < qe) pass(q0, std::false_type{});         // only the last block can be ragged
+      const int nb = SHARE ? qb / 4 : qb, full = SHARE ? (qb + QPC) / 4 : qb + QPC;
+      const int ne = nqw < full ? nqw : full;
+      int n0 = nb;
+      for (; n0 + NW <= ne; n0 += NW) pass(n0, std::true_type{});
+      if (n0 < ne) pass(n0, std::false_type{});         // only the last block can be ragged
     }
   }
   if (!active) return;                                // no workgroup barrier below
 
+  if constexpr (SHARE) {
+    // partial sums [wavefront][tile][lane] (16 KB over the codes and patches), then wavefront w finishes tile w
+    __syncthreads();
+    i32x4_t* part = reinterpret_cast<i32x4_t*>(dsm);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) part[(wave * 4 + t) * 64 + lane] = acc[t][0] + acc[t][1];
+    __syncthreads();
+    i32x4_t sum = part[wave * 64 + lane];
+#pragma unroll
+    for (int u = 1; u < 4; ++u) sum += part[(u * 4 + wave) * 64 + lane];
+    uint16_t* stage = reinterpret_cast<uint16_t*>(dsm + 16384);   // [token][64 rows]
+    if (i < p.B) {
+      const float sc = fp16_bits_to_f32(p.scale[layer]) / p.gamma[lx * p.B + i];
+      const int rs = p.rowsum[lx * p.B + i];
+      float y[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int s4 = sum[v];
+        const int a = -(s4 >> 6) - rs;                // 2 * (-acc / 128) - rowsum
+        const int n = grp * 64 + 16 * wave + 4 * g + v;
+        if (p.acc_out && n < p.N) p.acc_out[((size_t)layer * p.B + i) * p.N + n] = a;
+        y[v] = __fmul_rn(sc, (float)a) + p.alpha * accf[0][v];
+      }
+      *reinterpret_cast<uint2*>(stage + i * 64 + 16 * wave + 4 * g) = make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+    }
+    __syncthreads();
+    const int j = tid >> 3, c = tid & 7, n0 = grp * 64 + 8 * c;
+    if (j < p.B && n0 < p.N) {
+      uint16_t* dst = p.Y + ((size_t)layer * p.B + j) * p.N + n0;
+      const uint16_t* src = stage + j * 64 + 8 * c;
+      if (p.N % 8 == 0) *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
+      else
+        for (int v = 0; v < 8 && n0 + v < p.N; ++v) dst[v] = src[v];
+    }
+    return;
+  } else {
   // D[row 4 g + v][token i] -> patch as [token][64 rows] bf16, then 128-byte runs per token
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -1454,6 +1501,7 @@ __global__ __launch_bounds__(256, 4) void decode_gemm16_tiled_kernel(gemm16_para
         for (int v = 0; v < 8 && n0 + v < p.N; ++v) dst[v] = src[v];
       }
     }
+  }
   }
 }
 
@@ -1588,8 +1636,39 @@ static int decode_set_gemm16_limits() {
     set((const void*)decode_gemm16_tiled_kernel<16>);
     set((const void*)decode_gemm16_tiled_kernel<8, true>);
     set((const void*)decode_gemm16_tiled_kernel<16, true>);
+    set((const void*)decode_gemm16_tiled_kernel<8, false, true>);
+    set((const void*)decode_gemm16_tiled_kernel<16, false, true>);
+    set((const void*)decode_gemm16_tiled_kernel<8, true, true>);
+    set((const void*)decode_gemm16_tiled_kernel<16, true, true>);
   });
   return rc;
+}
+
+// One launch of the row-interleaved small-batch kernel over `sets` weight sets; hm: bytes of the experts' hidden states in LDS.
+static int launch_gemm16_tiled(const gemm16_params& p, int sets, int toks, size_t hm, bool i8, hipStream_t s) {
+  const int G = (p.N + 63) / 64;
+  size_t lds = g16_tiled_code_bytes(toks, p.K) + (hm > 8192 ? hm : 8192);
+  // Sharing a group out pays while all groups are resident at once (four workgroups on each of 256 CUs): over 40 calls of 2 to
+  // 16 tokens, 1.14 to 1.35 x up to 700 groups, 1.0 to 1.2 x up to 1024, 0.76 to 1.16 x above (5 tokens, 3 FFNs of 1920/7296: 52 ->
+  // 39 us; 4 tokens through 52 layers of 2304 -> 3804, 3120 groups: 63 -> 84 us).
+  const bool share = (long)G * sets <= 1024;
+  if (share && lds < 16384 + 2048) lds = 16384 + 2048;
+  const dim3 grid(share ? G : (G + 3) / 4, sets);
+#define PQ_G16(I8V)                                                                                                                  \
+  do {                                                                                                                               \
+    if (share) {                                                                                                                     \
+      if (toks == 8) decode_gemm16_tiled_kernel<8, I8V, true><<<grid, 256, lds, s>>>(p);                                              \
+      else decode_gemm16_tiled_kernel<16, I8V, true><<<grid, 256, lds, s>>>(p);                                                       \
+    } else {                                                                                                                         \
+      if (toks == 8) decode_gemm16_tiled_kernel<8, I8V><<<grid, 256, lds, s>>>(p);                                                    \
+      else decode_gemm16_tiled_kernel<16, I8V><<<grid, 256, lds, s>>>(p);                                                             \
+    }                                                                                                                                \
+  } while (0)
+  if (i8) PQ_G16(true);
+  else PQ_G16(false);
+#undef PQ_G16
+  PQ_CHECK_LAUNCH("decode_gemm16_tiled_kernel");
+  return PQ_OK;
 }
 
 // Several tokens per layer (2..16): the same four stages on the small-batch kernels.  The up and gate products are
@@ -1630,11 +1709,7 @@ static int launch_decode_ffn_batch(int L, int B, int D, int F, int r, int E, int
     pq_prof_scope prof(PQP_DECODE_MAIN, s);
     gemm16_params p{packed_upgate, scale_upgate, xq1, rs1, gm1, nullptr, nullptr, nullptr, nullptr, (uint16_t*)UG, acc_upgate,
                     B, F, D, 0, 0, 0, alpha, nullptr, 2};
-    const size_t lds = g16_tiled_code_bytes(toks, D) + 8192;
-    dim3 grid(((F + 63) / 64 + 3) / 4, 2 * L);
-    if (toks == 8) decode_gemm16_tiled_kernel<8><<<grid, 256, lds, s>>>(p);
-    else decode_gemm16_tiled_kernel<16><<<grid, 256, lds, s>>>(p);
-    PQ_CHECK_LAUNCH("decode_gemm16_tiled_kernel");
+    if (int e = launch_gemm16_tiled(p, 2 * L, toks, 0, false, s)) return e;
   }
   {
     pq_prof_scope prof(PQP_SWIGLU, s);
@@ -1647,12 +1722,7 @@ static int launch_decode_ffn_batch(int L, int B, int D, int F, int r, int E, int
     pq_prof_scope prof(PQP_DECODE_MAIN, s);
     gemm16_params p{packed_down, scale_down, xq2, rs2, gm2, (const uint16_t*)Down, idx, gate, act, (uint16_t*)Y, nullptr,
                     B, D, F, E, r, topk, alpha, nullptr, 1};
-    const size_t hm = 2 * (size_t)toks * E * r;
-    const size_t lds = g16_tiled_code_bytes(toks, F) + (hm > 8192 ? hm : 8192);
-    dim3 grid(((D + 63) / 64 + 3) / 4, L);
-    if (toks == 8) decode_gemm16_tiled_kernel<8><<<grid, 256, lds, s>>>(p);
-    else decode_gemm16_tiled_kernel<16><<<grid, 256, lds, s>>>(p);
-    PQ_CHECK_LAUNCH("decode_gemm16_tiled_kernel");
+    if (int e = launch_gemm16_tiled(p, L, toks, 2 * (size_t)toks * E * r, false, s)) return e;
   }
   return PQ_OK;
 }
@@ -1794,17 +1864,10 @@ int pq_launch_decode(const pq_decode_desc& d, const void* X, const uint32_t* pac
     const int toks = B <= 8 ? 8 : 16;
     const bool tiled = d.packed_layout == PQ_PACKED_TILED64;
     const size_t hm_bytes = 2 * (size_t)toks * d.n_experts * r;
-    const size_t lds = tiled ? g16_tiled_code_bytes(toks, K) + (hm_bytes > 8192 ? hm_bytes : 8192) : (size_t)toks * K + hm_bytes;
+    const size_t lds = (size_t)toks * K + hm_bytes;   // (row-major packing)
     if (int e = decode_set_gemm16_limits()) return e;
     if (tiled) {
-      dim3 grid(((N + 63) / 64 + 3) / 4, L);
-      if (i8) {
-        if (toks == 8) decode_gemm16_tiled_kernel<8, true><<<grid, 256, lds, s>>>(p);
-        else decode_gemm16_tiled_kernel<16, true><<<grid, 256, lds, s>>>(p);
-      } else {
-        if (toks == 8) decode_gemm16_tiled_kernel<8><<<grid, 256, lds, s>>>(p);
-        else decode_gemm16_tiled_kernel<16><<<grid, 256, lds, s>>>(p);
-      }
+      if (int e = launch_gemm16_tiled(p, L, toks, hm_bytes, i8, s)) return e;
     } else {
       if (i8) return pq_set_error(PQ_ERR_SHAPE, "INT8 experts with batch > 1 need the row-interleaved packing");
       dim3 grid((N + G16_ROWS_PER_BLOCK - 1) / G16_ROWS_PER_BLOCK, L);

@@ -197,3 +197,37 @@ def test_decode_largest_d_in_small_batch():
         check_decode(wl.decode_case(97 + B, B, d_in=16384, d_out=136, n_experts=2, hp_rank=32, n_layers=1), top_k=1, tiled=True)
     print("decode INT8 experts d_in = 12800, B = 8", flush=True)
     check_decode_int8(wl.decode_case(99, 8, d_in=12800, d_out=136, n_experts=2, hp_rank=64, n_layers=1), top_k=1, tiled=True)
+
+
+@pytest.mark.parametrize("B,K,N,E,r,k", [(2, 128, 64, 4, 64, 1), (5, 640, 140, 8, 64, 2), (16, 2304, 200, 4, 64, 2), (8, 4480, 72, 2, 64, 1)])
+@pytest.mark.parametrize("int8", [False, True])
+def test_decode_shared_groups_equal_unshared(B, K, N, E, r, k, int8):
+    """Calls of few 64-row groups share a group out over a workgroup's wavefronts; with more than 1024 groups every wavefront has
+    a group of its own.  The same layer as one weight set and as many copies: accumulators and outputs equal bit for bit
+    (exact integer sums; the experts' products run in the same order), and the single set agrees with the oracle."""
+    print(f"shared groups B={B} K={K} N={N} E={E} r={r} k={k} int8={int8}", flush=True)
+    c = wl.decode_case(90 + K + N + B, B, d_in=K, d_out=N, n_experts=E, hp_rank=r, n_layers=1)
+    P, _, ml = pq.pack_sign(dev(c["W"][0], True))
+    mu, lam = po.weight_stats(c["W"][0])
+    X, A, Bm, Wr = (dev(c[n], True) for n in ("X", "A", "B", "Wr"))
+    outs = []
+    for L in (1, 1024 // ((N + 63) // 64) + 1):
+        rep = lambda t: t.expand(L, *t.shape[1:]).contiguous()
+        Pin = rep(pq.pack_retile64(P, K)[None])
+        scale = dev(np.full((L,), np.float16(np.float32(0.2) * lam), np.float16).view(np.int16))
+        desc = pq.DecodeDesc(B, K, N, r, E, k, L, pq.PQ_PACKED_TILED64, 2.0)
+        Y = torch.empty((L, B, N), dtype=torch.bfloat16, device="cuda")
+        acc = torch.empty((L, B, N), dtype=torch.int32, device="cuda")
+        if int8:
+            (Aq, gA), (Bq, gB) = pq.quant_rows(A), pq.quant_rows(Bm)
+            pq.decode_gemv_int8(desc, rep(X), Pin, scale, Y, pq.decode_workspace(desc), rep(Aq), rep(gA), rep(Bq), rep(gB), rep(Wr), acc_out=acc)
+        else:
+            pq.decode_gemv(desc, rep(X), Pin, scale, Y, pq.decode_workspace(desc), A=rep(A), B=rep(Bm), Wr=rep(Wr), acc_out=acc)
+        torch.cuda.synchronize()
+        outs.append((Y.float(), acc))
+    (Y1, a1), (YL, aL) = outs
+    assert torch.equal(aL, a1.expand_as(aL)) and torch.equal(YL, Y1.expand_as(YL))
+    f = po.decode_gemv(c["X"][0], po.pack_sign(po.binarise(c["W"][0], mu)), (mu, lam), 2.0, 0.2, A=c["A"][0], B=c["B"][0], Wr=c["Wr"][0], top_k=k)
+    assert np.array_equal(a1[0].cpu().numpy().astype(np.int64), f["acc"])
+    if not int8:
+        assert relerr(Y1[0].cpu().numpy(), f["Y"]) <= 2e-2
