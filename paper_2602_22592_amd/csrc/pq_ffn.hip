@@ -70,7 +70,7 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   L.UG = c.take(E * 2 * r * D * 2);
   L.ctx_total = c.off;
   cursor w;
-  L.stat = w.take(2 * sizeof(double) * 1024);
+  L.stat = w.take(3 * 2 * sizeof(double) * 1024);
   L.n_red_a = pq_rowdot_blocks((int)S);
   L.n_red_b = pq_plan_gemm((int)D, (int)F, (int)T).red_blocks;      // dW_down GEMM
   L.red_a = w.take(sizeof(double) * (size_t)L.n_red_a);
@@ -89,6 +89,11 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   for (const auto& sh : {std::pair<int, int>{Fi, Di}, std::pair<int, int>{Di, Fi}}) {   // the 1-bit forward products
     const size_t b = Ti > 0 ? pq_plan_gemm(Ti, sh.first, sh.second, true, true).ws_bytes : 0;
     if (b > sk) sk = b;
+  }
+  {   // U and G, and dW_up and dW_gate, as one launch each
+    const size_t f2 = Ti > 0 ? pq_plan_dual(Ti, Fi, Di, true).ws_bytes : 0, w2 = pq_plan_dual(Fi, Di, Ti, false).ws_bytes;
+    if (f2 > sk) sk = f2;
+    if (w2 > sk) sk = w2;
   }
   // the expert up/gate projections and their input gradients split the contraction up to 8 ways: [8][S][r] fp32
   if (8 * S * r * sizeof(float) > sk) sk = 8 * S * r * sizeof(float);
@@ -129,13 +134,6 @@ pq_epilogue epi0() {
   memset(&e, 0, sizeof(e));
   e.scale = 1.0f;
   return e;
-}
-
-int pack_weight(const void* W, int N, int K, char* cx, size_t offP, size_t offPt, size_t offml, double* part, hipStream_t s) {
-  const size_t n = (size_t)N * K;
-  const int nb = pq_stats_blocks(n);
-  if (int e = pq_launch_wstats_partial(W, PQ_BF16, n, part, nb, s)) return e;
-  return pq_launch_pack(W, PQ_BF16, N, K, part, nb, (uint32_t*)(cx + offP), (uint32_t*)(cx + offPt), (float*)(cx + offml), s);
 }
 
 }  // namespace
@@ -188,40 +186,36 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
 
   int8_t* Xq = (int8_t*)(cx + L.Xq);
   float* gx = (float*)(cx + L.gx);
-  const bool combo = T > 0 && D <= 8192;   // the quantiser of X shares the launch of W_up's statistics
-  if (combo) {
-    const size_t n = (size_t)Fv * D;
-    const int nb = pq_stats_blocks(n);
-    if (int e = pq_launch_wstats_quant(W_up, PQ_BF16, n, part, nb, X, T, D, Xq, gx, (uint16_t*)(cx + L.Xt), s)) return e;
-    if (int e = pq_launch_pack(W_up, PQ_BF16, Fv, D, part, nb, (uint32_t*)(cx + L.P_up), (uint32_t*)(cx + L.Pt_up),
-                               (float*)(cx + L.ml_up), s)) return e;
-  } else if (int e = pack_weight(W_up, Fv, D, cx, L.P_up, L.Pt_up, L.ml_up, part, s)) return e;
+  const bool hp8 = d->hp_kind == PQ_HP_LOWRANK_INT8;
   // the packer pads partial words with +1 bits (columns Fv.. of P_down's rows, rows Fv.. of the transposed packings of
   // W_up and W_gate); rows Fv.. of P_up, P_gate and Pt_down are never written: whatever they hold lands in columns of
   // U, G and dHd that the gated unit and its backward replace by zeros
-  if (int e = pack_weight(W_gate, Fv, D, cx, L.P_gate, L.Pt_gate, L.ml_gate, part, s)) return e;
-  if (int e = pack_weight(W_down, D, Fv, cx, L.P_down, L.Pt_down, L.ml_down, part, s)) return e;
-  const bool hp8 = d->hp_kind == PQ_HP_LOWRANK_INT8;
+  pq_ffn_prep p;
+  memset(&p, 0, sizeof(p));
+  auto job = [&](const void* W, int N, int K, int slot, size_t P, size_t Pt, size_t ml) {
+    return pq_weight_job{W, N, K, part + 2 * 1024 * slot, pq_stats_blocks((size_t)N * K), (uint32_t*)(cx + P), (uint32_t*)(cx + Pt), (float*)(cx + ml)};
+  };
+  p.w[0] = job(W_up, Fv, D, 0, L.P_up, L.Pt_up, L.ml_up);
+  p.w[1] = job(W_gate, Fv, D, 1, L.P_gate, L.Pt_gate, L.ml_gate);
+  p.w[2] = job(W_down, D, Fv, 2, L.P_down, L.Pt_down, L.ml_down);
+  p.X = X; p.T = T; p.D = D; p.Xq = Xq; p.gamma = gx; p.Xt = (uint16_t*)(cx + L.Xt);
+  p.Up = Up; p.Gate = Gate; p.Down = Down; p.E = E; p.r = r; p.UG = cx + L.UG;
   if (hp8) {  // the experts' weight rows on the AbsMax grid (codes, gamma per row, de-quantised copy for the backward)
-    if (int e = pq_launch_concat_expert_rows(Up, Gate, E, r, D, cx + L.UG, s)) return e;
-    if (int e = pq_launch_quant_act(cx + L.UG, PQ_BF16, E * 2 * r, D, (int8_t*)(cx + L.UGQ), (float*)(cx + L.gUG), (uint16_t*)(cx + L.UGT), s)) return e;
-    if (int e = pq_launch_quant_act(Down, PQ_BF16, E * D, r, (int8_t*)(cx + L.DownQ), (float*)(cx + L.gDown), (uint16_t*)(cx + L.DownT), s)) return e;
+    p.UGQ = (int8_t*)(cx + L.UGQ); p.gUG = (float*)(cx + L.gUG); p.UGT = (uint16_t*)(cx + L.UGT);
+    p.DownQ = (int8_t*)(cx + L.DownQ); p.gDown = (float*)(cx + L.gDown); p.DownT = (uint16_t*)(cx + L.DownT);
   }
+  if (int e = pq_launch_ffn_prep(p, s)) return e;
+  if (int e = pq_launch_pack3(p.w, s)) return e;
   if (T == 0)  // no tokens: leave empty expert segments behind so that a backward call is well defined
     return pq_launch_route((const int*)(cx + L.idx), 0, E, (int*)(cx + L.counts), (int*)(cx + L.offsets), (int*)(cx + L.perm),
                            (int*)(cx + L.inv), s);
 
-  if (!combo)
-    if (int e = pq_launch_quant_act(X, PQ_BF16, T, D, Xq, gx, (uint16_t*)(cx + L.Xt), s)) return e;
-  {  // U and G: pure 1-bit linears (no feature scale of their own)
+  {  // U and G: pure 1-bit linears (no feature scale of their own), one launch
     pq_operand A{Xq, D, PQ_SRC_KC8, nullptr};
-    pq_operand Bu{cx + L.P_up, D / 8, PQ_SRC_BITS8, nullptr};
+    pq_operand Bu{cx + L.P_up, D / 8, PQ_SRC_BITS8, nullptr}, Bg{cx + L.P_gate, D / 8, PQ_SRC_BITS8, nullptr};
     pq_epilogue e = epi0();
-    e.C = cx + L.U; e.ldc = F; e.out_kind = PQ_OUT_BF16; e.dev_scale = (const float*)(cx + L.ml_up) + 1; e.row_div = gx; e.split_int8 = 1;
-    if (int err = pq_launch_gemm(T, F, D, A, Bu, e, s, PQP_GEMM_ONEBIT, sk)) return err;
-    pq_operand Bg{cx + L.P_gate, D / 8, PQ_SRC_BITS8, nullptr};
-    e.C = cx + L.G; e.dev_scale = (const float*)(cx + L.ml_gate) + 1;
-    if (int err = pq_launch_gemm(T, F, D, A, Bg, e, s, PQP_GEMM_ONEBIT, sk)) return err;
+    e.C = cx + L.U; e.ldc = F; e.out_kind = PQ_OUT_BF16; e.dev_scale = (const float*)(cx + L.ml_up) + 1; e.row_div = gx;
+    if (int err = pq_launch_gemm_dual(T, F, D, A, Bu, e, A, Bg, cx + L.G, (const float*)(cx + L.ml_gate) + 1, s, PQP_GEMM_ONEBIT, sk)) return err;
   }
   int8_t* Hq = (int8_t*)(cx + L.Hq);
   float* gh = (float*)(cx + L.gh);
@@ -285,7 +279,6 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
   if (!one)
     if (int e = pq_launch_gather_rows(X, perm, k, S, D, cx + L.Xp, s)) return e;
   // [u | g] = Xp [Up_e; Gate_e]^T: both projections as one product with 2 r outputs per slot
-  if (int e = pq_launch_concat_expert_rows(Up, Gate, E, r, D, cx + L.UG, s)) return e;
   {
     pq_operand A{xp, D, PQ_SRC_KC16, nullptr};
     pq_operand B{cx + L.UG, D, PQ_SRC_KC16, nullptr};
@@ -370,12 +363,9 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
     pq_epilogue e = epi0();
     e.ldc = D; e.out_kind = PQ_OUT_F32;
     if (Fv != F) e.m_limit = Fv;                     // rows Fv.. of the padded product do not exist in dW_up / dW_gate
-    pq_operand A{ws + L.dU, F, PQ_SRC_KS16, nullptr};
+    pq_operand A{ws + L.dU, F, PQ_SRC_KS16, nullptr}, A2{ws + L.dG, F, PQ_SRC_KS16, nullptr};
     e.C = dW_up;
-    if (int err = pq_launch_gemm(F, D, T, A, B, e, s, PQP_GEMM_DW, sk)) return err;
-    pq_operand A2{ws + L.dG, F, PQ_SRC_KS16, nullptr};
-    e.C = dW_gate;
-    if (int err = pq_launch_gemm(F, D, T, A2, B, e, s, PQP_GEMM_DW, sk)) return err;
+    if (int err = pq_launch_gemm_dual(F, D, T, A, B, e, A2, B, dW_gate, nullptr, s, PQP_GEMM_DW, sk)) return err;
   }
   // experts
   const int* idx = (const int*)(cx + L.idx);

@@ -282,9 +282,10 @@ struct pq_frag_set {
 // MFMA engine
 // ---------------------------------------------------------------------------------------------
 // One workgroup computes a BM x BN tile over the contraction range [z*kchunk, (z+1)*kchunk), z = blockIdx.y.
-// FAST: whole tiles (no validity masks in the register-staged second contraction); TAIL: the contraction may end inside a step
+// DUAL: two problems of the same sizes (mode 3), blockIdx.z selects (an instantiation of its own: the test turns kernel
+// arguments into run-time selections).  FAST: whole tiles (no validity masks in the register-staged second contraction); TAIL: the contraction may end inside a step
 // (an instantiation of its own: the registers its addresses take are spills elsewhere).
-template <int BM, int BN, int WGM, int WGN, int KB, bool FAST, bool TAIL, bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1>
+template <int BM, int BN, int WGM, int WGN, int KB, bool FAST, bool TAIL, bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1, bool DUAL = false>
 __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N, int K, pq_operand A,
                                                                      pq_operand B, pq_epilogue epi,
                                                                      int nbn, int total_tiles, int kchunk,
@@ -310,6 +311,12 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
   // Work items are ordered (contraction split, tile row, tile column) and XCD c takes the c-th eighth of
   // that order: with a split contraction an XCD then works on one split and a band of tile rows, so the
   // operand panels it streams are shared by its workgroups instead of being fetched by every XCD.
+  if constexpr (DUAL)
+    if (blockIdx.z == 1) {                           // uniform
+      A = grp.second.A; B = grp.second.B;
+      epi.C = grp.second.C; epi.dev_scale = grp.second.dev_scale;
+      splitk_part = grp.second.part;
+    }
   int pid = blockIdx.x, split = blockIdx.y;
   {
     const int nb = total_tiles * (int)gridDim.y;
@@ -1098,13 +1105,14 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(int M, int N, int sp
 
 // The reductions of a paired launch in one launch: the first nblk0 workgroups finish problem 0, the rest problem 1.
 // Up to two scalar reductions of the same call (d alpha, d beta) ride along as the last workgroups of the grid.
+template <bool INT>
 __global__ __launch_bounds__(256) void splitk_reduce_pair_kernel(int splits, int nblk0, int nblk1, int M0, int N0,
                                                                  const float* __restrict__ part0, pq_epilogue epi0, int M1, int N1,
                                                                  const float* __restrict__ part1, pq_epilogue epi1, pq_reduce_job j0,
                                                                  pq_reduce_job j1) {
   const int b = blockIdx.x;
-  if (b < nblk0) splitk_reduce_body<false>(M0, N0, splits, part0, epi0, b);
-  else if (b < nblk0 + nblk1) splitk_reduce_body<false>(M1, N1, splits, part1, epi1, b - nblk0);
+  if (b < nblk0) splitk_reduce_body<INT>(M0, N0, splits, part0, epi0, b);
+  else if (b < nblk0 + nblk1) splitk_reduce_body<INT>(M1, N1, splits, part1, epi1, b - nblk0);
   else pq_reduce_job_body(b == nblk0 + nblk1 ? j0 : j1);
 }
 
@@ -1142,13 +1150,18 @@ struct pq_frag_set_w4 {
 
 // RAGGED: the last stage of a range is not whole; its missing rows come from a page of zeros.  (An instantiation of its own: the
 // test behind every load cost the whole ones 3 to 4 %.)
-template <bool RAGGED>
+template <bool RAGGED, bool DUAL>
 __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn,
-                                                          int total_tiles, int kchunk, float* splitk_part) {
+                                                          int total_tiles, int kchunk, float* splitk_part, pq_gemm_second second) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int STG = 32768;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[4 * STG];
   __shared__ double red[4];
+  if constexpr (DUAL)
+    if (blockIdx.z == 1) {                           // uniform: the second of two problems of the same sizes
+      A = second.A; B = second.B; epi.C = second.C; epi.dev_scale = second.dev_scale;
+      splitk_part = second.part;
+    }
   int pid = blockIdx.x, split = blockIdx.y;
   {   // XCD-aware order, as in mfma_gemm_kernel
     const int nb = total_tiles * (int)gridDim.y;
@@ -1327,15 +1340,15 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
 #endif
 }
 
-template <int BM, int BN, int WGM, int WGN, int KB, bool FAST, bool TAIL, bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1>
+template <int BM, int BN, int WGM, int WGN, int KB, bool FAST, bool TAIL, bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1, bool DUAL = false>
 int launch_mfma(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B,
                 const pq_epilogue& epi, hipStream_t s, float* part, const pq_gemm_group& grp, const pq_phase2& ph2) {
   // grouped rows: every group may end in a partial tile, so at most ceil(rows / BM) + n_groups row tiles exist
   const int nbm = grp.mode == 1 ? (grp.max_rows + BM - 1) / BM + grp.n_groups : (M + BM - 1) / BM;
   const int nbn = (N + BN - 1) / BN;
   const int tiles = nbm * nbn;
-  dim3 grid(tiles, pl.splits), block(WGM * WGN * 64);
-  mfma_gemm_kernel<BM, BN, WGM, WGN, KB, FAST, TAIL, INT8, AK, BKIND, AK2, BK2><<<grid, block, 0, s>>>(
+  dim3 grid(tiles, pl.splits, DUAL ? 2 : 1), block(WGM * WGN * 64);
+  mfma_gemm_kernel<BM, BN, WGM, WGN, KB, FAST, TAIL, INT8, AK, BKIND, AK2, BK2, DUAL><<<grid, block, 0, s>>>(
       M, N, K, A, B, epi, nbn, tiles, pl.kchunk, pl.splits > 1 ? part : nullptr, grp, ph2);
   PQ_CHECK_LAUNCH("mfma_gemm_kernel");
   return PQ_OK;
@@ -1354,11 +1367,15 @@ int launch_mfma_cfg(const pq_gemm_plan& pl, int M, int N, int K, const pq_operan
   // weight gradients: the four-wavefront kernel (no per-row divisor, no int32 output)
   if constexpr (AK == PQ_SRC_KS16 && BKIND == PQ_SRC_KS16 && AK2 < 0) {
     const int nbm = (M + 255) / 256, nbn = (N + 255) / 256;
-    dim3 grid(nbm * nbn, pl.splits), block(256);
-    if (grp.mode || A.kdiv || B.kdiv || epi.row_div || epi.out_kind == PQ_OUT_I32) return pq_set_error(PQ_ERR_BAD_ARG, "no 256x256 weight-gradient kernel for this epilogue");
+    const bool dual = grp.mode == 3, ragged = K % 32 != 0 || pl.kchunk % 32 != 0;
+    dim3 grid(nbm * nbn, pl.splits, dual ? 2 : 1);
+    if ((grp.mode && !dual) || A.kdiv || B.kdiv || epi.row_div || epi.out_kind == PQ_OUT_I32) return pq_set_error(PQ_ERR_BAD_ARG, "no 256x256 weight-gradient kernel for this epilogue");
     float* p = pl.splits > 1 ? part : nullptr;
-    if (K % 32 == 0 && pl.kchunk % 32 == 0) gemm_tn_w4_kernel<false><<<grid, block, 0, s>>>(M, N, K, A, B, epi, nbn, nbm * nbn, pl.kchunk, p);
-    else gemm_tn_w4_kernel<true><<<grid, block, 0, s>>>(M, N, K, A, B, epi, nbn, nbm * nbn, pl.kchunk, p);
+#define PQ_W4(R, D) gemm_tn_w4_kernel<R, D><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, nbm * nbn, pl.kchunk, p, grp.second)
+    if (dual) { if (ragged) PQ_W4(true, true); else PQ_W4(false, true); }
+    else if (ragged) PQ_W4(true, false);
+    else PQ_W4(false, false);
+#undef PQ_W4
     PQ_CHECK_LAUNCH("gemm_tn_w4_kernel");
     return PQ_OK;
   } else {
@@ -1366,6 +1383,13 @@ int launch_mfma_cfg(const pq_gemm_plan& pl, int M, int N, int K, const pq_operan
     constexpr int EPB = INT8 ? 128 : 64;
     const bool steps = K % EPB == 0 && pl.kchunk % EPB == 0 && (!bits || B.ld % 16 == 0);
     const bool tiles = grp.mode == 0 && M % 256 == 0 && N % 256 == 0 && ph2.K2 % 64 == 0;
+    if constexpr (AK == PQ_SRC_KC8 && BKIND == PQ_SRC_BITS8 && AK2 < 0) {
+      if (grp.mode == 3) {
+        if (steps) return launch_mfma<256, 256, 2, 4, 128, false, false, INT8, AK, BKIND, AK2, BK2, true>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+        return launch_mfma<256, 256, 2, 4, 128, false, true, INT8, AK, BKIND, AK2, BK2, true>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+      }
+    }
+    if (grp.mode == 3) return pq_set_error(PQ_ERR_BAD_ARG, "no paired 256x256 kernel for these operand kinds");
     if (steps && tiles) return launch_mfma<256, 256, 2, 4, 128, true, false, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
     if (steps) return launch_mfma<256, 256, 2, 4, 128, false, false, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
     return launch_mfma<256, 256, 2, 4, 128, false, true, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
@@ -1907,11 +1931,53 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
   }
   if (pp.splits > 1) {
     pq_prof_scope prof(PQP_SPLITK_REDUCE, s);
-    splitk_reduce_pair_kernel<<<rb0 + rb1 + (jobs ? 2 : 0), 256, 0, s>>>(pp.splits, rb0, rb1, M0, N0, (const float*)splitk_ws0, e0, M1, N1,
+    splitk_reduce_pair_kernel<false><<<rb0 + rb1 + (jobs ? 2 : 0), 256, 0, s>>>(pp.splits, rb0, rb1, M0, N0, (const float*)splitk_ws0, e0, M1, N1,
                                                                         (const float*)splitk_ws1, e1, jobs ? jobs[0] : none,
                                                                         jobs ? jobs[1] : none);
     PQ_CHECK_LAUNCH("splitk_reduce_pair_kernel");
     if (jobs && jobs_done) *jobs_done = true;
+  }
+  return PQ_OK;
+}
+
+// Two products of the same sizes, kinds and epilogue but for C and the device scale (U and G of the FFN; dW_up and dW_gate) in
+// one launch: one start and one tail instead of two, and together they fill the chip where each alone does not.
+pq_gemm_plan pq_plan_dual(int M, int N, int K, bool int8) { return pq_plan_gemm_impl(2 * M, N, K, int8, true); }
+int pq_launch_gemm_dual(int M, int N, int K, const pq_operand& A0, const pq_operand& B0, const pq_epilogue& e0, const pq_operand& A1,
+                        const pq_operand& B1, void* C1, const float* dev_scale1, hipStream_t s, int prof_label, void* splitk_ws) {
+  if (M <= 0 || N <= 0) return PQ_OK;
+  const bool int8 = A0.kind == PQ_SRC_KC8;
+  const pq_gemm_plan pl = pq_plan_dual(M, N, K, int8);
+  if (pl.splits > 1 && !splitk_ws) return pq_set_error(PQ_ERR_WORKSPACE, "split contraction needs scratch");
+  if (e0.partials || e0.accumulate || e0.dot_comp || e0.sign_bytes || e0.maskW || e0.n_limit % 4)
+    return pq_set_error(PQ_ERR_BAD_ARG, "paired products take plain epilogues");
+  float* part = (float*)splitk_ws;
+  pq_gemm_group grp;
+  memset(&grp, 0, sizeof(grp));
+  grp.mode = 3;
+  grp.second.A = A1; grp.second.B = B1; grp.second.C = C1; grp.second.ldc = (int)e0.ldc; grp.second.scale = e0.scale; grp.second.dev_scale = dev_scale1;
+  grp.second.part = pl.splits > 1 ? part + (size_t)pl.splits * M * N : nullptr;
+  grp.second.M = M; grp.second.N = N; grp.second.nbn = (N + pl.bm - 1) / pl.bm;
+  pq_phase2 ph2;
+  memset(&ph2, 0, sizeof(ph2));
+  {
+    pq_prof_scope prof(prof_label, s);
+    int rc;
+    if (int8 && B0.kind == PQ_SRC_BITS8) rc = launch_mfma_cfg<true, PQ_SRC_KC8, PQ_SRC_BITS8>(pl, M, N, K, A0, B0, e0, s, part, grp, ph2);
+    else if (A0.kind == PQ_SRC_KS16 && B0.kind == PQ_SRC_KS16) rc = launch_mfma_cfg<false, PQ_SRC_KS16, PQ_SRC_KS16>(pl, M, N, K, A0, B0, e0, s, part, grp, ph2);
+    else return pq_set_error(PQ_ERR_BAD_ARG, "no paired kernel for operand kinds (%d, %d)", A0.kind, B0.kind);
+    if (rc) return rc;
+  }
+  if (pl.splits > 1) {
+    pq_prof_scope prof(PQP_SPLITK_REDUCE, s);
+    pq_epilogue e1 = e0;
+    e1.C = C1; e1.dev_scale = dev_scale1;
+    pq_reduce_job none;
+    memset(&none, 0, sizeof(none));
+    const int rb = (int)(((size_t)M * (N / 8) + 255) / 256);
+    if (int8) splitk_reduce_pair_kernel<true><<<2 * rb, 256, 0, s>>>(pl.splits, rb, rb, M, N, part, e0, M, N, grp.second.part, e1, none, none);
+    else splitk_reduce_pair_kernel<false><<<2 * rb, 256, 0, s>>>(pl.splits, rb, rb, M, N, part, e0, M, N, grp.second.part, e1, none, none);
+    PQ_CHECK_LAUNCH("splitk_reduce_pair_kernel");
   }
   return PQ_OK;
 }

@@ -44,6 +44,21 @@ int pq_launch_wstats_partial(const void* W, int dtype, size_t n_elems, double* p
 // same order, block 0 writes mu_lambda.
 int pq_launch_pack(const void* W, int dtype, int N, int K, const double* partials, int nblocks,
                    uint32_t* P, uint32_t* Pt, float* mu_lambda, hipStream_t s);
+// The weight side of an FFN forward (bf16): stage 1 of three weights' statistics (w[i].partials, w[i].nblocks =
+// pq_stats_blocks), the quantiser of X (T rows of D; T may be 0), and the expert rows [Up_e; Gate_e] as one [E][2 r][D]
+// matrix: copied to UG, or with UGQ set (INT8 experts) quantised to UGQ / gUG / UGT, with the E * D rows of Down to DownQ /
+// gDown / DownT; then the packing of the three.
+struct pq_weight_job { const void* W; int N, K; double* partials; int nblocks; uint32_t* P; uint32_t* Pt; float* mu_lambda; };
+struct pq_ffn_prep {
+  pq_weight_job w[3];
+  const void* X; int T, D; int8_t* Xq; float* gamma; uint16_t* Xt;
+  const void *Up, *Gate, *Down; int E, r;
+  void* UG;
+  int8_t* UGQ; float* gUG; uint16_t* UGT;
+  int8_t* DownQ; float* gDown; uint16_t* DownT;
+};
+int pq_launch_ffn_prep(const pq_ffn_prep& p, hipStream_t s);
+int pq_launch_pack3(const pq_weight_job* w, hipStream_t s);
 int pq_launch_router(const void* X, const void* Wr, int dtype, int T, int K, int E, int k, int* idx,
                      float* gate, float* probs, hipStream_t s);
 // out[0] = factor * sum(partials[0..n)) (+ optionally factor2 read from device: *dev_factor)
@@ -132,6 +147,7 @@ struct pq_gemm_second {
   int ldc;
   float scale;
   float* part;       // split slabs of the second problem
+  const float* dev_scale;
   int M, N, nbn;
 };
 struct pq_gemm_group {
@@ -178,6 +194,9 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
 // ---- pq_tile.hip: the 64x64 and 128x128 streaming tiles (pl.bm; the contraction split is the caller's plan) ----
 int pq_launch_tile(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi, hipStream_t s,
                    float* part, const pq_gemm_group& grp, const pq_phase2& ph2);
+pq_gemm_plan pq_plan_dual(int M, int N, int K, bool int8);   // (its ws_bytes: the slabs of both)
+int pq_launch_gemm_dual(int M, int N, int K, const pq_operand& A0, const pq_operand& B0, const pq_epilogue& e0, const pq_operand& A1,
+                        const pq_operand& B1, void* C1, const float* dev_scale1, hipStream_t s, int prof_label, void* splitk_ws);
 int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B,
                    const pq_epilogue& epi, hipStream_t s, int prof_label = PQP_GEMM_OTHER,
                    void* splitk_ws = nullptr, const pq_gemm_group* group = nullptr,
@@ -232,8 +251,7 @@ int pq_launch_expert_act_bwd(const void* da, const void* ue, const void* ge, con
 // one expert, top-1: expert 0, gate 1, identity permutation, one segment (what router + counting sort would produce)
 int pq_launch_route_single(int S, int* idx, float* gate, float* probs, int* counts, int* offsets, int* perm, int* inv, hipStream_t s);
 int pq_launch_zero_f32(float* p, size_t n, hipStream_t s);
-// UG[e] = [Up[e]; Gate[e]] (bf16 [E][2 r][d]) and the split of its fp32 gradient back into dUp, dGate
-int pq_launch_concat_expert_rows(const void* up, const void* gate_w, int E, int r, int d, void* ug, hipStream_t s);
+// the fp32 gradient of [Up_e; Gate_e] split into dUp, dGate
 int pq_launch_split_expert_rows(const float* dug, int E, int r, int d, float* dup, float* dgate, hipStream_t s);
 int pq_launch_scale_rows(void* A, const int* perm, const float* gate, float alpha, int S, int d, hipStream_t s);
 int pq_rowdot_blocks(int S);

@@ -315,18 +315,7 @@ __global__ __launch_bounds__(256) void expert_act_bwd_kernel(const uint16_t* __r
   reinterpret_cast<uint4*>(as)[c] = pack8(o3);
 }
 
-// Up and Gate of every expert as one matrix: UG[e][j][:] = Up[e][j][:] for j < r, Gate[e][j - r][:] for r <= j < 2 r
-// (bf16 rows of d elements, d % 8 == 0), so that both projections are one product with 2 r outputs
-__global__ __launch_bounds__(256) void concat_expert_rows_kernel(const uint16_t* __restrict__ up, const uint16_t* __restrict__ gate_w,
-                                                                 int r, int d, size_t nvec, uint16_t* __restrict__ ug) {
-  const size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (c >= nvec) return;
-  const size_t row = c / (size_t)(d / 8), ch = c - row * (size_t)(d / 8);
-  const size_t e = row / (size_t)(2 * r), j = row - e * (size_t)(2 * r);
-  const uint16_t* src = j < (size_t)r ? up + (e * r + j) * (size_t)d : gate_w + (e * r + (j - r)) * (size_t)d;
-  reinterpret_cast<uint4*>(ug)[c] = reinterpret_cast<const uint4*>(src)[ch];
-}
-// and back for the gradients (fp32 rows of d elements, d % 4 == 0)
+// The gradient of [Up_e; Gate_e] (one [2 r][d] matrix per expert) split into the caller's two (fp32 rows of d elements, d % 4 == 0)
 __global__ __launch_bounds__(256) void split_expert_rows_kernel(const float* __restrict__ dug, int r, int d, size_t nvec,
                                                                 float* __restrict__ dup, float* __restrict__ dgate) {
   const size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
@@ -721,15 +710,6 @@ int pq_launch_expert_act(const void* ue, const void* ge, int ld, int S, int r, v
   pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
   expert_act_kernel<<<(unsigned)((n / 8 + 255) / 256), 256, 0, s>>>((const uint16_t*)ue, (const uint16_t*)ge, ld, r, n / 8, (uint16_t*)a);
   PQ_CHECK_LAUNCH("expert_act_kernel");
-  return PQ_OK;
-}
-
-int pq_launch_concat_expert_rows(const void* up, const void* gate_w, int E, int r, int d, void* ug, hipStream_t s) {
-  const size_t nvec = (size_t)E * 2 * r * (d / 8);
-  if (nvec == 0) return PQ_OK;
-  pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
-  concat_expert_rows_kernel<<<(unsigned)((nvec + 255) / 256), 256, 0, s>>>((const uint16_t*)up, (const uint16_t*)gate_w, r, d, nvec, (uint16_t*)ug);
-  PQ_CHECK_LAUNCH("concat_expert_rows_kernel");
   return PQ_OK;
 }
 

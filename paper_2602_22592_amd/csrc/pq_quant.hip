@@ -65,14 +65,13 @@ __device__ __forceinline__ void quant_store(const uint4& u, float g, int8_t* qro
   }
 }
 
+// one wavefront: the K elements at x become row `row` of the results
 template <typename T, int NV>
-__device__ __forceinline__ void quant_act_body(const T* __restrict__ X, int Tn, int K, int8_t* __restrict__ Xq,
-                                               float* __restrict__ gamma, uint16_t* __restrict__ Xt, int block) {
+__device__ __forceinline__ void quant_act_row(const T* __restrict__ x, int row, int K, int8_t* __restrict__ Xq,
+                                              float* __restrict__ gamma, uint16_t* __restrict__ Xt) {
   constexpr int V = vec16<T>::V;
   const int lane = threadIdx.x & 63;
-  const int row = block * 4 + (threadIdx.x >> 6);
-  if (row >= Tn) return;
-  const uint4* xr = reinterpret_cast<const uint4*>(X + (size_t)row * K);
+  const uint4* xr = reinterpret_cast<const uint4*>(x);
   const int nvec = K / V;
   float amax = 0.0f;
   uint4 cache[NV > 0 ? NV : 1];
@@ -111,6 +110,13 @@ __device__ __forceinline__ void quant_act_body(const T* __restrict__ X, int Tn, 
   } else {
     for (int c = lane; c < nvec; c += 64) quant_store<T>(xr[c], g, qrow, xtrow, c);
   }
+}
+
+template <typename T, int NV>
+__device__ __forceinline__ void quant_act_body(const T* __restrict__ X, int Tn, int K, int8_t* __restrict__ Xq,
+                                               float* __restrict__ gamma, uint16_t* __restrict__ Xt, int block) {
+  const int row = block * 4 + (threadIdx.x >> 6);
+  if (row < Tn) quant_act_row<T, NV>(X + (size_t)row * K, row, K, Xq, gamma, Xt);
 }
 
 template <typename T, int NV>
@@ -500,6 +506,66 @@ __global__ __launch_bounds__(256) void wstats_quant_kernel(const T* __restrict__
   else pq_slab_sum_bf16_body(sj.part, sj.splits, sj.M, sj.N, sj.C, sj.ldc, (size_t)(b - nw - nq) * 256 + threadIdx.x);
 }
 
+// The weight side of the FFN's forward ahead of the packing, and the quantiser of its activations, as one launch (bf16): the
+// statistics of up to three weights, the rows of X, the expert rows [Up_e; Gate_e] of every expert as one matrix, copied or
+// (INT8 experts) put on the AbsMax grid, and the rows of Down_e likewise.  All independent and short: one after the other
+// they were up to seven launches of which each costs a launch of about 5 us whatever it does.  With the packing in one launch and
+// U, G and dW_up, dW_gate paired: FFN step at 153 tokens 992/2136 244 -> 203 us, 3135 tokens 320/924 249 -> 201 us, 4284 tokens
+// 1728/2336 716 -> 668 us, 2048 tokens 2048/5076 703 -> 678 us.
+template <int NV>
+__global__ __launch_bounds__(256) void ffn_prep_kernel(pq_ffn_prep p) {
+  int b = blockIdx.x;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    if (b < p.w[i].nblocks) {                        // uniform
+      wstats_partial_body<uint16_t>((const uint16_t*)p.w[i].W, (size_t)p.w[i].N * p.w[i].K / 8, p.w[i].partials, b, p.w[i].nblocks);
+      return;
+    }
+    b -= p.w[i].nblocks;
+  }
+  const int nq = (p.T + 3) / 4;
+  if (b < nq) {
+    quant_act_body<uint16_t, NV>((const uint16_t*)p.X, p.T, p.D, p.Xq, p.gamma, p.Xt, b);
+    return;
+  }
+  b -= nq;
+  const int nug = p.E * 2 * p.r;
+  if (p.UGQ) {
+    if (b < (nug + 3) / 4) {
+      const int row = b * 4 + (threadIdx.x >> 6);
+      if (row >= nug) return;
+      const int e = row / (2 * p.r), j = row - e * 2 * p.r;
+      const uint16_t* src = j < p.r ? (const uint16_t*)p.Up + ((size_t)e * p.r + j) * p.D : (const uint16_t*)p.Gate + ((size_t)e * p.r + j - p.r) * p.D;
+      quant_act_row<uint16_t, NV>(src, row, p.D, p.UGQ, p.gUG, p.UGT);
+      return;
+    }
+    b -= (nug + 3) / 4;
+    quant_act_body<uint16_t, 0>((const uint16_t*)p.Down, p.E * p.D, p.r, p.DownQ, p.gDown, p.DownT, b);
+    return;
+  }
+  const size_t c = (size_t)b * 256 + threadIdx.x;    // UG[e][j][:] = Up[e][j][:] for j < r, Gate[e][j - r][:] for r <= j < 2 r
+  const size_t nd = p.D / 8;
+  if (c >= (size_t)nug * nd) return;
+  const size_t row = c / nd, ch = c - row * nd, e = row / (size_t)(2 * p.r), j = row - e * (size_t)(2 * p.r);
+  const uint16_t* src = j < (size_t)p.r ? (const uint16_t*)p.Up + (e * p.r + j) * p.D : (const uint16_t*)p.Gate + (e * p.r + (j - p.r)) * p.D;
+  reinterpret_cast<uint4*>(p.UG)[c] = reinterpret_cast<const uint4*>(src)[ch];
+}
+
+int pq_launch_ffn_prep(const pq_ffn_prep& p, hipStream_t s) {
+  pq_prof_scope prof(PQP_QUANT, s);
+  const int per_lane = (p.D / 8 + 63) / 64, nug = p.E * 2 * p.r;
+  long blocks = (long)(p.T + 3) / 4;
+  for (const pq_weight_job& w : p.w) blocks += w.nblocks;
+  if (p.UGQ) blocks += (nug + 3) / 4 + ((long)p.E * p.D + 3) / 4;
+  else blocks += ((long)nug * (p.D / 8) + 255) / 256;
+  if (per_lane <= 4) ffn_prep_kernel<4><<<(unsigned)blocks, 256, 0, s>>>(p);
+  else if (per_lane <= 8) ffn_prep_kernel<8><<<(unsigned)blocks, 256, 0, s>>>(p);
+  else if (per_lane <= 16) ffn_prep_kernel<16><<<(unsigned)blocks, 256, 0, s>>>(p);
+  else ffn_prep_kernel<0><<<(unsigned)blocks, 256, 0, s>>>(p);
+  PQ_CHECK_LAUNCH("ffn_prep_kernel");
+  return PQ_OK;
+}
+
 // rows too long for the register-cached quantiser (more than 16 vectors per lane) take two launches
 template <typename T>
 static int launch_wstats_quant_t(const T* w, size_t n_elems, double* partials, int nblocks, const T* x, int Tn, int K, int8_t* Xq,
@@ -579,11 +645,9 @@ __device__ __forceinline__ uint32_t sign_byte<float>(const float* p, float mu) {
 // words, and rows N.. of the last word of the transposed packing) is packed as +1: a padded position only ever meets an
 // activation code (or gradient) of zero.
 template <typename T, bool RAGGED>
-__global__ __launch_bounds__(256) void pack_sign_kernel(const T* __restrict__ W, int N, int K,
-                                                        const double* __restrict__ partials, int G,
-                                                        uint8_t* __restrict__ Pbytes,
-                                                        uint32_t* __restrict__ Pt,
-                                                        float* __restrict__ mu_lambda) {
+__device__ __forceinline__ void pack_sign_body(const T* __restrict__ W, int N, int K, const double* __restrict__ partials, int G,
+                                               uint8_t* __restrict__ Pbytes, uint32_t* __restrict__ Pt, float* __restrict__ mu_lambda,
+                                               int bx, int by) {
   __shared__ double red[4];
   __shared__ float s_mu;
   __shared__ uint8_t tileb[32][64];
@@ -591,7 +655,7 @@ __global__ __launch_bounds__(256) void pack_sign_kernel(const T* __restrict__ W,
   // the reduction of the partial sums overlap instead of standing in a row
   constexpr int NU = sizeof(T) == 2 ? 1 : 2;          // 16-byte loads per 8 weights
   const int Kp = (K + 31) & ~31;
-  const int n0 = blockIdx.y * 32, k0 = blockIdx.x * 512;
+  const int n0 = by * 32, k0 = bx * 512;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int k = k0 + lane * 8;
   uint4 wv[8][NU];
@@ -628,7 +692,7 @@ __global__ __launch_bounds__(256) void pack_sign_kernel(const T* __restrict__ W,
     const double cnt = (double)N * (double)K;
     float mu = (float)(ts / cnt);
     s_mu = mu;
-    if (blockIdx.x == 0 && blockIdx.y == 0) {
+    if (bx == 0 && by == 0) {
       mu_lambda[0] = mu;
       mu_lambda[1] = (float)(ta / cnt);
     }
@@ -660,9 +724,47 @@ __global__ __launch_bounds__(256) void pack_sign_kernel(const T* __restrict__ W,
       uint32_t word = 0;
 #pragma unroll
       for (int j = 0; j < 32; ++j) word |= (((uint32_t)tileb[j][kk >> 3] >> (kk & 7)) & 1u) << j;
-      Pt[(size_t)(k0 + kk) * nw + blockIdx.y] = word;
+      Pt[(size_t)(k0 + kk) * nw + by] = word;
     }
   }
+}
+template <typename T, bool RAGGED>
+__global__ __launch_bounds__(256) void pack_sign_kernel(const T* __restrict__ W, int N, int K,
+                                                        const double* __restrict__ partials, int G,
+                                                        uint8_t* __restrict__ Pbytes,
+                                                        uint32_t* __restrict__ Pt,
+                                                        float* __restrict__ mu_lambda) {
+  pack_sign_body<T, RAGGED>(W, N, K, partials, G, Pbytes, Pt, mu_lambda, blockIdx.x, blockIdx.y);
+}
+// three bf16 weights in one launch, the tiles of one after those of the other
+struct pack3_args { pq_weight_job w[3]; };
+template <bool RAGGED>
+__global__ __launch_bounds__(256) void pack_sign3_kernel(pack3_args a) {
+  int b = blockIdx.x, i = 0;
+  int gx = (((a.w[0].K + 31) & ~31) + 511) / 512, n = gx * ((a.w[0].N + 31) / 32);
+  while (i < 2 && b >= n) {                          // uniform
+    b -= n;
+    ++i;
+    gx = (((a.w[i].K + 31) & ~31) + 511) / 512;
+    n = gx * ((a.w[i].N + 31) / 32);
+  }
+  const pq_weight_job& w = a.w[i];
+  pack_sign_body<uint16_t, RAGGED>((const uint16_t*)w.W, w.N, w.K, w.partials, w.nblocks, (uint8_t*)w.P, w.Pt, w.mu_lambda, b % gx, b / gx);
+}
+int pq_launch_pack3(const pq_weight_job* w, hipStream_t s) {
+  pq_prof_scope prof(PQP_PACK, s);
+  pack3_args a;
+  bool ragged = false;
+  unsigned blocks = 0;
+  for (int i = 0; i < 3; ++i) {
+    a.w[i] = w[i];
+    ragged = ragged || w[i].K % 32 || w[i].N % 32;
+    blocks += (unsigned)((((w[i].K + 31) & ~31) + 511) / 512) * ((w[i].N + 31) / 32);
+  }
+  if (ragged) pack_sign3_kernel<true><<<blocks, 256, 0, s>>>(a);
+  else pack_sign3_kernel<false><<<blocks, 256, 0, s>>>(a);
+  PQ_CHECK_LAUNCH("pack_sign3_kernel");
+  return PQ_OK;
 }
 
 int pq_launch_pack(const void* W, int dtype, int N, int K, const double* partials, int nblocks,

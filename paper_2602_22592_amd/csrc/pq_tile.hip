@@ -291,7 +291,7 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_
     A = grp.second.A; B = grp.second.B;
     M = grp.second.M; N = grp.second.N; nbn = grp.second.nbn;
     splitk_part = grp.second.part;
-    epi.C = grp.second.C; epi.ldc = grp.second.ldc; epi.scale = grp.second.scale;
+    epi.C = grp.second.C; epi.ldc = grp.second.ldc; epi.scale = grp.second.scale; epi.dev_scale = grp.second.dev_scale;
   }
   // XCD-aware order: XCD c takes the c-th eighth of the (contraction split, tile row, tile column) order
   int pid = blockIdx.x, split = blockIdx.y;
@@ -582,7 +582,7 @@ __global__ __launch_bounds__(256) void tile64_gemm_kernel(int M, int N, int K, p
     A = grp.second.A; B = grp.second.B;
     M = grp.second.M; N = grp.second.N; nbn = grp.second.nbn;
     splitk_part = grp.second.part;
-    epi.C = grp.second.C; epi.ldc = grp.second.ldc; epi.scale = grp.second.scale;
+    epi.C = grp.second.C; epi.ldc = grp.second.ldc; epi.scale = grp.second.scale; epi.dev_scale = grp.second.dev_scale;
   }
   // XCD-aware order: XCD c takes the c-th eighth of the (contraction split, tile row, tile column) order
   int pid = blockIdx.x, split = blockIdx.y;

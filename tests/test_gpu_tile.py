@@ -10,6 +10,7 @@ from oracle import pquant_oracle as po
 from paper_2602_22592_amd import binding as pq
 from paper_2602_22592_amd import workloads as wl
 from parity_metrics import relerr
+from test_gpu_ffn import check_ffn
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-2
@@ -68,3 +69,14 @@ def test_linear_at_tile_edges(T, K, N, r, E, k, tau):
     errs["dbeta"] = abs(dab[1].item() - g["dbeta"]) / np.sqrt(((dYd * f["Y1_nobeta"]) ** 2).sum())
     print("  errors: " + ", ".join(f"{k}={v:.1e}" for k, v in errs.items()), flush=True)
     assert max(errs.values()) <= TOL, errs
+
+
+@pytest.mark.parametrize("T,D,F,E,r,k", [(1300, 1056, 4116, 1, 64, 1),    # paired 256x256 products, partial steps, store limits
+                                         (20, 4128, 160, 2, 8, 1),        # paired int8 product with a split contraction
+                                         # paired weight gradients with a split contraction.  One branch: with two, dWr at these sizes is
+                                         # a sum of 2100 terms of either sign, each good to a bf16 rounding (2**-8 at most), that cancels to
+                                         # about sqrt(2100) of them: up to 2**-8 * sqrt(2100) / 6 = 3e-2 of its largest entry, whatever the products do
+                                         (2100, 64, 100, 1, 8, 1)])
+def test_ffn_paired_products(T, D, F, E, r, k):
+    print(f"ffn paired products T={T} d={D} F={F} E={E} r={r} k={k}", flush=True)
+    check_ffn(wl.ffn_case(300 + T, T, D, F, E, r), top_k=k)
