@@ -681,9 +681,8 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
     const int* inv = (const int*)(cx + L.inv);
     float* rd = (float*)(ws + L.rd);
     n_red_a = S > 0 ? pq_rowdot_blocks(S) : 0;
-    if (int e = pq_launch_gather_rows(dY, perm, k, S, N, ws + L.dYp, s)) return e;
-    if (int e = pq_launch_rowdot(ws + L.dYp, cx + L.Ys, perm, gate, S, N, rd, red_a, s)) return e;
-    if (int e = pq_launch_scale_rows(ws + L.dYp, perm, gate, d->alpha, S, N, s)) return e;   // dYp <- alpha gate dYp
+    // row dots with the experts' outputs, and dYp = alpha gate dY in slot order
+    if (int e = pq_launch_slot_grad(dY, cx + L.Ys, perm, gate, d->alpha, true, k, S, N, ws + L.dYp, rd, red_a, s)) return e;
     pq_gemm_group g1{offsets, E, 1, 0, 0, S};
     pq_gemm_group g2{offsets, E, 2, 0, 0, S};
     if (S > 0) {  // dH_e = (alpha gate dY)_e B_e
@@ -716,8 +715,8 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
       if (int err = pq_launch_gemm(S, K, re, A, B, e, s, PQP_GEMM_EXPERT, sk_ws, &g1)) return err;
     }
     float* dlogit = (float*)(ws + L.dlogit);
-    if (int e = pq_launch_router_bwd(rd, inv, idx, (const float*)(cx + L.probs), d->alpha, T, k, E, dlogit, s)) return e;
-    if (int e = pq_launch_dwr(dlogit, X, T, K, E, (float*)(ws + L.dwr), dWr, s)) return e;
+    const pq_reduce_job rj[2] = {{red_a, n_red_a, 1.0f, nullptr, dalpha_dbeta}, {red_b, L.n_red_b, 1.0f, mulam + 1, dalpha_dbeta + 1}};
+    if (int e = pq_launch_dwr(rd, inv, idx, (const float*)(cx + L.probs), d->alpha, k, dlogit, X, T, K, E, (float*)(ws + L.dwr), dWr, rj, s)) return e;
     if (int e = pq_launch_combine_bwd(dX, ws + L.dXs, inv, dlogit, Wr, T, k, K, E, s)) return e;
   }
   if (hp8) {   // STE backward of the INT8 branch on the de-quantised factors; its dH GEMM leaves the partials of d alpha
@@ -728,7 +727,7 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
   // d alpha and d beta: both fixed-order sums of per-workgroup partials
   const pq_reduce_job jobs[2] = {{red_a, (T > 0 && (r > 0 || routed || hp8)) ? n_red_a : 0, 1.0f, nullptr, dalpha_dbeta},
                                  {red_b, L.n_red_b, 1.0f, mulam + 1, dalpha_dbeta + 1}};
-  bool jobs_done = false;
+  bool jobs_done = routed;   // (the routed path's own last reduction carries them)
   if (r > 0 && T > 0) {
     // dB = alpha * dY^T H and dA = dH^T X (dH already carries alpha): two narrow GEMMs over the same contraction,
     // one launch when their plans agree; the two scalar reductions then ride along with their split reduction

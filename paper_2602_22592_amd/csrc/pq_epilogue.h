@@ -55,8 +55,15 @@ template <bool INT8>
 // row_scale: sc0 / row_div[m] when the caller has it at hand (NaN = not given, it is formed here)
 __device__ __forceinline__ void epi_vec8(const pq_epilogue& e, epi_state& st, int m, int n, const uint4& r0,
                                          const uint4& r1, float row_scale = __builtin_nanf("")) {
-  const size_t ci = (size_t)m * e.ldc + n;
+  size_t ci = (size_t)m * e.ldc + n;
   if ((e.m_limit > 0 && m >= e.m_limit) || (e.n_limit > 0 && n >= e.n_limit)) return;
+  void* cdst = e.C;
+  if (e.m_split > 0) {                               // uniform
+    const int z = m / (2 * e.m_split), mm = m - z * 2 * e.m_split;
+    const bool hi = mm >= e.m_split;
+    ci = (size_t)(z * e.m_split + (hi ? mm - e.m_split : mm)) * e.ldc + n;
+    if (hi) cdst = e.C2;
+  }
   const bool half = e.n_limit > 0 && n + 8 > e.n_limit;   // only the first four columns exist
   if (e.out_kind == PQ_OUT_I32) {
     *reinterpret_cast<uint4*>((int*)e.C + ci) = r0;
@@ -114,8 +121,8 @@ __device__ __forceinline__ void epi_vec8(const pq_epilogue& e, epi_state& st, in
           make_uint4(pack_bf16x2(val[0], val[1]), pack_bf16x2(val[2], val[3]), pack_bf16x2(val[4], val[5]),
                      pack_bf16x2(val[6], val[7]));
   } else {
-    *reinterpret_cast<float4*>((float*)e.C + ci) = make_float4(val[0], val[1], val[2], val[3]);
-    if (!half) *reinterpret_cast<float4*>((float*)e.C + ci + 4) = make_float4(val[4], val[5], val[6], val[7]);
+    *reinterpret_cast<float4*>((float*)cdst + ci) = make_float4(val[0], val[1], val[2], val[3]);
+    if (!half) *reinterpret_cast<float4*>((float*)cdst + ci + 4) = make_float4(val[4], val[5], val[6], val[7]);
   }
 }
 

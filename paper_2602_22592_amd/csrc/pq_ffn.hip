@@ -38,7 +38,7 @@ struct ffn_layout {
   // X~ instead of X)
   size_t UGQ, gUG, UGT, DownQ, gDown, DownT, XqP, gxP, aQ, gA, aT, ctx_total;
   // workspace
-  size_t stat, red_a, red_b, splitk, dHd, dU, dG, dYp, rd, da, du, dg, as, dXs, dlogit, dwr, dUG, ws_total;
+  size_t stat, red_a, red_b, splitk, dHd, dU, dG, dYp, rd, da, du, dg, as, dXs, dlogit, dwr, ws_total;
   int n_red_a, n_red_b;
 };
 
@@ -108,7 +108,6 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   L.da = w.take(S * r * 2); L.du = w.take(2 * S * r * 2); L.dg = L.du + S * r * 2; L.as = w.take(S * r * 2);
   L.dXs = w.take(S * D * 2); L.dlogit = w.take(T * E * 4);
   L.dwr = w.take(pq_dwr_scratch_bytes((int)T, (int)D, (int)E));
-  L.dUG = w.take(E * 2 * r * D * 4);
   L.ws_total = w.off;
   return L;
 }
@@ -251,9 +250,7 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
     const void* xqp = one ? (const void*)Xq : (const void*)(cx + L.XqP);
     const float* gxp = one ? (const float*)gx : (const float*)(cx + L.gxP);
     if (!one) {
-      if (int e = pq_launch_gather_rows(cx + L.Xt, perm, k, S, D, cx + L.Xp, s)) return e;
-      if (int e = pq_launch_gather_rows(Xq, perm, k, S, D / 2, cx + L.XqP, s)) return e;
-      if (int e = pq_launch_gather_f32(gx, perm, k, S, (float*)(cx + L.gxP), s)) return e;
+      if (int e = pq_launch_gather_quant_rows(cx + L.Xt, Xq, gx, perm, k, S, D, cx + L.Xp, (int8_t*)(cx + L.XqP), (float*)(cx + L.gxP), s)) return e;
     }
     {  // [u | g] = (q_x q_w^T) / (gamma_x gamma_w), bf16: both projections as one product with 2 r outputs per slot
       pq_operand A{xqp, D, PQ_SRC_KC8, nullptr};
@@ -379,12 +376,10 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
   const void* dyp = one ? dY : ws + L.dYp;
   // what the up and gate products multiplied: X, or with INT8 experts its de-quantised codes
   const void* xp = one ? (hp8 ? (const void*)(cx + L.Xt) : X) : (const void*)(cx + L.Xp);
-  if (!one)
-    if (int e = pq_launch_gather_rows(dY, perm, k, S, D, ws + L.dYp, s)) return e;
-  if (int e = pq_launch_rowdot(dyp, cx + L.Ys, perm, gate, S, D, rd, red_a, s)) return e;
-  // d alpha (row dots above) and d beta (partials of the dW_down GEMM): one launch for both fixed-order sums
-  if (int e = pq_launch_reduce_partials2(red_a, S > 0 ? L.n_red_a : 0, 1.0f, nullptr, dalpha_dbeta, red_b, L.n_red_b, 1.0f, ml_down + 1,
-                                         dalpha_dbeta + 1, s)) return e;
+  // row dots with the experts' outputs (d alpha, the gates' gradients) and dY in slot order
+  if (int e = pq_launch_slot_grad(dY, cx + L.Ys, perm, gate, d->alpha, false, k, S, D, one ? nullptr : ws + L.dYp, rd, red_a, s)) return e;
+  // d alpha and d beta (partials of the dW_down GEMM): both fixed-order sums ride along in the last reduction
+  const pq_reduce_job jobs[2] = {{red_a, S > 0 ? L.n_red_a : 0, 1.0f, nullptr, dalpha_dbeta}, {red_b, L.n_red_b, 1.0f, ml_down + 1, dalpha_dbeta + 1}};
   pq_gemm_group g1{offsets, E, 1, 0, 0, S};
   pq_gemm_group g2{offsets, E, 2, 0, 0, S};
   const pq_gemm_group* pg1 = one ? nullptr : &g1;
@@ -408,12 +403,11 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
     g2.c_stride = (long)D * r;
     if (int err = pq_launch_gemm(D, r, S, A, B, e, s, PQP_GEMM_EXPERT, sk, pg2)) return err;
     pq_operand Bx{xp, D, PQ_SRC_KS16, nullptr};
-    {   // d[Up_e; Gate_e] = [du | dg]^T Xp, then split into the caller's two gradients
+    {   // d[Up_e; Gate_e] = [du | dg]^T Xp, the halves of its rows stored to the caller's two gradients
       pq_operand Aug{ws + L.du, 2 * r, PQ_SRC_KS16, nullptr};
-      e.C = ws + L.dUG; e.ldc = D;
-      g2.c_stride = (long)2 * r * D;
+      e.C = dUp; e.C2 = dGate; e.m_split = r; e.ldc = D;
+      g2.c_stride = (long)r * D;
       if (int err = pq_launch_gemm(2 * r, D, S, Aug, Bx, e, s, PQP_GEMM_EXPERT, sk, pg2)) return err;
-      if (int err = pq_launch_split_expert_rows((const float*)(ws + L.dUG), E, r, D, dUp, dGate, s)) return err;
     }
   }
   if (S > 0) {  // dXs = [du | dg] [Up_e; Gate_e]  (INT8 experts: the de-quantised rows)
@@ -426,10 +420,9 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
   }
   float* dlogit = (float*)(ws + L.dlogit);
   if (one) {   // softmax over one logit is constant: no gradient reaches the router
-    if (int e = pq_launch_zero_f32(dWr, (size_t)D, s)) return e;
+    if (int e = pq_launch_dwr(nullptr, nullptr, nullptr, nullptr, 0.0f, k, nullptr, X, T, D, E, (float*)(ws + L.dwr), dWr, jobs, s)) return e;
     return pq_launch_combine_bwd(dX, ws + L.dXs, inv, nullptr, Wr, T, k, D, 0, s);
   }
-  if (int e = pq_launch_router_bwd(rd, inv, idx, (const float*)(cx + L.probs), d->alpha, T, k, E, dlogit, s)) return e;
-  if (int e = pq_launch_dwr(dlogit, X, T, D, E, (float*)(ws + L.dwr), dWr, s)) return e;
+  if (int e = pq_launch_dwr(rd, inv, idx, (const float*)(cx + L.probs), d->alpha, k, dlogit, X, T, D, E, (float*)(ws + L.dwr), dWr, jobs, s)) return e;
   return pq_launch_combine_bwd(dX, ws + L.dXs, inv, dlogit, Wr, T, k, D, E, s);
 }

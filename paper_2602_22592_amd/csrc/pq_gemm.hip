@@ -1280,7 +1280,7 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
   epi_begin(epi, st);
   float* slab = splitk_part ? splitk_part + (size_t)split * M * N : nullptr;
   const bool plain = !slab && epi.out_kind == PQ_OUT_F32 && !epi.col_div && !epi.maskW && !epi.accumulate && !epi.dot_comp &&
-                     !epi.sign_bytes;                 // uniform
+                     !epi.sign_bytes && epi.m_split == 0;                 // uniform
   unsigned tid_e = threadIdx.x;
   asm volatile("" : "+v"(tid_e));
   const int lane_e = tid_e & 63, wave_e = tid_e >> 6;
@@ -2018,6 +2018,9 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
   if (ph2.K2 > 0 && grp.mode) return pq_set_error(PQ_ERR_BAD_ARG, "a fused second contraction needs the plain MFMA engine");
   if ((epi.n_limit > 0 || epi.m_limit > 0) && (epi.accumulate || epi.maskW || epi.dot_comp || epi.n_limit % 4 != 0))
     return pq_set_error(PQ_ERR_BAD_ARG, "store limits go with plain stores and a column limit that is a multiple of 4");
+  if (epi.m_split > 0 && (A.kind != PQ_SRC_KS16 || B.kind != PQ_SRC_KS16 || epi.out_kind != PQ_OUT_F32 || epi.accumulate || epi.maskW || epi.dot_comp ||
+                          epi.m_limit || epi.n_limit || M % (2 * epi.m_split) != 0))
+    return pq_set_error(PQ_ERR_BAD_ARG, "a second destination goes with plain fp32 weight gradients");
   // plain rank-128 products over many rows: the streaming kernel (callers that want per-block partial sums or the
   // slabs of a split contraction choose it themselves, since it changes how many of those there are)
   if (!grp.mode && ph2.K2 == 0 && !epi.partials && !epi.defer_reduce && pq_skinny_applies(M, N, K, A, B, epi))
@@ -2033,7 +2036,7 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
     if (grp.mode == 2) {
       const mode2_plan p2 = plan_mode2(M, N, grp.n_groups, K);
       pl.bm = pl.bn = p2.bm;
-      if (p2.splits > 1 && splitk_ws && epi.out_kind == PQ_OUT_F32 && epi.ldc == N && grp.c_stride == (long)M * N && N % 8 == 0 &&
+      if (p2.splits > 1 && splitk_ws && epi.out_kind == PQ_OUT_F32 && epi.ldc == N && grp.c_stride == (long)(epi.m_split ? epi.m_split : M) * N && N % 8 == 0 &&
           !epi.partials && !epi.dot_comp && !epi.sign_bytes && !epi.maskW && !epi.accumulate && !epi.row_div && !epi.col_div &&
           epi.m_limit == 0 && epi.n_limit == 0) {
         pl.splits = p2.splits;

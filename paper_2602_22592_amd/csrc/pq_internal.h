@@ -119,6 +119,10 @@ struct pq_epilogue {
   // columns >= n_limit are computed but not stored (0 = no limit; n_limit % 4 == 0; plain stores only: no
   // accumulate, mask or dot_comp, whose loads would run past a row's end)
   int m_limit, n_limit;
+  // optional second destination: of every 2 * m_split rows the first m_split go to C, the others to C2 (both with their rows
+  // closed up): the gradients of matrices that are multiplied as one.  fp32, plain stores only.
+  void* C2;
+  int m_split;
 };
 
 // Optional second contraction accumulated into the same output tile (the rank-r branch fused into
@@ -239,8 +243,9 @@ int pq_launch_decode_ffn(int L, int B, int D, int F, int r, int E, int topk, flo
 // ---- pq_moe.hip ---------------------------------------------------------------------------
 int pq_launch_route(const int* idx, int S, int E, int* counts, int* offsets, int* perm, int* inv, hipStream_t s);
 int pq_launch_gather_rows(const void* src, const int* perm, int k, int S, int d, void* dst, hipStream_t s);
-// dst[pos] = src[perm[pos] / k]  (fp32 scalars, e.g. a token's gamma carried to its slots)
-int pq_launch_gather_f32(const float* src, const int* perm, int k, int S, float* dst, hipStream_t s);
+// the same for rows of bf16 with their INT8 codes and gammas (d % 16 == 0)
+int pq_launch_gather_quant_rows(const void* xt, const int8_t* xq, const float* gx, const int* perm, int k, int S, int d, void* xt_out,
+                                int8_t* xq_out, float* gx_out, hipStream_t s);
 // rows of F elements of which the first Fv exist (padded widths): the rest is written as zero
 int pq_launch_swiglu_quant(const void* U, const void* G, int T, int F, int Fv, int8_t* Hq, float* gamma, void* Ht, hipStream_t s);
 int pq_launch_swiglu_bwd(const void* dHd, const void* U, const void* G, int T, int F, int Fv, void* dU, void* dG, hipStream_t s);
@@ -250,18 +255,17 @@ int pq_launch_expert_act_bwd(const void* da, const void* ue, const void* ge, con
                              float alpha, int S, int r, int ld, void* du, void* dg, void* as, hipStream_t s);
 // one expert, top-1: expert 0, gate 1, identity permutation, one segment (what router + counting sort would produce)
 int pq_launch_route_single(int S, int* idx, float* gate, float* probs, int* counts, int* offsets, int* perm, int* inv, hipStream_t s);
-int pq_launch_zero_f32(float* p, size_t n, hipStream_t s);
-// the fp32 gradient of [Up_e; Gate_e] split into dUp, dGate
-int pq_launch_split_expert_rows(const float* dug, int E, int r, int d, float* dup, float* dgate, hipStream_t s);
-int pq_launch_scale_rows(void* A, const int* perm, const float* gate, float alpha, int S, int d, hipStream_t s);
 int pq_rowdot_blocks(int S);
-int pq_launch_rowdot(const void* A, const void* B, const int* perm, const float* gate, int S, int d, float* rd, double* partial,
-                     hipStream_t s);
+// rd[pos] = <dY[perm[pos] / k], Ys[pos]>, partial[pq_rowdot_blocks(S)] of sum gate * rd, dst[pos] (may be NULL) = the dY row
+// [* alpha * gate]
+int pq_launch_slot_grad(const void* dY, const void* Ys, const int* perm, const float* gate, float alpha, bool scale, int k, int S, int d,
+                        void* dst, float* rd, double* partial, hipStream_t s);
 int pq_launch_combine_fwd(void* Y, const void* Ys, const int* inv, const float* gate, float alpha, int T, int k, int d, hipStream_t s);
-int pq_launch_router_bwd(const float* rd, const int* inv, const int* idx, const float* probs, float alpha, int T, int k, int E,
-                         float* dlogit, hipStream_t s);
 size_t pq_dwr_scratch_bytes(int T, int d, int E);
-int pq_launch_dwr(const float* dlogit, const void* X, int T, int d, int E, float* part, float* dWr, hipStream_t s);
+// router backward and dWr: dlogit [T][E] from rd and the softmax, dWr = dlogit^T X; rd == NULL: dWr = 0.  jobs: two scalar
+// reductions of partials that earlier launches left, in the last launch.
+int pq_launch_dwr(const float* rd, const int* inv, const int* idx, const float* probs, float alpha, int k, float* dlogit, const void* X, int T,
+                  int d, int E, float* part, float* dWr, const pq_reduce_job* jobs, hipStream_t s);
 int pq_launch_combine_bwd(void* dX, const void* dXs, const int* inv, const float* dlogit, const void* Wr, int T, int k, int d, int E,
                           hipStream_t s);
 int pq_launch_lincomb(void* out, const void* x0, const void* x1, const void* x2, const void* x3, float c0, float c1, float c2,

@@ -136,11 +136,6 @@ __global__ __launch_bounds__(256) void route_single_kernel(int S, int* __restric
   perm[s] = s;
   inv[s] = s;
 }
-__global__ __launch_bounds__(256) void zero_f32_kernel(float* __restrict__ p, size_t n) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0.0f;
-}
-
 // dst[pos][:] = src[perm[pos] / k][:]   (rows of d bf16, d % 8 == 0), one wavefront per row
 __global__ __launch_bounds__(256) void gather_rows_kernel(const uint16_t* __restrict__ src, const int* __restrict__ perm, int k,
                                                           int S, int d, uint16_t* __restrict__ dst) {
@@ -152,10 +147,21 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint16_t* __rest
   for (int c = lane; c < d / 8; c += 64) d4[c] = s4[c];
 }
 
-__global__ __launch_bounds__(256) void gather_f32_kernel(const float* __restrict__ src, const int* __restrict__ perm, int k, int S,
-                                                         float* __restrict__ dst) {
-  const int pos = blockIdx.x * 256 + threadIdx.x;
-  if (pos < S) dst[pos] = src[perm[pos] / k];
+// the same for a row of bf16, its INT8 codes and its gamma (INT8 experts), one wavefront per slot
+__global__ __launch_bounds__(256) void gather_quant_rows_kernel(const uint16_t* __restrict__ xt, const int8_t* __restrict__ xq,
+                                                                const float* __restrict__ gx, const int* __restrict__ perm, int k, int S,
+                                                                int d, uint16_t* __restrict__ xt_out, int8_t* __restrict__ xq_out,
+                                                                float* __restrict__ gx_out) {
+  const int pos = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (pos >= S) return;
+  const int t = perm[pos] / k;
+  const uint4* a = reinterpret_cast<const uint4*>(xt + (size_t)t * d);
+  const uint4* q = reinterpret_cast<const uint4*>(xq + (size_t)t * d);
+  uint4* ao = reinterpret_cast<uint4*>(xt_out + (size_t)pos * d);
+  uint4* qo = reinterpret_cast<uint4*>(xq_out + (size_t)pos * d);
+  for (int c = lane; c < d / 8; c += 64) ao[c] = a[c];
+  for (int c = lane; c < d / 16; c += 64) qo[c] = q[c];
+  if (lane == 0) gx_out[pos] = gx[t];
 }
 
 // ---- the gated unit with fused AbsMax re-quantisation (one wavefront per token) -------------
@@ -315,60 +321,60 @@ __global__ __launch_bounds__(256) void expert_act_bwd_kernel(const uint16_t* __r
   reinterpret_cast<uint4*>(as)[c] = pack8(o3);
 }
 
-// The gradient of [Up_e; Gate_e] (one [2 r][d] matrix per expert) split into the caller's two (fp32 rows of d elements, d % 4 == 0)
-__global__ __launch_bounds__(256) void split_expert_rows_kernel(const float* __restrict__ dug, int r, int d, size_t nvec,
-                                                                float* __restrict__ dup, float* __restrict__ dgate) {
-  const size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (c >= nvec) return;
-  const size_t row = c / (size_t)(d / 4), ch = c - row * (size_t)(d / 4);
-  const size_t e = row / (size_t)(2 * r), j = row - e * (size_t)(2 * r);
-  float* dst = j < (size_t)r ? dup + (e * r + j) * (size_t)d : dgate + (e * r + (j - r)) * (size_t)d;
-  reinterpret_cast<uint4*>(dst)[ch] = reinterpret_cast<const uint4*>(dug)[c];
-}
-
-// rd[pos] = <A[pos,:], B[pos,:]> (fp32), partial[block] = sum gate[perm[pos]] * rd[pos]  (for d alpha)
-__global__ __launch_bounds__(256) void rowdot_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Bm,
-                                                     const int* __restrict__ perm, const float* __restrict__ gate, int S, int d,
-                                                     float* __restrict__ rd, double* __restrict__ partial) {
+// One pass over the upstream gradient in slot order: rd[pos] = <dY[t], Ys[pos]> (fp32) with t = perm[pos] / k,
+// partial[block] = sum gate[perm[pos]] * rd[pos] (for d alpha), and, unless dst is NULL, dst[pos] = dY[t], with SCALE times
+// alpha * gate (the upstream gradient of an expert's output).  Gather, dot and scaling in passes of their own read and wrote
+// the slot rows three times: routed linear of 1531 tokens 1056 -> 3104, two experts each, 6.9 + 8.2 + 6.8 us.
+template <bool SCALE>
+__global__ __launch_bounds__(256) void slot_grad_kernel(const uint16_t* __restrict__ dY, const uint16_t* __restrict__ Ys,
+                                                        const int* __restrict__ perm, const float* __restrict__ gate, float alpha, int k,
+                                                        int S, int d, uint16_t* __restrict__ dst, float* __restrict__ rd,
+                                                        double* __restrict__ partial) {
   __shared__ double red[4];
   const int pos = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   double contrib = 0.0;
   if (pos < S) {
-    const uint4* a4 = reinterpret_cast<const uint4*>(A + (size_t)pos * d);
-    const uint4* b4 = reinterpret_cast<const uint4*>(Bm + (size_t)pos * d);
+    const int slot = perm[pos];
+    const float gt = gate[slot], sc = alpha * gt;
+    const uint4* a4 = reinterpret_cast<const uint4*>(dY + (size_t)(slot / k) * d);
+    const uint4* b4 = reinterpret_cast<const uint4*>(Ys + (size_t)pos * d);
+    uint4* o4 = reinterpret_cast<uint4*>(dst + (size_t)pos * d);
+    const int n = d / 8;
     float acc = 0.0f;
-    for (int c = lane; c < d / 8; c += 64) {
-      float x[8], y[8];
-      unpack8(a4[c], x);
-      unpack8(b4[c], y);
+    for (int cb = lane; cb < n; cb += 256) {          // eight loads in flight (past the end: the last vector, dropped)
+      uint4 a[4], b[4];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) acc += x[j] * y[j];
+      for (int q = 0; q < 4; ++q) {
+        const int c = min(cb + 64 * q, n - 1);
+        a[q] = a4[c];
+        b[q] = b4[c];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int c = cb + 64 * q;
+        if (c >= n) break;
+        float x[8], y[8];
+        unpack8(a[q], x);
+        unpack8(b[q], y);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc += x[j] * y[j];
+        if (dst) {                                    // uniform
+          if constexpr (SCALE) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] *= sc;
+            o4[c] = pack8(x);
+          } else o4[c] = a[q];
+        }
+      }
     }
     acc = wave_sum(acc);
     if (lane == 0) {
       rd[pos] = acc;
-      contrib = (double)gate[perm[pos]] * (double)acc;
+      contrib = (double)gt * (double)acc;
     }
   }
   const double t = block_sum_d<256>(contrib, red);
   if (threadIdx.x == 0) partial[blockIdx.x] = t;
-}
-
-// A[pos,:] *= alpha * gate[perm[pos]]  (rows of d bf16 in slot order, one wavefront per row): the upstream gradient of
-// an expert's output for slot (t, j) is alpha * gate[t][j] * dY[t]
-__global__ __launch_bounds__(256) void scale_rows_kernel(uint16_t* __restrict__ A, const int* __restrict__ perm,
-                                                         const float* __restrict__ gate, float alpha, int S, int d) {
-  const int pos = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (pos >= S) return;
-  const float sc = alpha * gate[perm[pos]];
-  uint4* a4 = reinterpret_cast<uint4*>(A + (size_t)pos * d);
-  for (int c = lane; c < d / 8; c += 64) {
-    float v[8];
-    unpack8(a4[c], v);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] *= sc;
-    a4[c] = pack8(v);
-  }
 }
 
 // Y[t,:] += alpha * sum_j gate[t,j] * Ys[inv[t*k+j], :]   (one wavefront per token)
@@ -396,20 +402,16 @@ __global__ __launch_bounds__(256) void combine_fwd_kernel(uint16_t* __restrict__
 }
 
 // dlogit[t,e] = sum_j dgate[t,j] * p[idx_j] * (1[e == idx_j] - p[e]),  dgate[t,j] = alpha * rd[inv[t*k+j]]
-__global__ __launch_bounds__(256) void router_bwd_kernel(const float* __restrict__ rd, const int* __restrict__ inv,
-                                                         const int* __restrict__ idx, const float* __restrict__ probs, float alpha,
-                                                         int T, int k, int E, float* __restrict__ dlogit) {
-  const int i = blockIdx.x * 256 + threadIdx.x;   // t * E + e
-  if (i >= T * E) return;
-  const int t = i / E, e = i % E;
-  const float pe = probs[i];
+__device__ __forceinline__ float router_dlogit(const float* __restrict__ rd, const int* __restrict__ inv, const int* __restrict__ idx,
+                                               const float* __restrict__ probs, float alpha, int k, int E, int t, int e) {
+  const float pe = probs[(size_t)t * E + e];
   float acc = 0.0f;
   for (int j = 0; j < k; ++j) {
     const int ej = idx[t * k + j];
     const float dgt = alpha * rd[inv[t * k + j]];
-    acc += dgt * probs[t * E + ej] * ((e == ej ? 1.0f : 0.0f) - pe);
+    acc += dgt * probs[(size_t)t * E + ej] * ((e == ej ? 1.0f : 0.0f) - pe);
   }
-  dlogit[i] = acc;
+  return acc;
 }
 
 // dWr partials: part[tc][e][c] = sum_{t in chunk tc} dlogit[t,e] * X[t,c]   (chunks of 256 tokens).
@@ -417,8 +419,10 @@ __global__ __launch_bounds__(256) void router_bwd_kernel(const float* __restrict
 // 32 tokens t0 + sg, t0 + sg + 8, ... with 16-byte loads of 8 columns, then the 8 subgroups are summed in LDS
 // in a fixed order.
 constexpr int DWR_CHUNK = 128;                      // tokens per workgroup (a multiple of 64)
-__global__ __launch_bounds__(256) void dwr_partial_kernel(const float* __restrict__ dlogit, const uint16_t* __restrict__ X, int T,
-                                                          int d, int E, float* __restrict__ part) {
+// dlogit is formed here, by every column block for itself; the first one leaves it in memory for the input gradient.
+__global__ __launch_bounds__(256) void dwr_partial_kernel(const float* __restrict__ rd, const int* __restrict__ inv, const int* __restrict__ idx,
+                                                          const float* __restrict__ probs, float alpha, int k, float* __restrict__ dlogit,
+                                                          const uint16_t* __restrict__ X, int T, int d, int E, float* __restrict__ part) {
   __shared__ float red[8][4][8][32];                 // [subgroup][expert % 4][column % 8][column group]
   __shared__ __attribute__((aligned(16))) float sdl[DWR_CHUNK][8];   // the chunk's dlogit for the eight experts of a pass (zero past E and past T)
   const int tid = threadIdx.x, cg = tid & 31, sg = tid >> 5;
@@ -430,8 +434,11 @@ __global__ __launch_bounds__(256) void dwr_partial_kernel(const float* __restric
     // a branch waits for its own latency, and the loop over tokens becomes a chain of them
     for (int o = tid; o < DWR_CHUNK * 8; o += 256) {
       const int tt = o >> 3, u = o & 7;
-      const float g = dlogit[(size_t)min(t0 + tt, T - 1) * E + min(e0 + u, E - 1)];
-      sdl[tt][u] = (t0 + tt < T && e0 + u < E) ? g : 0.0f;
+      const int t = min(t0 + tt, T - 1), e = min(e0 + u, E - 1);
+      const float g = router_dlogit(rd, inv, idx, probs, alpha, k, E, t, e);
+      const bool in = t0 + tt < T && e0 + u < E;
+      sdl[tt][u] = in ? g : 0.0f;
+      if (in && blockIdx.x == 0) dlogit[(size_t)t * E + e] = g;
     }
     __syncthreads();
     float acc[8][8];
@@ -479,8 +486,15 @@ __global__ __launch_bounds__(256) void dwr_partial_kernel(const float* __restric
     }
   }
 }
-// dWr = the chunks' partial sums added in chunk order (eight loads in flight per thread)
-__global__ __launch_bounds__(256) void dwr_final_kernel(const float* __restrict__ part, int nchunks, int n, float* __restrict__ dWr) {
+// dWr = the chunks' partial sums added in chunk order (eight loads in flight per thread; no chunks: zeros).  Two scalar
+// reductions of the same call (d alpha, d beta) ride along as the last workgroups.
+__global__ __launch_bounds__(256) void dwr_final_kernel(const float* __restrict__ part, int nchunks, int n, float* __restrict__ dWr,
+                                                        pq_reduce_job j0, pq_reduce_job j1) {
+  const int nb = (n + 255) / 256;
+  if ((int)blockIdx.x >= nb) {                       // uniform
+    pq_reduce_job_body((int)blockIdx.x == nb ? j0 : j1);
+    return;
+  }
   const int i = blockIdx.x * 256 + threadIdx.x;   // e * d + c
   if (i >= n) return;
   float acc = 0.0f;
@@ -653,14 +667,6 @@ int pq_launch_route_single(int S, int* idx, float* gate, float* probs, int* coun
   return PQ_OK;
 }
 
-int pq_launch_zero_f32(float* p, size_t n, hipStream_t s) {
-  if (n == 0) return PQ_OK;
-  pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
-  zero_f32_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(p, n);
-  PQ_CHECK_LAUNCH("zero_f32_kernel");
-  return PQ_OK;
-}
-
 int pq_launch_gather_rows(const void* src, const int* perm, int k, int S, int d, void* dst, hipStream_t s) {
   if (S == 0) return PQ_OK;
   pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
@@ -669,11 +675,12 @@ int pq_launch_gather_rows(const void* src, const int* perm, int k, int S, int d,
   return PQ_OK;
 }
 
-int pq_launch_gather_f32(const float* src, const int* perm, int k, int S, float* dst, hipStream_t s) {
+int pq_launch_gather_quant_rows(const void* xt, const int8_t* xq, const float* gx, const int* perm, int k, int S, int d, void* xt_out,
+                                int8_t* xq_out, float* gx_out, hipStream_t s) {
   if (S == 0) return PQ_OK;
   pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
-  gather_f32_kernel<<<(S + 255) / 256, 256, 0, s>>>(src, perm, k, S, dst);
-  PQ_CHECK_LAUNCH("gather_f32_kernel");
+  gather_quant_rows_kernel<<<(S + 3) / 4, 256, 0, s>>>((const uint16_t*)xt, xq, gx, perm, k, S, d, (uint16_t*)xt_out, xq_out, gx_out);
+  PQ_CHECK_LAUNCH("gather_quant_rows_kernel");
   return PQ_OK;
 }
 
@@ -713,15 +720,6 @@ int pq_launch_expert_act(const void* ue, const void* ge, int ld, int S, int r, v
   return PQ_OK;
 }
 
-int pq_launch_split_expert_rows(const float* dug, int E, int r, int d, float* dup, float* dgate, hipStream_t s) {
-  const size_t nvec = (size_t)E * 2 * r * (d / 4);
-  if (nvec == 0) return PQ_OK;
-  pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
-  split_expert_rows_kernel<<<(unsigned)((nvec + 255) / 256), 256, 0, s>>>(dug, r, d, nvec, dup, dgate);
-  PQ_CHECK_LAUNCH("split_expert_rows_kernel");
-  return PQ_OK;
-}
-
 int pq_launch_expert_act_bwd(const void* da, const void* ue, const void* ge, const void* a, const int* perm, const float* gate,
                              float alpha, int S, int r, int ld, void* du, void* dg, void* as, hipStream_t s) {
   if (S == 0) return PQ_OK;
@@ -734,21 +732,14 @@ int pq_launch_expert_act_bwd(const void* da, const void* ue, const void* ge, con
   return PQ_OK;
 }
 
-int pq_launch_scale_rows(void* A, const int* perm, const float* gate, float alpha, int S, int d, hipStream_t s) {
-  if (S <= 0) return PQ_OK;
-  pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
-  scale_rows_kernel<<<(S + 3) / 4, 256, 0, s>>>((uint16_t*)A, perm, gate, alpha, S, d);
-  PQ_CHECK_LAUNCH("scale_rows_kernel");
-  return PQ_OK;
-}
-
 int pq_rowdot_blocks(int S) { return (S + 3) / 4; }
-int pq_launch_rowdot(const void* A, const void* B, const int* perm, const float* gate, int S, int d, float* rd, double* partial,
-                     hipStream_t s) {
+int pq_launch_slot_grad(const void* dY, const void* Ys, const int* perm, const float* gate, float alpha, bool scale, int k, int S, int d,
+                        void* dst, float* rd, double* partial, hipStream_t s) {
   if (S == 0) return PQ_OK;
   pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
-  rowdot_kernel<<<(S + 3) / 4, 256, 0, s>>>((const uint16_t*)A, (const uint16_t*)B, perm, gate, S, d, rd, partial);
-  PQ_CHECK_LAUNCH("rowdot_kernel");
+  if (scale) slot_grad_kernel<true><<<(S + 3) / 4, 256, 0, s>>>((const uint16_t*)dY, (const uint16_t*)Ys, perm, gate, alpha, k, S, d, (uint16_t*)dst, rd, partial);
+  else slot_grad_kernel<false><<<(S + 3) / 4, 256, 0, s>>>((const uint16_t*)dY, (const uint16_t*)Ys, perm, gate, alpha, k, S, d, (uint16_t*)dst, rd, partial);
+  PQ_CHECK_LAUNCH("slot_grad_kernel");
   return PQ_OK;
 }
 
@@ -760,25 +751,17 @@ int pq_launch_combine_fwd(void* Y, const void* Ys, const int* inv, const float* 
   return PQ_OK;
 }
 
-int pq_launch_router_bwd(const float* rd, const int* inv, const int* idx, const float* probs, float alpha, int T, int k, int E,
-                         float* dlogit, hipStream_t s) {
-  if (T == 0) return PQ_OK;
-  pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
-  router_bwd_kernel<<<(T * E + 255) / 256, 256, 0, s>>>(rd, inv, idx, probs, alpha, T, k, E, dlogit);
-  PQ_CHECK_LAUNCH("router_bwd_kernel");
-  return PQ_OK;
-}
-
 size_t pq_dwr_scratch_bytes(int T, int d, int E) { return (size_t)((T + DWR_CHUNK - 1) / DWR_CHUNK) * E * d * sizeof(float); }
-int pq_launch_dwr(const float* dlogit, const void* X, int T, int d, int E, float* part, float* dWr, hipStream_t s) {
+int pq_launch_dwr(const float* rd, const int* inv, const int* idx, const float* probs, float alpha, int k, float* dlogit, const void* X, int T,
+                  int d, int E, float* part, float* dWr, const pq_reduce_job* jobs, hipStream_t s) {
   pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
-  const int nchunks = (T + DWR_CHUNK - 1) / DWR_CHUNK;
+  const int nchunks = rd ? (T + DWR_CHUNK - 1) / DWR_CHUNK : 0;
   if (nchunks > 0) {
     dim3 grid((d + 255) / 256, nchunks);
-    dwr_partial_kernel<<<grid, 256, 0, s>>>(dlogit, (const uint16_t*)X, T, d, E, part);
+    dwr_partial_kernel<<<grid, 256, 0, s>>>(rd, inv, idx, probs, alpha, k, dlogit, (const uint16_t*)X, T, d, E, part);
     PQ_CHECK_LAUNCH("dwr_partial_kernel");
   }
-  dwr_final_kernel<<<(E * d + 255) / 256, 256, 0, s>>>(part, nchunks, E * d, dWr);
+  dwr_final_kernel<<<(E * d + 255) / 256 + 2, 256, 0, s>>>(part, nchunks, E * d, dWr, jobs[0], jobs[1]);
   PQ_CHECK_LAUNCH("dwr_final_kernel");
   return PQ_OK;
 }

@@ -337,6 +337,7 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_
       Mtot = grp.n_groups * M;
     }
     epi.C = (char*)epi.C + (size_t)z * grp.c_stride * (epi.out_kind == PQ_OUT_BF16 ? 2 : 4);
+    if (epi.m_split > 0) epi.C2 = (char*)epi.C2 + (size_t)z * grp.c_stride * 4;
   }
   const int klen = max(ke - kb, 0);
   const int nkt = (klen + EPB - 1) / EPB;
@@ -628,6 +629,7 @@ __global__ __launch_bounds__(256) void tile64_gemm_kernel(int M, int N, int K, p
       Mtot = grp.n_groups * M;
     }
     epi.C = (char*)epi.C + (size_t)z * grp.c_stride * (epi.out_kind == PQ_OUT_BF16 ? 2 : 4);
+    if (epi.m_split > 0) epi.C2 = (char*)epi.C2 + (size_t)z * grp.c_stride * 4;
   }
   const int klen = max(ke - kb, 0);
   const int ngr = (klen + 2 * EPB - 1) / (2 * EPB);  // groups; a stage past the end is fetched as zeros
