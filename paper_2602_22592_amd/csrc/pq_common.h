@@ -68,6 +68,34 @@ __device__ __forceinline__ double wave_sum_d(double v) {
   return v;
 }
 
+// N values per lane summed over the wavefront, transposed: every exchange step halves the values a lane carries (the
+// lane with the step's bit set keeps the upper half and hands over the lower), so that after log2(N) steps a lane holds
+// one value -- lane l the one with index l / (64 / N) -- and the remaining steps are plain exchanges.  The additions
+// are those of the butterfly sum (same pairs, same order), at a quarter of the instructions.  Every index is static.
+template <int N, int OFF>
+__device__ __forceinline__ void wave_sum_transposed(double* v, int lane) {
+  if constexpr (N > 1) {
+    const bool up = (lane & OFF) != 0;
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+      const double send = up ? v[i] : v[i + N / 2];
+      const double keep = up ? v[i + N / 2] : v[i];
+      v[i] = keep + __shfl_xor(send, OFF, 64);
+    }
+    if constexpr (OFF > 1) wave_sum_transposed<N / 2, OFF / 2>(v, lane);
+  } else {
+    v[0] += __shfl_xor(v[0], OFF, 64);
+    if constexpr (OFF > 1) wave_sum_transposed<1, OFF / 2>(v, lane);
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// Router: a wavefront takes TB tokens at once (a router row converted to fp64 serves all of them): fp64 dot products
+// against all E router rows, lane l accumulating the 16-byte chunks l, l + 64, ... of a token row in order, then the
+// wave sums, which leave one (token, expert) pair per lane; that lane rounds the logit to fp32 and evaluates its term
+// of the softmax in fp64; the first lane of a token's group selects the top-k (ties to the lower index).
+// ------------------------------------------------------------------------------------------
+
 // Block-wide sum in a fixed order (deterministic): wave sums, then wave 0 adds them in index order.
 template <int NT>
 __device__ __forceinline__ double block_sum_d(double v, double* smem /* NT/64 doubles */) {

@@ -173,20 +173,32 @@ __device__ __forceinline__ void prep_quantise_own(float amax, size_t tok, int K,
   if (tid == 0) atomicAdd(&rowsum[tok], sh.isum[0] + sh.isum[1] + sh.isum[2] + sh.isum[3]);
 }
 
-// Router of one token: fp64 logits rounded once to fp32, top-k on logits (ties to the lower index), softmax
-// gates over all experts; eight experts per pass over x.  Leaves the selection in sh.sel (valid after the
-// closing barrier); when idx is not null it also computes the gates and writes both out.
-__device__ __forceinline__ void prep_router(const uint16_t* __restrict__ Wr, int layer, size_t tok, int K, int E, int topk,
-                                            const float* xs, prep_shared& sh, int* __restrict__ idx,
-                                            float* __restrict__ gate) {
+// The first eight router rows' vectors of this thread; they depend on nothing, so a caller requests them ahead of the token.
+__device__ __forceinline__ void prep_router_first(const uint16_t* __restrict__ Wr, int layer, int K, int E, uint4* wv) {
+  const int c = min((int)threadIdx.x, K / 8 - 1);
+#pragma unroll
+  for (int u = 0; u < 8; ++u) wv[u] = reinterpret_cast<const uint4*>(Wr + ((size_t)layer * E + min(u, E - 1)) * K)[c];
+}
+
+// Router of one token: fp64 logits rounded once to fp32, top-k on logits (ties to the lower index); eight experts per pass
+// over x, whose vectors the caller has requested for the first pass (prep_router_first).  Leaves the selection in sh.sel
+// (valid after the closing barrier).
+__device__ __forceinline__ void prep_router(const uint16_t* __restrict__ Wr, int layer, int K, int E, int topk, const float* xs,
+                                            prep_shared& sh, const uint4* first) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int e0 = 0; e0 < E; e0 += 8) {
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    uint4 wv[8];
+    if (e0 == 0) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) wv[u] = first[u];
+    }
     for (int c = tid; c < K / 8; c += 256) {
       // the eight rows are requested together; experts past the end re-read the last one (their sums are dropped)
-      uint4 wv[8];
+      if (e0 > 0 || c != tid) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) wv[u] = reinterpret_cast<const uint4*>(Wr + ((size_t)layer * E + min(e0 + u, E - 1)) * K)[c];
+        for (int u = 0; u < 8; ++u) wv[u] = reinterpret_cast<const uint4*>(Wr + ((size_t)layer * E + min(e0 + u, E - 1)) * K)[c];
+      }
       const float4 xa = *reinterpret_cast<const float4*>(xs + 8 * c), xb = *reinterpret_cast<const float4*>(xs + 8 * c + 4);
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
@@ -198,19 +210,47 @@ __device__ __forceinline__ void prep_router(const uint16_t* __restrict__ Wr, int
       }
     }
     __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const double t = wave_sum_d(acc[u]);
-      if (lane == 0) sh.dred[wave][u] = t;
-    }
+    wave_sum_transposed<8, 32>(acc, lane);            // lane l: expert l / 8
+    if ((lane & 7) == 0) sh.dred[wave][lane >> 3] = acc[0];
     __syncthreads();
     if (tid < 8 && e0 + tid < E)
       sh.logit[e0 + tid] = (double)(float)(sh.dred[0][tid] + sh.dred[1][tid] + sh.dred[2][tid] + sh.dred[3][tid]);
   }
   __syncthreads();
-  // softmax terms in parallel (one expert per thread), summed in index order by thread 0
-  const bool need_gate = idx != nullptr;
-  if (need_gate && tid < E) {
+  if (tid == 0) {
+    unsigned long long taken = 0ull;
+    if (E <= 8) {                                     // the logits in registers: one LDS latency, not one per comparison
+      double lg[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) lg[e] = sh.logit[e < E ? e : 0];
+      for (int j = 0; j < topk; ++j) {
+        int best = -1;
+        double bv = 0.0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (e < E && !((taken >> e) & 1ull) && (best < 0 || lg[e] > bv)) { best = e; bv = lg[e]; }
+        taken |= 1ull << best;
+        sh.sel[j] = best;
+      }
+    } else {
+      for (int j = 0; j < topk; ++j) {
+        int best = -1;
+        for (int e = 0; e < E; ++e)
+          if (!((taken >> e) & 1ull) && (best < 0 || sh.logit[e] > sh.logit[best])) best = e;
+        taken |= 1ull << best;
+        sh.sel[j] = best;
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// Softmax gates over all experts of the token that prep_router has just handled: terms in parallel (one expert per thread),
+// summed in index order by thread 0, which writes selection and gates out.  All threads of the workgroup; nothing else waits
+// for it, so the callers do it last.
+__device__ __forceinline__ void prep_gates(size_t tok, int E, int topk, prep_shared& sh, int* __restrict__ idx, float* __restrict__ gate) {
+  const int tid = threadIdx.x;
+  if (tid < E) {
     double mx = -1e300;
     for (int e = 0; e < E; ++e) mx = fmax(mx, sh.logit[e]);
     sh.expo[tid] = exp(sh.logit[tid] - mx);
@@ -218,22 +258,13 @@ __device__ __forceinline__ void prep_router(const uint16_t* __restrict__ Wr, int
   __syncthreads();
   if (tid == 0) {
     double den = 0.0;
-    if (need_gate)
-      for (int e = 0; e < E; ++e) den += sh.expo[e];
-    unsigned long long taken = 0ull;
+    for (int e = 0; e < E; ++e) den += sh.expo[e];
     for (int j = 0; j < topk; ++j) {
-      int best = -1;
-      for (int e = 0; e < E; ++e)
-        if (!((taken >> e) & 1ull) && (best < 0 || sh.logit[e] > sh.logit[best])) best = e;
-      taken |= 1ull << best;
-      sh.sel[j] = best;
-      if (need_gate) {
-        idx[tok * topk + j] = best;
-        gate[tok * topk + j] = (float)(sh.expo[best] / den);
-      }
+      const int best = sh.sel[j];
+      idx[tok * topk + j] = best;
+      gate[tok * topk + j] = (float)(sh.expo[best] / den);
     }
   }
-  __syncthreads();
 }
 
 __global__ __launch_bounds__(256) void decode_prep_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wr,
@@ -248,23 +279,27 @@ __global__ __launch_bounds__(256) void decode_prep_kernel(const uint16_t* __rest
   const bool split = E > 0;
   const size_t tok = split ? blockIdx.x >> 1 : blockIdx.x;   // layer * B + b
   const int layer = (int)(tok / B);
+  uint4 first[8];
+  if (split && (blockIdx.x & 1)) prep_router_first(Wr, layer, K, E, first);
   const float amax = prep_load_x(X, tok, K, xs);
   if (!split || (blockIdx.x & 1) == 0) {
     if (zero_rs && threadIdx.x == 0) zero_rs[tok] = 0;   // a row sum that a later kernel of the call adds up with atomics
     prep_quantise(amax, tok, K, xs, sh, xq, planes, rowsum, gamma);
   } else {
     __syncthreads();                                  // xs complete
-    prep_router(Wr, layer, tok, K, E, topk, xs, sh, idx, gate);
+    prep_router(Wr, layer, K, E, topk, xs, sh, first);
+    prep_gates(tok, E, topk, sh, idx, gate);
   }
 }
 
 // Batch 1 with experts: workgroup 0 of a layer quantises the token; each of the other workgroups repeats the
-// (cheap) router for itself and computes PREP_H_ROWS rows of the selected experts' hidden state
+// (cheap) router for itself and computes `rows` rows of the selected experts' hidden state
 // h = A_e x (bf16 inputs, fp32 accumulate), two rows per wavefront.
-#ifndef PQ_PREP_H_ROWS
-#define PQ_PREP_H_ROWS 16
-#endif
-constexpr int PREP_H_ROWS = PQ_PREP_H_ROWS;   // rows per workgroup: few enough workgroups that the repeated router stays cheap
+// Rows per workgroup: 16 where the layers alone give the chip work (few enough workgroups that the repeated router stays
+// cheap), 8, one pair per wavefront, while all of them are still resident at once.  (One layer of 4096 -> 11008, two of eight
+// experts of rank 64: call 21.7 -> 16.5 us together with the router rows requested ahead of the token, the transposed wave sums,
+// the selection from registers and the gates formed last.)
+static inline int prep_h_rows(int L, int hidden) { return (long)L * (1 + (hidden + 7) / 8) <= 512 ? 8 : 16; }
 
 // I8 (Sec. 3.2, experts on the INT8 grid): hpA holds INT8 codes [L][E][r][K] with one gamma per row in gA; the
 // hidden state is the exact integer product of the token's codes with a row, de-quantised as
@@ -274,7 +309,7 @@ template <bool I8>
 __global__ __launch_bounds__(256) void decode_prep_h_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wr,
                                                             const void* __restrict__ hpA_, const float* __restrict__ gA,
                                                             int K, int E, int r, int topk,
-                                                            int parts, int8_t* __restrict__ xq, uint32_t* __restrict__ planes,
+                                                            int parts, int rows, int8_t* __restrict__ xq, uint32_t* __restrict__ planes,
                                                             int* __restrict__ rowsum, float* __restrict__ gamma,
                                                             int* __restrict__ idx, float* __restrict__ gate,
                                                             float* __restrict__ h, int* __restrict__ zero_rs) {
@@ -296,6 +331,8 @@ __global__ __launch_bounds__(256) void decode_prep_h_kernel(const uint16_t* __re
     }
   }
   const size_t tok = layer;
+  uint4 first[8];
+  if (part > 0) prep_router_first(Wr, layer, K, E, first);
   const float amax = prep_load_x(X, tok, K, xs);
   if (part == 0) {
     if (zero_rs && threadIdx.x == 0) zero_rs[tok] = 0;   // see decode_prep_kernel
@@ -310,8 +347,8 @@ __global__ __launch_bounds__(256) void decode_prep_h_kernel(const uint16_t* __re
   }
   __syncthreads();                                    // xs complete
   if constexpr (I8) gx = 128.0f / fmaxf(fmaxf(fmaxf(sh.red[0], sh.red[1]), fmaxf(sh.red[2], sh.red[3])), 1e-5f);
-  prep_router(Wr, layer, tok, K, E, topk, xs, sh, part == 1 ? idx : nullptr, gate);
-  const int oend = min(part * PREP_H_ROWS, topk * r);
+  prep_router(Wr, layer, K, E, topk, xs, sh, first);
+  const int oend = min(part * rows, topk * r);
   if constexpr (I8) {
     uint32_t* xc = reinterpret_cast<uint32_t*>(xs + K);          // K code bytes
     for (int c = threadIdx.x; c < K / 4; c += 256) {
@@ -328,7 +365,7 @@ __global__ __launch_bounds__(256) void decode_prep_h_kernel(const uint16_t* __re
     __syncthreads();
     const int8_t* __restrict__ A8 = (const int8_t*)hpA_;
     const float sx = 1.0f / gx;
-    for (int o0 = (part - 1) * PREP_H_ROWS + 2 * wave; o0 < oend; o0 += 8) {
+    for (int o0 = (part - 1) * rows + 2 * wave; o0 < oend; o0 += 8) {
       const bool two = o0 + 1 < oend;
       const int o1 = two ? o0 + 1 : o0;
       const size_t row0 = ((size_t)layer * E + sh.sel[o0 / r]) * r + o0 % r;
@@ -367,9 +404,10 @@ __global__ __launch_bounds__(256) void decode_prep_h_kernel(const uint16_t* __re
         if (two) h[(size_t)layer * topk * r + o1] = bf16_to_f32(f32_to_bf16(__fmul_rn(sx, (float)s1) / gA[row1]));
       }
     }
+    if (part == 1) prep_gates(tok, E, topk, sh, idx, gate);
     return;
   }
-  for (int o0 = (part - 1) * PREP_H_ROWS + 2 * wave; o0 < oend; o0 += 8) {   // rows of the [topk][r] hidden state
+  for (int o0 = (part - 1) * rows + 2 * wave; o0 < oend; o0 += 8) {   // rows of the [topk][r] hidden state
     const bool two = o0 + 1 < oend;
     const int o1 = two ? o0 + 1 : o0;
     const uint4* a0 = reinterpret_cast<const uint4*>(hpA + (((size_t)layer * E + sh.sel[o0 / r]) * r + o0 % r) * K);
@@ -407,6 +445,7 @@ __global__ __launch_bounds__(256) void decode_prep_h_kernel(const uint16_t* __re
       if (two) h[(size_t)layer * topk * r + o1] = s1;
     }
   }
+  if (part == 1) prep_gates(tok, E, topk, sh, idx, gate);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1748,9 +1787,9 @@ int pq_launch_decode_ffn(int L, int B, int D, int F, int r, int E, int topk, flo
   float* gm2 = (float*)(w2 + o2[3]); float* act = (float*)(w2 + o2[6]);
   {  // quantiser of x, router, expert hidden pairs [Up_e x ; Gate_e x]
     pq_prof_scope prof(PQP_DECODE_PREP, s);
-    const int parts = 1 + (topk * 2 * r + PREP_H_ROWS - 1) / PREP_H_ROWS;
+    const int rows = prep_h_rows(L, topk * 2 * r), parts = 1 + (topk * 2 * r + rows - 1) / rows;
     decode_prep_h_kernel<false><<<L * parts, 256, (size_t)D * sizeof(float), s>>>((const uint16_t*)X, (const uint16_t*)Wr, UpGate, nullptr, D, E,
-                                                                                 2 * r, topk, parts, xq1, pl1, rs1, gm1, idx, gate, hug, rs2);
+                                                                                 2 * r, topk, parts, rows, xq1, pl1, rs1, gm1, idx, gate, hug, rs2);
     PQ_CHECK_LAUNCH("decode_prep_h_kernel");
   }
   {  // U and G: 2 L weight sets, each pair reading its layer's token once quantised
@@ -1812,13 +1851,13 @@ int pq_launch_decode(const pq_decode_desc& d, const void* X, const uint32_t* pac
   const int L = d.n_layers, B = d.batch, K = d.d_in, N = d.d_out, r = d.hp_rank, E = r > 0 ? d.n_experts : 0;
   if (B == 1 && r > 0) {
     pq_prof_scope prof(PQP_DECODE_PREP, s);
-    const int parts = 1 + (d.top_k * r + PREP_H_ROWS - 1) / PREP_H_ROWS;
+    const int rows = prep_h_rows(L, d.top_k * r), parts = 1 + (d.top_k * r + rows - 1) / rows;
     if (i8)
       decode_prep_h_kernel<true><<<L * parts, 256, (size_t)K * 5, s>>>((const uint16_t*)X, (const uint16_t*)Wr, hpA, gA, K, E, r, d.top_k,
-                                                                      parts, xq, planes, rowsum, gamma, idx, gate, h, nullptr);
+                                                                      parts, rows, xq, planes, rowsum, gamma, idx, gate, h, nullptr);
     else
       decode_prep_h_kernel<false><<<L * parts, 256, (size_t)K * sizeof(float), s>>>((const uint16_t*)X, (const uint16_t*)Wr, hpA, nullptr,
-                                                                                   K, E, r, d.top_k, parts, xq, planes, rowsum, gamma,
+                                                                                   K, E, r, d.top_k, parts, rows, xq, planes, rowsum, gamma,
                                                                                    idx, gate, h, nullptr);
     PQ_CHECK_LAUNCH("decode_prep_h_kernel");
   } else {
