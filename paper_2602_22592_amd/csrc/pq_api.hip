@@ -361,6 +361,43 @@ extern "C" size_t pq_linear_workspace_bytes(const pq_linear_desc* d) {
   return make_layout(*d).ws_total;
 }
 
+namespace {
+struct hp8_layout { size_t Aq, gA, At, Bq, gB, Bt, H, Hq, gH, Ht, ctx_total, dH, splitk, splitk2, ws_total; };
+hp8_layout make_hp8_layout(int T, int K, int N, int r) {
+  hp8_layout L;
+  const size_t t = T, k = K, n = N, rr = r;
+  cursor c;
+  L.Aq = c.take(rr * k); L.gA = c.take(rr * sizeof(float)); L.At = c.take(rr * k * 2);
+  L.Bq = c.take(n * rr); L.gB = c.take(n * sizeof(float)); L.Bt = c.take(n * rr * 2);
+  L.H = c.take(t * rr * 2); L.Hq = c.take(t * rr); L.gH = c.take(t * sizeof(float)); L.Ht = c.take(t * rr * 2);
+  L.ctx_total = c.off;
+  cursor w;
+  L.dH = w.take(t * rr * 2);
+  size_t sk = 0;
+  const int shapes[4][3] = {{T, r, N}, {N, r, T}, {r, K, T}, {T, K, r}};
+  for (const auto& sh : shapes) {
+    if (sh[0] <= 0 || sh[1] <= 0) continue;
+    const size_t b = pq_plan_gemm(sh[0], sh[1], sh[2]).ws_bytes;
+    if (b > sk) sk = b;
+  }
+  if (T > 0) {   // the int8 H product splits its contraction (int32 slabs)
+    const size_t b = pq_plan_gemm(T, r, K, true, true).ws_bytes;
+    if (b > sk) sk = b;
+  }
+  const pq_pair_plan pair = pq_plan_pair(T, N, r, r, K);
+  if (pair.ws0 > sk) sk = pair.ws0;
+  L.splitk = w.take(sk);
+  const size_t alone = (r > 0 && K > 0) ? pq_plan_gemm(r, K, T).ws_bytes : 0;
+  L.splitk2 = w.take(pair.ws1 > alone ? pair.ws1 : alone);   // dA's slabs when dB and dA share a launch
+  L.ws_total = w.off;
+  return L;
+}
+}  // namespace
+// pq_hp_int8_fwd; rows_done: the rows of A and B are already on their grid in ctx
+static int hp_int8_fwd_impl(const int8_t* Xq, const float* gamma_x, const void* A, const void* B, int32_t dtype, int32_t T, int32_t K,
+                            int32_t N, int32_t r, float alpha, void* Y, int32_t accumulate, void* ctx, size_t ctx_bytes, void* workspace,
+                            size_t workspace_bytes, void* stream, bool rows_done);
+
 // ---------------------------------------------------------------------------------------------
 // Forward: [stats -> pack] -> quantise -> int8 MFMA GEMM with de-quantising epilogue -> hp branch
 // ---------------------------------------------------------------------------------------------
@@ -442,8 +479,14 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
       quant_done = true;
     } else if (int e = pq_launch_wstats_partial(W_or_packed, d->io_dtype, n, part, nb, s)) return e;
     uint32_t* Pt = (N % 32 == 0) ? (uint32_t*)(cx + L.Pt) : nullptr;
-    if (int e = pq_launch_pack(W_or_packed, d->io_dtype, N, K, part, nb, (uint32_t*)(cx + L.P), Pt,
-                               (float*)(cx + L.mulam), s)) return e;
+    if (hp8) {   // the rows of A and B on the AbsMax grid ride along
+      const hp8_layout H8 = make_hp8_layout(T, K, N, d->hp_rank);
+      char* c8 = cx + L.hp8;
+      const pq_quant_rows_job jobs[2] = {{hpA, d->hp_rank, K, (int8_t*)(c8 + H8.Aq), (float*)(c8 + H8.gA), (uint16_t*)(c8 + H8.At)},
+                                         {hpB, N, d->hp_rank, (int8_t*)(c8 + H8.Bq), (float*)(c8 + H8.gB), (uint16_t*)(c8 + H8.Bt)}};
+      if (int e = pq_launch_pack_quant_rows(W_or_packed, N, K, part, nb, (uint32_t*)(cx + L.P), Pt, (float*)(cx + L.mulam), jobs, s)) return e;
+    } else if (int e = pq_launch_pack(W_or_packed, d->io_dtype, N, K, part, nb, (uint32_t*)(cx + L.P), Pt,
+                                      (float*)(cx + L.mulam), s)) return e;
     P = (const uint32_t*)(cx + L.P);
     mulam = (const float*)(cx + L.mulam);
   } else {
@@ -497,8 +540,8 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
     }
   }
   if (hp8)   // Y += alpha * B~ Q(A~ Q(x)) on the codes and gamma formed above
-    return pq_hp_int8_fwd(Xq, gamma, hpA, hpB, PQ_BF16, T, K, N, d->hp_rank, d->alpha, Y, 1, cx + L.hp8, L.hp8_bytes,
-                          ws + L.hp8_ws, L.hp8_ws_bytes, stream);
+    return hp_int8_fwd_impl(Xq, gamma, hpA, hpB, PQ_BF16, T, K, N, d->hp_rank, d->alpha, Y, 1, cx + L.hp8, L.hp8_bytes,
+                            ws + L.hp8_ws, L.hp8_ws_bytes, stream, d->w_kind == PQ_W_MASTER);
   if (routed) {
     // router -> stable permutation by expert -> gather -> H_e = X_e A_e^T -> Y_e = H_e B_e^T -> gate-weighted combine
     const int E = d->n_experts, k = d->top_k, S = T * k, re = d->hp_rank;
@@ -541,10 +584,12 @@ extern "C" int pq_linear_fwd(const pq_linear_desc* d, const void* X, const void*
 // ---------------------------------------------------------------------------------------------
 // STE backward
 // ---------------------------------------------------------------------------------------------
-// pq_hp_int8_bwd with the per-workgroup partial sums of <dY, Y_hp> (= d alpha) left in red_a when it is not NULL
-static int hp_int8_bwd_impl(const void* dY, const void* Xt, int32_t dtype, int32_t T, int32_t K, int32_t N, int32_t r, float alpha,
-                            const void* ctx, size_t ctx_bytes, void* dX, int32_t accumulate_dX, float* dA, float* dB, void* workspace,
-                            size_t workspace_bytes, void* stream, double* red_a);
+// The two halves of pq_hp_int8_bwd that do not touch dX, on checked arguments.  dH = alpha dY B~, with the per-workgroup partial
+// sums of <dY, Y_hp> (= d alpha) left in red_a when it is not NULL; then dB and dA, two scalar reductions (may be NULL) riding
+// along where the launch has room for them.
+static int hp_int8_dh(const void* dY, int T, int N, int r, float alpha, const char* cx, const hp8_layout& L, char* ws, double* red_a, hipStream_t s);
+static int hp_int8_factor_grads(const void* dY, const void* Xt, int T, int K, int N, int r, float alpha, const char* cx, const hp8_layout& L,
+                                float* dA, float* dB, char* ws, const pq_reduce_job* jobs, bool* jobs_done, hipStream_t s);
 
 // fp32 I/O: the same products at reference precision.  What depends on nothing (dW, dH, dB) is one launch, what needs dH
 // (dX with dH A in the same sums, dA) and the two scalar reductions a second one: six products and a reduction in a row
@@ -635,27 +680,39 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
     } else if (int err = pq_launch_gemm(T, r, N, A, B, e, s, PQP_GEMM_DH, sk_ws)) return err;
   }
 
+  // INT8 branch: STE on the de-quantised factors; its dH GEMM leaves the partials of d alpha
+  hp8_layout H8;
+  memset(&H8, 0, sizeof(H8));
+  if (hp8) H8 = make_hp8_layout(T, K, N, d->hp_rank);
+  if (hp8 && T > 0) {
+    n_red_a = pq_plan_gemm(T, d->hp_rank, N).red_blocks;
+    if (int e = hp_int8_dh(dY, T, N, d->hp_rank, d->alpha, cx + L.hp8, H8, ws + L.hp8_ws, red_a, s)) return e;
+  }
   if (T > 0) {  // dX = beta*lambda * dY S  (+ dH A, fused into the same tile)
     pq_operand A{dY, N, PQ_SRC_KC16, nullptr};
     pq_operand B{cx + L.Pt, N / 8, PQ_SRC_BITS16, nullptr};
     pq_epilogue e = epi_zero();
     e.C = dX; e.ldc = K; e.out_kind = ok;
-    const bool fuse = r > 0 && pq_plan_fuses(pq_plan_gemm(T, K, N));
+    // the branch's share of dX: dH A, with the INT8 form on its de-quantised rows
+    const int r2 = hp8 ? d->hp_rank : r;
+    const void* dH2 = hp8 ? (const void*)(ws + L.hp8_ws + H8.dH) : dH;
+    const void* A2p = hp8 ? (const void*)(cx + L.hp8 + H8.At) : hpA;
+    const bool fuse = r2 > 0 && pq_plan_fuses(pq_plan_gemm(T, K, N));
     if (fuse) {
       pq_phase2 p2;
-      p2.A2 = pq_operand{dH, r, PQ_SRC_KC16, nullptr};
-      p2.B2 = pq_operand{hpA, K, PQ_SRC_KS16, nullptr};
-      p2.K2 = r; p2.scale1 = d->beta; p2.dev_scale1 = mulam + 1; p2.row_div1 = nullptr;
+      p2.A2 = pq_operand{dH2, r2, PQ_SRC_KC16, nullptr};
+      p2.B2 = pq_operand{A2p, K, PQ_SRC_KS16, nullptr};
+      p2.K2 = r2; p2.scale1 = d->beta; p2.dev_scale1 = mulam + 1; p2.row_div1 = nullptr;
       if (int err = pq_launch_gemm(T, K, N, A, B, e, s, PQP_GEMM_DX, sk_ws, nullptr, &p2)) return err;
     } else {
       e.scale = d->beta; e.dev_scale = mulam + 1;
       if (int err = pq_launch_gemm(T, K, N, A, B, e, s, PQP_GEMM_DX, sk_ws)) return err;
-      if (r > 0) {
-        pq_operand A2{dH, r, PQ_SRC_KC16, nullptr};
-        pq_operand B2{hpA, K, PQ_SRC_KS16, nullptr};
+      if (r2 > 0) {
+        pq_operand A2{dH2, r2, PQ_SRC_KC16, nullptr};
+        pq_operand B2{A2p, K, PQ_SRC_KS16, nullptr};
         pq_epilogue e2 = epi_zero();
         e2.C = dX; e2.ldc = K; e2.out_kind = ok; e2.accumulate = 1;
-        if (int err = pq_launch_gemm(T, K, r, A2, B2, e2, s, PQP_GEMM_DX_HP, sk_ws)) return err;
+        if (int err = pq_launch_gemm(T, K, r2, A2, B2, e2, s, PQP_GEMM_DX_HP, sk_ws)) return err;
       }
     }
   }
@@ -719,15 +776,12 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
     if (int e = pq_launch_dwr(rd, inv, idx, (const float*)(cx + L.probs), d->alpha, k, dlogit, X, T, K, E, (float*)(ws + L.dwr), dWr, rj, s)) return e;
     if (int e = pq_launch_combine_bwd(dX, ws + L.dXs, inv, dlogit, Wr, T, k, K, E, s)) return e;
   }
-  if (hp8) {   // STE backward of the INT8 branch on the de-quantised factors; its dH GEMM leaves the partials of d alpha
-    n_red_a = T > 0 ? pq_plan_gemm(T, d->hp_rank, N).red_blocks : 0;
-    if (int e = hp_int8_bwd_impl(dY, cx + L.Xt, PQ_BF16, T, K, N, d->hp_rank, d->alpha, cx + L.hp8, L.hp8_bytes, dX, 1, dhpA, dhpB,
-                                 ws + L.hp8_ws, L.hp8_ws_bytes, stream, red_a)) return e;
-  }
   // d alpha and d beta: both fixed-order sums of per-workgroup partials
   const pq_reduce_job jobs[2] = {{red_a, (T > 0 && (r > 0 || routed || hp8)) ? n_red_a : 0, 1.0f, nullptr, dalpha_dbeta},
                                  {red_b, L.n_red_b, 1.0f, mulam + 1, dalpha_dbeta + 1}};
   bool jobs_done = routed;   // (the routed path's own last reduction carries them)
+  if (hp8)
+    if (int e = hp_int8_factor_grads(dY, cx + L.Xt, T, K, N, d->hp_rank, d->alpha, cx + L.hp8, H8, dhpA, dhpB, ws + L.hp8_ws, jobs, &jobs_done, s)) return e;
   if (r > 0 && T > 0) {
     // dB = alpha * dY^T H and dA = dH^T X (dH already carries alpha): two narrow GEMMs over the same contraction,
     // one launch when their plans agree; the two scalar reductions then ride along with their split reduction
@@ -842,36 +896,6 @@ extern "C" int pq_linear_norm_bwd(const pq_linear_desc* d, const void* dY, const
 // workspace: [dH T*r bf16][split-contraction slabs]
 // ---------------------------------------------------------------------------------------------
 namespace {
-struct hp8_layout { size_t Aq, gA, At, Bq, gB, Bt, H, Hq, gH, Ht, ctx_total, dH, splitk, splitk2, ws_total; };
-hp8_layout make_hp8_layout(int T, int K, int N, int r) {
-  hp8_layout L;
-  const size_t t = T, k = K, n = N, rr = r;
-  cursor c;
-  L.Aq = c.take(rr * k); L.gA = c.take(rr * sizeof(float)); L.At = c.take(rr * k * 2);
-  L.Bq = c.take(n * rr); L.gB = c.take(n * sizeof(float)); L.Bt = c.take(n * rr * 2);
-  L.H = c.take(t * rr * 2); L.Hq = c.take(t * rr); L.gH = c.take(t * sizeof(float)); L.Ht = c.take(t * rr * 2);
-  L.ctx_total = c.off;
-  cursor w;
-  L.dH = w.take(t * rr * 2);
-  size_t sk = 0;
-  const int shapes[4][3] = {{T, r, N}, {N, r, T}, {r, K, T}, {T, K, r}};
-  for (const auto& sh : shapes) {
-    if (sh[0] <= 0 || sh[1] <= 0) continue;
-    const size_t b = pq_plan_gemm(sh[0], sh[1], sh[2]).ws_bytes;
-    if (b > sk) sk = b;
-  }
-  if (T > 0) {   // the int8 H product splits its contraction (int32 slabs)
-    const size_t b = pq_plan_gemm(T, r, K, true, true).ws_bytes;
-    if (b > sk) sk = b;
-  }
-  const pq_pair_plan pair = pq_plan_pair(T, N, r, r, K);
-  if (pair.ws0 > sk) sk = pair.ws0;
-  L.splitk = w.take(sk);
-  const size_t alone = (r > 0 && K > 0) ? pq_plan_gemm(r, K, T).ws_bytes : 0;
-  L.splitk2 = w.take(pair.ws1 > alone ? pair.ws1 : alone);   // dA's slabs when dB and dA share a launch
-  L.ws_total = w.off;
-  return L;
-}
 int check_hp8(int dtype, int T, int K, int N, int r) {
   PQ_REQUIRE(dtype == PQ_BF16, PQ_ERR_DTYPE, "the INT8 high-precision branch takes bf16 tensors");
   PQ_REQUIRE(T >= 0 && K > 0 && N > 0 && r > 0, PQ_ERR_BAD_ARG, "bad size T=%d K=%d N=%d r=%d", T, K, N, r);
@@ -892,6 +916,12 @@ extern "C" size_t pq_hp_int8_workspace_bytes(int32_t T, int32_t K, int32_t N, in
 extern "C" int pq_hp_int8_fwd(const int8_t* Xq, const float* gamma_x, const void* A, const void* B, int32_t dtype, int32_t T,
                               int32_t K, int32_t N, int32_t r, float alpha, void* Y, int32_t accumulate, void* ctx,
                               size_t ctx_bytes, void* workspace, size_t workspace_bytes, void* stream) {
+  return hp_int8_fwd_impl(Xq, gamma_x, A, B, dtype, T, K, N, r, alpha, Y, accumulate, ctx, ctx_bytes, workspace, workspace_bytes, stream, false);
+}
+
+static int hp_int8_fwd_impl(const int8_t* Xq, const float* gamma_x, const void* A, const void* B, int32_t dtype, int32_t T, int32_t K,
+                            int32_t N, int32_t r, float alpha, void* Y, int32_t accumulate, void* ctx, size_t ctx_bytes, void* workspace,
+                            size_t workspace_bytes, void* stream, bool rows_done) {
   if (int e = check_hp8(dtype, T, K, N, r)) return e;
   const hp8_layout L = make_hp8_layout(T, K, N, r);
   PQ_REQUIRE(A && B && ctx && workspace, PQ_ERR_BAD_ARG, "NULL buffer (A, B, ctx or workspace)");
@@ -904,8 +934,10 @@ extern "C" int pq_hp_int8_fwd(const int8_t* Xq, const float* gamma_x, const void
   char* cx = (char*)ctx;
   void* sk = (char*)workspace + L.splitk;
   // weight side: rows of A and B on the activation grid (codes, gamma, bf16 de-quantised copy for the backward)
-  if (int e = pq_launch_quant_act(A, dtype, r, K, (int8_t*)(cx + L.Aq), (float*)(cx + L.gA), (uint16_t*)(cx + L.At), s)) return e;
-  if (int e = pq_launch_quant_act(B, dtype, N, r, (int8_t*)(cx + L.Bq), (float*)(cx + L.gB), (uint16_t*)(cx + L.Bt), s)) return e;
+  if (!rows_done) {
+    if (int e = pq_launch_quant_act(A, dtype, r, K, (int8_t*)(cx + L.Aq), (float*)(cx + L.gA), (uint16_t*)(cx + L.At), s)) return e;
+    if (int e = pq_launch_quant_act(B, dtype, N, r, (int8_t*)(cx + L.Bq), (float*)(cx + L.gB), (uint16_t*)(cx + L.Bt), s)) return e;
+  }
   if (T == 0) return PQ_OK;
   {  // H = (q_x q_a^T) / (gamma_x gamma_a)
     pq_operand a{Xq, K, PQ_SRC_KC8, nullptr};
@@ -930,13 +962,6 @@ extern "C" int pq_hp_int8_fwd(const int8_t* Xq, const float* gamma_x, const void
 extern "C" int pq_hp_int8_bwd(const void* dY, const void* Xt, int32_t dtype, int32_t T, int32_t K, int32_t N, int32_t r,
                               float alpha, const void* ctx, size_t ctx_bytes, void* dX, int32_t accumulate_dX, float* dA, float* dB,
                               void* workspace, size_t workspace_bytes, void* stream) {
-  return hp_int8_bwd_impl(dY, Xt, dtype, T, K, N, r, alpha, ctx, ctx_bytes, dX, accumulate_dX, dA, dB, workspace, workspace_bytes, stream,
-                          nullptr);
-}
-
-static int hp_int8_bwd_impl(const void* dY, const void* Xt, int32_t dtype, int32_t T, int32_t K, int32_t N, int32_t r, float alpha,
-                            const void* ctx, size_t ctx_bytes, void* dX, int32_t accumulate_dX, float* dA, float* dB, void* workspace,
-                            size_t workspace_bytes, void* stream, double* red_a) {
   if (int e = check_hp8(dtype, T, K, N, r)) return e;
   const hp8_layout L = make_hp8_layout(T, K, N, r);
   PQ_REQUIRE(ctx && dA && dB && workspace, PQ_ERR_BAD_ARG, "NULL buffer (ctx, dA, dB or workspace)");
@@ -948,32 +973,38 @@ static int hp_int8_bwd_impl(const void* dY, const void* Xt, int32_t dtype, int32
   hipStream_t s = (hipStream_t)stream;
   const char* cx = (const char*)ctx;
   char* ws = (char*)workspace;
-  void* sk = ws + L.splitk;
-  void* dH = ws + L.dH;
-  if (T > 0) {  // dH = alpha * dY B~
-    pq_operand a{dY, N, PQ_SRC_KC16, nullptr};
-    pq_operand b{cx + L.Bt, r, PQ_SRC_KS16, nullptr};
-    pq_epilogue e = epi_zero();
-    e.C = dH; e.ldc = r; e.out_kind = PQ_OUT_BF16; e.scale = alpha;
-    if (red_a) {   // sum H~ .* (dY B~) = <dY, H~ B~^T>: the gradient of alpha, one partial per workgroup
-      e.dot_comp = cx + L.Ht; e.ld_comp = r; e.comp_kind = PQ_OUT_BF16; e.partials = red_a;
-    }
-    if (int err = pq_launch_gemm(T, r, N, a, b, e, s, PQP_GEMM_DH, sk)) return err;
-  }
-  {  // dB = alpha * dY^T H~ and dA = dH^T X~ (dH already carries alpha): one launch when their shapes allow it
-    pq_operand a0{dY, N, PQ_SRC_KS16, nullptr}, b0{cx + L.Ht, r, PQ_SRC_KS16, nullptr};
-    pq_operand a1{dH, r, PQ_SRC_KS16, nullptr}, b1{Xt, K, PQ_SRC_KS16, nullptr};
-    if (int err = pq_launch_gemm_pair_ks16(T, N, r, a0, b0, dB, r, alpha, r, K, a1, b1, dA, K, 1.0f, s, PQP_GEMM_DB, PQP_GEMM_DA, sk,
-                                           ws + L.splitk2, nullptr, nullptr)) return err;
-  }
+  if (T > 0)
+    if (int e = hp_int8_dh(dY, T, N, r, alpha, cx, L, ws, nullptr, s)) return e;
+  if (int e = hp_int8_factor_grads(dY, Xt, T, K, N, r, alpha, cx, L, dA, dB, ws, nullptr, nullptr, s)) return e;
   if (T > 0) {  // dX (+)= dH A~
-    pq_operand a{dH, r, PQ_SRC_KC16, nullptr};
+    pq_operand a{ws + L.dH, r, PQ_SRC_KC16, nullptr};
     pq_operand b{cx + L.At, K, PQ_SRC_KS16, nullptr};
     pq_epilogue e = epi_zero();
     e.C = dX; e.ldc = K; e.out_kind = PQ_OUT_BF16; e.accumulate = accumulate_dX ? 1 : 0;
-    if (int err = pq_launch_gemm(T, K, r, a, b, e, s, PQP_GEMM_DX_HP, sk)) return err;
+    if (int err = pq_launch_gemm(T, K, r, a, b, e, s, PQP_GEMM_DX_HP, ws + L.splitk)) return err;
   }
   return PQ_OK;
+}
+
+static int hp_int8_dh(const void* dY, int T, int N, int r, float alpha, const char* cx, const hp8_layout& L, char* ws, double* red_a, hipStream_t s) {
+  pq_operand a{dY, N, PQ_SRC_KC16, nullptr};
+  pq_operand b{cx + L.Bt, r, PQ_SRC_KS16, nullptr};
+  pq_epilogue e = epi_zero();
+  e.C = ws + L.dH; e.ldc = r; e.out_kind = PQ_OUT_BF16; e.scale = alpha;
+  if (red_a) {   // sum H~ .* (dY B~) = <dY, H~ B~^T>
+    e.dot_comp = cx + L.Ht; e.ld_comp = r; e.comp_kind = PQ_OUT_BF16; e.partials = red_a;
+  }
+  return pq_launch_gemm(T, r, N, a, b, e, s, PQP_GEMM_DH, ws + L.splitk);
+}
+
+static int hp_int8_factor_grads(const void* dY, const void* Xt, int T, int K, int N, int r, float alpha, const char* cx, const hp8_layout& L,
+                                float* dA, float* dB, char* ws, const pq_reduce_job* jobs, bool* jobs_done, hipStream_t s) {
+  // dB = alpha * dY^T H~ and dA = dH^T X~ (dH already carries alpha): one launch when their shapes allow it
+  const void* dH = ws + L.dH;
+  pq_operand a0{dY, N, PQ_SRC_KS16, nullptr}, b0{cx + L.Ht, r, PQ_SRC_KS16, nullptr};
+  pq_operand a1{dH, r, PQ_SRC_KS16, nullptr}, b1{Xt, K, PQ_SRC_KS16, nullptr};
+  return pq_launch_gemm_pair_ks16(T, N, r, a0, b0, dB, r, alpha, r, K, a1, b1, dA, K, 1.0f, s, PQP_GEMM_DB, PQP_GEMM_DA, ws + L.splitk,
+                                  ws + L.splitk2, jobs, jobs_done);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -1828,7 +1828,7 @@ static double est_reduce(int splits, double elems) {
   return 4.0 * splits * elems / 1.0e7 + (t > 4.0 ? t : 4.0);
 }
 
-static pq_gemm_plan pq_plan_gemm_impl(int M, int N, int K, bool int8, bool may_split) {
+static pq_gemm_plan plan_search(int M, int N, int K, bool int8, bool may_split) {
   pq_gemm_plan pl;
   memset(&pl, 0, sizeof(pl));
   pl.bm = 64;
@@ -1852,6 +1852,18 @@ static pq_gemm_plan pq_plan_gemm_impl(int M, int N, int K, bool int8, bool may_s
   pl.red_blocks = pl.splits > 1 ? (int)(((size_t)M * (N / 8) + 255) / 256) : (int)tiles;
   pl.ws_bytes = pl.splits > 1 ? (size_t)pl.splits * M * N * sizeof(float) : 0;
   return pl;
+}
+// The search is a pure function of its arguments and takes up to a microsecond; a call asks for a dozen plans (sizes of its
+// sections, then the launches), most of them the ones it asked for before: the last answers are kept per thread.
+static pq_gemm_plan pq_plan_gemm_impl(int M, int N, int K, bool int8, bool may_split) {
+  struct entry { int M, N, K, flags; pq_gemm_plan pl; };
+  static thread_local entry cache[64];               // (zeroed: no plan has M = 0, see below)
+  const int flags = (int8 ? 1 : 0) | (may_split ? 2 : 0);
+  if (M <= 0) return plan_search(M, N, K, int8, may_split);
+  const uint32_t hsh = ((uint32_t)M * 2654435761u) ^ ((uint32_t)N * 2246822519u) ^ ((uint32_t)K * 3266489917u) ^ ((uint32_t)flags * 668265263u);
+  entry& e = cache[(hsh ^ (hsh >> 15)) & 63u];
+  if (e.M != M || e.N != N || e.K != K || e.flags != flags) e = entry{M, N, K, flags, plan_search(M, N, K, int8, may_split)};
+  return e.pl;
 }
 pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8, bool split_int8) {
   return pq_plan_gemm_impl(M, N, K, int8, !int8 || split_int8);

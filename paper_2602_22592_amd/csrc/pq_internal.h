@@ -59,6 +59,10 @@ struct pq_ffn_prep {
 };
 int pq_launch_ffn_prep(const pq_ffn_prep& p, hipStream_t s);
 int pq_launch_pack3(const pq_weight_job* w, hipStream_t s);
+// pq_launch_pack of a bf16 weight (N, K multiples of 32) with the AbsMax quantiser of the rows of two more bf16 matrices in the launch
+struct pq_quant_rows_job { const void* src; int rows, cols; int8_t* codes; float* gamma; uint16_t* deq; };
+int pq_launch_pack_quant_rows(const void* W, int N, int K, const double* partials, int nblocks, uint32_t* P, uint32_t* Pt, float* mu_lambda,
+                              const pq_quant_rows_job* jobs, hipStream_t s);
 int pq_launch_router(const void* X, const void* Wr, int dtype, int T, int K, int E, int k, int* idx,
                      float* gate, float* probs, hipStream_t s);
 // out[0] = factor * sum(partials[0..n)) (+ optionally factor2 read from device: *dev_factor)

@@ -736,6 +736,32 @@ __global__ __launch_bounds__(256) void pack_sign_kernel(const T* __restrict__ W,
                                                         float* __restrict__ mu_lambda) {
   pack_sign_body<T, RAGGED>(W, N, K, partials, G, Pbytes, Pt, mu_lambda, blockIdx.x, blockIdx.y);
 }
+// one bf16 weight, and behind its tiles the rows of two small matrices on the AbsMax grid (the factors of the INT8 branch: two
+// launches of about 5 us less)
+__global__ __launch_bounds__(256) void pack_quant_rows_kernel(const uint16_t* __restrict__ W, int N, int K, const double* __restrict__ partials,
+                                                              int G, uint8_t* __restrict__ Pbytes, uint32_t* __restrict__ Pt,
+                                                              float* __restrict__ mu_lambda, int gx, int npack, pq_quant_rows_job j0,
+                                                              pq_quant_rows_job j1) {
+  int b = blockIdx.x;
+  if (b < npack) {                                   // uniform (N and K are whole words here)
+    pack_sign_body<uint16_t, false>(W, N, K, partials, G, Pbytes, Pt, mu_lambda, b % gx, b / gx);
+    return;
+  }
+  b -= npack;
+  const int n0 = (j0.rows + 3) / 4;
+  const pq_quant_rows_job& j = b < n0 ? j0 : j1;
+  quant_act_body<uint16_t, 0>((const uint16_t*)j.src, j.rows, j.cols, j.codes, j.gamma, j.deq, b < n0 ? b : b - n0);
+}
+int pq_launch_pack_quant_rows(const void* W, int N, int K, const double* partials, int nblocks, uint32_t* P, uint32_t* Pt, float* mu_lambda,
+                              const pq_quant_rows_job* jobs, hipStream_t s) {
+  if (N % 32 != 0 || K % 32 != 0) return pq_set_error(PQ_ERR_SHAPE, "N=%d and K=%d must be multiples of 32", N, K);
+  pq_prof_scope prof(PQP_PACK, s);
+  const int gx = (K + 511) / 512, npack = gx * (N / 32);
+  const int nrow = (jobs[0].rows + 3) / 4 + (jobs[1].rows + 3) / 4;
+  pack_quant_rows_kernel<<<npack + nrow, 256, 0, s>>>((const uint16_t*)W, N, K, partials, nblocks, (uint8_t*)P, Pt, mu_lambda, gx, npack, jobs[0], jobs[1]);
+  PQ_CHECK_LAUNCH("pack_quant_rows_kernel");
+  return PQ_OK;
+}
 // three bf16 weights in one launch, the tiles of one after those of the other
 struct pack3_args { pq_weight_job w[3]; };
 template <bool RAGGED>
