@@ -110,7 +110,7 @@ struct lin_layout {
   // INT8 form of the dense branch: the ctx of pq_hp_int8_* behind the linear's own
   size_t hp8, hp8_bytes;
   // workspace (scratch)
-  size_t stat_partials, red_a, red_b, dH, w_Xq, w_gamma, w_H, splitk, splitk2, ws_total;
+  size_t stat_partials, red_a, red_b, dH, w_Xq, w_gamma, w_H, splitk, splitk2, splitk_bytes, splitk2_bytes, ws_total;
   size_t dYp, rd, dHs, dXs, dlogit, dwr, hp8_ws, hp8_ws_bytes;
   int n_red_a, n_red_b;
 };
@@ -185,9 +185,11 @@ lin_layout make_layout(const pq_linear_desc& d) {
   L.w_gamma = w.take(T * sizeof(float));
   L.w_H = w.take(T * r * es);
   L.splitk = w.take(sk);
+  L.splitk_bytes = sk;
   // slabs of dA, which shares a launch with dB (whose slabs are in the region above)
   const size_t sk2a = (bf16 && ri > 0) ? pq_plan_gemm(ri, Ki, Ti).ws_bytes : 0, sk2b = (bf16 && ri > 0) ? pq_plan_pair(Ti, Ni, ri, ri, Ki).ws1 : 0;
-  L.splitk2 = w.take(sk2a > sk2b ? sk2a : sk2b);
+  L.splitk2_bytes = sk2a > sk2b ? sk2a : sk2b;
+  L.splitk2 = w.take(L.splitk2_bytes);
   if (routed) {
     L.dYp = w.take(S * N * 2); L.rd = w.take(S * 4); L.dHs = w.take(S * re * 2); L.dXs = w.take(S * K * 2);
     L.dlogit = w.take(T * E * 4);
@@ -362,7 +364,7 @@ extern "C" size_t pq_linear_workspace_bytes(const pq_linear_desc* d) {
 }
 
 namespace {
-struct hp8_layout { size_t Aq, gA, At, Bq, gB, Bt, H, Hq, gH, Ht, ctx_total, dH, splitk, splitk2, ws_total; };
+struct hp8_layout { size_t Aq, gA, At, Bq, gB, Bt, H, Hq, gH, Ht, ctx_total, dH, splitk, splitk2, splitk_bytes, splitk2_bytes, ws_total; };
 hp8_layout make_hp8_layout(int T, int K, int N, int r) {
   hp8_layout L;
   const size_t t = T, k = K, n = N, rr = r;
@@ -387,8 +389,10 @@ hp8_layout make_hp8_layout(int T, int K, int N, int r) {
   const pq_pair_plan pair = pq_plan_pair(T, N, r, r, K);
   if (pair.ws0 > sk) sk = pair.ws0;
   L.splitk = w.take(sk);
+  L.splitk_bytes = sk;
   const size_t alone = (r > 0 && K > 0) ? pq_plan_gemm(r, K, T).ws_bytes : 0;
-  L.splitk2 = w.take(pair.ws1 > alone ? pair.ws1 : alone);   // dA's slabs when dB and dA share a launch
+  L.splitk2_bytes = pair.ws1 > alone ? pair.ws1 : alone;
+  L.splitk2 = w.take(L.splitk2_bytes);   // dA's slabs when dB and dA share a launch
   L.ws_total = w.off;
   return L;
 }
@@ -426,7 +430,7 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
   hipStream_t s = (hipStream_t)stream;
   char* cx = (char*)ctx;
   char* ws = (char*)workspace;
-  void* sk_ws = ws + L.splitk;
+  const pq_scratch sk_ws{ws + L.splitk, L.splitk_bytes};
   const bool bf16 = d->io_dtype == PQ_BF16;
   const int ok = out_kind_of(d->io_dtype);
 
@@ -474,7 +478,7 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
     double* part = (double*)(ws + L.stat_partials);
     if (combo) {
       const bool sum = H_done && H_splits > 1;
-      if (int e = pq_launch_wstats_quant(W_or_packed, d->io_dtype, n, part, nb, X, T, K, Xq, gamma, Xt, s, sum ? (const float*)sk_ws : nullptr, H_splits,
+      if (int e = pq_launch_wstats_quant(W_or_packed, d->io_dtype, n, part, nb, X, T, K, Xq, gamma, Xt, s, sum ? (const float*)sk_ws.p : nullptr, H_splits,
                                          T, r, H, r)) return e;
       quant_done = true;
     } else if (int e = pq_launch_wstats_partial(W_or_packed, d->io_dtype, n, part, nb, s)) return e;
@@ -657,7 +661,7 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
   hipStream_t s = (hipStream_t)stream;
   const char* cx = (const char*)ctx;
   char* ws = (char*)workspace;
-  void* sk_ws = ws + L.splitk;
+  const pq_scratch sk_ws{ws + L.splitk, L.splitk_bytes};
   const bool bf16 = d->io_dtype == PQ_BF16;
   const int ok = out_kind_of(d->io_dtype);
   const float* mulam = (const float*)(cx + L.mulam);
@@ -712,7 +716,9 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
         pq_operand B2{A2p, K, PQ_SRC_KS16, nullptr};
         pq_epilogue e2 = epi_zero();
         e2.C = dX; e2.ldc = K; e2.out_kind = ok; e2.accumulate = 1;
-        if (int err = pq_launch_gemm(T, K, r2, A2, B2, e2, s, PQP_GEMM_DX_HP, sk_ws)) return err;
+        // (the INT8 branch's products split into the branch's own section, which is sized for them)
+        const pq_scratch sk2 = hp8 ? pq_scratch{ws + L.hp8_ws + H8.splitk, H8.splitk_bytes} : sk_ws;
+        if (int err = pq_launch_gemm(T, K, r2, A2, B2, e2, s, PQP_GEMM_DX_HP, sk2)) return err;
       }
     }
   }
@@ -788,7 +794,7 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
     pq_operand A0{dY, N, PQ_SRC_KS16, nullptr}, B0{H, r, PQ_SRC_KS16, nullptr};
     pq_operand A1{dH, r, PQ_SRC_KS16, nullptr}, B1{X, K, PQ_SRC_KS16, nullptr};
     if (int err = pq_launch_gemm_pair_ks16(T, N, r, A0, B0, dhpB, r, d->alpha, r, K, A1, B1, dhpA, K, 1.0f, s, PQP_GEMM_DB, PQP_GEMM_DA,
-                                           sk_ws, ws + L.splitk2, jobs, &jobs_done)) return err;
+                                           sk_ws, {ws + L.splitk2, L.splitk2_bytes}, jobs, &jobs_done)) return err;
   }
   if (!jobs_done)
     if (int err = pq_launch_reduce_partials2(jobs[0].partials, jobs[0].n, 1.0f, nullptr, jobs[0].out, jobs[1].partials, jobs[1].n, 1.0f,
@@ -932,7 +938,7 @@ static int hp_int8_fwd_impl(const int8_t* Xq, const float* gamma_x, const void* 
   PQ_REQUIRE(workspace_bytes >= L.ws_total, PQ_ERR_WORKSPACE, "workspace too small: %zu < %zu", workspace_bytes, L.ws_total);
   hipStream_t s = (hipStream_t)stream;
   char* cx = (char*)ctx;
-  void* sk = (char*)workspace + L.splitk;
+  const pq_scratch sk{(char*)workspace + L.splitk, L.splitk_bytes};
   // weight side: rows of A and B on the activation grid (codes, gamma, bf16 de-quantised copy for the backward)
   if (!rows_done) {
     if (int e = pq_launch_quant_act(A, dtype, r, K, (int8_t*)(cx + L.Aq), (float*)(cx + L.gA), (uint16_t*)(cx + L.At), s)) return e;
@@ -981,7 +987,7 @@ extern "C" int pq_hp_int8_bwd(const void* dY, const void* Xt, int32_t dtype, int
     pq_operand b{cx + L.At, K, PQ_SRC_KS16, nullptr};
     pq_epilogue e = epi_zero();
     e.C = dX; e.ldc = K; e.out_kind = PQ_OUT_BF16; e.accumulate = accumulate_dX ? 1 : 0;
-    if (int err = pq_launch_gemm(T, K, r, a, b, e, s, PQP_GEMM_DX_HP, ws + L.splitk)) return err;
+    if (int err = pq_launch_gemm(T, K, r, a, b, e, s, PQP_GEMM_DX_HP, {ws + L.splitk, L.splitk_bytes})) return err;
   }
   return PQ_OK;
 }
@@ -994,7 +1000,7 @@ static int hp_int8_dh(const void* dY, int T, int N, int r, float alpha, const ch
   if (red_a) {   // sum H~ .* (dY B~) = <dY, H~ B~^T>
     e.dot_comp = cx + L.Ht; e.ld_comp = r; e.comp_kind = PQ_OUT_BF16; e.partials = red_a;
   }
-  return pq_launch_gemm(T, r, N, a, b, e, s, PQP_GEMM_DH, ws + L.splitk);
+  return pq_launch_gemm(T, r, N, a, b, e, s, PQP_GEMM_DH, {ws + L.splitk, L.splitk_bytes});
 }
 
 static int hp_int8_factor_grads(const void* dY, const void* Xt, int T, int K, int N, int r, float alpha, const char* cx, const hp8_layout& L,
@@ -1003,8 +1009,8 @@ static int hp_int8_factor_grads(const void* dY, const void* Xt, int T, int K, in
   const void* dH = ws + L.dH;
   pq_operand a0{dY, N, PQ_SRC_KS16, nullptr}, b0{cx + L.Ht, r, PQ_SRC_KS16, nullptr};
   pq_operand a1{dH, r, PQ_SRC_KS16, nullptr}, b1{Xt, K, PQ_SRC_KS16, nullptr};
-  return pq_launch_gemm_pair_ks16(T, N, r, a0, b0, dB, r, alpha, r, K, a1, b1, dA, K, 1.0f, s, PQP_GEMM_DB, PQP_GEMM_DA, ws + L.splitk,
-                                  ws + L.splitk2, jobs, jobs_done);
+  return pq_launch_gemm_pair_ks16(T, N, r, a0, b0, dB, r, alpha, r, K, a1, b1, dA, K, 1.0f, s, PQP_GEMM_DB, PQP_GEMM_DA, {ws + L.splitk, L.splitk_bytes},
+                                  {ws + L.splitk2, L.splitk2_bytes}, jobs, jobs_done);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -38,7 +38,7 @@ struct ffn_layout {
   // X~ instead of X)
   size_t UGQ, gUG, UGT, DownQ, gDown, DownT, XqP, gxP, aQ, gA, aT, ctx_total;
   // workspace
-  size_t stat, red_a, red_b, splitk, dHd, dU, dG, dYp, rd, da, du, dg, as, dXs, dlogit, dwr, ws_total;
+  size_t stat, red_a, red_b, splitk, dHd, dU, dG, dYp, rd, da, du, dg, as, dXs, dlogit, dwr, splitk_bytes, ws_total;
   int n_red_a, n_red_b;
 };
 
@@ -103,6 +103,7 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   if (pq_mode2_ws_bytes(2 * (int)r, (int)D, (int)E, (int)S) > sk) sk = pq_mode2_ws_bytes(2 * (int)r, (int)D, (int)E, (int)S);
   if (8 * S * 2 * r * sizeof(float) > sk) sk = 8 * S * 2 * r * sizeof(float);
   L.splitk = w.take(sk);
+  L.splitk_bytes = sk;
   L.dHd = w.take(T * F * 2); L.dU = w.take(T * F * 2); L.dG = w.take(T * F * 2);
   L.dYp = w.take(S * D * 2); L.rd = w.take(S * 4);
   L.da = w.take(S * r * 2); L.du = w.take(2 * S * r * 2); L.dg = L.du + S * r * 2; L.as = w.take(S * r * 2);
@@ -181,7 +182,7 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
   // Fv: the width of the 1-bit FFN as the caller's weights have it; F: that width in whole packed words
   const int T = d->tokens, D = d->d_model, Fv = d->d_ffn, F = (Fv + 31) / 32 * 32, r = d->hp_rank, E = d->n_experts, k = d->top_k, S = T * k;
   double* part = (double*)(ws + L.stat);
-  void* sk = ws + L.splitk;
+  const pq_scratch sk{ws + L.splitk, L.splitk_bytes};
 
   int8_t* Xq = (int8_t*)(cx + L.Xq);
   float* gx = (float*)(cx + L.gx);
@@ -314,7 +315,7 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
   const char* cx = (const char*)ctx;
   char* ws = (char*)workspace;
   const int T = d->tokens, D = d->d_model, Fv = d->d_ffn, F = (Fv + 31) / 32 * 32, r = d->hp_rank, E = d->n_experts, k = d->top_k, S = T * k;
-  void* sk = ws + L.splitk;
+  const pq_scratch sk{ws + L.splitk, L.splitk_bytes};
   if (d->hp_kind == PQ_HP_LOWRANK_INT8) {  // STE: each product is differentiated with the de-quantised factors it multiplied
     Down = cx + L.DownT;
   }

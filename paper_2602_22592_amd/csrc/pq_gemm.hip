@@ -1869,6 +1869,11 @@ pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8, bool split_int8) {
   return pq_plan_gemm_impl(M, N, K, int8, !int8 || split_int8);
 }
 
+static int check_scratch(size_t need, const pq_scratch& sk) {
+  if (need == 0 || (sk.p && need <= sk.bytes)) return PQ_OK;
+  return pq_set_error(PQ_ERR_WORKSPACE, "split contraction needs %zu bytes of scratch, its section has %zu", need, sk.p ? sk.bytes : 0);
+}
+
 // Two narrow products over the same contraction in one launch (dB and dA of the rank-r branch).  tn: rank 128 over many
 // tokens, the streaming pair kernel (problem 1 runs transposed): four token ranges when that already gives a workgroup per
 // CU (fewer slabs to write and add), up to sixteen for small matrices, never shorter than 256 tokens.  Otherwise 64x64 tiles.
@@ -1899,7 +1904,7 @@ pq_pair_plan pq_plan_pair(int K, int M0, int N0, int M1, int N1) {
 
 int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const pq_operand& B0, float* C0, int ldc0, float scale0,
                              int M1, int N1, const pq_operand& A1, const pq_operand& B1, float* C1, int ldc1, float scale1,
-                             hipStream_t s, int prof_label0, int prof_label1, void* splitk_ws0, void* splitk_ws1,
+                             hipStream_t s, int prof_label0, int prof_label1, pq_scratch sk0, pq_scratch sk1,
                              const pq_reduce_job* jobs, bool* jobs_done) {
   if (jobs_done) *jobs_done = false;
   pq_epilogue e0;
@@ -1914,16 +1919,18 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
   auto al = [](const pq_operand& o) { return o.kind == PQ_SRC_KS16 && !o.kdiv && (o.ld * 2) % 16 == 0 && ((uintptr_t)o.p % 16) == 0; };
   const bool one = M0 > 0 && N0 > 0 && M1 > 0 && N1 > 0 && K > 0 && al(A0) && al(B0) && al(A1) && al(B1) && A0.ld >= M0 && B0.ld >= N0 &&
                    A1.ld >= M1 && B1.ld >= N1 &&
-                   (pp.splits == 1 || (splitk_ws0 && splitk_ws1 && ((uintptr_t)splitk_ws0 % 16) == 0 && ((uintptr_t)splitk_ws1 % 16) == 0));
+                   (pp.splits == 1 || (sk0.p && sk1.p && ((uintptr_t)sk0.p % 16) == 0 && ((uintptr_t)sk1.p % 16) == 0));
   if (!one) {
-    if (int rc = pq_launch_gemm(M0, N0, K, A0, B0, e0, s, prof_label0, splitk_ws0)) return rc;
-    return pq_launch_gemm(M1, N1, K, A1, B1, e1, s, prof_label1, splitk_ws1);
+    if (int rc = pq_launch_gemm(M0, N0, K, A0, B0, e0, s, prof_label0, sk0)) return rc;
+    return pq_launch_gemm(M1, N1, K, A1, B1, e1, s, prof_label1, sk1);
   }
+  if (int rc = check_scratch(pp.ws0, sk0)) return rc;
+  if (int rc = check_scratch(pp.ws1, sk1)) return rc;
   {
     pq_prof_scope prof(prof_label0, s);
     if (pp.tn) {
-      skt_problem q0{(const uint16_t*)A0.p, A0.ld, (const uint16_t*)B0.p, B0.ld, M0, 0, (float*)splitk_ws0};
-      skt_problem q1{(const uint16_t*)B1.p, B1.ld, (const uint16_t*)A1.p, A1.ld, N1, 1, (float*)splitk_ws1};
+      skt_problem q0{(const uint16_t*)A0.p, A0.ld, (const uint16_t*)B0.p, B0.ld, M0, 0, (float*)sk0.p};
+      skt_problem q1{(const uint16_t*)B1.p, B1.ld, (const uint16_t*)A1.p, A1.ld, N1, 1, (float*)sk1.p};
       const dim3 grid((M0 > N1 ? M0 : N1) / 64, pp.splits, 2);
       skinny_tn_pair_kernel<<<grid, 256, 0, s>>>(q0, q1, K / pp.splits);
       PQ_CHECK_LAUNCH("skinny_tn_pair_kernel");
@@ -1935,16 +1942,16 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
       memset(&grp, 0, sizeof(grp));
       grp.mode = 3;
       grp.second.A = A1; grp.second.B = B1; grp.second.C = C1; grp.second.ldc = ldc1; grp.second.scale = scale1;
-      grp.second.part = pp.splits > 1 ? (float*)splitk_ws1 : nullptr; grp.second.M = M1; grp.second.N = N1; grp.second.nbn = (N1 + 63) / 64;
+      grp.second.part = pp.splits > 1 ? (float*)sk1.p : nullptr; grp.second.M = M1; grp.second.N = N1; grp.second.nbn = (N1 + 63) / 64;
       pq_phase2 ph2;
       memset(&ph2, 0, sizeof(ph2));
-      if (int rc = pq_launch_tile(pl, M0, N0, K, A0, B0, e0, s, (float*)splitk_ws0, grp, ph2)) return rc;
+      if (int rc = pq_launch_tile(pl, M0, N0, K, A0, B0, e0, s, (float*)sk0.p, grp, ph2)) return rc;
     }
   }
   if (pp.splits > 1) {
     pq_prof_scope prof(PQP_SPLITK_REDUCE, s);
-    splitk_reduce_pair_kernel<false><<<rb0 + rb1 + (jobs ? 2 : 0), 256, 0, s>>>(pp.splits, rb0, rb1, M0, N0, (const float*)splitk_ws0, e0, M1, N1,
-                                                                        (const float*)splitk_ws1, e1, jobs ? jobs[0] : none,
+    splitk_reduce_pair_kernel<false><<<rb0 + rb1 + (jobs ? 2 : 0), 256, 0, s>>>(pp.splits, rb0, rb1, M0, N0, (const float*)sk0.p, e0, M1, N1,
+                                                                        (const float*)sk1.p, e1, jobs ? jobs[0] : none,
                                                                         jobs ? jobs[1] : none);
     PQ_CHECK_LAUNCH("splitk_reduce_pair_kernel");
     if (jobs && jobs_done) *jobs_done = true;
@@ -1956,14 +1963,14 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
 // one launch: one start and one tail instead of two, and together they fill the chip where each alone does not.
 pq_gemm_plan pq_plan_dual(int M, int N, int K, bool int8) { return pq_plan_gemm_impl(2 * M, N, K, int8, true); }
 int pq_launch_gemm_dual(int M, int N, int K, const pq_operand& A0, const pq_operand& B0, const pq_epilogue& e0, const pq_operand& A1,
-                        const pq_operand& B1, void* C1, const float* dev_scale1, hipStream_t s, int prof_label, void* splitk_ws) {
+                        const pq_operand& B1, void* C1, const float* dev_scale1, hipStream_t s, int prof_label, pq_scratch sk) {
   if (M <= 0 || N <= 0) return PQ_OK;
   const bool int8 = A0.kind == PQ_SRC_KC8;
   const pq_gemm_plan pl = pq_plan_dual(M, N, K, int8);
-  if (pl.splits > 1 && !splitk_ws) return pq_set_error(PQ_ERR_WORKSPACE, "split contraction needs scratch");
+  if (int rc = check_scratch(pl.ws_bytes, sk)) return rc;
   if (e0.partials || e0.accumulate || e0.dot_comp || e0.sign_bytes || e0.maskW || e0.n_limit % 4)
     return pq_set_error(PQ_ERR_BAD_ARG, "paired products take plain epilogues");
-  float* part = (float*)splitk_ws;
+  float* part = (float*)sk.p;
   pq_gemm_group grp;
   memset(&grp, 0, sizeof(grp));
   grp.mode = 3;
@@ -2018,7 +2025,7 @@ size_t pq_mode2_ws_bytes(int M, int N, int n_groups, int total_k) {
 }
 
 int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B,
-                   const pq_epilogue& epi, hipStream_t s, int prof_label, void* splitk_ws,
+                   const pq_epilogue& epi, hipStream_t s, int prof_label, pq_scratch sk,
                    const pq_gemm_group* group, const pq_phase2* phase2) {
   if (M <= 0 || N <= 0) return PQ_OK;
   pq_gemm_group grp;
@@ -2043,12 +2050,13 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
   if (grp.mode) {
     pl.splits = 1;
     pl.kchunk = K > 0 ? K : 1;
+    pl.ws_bytes = 0;
     pl.bm = pl.bn = 64;
     // contraction ranges: pieces only for a plain fp32 output whose groups lie one behind the other
     if (grp.mode == 2) {
       const mode2_plan p2 = plan_mode2(M, N, grp.n_groups, K);
       pl.bm = pl.bn = p2.bm;
-      if (p2.splits > 1 && splitk_ws && epi.out_kind == PQ_OUT_F32 && epi.ldc == N && grp.c_stride == (long)(epi.m_split ? epi.m_split : M) * N && N % 8 == 0 &&
+      if (p2.splits > 1 && sk.p && epi.out_kind == PQ_OUT_F32 && epi.ldc == N && grp.c_stride == (long)(epi.m_split ? epi.m_split : M) * N && N % 8 == 0 &&
           !epi.partials && !epi.dot_comp && !epi.sign_bytes && !epi.maskW && !epi.accumulate && !epi.row_div && !epi.col_div &&
           epi.m_limit == 0 && epi.n_limit == 0) {
         pl.splits = p2.splits;
@@ -2062,7 +2070,7 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
     if (grp.mode == 1) {
       const bool narrow = N <= 128, wide = N >= 256 && K % 512 == 0 && epi.out_kind == PQ_OUT_BF16 && !epi.accumulate && !epi.row_div;
       // (N <= K: callers size the scratch for eight slabs as wide as the hidden states)
-      const bool may = (narrow || wide) && N <= K && K >= 1024 && splitk_ws && !(epi.col_div && grp.coldiv_stride);
+      const bool may = (narrow || wide) && N <= K && K >= 1024 && sk.p && !(epi.col_div && grp.coldiv_stride);
       const int epb = int8 ? 128 : 64;
       double best = 1e30;
       for (int bm = 64; bm <= 256; bm *= 2) {
@@ -2082,8 +2090,8 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
       }
     }
   }
-  if (pl.splits > 1 && !splitk_ws) return pq_set_error(PQ_ERR_WORKSPACE, "split contraction needs scratch");
-  float* part = (float*)splitk_ws;
+  if (int rc = check_scratch(pl.ws_bytes, sk)) return rc;
+  float* part = (float*)sk.p;
   int rc;
   {
     pq_prof_scope prof(prof_label, s);   // the MFMA kernel alone; a split's reduction is timed under its own label

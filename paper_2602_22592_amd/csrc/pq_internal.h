@@ -169,6 +169,13 @@ struct pq_gemm_group {
   long coldiv_stride;  // mode 1: group e divides its columns by col_div[e * coldiv_stride + n] (per-expert weight-row scales)
 };
 
+// A section of the caller's workspace that a split contraction leaves its slabs in.  Every launch compares what its plan
+// writes with `bytes` and is refused (PQ_ERR_WORKSPACE) when the section is too small for it.
+struct pq_scratch {
+  void* p;
+  size_t bytes;
+};
+
 struct pq_gemm_plan {
   int bm, bn;        // tile
   int splits;        // contraction splits (1 = none)
@@ -197,17 +204,17 @@ int pq_launch_skinny(int M, int K, const pq_operand& A, const pq_operand& B, con
 
 int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const pq_operand& B0, float* C0, int ldc0, float scale0,
                              int M1, int N1, const pq_operand& A1, const pq_operand& B1, float* C1, int ldc1, float scale1,
-                             hipStream_t s, int prof_label0, int prof_label1, void* splitk_ws0, void* splitk_ws1,
+                             hipStream_t s, int prof_label0, int prof_label1, pq_scratch sk0, pq_scratch sk1,
                              const pq_reduce_job* jobs = nullptr, bool* jobs_done = nullptr);   // jobs: two scalar reductions to ride along
 // ---- pq_tile.hip: the 64x64 and 128x128 streaming tiles (pl.bm; the contraction split is the caller's plan) ----
 int pq_launch_tile(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi, hipStream_t s,
                    float* part, const pq_gemm_group& grp, const pq_phase2& ph2);
 pq_gemm_plan pq_plan_dual(int M, int N, int K, bool int8);   // (its ws_bytes: the slabs of both)
 int pq_launch_gemm_dual(int M, int N, int K, const pq_operand& A0, const pq_operand& B0, const pq_epilogue& e0, const pq_operand& A1,
-                        const pq_operand& B1, void* C1, const float* dev_scale1, hipStream_t s, int prof_label, void* splitk_ws);
+                        const pq_operand& B1, void* C1, const float* dev_scale1, hipStream_t s, int prof_label, pq_scratch sk);
 int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B,
                    const pq_epilogue& epi, hipStream_t s, int prof_label = PQP_GEMM_OTHER,
-                   void* splitk_ws = nullptr, const pq_gemm_group* group = nullptr,
+                   pq_scratch sk = {nullptr, 0}, const pq_gemm_group* group = nullptr,
                    const pq_phase2* phase2 = nullptr);
 
 // ---- pq_ref.hip ---------------------------------------------------------------------------

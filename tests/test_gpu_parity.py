@@ -337,7 +337,10 @@ def test_linear_routed_experts_reject_fp32():
 
 
 # ---------------------------------------------------------------------------- INT8 form of the dense branch via hp_kind
-@pytest.mark.parametrize("T,K,N,r", [(64, 256, 256, 32), (300, 1024, 768, 64), (1100, 512, 384, 128), (0, 64, 64, 32)])
+@pytest.mark.parametrize("T,K,N,r", [(64, 256, 256, 32), (300, 1024, 768, 64), (1100, 512, 384, 128), (0, 64, 64, 32),
+                                     # the input gradient's 1-bit product splits its contraction over 256x256 tiles: the branch's share is
+                                     # a launch of its own; at rank 2560 with more splits than the first one's
+                                     (1111, 1824, 2400, 96), (658, 3712, 4000, 2560)])
 def test_linear_with_int8_high_precision_branch(T, K, N, r):
     """hp_kind = PQ_HP_LOWRANK_INT8 through pq_linear_fwd / pq_linear_bwd (Sec. 3.2): the branch consumes the codes of
     the 1-bit branch; expected values are oracle.linear_fwd without a branch plus oracle.hp_int8_fwd / hp_int8_bwd."""
