@@ -1,12 +1,28 @@
 // Pieces shared by the MFMA GEMM kernels (pq_gemm.hip, pq_tile.hip): the epilogue over eight consecutive columns and the
 // expansion of packed signs into MFMA operands.
 #pragma once
+#include <string.h>
+#include <type_traits>
 #include "pq_internal.h"
 
 typedef int pq_i32x2 __attribute__((ext_vector_type(2)));
 #define PQ_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 
 namespace {
+
+// The second problem of a paired launch as a kernel argument: empty in kernels that are never paired.
+struct pq_no_second {};
+template <bool PAIR>
+using pq_second_arg = typename std::conditional<PAIR, pq_gemm_second, pq_no_second>::type;
+template <bool PAIR>
+pq_second_arg<PAIR> second_arg(const pq_gemm_second* second) {
+  if constexpr (PAIR) {
+    if (second) return *second;
+    pq_gemm_second none;
+    memset(&none, 0, sizeof(none));
+    return none;
+  } else return pq_no_second{};
+}
 
 // ---------------------------------------------------------------------------------------------
 // Epilogue
@@ -51,14 +67,16 @@ __device__ __forceinline__ void load_io8(const void* p, int kind, size_t i, floa
   }
 }
 
-template <bool INT8>
-// row_scale: sc0 / row_div[m] when the caller has it at hand (NaN = not given, it is formed here)
+// row_scale: sc0 / row_div[m] when the caller has it at hand (NaN = not given, it is formed here).  TWO: the epilogue may have a
+// second destination (C2, m_split); a template argument because the address arithmetic, inlined into every kernel, cost registers
+// in all of them (step of 8192 tokens 2048x2048 r=128: 275.3 us with it everywhere, 272.1 without).
+template <bool INT8, bool TWO = false>
 __device__ __forceinline__ void epi_vec8(const pq_epilogue& e, epi_state& st, int m, int n, const uint4& r0,
                                          const uint4& r1, float row_scale = __builtin_nanf("")) {
   size_t ci = (size_t)m * e.ldc + n;
   if ((e.m_limit > 0 && m >= e.m_limit) || (e.n_limit > 0 && n >= e.n_limit)) return;
   void* cdst = e.C;
-  if (e.m_split > 0) {                               // uniform
+  if (TWO && e.m_split > 0) {                        // uniform
     const int z = m / (2 * e.m_split), mm = m - z * 2 * e.m_split;
     const bool hi = mm >= e.m_split;
     ci = (size_t)(z * e.m_split + (hi ? mm - e.m_split : mm)) * e.ldc + n;

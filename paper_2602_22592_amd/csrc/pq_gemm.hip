@@ -290,7 +290,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
                                                                      pq_operand B, pq_epilogue epi,
                                                                      int nbn, int total_tiles, int kchunk,
                                                                      float* splitk_part, pq_gemm_group grp,
-                                                                     pq_phase2 ph2) {
+                                                                     pq_phase2 ph2, pq_second_arg<DUAL> second) {
   constexpr int NT = WGM * WGN * 64;
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -313,9 +313,9 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
   // operand panels it streams are shared by its workgroups instead of being fetched by every XCD.
   if constexpr (DUAL)
     if (blockIdx.z == 1) {                           // uniform
-      A = grp.second.A; B = grp.second.B;
-      epi.C = grp.second.C; epi.dev_scale = grp.second.dev_scale;
-      splitk_part = grp.second.part;
+      A = second.A; B = second.B;
+      epi.C = second.C; epi.dev_scale = second.dev_scale;
+      splitk_part = second.part;
     }
   int pid = blockIdx.x, split = blockIdx.y;
   {
@@ -1050,7 +1050,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
 // Second stage of a split contraction: sum the slabs in index order (deterministic), then apply
 // the caller's epilogue.  One thread per 8 consecutive columns.
 // INT: the slabs hold int32 accumulators (int8 engine); their sum is exact.
-template <bool INT>
+template <bool INT, bool TWO>
 __device__ __forceinline__ void splitk_reduce_body(int M, int N, int splits, const float* __restrict__ part, const pq_epilogue& epi,
                                                    int block) {
   __shared__ double red[4];
@@ -1091,16 +1091,16 @@ __device__ __forceinline__ void splitk_reduce_body(int M, int N, int splits, con
     } else {
       const uint4 r0 = make_uint4(__float_as_uint(a.x), __float_as_uint(a.y), __float_as_uint(a.z), __float_as_uint(a.w));
       const uint4 r1 = make_uint4(__float_as_uint(b.x), __float_as_uint(b.y), __float_as_uint(b.z), __float_as_uint(b.w));
-      epi_vec8<false>(epi, st, m, n, r0, r1);
+      epi_vec8<false, TWO>(epi, st, m, n, r0, r1);
     }
   }
   epi_end<256>(epi, st, red, block);
 }
 
-template <bool INT>
+template <bool INT, bool TWO>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(int M, int N, int splits, const float* __restrict__ part,
                                                             pq_epilogue epi) {
-  splitk_reduce_body<INT>(M, N, splits, part, epi, blockIdx.x);
+  splitk_reduce_body<INT, TWO>(M, N, splits, part, epi, blockIdx.x);
 }
 
 // The reductions of a paired launch in one launch: the first nblk0 workgroups finish problem 0, the rest problem 1.
@@ -1111,8 +1111,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_pair_kernel(int splits, int
                                                                  const float* __restrict__ part1, pq_epilogue epi1, pq_reduce_job j0,
                                                                  pq_reduce_job j1) {
   const int b = blockIdx.x;
-  if (b < nblk0) splitk_reduce_body<INT>(M0, N0, splits, part0, epi0, b);
-  else if (b < nblk0 + nblk1) splitk_reduce_body<INT>(M1, N1, splits, part1, epi1, b - nblk0);
+  if (b < nblk0) splitk_reduce_body<INT, false>(M0, N0, splits, part0, epi0, b);
+  else if (b < nblk0 + nblk1) splitk_reduce_body<INT, false>(M1, N1, splits, part1, epi1, b - nblk0);
   else pq_reduce_job_body(b == nblk0 + nblk1 ? j0 : j1);
 }
 
@@ -1149,10 +1149,10 @@ struct pq_frag_set_w4 {
 };
 
 // RAGGED: the last stage of a range is not whole; its missing rows come from a page of zeros.  (An instantiation of its own: the
-// test behind every load cost the whole ones 3 to 4 %.)
-template <bool RAGGED, bool DUAL>
+// test behind every load cost the whole ones 3 to 4 %.)  TWO: the epilogue has a second destination.
+template <bool RAGGED, bool DUAL, bool TWO>
 __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn,
-                                                          int total_tiles, int kchunk, float* splitk_part, pq_gemm_second second) {
+                                                          int total_tiles, int kchunk, float* splitk_part, pq_second_arg<DUAL> second) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int STG = 32768;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[4 * STG];
@@ -1180,14 +1180,6 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm0 = (wv >> 1) * 128, wn0 = (wv & 1) * 128;
   const uint32_t lds0 = (uint32_t)(size_t)smem;
-
-  f32x16_t acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
   // direct loads: instruction block qi of an operand is 1 KB of its stage (two contraction rows); a wavefront owns four
   // blocks of each operand.  Columns past the end fetch the tile's first chunk (any valid address: never stored).
@@ -1232,10 +1224,6 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
     PQ_DS_READ_TR(F.h[2 * q], pa, ks * 8192);
     PQ_DS_READ_TR(F.h[2 * q + 1], pa, ks * 8192 + 2048);
   };
-  auto mf = [&](const pq_frag_set_w4& X, int n) {
-    const int i = n >> 2, j = (n & 3) ^ ((i & 1) ? 3 : 0);   // a block of B stays for two MFMAs in a row
-    PQ_MFMA_BF16_ACC(acc[i][j], X.op(i), X.op(4 + j));
-  };
   using c0 = std::integral_constant<int, 0>;
   using c1 = std::integral_constant<int, 1>;
 
@@ -1244,11 +1232,29 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
     for (int u = 0; u < 3; ++u)
 #pragma unroll
       for (int i = 0; i < 8; ++i) issue1(min(u, nkt - 1), u, i);
+  }
+  // 256 register writes per wavefront, under the latency of the first loads.  (The empty statements keep them here and make the
+  // values opaque: left to itself the compiler zeroed the registers ahead of the loads and a second time behind them, 1.3 us
+  // of a 65 us product.)
+  f32x16_t acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+      asm volatile("" : "+a"(acc[i][j]));
+    }
+  if (nkt > 0) {
     asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
     asm volatile("s_barrier" ::: "memory");
 #pragma unroll
     for (int q = 0; q < 8; ++q) rd(F0, q, 0u, c0{});
   }
+  auto mf = [&](const pq_frag_set_w4& X, int n) {
+    const int i = n >> 2, j = (n & 3) ^ ((i & 1) ? 3 : 0);   // a block of B stays for two MFMAs in a row
+    PQ_MFMA_BF16_ACC(acc[i][j], X.op(i), X.op(4 + j));
+  };
   for (int kt = 0; kt < nkt; ++kt) {
     const uint32_t so = (uint32_t)(kt & 3) * STG, sn = (uint32_t)((kt + 1) & 3) * STG;
     const int ktl = min(kt + 3, nkt - 1), sl = (kt + 3) & 3;
@@ -1280,7 +1286,7 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
   epi_begin(epi, st);
   float* slab = splitk_part ? splitk_part + (size_t)split * M * N : nullptr;
   const bool plain = !slab && epi.out_kind == PQ_OUT_F32 && !epi.col_div && !epi.maskW && !epi.accumulate && !epi.dot_comp &&
-                     !epi.sign_bytes && epi.m_split == 0;                 // uniform
+                     !epi.sign_bytes && !TWO;                 // uniform
   unsigned tid_e = threadIdx.x;
   asm volatile("" : "+v"(tid_e));
   const int lane_e = tid_e & 63, wave_e = tid_e >> 6;
@@ -1330,7 +1336,7 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
         const uint4 r0 = *reinterpret_cast<const uint4*>(wreg + rl * 512 + ((c ^ (rl & 31)) << 4));
         const uint4 r1 = *reinterpret_cast<const uint4*>(wreg + rl * 512 + (((c + 1) ^ (rl & 31)) << 4));
         const int m = m0 + wm_e + pass * 64 + rl, n = n0 + wn_e + c * 4;
-        if (m < M && n < N) epi_vec8<false>(epi, st, m, n, r0, r1);
+        if (m < M && n < N) epi_vec8<false, TWO>(epi, st, m, n, r0, r1);
       }
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -1342,22 +1348,24 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
 
 template <int BM, int BN, int WGM, int WGN, int KB, bool FAST, bool TAIL, bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1, bool DUAL = false>
 int launch_mfma(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B,
-                const pq_epilogue& epi, hipStream_t s, float* part, const pq_gemm_group& grp, const pq_phase2& ph2) {
+                const pq_epilogue& epi, hipStream_t s, float* part, const pq_gemm_group& grp, const pq_phase2& ph2,
+                const pq_gemm_second* second = nullptr) {
   // grouped rows: every group may end in a partial tile, so at most ceil(rows / BM) + n_groups row tiles exist
   const int nbm = grp.mode == 1 ? (grp.max_rows + BM - 1) / BM + grp.n_groups : (M + BM - 1) / BM;
   const int nbn = (N + BN - 1) / BN;
   const int tiles = nbm * nbn;
   dim3 grid(tiles, pl.splits, DUAL ? 2 : 1), block(WGM * WGN * 64);
   mfma_gemm_kernel<BM, BN, WGM, WGN, KB, FAST, TAIL, INT8, AK, BKIND, AK2, BK2, DUAL><<<grid, block, 0, s>>>(
-      M, N, K, A, B, epi, nbn, tiles, pl.kchunk, pl.splits > 1 ? part : nullptr, grp, ph2);
+      M, N, K, A, B, epi, nbn, tiles, pl.kchunk, pl.splits > 1 ? part : nullptr, grp, ph2, second_arg<DUAL>(second));
   PQ_CHECK_LAUNCH("mfma_gemm_kernel");
   return PQ_OK;
 }
 
 template <bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1>
 int launch_mfma_cfg(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B,
-                    const pq_epilogue& epi, hipStream_t s, float* part, const pq_gemm_group& grp, const pq_phase2& ph2) {
-  if (pl.bm != 256) return pq_launch_tile(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+                    const pq_epilogue& epi, hipStream_t s, float* part, const pq_gemm_group& grp, const pq_phase2& ph2,
+                    const pq_gemm_second* second = nullptr) {
+  if (pl.bm != 256) return pq_launch_tile(pl, M, N, K, A, B, epi, s, part, grp, ph2, second);
   // rows of 16-byte chunks on 16-byte boundaries, as every width and section of this library has them
   const long aes = AK == PQ_SRC_KC8 ? 1 : 2, bes = BKIND == PQ_SRC_KC8 ? 1 : 2;
   constexpr bool bits = BKIND == PQ_SRC_BITS8 || BKIND == PQ_SRC_BITS16;
@@ -1371,10 +1379,11 @@ int launch_mfma_cfg(const pq_gemm_plan& pl, int M, int N, int K, const pq_operan
     dim3 grid(nbm * nbn, pl.splits, dual ? 2 : 1);
     if ((grp.mode && !dual) || A.kdiv || B.kdiv || epi.row_div || epi.out_kind == PQ_OUT_I32) return pq_set_error(PQ_ERR_BAD_ARG, "no 256x256 weight-gradient kernel for this epilogue");
     float* p = pl.splits > 1 ? part : nullptr;
-#define PQ_W4(R, D) gemm_tn_w4_kernel<R, D><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, nbm * nbn, pl.kchunk, p, grp.second)
-    if (dual) { if (ragged) PQ_W4(true, true); else PQ_W4(false, true); }
-    else if (ragged) PQ_W4(true, false);
-    else PQ_W4(false, false);
+#define PQ_W4(R, D, T) gemm_tn_w4_kernel<R, D, T><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, nbm * nbn, pl.kchunk, p, second_arg<D>(second))
+    if (dual) { if (ragged) PQ_W4(true, true, false); else PQ_W4(false, true, false); }
+    else if (epi.m_split > 0) { if (ragged) PQ_W4(true, false, true); else PQ_W4(false, false, true); }
+    else if (ragged) PQ_W4(true, false, false);
+    else PQ_W4(false, false, false);
 #undef PQ_W4
     PQ_CHECK_LAUNCH("gemm_tn_w4_kernel");
     return PQ_OK;
@@ -1385,8 +1394,8 @@ int launch_mfma_cfg(const pq_gemm_plan& pl, int M, int N, int K, const pq_operan
     const bool tiles = grp.mode == 0 && M % 256 == 0 && N % 256 == 0 && ph2.K2 % 64 == 0;
     if constexpr (AK == PQ_SRC_KC8 && BKIND == PQ_SRC_BITS8 && AK2 < 0) {
       if (grp.mode == 3) {
-        if (steps) return launch_mfma<256, 256, 2, 4, 128, false, false, INT8, AK, BKIND, AK2, BK2, true>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
-        return launch_mfma<256, 256, 2, 4, 128, false, true, INT8, AK, BKIND, AK2, BK2, true>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+        if (steps) return launch_mfma<256, 256, 2, 4, 128, false, false, INT8, AK, BKIND, AK2, BK2, true>(pl, M, N, K, A, B, epi, s, part, grp, ph2, second);
+        return launch_mfma<256, 256, 2, 4, 128, false, true, INT8, AK, BKIND, AK2, BK2, true>(pl, M, N, K, A, B, epi, s, part, grp, ph2, second);
       }
     }
     if (grp.mode == 3) return pq_set_error(PQ_ERR_BAD_ARG, "no paired 256x256 kernel for these operand kinds");
@@ -1941,11 +1950,10 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
       pq_gemm_group grp;
       memset(&grp, 0, sizeof(grp));
       grp.mode = 3;
-      grp.second.A = A1; grp.second.B = B1; grp.second.C = C1; grp.second.ldc = ldc1; grp.second.scale = scale1;
-      grp.second.part = pp.splits > 1 ? (float*)sk1.p : nullptr; grp.second.M = M1; grp.second.N = N1; grp.second.nbn = (N1 + 63) / 64;
+      pq_gemm_second second{A1, B1, C1, ldc1, scale1, pp.splits > 1 ? (float*)sk1.p : nullptr, nullptr, M1, N1, (N1 + 63) / 64};
       pq_phase2 ph2;
       memset(&ph2, 0, sizeof(ph2));
-      if (int rc = pq_launch_tile(pl, M0, N0, K, A0, B0, e0, s, (float*)sk0.p, grp, ph2)) return rc;
+      if (int rc = pq_launch_tile(pl, M0, N0, K, A0, B0, e0, s, (float*)sk0.p, grp, ph2, &second)) return rc;
     }
   }
   if (pp.splits > 1) {
@@ -1968,22 +1976,21 @@ int pq_launch_gemm_dual(int M, int N, int K, const pq_operand& A0, const pq_oper
   const bool int8 = A0.kind == PQ_SRC_KC8;
   const pq_gemm_plan pl = pq_plan_dual(M, N, K, int8);
   if (int rc = check_scratch(pl.ws_bytes, sk)) return rc;
-  if (e0.partials || e0.accumulate || e0.dot_comp || e0.sign_bytes || e0.maskW || e0.n_limit % 4)
+  if (e0.partials || e0.accumulate || e0.dot_comp || e0.sign_bytes || e0.maskW || e0.m_split || e0.n_limit % 4)
     return pq_set_error(PQ_ERR_BAD_ARG, "paired products take plain epilogues");
   float* part = (float*)sk.p;
   pq_gemm_group grp;
   memset(&grp, 0, sizeof(grp));
   grp.mode = 3;
-  grp.second.A = A1; grp.second.B = B1; grp.second.C = C1; grp.second.ldc = (int)e0.ldc; grp.second.scale = e0.scale; grp.second.dev_scale = dev_scale1;
-  grp.second.part = pl.splits > 1 ? part + (size_t)pl.splits * M * N : nullptr;
-  grp.second.M = M; grp.second.N = N; grp.second.nbn = (N + pl.bm - 1) / pl.bm;
+  const pq_gemm_second second{A1, B1, C1, (int)e0.ldc, e0.scale, pl.splits > 1 ? part + (size_t)pl.splits * M * N : nullptr, dev_scale1,
+                              M, N, (N + pl.bm - 1) / pl.bm};
   pq_phase2 ph2;
   memset(&ph2, 0, sizeof(ph2));
   {
     pq_prof_scope prof(prof_label, s);
     int rc;
-    if (int8 && B0.kind == PQ_SRC_BITS8) rc = launch_mfma_cfg<true, PQ_SRC_KC8, PQ_SRC_BITS8>(pl, M, N, K, A0, B0, e0, s, part, grp, ph2);
-    else if (A0.kind == PQ_SRC_KS16 && B0.kind == PQ_SRC_KS16) rc = launch_mfma_cfg<false, PQ_SRC_KS16, PQ_SRC_KS16>(pl, M, N, K, A0, B0, e0, s, part, grp, ph2);
+    if (int8 && B0.kind == PQ_SRC_BITS8) rc = launch_mfma_cfg<true, PQ_SRC_KC8, PQ_SRC_BITS8>(pl, M, N, K, A0, B0, e0, s, part, grp, ph2, &second);
+    else if (A0.kind == PQ_SRC_KS16 && B0.kind == PQ_SRC_KS16) rc = launch_mfma_cfg<false, PQ_SRC_KS16, PQ_SRC_KS16>(pl, M, N, K, A0, B0, e0, s, part, grp, ph2, &second);
     else return pq_set_error(PQ_ERR_BAD_ARG, "no paired kernel for operand kinds (%d, %d)", A0.kind, B0.kind);
     if (rc) return rc;
   }
@@ -1994,8 +2001,8 @@ int pq_launch_gemm_dual(int M, int N, int K, const pq_operand& A0, const pq_oper
     pq_reduce_job none;
     memset(&none, 0, sizeof(none));
     const int rb = (int)(((size_t)M * (N / 8) + 255) / 256);
-    if (int8) splitk_reduce_pair_kernel<true><<<2 * rb, 256, 0, s>>>(pl.splits, rb, rb, M, N, part, e0, M, N, grp.second.part, e1, none, none);
-    else splitk_reduce_pair_kernel<false><<<2 * rb, 256, 0, s>>>(pl.splits, rb, rb, M, N, part, e0, M, N, grp.second.part, e1, none, none);
+    if (int8) splitk_reduce_pair_kernel<true><<<2 * rb, 256, 0, s>>>(pl.splits, rb, rb, M, N, part, e0, M, N, second.part, e1, none, none);
+    else splitk_reduce_pair_kernel<false><<<2 * rb, 256, 0, s>>>(pl.splits, rb, rb, M, N, part, e0, M, N, second.part, e1, none, none);
     PQ_CHECK_LAUNCH("splitk_reduce_pair_kernel");
   }
   return PQ_OK;
@@ -2115,8 +2122,9 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
     pq_prof_scope prof(PQP_SPLITK_REDUCE, s);
     const int Mred = grp.mode == 2 ? grp.n_groups * M : M;   // grouped ranges: the groups' outputs as one matrix
     // (with a second contraction the slabs are already floating-point numbers)
-    if (int8 && ph2.K2 == 0) splitk_reduce_kernel<true><<<pl.red_blocks, 256, 0, s>>>(Mred, N, pl.splits, part, epi);
-    else splitk_reduce_kernel<false><<<pl.red_blocks, 256, 0, s>>>(Mred, N, pl.splits, part, epi);
+    if (int8 && ph2.K2 == 0) splitk_reduce_kernel<true, false><<<pl.red_blocks, 256, 0, s>>>(Mred, N, pl.splits, part, epi);
+    else if (epi.m_split > 0) splitk_reduce_kernel<false, true><<<pl.red_blocks, 256, 0, s>>>(Mred, N, pl.splits, part, epi);
+    else splitk_reduce_kernel<false, false><<<pl.red_blocks, 256, 0, s>>>(Mred, N, pl.splits, part, epi);
     PQ_CHECK_LAUNCH("splitk_reduce_kernel");
   }
   return PQ_OK;

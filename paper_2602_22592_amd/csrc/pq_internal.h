@@ -148,7 +148,8 @@ struct pq_phase2 {
 // contraction index runs over [offsets[e], offsets[e+1]) and the result goes to C + e*c_stride
 // (elements of C's type) -- the per-expert weight gradients.  max_rows bounds a segment (launch size).
 // mode 3: two independent GEMMs of the same operand kinds, tile shape and contraction split in one launch;
-// workgroups with blockIdx.z == 1 work on `second` (plain epilogue: C = scale * acc, or raw slabs when split).
+// workgroups with blockIdx.z == 1 work on the second (plain epilogue: C = scale * acc, or raw slabs when split).  Its
+// description is an argument of the paired kernels only.
 struct pq_gemm_second {
   pq_operand A, B;
   void* C;
@@ -165,7 +166,6 @@ struct pq_gemm_group {
   long b_stride;
   long c_stride;
   int max_rows;
-  pq_gemm_second second;
   long coldiv_stride;  // mode 1: group e divides its columns by col_div[e * coldiv_stride + n] (per-expert weight-row scales)
 };
 
@@ -208,7 +208,7 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
                              const pq_reduce_job* jobs = nullptr, bool* jobs_done = nullptr);   // jobs: two scalar reductions to ride along
 // ---- pq_tile.hip: the 64x64 and 128x128 streaming tiles (pl.bm; the contraction split is the caller's plan) ----
 int pq_launch_tile(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi, hipStream_t s,
-                   float* part, const pq_gemm_group& grp, const pq_phase2& ph2);
+                   float* part, const pq_gemm_group& grp, const pq_phase2& ph2, const pq_gemm_second* second = nullptr);
 pq_gemm_plan pq_plan_dual(int M, int N, int K, bool int8);   // (its ws_bytes: the slabs of both)
 int pq_launch_gemm_dual(int M, int N, int K, const pq_operand& A0, const pq_operand& B0, const pq_epilogue& e0, const pq_operand& A1,
                         const pq_operand& B1, void* C1, const float* dev_scale1, hipStream_t s, int prof_label, pq_scratch sk);

@@ -21,6 +21,10 @@ namespace {
 
 [[maybe_unused]] __device__ __attribute__((aligned(256))) unsigned char pq_zero_page[256];   // never written
 
+// operand kinds that launches of two products come in: U and G, dW_up and dW_gate, dB and dA
+template <int AK, int BK, int BK2>
+constexpr bool pair_kinds() { return BK2 < 0 && ((AK == PQ_SRC_KS16 && BK == PQ_SRC_KS16) || (AK == PQ_SRC_KC8 && BK == PQ_SRC_BITS8)); }
+
 // Operand tile of ROWS rows (or columns, KS16) x 128 bytes of contraction per step.
 template <int KIND, int ROWS>
 struct tile_src {
@@ -269,7 +273,8 @@ __device__ __forceinline__ void tile_step(const FA& fa, const FB& fb, uint32_t s
 
 template <int BM, int BN, int NST, bool INT8, int AK, int BK, int BK2>
 __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn,
-                                                        int total_tiles, int kchunk, float* splitk_part, pq_gemm_group grp, pq_phase2 ph2) {
+                                                        int total_tiles, int kchunk, float* splitk_part, pq_gemm_group grp, pq_phase2 ph2,
+                                                        pq_second_arg<pair_kinds<AK, BK, BK2>()> second) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;
   constexpr int EPB = INT8 ? 128 : 64;
@@ -287,12 +292,14 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
   __shared__ double red[4];
 
-  if (grp.mode == 3 && blockIdx.z == 1) {            // uniform: the second problem of a paired launch
-    A = grp.second.A; B = grp.second.B;
-    M = grp.second.M; N = grp.second.N; nbn = grp.second.nbn;
-    splitk_part = grp.second.part;
-    epi.C = grp.second.C; epi.ldc = grp.second.ldc; epi.scale = grp.second.scale; epi.dev_scale = grp.second.dev_scale;
-  }
+  constexpr bool PAIR = pair_kinds<AK, BK, BK2>();
+  if constexpr (PAIR)
+    if (grp.mode == 3 && blockIdx.z == 1) {          // uniform: the second problem of a paired launch
+      A = second.A; B = second.B;
+      M = second.M; N = second.N; nbn = second.nbn;
+      splitk_part = second.part;
+      epi.C = second.C; epi.ldc = second.ldc; epi.scale = second.scale; epi.dev_scale = second.dev_scale;
+    }
   // XCD-aware order: XCD c takes the c-th eighth of the (contraction split, tile row, tile column) order
   int pid = blockIdx.x, split = blockIdx.y;
   {
@@ -307,7 +314,7 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_
   const int bm = pid / nbn, bn = pid % nbn;
   int m0 = bm * BM;
   const int n0 = bn * BN;
-  if (grp.mode == 3 && m0 >= M) return;              // uniform: the two problems of a pair may have different tile counts
+  if (PAIR && grp.mode == 3 && m0 >= M) return;              // uniform: the two problems of a pair may have different tile counts
   int kb = split * kchunk;
   int ke = min(K, kb + kchunk);
   int Mtot = M;
@@ -337,7 +344,7 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_
       Mtot = grp.n_groups * M;
     }
     epi.C = (char*)epi.C + (size_t)z * grp.c_stride * (epi.out_kind == PQ_OUT_BF16 ? 2 : 4);
-    if (epi.m_split > 0) epi.C2 = (char*)epi.C2 + (size_t)z * grp.c_stride * 4;
+    if (AK == PQ_SRC_KS16 && epi.m_split > 0) epi.C2 = (char*)epi.C2 + (size_t)z * grp.c_stride * 4;
   }
   const int klen = max(ke - kb, 0);
   const int nkt = (klen + EPB - 1) / EPB;
@@ -477,7 +484,7 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_
             *reinterpret_cast<uint4*>(slab + (size_t)m * N + n) = r0;
             *reinterpret_cast<uint4*>(slab + (size_t)m * N + n + 4) = r1;
           } else {
-            epi_vec8<INT8 && !PH2>(epi, st, m, n, r0, r1, rs);
+            epi_vec8<INT8 && !PH2, AK == PQ_SRC_KS16>(epi, st, m, n, r0, r1, rs);
           }
         }
       }
@@ -561,7 +568,8 @@ __device__ __forceinline__ void rd64_pair(const rd64<AK>& fa, const rd64<BK>& fb
 // NG: groups of two stages in the ring (NG - 1 of them in flight ahead of the MFMAs)
 template <int NG, bool INT8, int AK, int BK, int BK2>
 __global__ __launch_bounds__(256) void tile64_gemm_kernel(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn,
-                                                          int total_tiles, int kchunk, float* splitk_part, pq_gemm_group grp, pq_phase2 ph2) {
+                                                          int total_tiles, int kchunk, float* splitk_part, pq_gemm_group grp, pq_phase2 ph2,
+                                                        pq_second_arg<pair_kinds<AK, BK, BK2>()> second) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int EPB = INT8 ? 128 : 64;
   using SA = tile_src<AK, 64>;
@@ -579,12 +587,14 @@ __global__ __launch_bounds__(256) void tile64_gemm_kernel(int M, int N, int K, p
   using acc_t = typename std::conditional<INT8, i32x16_t, f32x16_t>::type;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
   __shared__ double red[4];
-  if (grp.mode == 3 && blockIdx.z == 1) {            // uniform: the second problem of a paired launch
-    A = grp.second.A; B = grp.second.B;
-    M = grp.second.M; N = grp.second.N; nbn = grp.second.nbn;
-    splitk_part = grp.second.part;
-    epi.C = grp.second.C; epi.ldc = grp.second.ldc; epi.scale = grp.second.scale; epi.dev_scale = grp.second.dev_scale;
-  }
+  constexpr bool PAIR = pair_kinds<AK, BK, BK2>();
+  if constexpr (PAIR)
+    if (grp.mode == 3 && blockIdx.z == 1) {          // uniform: the second problem of a paired launch
+      A = second.A; B = second.B;
+      M = second.M; N = second.N; nbn = second.nbn;
+      splitk_part = second.part;
+      epi.C = second.C; epi.ldc = second.ldc; epi.scale = second.scale; epi.dev_scale = second.dev_scale;
+    }
   // XCD-aware order: XCD c takes the c-th eighth of the (contraction split, tile row, tile column) order
   int pid = blockIdx.x, split = blockIdx.y;
   {
@@ -599,7 +609,7 @@ __global__ __launch_bounds__(256) void tile64_gemm_kernel(int M, int N, int K, p
   const int bm = pid / nbn, bn = pid % nbn;
   int m0 = bm * 64;
   const int n0 = bn * 64;
-  if (grp.mode == 3 && m0 >= M) return;              // uniform: the two problems of a pair may have different tile counts
+  if (PAIR && grp.mode == 3 && m0 >= M) return;              // uniform: the two problems of a pair may have different tile counts
   int kb = split * kchunk;
   int ke = min(K, kb + kchunk);
   int Mtot = M;
@@ -629,7 +639,7 @@ __global__ __launch_bounds__(256) void tile64_gemm_kernel(int M, int N, int K, p
       Mtot = grp.n_groups * M;
     }
     epi.C = (char*)epi.C + (size_t)z * grp.c_stride * (epi.out_kind == PQ_OUT_BF16 ? 2 : 4);
-    if (epi.m_split > 0) epi.C2 = (char*)epi.C2 + (size_t)z * grp.c_stride * 4;
+    if (AK == PQ_SRC_KS16 && epi.m_split > 0) epi.C2 = (char*)epi.C2 + (size_t)z * grp.c_stride * 4;
   }
   const int klen = max(ke - kb, 0);
   const int ngr = (klen + 2 * EPB - 1) / (2 * EPB);  // groups; a stage past the end is fetched as zeros
@@ -797,7 +807,7 @@ __global__ __launch_bounds__(256) void tile64_gemm_kernel(int M, int N, int K, p
         *reinterpret_cast<uint4*>(slab + (size_t)m * N + n) = r0;
         *reinterpret_cast<uint4*>(slab + (size_t)m * N + n + 4) = r1;
       } else {
-        epi_vec8<INT8 && !PH2>(epi, st, m, n, r0, r1);
+        epi_vec8<INT8 && !PH2, AK == PQ_SRC_KS16>(epi, st, m, n, r0, r1);
       }
     }
   }
@@ -813,23 +823,25 @@ __global__ __launch_bounds__(256) void tile64_gemm_kernel(int M, int N, int K, p
 #endif
 template <int BM, int NST, bool INT8, int AK, int BK, int BK2>
 int launch_tile(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi, hipStream_t s,
-                float* part, const pq_gemm_group& grp, const pq_phase2& ph2) {
+                float* part, const pq_gemm_group& grp, const pq_phase2& ph2, const pq_gemm_second* second) {
+  constexpr bool PAIR = pair_kinds<AK, BK, BK2>();
+  if (grp.mode == 3 && (!PAIR || !second)) return pq_set_error(PQ_ERR_BAD_ARG, "no paired kernel for operand kinds (%d, %d)", AK, BK);
   // grouped rows: every group may end in a partial tile, so at most ceil(rows / BM) + n_groups row tiles exist
   const int nbm = grp.mode == 1 ? (grp.max_rows + BM - 1) / BM + grp.n_groups : (M + BM - 1) / BM;
   const int nbn = (N + BM - 1) / BM;
   int tiles = nbm * nbn;
   if (grp.mode == 3) {
-    const int t2 = (grp.second.M + BM - 1) / BM * ((grp.second.N + BM - 1) / BM);
+    const int t2 = (second->M + BM - 1) / BM * ((second->N + BM - 1) / BM);
     if (t2 > tiles) tiles = t2;
   }
   dim3 grid(tiles, pl.splits, grp.mode == 2 ? grp.n_groups : grp.mode == 3 ? 2 : 1);
   float* p = pl.splits > 1 ? part : nullptr;
   if constexpr (BM == 64) {
     // up to one workgroup per CU: the deep ring; otherwise the one that lets two or more share a CU
-    if ((long)grid.x * grid.y * grid.z <= 256) tile64_gemm_kernel<PQ_NG_DEEP, INT8, AK, BK, BK2><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, tiles, pl.kchunk, p, grp, ph2);
-    else tile64_gemm_kernel<NST, INT8, AK, BK, BK2><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, tiles, pl.kchunk, p, grp, ph2);
+    if ((long)grid.x * grid.y * grid.z <= 256) tile64_gemm_kernel<PQ_NG_DEEP, INT8, AK, BK, BK2><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, tiles, pl.kchunk, p, grp, ph2, second_arg<PAIR>(second));
+    else tile64_gemm_kernel<NST, INT8, AK, BK, BK2><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, tiles, pl.kchunk, p, grp, ph2, second_arg<PAIR>(second));
   } else {
-    tile_gemm_kernel<BM, BM, NST, INT8, AK, BK, BK2><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, tiles, pl.kchunk, p, grp, ph2);
+    tile_gemm_kernel<BM, BM, NST, INT8, AK, BK, BK2><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, tiles, pl.kchunk, p, grp, ph2, second_arg<PAIR>(second));
   }
   PQ_CHECK_LAUNCH("tile_gemm_kernel");
   return PQ_OK;
@@ -843,18 +855,18 @@ int launch_tile(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A
 #endif
 template <bool INT8, int AK, int BK, int BK2 = -1>
 int launch_kinds(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi, hipStream_t s,
-                 float* part, const pq_gemm_group& grp, const pq_phase2& ph2) {
+                 float* part, const pq_gemm_group& grp, const pq_phase2& ph2, const pq_gemm_second* second) {
   constexpr bool bits = BK == PQ_SRC_BITS8 || BK == PQ_SRC_BITS16;
-  if (pl.bm == 64) return launch_tile<64, PQ_NG, INT8, AK, BK, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
-  return launch_tile<128, bits ? PQ_NST128B : PQ_NST128, INT8, AK, BK, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+  if (pl.bm == 64) return launch_tile<64, PQ_NG, INT8, AK, BK, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2, second);
+  return launch_tile<128, bits ? PQ_NST128B : PQ_NST128, INT8, AK, BK, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2, second);
 }
 
 }  // namespace
 
 int pq_launch_tile(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi, hipStream_t s,
-                   float* part, const pq_gemm_group& grp, const pq_phase2& ph2) {
+                   float* part, const pq_gemm_group& grp, const pq_phase2& ph2, const pq_gemm_second* second) {
   const int ak = A.kind, bk = B.kind;
-#define PQ_TILE_KINDS(...) return launch_kinds<__VA_ARGS__>(pl, M, N, K, A, B, epi, s, part, grp, ph2)
+#define PQ_TILE_KINDS(...) return launch_kinds<__VA_ARGS__>(pl, M, N, K, A, B, epi, s, part, grp, ph2, second)
   if (ph2.K2 > 0) {
     if (ak == PQ_SRC_KC8 && bk == PQ_SRC_BITS8 && ph2.A2.kind == PQ_SRC_KC16 && ph2.B2.kind == PQ_SRC_KC16)
       PQ_TILE_KINDS(true, PQ_SRC_KC8, PQ_SRC_BITS8, PQ_SRC_KC16);

@@ -3,8 +3,8 @@
 `trace(calls)` runs the calls in a child process in which the HIP runtime's symbols are those of host_launches.c (a launch
 records the kernel's name and grid and does nothing).  Buffers are addresses that nobody reads; workspace and ctx sizes are
 exactly what the library's own queries say.  A call is a dict: `op` (linear, linear_norm, prefill, ffn, hp_int8) and the
-fields of its descriptor.  The result is one dict per call: `rc`, `error`, and `launches`, a list of [kernel, template
-arguments, grid]."""
+fields of its descriptor.  The result is one dict per call: `rc`, `error`, `launches`, a list of [kernel, template
+arguments, grid], and `symbols`, the launches' mangled kernel names."""
 import ctypes as C
 import json
 import os
@@ -110,8 +110,9 @@ def _child(shim_path, lib_path):
     for c in json.load(sys.stdin):
         shim.trace_reset()
         rc = run(c)
-        out.append(dict(rc=rc, error=lib.pq_last_error_string().decode() if rc else "",
-                        launches=[[*_demangle(shim.trace_name(i).decode()), [shim.trace_grid(i, a) for a in range(3)]] for i in range(shim.trace_count())]))
+        symbols = [shim.trace_name(i).decode() for i in range(shim.trace_count())]
+        out.append(dict(rc=rc, error=lib.pq_last_error_string().decode() if rc else "", symbols=symbols,
+                        launches=[[*_demangle(s), [shim.trace_grid(i, a) for a in range(3)]] for i, s in enumerate(symbols)]))
     json.dump(out, sys.stdout)
 
 
