@@ -1687,10 +1687,14 @@ static int decode_set_gemm16_limits() {
 static int launch_gemm16_tiled(const gemm16_params& p, int sets, int toks, size_t hm, bool i8, hipStream_t s) {
   const int G = (p.N + 63) / 64;
   size_t lds = g16_tiled_code_bytes(toks, p.K) + (hm > 8192 ? hm : 8192);
-  // Sharing a group out pays while all groups are resident at once (four workgroups on each of 256 CUs): over 40 calls of 2 to
-  // 16 tokens, 1.14 to 1.35 x up to 700 groups, 1.0 to 1.2 x up to 1024, 0.76 to 1.16 x above (5 tokens, 3 FFNs of 1920/7296: 52 ->
-  // 39 us; 4 tokens through 52 layers of 2304 -> 3804, 3120 groups: 63 -> 84 us).
-  const bool share = (long)G * sets <= 1024;
+  // Sharing a group out pays while all groups are resident at once: by registers four workgroups on each of 256 CUs, fewer when
+  // their LDS (codes and the experts' hidden states, which every group then stages for itself) leaves room for fewer.  4096 -> 4096,
+  // two of E experts of rank 64, against a wavefront per group: 1.12 to 1.45 x below the line and 1.02 to 1.18 x on it, beyond it 0.96
+  // (8 tokens, E = 16, 1024 groups of 48 KB), 0.94 (16 tokens, E = 16, 768 groups of 64 KB), 0.70 (16 tokens, E = 32, 1024 groups of 96 KB:
+  // 115 -> 164 us); without experts 0.76 at 3120 groups.
+  constexpr size_t CU_LDS = 160 * 1024;
+  const size_t fit = CU_LDS / (lds < 16384 + 2048 ? 16384 + 2048 : lds);
+  const bool share = (size_t)G * sets <= 256 * (fit < 4 ? fit : 4);
   if (share && lds < 16384 + 2048) lds = 16384 + 2048;
   const dim3 grid(share ? G : (G + 3) / 4, sets);
 #define PQ_G16(I8V)                                                                                                                  \

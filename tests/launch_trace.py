@@ -2,7 +2,7 @@
 
 `trace(calls)` runs the calls in a child process in which the HIP runtime's symbols are those of host_launches.c (a launch
 records the kernel's name and grid and does nothing).  Buffers are addresses that nobody reads; workspace and ctx sizes are
-exactly what the library's own queries say.  A call is a dict: `op` (linear, linear_norm, prefill, ffn, hp_int8) and the
+exactly what the library's own queries say.  A call is a dict: `op` (linear, linear_norm, prefill, ffn, hp_int8, decode) and the
 fields of its descriptor.  The result is one dict per call: `rc`, `error`, `launches`, a list of [kernel, template
 arguments, grid], and `symbols`, the launches' mangled kernel names."""
 import ctypes as C
@@ -74,6 +74,10 @@ def _child(shim_path, lib_path):
         _fields_ = [(n, C.c_float if n in ("alpha", "beta") else C.c_int32) for n in (
             "tokens", "d_model", "d_ffn", "hp_rank", "n_experts", "top_k", "io_dtype", "alpha", "beta", "hp_kind")]
 
+    class Decode(C.Structure):
+        _fields_ = [(n, C.c_float if n == "alpha" else C.c_int32) for n in (
+            "batch", "d_in", "d_out", "hp_rank", "n_experts", "top_k", "n_layers", "packed_layout", "alpha")]
+
     def buf(i):                                       # distinct aligned addresses, far apart
         return C.c_void_p((i + 1) << 44)
 
@@ -91,6 +95,14 @@ def _child(shim_path, lib_path):
             nc, nw = query("pq_ffn_ctx_bytes", p), query("pq_ffn_workspace_bytes", p)
             return (lib.pq_ffn_fwd(p, *map(buf, range(9)), buf(9), size(nc), buf(10), size(nw), None)
                     or lib.pq_ffn_bwd(p, buf(11), buf(0), buf(4), buf(5), buf(6), buf(7), buf(9), size(nc), *map(buf, range(12, 21)), buf(10), size(nw), None))
+        if op == "decode":
+            i8 = c.pop("int8", False)
+            d = Decode(**{**dict(n_layers=1, packed_layout=1, alpha=2.0), **c})
+            p = C.byref(d)
+            nw = query("pq_decode_workspace_bytes", p)
+            if i8:
+                return lib.pq_decode_gemv_int8(p, *map(buf, range(9)), None, buf(9), size(nw), None)
+            return lib.pq_decode_gemv(p, *map(buf, range(7)), None, buf(9), size(nw), None)
         d = Linear(**{**dict(hp_rank=0, n_experts=1, top_k=1, io_dtype=1, w_kind=1 if op == "prefill" else 0, alpha=2.0, beta=0.2), **c})
         p = C.byref(d)
         kind = "pq_linear_norm" if op == "linear_norm" else "pq_linear"

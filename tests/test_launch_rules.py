@@ -1,0 +1,27 @@
+"""Which kernel a call takes, where the choice depends on more than its sizes: host side only (launch_trace.py)."""
+import os
+
+import pytest
+
+from launch_trace import kernels, trace
+from paper_2602_22592_amd import binding as pq
+
+
+@pytest.fixture(scope="module", autouse=True)
+def built():
+    if not os.path.exists(pq.LIB_PATH):
+        from paper_2602_22592_amd.build import build
+        build(verbose=False)
+
+
+@pytest.mark.parametrize("int8", [False, True])
+@pytest.mark.parametrize("batch,experts,layers,shared", [(8, 8, 16, True), (8, 16, 12, True), (8, 16, 16, False), (8, 32, 8, True), (8, 32, 12, False),
+                                                         (16, 8, 12, True), (16, 8, 16, False), (16, 16, 8, True), (16, 16, 12, False),
+                                                         (16, 32, 4, True), (16, 32, 6, False), (4, 4, 17, False)])
+def test_small_batch_decode_shares_a_group_while_all_are_resident(batch, experts, layers, shared, int8):
+    """4096 -> 4096: 64 groups a layer; a workgroup's LDS is 32 KB of codes and the hidden states of all experts."""
+    r = trace([dict(op="decode", batch=batch, d_in=4096, d_out=4096, hp_rank=64, n_experts=experts, top_k=2, n_layers=layers, int8=int8)])[0]
+    assert r["rc"] == 0, r["error"]
+    (toks, i8, share), grid = kernels(r, "decode_gemm16_tiled_kernel")[0]
+    assert (toks, i8, share) == (8 if batch <= 8 else 16, int(int8), int(shared))
+    assert grid == [64 if shared else 16, layers, 1]
