@@ -1860,6 +1860,7 @@ static pq_gemm_plan plan_search(int M, int N, int K, bool int8, bool may_split) 
   const long tiles = (long)((M + pl.bm - 1) / pl.bm) * ((N + pl.bn - 1) / pl.bn);
   pl.red_blocks = pl.splits > 1 ? (int)(((size_t)M * (N / 8) + 255) / 256) : (int)tiles;
   pl.ws_bytes = pl.splits > 1 ? (size_t)pl.splits * M * N * sizeof(float) : 0;
+  pl.us = best;
   return pl;
 }
 // The search is a pure function of its arguments and takes up to a microsecond; a call asks for a dozen plans (sizes of its
@@ -1885,7 +1886,12 @@ static int check_scratch(size_t need, const pq_scratch& sk) {
 
 // Two narrow products over the same contraction in one launch (dB and dA of the rank-r branch).  tn: rank 128 over many
 // tokens, the streaming pair kernel (problem 1 runs transposed): four token ranges when that already gives a workgroup per
-// CU (fewer slabs to write and add), up to sixteen for small matrices, never shorter than 256 tokens.  Otherwise 64x64 tiles.
+// CU (fewer slabs to write and add), up to sixteen for small matrices, never shorter than 256 tokens.  Otherwise 64x64 tiles,
+// while they are not slower than a launch for each product with the tile it would choose: their time as above, but no less than
+// it takes to fetch the tiles' operands (16 KB a step and tile, 13 TB/s out of the caches, 6.5 TB/s from 64 MB of operands on),
+// against the two plans' times and 6 us for the second launch.  Over 286 shapes (300 to 16384 tokens, rank 16 to 1024) the choice
+// costs 0.3 % of the whole step on average; 64x64 tiles always cost up to 26 % (16384 tokens 4096 -> 1024, r = 512: 709 -> 846 us,
+// this rule 690).
 pq_pair_plan pq_plan_pair(int K, int M0, int N0, int M1, int N1) {
   pq_pair_plan p;
   memset(&p, 0, sizeof(p));
@@ -1904,6 +1910,15 @@ pq_pair_plan pq_plan_pair(int K, int M0, int N0, int M1, int N1) {
       const int n = want == 1 ? 1 : (K + chunk - 1) / chunk;
       const double t = est_tile(64, tiles * n, (chunk + 63) / 64, false) + est_reduce(n, elems);
       if (t < best) { best = t; p.splits = n; p.kchunk = chunk; }
+    }
+    const pq_gemm_plan p0 = pq_plan_gemm(M0, N0, K), p1 = pq_plan_gemm(M1, N1, K);
+    const double staged = (double)tiles * ((K + 63) / 64) * 16384.0, operands = 2.0 * K * ((double)M0 + N0 + M1 + N1);
+    const double fetch = 5.0 + staged / (operands > 64.0e6 ? 6.5e6 : 13.0e6) + est_reduce(p.splits, elems);
+    if (p0.us + p1.us + 6.0 < (fetch > best ? fetch : best)) {
+      p.apart = true;
+      p.ws0 = p0.ws_bytes;
+      p.ws1 = p1.ws_bytes;
+      return p;
     }
   }
   p.ws0 = p.splits > 1 ? (size_t)p.splits * M0 * N0 * sizeof(float) : 0;
@@ -1929,7 +1944,7 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
   const bool one = M0 > 0 && N0 > 0 && M1 > 0 && N1 > 0 && K > 0 && al(A0) && al(B0) && al(A1) && al(B1) && A0.ld >= M0 && B0.ld >= N0 &&
                    A1.ld >= M1 && B1.ld >= N1 &&
                    (pp.splits == 1 || (sk0.p && sk1.p && ((uintptr_t)sk0.p % 16) == 0 && ((uintptr_t)sk1.p % 16) == 0));
-  if (!one) {
+  if (!one || pp.apart) {
     if (int rc = pq_launch_gemm(M0, N0, K, A0, B0, e0, s, prof_label0, sk0)) return rc;
     return pq_launch_gemm(M1, N1, K, A1, B1, e1, s, prof_label1, sk1);
   }

@@ -182,11 +182,13 @@ struct pq_gemm_plan {
   int kchunk;        // contraction elements per split
   int red_blocks;    // number of per-block partial sums written when a reduction is requested
   size_t ws_bytes;   // scratch for the split slabs
+  double us;         // the time that the choice expects
 };
 pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8 = false, bool split_int8 = false);
 // whether a second contraction (pq_phase2) can be fused into a GEMM of this plan
 inline bool pq_plan_fuses(const pq_gemm_plan& pl) { return pl.splits == 1 || pl.bm < 256; }
-struct pq_pair_plan { bool tn; int splits, kchunk; size_t ws0, ws1; };   // scratch of pq_launch_gemm_pair_ks16's two problems
+// tn: the streaming pair kernel; apart: a launch each; otherwise 64x64 tiles.  ws0, ws1: scratch of the two problems.
+struct pq_pair_plan { bool tn, apart; int splits, kchunk; size_t ws0, ws1; };
 pq_pair_plan pq_plan_pair(int K, int M0, int N0, int M1, int N1);
 // Scratch a grouped launch over contraction ranges (mode 2; M x N per group, total_k indices over all groups) may use
 size_t pq_mode2_ws_bytes(int M, int N, int n_groups, int total_k);

@@ -25,3 +25,14 @@ def test_small_batch_decode_shares_a_group_while_all_are_resident(batch, experts
     (toks, i8, share), grid = kernels(r, "decode_gemm16_tiled_kernel")[0]
     assert (toks, i8, share) == (8 if batch <= 8 else 16, int(int8), int(shared))
     assert grid == [64 if shared else 16, layers, 1]
+
+
+@pytest.mark.parametrize("T,K,N,r,hp_kind,paired", [(300, 1024, 4096, 160, 0, True), (2048, 2048, 2048, 64, 0, True), (7680, 256, 4608, 64, 0, True),
+                                                    (2048, 2048, 2048, 256, 1, True), (16384, 1024, 4096, 160, 0, False),
+                                                    (16384, 4096, 1024, 512, 0, False), (7680, 256, 4608, 672, 1, False)])
+def test_factor_gradients_share_a_launch_only_where_small_tiles_serve_both(T, K, N, r, hp_kind, paired):
+    """dB and dA on 64x64 tiles in one launch, or each with the tile of its own plan."""
+    res = trace([dict(op="linear", tokens=T, d_in=K, d_out=N, hp_rank=r, hp_kind=hp_kind)])[0]
+    assert res["rc"] == 0, res["error"]
+    pairs = [grid for args, grid in kernels(res, "tile64_gemm_kernel") if args[2:4] == [1, 1] and grid[2] == 2]
+    assert len(pairs) == (1 if paired else 0), res["launches"]
