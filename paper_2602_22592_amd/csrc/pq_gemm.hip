@@ -1887,11 +1887,10 @@ static int check_scratch(size_t need, const pq_scratch& sk) {
 // Two narrow products over the same contraction in one launch (dB and dA of the rank-r branch).  tn: rank 128 over many
 // tokens, the streaming pair kernel (problem 1 runs transposed): four token ranges when that already gives a workgroup per
 // CU (fewer slabs to write and add), up to sixteen for small matrices, never shorter than 256 tokens.  Otherwise 64x64 tiles,
-// while they are not slower than a launch for each product with the tile it would choose: their time as above, but no less than
-// it takes to fetch the tiles' operands (16 KB a step and tile, 13 TB/s out of the caches, 6.5 TB/s from 64 MB of operands on),
-// against the two plans' times and 6 us for the second launch.  Over 286 shapes (300 to 16384 tokens, rank 16 to 1024) the choice
-// costs 0.3 % of the whole step on average; 64x64 tiles always cost up to 26 % (16384 tokens 4096 -> 1024, r = 512: 709 -> 846 us,
-// this rule 690).
+// while they are not slower than a launch for each product with the tile it would choose: times as above, but no less than it
+// takes to fetch the tiles' operands (20 TB/s out of the caches, 6.5 TB/s from 64 MB of operands on).  Over 286 shapes (300 to
+// 16384 tokens, rank 16 to 1024) the choice costs 0.2 % of the whole step on average; 64x64 tiles always cost up to 26 % (16384
+// tokens 4096 -> 1024, r = 512: 709 -> 846 us; this rule 690).
 pq_pair_plan pq_plan_pair(int K, int M0, int N0, int M1, int N1) {
   pq_pair_plan p;
   memset(&p, 0, sizeof(p));
@@ -1912,9 +1911,15 @@ pq_pair_plan pq_plan_pair(int K, int M0, int N0, int M1, int N1) {
       if (t < best) { best = t; p.splits = n; p.kchunk = chunk; }
     }
     const pq_gemm_plan p0 = pq_plan_gemm(M0, N0, K), p1 = pq_plan_gemm(M1, N1, K);
-    const double staged = (double)tiles * ((K + 63) / 64) * 16384.0, operands = 2.0 * K * ((double)M0 + N0 + M1 + N1);
-    const double fetch = 5.0 + staged / (operands > 64.0e6 ? 6.5e6 : 13.0e6) + est_reduce(p.splits, elems);
-    if (p0.us + p1.us + 6.0 < (fetch > best ? fetch : best)) {
+    const double rate = 2.0 * K * ((double)M0 + N0 + M1 + N1) > 64.0e6 ? 6.5e6 : 20.0e6;
+    auto bound = [&](double us, long n, int bm, double reduce) {
+      const double fetch = 5.0 + (double)n * ((K + 63) / 64) * bm * 256.0 / rate + reduce;
+      return fetch > us ? fetch : us;
+    };
+    auto alone = [&](const pq_gemm_plan& q, int M, int N) {
+      return bound(q.us, (long)((M + q.bm - 1) / q.bm) * ((N + q.bn - 1) / q.bn), q.bm, est_reduce(q.splits, (double)M * N));
+    };
+    if (alone(p0, M0, N0) + alone(p1, M1, N1) < bound(best, tiles, 64, est_reduce(p.splits, elems))) {
       p.apart = true;
       p.ws0 = p0.ws_bytes;
       p.ws1 = p1.ws_bytes;
