@@ -173,7 +173,10 @@ __device__ __forceinline__ void prep_quantise_own(float amax, size_t tok, int K,
   if (tid == 0) atomicAdd(&rowsum[tok], sh.isum[0] + sh.isum[1] + sh.isum[2] + sh.isum[3]);
 }
 
-// The first eight router rows' vectors of this thread; they depend on nothing, so a caller requests them ahead of the token.
+// The first eight router rows' vectors of this thread; they depend on nothing, so a caller requests them ahead of the token,
+// while all workgroups of the launch are resident at once: the registers they wait in leave room for four on a CU instead of five
+// (16 tokens through 35 layers, 1120 workgroups: 24.8 us with, 21.6 without; one token, one layer: see decode_prep_h_kernel).
+static inline bool prep_early(long workgroups) { return workgroups <= 1024; }
 __device__ __forceinline__ void prep_router_first(const uint16_t* __restrict__ Wr, int layer, int K, int E, uint4* wv) {
   const int c = min((int)threadIdx.x, K / 8 - 1);
 #pragma unroll
@@ -181,21 +184,22 @@ __device__ __forceinline__ void prep_router_first(const uint16_t* __restrict__ W
 }
 
 // Router of one token: fp64 logits rounded once to fp32, top-k on logits (ties to the lower index); eight experts per pass
-// over x, whose vectors the caller has requested for the first pass (prep_router_first).  Leaves the selection in sh.sel
-// (valid after the closing barrier).
+// over x, whose vectors the caller has, with EARLY, requested for the first pass (prep_router_first).  Leaves the selection in
+// sh.sel (valid after the closing barrier).
+template <bool EARLY>
 __device__ __forceinline__ void prep_router(const uint16_t* __restrict__ Wr, int layer, int K, int E, int topk, const float* xs,
                                             prep_shared& sh, const uint4* first) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int e0 = 0; e0 < E; e0 += 8) {
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     uint4 wv[8];
-    if (e0 == 0) {
+    if (EARLY && e0 == 0) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) wv[u] = first[u];
     }
     for (int c = tid; c < K / 8; c += 256) {
       // the eight rows are requested together; experts past the end re-read the last one (their sums are dropped)
-      if (e0 > 0 || c != tid) {
+      if (!EARLY || e0 > 0 || c != tid) {
 #pragma unroll
         for (int u = 0; u < 8; ++u) wv[u] = reinterpret_cast<const uint4*>(Wr + ((size_t)layer * E + min(e0 + u, E - 1)) * K)[c];
       }
@@ -267,6 +271,7 @@ __device__ __forceinline__ void prep_gates(size_t tok, int E, int topk, prep_sha
   }
 }
 
+template <bool EARLY>
 __global__ __launch_bounds__(256) void decode_prep_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wr,
                                                           int B, int K, int E, int topk, int8_t* __restrict__ xq,
                                                           uint32_t* __restrict__ planes, int* __restrict__ rowsum,
@@ -280,14 +285,14 @@ __global__ __launch_bounds__(256) void decode_prep_kernel(const uint16_t* __rest
   const size_t tok = split ? blockIdx.x >> 1 : blockIdx.x;   // layer * B + b
   const int layer = (int)(tok / B);
   uint4 first[8];
-  if (split && (blockIdx.x & 1)) prep_router_first(Wr, layer, K, E, first);
+  if (EARLY && split && (blockIdx.x & 1)) prep_router_first(Wr, layer, K, E, first);
   const float amax = prep_load_x(X, tok, K, xs);
   if (!split || (blockIdx.x & 1) == 0) {
     if (zero_rs && threadIdx.x == 0) zero_rs[tok] = 0;   // a row sum that a later kernel of the call adds up with atomics
     prep_quantise(amax, tok, K, xs, sh, xq, planes, rowsum, gamma);
   } else {
     __syncthreads();                                  // xs complete
-    prep_router(Wr, layer, K, E, topk, xs, sh, first);
+    prep_router<EARLY>(Wr, layer, K, E, topk, xs, sh, first);
     prep_gates(tok, E, topk, sh, idx, gate);
   }
 }
@@ -305,7 +310,7 @@ static inline int prep_h_rows(int L, int hidden) { return (long)L * (1 + (hidden
 // hidden state is the exact integer product of the token's codes with a row, de-quantised as
 // fl32(fl32(1/gamma_x) * acc) / gamma_a and rounded to bf16 (stored as fp32).  The token's codes (natural column
 // order) sit in LDS behind its fp32 activations.
-template <bool I8>
+template <bool I8, bool EARLY>
 __global__ __launch_bounds__(256) void decode_prep_h_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wr,
                                                             const void* __restrict__ hpA_, const float* __restrict__ gA,
                                                             int K, int E, int r, int topk,
@@ -332,7 +337,7 @@ __global__ __launch_bounds__(256) void decode_prep_h_kernel(const uint16_t* __re
   }
   const size_t tok = layer;
   uint4 first[8];
-  if (part > 0) prep_router_first(Wr, layer, K, E, first);
+  if (EARLY && part > 0) prep_router_first(Wr, layer, K, E, first);
   const float amax = prep_load_x(X, tok, K, xs);
   if (part == 0) {
     if (zero_rs && threadIdx.x == 0) zero_rs[tok] = 0;   // see decode_prep_kernel
@@ -347,7 +352,7 @@ __global__ __launch_bounds__(256) void decode_prep_h_kernel(const uint16_t* __re
   }
   __syncthreads();                                    // xs complete
   if constexpr (I8) gx = 128.0f / fmaxf(fmaxf(fmaxf(sh.red[0], sh.red[1]), fmaxf(sh.red[2], sh.red[3])), 1e-5f);
-  prep_router(Wr, layer, K, E, topk, xs, sh, first);
+  prep_router<EARLY>(Wr, layer, K, E, topk, xs, sh, first);
   const int oend = min(part * rows, topk * r);
   if constexpr (I8) {
     uint32_t* xc = reinterpret_cast<uint32_t*>(xs + K);          // K code bytes
@@ -1653,9 +1658,12 @@ static int decode_raise_lds_limits() {
       if (rc == PQ_OK && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim) != hipSuccess)
         rc = pq_set_error(PQ_ERR_HIP, "hipFuncSetAttribute failed for a decode kernel");
     };
-    set((const void*)decode_prep_kernel);
-    set((const void*)decode_prep_h_kernel<false>);
-    set((const void*)decode_prep_h_kernel<true>);
+    set((const void*)decode_prep_kernel<false>);
+    set((const void*)decode_prep_kernel<true>);
+    set((const void*)decode_prep_h_kernel<false, false>);
+    set((const void*)decode_prep_h_kernel<false, true>);
+    set((const void*)decode_prep_h_kernel<true, false>);
+    set((const void*)decode_prep_h_kernel<true, true>);
     set((const void*)decode_ffn_mid_kernel);
   });
   return rc;
@@ -1737,8 +1745,8 @@ static int launch_decode_ffn_batch(int L, int B, int D, int F, int r, int E, int
   const int toks = B <= 8 ? 8 : 16;
   {
     pq_prof_scope prof(PQP_DECODE_PREP, s);
-    decode_prep_kernel<<<L * B * 2, 256, (size_t)D * sizeof(float), s>>>((const uint16_t*)X, (const uint16_t*)Wr, B, D, E, topk, xq1, pl1, rs1,
-                                                                        gm1, idx, gate, rs2);
+    const auto prep = prep_early((long)L * B * 2) ? decode_prep_kernel<true> : decode_prep_kernel<false>;
+    prep<<<L * B * 2, 256, (size_t)D * sizeof(float), s>>>((const uint16_t*)X, (const uint16_t*)Wr, B, D, E, topk, xq1, pl1, rs1, gm1, idx, gate, rs2);
     PQ_CHECK_LAUNCH("decode_prep_kernel");
   }
   {  // hidden pairs [Up_e x ; Gate_e x] of every (token, selected expert)
@@ -1792,8 +1800,9 @@ int pq_launch_decode_ffn(int L, int B, int D, int F, int r, int E, int topk, flo
   {  // quantiser of x, router, expert hidden pairs [Up_e x ; Gate_e x]
     pq_prof_scope prof(PQP_DECODE_PREP, s);
     const int rows = prep_h_rows(L, topk * 2 * r), parts = 1 + (topk * 2 * r + rows - 1) / rows;
-    decode_prep_h_kernel<false><<<L * parts, 256, (size_t)D * sizeof(float), s>>>((const uint16_t*)X, (const uint16_t*)Wr, UpGate, nullptr, D, E,
-                                                                                 2 * r, topk, parts, rows, xq1, pl1, rs1, gm1, idx, gate, hug, rs2);
+    const auto prep = prep_early((long)L * parts) ? decode_prep_h_kernel<false, true> : decode_prep_h_kernel<false, false>;
+    prep<<<L * parts, 256, (size_t)D * sizeof(float), s>>>((const uint16_t*)X, (const uint16_t*)Wr, UpGate, nullptr, D, E, 2 * r, topk, parts, rows,
+                                                           xq1, pl1, rs1, gm1, idx, gate, hug, rs2);
     PQ_CHECK_LAUNCH("decode_prep_h_kernel");
   }
   {  // U and G: 2 L weight sets, each pair reading its layer's token once quantised
@@ -1856,19 +1865,19 @@ int pq_launch_decode(const pq_decode_desc& d, const void* X, const uint32_t* pac
   if (B == 1 && r > 0) {
     pq_prof_scope prof(PQP_DECODE_PREP, s);
     const int rows = prep_h_rows(L, d.top_k * r), parts = 1 + (d.top_k * r + rows - 1) / rows;
-    if (i8)
-      decode_prep_h_kernel<true><<<L * parts, 256, (size_t)K * 5, s>>>((const uint16_t*)X, (const uint16_t*)Wr, hpA, gA, K, E, r, d.top_k,
-                                                                      parts, rows, xq, planes, rowsum, gamma, idx, gate, h, nullptr);
-    else
-      decode_prep_h_kernel<false><<<L * parts, 256, (size_t)K * sizeof(float), s>>>((const uint16_t*)X, (const uint16_t*)Wr, hpA, nullptr,
-                                                                                   K, E, r, d.top_k, parts, rows, xq, planes, rowsum, gamma,
-                                                                                   idx, gate, h, nullptr);
+    const bool early = prep_early((long)L * parts);
+    const auto prep = i8 ? (early ? decode_prep_h_kernel<true, true> : decode_prep_h_kernel<true, false>)
+                         : (early ? decode_prep_h_kernel<false, true> : decode_prep_h_kernel<false, false>);
+    prep<<<L * parts, 256, (size_t)K * (i8 ? 5 : sizeof(float)), s>>>((const uint16_t*)X, (const uint16_t*)Wr, hpA, i8 ? gA : nullptr, K, E, r, d.top_k, parts,
+                                                                      rows, xq, planes, rowsum, gamma, idx, gate, h, nullptr);
     PQ_CHECK_LAUNCH("decode_prep_h_kernel");
   } else {
     {
       pq_prof_scope prof(PQP_DECODE_PREP, s);
-      decode_prep_kernel<<<L * B * (E > 0 ? 2 : 1), 256, (size_t)K * sizeof(float), s>>>((const uint16_t*)X, (const uint16_t*)Wr, B, K, E, d.top_k, xq,
-                                                                      planes, rowsum, gamma, idx, gate, nullptr);
+      const int groups = L * B * (E > 0 ? 2 : 1);
+      const auto prep = E > 0 && prep_early(groups) ? decode_prep_kernel<true> : decode_prep_kernel<false>;
+      prep<<<groups, 256, (size_t)K * sizeof(float), s>>>((const uint16_t*)X, (const uint16_t*)Wr, B, K, E, d.top_k, xq, planes, rowsum, gamma, idx, gate,
+                                                          nullptr);
       PQ_CHECK_LAUNCH("decode_prep_kernel");
     }
     if (r > 0) {

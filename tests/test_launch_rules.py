@@ -36,3 +36,13 @@ def test_factor_gradients_share_a_launch_only_where_small_tiles_serve_both(T, K,
     assert res["rc"] == 0, res["error"]
     pairs = [grid for args, grid in kernels(res, "tile64_gemm_kernel") if args[2:4] == [1, 1] and grid[2] == 2]
     assert len(pairs) == (1 if paired else 0), res["launches"]
+
+
+@pytest.mark.parametrize("batch,layers,kernel,early", [(16, 32, "decode_prep_kernel", True), (16, 33, "decode_prep_kernel", False),
+                                                       (1, 60, "decode_prep_h_kernel", True), (1, 64, "decode_prep_h_kernel", False)])
+def test_router_rows_are_requested_early_while_all_workgroups_are_resident(batch, layers, kernel, early):
+    """Two workgroups a token; one token: one and, at 8 x 32 hidden rows, sixteen more a layer."""
+    r = trace([dict(op="decode", batch=batch, d_in=4096, d_out=2048, hp_rank=32, n_experts=8, top_k=8 if batch == 1 else 2, n_layers=layers)])[0]
+    assert r["rc"] == 0, r["error"]
+    args, grid = kernels(r, kernel)[0]
+    assert args[-1] == int(early) and (grid[0] <= 1024) == early
