@@ -200,11 +200,10 @@ def test_linear_config1_fp32():
 @pytest.mark.parametrize("T,K,N,r,bf16", [(333, 544, 416, 24, False), (333, 544, 416, 24, True),
                                          (70, 96, 64, 0, True), (70, 96, 64, 0, False),
                                          (1, 64, 32, 8, True), (600, 1056, 1312, 136, True),
-                                         # rank 64 / 128 with ragged token and channel tiles: the streaming loop of the
-                                         # fused GEMMs with a second contraction of one and of two whole steps
+                                         # rank 64 / 128 with ragged token and channel tiles: the fused products on 64x64 tiles
+                                         # with a second contraction of one and of two whole steps (larger tiles: fused_cases.py)
                                          (600, 1152, 1408, 64, True), (300, 640, 384, 128, True),
-                                         # 7 and 5 contraction steps forward: the second contraction's tiles start in the
-                                         # ring's last and second stage
+                                         # 7 and 5 contraction steps forward, two at a time: a last group of one step
                                          (300, 896, 384, 128, True), (280, 640, 896, 64, True),
                                          # many tokens at rank 128: the streaming rank-r kernel computes H (ragged last block)
                                          (1100, 640, 384, 128, True), (1024, 64, 256, 128, True),

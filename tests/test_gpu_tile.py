@@ -1,7 +1,8 @@
 """The 64x64, 128x128 and 256x256 streaming tiles at the edges they have: rows, columns and contractions that end inside a tile, a step
 or a group of two steps, a second contraction longer than its first group, split contractions, expert segments shorter than a
-tile.  Accumulators are exact; bf16 results hold the 2e-2 bar of the other parity tests.  X and dY lie inside buffers of NaN,
-so that anything fetched past the last token shows."""
+tile; and the fused products in each of their forms on 128x128 and 256x256 tiles (fused_cases.py).  Accumulators are exact; bf16
+results hold the 2e-2 bar of the other parity tests.  X and dY lie inside buffers of NaN, so that anything fetched past the last
+token shows."""
 import numpy as np
 import pytest
 import torch
@@ -9,6 +10,7 @@ import torch
 from oracle import pquant_oracle as po
 from paper_2602_22592_amd import binding as pq
 from paper_2602_22592_amd import workloads as wl
+from fused_cases import CASES
 from parity_metrics import relerr
 from test_gpu_ffn import check_ffn
 
@@ -67,8 +69,47 @@ def test_linear_at_tile_edges(T, K, N, r, E, k, tau):
         errs[n] = relerr(host(t), g[n])
     dYd = c["dY"].astype(np.float64)
     errs["dbeta"] = abs(dab[1].item() - g["dbeta"]) / np.sqrt(((dYd * f["Y1_nobeta"]) ** 2).sum())
+    if r:
+        errs["dalpha"] = abs(dab[0].item() - g["dalpha"]) / np.sqrt(((dYd * f["Yhp"]) ** 2).sum())
+    else:
+        assert dab[0].item() == 0.0
     print("  errors: " + ", ".join(f"{k}={v:.1e}" for k, v in errs.items()), flush=True)
     assert max(errs.values()) <= TOL, errs
+
+
+@pytest.mark.parametrize("T,K,N,r,int8", CASES)
+def test_fused_products(T, K, N, r, int8):
+    """Y and dX of sampled tokens (each depends on its token alone): the first and last, both sides of tile edges, others at random."""
+    print(f"fused products T={T} K={K} N={N} r={r} int8={int8}", flush=True)
+    c = wl.linear_case(900 + T, T, K, N, hp_rank=r, bf16=True, outlier_count=2, outlier_scale=10.0)
+    to = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda().to(torch.bfloat16)
+    nan = lambda *s, dt=torch.float32: torch.full(s, float("nan"), dtype=dt, device="cuda")
+    alpha, beta = 2.0, 0.2
+    desc = pq.make_desc(T, K, N, hp_rank=r, alpha=alpha, beta=beta, hp_kind=pq.PQ_HP_LOWRANK_INT8 if int8 else pq.PQ_HP_LOWRANK_BF16)
+    bufs = pq.LinearBuffers(desc)
+    X, dY, W, A, B = padded(c["X"]), padded(c["dY"]), to(c["W"]), to(c["A"]), to(c["B"])
+    Y, dX = nan(T, N, dt=torch.bfloat16), nan(T, K, dt=torch.bfloat16)
+    pq.linear_fwd(desc, X, W, Y, bufs, A=A, B=B)
+    pq.linear_bwd(desc, dY, X, W, bufs, dX, nan(N, K), nan(2), A=A, B=B, dA=nan(r, K), dB=nan(N, r))
+    torch.cuda.synchronize()
+    rng = np.random.default_rng(T)
+    edges = [t for t in (0, 1, 63, 64, 127, 128, 255, 256, 257, T // 256 * 256 - 1, T // 256 * 256, T - 2, T - 1) if 0 <= t < T]
+    tok = np.unique(np.concatenate([edges, rng.choice(T, min(T, 100), replace=False)])).astype(int)
+    x, dy = c["X"][tok], c["dY"][tok]
+    if int8:
+        f = po.linear_fwd(x, c["W"], 0.0, beta)
+        h = po.hp_int8_fwd(None, c["A"], c["B"], bf16=True, q_gamma=(f["q"], f["gamma"]))
+        y = f["Y1"].astype(np.float64) + alpha * h["Yhp"].astype(np.float64)
+        dx = po.linear_bwd(dy, x, c["W"], 0.0, beta, f)["dX"] + po.hp_int8_bwd(alpha * dy.astype(np.float64), h)["dX"]
+    else:
+        f = po.linear_fwd(x, c["W"], alpha, beta, A=c["A"], B=c["B"])
+        y, dx = f["Y"], po.linear_bwd(dy, x, c["W"], alpha, beta, f, A=c["A"], B=c["B"])["dX"]
+    sel = torch.from_numpy(tok).cuda()
+    host = lambda t: t[sel].float().cpu().numpy()
+    errs = {"Y": relerr(host(Y), y), "dX": relerr(host(dX), dx)}
+    print("  errors: " + ", ".join(f"{k}={v:.1e}" for k, v in errs.items()), flush=True)
+    assert max(errs.values()) <= TOL, errs
+    assert torch.isfinite(Y).all() and torch.isfinite(dX).all()
 
 
 @pytest.mark.parametrize("T,D,F,E,r,k", [(1300, 1056, 4116, 1, 64, 1),    # paired 256x256 products, partial steps, store limits

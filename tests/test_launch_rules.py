@@ -3,7 +3,8 @@ import os
 
 import pytest
 
-from launch_trace import kernels, trace
+from fused_cases import CASES
+from launch_trace import MFMA, kernels, trace
 from paper_2602_22592_amd import binding as pq
 
 
@@ -46,3 +47,33 @@ def test_router_rows_are_requested_early_while_all_workgroups_are_resident(batch
     assert r["rc"] == 0, r["error"]
     args, grid = kernels(r, kernel)[0]
     assert args[-1] == int(early) and (grid[0] <= 1024) == early
+
+
+def fused_route(result, forward, contraction, rank):
+    """The form of the 1-bit product with the branch in it (fused_cases.py), from the launches of a linear."""
+    bits = 3 if forward else 4
+    for name, a, grid in result["launches"]:
+        if name == "mfma_gemm_kernel":
+            d = dict(zip(MFMA, a))
+            if d["b"] != bits:
+                continue
+            assert not d["whole_tiles"]
+            steps = "partial" if d["partial_steps"] else "whole"
+            if d["a2"] < 0:
+                return 256, "unfused", steps
+            n = -(-contraction // (128 if forward else 64))          # contraction steps; the ring has four stages
+            return (256, "ring", steps, n % 4) if rank in (64, 128) and n >= 4 else (256, "registers", steps)
+        if name in ("tile_gemm_kernel", "tile64_gemm_kernel") and a[-2] == bits:
+            assert a[-1] >= 0, "not fused"
+            return (128 if name == "tile_gemm_kernel" else 64), grid[1] > 1
+    raise AssertionError(result["launches"])
+
+
+def test_fused_cases_take_the_forms_they_stand_for():
+    calls = [dict(op="linear", tokens=T, d_in=K, d_out=N, hp_rank=r, hp_kind=i8) for T, K, N, r, i8 in CASES]
+    for (case, (fwd, dx)), res in zip(CASES.items(), trace(calls)):
+        T, K, N, r, i8 = case
+        assert res["rc"] == 0, (case, res["error"])
+        if fwd is not None:
+            assert fused_route(res, True, K, r) == fwd, case
+        assert fused_route(res, False, N, r) == dx, case
