@@ -63,7 +63,8 @@ def check_decode(c, top_k=2, alpha=2.0, beta=0.2, tiled=False):
 
 
 @pytest.mark.parametrize("L,B,K,N,E,r,k", [(1, 1, 256, 136, 4, 16, 2), (2, 1, 4096, 1000, 8, 64, 2), (1, 1, 128, 64, 1, 0, 1),
-                                           (3, 1, 640, 328, 8, 8, 1), (1, 1, 8192, 260, 4, 24, 3)])
+                                           (3, 1, 640, 328, 8, 8, 1), (1, 1, 8192, 260, 4, 24, 3),
+                                           (64, 1, 256, 64, 8, 32, 8)])   # 1088 workgroups of preparation: more than are resident at once
 @pytest.mark.parametrize("tiled", [False, True])
 def test_decode_gemv_batch1(L, B, K, N, E, r, k, tiled):
     print(f"decode B=1: L={L} K={K} N={N} E={E} r={r} k={k} tiled={tiled}", flush=True)
@@ -142,7 +143,7 @@ def check_decode_int8(c, top_k=2, alpha=2.0, beta=0.2, tiled=False):
 
 
 @pytest.mark.parametrize("L,K,N,E,r,k", [(1, 256, 136, 4, 32, 2), (2, 4096, 1000, 8, 64, 2), (3, 640, 328, 8, 32, 1),
-                                         (1, 8192, 260, 4, 96, 3), (1, 128, 64, 1, 32, 1)])
+                                         (1, 8192, 260, 4, 96, 3), (1, 128, 64, 1, 32, 1), (64, 256, 64, 8, 32, 8)])
 @pytest.mark.parametrize("tiled", [False, True])
 def test_decode_int8_experts_batch1(L, K, N, E, r, k, tiled):
     print(f"decode INT8 experts: L={L} K={K} N={N} E={E} r={r} k={k} tiled={tiled}", flush=True)
@@ -202,8 +203,8 @@ def test_decode_largest_d_in_small_batch():
 @pytest.mark.parametrize("B,K,N,E,r,k", [(2, 128, 64, 4, 64, 1), (5, 640, 140, 8, 64, 2), (16, 2304, 200, 4, 64, 2), (8, 4480, 72, 2, 64, 1)])
 @pytest.mark.parametrize("int8", [False, True])
 def test_decode_shared_groups_equal_unshared(B, K, N, E, r, k, int8):
-    """Calls of few 64-row groups share a group out over a workgroup's wavefronts; with more than 1024 groups every wavefront has
-    a group of its own.  The same layer as one weight set and as many copies: accumulators and outputs equal bit for bit
+    """Calls of few 64-row groups share a group out over a workgroup's wavefronts; with more groups than fit the chip at once (1024
+    at most) every wavefront has a group of its own.  The same layer as one weight set and as many copies: accumulators and outputs equal bit for bit
     (exact integer sums; the experts' products run in the same order), and the single set agrees with the oracle."""
     print(f"shared groups B={B} K={K} N={N} E={E} r={r} k={k} int8={int8}", flush=True)
     c = wl.decode_case(90 + K + N + B, B, d_in=K, d_out=N, n_experts=E, hp_rank=r, n_layers=1)

@@ -121,3 +121,10 @@ def test_fused_products(T, K, N, r, int8):
 def test_ffn_paired_products(T, D, F, E, r, k):
     print(f"ffn paired products T={T} d={D} F={F} E={E} r={r} k={k}", flush=True)
     check_ffn(wl.ffn_case(300 + T, T, D, F, E, r), top_k=k)
+
+
+@pytest.mark.parametrize("T,D,F,r", [(3904, 672, 36, 976), (7084, 448, 36, 776)])   # whole and partial steps
+def test_ffn_single_branch_of_large_rank(T, D, F, r):
+    """The gradient of [Up; Gate] on split 256x256 tiles, its rows' halves stored to two buffers by the slab sum."""
+    print(f"ffn single branch T={T} d={D} F={F} r={r}", flush=True)
+    check_ffn(wl.ffn_case(500 + T, T, D, F, 1, r), top_k=1)

@@ -77,3 +77,11 @@ def test_fused_cases_take_the_forms_they_stand_for():
         if fwd is not None:
             assert fused_route(res, True, K, r) == fwd, case
         assert fused_route(res, False, N, r) == dx, case
+
+
+@pytest.mark.parametrize("T,D,F,r", [(3904, 672, 36, 976), (7084, 448, 36, 776)])
+def test_single_branch_of_large_rank_takes_split_256_tiles(T, D, F, r):
+    res = trace([dict(op="ffn", tokens=T, d_model=D, d_ffn=F, hp_rank=r)])[0]
+    (args, grid), = [k for k in kernels(res, "gemm_tn_w4_kernel") if k[0][2]]
+    assert args == [int(T % 32 != 0), 0, 1] and grid[1] > 1
+    assert [0, 1] in [a for a, _ in kernels(res, "splitk_reduce_kernel")]
