@@ -89,13 +89,6 @@ __device__ __forceinline__ void wave_sum_transposed(double* v, int lane) {
   }
 }
 
-// ------------------------------------------------------------------------------------------
-// Router: a wavefront takes TB tokens at once (a router row converted to fp64 serves all of them): fp64 dot products
-// against all E router rows, lane l accumulating the 16-byte chunks l, l + 64, ... of a token row in order, then the
-// wave sums, which leave one (token, expert) pair per lane; that lane rounds the logit to fp32 and evaluates its term
-// of the softmax in fp64; the first lane of a token's group selects the top-k (ties to the lower index).
-// ------------------------------------------------------------------------------------------
-
 // Block-wide sum in a fixed order (deterministic): wave sums, then wave 0 adds them in index order.
 template <int NT>
 __device__ __forceinline__ double block_sum_d(double v, double* smem /* NT/64 doubles */) {

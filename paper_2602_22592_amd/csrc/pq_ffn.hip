@@ -246,8 +246,8 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
   // (they then take the split rules and kernels of plain GEMMs, the four-wavefront weight-gradient kernel among them)
   const pq_gemm_group* pg1 = one ? nullptr : &g1;
   if (hp8) {
-    // slot-ordered X~ (for the backward), codes (int8 rows moved as D/2 16-bit units) and gamma of x; with a single
-    // branch the slot order is the token order and the originals serve
+    // slot-ordered X~ (for the backward), codes and gamma of x; with a single branch the slot order is the token order and
+    // the originals serve
     const void* xqp = one ? (const void*)Xq : (const void*)(cx + L.XqP);
     const float* gxp = one ? (const float*)gx : (const float*)(cx + L.gxP);
     if (!one) {

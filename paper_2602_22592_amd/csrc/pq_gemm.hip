@@ -1377,7 +1377,7 @@ int launch_mfma_cfg(const pq_gemm_plan& pl, int M, int N, int K, const pq_operan
     const int nbm = (M + 255) / 256, nbn = (N + 255) / 256;
     const bool dual = grp.mode == 3, ragged = K % 32 != 0 || pl.kchunk % 32 != 0;
     dim3 grid(nbm * nbn, pl.splits, dual ? 2 : 1);
-    if ((grp.mode && !dual) || A.kdiv || B.kdiv || epi.row_div || epi.out_kind == PQ_OUT_I32) return pq_set_error(PQ_ERR_BAD_ARG, "no 256x256 weight-gradient kernel for this epilogue");
+    if ((grp.mode && !dual) || epi.row_div || epi.out_kind == PQ_OUT_I32) return pq_set_error(PQ_ERR_BAD_ARG, "no 256x256 weight-gradient kernel for this epilogue");
     float* p = pl.splits > 1 ? part : nullptr;
 #define PQ_W4(R, D, T) gemm_tn_w4_kernel<R, D, T><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, nbm * nbn, pl.kchunk, p, second_arg<D>(second))
     if (dual) { if (ragged) PQ_W4(true, true, false); else PQ_W4(false, true, false); }
@@ -1780,7 +1780,7 @@ bool pq_skinny_applies(int M, int N, int K, const pq_operand& A, const pq_operan
   const bool b16 = A.kind == PQ_SRC_KC16 && (B.kind == PQ_SRC_KC16 || btr);
   const long es = i8 ? 1 : 2;
   if (!(i8 || b16)) return false;
-  if (!(M >= 1024 && N == SK_BN && K * es >= 128 && (K * es) % 128 == 0 && !A.kdiv && !B.kdiv && A.ld >= K && B.ld >= (btr ? N : K) &&
+  if (!(M >= 1024 && N == SK_BN && K * es >= 128 && (K * es) % 128 == 0 && A.ld >= K && B.ld >= (btr ? N : K) &&
         (A.ld * es) % 16 == 0 && (B.ld * es) % 16 == 0 && ((uintptr_t)A.p % 16) == 0 && ((uintptr_t)B.p % 16) == 0))
     return false;
   if (!(e.out_kind == PQ_OUT_BF16 && e.ldc >= N && (e.ldc * 2) % 8 == 0 && ((uintptr_t)e.C % 8) == 0 && !e.sign_bytes && !e.maskW &&
@@ -1945,7 +1945,7 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
   pq_reduce_job none;
   memset(&none, 0, sizeof(none));
   const int rb0 = (int)(((size_t)M0 * (N0 / 8) + 255) / 256), rb1 = (int)(((size_t)M1 * (N1 / 8) + 255) / 256);
-  auto al = [](const pq_operand& o) { return o.kind == PQ_SRC_KS16 && !o.kdiv && (o.ld * 2) % 16 == 0 && ((uintptr_t)o.p % 16) == 0; };
+  auto al = [](const pq_operand& o) { return o.kind == PQ_SRC_KS16 && (o.ld * 2) % 16 == 0 && ((uintptr_t)o.p % 16) == 0; };
   const bool one = M0 > 0 && N0 > 0 && M1 > 0 && N1 > 0 && K > 0 && al(A0) && al(B0) && al(A1) && al(B1) && A0.ld >= M0 && B0.ld >= N0 &&
                    A1.ld >= M1 && B1.ld >= N1 &&
                    (pp.splits == 1 || (sk0.p && sk1.p && ((uintptr_t)sk0.p % 16) == 0 && ((uintptr_t)sk1.p % 16) == 0));
@@ -2091,7 +2091,7 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
         pl.ws_bytes = pq_mode2_ws_bytes(M, N, grp.n_groups, K);
       }
     }
-    // row groups (expert segments): the tile by the same times (the streaming 256x256 form only on whole steps), the
+    // row groups (expert segments): the tile by the same times, the
     // contraction of a product with few tiles split as for plain GEMMs.  A per-group column divisor is applied in the
     // GEMM's own epilogue only, so such products are not split.
     if (grp.mode == 1) {

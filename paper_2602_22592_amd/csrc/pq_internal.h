@@ -65,9 +65,7 @@ int pq_launch_pack_quant_rows(const void* W, int N, int K, const double* partial
                               const pq_quant_rows_job* jobs, hipStream_t s);
 int pq_launch_router(const void* X, const void* Wr, int dtype, int T, int K, int E, int k, int* idx,
                      float* gate, float* probs, hipStream_t s);
-// out[0] = factor * sum(partials[0..n)) (+ optionally factor2 read from device: *dev_factor)
-int pq_launch_reduce_partials(const double* partials, int n, float factor, const float* dev_factor,
-                              float* out, hipStream_t s);
+// two sums of partials in one launch: out[0] = factor [* *dev_factor] * sum(partials[0..n))
 int pq_launch_reduce_partials2(const double* pa, int na, float fa, const float* dfa, float* oa, const double* pb, int nb, float fb,
                                const float* dfb, float* ob, hipStream_t s);
 
@@ -192,11 +190,8 @@ struct pq_pair_plan { bool tn, apart; int splits, kchunk; size_t ws0, ws1; };
 pq_pair_plan pq_plan_pair(int K, int M0, int N0, int M1, int N1);
 // Scratch a grouped launch over contraction ranges (mode 2; M x N per group, total_k indices over all groups) may use
 size_t pq_mode2_ws_bytes(int M, int N, int n_groups, int total_k);
-// Two bf16 GEMMs with contraction-strided operands on both sides (the rank-r weight gradients dA and dB) in one
-// launch (pq_plan_pair).
-// Both have plain epilogues: C (fp32) = scale * acc.
 // C[M][128] = scale * A B^T for bf16 operands and many rows (the hidden state of the dense high-precision branch
-// and its gradient, Sec. 3.2): one workgroup per 64 rows runs the whole contraction through a six-stage ring of
+// and its gradient, Sec. 3.2): one workgroup per 32 rows runs the whole contraction through a ring of seven stages of
 // direct-to-LDS loads, so nothing is split or reduced.  B is contraction-contiguous or contraction-strided; the
 // epilogue may carry dot_comp / partials (one partial sum per workgroup: pq_skinny_blocks(M) of them).
 // `applies` states the shapes, alignments and epilogues it takes.
@@ -204,6 +199,8 @@ bool pq_skinny_applies(int M, int N, int K, const pq_operand& A, const pq_operan
 int pq_skinny_blocks(int M);
 int pq_launch_skinny(int M, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& e, hipStream_t s, int prof_label);
 
+// Two bf16 GEMMs with contraction-strided operands on both sides (the rank-r weight gradients dA and dB), in one launch where
+// pq_plan_pair finds that better.  Both have plain epilogues: C (fp32) = scale * acc.
 int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const pq_operand& B0, float* C0, int ldc0, float scale0,
                              int M1, int N1, const pq_operand& A1, const pq_operand& B1, float* C1, int ldc1, float scale1,
                              hipStream_t s, int prof_label0, int prof_label1, pq_scratch sk0, pq_scratch sk1,

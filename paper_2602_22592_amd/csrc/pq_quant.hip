@@ -810,6 +810,12 @@ int pq_launch_pack(const void* W, int dtype, int N, int K, const double* partial
   return PQ_OK;
 }
 
+// ------------------------------------------------------------------------------------------
+// Router: a wavefront takes TB tokens at once (a router row converted to fp64 serves all of them): fp64 dot products
+// against all E router rows, lane l accumulating the 16-byte chunks l, l + 64, ... of a token row in order, then the
+// wave sums, which leave one (token, expert) pair per lane; that lane rounds the logit to fp32 and evaluates its term
+// of the softmax in fp64; the first lane of a token's group selects the top-k (ties to the lower index).
+// ------------------------------------------------------------------------------------------
 template <typename T, int EMAX, int TB>
 __global__ __launch_bounds__(256) void router_kernel(const T* __restrict__ X, const T* __restrict__ Wr,
                                                      int Tn, int K, int E, int k, int* __restrict__ idx,
@@ -933,15 +939,6 @@ typedef pq_reduce_job reduce_job;
 
 __global__ __launch_bounds__(256) void reduce_partials_kernel(reduce_job j0, reduce_job j1) {   // one workgroup per job
   pq_reduce_job_body(blockIdx.x == 0 ? j0 : j1);
-}
-
-int pq_launch_reduce_partials(const double* partials, int n, float factor, const float* dev_factor,
-                              float* out, hipStream_t s) {
-  pq_prof_scope prof(PQP_REDUCE, s);
-  const reduce_job j{partials, n, factor, dev_factor, out};
-  reduce_partials_kernel<<<1, 256, 0, s>>>(j, j);
-  PQ_CHECK_LAUNCH("reduce_partials_kernel");
-  return PQ_OK;
 }
 
 // two independent reductions in one launch

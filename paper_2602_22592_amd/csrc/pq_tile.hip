@@ -5,8 +5,9 @@
 // Takes what the 256x256 kernels of pq_gemm.hip leave idle: outputs of few tiles, narrow outputs, expert segments and
 // contractions that are not whole steps.  Such a product is a chain of memory latencies, so everything here is about
 // having the whole of it in flight: operand tiles of a 128-byte contraction step go from global memory straight into a
-// ring of LDS stages (NST - 1 steps ahead of the MFMAs, two workgroups per CU), the second contraction's tiles are
-// requested before the first one's at 64x64, and there is one barrier per step.
+// ring of LDS stages.  128x128: NST stages, NST - 1 of them ahead of the MFMAs, one barrier per step, two workgroups per CU.
+// 64x64: groups of two steps, one barrier per group; two groups (two workgroups per CU), or four while the launch leaves a
+// workgroup a CU to itself; the second contraction's first tiles are requested before the first one's.
 // A chunk past the end of the contraction is fetched from a page of zeros, so any length that is a whole number of 16-byte
 // chunks (KC kinds) or of rows (KS16) runs without masks; rows and columns past the edge re-read a valid one and are not
 // stored.  Packed signs stay packed in LDS (one dword per lane and load, no alignment beyond the word) and are expanded
@@ -105,65 +106,12 @@ struct tile_frag {
 };
 
 // LDS reads are asm blocks that carry their own wait, so a register is valid when its block ends; what a wavefront needs
-// next goes into one block, and in the second half of a 128x128 step the MFMAs of the first half sit between the reads and
-// the wait.  (Reads per sub-step with a wait each ran a 64x64 step in 1000 clocks whatever the depth of the ring.)
-// q: 16-byte operands, o[2 or 4 sub-steps x NB]; h: 8-byte halves of transposing reads, two per operand.
+// next goes into one block: two sub-steps of a 128x128 step (all four with packed signs).  (Reads per sub-step with a wait
+// each ran a 64x64 step in 1000 clocks whatever the depth of the ring.)  t, u: 8-byte halves of transposing reads, two per operand.
 __device__ __forceinline__ i32x4_t join(const pq_i32x2& lo, const pq_i32x2& hi) { return i32x4_t{lo[0], lo[1], hi[0], hi[1]}; }
 #define RD "ds_read_b128 "
 #define RT "ds_read_b64_tr_b16 "
 #define W0 "s_waitcnt lgkmcnt(0)"
-
-// one 32-row block, all four sub-steps
-__device__ __forceinline__ void rd_kc4(i32x4_t* o, uint32_t p) {
-  asm volatile(RD "%0, %4\n\t" RD "%1, %5\n\t" RD "%2, %6\n\t" RD "%3, %7\n\t" W0
-               : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]) : "v"(p), "v"(p ^ 32u), "v"(p ^ 64u), "v"(p ^ 96u) : "memory");
-}
-// ... with the packed words of the B block(s)
-__device__ __forceinline__ void rd_kc4_bits(i32x4_t* o, i32x4_t& q, uint32_t p, uint32_t pq, std::true_type) {
-  asm volatile(RD "%4, %9\n\t" RD "%0, %5\n\t" RD "%1, %6\n\t" RD "%2, %7\n\t" RD "%3, %8\n\t" W0
-               : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(q)
-               : "v"(p), "v"(p ^ 32u), "v"(p ^ 64u), "v"(p ^ 96u), "v"(pq) : "memory");
-}
-__device__ __forceinline__ void rd_kc4_bits(i32x4_t* o, i32x4_t& q, uint32_t p, uint32_t pq, std::false_type) {
-  pq_i32x2 t;
-  asm volatile("ds_read_b64 %4, %9\n\t" RD "%0, %5\n\t" RD "%1, %6\n\t" RD "%2, %7\n\t" RD "%3, %8\n\t" W0
-               : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(t)
-               : "v"(p), "v"(p ^ 32u), "v"(p ^ 64u), "v"(p ^ 96u), "v"(pq) : "memory");
-  q[0] = t[0]; q[1] = t[1];
-}
-__device__ __forceinline__ void rd_kc4_kc4(i32x4_t* a, i32x4_t* b, uint32_t p, uint32_t r) {
-  asm volatile(RD "%0, %8\n\t" RD "%4, %12\n\t" RD "%1, %9\n\t" RD "%5, %13\n\t" RD "%2, %10\n\t" RD "%6, %14\n\t" RD "%3, %11\n\t" RD "%7, %15\n\t" W0
-               : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3]), "=&v"(b[0]), "=&v"(b[1]), "=&v"(b[2]), "=&v"(b[3])
-               : "v"(p), "v"(p ^ 32u), "v"(p ^ 64u), "v"(p ^ 96u), "v"(r), "v"(r ^ 32u), "v"(r ^ 64u), "v"(r ^ 96u) : "memory");
-}
-// ROWS: columns of the KS16 tile; sub-step ks and half hf lie (16 ks + 4 hf) rows on
-template <int ROWS>
-__device__ __forceinline__ void rd_kc4_ks4(i32x4_t* a, i32x4_t* b, uint32_t p, uint32_t r) {
-  pq_i32x2 t[8];
-  constexpr int R = ROWS * 2;
-  asm volatile(RT "%4, %16\n\t" RT "%5, %16 offset:%17\n\t" RD "%0, %12\n\t" RT "%6, %16 offset:%18\n\t" RT "%7, %16 offset:%19\n\t" RD "%1, %13\n\t"
-               RT "%8, %16 offset:%20\n\t" RT "%9, %16 offset:%21\n\t" RD "%2, %14\n\t" RT "%10, %16 offset:%22\n\t" RT "%11, %16 offset:%23\n\t" RD "%3, %15\n\t" W0
-               : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3]), "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3]), "=&v"(t[4]), "=&v"(t[5]),
-                 "=&v"(t[6]), "=&v"(t[7])
-               : "v"(p), "v"(p ^ 32u), "v"(p ^ 64u), "v"(p ^ 96u), "v"(r), "n"(4 * R), "n"(16 * R), "n"(20 * R), "n"(32 * R), "n"(36 * R), "n"(48 * R),
-                 "n"(52 * R) : "memory");
-#pragma unroll
-  for (int k = 0; k < 4; ++k) b[k] = join(t[2 * k], t[2 * k + 1]);
-}
-template <int ROWS>
-__device__ __forceinline__ void rd_ks4_ks4(i32x4_t* a, i32x4_t* b, uint32_t p, uint32_t r) {
-  pq_i32x2 t[8], u[8];
-  constexpr int R = ROWS * 2;
-  asm volatile(RT "%0, %16\n\t" RT "%1, %16 offset:%18\n\t" RT "%8, %17\n\t" RT "%9, %17 offset:%18\n\t"
-               RT "%2, %16 offset:%19\n\t" RT "%3, %16 offset:%20\n\t" RT "%10, %17 offset:%19\n\t" RT "%11, %17 offset:%20\n\t"
-               RT "%4, %16 offset:%21\n\t" RT "%5, %16 offset:%22\n\t" RT "%12, %17 offset:%21\n\t" RT "%13, %17 offset:%22\n\t"
-               RT "%6, %16 offset:%23\n\t" RT "%7, %16 offset:%24\n\t" RT "%14, %17 offset:%23\n\t" RT "%15, %17 offset:%24\n\t" W0
-               : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3]), "=&v"(t[4]), "=&v"(t[5]), "=&v"(t[6]), "=&v"(t[7]),
-                 "=&v"(u[0]), "=&v"(u[1]), "=&v"(u[2]), "=&v"(u[3]), "=&v"(u[4]), "=&v"(u[5]), "=&v"(u[6]), "=&v"(u[7])
-               : "v"(p), "v"(r), "n"(4 * R), "n"(16 * R), "n"(20 * R), "n"(32 * R), "n"(36 * R), "n"(48 * R), "n"(52 * R) : "memory");
-#pragma unroll
-  for (int k = 0; k < 4; ++k) { a[k] = join(t[2 * k], t[2 * k + 1]); b[k] = join(u[2 * k], u[2 * k + 1]); }
-}
 
 // Two 32-row blocks per operand (128x128 tiles), sub-steps ks and ks + 1 (x = ks << 5): o[2 * (ks & 1) + block].
 __device__ __forceinline__ void rd_kc_kc_x2(i32x4_t* a, i32x4_t* b, uint32_t p0, uint32_t p1, uint32_t r0, uint32_t r1, uint32_t x) {
@@ -222,28 +170,15 @@ __device__ __forceinline__ void mma(ACC& c, const i32x4_t& a, const i32x4_t& b) 
   else c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, b), __builtin_bit_cast(bf16x8_t, a), c, 0, 0, 0);
 }
 
-// The products of one stage (byte offset so): four sub-steps of the wavefront's TM x TN blocks.
-template <bool INT8, int AK, int BK, int BM, int TM, int TN, typename FA, typename FB, typename ACC>
-__device__ __forceinline__ void tile_step(const FA& fa, const FB& fb, uint32_t so, int lane, ACC (&acc)[TM][TN]) {
+// The products of one stage (byte offset so): four sub-steps of the wavefront's 2 x 2 blocks.
+template <bool INT8, int AK, int BK, int BM, typename FA, typename FB, typename ACC>
+__device__ __forceinline__ void tile_step(const FA& fa, const FB& fb, uint32_t so, int lane, ACC (&acc)[2][2]) {
   constexpr bool bits = BK == PQ_SRC_BITS8 || BK == PQ_SRC_BITS16;
   auto expand = [&](const i32x4_t& q, int ks) -> i32x4_t {
     if constexpr (BK == PQ_SRC_BITS8) return pq_bits_to_i8((uint32_t)q[ks] >> (16 * (lane >> 5)));
     else return pq_bits_to_bf16((uint32_t)q[ks >> 1] >> (16 * (ks & 1) + 8 * (lane >> 5)));
   };
-  if constexpr (TM == 1) {
-    i32x4_t oa[4], ob[4];
-    const uint32_t p = fa.ad[0] + so, r = fb.ad[0] + so;
-    if constexpr (bits) {
-      i32x4_t q;
-      rd_kc4_bits(oa, q, p, r, std::integral_constant<bool, BK == PQ_SRC_BITS8>{});
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) ob[ks] = expand(q, ks);
-    } else if constexpr (AK == PQ_SRC_KS16) rd_ks4_ks4<BM>(oa, ob, p, r);
-    else if constexpr (BK == PQ_SRC_KS16) rd_kc4_ks4<BM>(oa, ob, p, r);
-    else rd_kc4_kc4(oa, ob, p, r);
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) mma<INT8>(acc[0][0], oa[ks], ob[ks]);
-  } else if constexpr (bits) {
+  if constexpr (bits) {
     i32x4_t oa[8], q[2];
     rd_kc_bits_x4<BK == PQ_SRC_BITS8>(oa, q, fa.ad[0] + so, fa.ad[1] + so, fb.ad[0] + so, fb.ad[1] + so);
 #pragma unroll
@@ -271,12 +206,13 @@ __device__ __forceinline__ void tile_step(const FA& fa, const FB& fb, uint32_t s
   }
 }
 
-template <int BM, int BN, int NST, bool INT8, int AK, int BK, int BK2>
+// 128x128 tiles: wavefront (wv >> 1, wv & 1) multiplies a 64x64 quadrant.  NST: ring stages.
+template <int NST, bool INT8, int AK, int BK, int BK2>
 __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn,
                                                         int total_tiles, int kchunk, float* splitk_part, pq_gemm_group grp, pq_phase2 ph2,
                                                         pq_second_arg<pair_kinds<AK, BK, BK2>()> second) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;
+  constexpr int BM = 128, BN = 128, WM = 64, WN = 64, TM = 2, TN = 2;
   constexpr int EPB = INT8 ? 128 : 64;
   using SA = tile_src<AK, BM>;
   using SB = tile_src<BK, BN>;
@@ -284,10 +220,8 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_
   constexpr int STG = SA::BYTES + SB::BYTES;
   constexpr bool PH2 = BK2 >= 0;
   constexpr int STG2 = PH2 ? (BM + BN) * 128 : 0;
-  constexpr bool EARLY2 = PH2 && BM == 64;           // the second contraction's first two steps have LDS of their own
   constexpr int RING = NST * STG;
-  constexpr int OFF2 = EARLY2 ? RING : 0;
-  constexpr int SMEM = EARLY2 ? RING + 2 * STG2 : (RING > 2 * STG2 ? RING : 2 * STG2);
+  constexpr int SMEM = RING > 2 * STG2 ? RING : 2 * STG2;   // (the second contraction's stages follow in the same place)
   using acc_t = typename std::conditional<INT8, i32x16_t, f32x16_t>::type;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
   __shared__ double red[4];
@@ -363,15 +297,11 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_
       SB2 b2;
       a2.setup(ph2.A2, m0, M, 0, wv, lane);
       b2.setup(ph2.B2, n0, N, 0, wv, lane);
-      unsigned char* base = smem + OFF2 + (t & 1) * STG2;
+      unsigned char* base = smem + (t & 1) * STG2;
       a2.issue(t, ph2.K2, base, wv);
       b2.issue(t, ph2.K2, base + BM * 128, wv);
     }
   };
-  if constexpr (EARLY2) {                            // oldest loads: every wait of the main loop covers them
-    if (nk2 > 0) issue2(0);
-    if (nk2 > 1) issue2(1);
-  }
   SA sa;
   SB sb;
   sa.setup(A, m0, M, kb, wv, lane);
@@ -412,11 +342,9 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_
 
   f32x16_t accf[PH2 ? TM : 1][PH2 ? TN : 1];
   if constexpr (PH2) {
-    if constexpr (!EARLY2) {
-      asm volatile("s_barrier" ::: "memory");        // the ring's last stage has been read by everybody
-      if (nk2 > 0) issue2(0);
-      if (nk2 > 1) issue2(1);
-    }
+    asm volatile("s_barrier" ::: "memory");          // the ring's last stage has been read by everybody
+    if (nk2 > 0) issue2(0);
+    if (nk2 > 1) issue2(1);
     const float sc1 = ph2.dev_scale1 ? __fmul_rn(ph2.scale1, *ph2.dev_scale1) : ph2.scale1;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -431,8 +359,8 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_
     }
     tile_frag<PQ_SRC_KC16, BM, TM> f2a;
     tile_frag<BK2 == PQ_SRC_KS16 ? PQ_SRC_KS16 : PQ_SRC_KC16, BN, TN> f2b;
-    f2a.setup(lds0 + OFF2, wm0, lane);
-    f2b.setup(lds0 + OFF2 + BM * 128, wn0, lane);
+    f2a.setup(lds0, wm0, lane);
+    f2b.setup(lds0 + BM * 128, wn0, lane);
     for (int t = 0; t < nk2; ++t) {
       // (two steps in flight; the older one has landed when at most one step's loads are outstanding)
       if (t + 1 < nk2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(SA2::LPW + SB2::LPW) : "memory");
@@ -841,7 +769,7 @@ int launch_tile(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A
     if ((long)grid.x * grid.y * grid.z <= 256) tile64_gemm_kernel<PQ_NG_DEEP, INT8, AK, BK, BK2><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, tiles, pl.kchunk, p, grp, ph2, second_arg<PAIR>(second));
     else tile64_gemm_kernel<NST, INT8, AK, BK, BK2><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, tiles, pl.kchunk, p, grp, ph2, second_arg<PAIR>(second));
   } else {
-    tile_gemm_kernel<BM, BM, NST, INT8, AK, BK, BK2><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, tiles, pl.kchunk, p, grp, ph2, second_arg<PAIR>(second));
+    tile_gemm_kernel<NST, INT8, AK, BK, BK2><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, tiles, pl.kchunk, p, grp, ph2, second_arg<PAIR>(second));
   }
   PQ_CHECK_LAUNCH("tile_gemm_kernel");
   return PQ_OK;
