@@ -38,7 +38,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 # operand kinds of A and B, kinds of the fused second contraction, paired)
 TRAFFIC_KERNELS = {"gemm_dW": "gemm_tn_w4_kernel", "gemm_dX": "128, true, false, false, 0, 4, 0, 1, false>",
                    "gemm_onebit_fwd": "128, true, false, true, 2, 3, 0, 0, false>", "decode_main_B1": "decode_gemv_tiled_kernel<1, false>",
-                   "decode_main_B8": "decode_gemm16_tiled_kernel<8, false, false>", "decode_prep_B1": "decode_prep_h_kernel<false>",
+                   "decode_main_B8": "decode_gemm16_tiled_kernel<8, false, false>", "decode_prep_B1": "decode_prep_h_kernel<false, true>",
                    "decode_prep_B8": "decode_prep_kernel", "decode_h_B8": "decode_h_grouped_kernel<8>"}
 
 
@@ -365,17 +365,18 @@ def ffn_bench(pq, torch, T=8192, D=2048, F=5504, E=8, r=32, steps=20, warmup=5, 
     prof = _profile_steps(pq, torch, step, steps)
     # one active expert per token: 3 projections of width r forward, 6 GEMMs backward (bf16)
     t_mfma = 3 * 2.0 * T * D * F / PEAK_I8 + 6 * 2.0 * T * D * F / PEAK_BF16 + 9 * 2.0 * T * D * r / PEAK_BF16
-    # roofline of the label with the largest total time: its launches are GEMMs of 2 T D F flops each
+    # roofline of the label with the largest total time: three products of 2 T D F flops a step (a launch may hold two of them)
     big = {k: v for k, v in prof.items() if k in ("gemm_dW", "gemm_dX", "gemm_onebit_fwd")}
     dom = max(big, key=lambda k: big[k][0])
     peak = PEAK_I8 if dom == "gemm_onebit_fwd" else PEAK_BF16
-    ach = 2.0 * T * D * F * big[dom][1] / (big[dom][0] * 1e-3)
+    products = 3 * steps
+    ach = 2.0 * T * D * F * products / (big[dom][0] * 1e-3)
     return {"workload": f"tokens={T}, d_model={D}, d_ffn={F}, E={E} {'INT8' if int8_experts else 'bf16'} experts of width {r}, top-1, "
                         "bf16 I/O, fwd+bwd",
             "ms_per_step": round(ms, 4), "tokens_per_s": round(T / ms * 1e3, 1), "mfma_frac_of_step": round(t_mfma / (ms * 1e-3), 4),
             "roofline": {"bound": "mfma", "kernel": dom, "achieved": round(ach / 1e12, 2), "peak": peak / 1e12,
                          "unit": "TOP/s" if dom == "gemm_onebit_fwd" else "TFLOP/s", "frac": round(ach / peak, 4),
-                         "avg_us": round(1e3 * big[dom][0] / big[dom][1], 2), "traffic": None},
+                         "avg_us": round(1e3 * big[dom][0] / products, 2), "traffic": None},
             "kernels_us_total_per_step": {k: round(1e3 * v[0] / steps, 1) for k, v in sorted(prof.items())}}
 
 
