@@ -240,6 +240,31 @@ struct tile_stage {
 #define PQ_MFMA_BF16(acc, a, b) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %2, %1, %0" : "+v"(acc) : "v"(a), "v"(b))
 #define PQ_MFMA_I8(acc, a, b) asm volatile("v_mfma_i32_32x32x32_i8 %0, %2, %1, %0" : "+v"(acc) : "v"(a), "v"(b))
 
+// The result registers of an asm MFMA may be read by other instructions only when the matrix pipe has written them, up to 19
+// issue slots later, and the compiler, which does not see an MFMA in the statement, puts no such distance there.  Whoever leaves
+// a loop of asm MFMAs passes its accumulators through here: the waits, then a statement per accumulator that everything
+// behind it depends on.  (A barrier in between hides the hazard by chance only: with four wavefronts to a workgroup the last
+// register of the last block came out one product short.)
+#define PQ_MFMA_SETTLE_FIRST() asm volatile("s_nop 15\n\ts_nop 3" ::: "memory")
+template <typename ACC, int NB>
+__device__ __forceinline__ void pq_mfma_settle(ACC (&acc)[NB]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  PQ_MFMA_SETTLE_FIRST();
+#pragma unroll
+  for (int j = 0; j < NB; ++j) asm volatile("" : "+v"(acc[j]));
+#endif
+}
+template <typename ACC, int NA, int NB>
+__device__ __forceinline__ void pq_mfma_settle(ACC (&acc)[NA][NB]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  PQ_MFMA_SETTLE_FIRST();
+#pragma unroll
+  for (int i = 0; i < NA; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) asm volatile("" : "+v"(acc[i][j]));
+#endif
+}
+
 // One fragment set of a 128x64 wavefront tile: four A and two B operands of 16 bytes per lane.  Operands
 // read with ds_read_b128 are whole (q), transposing reads deliver 8-byte halves (h) that the register
 // allocator places next to each other.
@@ -712,6 +737,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
       }
       PQ_SETPRIO(0);
       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      pq_mfma_settle(acc);
 #undef PQ_EXPAND
 #undef PQ_MFMA_AB
     } else {
@@ -797,6 +823,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
     }
     PQ_SETPRIO(0);
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    pq_mfma_settle(acc);
     }
 #endif
   }
@@ -1279,6 +1306,11 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
     }
   }
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  PQ_MFMA_SETTLE_FIRST();
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) asm volatile("" : "+a"(acc[i][j]));
   asm volatile("s_barrier" ::: "memory");
 
   // ---- epilogue ----------------------------------------------------------------------------------
@@ -1591,6 +1623,7 @@ __global__ __launch_bounds__(256) void skinny_gemm_kernel(const void* __restrict
     st = st == NST - 1 ? 0 : st + 1;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the redundant loads of the last steps are done before the workgroup ends
+  pq_mfma_settle(acc);
 
   // the B fragment was the first MFMA operand: lane l holds row l & 31, register v column 8 (v >> 2) + 4 (l >> 5) + (v & 3)
   const int m = m0 + wr0 + (lane & 31);
@@ -1753,6 +1786,7 @@ __global__ __launch_bounds__(256) void skinny_tn_pair_kernel(skt_problem p0, skt
     st = st == NST - 1 ? 0 : st + 1;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  pq_mfma_settle(acc);
 
   // lane l holds row l & 31 (a column of the wide operand), register v column 8 (v >> 2) + 4 (l >> 5) + (v & 3)
   const int m = m0 + wr0 + (lane & 31);
