@@ -79,17 +79,18 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   const int Ti = d.tokens, Di = d.d_model, Fi = (int)F;
   // (the last seven: the expert products of a single high-precision branch, which run as plain GEMMs over all slots)
   const int Si = (int)S, ri = (int)r;
-  const int shapes[11][3] = {{Di, Fi, Ti}, {Ti, Fi, Di}, {Ti, Di, Fi}, {Fi, Di, Ti},
+  const int shapes[9][3] = {{Di, Fi, Ti}, {Fi, Di, Ti},
                              {Si, 2 * ri, Di}, {Si, ri, Di}, {Si, Di, 2 * ri}, {Si, Di, ri}, {Di, ri, Si}, {2 * ri, Di, Si}, {ri, Di, Si}};
   for (const auto& sh : shapes) {
     if (sh[0] <= 0 || sh[1] <= 0) continue;
     const size_t b = pq_plan_gemm(sh[0], sh[1], sh[2]).ws_bytes;
     if (b > sk) sk = b;
   }
-  for (const auto& sh : {std::pair<int, int>{Fi, Di}, std::pair<int, int>{Di, Fi}}) {   // the 1-bit forward products
-    const size_t b = Ti > 0 ? pq_plan_gemm(Ti, sh.first, sh.second, true, true).ws_bytes : 0;
-    if (b > sk) sk = b;
-  }
+  for (const auto& sh : {std::pair<int, int>{Fi, Di}, std::pair<int, int>{Di, Fi}})   // the products with packed signs: forward and input gradients
+    for (const bool fwd : {true, false}) {
+      const size_t b = Ti > 0 ? pq_plan_gemm(Ti, sh.first, sh.second, fwd, fwd, true).ws_bytes : 0;
+      if (b > sk) sk = b;
+    }
   {   // U and G, and dW_up and dW_gate, as one launch each
     const size_t f2 = Ti > 0 ? pq_plan_dual(Ti, Fi, Di, true).ws_bytes : 0, w2 = pq_plan_dual(Fi, Di, Ti, false).ws_bytes;
     if (f2 > sk) sk = f2;

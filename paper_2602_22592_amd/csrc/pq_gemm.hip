@@ -6,11 +6,10 @@
 //   KC16 / KC8   contraction-contiguous rows, 16 bytes at a time;
 //   KS16         contraction-strided sources (the transposed operands of the weight-gradient GEMMs);
 //   BITS8/BITS16 packed sign bits, expanded to +/-1 (int8 or bf16).
-// 256x256 tiles here, smaller ones in pq_tile.hip.  The main loop sends operands from global memory straight into LDS: KC
+// 256x256 tiles here, 128x256 where B is packed signs, smaller ones in pq_tile.hip.  The main loop sends operands from global memory straight into LDS: KC
 // tiles as ROWS x 128 bytes, KS16 tiles as they lie in memory (read back with the transposing LDS read), and packed bits stay
 // packed in LDS and are expanded in registers next to the MFMAs that consume them.  Contractions that are not whole steps
-// fetch what is missing from a page of zeros.  The rank-r branch's second contraction rides in on the same ring, or, when it
-// is not one or two whole steps, through registers (KS16 blocks are then transposed with byte permutes).
+// fetch what is missing from a page of zeros.  The rank-r branch's second contraction rides in on the same ring.
 // A wavefront owns a (BM/WGM) x (BN/WGN) sub-tile as 32x32 MFMA blocks:
 //   v_mfma_f32_32x32x16_bf16 / v_mfma_i32_32x32x32_i8, 16 bytes of operand per lane per issue.
 // LDS rows are 128 bytes with the 16-byte chunk index XOR-swizzled by the row so that the MFMA
@@ -42,11 +41,6 @@ namespace {
 
 [[maybe_unused]] __device__ __attribute__((aligned(256))) unsigned char pq_zero_page[256];   // never written
 
-__device__ __forceinline__ uint4 mask4(const uint4& t, bool keep) {
-  const uint32_t m = keep ? 0xFFFFFFFFu : 0u;
-  return make_uint4(t.x & m, t.y & m, t.z & m, t.w & m);
-}
-
 // Byte offset of 16-byte chunk c of row r in a tile whose rows are KB bytes (128 or 64).  The chunk
 // index is XOR-swizzled by the row so that 8 consecutive rows at one logical chunk, and rows 8 apart
 // at consecutive chunks (the transposing stores), fall into distinct 16-byte bank groups.
@@ -55,156 +49,6 @@ __device__ __forceinline__ int lds_off(int r, int c) {
   if constexpr (KB == 128) return r * 128 + (((c ^ r ^ (r >> 3)) & 7) << 4);
   else return r * 64 + (((c ^ (r >> 1) ^ (r >> 3)) & 3) << 4);
 }
-
-// ---------------------------------------------------------------------------------------------
-// Operand tile staging of the second contraction: global -> registers (load) and registers -> LDS (store)
-// ---------------------------------------------------------------------------------------------
-// Everything that does not change from one contraction step to the next (which rows and LDS slots a
-// thread serves, their byte offsets) is computed once in setup(); a step then costs one load per
-// 16 bytes with a uniform base pointer.  FAST instantiations are for shapes made of whole tiles:
-// they carry no validity masks at all.  Otherwise loads stay unconditional (an out-of-range chunk
-// reads element (0,0), which always exists, and is replaced by zeros on the way into LDS) so that
-// all of a thread's loads are in flight together.
-template <int KIND, int ROWS, int NT, int KB, bool FAST>
-struct tile_stage {
-  static constexpr int CPR = KB / 16;                        // 16-byte chunks per LDS row
-  static constexpr int NCH = (ROWS * CPR + NT - 1) / NT;     // chunks per thread
-  static_assert(KIND == PQ_SRC_KC16 || KIND == PQ_SRC_KS16, "bf16 operands");
-  static constexpr bool kStrided = (KIND == PQ_SRC_KS16);
-  static constexpr int EPC = 8;                              // elements per chunk
-  // KS16: a unit is 8 rows x KQ contraction indices (KQ 16-byte loads, transposed in registers);
-  // KQ is the largest of 8, 4, 2 that still gives every thread a unit
-  static constexpr int KQ = (ROWS * KB / 128 >= NT) ? 8 : (ROWS * KB / 64 >= NT) ? 4 : 2;
-  static constexpr int UPR = (KB / 2) / KQ;                  // units per 8-row group
-  static constexpr int UPC = 8 / KQ;                         // units per 16-byte chunk
-  static constexpr int NU = (ROWS / 8 * UPR + NT - 1) / NT;  // units per thread
-  static_assert(NT % CPR == 0 && NT % UPR == 0, "a thread keeps its contraction position across chunks");
-  uint4 v[kStrided ? NU * KQ : NCH];
-  uint32_t boff[kStrided ? NU : NCH];      // byte offset of each load at contraction index 0
-  uint32_t ldst[kStrided ? NU * 8 : NCH];  // LDS byte offset of each store
-  uint32_t rowok;                          // bit i: chunk / unit i lies in a valid row
-  uint32_t okbits;                         // validity of each load of the step in flight
-  uint32_t jstride;                        // KS16: bytes between consecutive contraction indices
-  int kpos;                                // this thread's contraction offset inside a tile (elements)
-
-  __device__ __forceinline__ void setup(const pq_operand& op, int row0, int rows, int tid) {
-    rowok = 0u;
-    okbits = 0u;
-    if constexpr (kStrided) {
-      jstride = (uint32_t)op.ld * 2u;
-      kpos = (tid % UPR) * KQ;
-#pragma unroll
-      for (int i = 0; i < NU; ++i) {
-        const int u = tid + i * NT;
-        const int r8 = u / UPR, kq = u % UPR;
-        const int col = row0 + r8 * 8;
-        const bool ok = (u < ROWS / 8 * UPR) && (col < rows);
-        rowok |= (ok ? 1u : 0u) << i;
-        boff[i] = ((uint32_t)(kq * KQ) * (uint32_t)op.ld + (uint32_t)(ok ? col : 0)) * 2u;
-#pragma unroll
-        for (int rr = 0; rr < 8; ++rr)
-          ldst[i * 8 + rr] = (uint32_t)(lds_off<KB>(r8 * 8 + rr, kq / UPC) + (kq % UPC) * (KQ * 2));
-      }
-    } else {
-      jstride = 0u;
-      kpos = (tid % CPR) * EPC;
-#pragma unroll
-      for (int i = 0; i < NCH; ++i) {
-        const int c = tid + i * NT;
-        const int r = c / CPR, kc = c % CPR;
-        const int grow = row0 + r;
-        const bool ok = (c < ROWS * CPR) && (grow < rows);
-        rowok |= (ok ? 1u : 0u) << i;
-        boff[i] = ((uint32_t)(ok ? grow : 0) * (uint32_t)op.ld + (uint32_t)(kc * EPC)) * 2u;
-        ldst[i] = (uint32_t)lds_off<KB>(r, kc);
-      }
-    }
-  }
-
-  // k0: contraction index of the tile's first element; K: end of the valid contraction range.  The loads of
-  // a step can be issued in `np` pieces (piece = 0..np-1, both compile-time constants after unrolling) so
-  // that the caller can spread them between its MFMA groups.
-  __device__ __forceinline__ void load(const pq_operand& op, int k0, int K, int piece = 0, int np = 1) {
-    if constexpr (kStrided) {
-      constexpr int NL = NU * KQ;
-      const char* base = FAST ? (const char*)op.p + (size_t)k0 * jstride : (const char*)op.p;
-      const uint32_t kbyte = FAST ? 0u : (uint32_t)k0 * jstride;
-      if (piece == 0) okbits = 0u;
-#pragma unroll
-      for (int i = 0; i < NU; ++i) {
-#pragma unroll
-        for (int j = 0; j < KQ; ++j) {
-          if (((i * KQ + j) * np) / NL != piece) continue;
-          uint32_t off = boff[i] + (uint32_t)j * jstride;
-          if constexpr (!FAST) {
-            const bool ok = ((rowok >> i) & 1u) && (k0 + kpos + j < K);
-            off = ok ? off + kbyte : 0u;
-            okbits |= (ok ? 1u : 0u) << (i * KQ + j);
-          }
-          v[i * KQ + j] = *reinterpret_cast<const uint4*>(base + off);
-        }
-      }
-    } else {
-      const size_t kb8 = (size_t)k0 * 2;
-      const char* base = FAST ? (const char*)op.p + kb8 : (const char*)op.p;
-      const bool kv = FAST ? true : (k0 + kpos < K);
-      okbits = kv ? rowok : 0u;
-#pragma unroll
-      for (int i = 0; i < NCH; ++i) {
-        if ((i * np) / NCH != piece) continue;
-        uint32_t off = boff[i];
-        if constexpr (!FAST) off = ((okbits >> i) & 1u) ? off + (uint32_t)kb8 : 0u;
-        v[i] = *reinterpret_cast<const uint4*>(base + off);
-      }
-    }
-  }
-
-  __device__ __forceinline__ uint4 valid(const uint4& t, int bit) const {
-    if constexpr (FAST) return t;
-    else return mask4(t, (okbits >> bit) & 1u);
-  }
-
-  // np > 1: only the chunks of piece `piece` (contraction-contiguous kinds)
-  __device__ __forceinline__ void store(unsigned char* lds, int tid, int piece = 0, int np = 1) const {
-    if constexpr (kStrided) {
-#pragma unroll
-      for (int i = 0; i < NU; ++i) {
-        const int u = tid + i * NT;
-        if (u < ROWS / 8 * UPR) {
-          // transpose of 16-bit elements: v[i*KQ+j] holds rows r8*8..+7 at contraction index j
-#pragma unroll
-          for (int rr = 0; rr < 8; ++rr) {
-            uint32_t o[KQ / 2];
-#pragma unroll
-            for (int p = 0; p < KQ / 2; ++p) {
-              const uint4 lo4 = valid(v[i * KQ + 2 * p], i * KQ + 2 * p);
-              const uint4 hi4 = valid(v[i * KQ + 2 * p + 1], i * KQ + 2 * p + 1);
-              const uint32_t lo = (rr >> 1) == 0 ? lo4.x : (rr >> 1) == 1 ? lo4.y : (rr >> 1) == 2 ? lo4.z : lo4.w;
-              const uint32_t hi = (rr >> 1) == 0 ? hi4.x : (rr >> 1) == 1 ? hi4.y : (rr >> 1) == 2 ? hi4.z : hi4.w;
-              // result = [lo.half, hi.half]; v_perm selects bytes 0-3 from the 2nd operand, 4-7 from the 1st
-              o[p] = (rr & 1) ? __builtin_amdgcn_perm(hi, lo, 0x07060302u)
-                              : __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-            }
-            unsigned char* dst = lds + ldst[i * 8 + rr];
-            if constexpr (KQ == 8) *reinterpret_cast<uint4*>(dst) = make_uint4(o[0], o[1], o[2], o[3]);
-            else if constexpr (KQ == 4) *reinterpret_cast<uint2*>(dst) = make_uint2(o[0], o[1]);
-            else *reinterpret_cast<uint32_t*>(dst) = o[0];
-          }
-        }
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < NCH; ++i) {
-        if ((i * np) / NCH != piece) continue;
-        const int c = tid + i * NT;
-        if (c < ROWS * CPR) {
-          const uint4 out = valid(v[i], i);
-          *reinterpret_cast<uint4*>(lds + ldst[i]) = out;
-        }
-      }
-    }
-  }
-};
 
 // ---------------------------------------------------------------------------------------------
 // Main loop: operands go from global memory straight into LDS
@@ -221,9 +65,15 @@ struct tile_stage {
 //     hands lane i of a 16-lane group element (i % 4) of the 8-byte row addressed by lane 4 e + i / 4,
 //     e = 0..3: with lane j addressing (t = j / 4, 4 columns at 4 (j % 4)) lane i receives four consecutive
 //     t of column i.
-//   * packed-bit B operands stay packed in LDS (32-byte chunks of a row, one 16-byte direct load per
-//     wavefront and chunk, three chunk buffers) and are expanded to MFMA operands in registers, one dword
+//   * packed-bit B operands stay packed in LDS (32-byte chunks of a row, two 16-byte direct loads per
+//     wavefront and chunk, two chunk buffers) and are expanded to MFMA operands in registers, one dword
 //     behind each MFMA; with B that small the A operand gets a ring of four stages instead of two.
+//     Such a tile is 128x256 on four wavefronts, each with the 128x64 of the eight-wavefront tiles, and takes
+//     exactly half of a CU's LDS: two workgroups that no barrier ties together share a CU, one multiplies while the
+//     other starts, ends or waits, and a launch ends at half tiles.  Against 256x256 on eight wavefronts (same loop, 152 KB;
+//     kernel times, us): 4096 rows 2048x2048 bf16 46.5 -> 35.9, 2048 rows 4096 -> 11008 int8 with r = 64 111.1 -> 98.7, 13032 rows
+//     4096 -> 1472 bf16 184.6 -> 155.3, 8192 rows 2048x2048 59.6 -> 58.7; over 347 products 1.13 x, 0.93 x at worst (282
+//     tiles: 26 CUs have two, the others one).  Where both fill the chip alike the matrix clock decides, which is the same.
 // A wait on asm-issued reads names the registers it releases ("+v"), which orders their uses after it.
 // ---------------------------------------------------------------------------------------------
 #define PQ_DS_READ128(dst, addr, off) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(off) : "memory")
@@ -308,10 +158,10 @@ struct pq_frag_set {
 // ---------------------------------------------------------------------------------------------
 // One workgroup computes a BM x BN tile over the contraction range [z*kchunk, (z+1)*kchunk), z = blockIdx.y.
 // DUAL: two problems of the same sizes (mode 3), blockIdx.z selects (an instantiation of its own: the test turns kernel
-// arguments into run-time selections).  FAST: whole tiles (no validity masks in the register-staged second contraction); TAIL: the contraction may end inside a step
-// (an instantiation of its own: the registers its addresses take are spills elsewhere).
-template <int BM, int BN, int WGM, int WGN, int KB, bool FAST, bool TAIL, bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1, bool DUAL = false>
-__global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N, int K, pq_operand A,
+// arguments into run-time selections).  WHOLE: whole tiles (bf16 rows are stored without a look at the edges); TAIL: the contraction
+// may end inside a step (an instantiation of its own: the registers its addresses take are spills elsewhere).
+template <int BM, int BN, int WGM, int WGN, int KB, bool WHOLE, bool TAIL, bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1, bool DUAL = false>
+__global__ __launch_bounds__(WGM * WGN * 64, 2) void mfma_gemm_kernel(int M, int N, int K, pq_operand A,
                                                                      pq_operand B, pq_epilogue epi,
                                                                      int nbn, int total_tiles, int kchunk,
                                                                      float* splitk_part, pq_gemm_group grp,
@@ -323,13 +173,14 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
   constexpr int STAGE = (BM + BN) * KB;
   using acc_t = typename std::conditional<INT8, i32x16_t, f32x16_t>::type;
 
-  // A packed-bit B operand stays packed in LDS (three buffers of
-  // 32 bytes per row), which leaves room for a ring of four stages of the A operand.
+  // A packed-bit B operand stays packed in LDS (two buffers of 32 bytes per row), which leaves room for a ring of four stages
+  // of the A operand: 80 KB with BM = 128, half of what a CU has, so the epilogue's few values lie where the bits were.
   constexpr bool BBITS = BKIND == PQ_SRC_BITS8 || BKIND == PQ_SRC_BITS16;
-  constexpr int SMEM_BYTES = BBITS ? 4 * BM * KB + 3 * BN * 32 : 2 * STAGE;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM_BYTES];
-  __shared__ double red[NT / 64];
-  __shared__ float rowscale[BM];                     // per-row scale of the tile (one division per row, not per element)
+  constexpr int SMEM_BYTES = BBITS ? 4 * BM * KB + 2 * BN * 32 : 2 * STAGE;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM_BYTES + (BBITS ? 0 : 8 * (NT / 64) + 4 * BM)];
+  unsigned char* const side = smem + (BBITS ? 4 * BM * KB : SMEM_BYTES);
+  double* const red = (double*)side;
+  float* const rowscale = (float*)(side + 8 * (NT / 64));   // per-row scale of the tile (one division per row, not per element)
 
   // XCD-aware tile order: consecutive workgroups go to different XCDs, so give each XCD a
   // contiguous range of tiles (its L2 then sees the same A row-panel for a run of tiles).
@@ -385,19 +236,50 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
 
   const int nkt = ke > kb ? (ke - kb + EPB - 1) / EPB : 0;
   constexpr int NKS = KB / 32;   // MFMA issues along the contraction per LDS stage
-  // Streaming loop with a fused second contraction of one or two 64-element steps: its operand tiles (32 KB each:
-  // A2 step 0, B2 step 0, A2 step 1, B2 step 1) ride in on the ring's last four refills, which the main loop no longer
-  // needs, instead of being requested after it (a chain of four memory latencies in front of 64 MFMAs per wavefront).
-  // Tile j goes to ring stage (pf2_s0 + j) mod 4.
-  bool pf2 = false;                                  // uniform
-  [[maybe_unused]] const int pf2_s0 = nkt & 3;
-  if constexpr (BBITS && AK2 == PQ_SRC_KC16 && (BK2 == PQ_SRC_KC16 || BK2 == PQ_SRC_KS16)) {
-#ifndef PQ_NO_PF2
-    pf2 = ph2.K2 > 0 && ph2.K2 <= 128 && ph2.K2 % 64 == 0 && nkt >= 4 && ((uintptr_t)ph2.A2.p % 16) == 0 && (ph2.A2.ld * 2) % 16 == 0 &&
-          ((uintptr_t)ph2.B2.p % 16) == 0 && (ph2.B2.ld * 2) % 16 == 0 && (BK2 != PQ_SRC_KS16 || N % 8 == 0);
+  constexpr bool PH2 = (AK2 >= 0);
+  static_assert(!PH2 || (BBITS && AK2 == PQ_SRC_KC16 && (BK2 == PQ_SRC_KC16 || BK2 == PQ_SRC_KS16)), "a second contraction rides in the ring of four");
+  // A fused second contraction (K2 long, 64 to a step) comes in pieces of 16 KB, a ring stage each: 3 s: A2 of step s, 3 s + 1 and
+  // 3 s + 2: the halves of its B2 (columns of a contraction-contiguous B2, contraction rows of a strided one).  Pieces 0 to 3 take
+  // the ring's last four refills, which the main loop no longer needs, instead of being requested after it; piece j goes to
+  // ring stage (nkt + j) mod 4.  Chunks past the end of K2 come from the page of zeros, in both operands.
+  [[maybe_unused]] const int nk2 = PH2 ? (ph2.K2 + 63) >> 6 : 0;
+  [[maybe_unused]] auto issue_ph2 = [&](int j, int stage) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (PH2) {
+      const int s2 = j / 3, part = j - 3 * s2, k2 = s2 * 64;
+      if (k2 >= ph2.K2) return;                      // uniform
+      const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+      unsigned char* base = smem + stage * (BM * KB) + w * 4096;
+      // the addresses are formed here, from opaque copies, so that nothing of them stays in registers across the main loop
+      int ln = threadIdx.x & 63;
+      asm volatile("" : "+v"(ln));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int qi = w * 4 + i;
+        const char* g;
+        int pos;
+        if (part == 0 || BK2 != PQ_SRC_KS16) {
+          const pq_operand& op = part ? ph2.B2 : ph2.A2;
+          const int row0 = part ? n0 + (part - 1) * 128 : m0, rows = part ? N : M;
+          const int r = qi * 8 + (ln >> 3), pc = ln & 7;
+          const int c = pc ^ ((r ^ (r >> 3)) & 7);
+          const int grow = min(row0 + r, rows - 1);
+          g = (const char*)op.p + ((size_t)grow * op.ld + k2) * 2 + c * 16;
+          pos = k2 + c * 8;
+        } else {
+          const int t = (part - 1) * 32 + qi * 2 + (ln >> 5), pc = ln & 31;
+          const int c = pc ^ (4 * (t & 3));
+          int col = n0 + c * 8;
+          if (col + 8 > N) col = n0;
+          g = (const char*)ph2.B2.p + ((size_t)(k2 + t) * ph2.B2.ld + col) * 2;
+          pos = k2 + t;
+        }
+        if (pos >= ph2.K2) g = (const char*)pq_zero_page;
+        __builtin_amdgcn_global_load_lds(g, PQ_LDS_PTR(base + i * 1024), 16, 0, 0);
+      }
+    }
 #endif
-  }
-
+  };
   // per-thread LDS read offsets of the MFMA operand fragments (row part and swizzle part)
   int a_rb[TM], a_fx[TM], b_rb[TN], b_fx[TN];
 #pragma unroll
@@ -412,18 +294,9 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
     b_rb[j] = BM * KB + (lds_off<KB>(r, 0) & ~(KB - 1));
     b_fx[j] = (lds_off<KB>(r, 0) & (KB - 1)) >> 4;
   }
-  uint4 af[2][TM], bf[2][TN];
-  auto read_frags = [&](const unsigned char* stage, int ks, uint4* fa, uint4* fb) {
-    const int ch = 2 * ks + (lane >> 5);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) fa[i] = *reinterpret_cast<const uint4*>(stage + a_rb[i] + ((ch ^ a_fx[i]) << 4));
-#pragma unroll
-    for (int j = 0; j < TN; ++j) fb[j] = *reinterpret_cast<const uint4*>(stage + b_rb[j] + ((ch ^ b_fx[j]) << 4));
-  };
-
   {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the kernel's signature (LDS address-space casts are device-only)
-    static_assert(BM == 256 && BN == 256 && WGM == 2 && WGN == 4 && KB == 128, "streaming loop: 256x256 tile on 8 wavefronts");
+    static_assert(BM == (BBITS ? 128 : 256) && BM == 128 * WGM && BN == 256 && WGN == 4 && KB == 128, "streaming loop: wavefront tiles of 128x64");
     constexpr bool ATR = (AK == PQ_SRC_KS16), BTR = (BKIND == PQ_SRC_KS16);
     constexpr bool BREG = BBITS;                      // B stays packed in LDS and is expanded per fragment
     constexpr int IPW = BREG ? 4 : 8;                 // 16-byte direct-load instructions per wavefront and stage
@@ -431,7 +304,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
     constexpr int STG = BREG ? BM * KB : STAGE;       // bytes per ring stage
     constexpr int RB = INT8 ? 16 : 8;                 // bytes of packed bits per B row and step
     constexpr int CH = 32 / RB;                       // steps covered by a 32-byte chunk of a packed row
-    constexpr int BITS0 = NSTAGE * BM * KB;           // LDS offset of the three chunk buffers [256 rows][32 B]
+    constexpr int BITS0 = NSTAGE * BM * KB;           // LDS offset of the two chunk buffers [256 rows][32 B]
     constexpr int AES = (AK == PQ_SRC_KC8) ? 1 : 2, BES = (BKIND == PQ_SRC_KC8) ? 1 : 2;
     const int wv = __builtin_amdgcn_readfirstlane(wave);
     const uint32_t lds0 = (uint32_t)(size_t)smem;
@@ -491,34 +364,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
       for (int i = 0; i < IPW; ++i)
         __builtin_amdgcn_global_load_lds(src[i] + (size_t)kt * adv, PQ_LDS_PTR(base + i * 1024), 16, 0, 0);
     };
-    // tile j of the second contraction (step j >> 1; even: A2, odd: B2) into a ring stage, in the layouts of the
-    // loaders above; the addresses are formed here, in the four steps that use them, not kept across the loop
-    auto issue_ph2 = [&](int j, int stage) {
-      if constexpr (AK2 >= 0) {
-        unsigned char* base = smem + stage * STG + q0 * 1024;
-        const int k2 = (j >> 1) * 64;
-#pragma unroll
-        for (int i = 0; i < IPW; ++i) {
-          const int qi = q0 + i;
-          const char* g;
-          if (!(j & 1) || BK2 != PQ_SRC_KS16) {
-            const pq_operand& op = (j & 1) ? ph2.B2 : ph2.A2;
-            const int row0 = (j & 1) ? n0 : m0, rows = (j & 1) ? N : M;
-            const int r = qi * 8 + (lane >> 3), pc = lane & 7;
-            const int c = pc ^ ((r ^ (r >> 3)) & 7);
-            const int grow = min(row0 + r, rows - 1);
-            g = (const char*)op.p + ((size_t)grow * op.ld + k2) * 2 + c * 16;
-          } else {
-            const int t = qi * 2 + (lane >> 5), pc = lane & 31;
-            const int c = pc ^ (4 * (t & 3));
-            int col = n0 + c * 8;
-            if (col + 8 > N) col = n0;
-            g = (const char*)ph2.B2.p + ((size_t)(k2 + t) * ph2.B2.ld + col) * 2;
-          }
-          __builtin_amdgcn_global_load_lds(g, PQ_LDS_PTR(base + i * 1024), 16, 0, 0);
-        }
-      }
-    };
     // Packed bits of B: a row's bits are fetched 32 bytes (CH steps) at a time, two lanes per row, so a chunk
     // (256 rows, 8 KB) is one 16-byte load instruction per wavefront every CH steps.  Lanes 0..31 take the first
     // 16 bytes of the wavefront's 32 rows and lanes 32..63 the second, so in LDS a block of 32 rows is
@@ -530,22 +375,28 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
     const int range_bytes = (ke - kb) >> 3;
     const bool words = TAIL && (B.ld & 15) != 0;     // uniform
     auto issue_bits = [&](int chunk, int buf) {
-      if (words) {
+      constexpr int NB = 8 / (NT / 64);              // 32-row blocks per wavefront
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = min(n0 + wv * 32 + (i & 1) * 16 + (lane >> 2), N - 1);
-          int off = chunk * 32 + (i >> 1) * 16 + (lane & 3) * 4;
-          if (off + 4 > range_bytes) off = 0;
-          const char* g = (const char*)B.p + (size_t)row * B.ld + (kb >> 3) + off;
-          __builtin_amdgcn_global_load_lds(g, PQ_LDS_PTR(smem + BITS0 + buf * (BN * 32) + wv * 1024 + i * 256), 4, 0, 0);
+      for (int u = 0; u < NB; ++u) {
+        const int blk = wv * NB + u;
+        unsigned char* dst = smem + BITS0 + buf * (BN * 32) + blk * 1024;
+        if (words) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int row = min(n0 + blk * 32 + (i & 1) * 16 + (lane >> 2), N - 1);
+            int off = chunk * 32 + (i >> 1) * 16 + (lane & 3) * 4;
+            if (off + 4 > range_bytes) off = 0;
+            const char* g = (const char*)B.p + (size_t)row * B.ld + (kb >> 3) + off;
+            __builtin_amdgcn_global_load_lds(g, PQ_LDS_PTR(dst + i * 256), 4, 0, 0);
+          }
+          continue;
         }
-        return;
+        const int row = min(n0 + blk * 32 + (lane & 31), N - 1);
+        int off = chunk * 32 + (lane >> 5) * 16;
+        if (off + 16 > range_bytes) off = 0;
+        const char* g = (const char*)B.p + (size_t)row * B.ld + (kb >> 3) + off;
+        __builtin_amdgcn_global_load_lds(g, PQ_LDS_PTR(dst), 16, 0, 0);
       }
-      const int row = min(n0 + wv * 32 + (lane & 31), N - 1);
-      int off = chunk * 32 + (lane >> 5) * 16;
-      if (off + 16 > range_bytes) off = 0;
-      const char* g = (const char*)B.p + (size_t)row * B.ld + (kb >> 3) + off;
-      __builtin_amdgcn_global_load_lds(g, PQ_LDS_PTR(smem + BITS0 + buf * (BN * 32) + wv * 1024), 16, 0, 0);
     };
 
     // ---- fragment read addresses (stage 0) ------------------------------------------------------------
@@ -581,14 +432,15 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
       // ---- ring of four stages: A streams as above, B stays packed ------------------------------------
       // A step's bits of a B row (8 or 16 bytes) are read once per wavefront tile column; the operand of
       // contraction sub-step s+1 is expanded from them in registers while the MFMAs of sub-step s issue,
-      // one 4-byte piece behind each MFMA (the two wavefronts of a SIMD run in step, so a block of
-      // expansion instructions ahead of a block of MFMAs would leave the matrix pipe idle for its length).
+      // one 4-byte piece behind each MFMA (a block of expansion instructions ahead of a block of MFMAs would
+      // leave the matrix pipe idle for its length where the wavefronts of a SIMD run in step).
       // Every wavefront issues IPW direct loads of A per step, whatever the step (steps and chunks past the end
-      // re-load the last one into a place nobody reads), plus one load of bits, ahead of them, in the first
+      // re-load the last one into a place nobody reads), plus its loads of bits, ahead of them, in the last
       // step of a chunk.  At the barrier of step t at most 2 IPW loads stay in flight, which leaves A up to
-      // step t + 1 and the bits issued up to step t - 2 in LDS (when a load of bits is among the last 2 IPW,
-      // the wait merely covers one more load of A).  Chunk c is issued in the first step of chunk c - 2 and
-      // goes to buffer c mod 3, whose previous content (chunk c - 3) was last read one barrier earlier.
+      // step t + 1 and the bits issued up to step t - 2 in LDS (when loads of bits are among the last 2 IPW,
+      // the wait merely covers more loads of A).  Chunk c is issued behind the barrier of the last step of chunk
+      // c - 2, from where on nobody reads that chunk, into its buffer, c mod 2; it is first read behind the
+      // barrier of the last step of chunk c - 1, two steps later at least.
       static_assert(!ATR, "packed B goes with a contraction-contiguous A");
       using bits_t = typename std::conditional<INT8, i32x4_t, pq_i32x2>::type;
       struct aset {
@@ -697,7 +549,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
         const uint32_t sn = (uint32_t)stn * STG;
         const bool wrap = (part == CH - 1);
         const int partn = wrap ? 0 : part + 1;
-        const int bufn = wrap ? (buf == 2 ? 0 : buf + 1) : buf;
+        const int bufn = wrap ? buf ^ 1 : buf;
         PQ_SETPRIO(2);
         read_a(G1, c1{}, so);
         G0.wait4();
@@ -716,9 +568,9 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
         asm volatile("s_barrier" ::: "memory");
         PQ_STAMP(trace_slot, wv, kt, 1);
         PQ_SETPRIO(3);
-        if (part == 0) issue_bits(min(chunk + 2, nch - 1), buf == 0 ? 2 : buf - 1);   // (buf + 2) mod 3
-        // refill the stage just read: with the step four ahead, or, once there is none, with a tile of the second contraction
-        if (pf2 && kt + NSTAGE >= nkt && kt + NSTAGE - nkt < (ph2.K2 >> 5)) issue_ph2(kt + NSTAGE - nkt, st);
+        if (wrap) issue_bits(min(chunk + 2, nch - 1), buf);   // everybody is done with this chunk
+        // refill the stage just read: with the step four ahead, or, once there is none, with a piece of the second contraction
+        if (PH2 && nk2 > 0 && nkt >= NSTAGE && kt + NSTAGE >= nkt) issue_ph2(kt + NSTAGE - nkt, st);
         else issue(min(kt + NSTAGE, nkt - 1), st);
         read_bits((uint32_t)(bufn * (BN * 32) + ((partn * RB) >> 4) * 512 + ((partn * RB) & 15)));   // past the last step: a place nobody uses
         read_a(G0, c0{}, sn);
@@ -829,22 +681,18 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
   }
   __syncthreads();  // all MFMA operand reads are done: LDS is reused below
 
-  // Optional second contraction (rank-r branch): rescale the first accumulator, then run a short bf16 loop
-  // over K2 into the same tile.  The first operand tiles are requested before the rescale arithmetic and the
-  // tiles of step s+1 before the MFMAs of step s (two LDS stages), so the memory latencies overlap with work
-  // instead of standing in a row.
-  constexpr bool PH2 = (AK2 >= 0);
+  // Optional second contraction (rank-r branch): rescale the first accumulator, then a short bf16 loop over K2 into the same
+  // tile.  The pieces of its first step (and A2 of the second) already sit in the ring; what a third and later steps need is
+  // requested when the one before has been read, and the other workgroup of the CU has the matrix pipe meanwhile.
   constexpr bool ACC_INT = INT8 && !PH2;
   f32x16_t accf[PH2 ? TM : 1][PH2 ? TN : 1];
   if constexpr (PH2) {
-    constexpr int KS2 = KB / 2;                      // contraction elements per step
-    tile_stage<AK2, BM, NT, KB, FAST> sa2;
-    tile_stage<BK2, BN, NT, KB, FAST> sb2;
-    sa2.setup(ph2.A2, m0, M, tid);
-    sb2.setup(ph2.B2, n0, N, tid);
-    // the first A2 tile (activation-sized, far away) is requested before the rescale arithmetic, the first B2 tile
-    // (a small factor, cache-resident) after it: holding both across the rescale overflows the register file
-    if (ph2.K2 > 0 && !pf2) sa2.load(ph2.A2, 0, ph2.K2);
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef short v4s_t __attribute__((ext_vector_type(4)));
+    if (nkt < 4) {                                   // uniform: the loop had no refills to spare
+#pragma unroll
+      for (int j = 0; j < 4; ++j) issue_ph2(j, (nkt + j) & 3);
+    }
     const float sc1 = ph2.dev_scale1 ? __fmul_rn(ph2.scale1, *ph2.dev_scale1) : ph2.scale1;
     if (ph2.row_div1) {                              // uniform: one divisor load and one division per row of the tile
       for (int r = tid; r < BM; r += NT) rowscale[r] = sc1 / ph2.row_div1[min(m0 + r, M - 1)];
@@ -861,69 +709,54 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
           accf[i][j][v] = (float)e1 * sr;
         }
     }
-    if (pf2) {
-#if defined(__HIP_DEVICE_COMPILE__)
-      // both operands of every step already sit in the ring (all loads were waited for after the main loop)
-      typedef short v4s_t __attribute__((ext_vector_type(4)));
-      const int hh = lane >> 5;
-      for (int s2 = 0; s2 < (ph2.K2 >> 6); ++s2) {
-        const unsigned char* ta = smem + ((pf2_s0 + 2 * s2) & 3) * (BM * KB);
-        const unsigned char* tb = smem + ((pf2_s0 + 2 * s2 + 1) & 3) * (BM * KB);
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
-          const int ch = 2 * ks + hh;
-          uint4 fa[TM], fb[TN];
-#pragma unroll
-          for (int i = 0; i < TM; ++i) fa[i] = *reinterpret_cast<const uint4*>(ta + a_rb[i] + ((ch ^ a_fx[i]) << 4));
-#pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            if constexpr (BK2 == PQ_SRC_KS16) {
-              // [64 contraction rows][256 columns] as it lies in memory, 16-byte chunks of a row swizzled by the row:
-              // two transposing reads (rows 16 ks + 8 h + (0..3), then + 4) make the operand of 8 contraction indices
-              const int tl = 8 * hh + ((lane & 15) >> 2), cl = 16 * ((lane >> 4) & 1) + 4 * (lane & 3), sw = 4 * ((lane & 15) >> 2);
-              const int col = wn0 + 32 * j + cl;
-              const unsigned char* pb = tb + ks * 8192 + tl * 512 + (((col >> 3) ^ sw) << 4) + (col & 7) * 2;
-              const v4s_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s_t*)(pb));
-              const v4s_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s_t*)(pb + 2048));
-              const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-              fb[j] = make_uint4(l2.x, l2.y, h2.x, h2.y);
-            } else {
-              fb[j] = *reinterpret_cast<const uint4*>(tb + (b_rb[j] - BM * KB) + ((ch ^ b_fx[j]) << 4));
-            }
-          }
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-              accf[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fb[j]), __builtin_bit_cast(bf16x8_t, fa[i]),
-                                                                   accf[i][j], 0, 0, 0);
-        }
+    const int hh = lane >> 5;
+    auto piece = [&](int j) { return smem + ((nkt + j) & 3) * (BM * KB); };
+    for (int s2 = 0; s2 < nk2; ++s2) {
+      if (s2 > 0) {
+        // both halves of this step's B2, and the next one's A2 where that of the step before was
+        __syncthreads();
+        issue_ph2(3 * s2 + 1, (nkt + 1) & 3);
+        issue_ph2(3 * s2 + 2, (nkt + 2) & 3);
+        if (s2 + 1 < nk2) issue_ph2(3 * s2 + 3, (nkt + (s2 & 1 ? 0 : 3)) & 3);
       }
-#endif
-    }
-    if (ph2.K2 > 0 && !pf2) sb2.load(ph2.B2, 0, ph2.K2);
-    int st2 = 0;
-    for (int k2 = 0; k2 < (pf2 ? 0 : ph2.K2); k2 += KS2) {
-      unsigned char* stage = smem + st2 * STAGE;
-      sa2.store(stage, tid);
-      sb2.store(stage + BM * KB, tid);
-      const int kn = (k2 + KS2 < ph2.K2) ? k2 + KS2 : k2;   // the last step re-requests itself (harmless, never stored)
-      sa2.load(ph2.A2, kn, ph2.K2);
-      sb2.load(ph2.B2, kn, ph2.K2);
-      __syncthreads();                               // this stage is complete; the other one is free again
-      read_frags(stage, 0, af[0], bf[0]);
+      if (s2 > 0 || nkt < 4) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+      }
+      const unsigned char* ta = piece(s2 & 1 ? 3 : 0);
 #pragma unroll
-      for (int ks = 0; ks < NKS; ++ks) {             // the fragments of sub-step ks + 1 are read under the MFMAs of sub-step ks
-        if (ks + 1 < NKS) read_frags(stage, ks + 1, af[(ks + 1) & 1], bf[(ks + 1) & 1]);
+      for (int ks = 0; ks < NKS; ++ks) {
+        const int ch = 2 * ks + hh;
+        uint4 fa[TM], fb[TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[i] = *reinterpret_cast<const uint4*>(ta + a_rb[i] + ((ch ^ a_fx[i]) << 4));
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          if constexpr (BK2 == PQ_SRC_KS16) {
+            // [64 contraction rows][256 columns] as it lies in memory, 16-byte chunks of a row swizzled by the row:
+            // two transposing reads (rows 16 ks + 8 h + (0..3), then + 4) make the operand of 8 contraction indices
+            const int tl = 8 * hh + ((lane & 15) >> 2), cl = 16 * ((lane >> 4) & 1) + 4 * (lane & 3), sw = 4 * ((lane & 15) >> 2);
+            const int col = wn0 + 32 * j + cl;
+            const unsigned char* pb = piece(1 + (ks >> 1)) + (ks & 1) * 8192 + tl * 512 + (((col >> 3) ^ sw) << 4) + (col & 7) * 2;
+            const v4s_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s_t*)(pb));
+            const v4s_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s_t*)(pb + 2048));
+            const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+            fb[j] = make_uint4(l2.x, l2.y, h2.x, h2.y);
+          } else {
+            // [256 columns][128 B], 128 columns to a piece
+            const int r = (wn0 & 127) + 32 * j + (lane & 31), o = lds_off<KB>(r, 0);
+            fb[j] = *reinterpret_cast<const uint4*>(piece(1 + (wn0 >> 7)) + (o & ~(KB - 1)) + ((ch ^ ((o & (KB - 1)) >> 4)) << 4));
+          }
+        }
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int j = 0; j < TN; ++j)
-            accf[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, bf[ks & 1][j]),
-                                                                 __builtin_bit_cast(bf16x8_t, af[ks & 1][i]), accf[i][j], 0, 0, 0);
+            accf[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fb[j]), __builtin_bit_cast(bf16x8_t, fa[i]),
+                                                                 accf[i][j], 0, 0, 0);
       }
-      st2 ^= 1;
     }
+#endif
     __syncthreads();
   }
   // Epilogue: in a 32x32 accumulator block lane l holds row (l & 31) and, per group g = v >> 2, the four columns
@@ -943,7 +776,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
 #ifdef PQ_NO_STAGE
   constexpr bool CAN_STAGE = false;
 #else
-  constexpr bool CAN_STAGE = (BM == 256 && BN == 256 && SMEM_BYTES >= 8 * 16384);
+  constexpr bool CAN_STAGE = SMEM_BYTES >= (NT / 64) * 16384;
 #endif
   // (store limits: fp32 outputs only, where a 16-byte chunk is four columns and the column limit a multiple of four)
   const bool staged = CAN_STAGE && (slab || ((epi.out_kind == PQ_OUT_F32 || (epi.out_kind == PQ_OUT_BF16 && epi.m_limit == 0 && epi.n_limit == 0)) &&
@@ -1013,7 +846,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void mfma_gemm_kernel(int M, int N,
           const int rl = it * 8 + (lane_e >> 3), c = lane_e & 7;
           const uint4 v = *reinterpret_cast<const uint4*>(wreg + rl * 128 + ((c ^ (rl & 7)) << 4));
           const int m = m0 + wm0_e + rl, n = n0 + wn0_e + c * 8;
-          if (m < M && n < N) *reinterpret_cast<uint4*>(outp + (size_t)m * ldo + (size_t)n * 2) = v;
+          if (WHOLE || (m < M && n < N)) *reinterpret_cast<uint4*>(outp + (size_t)m * ldo + (size_t)n * 2) = v;
         }
       } else {
 #pragma unroll
@@ -1378,7 +1211,7 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
 #endif
 }
 
-template <int BM, int BN, int WGM, int WGN, int KB, bool FAST, bool TAIL, bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1, bool DUAL = false>
+template <int BM, int BN, int WGM, int WGN, int KB, bool WHOLE, bool TAIL, bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1, bool DUAL = false>
 int launch_mfma(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B,
                 const pq_epilogue& epi, hipStream_t s, float* part, const pq_gemm_group& grp, const pq_phase2& ph2,
                 const pq_gemm_second* second = nullptr) {
@@ -1387,7 +1220,7 @@ int launch_mfma(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A
   const int nbn = (N + BN - 1) / BN;
   const int tiles = nbm * nbn;
   dim3 grid(tiles, pl.splits, DUAL ? 2 : 1), block(WGM * WGN * 64);
-  mfma_gemm_kernel<BM, BN, WGM, WGN, KB, FAST, TAIL, INT8, AK, BKIND, AK2, BK2, DUAL><<<grid, block, 0, s>>>(
+  mfma_gemm_kernel<BM, BN, WGM, WGN, KB, WHOLE, TAIL, INT8, AK, BKIND, AK2, BK2, DUAL><<<grid, block, 0, s>>>(
       M, N, K, A, B, epi, nbn, tiles, pl.kchunk, pl.splits > 1 ? part : nullptr, grp, ph2, second_arg<DUAL>(second));
   PQ_CHECK_LAUNCH("mfma_gemm_kernel");
   return PQ_OK;
@@ -1397,7 +1230,7 @@ template <bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1>
 int launch_mfma_cfg(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B,
                     const pq_epilogue& epi, hipStream_t s, float* part, const pq_gemm_group& grp, const pq_phase2& ph2,
                     const pq_gemm_second* second = nullptr) {
-  if (pl.bm != 256) return pq_launch_tile(pl, M, N, K, A, B, epi, s, part, grp, ph2, second);
+  if (pl.bn != 256) return pq_launch_tile(pl, M, N, K, A, B, epi, s, part, grp, ph2, second);
   // rows of 16-byte chunks on 16-byte boundaries, as every width and section of this library has them
   const long aes = AK == PQ_SRC_KC8 ? 1 : 2, bes = BKIND == PQ_SRC_KC8 ? 1 : 2;
   constexpr bool bits = BKIND == PQ_SRC_BITS8 || BKIND == PQ_SRC_BITS16;
@@ -1423,17 +1256,23 @@ int launch_mfma_cfg(const pq_gemm_plan& pl, int M, int N, int K, const pq_operan
     // whole steps (packed rows of whole 16 bytes): no tail to look for; whole tiles too: no validity masks in the second contraction
     constexpr int EPB = INT8 ? 128 : 64;
     const bool steps = K % EPB == 0 && pl.kchunk % EPB == 0 && (!bits || B.ld % 16 == 0);
-    const bool tiles = grp.mode == 0 && M % 256 == 0 && N % 256 == 0 && ph2.K2 % 64 == 0;
-    if constexpr (AK == PQ_SRC_KC8 && BKIND == PQ_SRC_BITS8 && AK2 < 0) {
-      if (grp.mode == 3) {
-        if (steps) return launch_mfma<256, 256, 2, 4, 128, false, false, INT8, AK, BKIND, AK2, BK2, true>(pl, M, N, K, A, B, epi, s, part, grp, ph2, second);
-        return launch_mfma<256, 256, 2, 4, 128, false, true, INT8, AK, BKIND, AK2, BK2, true>(pl, M, N, K, A, B, epi, s, part, grp, ph2, second);
-      }
+    if constexpr (bits) {
+      if (grp.mode != 0 && grp.mode != 3) return pq_set_error(PQ_ERR_BAD_ARG, "no grouped kernel for packed signs");
+      const bool whole = grp.mode == 0 && steps && M % 128 == 0 && N % 256 == 0;
+      if constexpr (AK == PQ_SRC_KC8 && AK2 < 0)
+        if (grp.mode == 3) {
+          if (steps) return launch_mfma<128, 256, 1, 4, 128, false, false, INT8, AK, BKIND, AK2, BK2, true>(pl, M, N, K, A, B, epi, s, part, grp, ph2, second);
+          return launch_mfma<128, 256, 1, 4, 128, false, true, INT8, AK, BKIND, AK2, BK2, true>(pl, M, N, K, A, B, epi, s, part, grp, ph2, second);
+        }
+      if (grp.mode == 3) return pq_set_error(PQ_ERR_BAD_ARG, "no paired 128x256 kernel for these operand kinds");
+      if (whole) return launch_mfma<128, 256, 1, 4, 128, true, false, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+      if (steps) return launch_mfma<128, 256, 1, 4, 128, false, false, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+      return launch_mfma<128, 256, 1, 4, 128, false, true, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+    } else {
+      if (grp.mode == 3) return pq_set_error(PQ_ERR_BAD_ARG, "no paired 256x256 kernel for these operand kinds");
+      if (steps) return launch_mfma<256, 256, 2, 4, 128, false, false, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
+      return launch_mfma<256, 256, 2, 4, 128, false, true, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
     }
-    if (grp.mode == 3) return pq_set_error(PQ_ERR_BAD_ARG, "no paired 256x256 kernel for these operand kinds");
-    if (steps && tiles) return launch_mfma<256, 256, 2, 4, 128, true, false, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
-    if (steps) return launch_mfma<256, 256, 2, 4, 128, false, false, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
-    return launch_mfma<256, 256, 2, 4, 128, false, true, INT8, AK, BKIND, AK2, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
   }
 }
 
@@ -1854,9 +1693,14 @@ int pq_launch_skinny(int M, int K, const pq_operand& A, const pq_operand& B, con
 //   128x128: 6 + 0.76 per step alone on a CU (int8 0.85), 0.58 c (0.61) when two workgroups share it, + 2.4 per further workgroup
 //   256x256: c (9.5 + 1.38 per step); split only while the tiles are at most half of the CUs: beyond that more active CUs
 //            lower the clock instead
+//   128x256, packed signs: 6 + 0.7 per step alone on a CU (int8 6.5 + 0.8; up to 0.12 more as the CUs fill up), u workgroups to a
+//            CU 6 + 0.75 u per step (0.83 u) + 3 per workgroup behind the first.  These times count from 1024 columns or 192 tiles on,
+//            512 rows and four steps; narrower and shorter outputs, where the two sizes of tiles measured 0.98-1.24 x
+//            of each other either way, take it where 256x256 would have been the choice
 //   a split: its slabs written at 10 TB/s (the caches take part of them), then 2 + slabs and result at 7 TB/s, at least 4
 // Fitted to 997 timings of 141 shapes (64 to 16384 rows, 16 to 8192 columns, contractions of 16 to 8192; int8, bf16 and
-// packed-sign operands): the tile and split these pick are 1 to 3 % slower than the fastest of all, averaged over the shapes.
+// packed-sign operands): the tile and split these pick are 1 to 3 % slower than the fastest of all, averaged over the shapes;
+// 128x256 to 347 timings of its own (1.4 %) and 60 of split ones (1.6 %, with 4 us more for the second launch).
 // (2048 x 2048 outputs over 2048 / 8192 tokens: 64x64 37 / 126, 128x128 35 / 109, 256x256 in four splits 43 / 82 with the
 // reduction; 765 x 672 over 672: 7, 13, 22.)
 static double est_tile(int bm, long wgs, long steps, bool int8) {
@@ -1871,27 +1715,40 @@ static double est_reduce(int splits, double elems) {
   return 4.0 * splits * elems / 1.0e7 + (t > 4.0 ? t : 4.0);
 }
 
-static pq_gemm_plan plan_search(int M, int N, int K, bool int8, bool may_split) {
+// Packed signs on 128x256 tiles: n tiles, two to a CU at a time.
+static double est_signs(long n, long steps, bool int8) {
+  const double u = (double)((n + 255) / 256);
+  if (u == 1.0) return (int8 ? 6.5 + 0.8 * steps : 6.0 + 0.7 * steps) + (n > 128 ? 0.12 * (n - 128) / 128.0 * steps : 0.0);
+  return 6.0 + u * steps * (int8 ? 0.83 : 0.75) + 3.0 * (u - 1.0);
+}
+
+static pq_gemm_plan plan_search(int M, int N, int K, bool int8, bool may_split, bool signs) {
   pq_gemm_plan pl;
   memset(&pl, 0, sizeof(pl));
-  pl.bm = 64;
+  pl.bm = pl.bn = 64;
   pl.splits = 1;
   pl.kchunk = K > 0 ? K : 1;
   const int epb = int8 ? 128 : 64;
+  auto tiles_of = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  const long t256 = tiles_of(256, 256);
+  // 128x256 tiles of packed signs by their own times from 1024 columns or 192 tiles on (512 rows and four steps at least)
+  const bool wide = M >= 512 && K > 3 * epb && (N >= 1024 || tiles_of(128, 256) >= 192);
   double best = 1e30;
-  for (int bm = 64; bm <= 256; bm *= 2) {
-    if (bm == 256 && !(M >= 256 && N >= 256)) continue;
-    const long tiles = (long)((M + bm - 1) / bm) * ((N + bm - 1) / bm);
+  for (int c = 64; c <= 256; c *= 2) {
+    if (c == 256 && !(M >= 256 && N >= 256)) continue;
+    const int bm = (c == 256 && signs) ? 128 : c;
+    const long tiles = tiles_of(bm, c);
     for (int want = 1; want <= 16; ++want) {
-      if (want > 1 && (!may_split || K / want < 256 || tiles * want > 1024 || (bm == 256 && (int8 || tiles > 128)))) break;
+      if (want > 1 && (!may_split || K / want < 256 || tiles * want > 1024 || (c == 256 && (int8 || t256 > 128)))) break;
       const int chunk = want == 1 ? (K > 0 ? K : 1) : ((K + want - 1) / want + 255) / 256 * 256;   // whole 128-byte steps, at least two
       const int sp = want == 1 ? 1 : (K + chunk - 1) / chunk;
-      const double t = est_tile(bm, tiles * sp, (chunk + epb - 1) / epb, int8) + est_reduce(sp, (double)M * N);
-      if (t < best) { best = t; pl.bm = bm; pl.splits = sp; pl.kchunk = chunk; }
+      const long steps = (chunk + epb - 1) / epb;
+      const double t = (bm != c && wide ? est_signs(tiles * sp, steps, int8) + (sp > 1 ? 4.0 : 0.0) : est_tile(c, (c == 256 ? t256 : tiles) * sp, steps, int8)) +
+                       est_reduce(sp, (double)M * N);
+      if (t < best) { best = t; pl.bm = bm; pl.bn = c; pl.splits = sp; pl.kchunk = chunk; }
     }
   }
-  pl.bn = pl.bm;
-  const long tiles = (long)((M + pl.bm - 1) / pl.bm) * ((N + pl.bn - 1) / pl.bn);
+  const long tiles = tiles_of(pl.bm, pl.bn);
   pl.red_blocks = pl.splits > 1 ? (int)(((size_t)M * (N / 8) + 255) / 256) : (int)tiles;
   pl.ws_bytes = pl.splits > 1 ? (size_t)pl.splits * M * N * sizeof(float) : 0;
   pl.us = best;
@@ -1899,18 +1756,18 @@ static pq_gemm_plan plan_search(int M, int N, int K, bool int8, bool may_split) 
 }
 // The search is a pure function of its arguments and takes up to a microsecond; a call asks for a dozen plans (sizes of its
 // sections, then the launches), most of them the ones it asked for before: the last answers are kept per thread.
-static pq_gemm_plan pq_plan_gemm_impl(int M, int N, int K, bool int8, bool may_split) {
+static pq_gemm_plan pq_plan_gemm_impl(int M, int N, int K, bool int8, bool may_split, bool signs) {
   struct entry { int M, N, K, flags; pq_gemm_plan pl; };
   static thread_local entry cache[64];               // (zeroed: no plan has M = 0, see below)
-  const int flags = (int8 ? 1 : 0) | (may_split ? 2 : 0);
-  if (M <= 0) return plan_search(M, N, K, int8, may_split);
+  const int flags = (int8 ? 1 : 0) | (may_split ? 2 : 0) | (signs ? 4 : 0);
+  if (M <= 0) return plan_search(M, N, K, int8, may_split, signs);
   const uint32_t hsh = ((uint32_t)M * 2654435761u) ^ ((uint32_t)N * 2246822519u) ^ ((uint32_t)K * 3266489917u) ^ ((uint32_t)flags * 668265263u);
   entry& e = cache[(hsh ^ (hsh >> 15)) & 63u];
-  if (e.M != M || e.N != N || e.K != K || e.flags != flags) e = entry{M, N, K, flags, plan_search(M, N, K, int8, may_split)};
+  if (e.M != M || e.N != N || e.K != K || e.flags != flags) e = entry{M, N, K, flags, plan_search(M, N, K, int8, may_split, signs)};
   return e.pl;
 }
-pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8, bool split_int8) {
-  return pq_plan_gemm_impl(M, N, K, int8, !int8 || split_int8);
+pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8, bool split_int8, bool signs) {
+  return pq_plan_gemm_impl(M, N, K, int8, !int8 || split_int8, signs);
 }
 
 static int check_scratch(size_t need, const pq_scratch& sk) {
@@ -2023,7 +1880,8 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
 
 // Two products of the same sizes, kinds and epilogue but for C and the device scale (U and G of the FFN; dW_up and dW_gate) in
 // one launch: one start and one tail instead of two, and together they fill the chip where each alone does not.
-pq_gemm_plan pq_plan_dual(int M, int N, int K, bool int8) { return pq_plan_gemm_impl(2 * M, N, K, int8, true); }
+// (int8: U and G, with packed signs; otherwise dW_up and dW_gate)
+pq_gemm_plan pq_plan_dual(int M, int N, int K, bool int8) { return pq_plan_gemm_impl(2 * M, N, K, int8, true, int8); }
 int pq_launch_gemm_dual(int M, int N, int K, const pq_operand& A0, const pq_operand& B0, const pq_epilogue& e0, const pq_operand& A1,
                         const pq_operand& B1, void* C1, const float* dev_scale1, hipStream_t s, int prof_label, pq_scratch sk) {
   if (M <= 0 || N <= 0) return PQ_OK;
@@ -2037,7 +1895,7 @@ int pq_launch_gemm_dual(int M, int N, int K, const pq_operand& A0, const pq_oper
   memset(&grp, 0, sizeof(grp));
   grp.mode = 3;
   const pq_gemm_second second{A1, B1, C1, (int)e0.ldc, e0.scale, pl.splits > 1 ? part + (size_t)pl.splits * M * N : nullptr, dev_scale1,
-                              M, N, (N + pl.bm - 1) / pl.bm};
+                              M, N, (N + pl.bn - 1) / pl.bn};
   pq_phase2 ph2;
   memset(&ph2, 0, sizeof(ph2));
   {
@@ -2107,7 +1965,7 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
     return pq_launch_skinny(M, K, A, B, epi, s, prof_label);
   const int ak = A.kind, bk = B.kind;
   const bool int8 = (ak == PQ_SRC_KC8);
-  pq_gemm_plan pl = pq_plan_gemm(M, N, K, int8, epi.split_int8 != 0);
+  pq_gemm_plan pl = pq_plan_gemm(M, N, K, int8, epi.split_int8 != 0, bk == PQ_SRC_BITS8 || bk == PQ_SRC_BITS16);
   if (grp.mode) {
     pl.splits = 1;
     pl.kchunk = K > 0 ? K : 1;
@@ -2157,7 +2015,7 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
   {
     pq_prof_scope prof(prof_label, s);   // the MFMA kernel alone; a split's reduction is timed under its own label
     if (ph2.K2 > 0) {
-      if (!pq_plan_fuses(pl)) return pq_set_error(PQ_ERR_BAD_ARG, "a fused second contraction cannot be combined with a split contraction of 256x256 tiles");
+      if (!pq_plan_fuses(pl)) return pq_set_error(PQ_ERR_BAD_ARG, "a fused second contraction cannot be combined with a split contraction of 128x256 tiles");
       if (ak == PQ_SRC_KC8 && bk == PQ_SRC_BITS8 && ph2.A2.kind == PQ_SRC_KC16 && ph2.B2.kind == PQ_SRC_KC16)
         rc = launch_mfma_cfg<true, PQ_SRC_KC8, PQ_SRC_BITS8, PQ_SRC_KC16, PQ_SRC_KC16>(pl, M, N, K, A, B, epi, s, part, grp, ph2);
       else if (ak == PQ_SRC_KC16 && bk == PQ_SRC_BITS16 && ph2.A2.kind == PQ_SRC_KC16 && ph2.B2.kind == PQ_SRC_KS16)

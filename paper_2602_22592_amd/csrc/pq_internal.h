@@ -175,16 +175,17 @@ struct pq_scratch {
 };
 
 struct pq_gemm_plan {
-  int bm, bn;        // tile
+  int bm, bn;        // tile: 64x64, 128x128, 256x256, with packed signs 128x256 instead of the last
   int splits;        // contraction splits (1 = none)
   int kchunk;        // contraction elements per split
   int red_blocks;    // number of per-block partial sums written when a reduction is requested
   size_t ws_bytes;   // scratch for the split slabs
   double us;         // the time that the choice expects
 };
-pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8 = false, bool split_int8 = false);
+// signs: the B operand is packed signs (the 1-bit forward with int8, dX without)
+pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8 = false, bool split_int8 = false, bool signs = false);
 // whether a second contraction (pq_phase2) can be fused into a GEMM of this plan
-inline bool pq_plan_fuses(const pq_gemm_plan& pl) { return pl.splits == 1 || pl.bm < 256; }
+inline bool pq_plan_fuses(const pq_gemm_plan& pl) { return pl.splits == 1 || pl.bn < 256; }
 // tn: the streaming pair kernel; apart: a launch each; otherwise 64x64 tiles.  ws0, ws1: scratch of the two problems.
 struct pq_pair_plan { bool tn, apart; int splits, kchunk; size_t ws0, ws1; };
 pq_pair_plan pq_plan_pair(int K, int M0, int N0, int M1, int N1);
