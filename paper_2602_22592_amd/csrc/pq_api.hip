@@ -156,7 +156,7 @@ lin_layout make_layout(const pq_linear_desc& d) {
   const int Ti = d.tokens, Ki = d.d_in, Ni = d.d_out, ri = (int)r;
   L.n_red_a = r ? (bf16 ? pq_plan_gemm(Ti, ri, Ni).red_blocks : pq_ref_red_blocks(Ti, ri, Ni)) : 0;   // dH GEMM
   if (r && pq_skinny_blocks(Ti) > L.n_red_a) L.n_red_a = pq_skinny_blocks(Ti);   // room for the streaming rank-r kernel's partials
-  L.n_red_b = bf16 ? pq_plan_gemm(Ni, Ki, Ti).red_blocks : pq_ref_red_blocks(Ni, Ki, Ti);              // dW GEMM
+  L.n_red_b = bf16 ? pq_plan_gemm(Ni, Ki, Ti, false, false, PQ_PLAN_WGRAD).red_blocks : pq_ref_red_blocks(Ni, Ki, Ti);              // dW GEMM
   size_t sk = 0;
   const int shapes[7][3] = {{Ti, ri, Ki}, {Ti, Ni, ri}, {Ti, ri, Ni}, {Ti, Ki, ri}, {Ni, Ki, Ti}, {Ni, ri, Ti}, {ri, Ki, Ti}};
   for (const auto& sh : shapes) {
@@ -165,7 +165,8 @@ lin_layout make_layout(const pq_linear_desc& d) {
     if (b > sk) sk = b;
   }
   if (bf16) {   // the products with packed signs (forward and dX) and the paired factor gradients
-    const size_t f = pq_plan_gemm(Ti, Ni, Ki, true, true, true).ws_bytes, x = pq_plan_gemm(Ti, Ki, Ni, false, false, true).ws_bytes;
+    const size_t f = pq_plan_gemm(Ti, Ni, Ki, true, true, PQ_PLAN_SIGNS).ws_bytes,
+                 x = pq_plan_gemm(Ti, Ki, Ni, false, false, PQ_PLAN_SIGNS).ws_bytes;
     if (Ti > 0 && f > sk) sk = f;
     if (Ti > 0 && x > sk) sk = x;
     if (ri > 0 && pq_plan_pair(Ti, Ni, ri, ri, Ki).ws0 > sk) sk = pq_plan_pair(Ti, Ni, ri, ri, Ki).ws0;
@@ -511,7 +512,7 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
   // (the fused form carries beta / alpha through the tile: only while that ratio stays far from the fp32 range, otherwise
   // the two branches are scaled separately as in the Sec. 3.2 sum)
   const bool fuse_hp = bf16 && r > 0 && d->alpha != 0.0f && fabsf(d->alpha) >= 9.5367431640625e-7f * fabsf(d->beta) &&
-                       pq_plan_fuses(pq_plan_gemm(T, N, K, true, true, true));
+                       pq_plan_fuses(pq_plan_gemm(T, N, K, true, true, PQ_PLAN_SIGNS));
   if (r > 0 && !H_done)
     if (int err = launch_H(false)) return err;
   {  // 1-bit branch: Y = fl32(fl32(beta*lambda)/gamma_t) * acc   [+ alpha * H B^T when fused]
@@ -701,7 +702,7 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
     const int r2 = hp8 ? d->hp_rank : r;
     const void* dH2 = hp8 ? (const void*)(ws + L.hp8_ws + H8.dH) : dH;
     const void* A2p = hp8 ? (const void*)(cx + L.hp8 + H8.At) : hpA;
-    const bool fuse = r2 > 0 && pq_plan_fuses(pq_plan_gemm(T, K, N, false, false, true));
+    const bool fuse = r2 > 0 && pq_plan_fuses(pq_plan_gemm(T, K, N, false, false, PQ_PLAN_SIGNS));
     if (fuse) {
       pq_phase2 p2;
       p2.A2 = pq_operand{dH2, r2, PQ_SRC_KC16, nullptr};

@@ -72,7 +72,7 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   cursor w;
   L.stat = w.take(3 * 2 * sizeof(double) * 1024);
   L.n_red_a = pq_rowdot_blocks((int)S);
-  L.n_red_b = pq_plan_gemm((int)D, (int)F, (int)T).red_blocks;      // dW_down GEMM
+  L.n_red_b = pq_plan_gemm((int)D, (int)F, (int)T, false, false, PQ_PLAN_WGRAD).red_blocks;      // dW_down GEMM
   L.red_a = w.take(sizeof(double) * (size_t)L.n_red_a);
   L.red_b = w.take(sizeof(double) * (size_t)L.n_red_b);
   size_t sk = 0;
@@ -88,7 +88,7 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   }
   for (const auto& sh : {std::pair<int, int>{Fi, Di}, std::pair<int, int>{Di, Fi}})   // the products with packed signs: forward and input gradients
     for (const bool fwd : {true, false}) {
-      const size_t b = Ti > 0 ? pq_plan_gemm(Ti, sh.first, sh.second, fwd, fwd, true).ws_bytes : 0;
+      const size_t b = Ti > 0 ? pq_plan_gemm(Ti, sh.first, sh.second, fwd, fwd, PQ_PLAN_SIGNS).ws_bytes : 0;
       if (b > sk) sk = b;
     }
   {   // U and G, and dW_up and dW_gate, as one launch each

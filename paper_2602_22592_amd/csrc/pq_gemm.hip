@@ -978,7 +978,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_pair_kernel(int splits, int
 
 // ---------------------------------------------------------------------------------------------
 // Weight-gradient GEMMs (both operands bf16 with the contraction index as rows: dW = dY^T X over the tokens):
-// a 256x256 tile on FOUR wavefronts.
+// a 256x256 or 192x256 tile on FOUR wavefronts.
 // ---------------------------------------------------------------------------------------------
 // With real (non-constant) operand data the chip runs these kernels against its power limit: the shader clock of the
 // eight-wavefront kernel above falls from 2.3 GHz on all-zero operands to 1.7 GHz on normally distributed ones, and what
@@ -994,14 +994,23 @@ __global__ __launch_bounds__(256) void splitk_reduce_pair_kernel(int splits, int
 // loads of the next stage have landed (vmcnt), after it everybody's have and nobody reads the stage before the current
 // one, whose slot the new loads take.  Past the last stage the loads re-request the last one into a free slot, so the
 // counters stay uniform.
+// With 192 rows to a tile a wavefront has three blocks of A instead of four, i.e. 24 MFMAs to fourteen reads of operand blocks
+// (32 to sixteen) and 28 KB of loads a stage: 0.86 of a 256x256 stage for 0.75 of its products, worth it where the larger tile
+// leaves CUs idle (5504x2048: 176 tiles, or 232).  A's contraction rows are 384 bytes then, chunk c of row t at c ^ 4 (t >> 1 & 1).
 // The epilogue passes the accumulators through the wavefront's 32 KB of the ring, 64 rows at a time, and reads whole
 // 512-byte rows back: raw slabs of a split contraction and plain fp32 outputs leave as 16-byte stores of whole rows, every
 // other epilogue goes through epi_vec8 with eight consecutive columns per lane.
 #define PQ_MFMA_BF16_ACC(acc, a, b) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %2, %1, %0" : "+a"(acc) : "v"(a), "v"(b))
+template <int TA>
 struct pq_frag_set_w4 {
-  pq_i32x2 h[16];   // h[2q], h[2q+1]: the halves of operand block q; q = 0..3 rows of A (tile rows), 4..7 rows of B (tile columns)
+  pq_i32x2 h[2 * TA + 8];   // h[2q], h[2q+1]: the halves of operand block q; q < TA rows of A (tile rows), then four of B (tile columns)
   __device__ __forceinline__ i32x4_t op(int q) const { return i32x4_t{h[2 * q][0], h[2 * q][1], h[2 * q + 1][0], h[2 * q + 1][1]}; }
   __device__ __forceinline__ void wait_all() {
+    if constexpr (TA == 3)
+      asm volatile("s_waitcnt lgkmcnt(0)"
+                   : "+v"(h[0]), "+v"(h[1]), "+v"(h[2]), "+v"(h[3]), "+v"(h[4]), "+v"(h[5]), "+v"(h[6]), "+v"(h[7]), "+v"(h[8]), "+v"(h[9]),
+                     "+v"(h[10]), "+v"(h[11]), "+v"(h[12]), "+v"(h[13]));
+    else
     asm volatile("s_waitcnt lgkmcnt(0)"
                  : "+v"(h[0]), "+v"(h[1]), "+v"(h[2]), "+v"(h[3]), "+v"(h[4]), "+v"(h[5]), "+v"(h[6]), "+v"(h[7]), "+v"(h[8]), "+v"(h[9]),
                    "+v"(h[10]), "+v"(h[11]), "+v"(h[12]), "+v"(h[13]), "+v"(h[14]), "+v"(h[15]));
@@ -1009,11 +1018,17 @@ struct pq_frag_set_w4 {
 };
 
 // RAGGED: the last stage of a range is not whole; its missing rows come from a page of zeros.  (An instantiation of its own: the
-// test behind every load cost the whole ones 3 to 4 %.)  TWO: the epilogue has a second destination.
-template <bool RAGGED, bool DUAL, bool TWO>
-__global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn,
-                                                          int total_tiles, int kchunk, float* splitk_part, pq_second_arg<DUAL> second) {
+// test behind every load cost the whole ones 3 to 4 %.)  TWO: the epilogue has a second destination.  TA: 32-row blocks of A that a
+// wavefront multiplies, 4 (256x256 tiles) or 3 (192x256).
+template <int TA, bool RAGGED, bool DUAL, bool TWO>
+__device__ __forceinline__ void gemm_tn_w4_body(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn,
+                                                int total_tiles, int kchunk, float* splitk_part, pq_second_arg<DUAL> second) {
 #if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int BM = 64 * TA, RSA = 2 * BM;          // tile rows; bytes of a contraction row of A in LDS
+  constexpr int IPS = TA + 4;                        // load instructions per wavefront and stage
+  constexpr int NM = 4 * TA;                         // MFMAs per wavefront and half stage
+  // chunk c of contraction row t lies at c ^ swzA(t), four rows of 32 columns on distinct banks whatever the row length
+  auto swzA = [](int t) { return TA == 4 ? 4 * (t & 3) : 4 * ((t >> 1) & 1); };
   constexpr int STG = 32768;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[4 * STG];
   __shared__ double red[4];
@@ -1033,56 +1048,62 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
     }
   }
   const int bm = pid / nbn, bn = pid % nbn;
-  const int m0 = bm * 256, n0 = bn * 256;
+  const int m0 = bm * BM, n0 = bn * 256;
   const int kb = split * kchunk, ke = min(K, kb + kchunk);
   const int nkt = ke > kb ? (ke - kb + (RAGGED ? 31 : 0)) >> 5 : 0;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm0 = (wv >> 1) * 128, wn0 = (wv & 1) * 128;
+  const int wm0 = (wv >> 1) * 32 * TA, wn0 = (wv & 1) * 128;
   const uint32_t lds0 = (uint32_t)(size_t)smem;
 
-  // direct loads: instruction block qi of an operand is 1 KB of its stage (two contraction rows); a wavefront owns four
-  // blocks of each operand.  Columns past the end fetch the tile's first chunk (any valid address: never stored).
-  const char* src[8];
+  // direct loads: instruction block qi of an operand is 1 KB of its stage (of B: two contraction rows); a wavefront owns TA
+  // blocks of A and four of B.  Columns past the end fetch the tile's first chunk (any valid address: never stored).
+  const char* src[IPS];
+  int trow[IPS];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int qi = wv * 4 + (i & 3);
-    const int t = qi * 2 + (lane >> 5), pc = lane & 31;
-    const int c = pc ^ (4 * (t & 3));
-    const pq_operand& op = i < 4 ? A : B;
-    const int col0 = i < 4 ? m0 : n0, cols = i < 4 ? M : N;
+  for (int i = 0; i < IPS; ++i) {
+    const bool isA = i < TA;
+    const int l = (isA ? wv * TA + i : wv * 4 + i - TA) * 64 + lane, cpr = isA ? 8 * TA : 32;
+    const int t = l / cpr, pc = l - t * cpr;
+    const int c = pc ^ (isA ? swzA(t) : 4 * (t & 3));
+    const pq_operand& op = isA ? A : B;
+    const int col0 = isA ? m0 : n0, cols = isA ? M : N;
+    trow[i] = t;
     int col = col0 + c * 8;
     if (col + 8 > cols) col = col0;
     src[i] = (const char*)op.p + ((size_t)(kb + t) * op.ld + col) * 2;
   }
   const size_t advA = (size_t)32 * A.ld * 2, advB = (size_t)32 * B.ld * 2;
   auto issue1 = [&](int kt, int slot, int i) {
-    unsigned char* base = smem + slot * STG + wv * 4096;
-    if (RAGGED && kt == nkt - 1) {
-      const int t = (wv * 4 + (i & 3)) * 2 + (lane >> 5);
-      const char* g = kt * 32 + t < ke - kb ? src[i] + (size_t)kt * (i < 4 ? advA : advB) : (const char*)pq_zero_page;
-      __builtin_amdgcn_global_load_lds(g, PQ_LDS_PTR(base + (i < 4 ? i * 1024 : 16384 + (i - 4) * 1024)), 16, 0, 0);
-    } else if (i < 4) __builtin_amdgcn_global_load_lds(src[i] + (size_t)kt * advA, PQ_LDS_PTR(base + i * 1024), 16, 0, 0);
-    else __builtin_amdgcn_global_load_lds(src[i] + (size_t)kt * advB, PQ_LDS_PTR(base + 16384 + (i - 4) * 1024), 16, 0, 0);
+    unsigned char* dst = smem + slot * STG + (i < TA ? (wv * TA + i) * 1024 : 16384 + (wv * 4 + i - TA) * 1024);
+    const char* g = src[i] + (size_t)kt * (i < TA ? advA : advB);
+    if (RAGGED && kt == nkt - 1 && kt * 32 + trow[i] >= ke - kb) g = (const char*)pq_zero_page;
+    __builtin_amdgcn_global_load_lds(g, PQ_LDS_PTR(dst), 16, 0, 0);
   };
 
   // fragment read addresses (slot 0, contraction rows 0..15): see the transposing reads of the streaming loop
-  uint32_t ad[8];
+  uint32_t ad[IPS];
   {
     const int h = lane >> 5;
-    const int tl = 8 * h + ((lane & 15) >> 2), cl = 16 * ((lane >> 4) & 1) + 4 * (lane & 3), sw = 4 * ((lane & 15) >> 2);
+    const int tl = 8 * h + ((lane & 15) >> 2), cl = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int col = (q < 4 ? wm0 + 32 * q : wn0 + 32 * (q - 4)) + cl;
-      ad[q] = lds0 + (q < 4 ? 0 : 16384) + tl * 512 + (((col >> 3) ^ sw) << 4) + (col & 7) * 2;
+    for (int q = 0; q < IPS; ++q) {
+      const int col = (q < TA ? wm0 + 32 * q : wn0 + 32 * (q - TA)) + cl;
+      ad[q] = lds0 + (q < TA ? tl * RSA : 16384 + tl * 512) + (((col >> 3) ^ (q < TA ? swzA(tl) : 4 * (tl & 3))) << 4) + (col & 7) * 2;
     }
   }
-  pq_frag_set_w4 F0, F1;
-  auto rd = [&](pq_frag_set_w4& F, int q, uint32_t so, auto ks_c) {
+  using fset = pq_frag_set_w4<TA>;
+  fset F0, F1;
+  auto rd = [&](fset& F, int q, uint32_t so, auto ks_c) {
     constexpr int ks = decltype(ks_c)::value;
     const uint32_t pa = ad[q] + so;
-    PQ_DS_READ_TR(F.h[2 * q], pa, ks * 8192);
-    PQ_DS_READ_TR(F.h[2 * q + 1], pa, ks * 8192 + 2048);
+    if (q < TA) {                                    // (constant after unrolling)
+      PQ_DS_READ_TR(F.h[2 * q], pa, ks * 16 * RSA);
+      PQ_DS_READ_TR(F.h[2 * q + 1], pa, ks * 16 * RSA + 4 * RSA);
+    } else {
+      PQ_DS_READ_TR(F.h[2 * q], pa, ks * 8192);
+      PQ_DS_READ_TR(F.h[2 * q + 1], pa, ks * 8192 + 2048);
+    }
   };
   using c0 = std::integral_constant<int, 0>;
   using c1 = std::integral_constant<int, 1>;
@@ -1091,14 +1112,14 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
 #pragma unroll
     for (int u = 0; u < 3; ++u)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) issue1(min(u, nkt - 1), u, i);
+      for (int i = 0; i < IPS; ++i) issue1(min(u, nkt - 1), u, i);
   }
   // 256 register writes per wavefront, under the latency of the first loads.  (The empty statements keep them here and make the
   // values opaque: left to itself the compiler zeroed the registers ahead of the loads and a second time behind them, 1.3 us
   // of a 65 us product.)
-  f32x16_t acc[4][4];
+  f32x16_t acc[TA][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TA; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
 #pragma unroll
@@ -1106,42 +1127,44 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
       asm volatile("" : "+a"(acc[i][j]));
     }
   if (nkt > 0) {
-    asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * IPS) : "memory");
     asm volatile("s_barrier" ::: "memory");
 #pragma unroll
-    for (int q = 0; q < 8; ++q) rd(F0, q, 0u, c0{});
+    for (int q = 0; q < IPS; ++q) rd(F0, q, 0u, c0{});
   }
-  auto mf = [&](const pq_frag_set_w4& X, int n) {
+  auto mf = [&](const fset& X, int n) {
     const int i = n >> 2, j = (n & 3) ^ ((i & 1) ? 3 : 0);   // a block of B stays for two MFMAs in a row
-    PQ_MFMA_BF16_ACC(acc[i][j], X.op(i), X.op(4 + j));
+    PQ_MFMA_BF16_ACC(acc[i][j], X.op(i), X.op(TA + j));
   };
   for (int kt = 0; kt < nkt; ++kt) {
     const uint32_t so = (uint32_t)(kt & 3) * STG, sn = (uint32_t)((kt + 1) & 3) * STG;
     const int ktl = min(kt + 3, nkt - 1), sl = (kt + 3) & 3;
     F0.wait_all();
 #pragma unroll
-    for (int n = 0; n < 8; ++n) {
+    for (int n = 0; n < NM / 2; ++n) {                 // (with TA = 3 one block more than MFMAs to hide it behind)
       mf(F0, n);
       rd(F1, n, so, c1{});
+      if (TA == 3 && n == 0) rd(F1, NM / 2, so, c1{});
     }
-    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");   // the wavefront's own loads of stage kt+1 have landed
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(IPS) : "memory");   // the wavefront's own loads of stage kt+1 have landed
     asm volatile("s_barrier" ::: "memory");            // everybody's have; nobody reads stage kt-1 any more
 #pragma unroll
-    for (int n = 8; n < 16; ++n) {
+    for (int n = NM / 2; n < NM; ++n) {
       mf(F0, n);
-      issue1(ktl, sl, n - 8);
+      issue1(ktl, sl, n - NM / 2);
+      if (TA == 3 && n == NM / 2) issue1(ktl, sl, NM / 2);
     }
     F1.wait_all();
 #pragma unroll
-    for (int n = 0; n < 16; ++n) {
+    for (int n = 0; n < NM; ++n) {
       mf(F1, n);
-      if (n < 8) rd(F0, n, sn, c0{});                  // past the last stage: a slot nobody uses
+      if (n < IPS) rd(F0, n, sn, c0{});                // past the last stage: a slot nobody uses
     }
   }
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
   PQ_MFMA_SETTLE_FIRST();
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TA; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) asm volatile("" : "+a"(acc[i][j]));
   asm volatile("s_barrier" ::: "memory");
@@ -1155,14 +1178,15 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
   unsigned tid_e = threadIdx.x;
   asm volatile("" : "+v"(tid_e));
   const int lane_e = tid_e & 63, wave_e = tid_e >> 6;
-  const int wm_e = (wave_e >> 1) * 128, wn_e = (wave_e & 1) * 128;
+  const int wm_e = (wave_e >> 1) * 32 * TA, wn_e = (wave_e & 1) * 128;
   unsigned char* wreg = smem + wave_e * STG;
   const int mlim = (!slab && epi.m_limit > 0 && epi.m_limit < M) ? epi.m_limit : M;
   const int nlim = (!slab && epi.n_limit > 0 && epi.n_limit < N) ? epi.n_limit : N;
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass) {
+    const int nb = TA == 3 && pass == 1 ? 1 : 2;       // 32-row blocks of this pass
 #pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
+    for (int ii = 0; ii < nb; ++ii)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -1182,7 +1206,7 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
       char* outp = slab ? (char*)slab : (char*)epi.C;
       const size_t ldo = (slab ? (size_t)N : (size_t)epi.ldc) * 4;
 #pragma unroll 4
-      for (int it = 0; it < 32; ++it) {
+      for (int it = 0; it < 16 * nb; ++it) {
         const int rl = it * 2 + (lane_e >> 5), c = lane_e & 31;
         uint4 v = *reinterpret_cast<const uint4*>(wreg + rl * 512 + ((c ^ (rl & 31)) << 4));
         if (!slab) {
@@ -1196,7 +1220,7 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
       }
     } else {
 #pragma unroll 2
-      for (int it = 0; it < 16; ++it) {
+      for (int it = 0; it < 8 * nb; ++it) {
         const int rl = it * 4 + (lane_e >> 4), c = (lane_e & 15) * 2;
         const uint4 r0 = *reinterpret_cast<const uint4*>(wreg + rl * 512 + ((c ^ (rl & 31)) << 4));
         const uint4 r1 = *reinterpret_cast<const uint4*>(wreg + rl * 512 + (((c + 1) ^ (rl & 31)) << 4));
@@ -1209,6 +1233,17 @@ __global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq
   }
   if (!slab) epi_end<256>(epi, st, red, blockIdx.x);
 #endif
+}
+
+template <bool RAGGED, bool DUAL, bool TWO>
+__global__ __launch_bounds__(256) void gemm_tn_w4_kernel(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn,
+                                                          int total_tiles, int kchunk, float* splitk_part, pq_second_arg<DUAL> second) {
+  gemm_tn_w4_body<4, RAGGED, DUAL, TWO>(M, N, K, A, B, epi, nbn, total_tiles, kchunk, splitk_part, second);
+}
+template <bool RAGGED, bool DUAL>
+__global__ __launch_bounds__(256) void gemm_tn_192_kernel(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn,
+                                                           int total_tiles, int kchunk, float* splitk_part, pq_second_arg<DUAL> second) {
+  gemm_tn_w4_body<3, RAGGED, DUAL, false>(M, N, K, A, B, epi, nbn, total_tiles, kchunk, splitk_part, second);
 }
 
 template <int BM, int BN, int WGM, int WGN, int KB, bool WHOLE, bool TAIL, bool INT8, int AK, int BKIND, int AK2 = -1, int BK2 = -1, bool DUAL = false>
@@ -1239,17 +1274,23 @@ int launch_mfma_cfg(const pq_gemm_plan& pl, int M, int N, int K, const pq_operan
     return pq_set_error(PQ_ERR_SHAPE, "GEMM operands must have 16-byte aligned rows");
   // weight gradients: the four-wavefront kernel (no per-row divisor, no int32 output)
   if constexpr (AK == PQ_SRC_KS16 && BKIND == PQ_SRC_KS16 && AK2 < 0) {
-    const int nbm = (M + 255) / 256, nbn = (N + 255) / 256;
+    const int nbm = (M + pl.bm - 1) / pl.bm, nbn = (N + 255) / 256;
     const bool dual = grp.mode == 3, ragged = K % 32 != 0 || pl.kchunk % 32 != 0;
     dim3 grid(nbm * nbn, pl.splits, dual ? 2 : 1);
     if ((grp.mode && !dual) || epi.row_div || epi.out_kind == PQ_OUT_I32) return pq_set_error(PQ_ERR_BAD_ARG, "no 256x256 weight-gradient kernel for this epilogue");
     float* p = pl.splits > 1 ? part : nullptr;
 #define PQ_W4(R, D, T) gemm_tn_w4_kernel<R, D, T><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, nbm * nbn, pl.kchunk, p, second_arg<D>(second))
-    if (dual) { if (ragged) PQ_W4(true, true, false); else PQ_W4(false, true, false); }
+#define PQ_192(R, D) gemm_tn_192_kernel<R, D><<<grid, 256, 0, s>>>(M, N, K, A, B, epi, nbn, nbm * nbn, pl.kchunk, p, second_arg<D>(second))
+    if (pl.bm == 192) {                              // (never with a second destination)
+      if (dual) { if (ragged) PQ_192(true, true); else PQ_192(false, true); }
+      else if (ragged) PQ_192(true, false);
+      else PQ_192(false, false);
+    } else if (dual) { if (ragged) PQ_W4(true, true, false); else PQ_W4(false, true, false); }
     else if (epi.m_split > 0) { if (ragged) PQ_W4(true, false, true); else PQ_W4(false, false, true); }
     else if (ragged) PQ_W4(true, false, false);
     else PQ_W4(false, false, false);
 #undef PQ_W4
+#undef PQ_192
     PQ_CHECK_LAUNCH("gemm_tn_w4_kernel");
     return PQ_OK;
   } else {
@@ -1693,6 +1734,8 @@ int pq_launch_skinny(int M, int K, const pq_operand& A, const pq_operand& B, con
 //   128x128: 6 + 0.76 per step alone on a CU (int8 0.85), 0.58 c (0.61) when two workgroups share it, + 2.4 per further workgroup
 //   256x256: c (9.5 + 1.38 per step); split only while the tiles are at most half of the CUs: beyond that more active CUs
 //            lower the clock instead
+//   192x256, weight gradients: c (9 + 1.19 per step): of use where 256x256 tiles leave a third of the CUs idle, or of the last
+//            round (5504x2048 over 8192 tokens 216 -> 188, two such in one launch 383 -> 338; 5076x2048 over 2048 72 -> 65)
 //   128x256, packed signs: 6 + 0.7 per step alone on a CU (int8 6.5 + 0.8; up to 0.12 more as the CUs fill up), u workgroups to a
 //            CU 6 + 0.75 u per step (0.83 u) + 3 per workgroup behind the first.  These times count from 1024 columns or 192 tiles on,
 //            512 rows and four steps; narrower and shorter outputs, where the two sizes of tiles measured 0.98-1.24 x
@@ -1722,7 +1765,14 @@ static double est_signs(long n, long steps, bool int8) {
   return 6.0 + u * steps * (int8 ? 0.83 : 0.75) + 3.0 * (u - 1.0);
 }
 
-static pq_gemm_plan plan_search(int M, int N, int K, bool int8, bool may_split, bool signs) {
+// Weight gradients on 192x256 tiles, never split.
+static double est_192(long tiles, long steps) {
+  const double c = (double)((tiles + 255) / 256);
+  return c * (9.0 + 1.19 * steps);
+}
+
+static pq_gemm_plan plan_search(int M, int N, int K, bool int8, bool may_split, pq_plan_kind kind) {
+  const bool signs = kind == PQ_PLAN_SIGNS;
   pq_gemm_plan pl;
   memset(&pl, 0, sizeof(pl));
   pl.bm = pl.bn = 64;
@@ -1748,6 +1798,10 @@ static pq_gemm_plan plan_search(int M, int N, int K, bool int8, bool may_split, 
       if (t < best) { best = t; pl.bm = bm; pl.bn = c; pl.splits = sp; pl.kchunk = chunk; }
     }
   }
+  if (kind == PQ_PLAN_WGRAD && M >= 192 && N >= 256) {
+    const double t = est_192(tiles_of(192, 256), (K + 63) / 64);
+    if (t < best) { best = t; pl.bm = 192; pl.bn = 256; pl.splits = 1; pl.kchunk = K > 0 ? K : 1; }
+  }
   const long tiles = tiles_of(pl.bm, pl.bn);
   pl.red_blocks = pl.splits > 1 ? (int)(((size_t)M * (N / 8) + 255) / 256) : (int)tiles;
   pl.ws_bytes = pl.splits > 1 ? (size_t)pl.splits * M * N * sizeof(float) : 0;
@@ -1756,18 +1810,18 @@ static pq_gemm_plan plan_search(int M, int N, int K, bool int8, bool may_split, 
 }
 // The search is a pure function of its arguments and takes up to a microsecond; a call asks for a dozen plans (sizes of its
 // sections, then the launches), most of them the ones it asked for before: the last answers are kept per thread.
-static pq_gemm_plan pq_plan_gemm_impl(int M, int N, int K, bool int8, bool may_split, bool signs) {
+static pq_gemm_plan pq_plan_gemm_impl(int M, int N, int K, bool int8, bool may_split, pq_plan_kind kind) {
   struct entry { int M, N, K, flags; pq_gemm_plan pl; };
   static thread_local entry cache[64];               // (zeroed: no plan has M = 0, see below)
-  const int flags = (int8 ? 1 : 0) | (may_split ? 2 : 0) | (signs ? 4 : 0);
-  if (M <= 0) return plan_search(M, N, K, int8, may_split, signs);
+  const int flags = (int8 ? 1 : 0) | (may_split ? 2 : 0) | (int)kind << 2;
+  if (M <= 0) return plan_search(M, N, K, int8, may_split, kind);
   const uint32_t hsh = ((uint32_t)M * 2654435761u) ^ ((uint32_t)N * 2246822519u) ^ ((uint32_t)K * 3266489917u) ^ ((uint32_t)flags * 668265263u);
   entry& e = cache[(hsh ^ (hsh >> 15)) & 63u];
-  if (e.M != M || e.N != N || e.K != K || e.flags != flags) e = entry{M, N, K, flags, plan_search(M, N, K, int8, may_split, signs)};
+  if (e.M != M || e.N != N || e.K != K || e.flags != flags) e = entry{M, N, K, flags, plan_search(M, N, K, int8, may_split, kind)};
   return e.pl;
 }
-pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8, bool split_int8, bool signs) {
-  return pq_plan_gemm_impl(M, N, K, int8, !int8 || split_int8, signs);
+pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8, bool split_int8, pq_plan_kind kind) {
+  return pq_plan_gemm_impl(M, N, K, int8, !int8 || split_int8, kind);
 }
 
 static int check_scratch(size_t need, const pq_scratch& sk) {
@@ -1881,7 +1935,7 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
 // Two products of the same sizes, kinds and epilogue but for C and the device scale (U and G of the FFN; dW_up and dW_gate) in
 // one launch: one start and one tail instead of two, and together they fill the chip where each alone does not.
 // (int8: U and G, with packed signs; otherwise dW_up and dW_gate)
-pq_gemm_plan pq_plan_dual(int M, int N, int K, bool int8) { return pq_plan_gemm_impl(2 * M, N, K, int8, true, int8); }
+pq_gemm_plan pq_plan_dual(int M, int N, int K, bool int8) { return pq_plan_gemm_impl(2 * M, N, K, int8, true, int8 ? PQ_PLAN_SIGNS : PQ_PLAN_WGRAD); }
 int pq_launch_gemm_dual(int M, int N, int K, const pq_operand& A0, const pq_operand& B0, const pq_epilogue& e0, const pq_operand& A1,
                         const pq_operand& B1, void* C1, const float* dev_scale1, hipStream_t s, int prof_label, pq_scratch sk) {
   if (M <= 0 || N <= 0) return PQ_OK;
@@ -1965,7 +2019,10 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
     return pq_launch_skinny(M, K, A, B, epi, s, prof_label);
   const int ak = A.kind, bk = B.kind;
   const bool int8 = (ak == PQ_SRC_KC8);
-  pq_gemm_plan pl = pq_plan_gemm(M, N, K, int8, epi.split_int8 != 0, bk == PQ_SRC_BITS8 || bk == PQ_SRC_BITS16);
+  pq_gemm_plan pl = pq_plan_gemm(M, N, K, int8, epi.split_int8 != 0,
+                                 bk == PQ_SRC_BITS8 || bk == PQ_SRC_BITS16                             ? PQ_PLAN_SIGNS
+                                 : ak == PQ_SRC_KS16 && bk == PQ_SRC_KS16 && epi.m_split == 0 ? PQ_PLAN_WGRAD
+                                                                                              : PQ_PLAN_ANY);
   if (grp.mode) {
     pl.splits = 1;
     pl.kchunk = K > 0 ? K : 1;

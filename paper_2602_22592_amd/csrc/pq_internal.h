@@ -175,15 +175,17 @@ struct pq_scratch {
 };
 
 struct pq_gemm_plan {
-  int bm, bn;        // tile: 64x64, 128x128, 256x256, with packed signs 128x256 instead of the last
+  int bm, bn;        // tile: 64x64, 128x128, 256x256; 128x256 (packed signs, instead of the last), 192x256 (weight gradients)
   int splits;        // contraction splits (1 = none)
   int kchunk;        // contraction elements per split
   int red_blocks;    // number of per-block partial sums written when a reduction is requested
   size_t ws_bytes;   // scratch for the split slabs
   double us;         // the time that the choice expects
 };
-// signs: the B operand is packed signs (the 1-bit forward with int8, dX without)
-pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8 = false, bool split_int8 = false, bool signs = false);
+// what decides between tiles of 256 columns: packed signs in B (the 1-bit forward with int8, dX without), or contraction-strided
+// operands on both sides with one destination (weight gradients)
+enum pq_plan_kind { PQ_PLAN_ANY = 0, PQ_PLAN_SIGNS = 1, PQ_PLAN_WGRAD = 2 };
+pq_gemm_plan pq_plan_gemm(int M, int N, int K, bool int8 = false, bool split_int8 = false, pq_plan_kind kind = PQ_PLAN_ANY);
 // whether a second contraction (pq_phase2) can be fused into a GEMM of this plan
 inline bool pq_plan_fuses(const pq_gemm_plan& pl) { return pl.splits == 1 || pl.bn < 256; }
 // tn: the streaming pair kernel; apart: a launch each; otherwise 64x64 tiles.  ws0, ws1: scratch of the two problems.
