@@ -112,6 +112,9 @@ struct lin_layout {
   // workspace (scratch)
   size_t stat_partials, red_a, red_b, dH, w_Xq, w_gamma, w_H, splitk, splitk2, splitk_bytes, splitk2_bytes, ws_total;
   size_t dYp, rd, dHs, dXs, dlogit, dwr, hp8_ws, hp8_ws_bytes;
+  // fp32 I/O in fixed point (pq_fixed.hip)
+  bool fixed;
+  size_t fx_drow, fx_rexp, fx_dcol, fx_cexp, fx_qT, fx_colmax, fx_planes;
   int n_red_a, n_red_b;
 };
 
@@ -123,6 +126,13 @@ struct cursor {
     return o;
   }
 };
+
+inline int fixed_Tp(int T) { return (T + 15) / 16 * 16; }
+// The two large contractions of the fp32 backward in fixed point: four more launches (about 40 us) and passes over dY and the
+// sums, a fifth of the time of the products.  44 shapes of 64 to 2048 tokens: 0.55-0.9 x up to tokens * d_in * d_out = 0.54e9,
+// 0.96-1.11 x at 1.07e9, 1.2-1.4 x from 1.9e9 on, 1.75 x at 8.6e9 (2048 tokens 2048x2048 r=128: 716 -> 410 us).  The int32 sums of dW hold
+// tokens * 2^14, those of dX d_out * 2^7.
+bool fixed_applies(int T, int K, int N) { return T >= 64 && T <= 65536 && N <= 65536 && (double)T * K * N >= 1.2e9; }
 
 lin_layout make_layout(const pq_linear_desc& d) {
   lin_layout L;
@@ -154,9 +164,10 @@ lin_layout make_layout(const pq_linear_desc& d) {
   cursor w;
   L.stat_partials = w.take(2 * sizeof(double) * 1024);
   const int Ti = d.tokens, Ki = d.d_in, Ni = d.d_out, ri = (int)r;
+  L.fixed = !bf16 && fixed_applies(Ti, Ki, Ni);
   L.n_red_a = r ? (bf16 ? pq_plan_gemm(Ti, ri, Ni).red_blocks : pq_ref_red_blocks(Ti, ri, Ni)) : 0;   // dH GEMM
   if (r && pq_skinny_blocks(Ti) > L.n_red_a) L.n_red_a = pq_skinny_blocks(Ti);   // room for the streaming rank-r kernel's partials
-  L.n_red_b = bf16 ? pq_plan_gemm(Ni, Ki, Ti, false, false, PQ_PLAN_WGRAD).red_blocks : pq_ref_red_blocks(Ni, Ki, Ti);              // dW GEMM
+  L.n_red_b = bf16 ? pq_plan_gemm(Ni, Ki, Ti, false, false, PQ_PLAN_WGRAD).red_blocks : pq_ref_red_blocks(Ni, Ki, L.fixed ? -1 : Ti);              // dW GEMM
   size_t sk = 0;
   const int shapes[7][3] = {{Ti, ri, Ki}, {Ti, Ni, ri}, {Ti, ri, Ni}, {Ti, Ki, ri}, {Ni, Ki, Ti}, {Ni, ri, Ti}, {ri, Ki, Ti}};
   for (const auto& sh : shapes) {
@@ -185,6 +196,13 @@ lin_layout make_layout(const pq_linear_desc& d) {
   L.w_Xq = w.take(T * K);          // used when forward runs without a ctx (inference)
   L.w_gamma = w.take(T * sizeof(float));
   L.w_H = w.take(T * r * es);
+  if (L.fixed) {
+    const size_t Tp = fixed_Tp(Ti), pl = PQ_FIXED_DIGITS * K * (T > N ? T : N) * sizeof(int);   // (dW's planes, then dX's)
+    L.fx_drow = w.take(PQ_FIXED_DIGITS * T * N); L.fx_rexp = w.take(T * sizeof(int));
+    L.fx_dcol = w.take(PQ_FIXED_DIGITS * N * Tp); L.fx_cexp = w.take(N * sizeof(int));
+    L.fx_qT = w.take(K * Tp); L.fx_colmax = w.take(pq_fixed_max_rows(Ti) * N * sizeof(uint32_t));
+    L.fx_planes = w.take(pl);
+  }
   L.splitk = w.take(sk);
   L.splitk_bytes = sk;
   // slabs of dA, which shares a launch with dB (whose slabs are in the region above)
@@ -596,7 +614,8 @@ static int hp_int8_dh(const void* dY, int T, int N, int r, float alpha, const ch
 static int hp_int8_factor_grads(const void* dY, const void* Xt, int T, int K, int N, int r, float alpha, const char* cx, const hp8_layout& L,
                                 float* dA, float* dB, char* ws, const pq_reduce_job* jobs, bool* jobs_done, hipStream_t s);
 
-// fp32 I/O: the same products at reference precision.  What depends on nothing (dW, dH, dB) is one launch, what needs dH
+// fp32 I/O: the same products at reference precision; large ones of dX and dW as exact integer products of fixed-point digits
+// (pq_fixed.hip), whose sums the launches below finish.  What depends on nothing (dW, dH, dB) is one launch, what needs dH
 // (dX with dH A in the same sums, dA) and the two scalar reductions a second one: six products and a reduction in a row
 // left most of the chip idle at every size, and at 64 tokens their starts were most of the time.
 static int linear_bwd_f32(const pq_linear_desc* d, const lin_layout& L, const void* dY, const void* X, const void* W, const void* hpA,
@@ -610,13 +629,28 @@ static int linear_bwd_f32(const pq_linear_desc* d, const lin_layout& L, const vo
   void* dH = ws + L.dH;
   pq_ref_problem p[PQ_REF_MAX];
   int n = 0;
-  {  // dW = beta * dY^T (q / gamma)  [masked];  d beta = lambda * sum S .* (dY^T (q / gamma))
+  int* planes = (int*)(ws + L.fx_planes);
+  const int Tp = fixed_Tp(T);
+  if (L.fixed) {                     // (dY / gamma)^T q: the digits of dY's columns, one behind the other, times q
+    if (int err = pq_launch_fixed_split((const float*)dY, (const float*)(cx + L.gamma), (const int8_t*)(cx + L.Xq), T, Tp, N, K, (int8_t*)(ws + L.fx_drow),
+                                        (int*)(ws + L.fx_rexp), (int8_t*)(ws + L.fx_dcol), (int*)(ws + L.fx_cexp), (int8_t*)(ws + L.fx_qT),
+                                        (uint32_t*)(ws + L.fx_colmax), s)) return err;
+    pq_epilogue e = epi_zero();
+    e.C = planes; e.ldc = K; e.out_kind = PQ_OUT_I32;
+    if (int err = pq_launch_gemm(PQ_FIXED_DIGITS * N, K, Tp, {ws + L.fx_dcol, Tp, PQ_SRC_KC8, nullptr}, {ws + L.fx_qT, Tp, PQ_SRC_KC8, nullptr}, e, s,
+                                 PQP_GEMM_DW)) return err;
+  }
+  auto add_dW = [&] {  // dW = beta * dY^T (q / gamma)  [masked];  d beta = lambda * sum S .* (dY^T (q / gamma))
     pq_epilogue e = epi_zero();
     e.C = dW; e.ldc = K; e.scale = d->beta;
     e.sign_bytes = (const uint8_t*)(cx + L.P); e.ld_sign = K / 8; e.partials = red_b;
     if (d->ste_mode == PQ_STE_CLIP) { e.maskW = W; e.mu_dev = mulam; e.tau = d->ste_tau; }
-    p[n++] = ref_problem(PQ_REF_SS8, N, K, T, {dY, N, PQ_SRC_KS32, nullptr}, {cx + L.Xq, K, PQ_SRC_KS8, (const float*)(cx + L.gamma)}, e);
-  }
+    p[n] = ref_problem(L.fixed ? PQ_REF_SUM_SS8 : PQ_REF_SS8, N, K, T, {dY, N, PQ_SRC_KS32, nullptr},
+                       {cx + L.Xq, K, PQ_SRC_KS8, (const float*)(cx + L.gamma)}, e);
+    p[n].planes = planes; p[n].exps = (const int*)(ws + L.fx_cexp);
+    ++n;
+  };
+  if (!L.fixed) add_dW();            // (the longest first: products before sums of planes)
   if (r > 0) {
     pq_epilogue e = epi_zero();      // dB = alpha * dY^T H
     e.C = dhpB; e.ldc = r; e.scale = d->alpha;
@@ -625,19 +659,33 @@ static int linear_bwd_f32(const pq_linear_desc* d, const lin_layout& L, const vo
     e.C = dH; e.ldc = r; e.scale = d->alpha; e.dot_comp = H; e.ld_comp = r; e.partials = red_a;
     p[n++] = ref_problem(PQ_REF_CS, T, r, N, {dY, N, PQ_SRC_KC32, nullptr}, {hpB, r, PQ_SRC_KS32, nullptr}, e);
   }
+  if (L.fixed) add_dW();
   if (int err = pq_launch_ref(p, n, nullptr, 0, s, PQP_GEMM_DW)) return err;
+  if (L.fixed) {                     // dY S: the digits of dY's rows, one behind the other, times the signs
+    pq_epilogue e = epi_zero();
+    e.C = planes; e.ldc = K; e.out_kind = PQ_OUT_I32;
+    if (int err = pq_launch_gemm(PQ_FIXED_DIGITS * T, K, N, {ws + L.fx_drow, N, PQ_SRC_KC8, nullptr}, {cx + L.Pt, N / 8, PQ_SRC_BITS8, nullptr}, e, s,
+                                 PQP_GEMM_DX)) return err;
+  }
   const pq_reduce_job jobs[2] = {{red_a, (T > 0 && r > 0) ? pq_ref_red_blocks(T, r, N) : 0, 1.0f, nullptr, dalpha_dbeta},
                                  {red_b, L.n_red_b, 1.0f, mulam + 1, dalpha_dbeta + 1}};
-  pq_epilogue e = epi_zero();        // dX = beta * lambda * dY S + dH A
-  e.C = dX; e.ldc = K;
-  p[0] = ref_problem(PQ_REF_CBITS, T, K, N, {dY, N, PQ_SRC_KC32, nullptr}, {cx + L.Pt, N / 8, PQ_SRC_BITSF, nullptr}, e);
-  p[0].scale1 = d->beta; p[0].dev_scale1 = mulam + 1;
-  n = 1;
-  if (r > 0) {
-    p[0].K2 = r; p[0].A2 = pq_operand{dH, r, PQ_SRC_KC32, nullptr}; p[0].B2 = pq_operand{hpA, K, PQ_SRC_KS32, nullptr};
-    e.C = dhpA; e.ldc = K;           // dA = dH^T X   (dH already carries alpha)
+  n = 0;
+  auto add_dX = [&] {                // dX = beta * lambda * dY S + dH A
+    pq_epilogue e = epi_zero();
+    e.C = dX; e.ldc = K;
+    p[n] = ref_problem(L.fixed ? PQ_REF_SUM_CBITS : PQ_REF_CBITS, T, K, N, {dY, N, PQ_SRC_KC32, nullptr}, {cx + L.Pt, N / 8, PQ_SRC_BITSF, nullptr}, e);
+    p[n].planes = planes; p[n].exps = (const int*)(ws + L.fx_rexp);
+    p[n].scale1 = d->beta; p[n].dev_scale1 = mulam + 1;
+    if (r > 0) { p[n].K2 = r; p[n].A2 = pq_operand{dH, r, PQ_SRC_KC32, nullptr}; p[n].B2 = pq_operand{hpA, K, PQ_SRC_KS32, nullptr}; }
+    ++n;
+  };
+  if (!L.fixed) add_dX();
+  if (r > 0) {                       // dA = dH^T X   (dH already carries alpha)
+    pq_epilogue e = epi_zero();
+    e.C = dhpA; e.ldc = K;
     p[n++] = ref_problem(PQ_REF_SS, r, K, T, {dH, r, PQ_SRC_KS32, nullptr}, {X, K, PQ_SRC_KS32, nullptr}, e);
   }
+  if (L.fixed) add_dX();
   return pq_launch_ref(p, n, jobs, 2, s, PQP_GEMM_DX);
 }
 

@@ -779,7 +779,8 @@ __global__ __launch_bounds__(WGM * WGN * 64, 2) void mfma_gemm_kernel(int M, int
   constexpr bool CAN_STAGE = SMEM_BYTES >= (NT / 64) * 16384;
 #endif
   // (store limits: fp32 outputs only, where a 16-byte chunk is four columns and the column limit a multiple of four)
-  const bool staged = CAN_STAGE && (slab || ((epi.out_kind == PQ_OUT_F32 || (epi.out_kind == PQ_OUT_BF16 && epi.m_limit == 0 && epi.n_limit == 0)) &&
+  const bool raw = slab || epi.out_kind == PQ_OUT_I32;       // uniform: the accumulators as they are
+  const bool staged = CAN_STAGE && (slab || (epi.out_kind == PQ_OUT_I32 && epi.m_limit == 0 && epi.n_limit == 0) || ((epi.out_kind == PQ_OUT_F32 || (epi.out_kind == PQ_OUT_BF16 && epi.m_limit == 0 && epi.n_limit == 0)) &&
                                              !epi.col_div && !epi.maskW && !epi.accumulate && !epi.dot_comp &&
                                              !epi.sign_bytes));   // uniform
   if (staged) {
@@ -811,7 +812,7 @@ __global__ __launch_bounds__(WGM * WGN * 64, 2) void mfma_gemm_kernel(int M, int
             uint32_t w[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-              if (slab) {
+              if (raw) {
                 // copy the element out first: a vector element is not a bit_cast-able lvalue
                 if constexpr (PH2) { const float e = accf[i][j][4 * g + t]; w[t] = __float_as_uint(e); }
                 else { const auto e = acc[i][j][4 * g + t]; w[t] = __builtin_bit_cast(uint32_t, e); }

@@ -227,20 +227,36 @@ enum pq_ref_form {
   PQ_REF_CBITS = 2,   // A KC32, B packed signs; then, K2 > 0, a second contraction A2 (KC32) x B2 (KS32) into the same sums:
                       // (scale1 [* *dev_scale1]) * sum_k A B + sum_k2 A2 B2
   PQ_REF_SS8 = 3,     // A KS32, B KS8 divided by its kdiv
-  PQ_REF_SS = 4       // A KS32, B KS32
+  PQ_REF_SS = 4,      // A KS32, B KS32
+  // the same with the first contraction already done in fixed point (pq_fixed.hip): its sums are read from `planes` and A, B are
+  // looked at only for rows that are not finite
+  PQ_REF_SUM_CBITS = 5,
+  PQ_REF_SUM_SS8 = 6
 };
 struct pq_ref_problem {
   int form, M, N, K, K2, cfg;   // cfg is set by the launcher
   pq_operand A, B, A2, B2;
   float scale1;
   const float* dev_scale1;
+  const int* planes;            // SUM forms: [PQ_FIXED_DIGITS][M][N] int32 sums of the digit products, lowest digit first
+  const int* exps;              // ... and the rows' exponents
   pq_epilogue epi;              // scale, dev_scale, accumulate, dot_comp, sign_bytes, partials and the clip mask; C is fp32
 };
 constexpr int PQ_REF_MAX = 3;
-int pq_ref_red_blocks(int M, int N, int K);   // partial sums one product leaves when its epilogue asks for them
+int pq_ref_red_blocks(int M, int N, int K);   // partial sums one product leaves when its epilogue asks for them (SUM forms: K = -1)
 // Up to PQ_REF_MAX independent products in one launch per tile class (at most two launches); up to two scalar reductions of
 // partials that EARLIER launches left ride along.
 int pq_launch_ref(pq_ref_problem* p, int n, const pq_reduce_job* jobs, int njobs, hipStream_t s, int prof_label);
+
+// ---- pq_fixed.hip -------------------------------------------------------------------------
+// Fixed-point form of dY for the two large contractions of the fp32 backward: row digits Drow [7][T][N] with exponents rexp [T],
+// digits of the columns of dY / gamma Dcol [7][N][Tp] with exponents cexp [N], q transposed qT [K][Tp]; Tp = T rounded up to a
+// multiple of 16.  colmax: [pq_fixed_max_rows(T)][N] words of scratch.
+constexpr int PQ_FIXED_DIGITS = 7;
+constexpr int PQ_FIXED_NOT_FINITE = 1 << 20;         // the exponent of a row with infinities or NaN (its digits are zero)
+int pq_fixed_max_rows(int T);
+int pq_launch_fixed_split(const float* dY, const float* gamma, const int8_t* q, int T, int Tp, int N, int K, int8_t* Drow, int* rexp, int8_t* Dcol,
+                          int* cexp, int8_t* qT, uint32_t* colmax, hipStream_t s);
 
 // ---- pq_decode.hip ------------------------------------------------------------------------
 size_t pq_decode_ws_layout(const pq_decode_desc& d, size_t* off);

@@ -241,11 +241,85 @@ __device__ __forceinline__ void ref_contract(const pq_operand& A, const pq_opera
   }
 }
 
+// NB columns of one row of a SUM form's first contraction the long way, for rows with infinities or NaN.
+template <int FORM, int NB>
+__device__ __forceinline__ void ref_direct(const pq_ref_problem& p, int m, int n, double (&s)[NB]) {
+#pragma unroll
+  for (int j = 0; j < NB; ++j) s[j] = 0.0;
+#pragma unroll 1
+  for (int k = 0; k < p.K; ++k) {
+    if constexpr (FORM == PQ_REF_SUM_CBITS) {
+      const double a = (double)((const float*)p.A.p)[(size_t)m * p.A.ld + k];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) s[j] += ((((const uint8_t*)p.B.p)[(size_t)(n + j) * p.B.ld + (k >> 3)] >> (k & 7)) & 1) ? a : -a;
+    } else {
+      const double d = (double)p.B.kdiv[k], a = (double)((const float*)p.A.p)[(size_t)k * p.A.ld + m];
+      double r = __builtin_amdgcn_rcp(d);
+      r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
+      r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) s[j] = __builtin_fma(a, (double)((const int8_t*)p.B.p)[(size_t)k * p.B.ld + n + j] * r, s[j]);
+    }
+  }
+}
+
+// The sums of a SUM form: sum_d 256^d acc_d 2^(E - 54), from the top digit down.  (A lane's NB columns of a row are one load a plane.)
+template <int FORM, int NB>
+__device__ __forceinline__ void ref_planes(const pq_ref_problem& p, int m0, int n0, int li, int lk, f64x4_t (&acc)[NB][NB]) {
+  const size_t stride = (size_t)p.M * p.N;
+  const int n = min(n0 + NB * li, p.N - NB);
+  bool marked = false;
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int m = min(m0 + NB * (lk + 4 * v) + i, p.M - 1);
+      const int* src = p.planes + (size_t)m * p.N + n;
+      int x[PQ_FIXED_DIGITS][NB];
+#pragma unroll
+      for (int d = 0; d < PQ_FIXED_DIGITS; ++d) {
+        if constexpr (NB == 4) {
+          const int4 t = *reinterpret_cast<const int4*>(src + d * stride);
+          x[d][0] = t.x; x[d][1] = t.y; x[d][2] = t.z; x[d][3] = t.w;
+        } else if constexpr (NB == 2) {
+          const int2 t = *reinterpret_cast<const int2*>(src + d * stride);
+          x[d][0] = t.x; x[d][1] = t.y;
+        } else x[d][0] = src[d * stride];
+      }
+      const int e = p.exps[m];
+      const double sc = ldexp(1.0, e - 54);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        double s = 0.0;
+#pragma unroll
+        for (int d = PQ_FIXED_DIGITS - 1; d >= 0; --d) s = __builtin_fma(s, 256.0, (double)x[d][j]);
+        acc[i][j][v] = s * sc;
+      }
+      marked |= e == PQ_FIXED_NOT_FINITE;
+    }
+  if (__any(marked)) {
+#pragma unroll 1
+    for (int q = 0; q < 4 * NB; ++q) {
+      const int m = min(m0 + NB * (lk + 4 * (q & 3)) + (q >> 2), p.M - 1);
+      if (p.exps[m] != PQ_FIXED_NOT_FINITE) continue;
+      double s[NB];
+      ref_direct<FORM, NB>(p, m, n, s);
+#pragma unroll
+      for (int i = 0; i < NB; ++i)                   // (static indices: the accumulators stay in registers)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+          for (int j = 0; j < NB; ++j) acc[i][j][v] = q == 4 * i + v ? s[j] : acc[i][j][v];
+    }
+  }
+}
+
 // One workgroup's tile of one product.  KS = 1: the four wavefronts own a 2 x 2 arrangement of tiles; KS = 4: they share one
 // tile, wavefront w taking every fourth step, and wavefront 0 adds their sums in order.
 template <int FORM, int NB, int KS>
 __device__ __forceinline__ void ref_tile(const pq_ref_problem& p, int block, double* lds, double* red) {
   constexpr int WT = 16 * NB, DEPTH = NB == 4 ? 2 : NB == 2 ? 3 : 4;
+  constexpr bool SUM = FORM == PQ_REF_SUM_CBITS || FORM == PQ_REF_SUM_SS8;
   constexpr int AK = (FORM == PQ_REF_SS8 || FORM == PQ_REF_SS) ? PQ_SRC_KS32 : PQ_SRC_KC32;
   constexpr int BK = FORM == PQ_REF_CC ? PQ_SRC_KC32 : FORM == PQ_REF_CBITS ? PQ_SRC_BITSF : FORM == PQ_REF_SS8 ? PQ_SRC_KS8 : PQ_SRC_KS32;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 15, lk = lane >> 4;
@@ -260,8 +334,9 @@ __device__ __forceinline__ void ref_tile(const pq_ref_problem& p, int block, dou
   const int first = KS == 1 ? 0 : wave;
   const bool live = KS == 4 || (m0 < p.M && n0 < p.N);    // uniform for the wavefront
   if (live) {
-    ref_contract<AK, BK, NB, DEPTH>(p.A, p.B, m0, p.M, n0, p.N, p.K, first, KS, li, lk, acc);
-    if constexpr (FORM == PQ_REF_CBITS) {
+    if constexpr (!SUM) ref_contract<AK, BK, NB, DEPTH>(p.A, p.B, m0, p.M, n0, p.N, p.K, first, KS, li, lk, acc);
+    else if (KS == 1 || wave == 0) ref_planes<FORM, NB>(p, m0, n0, li, lk, acc);
+    if constexpr (FORM == PQ_REF_CBITS || FORM == PQ_REF_SUM_CBITS) {
       // the rank-r product rides in the same accumulators; the 1-bit sum carries its scale from here on
       const double sc1 = (double)(p.dev_scale1 ? __fmul_rn(p.scale1, *p.dev_scale1) : p.scale1);
 #pragma unroll
@@ -387,6 +462,8 @@ __global__ __launch_bounds__(256, 2) void ref_gemm_kernel(ref_launch L) {
     case PQ_REF_CS: ref_tile<PQ_REF_CS, NB, KS>(p, blk, LDS, red); break;              \
     case PQ_REF_CBITS: ref_tile<PQ_REF_CBITS, NB, KS>(p, blk, LDS, red); break;          \
     case PQ_REF_SS8: ref_tile<PQ_REF_SS8, NB, KS>(p, blk, LDS, red); break;        \
+    case PQ_REF_SUM_CBITS: ref_tile<PQ_REF_SUM_CBITS, NB, KS>(p, blk, LDS, red); break;   \
+    case PQ_REF_SUM_SS8: ref_tile<PQ_REF_SUM_SS8, NB, KS>(p, blk, LDS, red); break;       \
     default: ref_tile<PQ_REF_SS, NB, KS>(p, blk, LDS, red);                            \
   }
   if constexpr (BIG) {
@@ -426,7 +503,8 @@ int ref_config(int M, int N, int K) {
 
 }  // namespace
 
-int pq_ref_red_blocks(int M, int N, int K) { return ref_blocks(ref_config(M, N, K), M, N); }
+// (the SUM forms read and add planes: 32x32 tiles, in the launch of the small products)
+int pq_ref_red_blocks(int M, int N, int K) { return ref_blocks(K < 0 ? 1 : ref_config(M, N, K), M, N); }
 
 int pq_launch_ref(pq_ref_problem* p, int n, const pq_reduce_job* jobs, int njobs, hipStream_t s, int prof_label) {
   for (int i = 0; i < n; ++i)
@@ -440,7 +518,7 @@ int pq_launch_ref(pq_ref_problem* p, int n, const pq_reduce_job* jobs, int njobs
     int total = 0;
     for (int i = 0; i < n; ++i) {
       if (p[i].M <= 0 || p[i].N <= 0) continue;
-      p[i].cfg = ref_config(p[i].M, p[i].N, p[i].K);
+      p[i].cfg = p[i].form == PQ_REF_SUM_CBITS || p[i].form == PQ_REF_SUM_SS8 ? 1 : ref_config(p[i].M, p[i].N, p[i].K);
       if ((p[i].cfg == 0) != (big == 1)) continue;
       L.p[L.n] = p[i];
       L.first[L.n++] = total;

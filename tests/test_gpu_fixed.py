@@ -1,0 +1,81 @@
+"""fp32 I/O, calls large enough for the fixed-point form of dX and dW: against the fp64 oracle at sizes where rows, tokens and tiles end
+inside their blocks (bound as for the fp64 products: one rounding to fp32), rows whose elements span the whole range of fp32 and
+cancel (an fp64 sum's own rounding is the bound), and infinities and NaN, which must come out where plain arithmetic has them."""
+import numpy as np
+import pytest
+import torch
+
+from launch_trace import kernels, trace
+from paper_2602_22592_amd import binding as pq
+from paper_2602_22592_amd import workloads as wl
+from test_gpu_ref import test_fp32_products_at_tile_edges as check_fp32
+
+SHAPES = [(1037, 1056, 1120, 40, None), (517, 1568, 1504, 0, 0.02), (2049, 544, 1312, 8, None), (64, 4640, 4096, 16, None)]
+
+
+@pytest.mark.parametrize("T,K,N,r,tau", SHAPES)
+def test_shapes_take_the_form(T, K, N, r, tau):
+    res = trace([dict(op="linear", tokens=T, d_in=K, d_out=N, hp_rank=r, io_dtype=0)])[0]
+    assert res["rc"] == 0, res["error"]
+    assert len(kernels(res, "fixed_rows_kernel")) == 1 and len(kernels(res, "fixed_cols_kernel")) == 1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T,K,N,r,tau", SHAPES)
+def test_against_the_oracle(T, K, N, r, tau):
+    check_fp32(T, K, N, r, tau)
+
+
+def run(dY, T, K, N):
+    c = wl.linear_case(7, T, K, N, hp_rank=0, bf16=False, outlier_count=2, outlier_scale=10.0)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    desc = pq.make_desc(T, K, N, hp_rank=0, io_dtype=pq.PQ_F32, alpha=2.0, beta=0.5)
+    bufs = pq.LinearBuffers(desc)
+    X, W, g = dev(c["X"]), dev(c["W"]), dev(dY)
+    Y, dX, dW, dab = (torch.empty(s, dtype=torch.float32, device="cuda") for s in ((T, N), (T, K), (N, K), (2,)))
+    pq.linear_fwd(desc, X, W, Y, bufs)
+    pq.linear_bwd(desc, g, X, W, bufs, dX, dW, dab)
+    torch.cuda.synchronize()
+    w, x = c["W"].astype(np.float64), c["X"]
+    mu, lam = np.float32(w.mean()), np.float32(np.abs(w).mean())
+    S = np.where(c["W"] >= mu, 1.0, -1.0)
+    gam = np.float32(128.0) / np.maximum(np.abs(x).max(1), np.float32(1e-5)).astype(np.float32)
+    q = np.clip(np.rint(x * gam[:, None]), -128, 127).astype(np.float64)
+    return dX.cpu().numpy(), dW.cpu().numpy(), dab.cpu().numpy(), S, q, gam.astype(np.float64), np.float64(np.float32(0.5) * lam)
+
+
+@pytest.mark.gpu
+def test_wide_ranges_and_cancellation():
+    T, K, N = 1030, 1056, 1120
+    rng = np.random.default_rng(5)
+    dY = (rng.standard_normal((T, N)) * np.exp(rng.uniform(-40, 40, (T, N)))).astype(np.float32)
+    dY[:, 1::2] -= dY[:, 0::2]                        # pairs that nearly cancel where their signs agree
+    dX, dW, _, S, q, gam, bl = run(dY, T, K, N)
+    rows, cols = rng.choice(T, 24, replace=False), rng.choice(N, 24, replace=False)
+    L = np.longdouble
+    ref = (dY[rows].astype(L) @ S.astype(L)) * bl
+    # one rounding to fp32, and what N additions in fp64 may lose against the row's largest element
+    bound = 2.0**-24 * np.abs(ref) + bl * N * 2.0**-53 * np.abs(dY[rows]).max(1, keepdims=True)
+    assert (np.abs(dX[rows] - ref) <= bound).all()
+    E = dY[:, cols].astype(L) / gam[:, None]
+    ref = (E.T @ q.astype(L)) * 0.5
+    bound = 2.0**-24 * np.abs(ref) + 0.5 * T * 128 * 2.0**-53 * np.abs(E).max(0)[:, None]
+    assert (np.abs(dW[cols] - ref) <= bound).all()
+
+
+@pytest.mark.gpu
+def test_infinities_and_nan():
+    T, K, N = 1030, 1056, 1120
+    rng = np.random.default_rng(6)
+    dY = rng.standard_normal((T, N)).astype(np.float32)
+    dY[3, 17] = np.inf
+    dY[700, [5, 900]] = np.inf, -np.inf
+    dY[1029, 1119] = np.nan
+    dX, dW, dab, S, q, gam, bl = run(dY, T, K, N)
+    with np.errstate(invalid="ignore"):
+        for got, ref in ((dX, (dY.astype(np.float64) @ S) * bl), (dW, 0.5 * (dY.astype(np.float64).T @ (q / gam[:, None])))):
+            assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+            assert np.array_equal(np.sign(got[np.isinf(ref)]), np.sign(ref[np.isinf(ref)]))
+            ok = np.isfinite(ref)
+            assert np.abs(got[ok] - ref[ok]).max() <= 1e-6 * np.abs(ref[ok]).max()
+    assert np.isnan(dab[1])
