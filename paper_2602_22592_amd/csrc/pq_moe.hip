@@ -384,20 +384,56 @@ __global__ __launch_bounds__(256) void combine_fwd_kernel(uint16_t* __restrict__
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (t >= T) return;
   uint4* y4 = reinterpret_cast<uint4*>(Y + (size_t)t * d);
-  for (int c = lane; c < d / 8; c += 64) {
-    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int j = 0; j < k; ++j) {
-      const float gt = gate[t * k + j];
-      float v[8];
-      unpack8(reinterpret_cast<const uint4*>(Ys + (size_t)inv[t * k + j] * d)[c], v);
+  const int n = d / 8;
+  // four vectors of Y and of two slots in flight (past the end: the last vector, dropped); one at a time it was a chain of memory
+  // latencies (1531 tokens, 3104 columns, two slots each: 14 us, now 8)
+  for (int cb = lane; cb < n; cb += 256) {
+    uint4 yv[4];
+    float acc[4][8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] += gt * v[i];
+    for (int q = 0; q < 4; ++q) {
+      yv[q] = y4[min(cb + 64 * q, n - 1)];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[q][i] = 0.0f;
     }
-    float y[8];
-    unpack8(y4[c], y);
+    for (int j = 0; j < k; j += 2) {
+      const int j1 = min(j + 1, k - 1);
+      const float g0 = gate[t * k + j], g1 = gate[t * k + j1];
+      const uint4* s0 = reinterpret_cast<const uint4*>(Ys + (size_t)inv[t * k + j] * d);
+      const uint4* s1 = reinterpret_cast<const uint4*>(Ys + (size_t)inv[t * k + j1] * d);
+      uint4 a[4], b[4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) y[i] += alpha * acc[i];
-    y4[c] = pack8(y);
+      for (int q = 0; q < 4; ++q) a[q] = s0[min(cb + 64 * q, n - 1)];
+      if (j + 1 < k) {                                // uniform
+#pragma unroll
+        for (int q = 0; q < 4; ++q) b[q] = s1[min(cb + 64 * q, n - 1)];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float v[8];
+        unpack8(a[q], v);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[q][i] += g0 * v[i];
+      }
+      if (j + 1 < k) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float v[8];
+          unpack8(b[q], v);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) acc[q][i] += g1 * v[i];
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (cb + 64 * q >= n) break;
+      float y[8];
+      unpack8(yv[q], y);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) y[i] += alpha * acc[q][i];
+      y4[cb + 64 * q] = pack8(y);
+    }
   }
 }
 
@@ -414,12 +450,16 @@ __device__ __forceinline__ float router_dlogit(const float* __restrict__ rd, con
   return acc;
 }
 
-// dWr partials: part[tc][e][c] = sum_{t in chunk tc} dlogit[t,e] * X[t,c]   (chunks of 256 tokens).
-// A workgroup covers 256 columns of one chunk: thread = (token subgroup sg, column group cg); it walks the
-// 32 tokens t0 + sg, t0 + sg + 8, ... with 16-byte loads of 8 columns, then the 8 subgroups are summed in LDS
+// Tokens to a chunk: 128, or 32 while 128 leave CUs without a workgroup (1531 tokens, 1056 columns, four experts: 60 workgroups
+// 18 us, 240 of them 6; 8192 tokens, 2048 columns: 128 20 us, 32 27).
+int dwr_chunk(int T, int d) { return ((d + 255) / 256) * ((T + 127) / 128) < 256 ? 32 : 128; }
+
+// dWr partials: part[tc][e][c] = sum_{t in chunk tc} dlogit[t,e] * X[t,c].
+// A workgroup covers 256 columns of one chunk: thread = (token subgroup sg, column group cg); it walks every
+// eighth token t0 + sg, t0 + sg + 8, ... with 16-byte loads of 8 columns, then the 8 subgroups are summed in LDS
 // in a fixed order.
-constexpr int DWR_CHUNK = 128;                      // tokens per workgroup (a multiple of 64)
 // dlogit is formed here, by every column block for itself; the first one leaves it in memory for the input gradient.
+template <int DWR_CHUNK>
 __global__ __launch_bounds__(256) void dwr_partial_kernel(const float* __restrict__ rd, const int* __restrict__ inv, const int* __restrict__ idx,
                                                           const float* __restrict__ probs, float alpha, int k, float* __restrict__ dlogit,
                                                           const uint16_t* __restrict__ X, int T, int d, int E, float* __restrict__ part) {
@@ -447,14 +487,15 @@ __global__ __launch_bounds__(256) void dwr_partial_kernel(const float* __restric
 #pragma unroll
       for (int j = 0; j < 8; ++j) acc[u][j] = 0.0f;
     if (okc) {
-      for (int grp = 0; grp < DWR_CHUNK / 64; ++grp) {   // eight of the subgroup's tokens at a time, their loads issued together
-        uint4 xv[8];
+      constexpr int Q = DWR_CHUNK < 64 ? DWR_CHUNK / 8 : 8;
+      for (int grp = 0; grp < DWR_CHUNK / (8 * Q); ++grp) {   // Q of the subgroup's tokens at a time, their loads issued together
+        uint4 xv[Q];
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
-          xv[q] = *reinterpret_cast<const uint4*>(X + (size_t)min(t0 + sg + 8 * (8 * grp + q), T - 1) * d + c0);
+        for (int q = 0; q < Q; ++q)
+          xv[q] = *reinterpret_cast<const uint4*>(X + (size_t)min(t0 + sg + 8 * (Q * grp + q), T - 1) * d + c0);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const int tt = sg + 8 * (8 * grp + q);
+        for (int q = 0; q < Q; ++q) {
+          const int tt = sg + 8 * (Q * grp + q);
           const float4 ga = *reinterpret_cast<const float4*>(&sdl[tt][0]), gb = *reinterpret_cast<const float4*>(&sdl[tt][4]);
           const float g[8] = {ga.x, ga.y, ga.z, ga.w, gb.x, gb.y, gb.z, gb.w};
           float x[8];
@@ -515,23 +556,37 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(uint16_t* __restrict__
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (t >= T) return;
   uint4* x4 = reinterpret_cast<uint4*>(dX + (size_t)t * d);
-  for (int c = lane; c < d / 8; c += 64) {
-    float acc[8];
-    unpack8(x4[c], acc);
-    for (int j = 0; j < k; ++j) {
-      float v[8];
-      unpack8(reinterpret_cast<const uint4*>(dXs + (size_t)inv[t * k + j] * d)[c], v);
+  const int n = d / 8;
+  // four vectors of a row in flight (past the end: the last vector, dropped), and the next row's while one is added
+  for (int cb = lane; cb < n; cb += 256) {
+    float acc[4][8];
+    uint4 x[4], w[4];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] += v[i];
-    }
-    for (int e = 0; e < E; ++e) {
-      const float dl = dlogit[(size_t)t * E + e];
-      float w[8];
-      unpack8(reinterpret_cast<const uint4*>(Wr + (size_t)e * d)[c], w);
+    for (int q = 0; q < 4; ++q) x[q] = x4[min(cb + 64 * q, n - 1)];
+    const int rows = k + E;                           // the slots' rows, then the router's
+    auto row = [&](int j) { return reinterpret_cast<const uint4*>(j < k ? dXs + (size_t)inv[t * k + j] * d : Wr + (size_t)(j - k) * d); };
+    auto fetch = [&](int j) {
+      const uint4* r = row(j);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] += dl * w[i];
+      for (int q = 0; q < 4; ++q) w[q] = r[min(cb + 64 * q, n - 1)];
+    };
+    fetch(0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) unpack8(x[q], acc[q]);
+    for (int j = 0; j < rows; ++j) {
+      const float f = j < k ? 1.0f : dlogit[(size_t)t * E + j - k];
+      float v[4][8];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) unpack8(w[q], v[q]);
+      fetch(min(j + 1, rows - 1));
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[q][i] += f * v[q][i];
     }
-    x4[c] = pack8(acc);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (cb + 64 * q < n) x4[cb + 64 * q] = pack8(acc[q]);
   }
 }
 
@@ -751,14 +806,18 @@ int pq_launch_combine_fwd(void* Y, const void* Ys, const int* inv, const float* 
   return PQ_OK;
 }
 
-size_t pq_dwr_scratch_bytes(int T, int d, int E) { return (size_t)((T + DWR_CHUNK - 1) / DWR_CHUNK) * E * d * sizeof(float); }
+size_t pq_dwr_scratch_bytes(int T, int d, int E) {
+  const int c = dwr_chunk(T, d);
+  return (size_t)((T + c - 1) / c) * E * d * sizeof(float);
+}
 int pq_launch_dwr(const float* rd, const int* inv, const int* idx, const float* probs, float alpha, int k, float* dlogit, const void* X, int T,
                   int d, int E, float* part, float* dWr, const pq_reduce_job* jobs, hipStream_t s) {
   pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
-  const int nchunks = rd ? (T + DWR_CHUNK - 1) / DWR_CHUNK : 0;
+  const int chunk = dwr_chunk(T, d), nchunks = rd ? (T + chunk - 1) / chunk : 0;
   if (nchunks > 0) {
     dim3 grid((d + 255) / 256, nchunks);
-    dwr_partial_kernel<<<grid, 256, 0, s>>>(rd, inv, idx, probs, alpha, k, dlogit, (const uint16_t*)X, T, d, E, part);
+    if (chunk == 32) dwr_partial_kernel<32><<<grid, 256, 0, s>>>(rd, inv, idx, probs, alpha, k, dlogit, (const uint16_t*)X, T, d, E, part);
+    else dwr_partial_kernel<128><<<grid, 256, 0, s>>>(rd, inv, idx, probs, alpha, k, dlogit, (const uint16_t*)X, T, d, E, part);
     PQ_CHECK_LAUNCH("dwr_partial_kernel");
   }
   dwr_final_kernel<<<(E * d + 255) / 256 + 2, 256, 0, s>>>(part, nchunks, E * d, dWr, jobs[0], jobs[1]);
