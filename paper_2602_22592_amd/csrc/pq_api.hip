@@ -481,14 +481,19 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
   };
   // The weight statistics' first stage and the activation quantiser share a launch (rows of up to 8192 elements stay
   // in registers); when H = X A^T splits its contraction it goes first and the sum of its slabs rides along too.
-  const bool combo = d->w_kind == PQ_W_MASTER && !prequant && T > 0 && K <= (bf16 ? 8192 : 4096);
+  // Packed weights have no statistics to take: the quantiser and the slabs' sum share the launch there.
+  const int H_splits = bf16 && r > 0 && T > 0 ? (H_skinny ? 1 : pq_plan_gemm(T, r, K).splits) : 0;
+  const bool combo = !prequant && T > 0 && K <= (bf16 ? 8192 : 4096) && (d->w_kind == PQ_W_MASTER || H_splits > 1);
   bool H_done = false;
-  int H_splits = 0;
   if (combo && bf16 && r > 0) {
-    H_splits = H_skinny ? 1 : pq_plan_gemm(T, r, K).splits;
     if (int e = launch_H(H_splits > 1)) return e;
     H_done = true;
   }
+  auto launch_combo = [&](const void* w, size_t n, double* part, int nb) -> int {
+    const bool sum = H_done && H_splits > 1;
+    quant_done = true;
+    return pq_launch_wstats_quant(w, d->io_dtype, n, part, nb, X, T, K, Xq, gamma, Xt, s, sum ? (const float*)sk_ws.p : nullptr, H_splits, T, r, H, r);
+  };
   const uint32_t* P;
   const float* mulam;
   if (d->w_kind == PQ_W_MASTER) {
@@ -496,10 +501,7 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
     const int nb = pq_stats_blocks(n);
     double* part = (double*)(ws + L.stat_partials);
     if (combo) {
-      const bool sum = H_done && H_splits > 1;
-      if (int e = pq_launch_wstats_quant(W_or_packed, d->io_dtype, n, part, nb, X, T, K, Xq, gamma, Xt, s, sum ? (const float*)sk_ws.p : nullptr, H_splits,
-                                         T, r, H, r)) return e;
-      quant_done = true;
+      if (int e = launch_combo(W_or_packed, n, part, nb)) return e;
     } else if (int e = pq_launch_wstats_partial(W_or_packed, d->io_dtype, n, part, nb, s)) return e;
     uint32_t* Pt = (N % 32 == 0) ? (uint32_t*)(cx + L.Pt) : nullptr;
     if (hp8) {   // the rows of A and B on the AbsMax grid ride along
@@ -515,6 +517,8 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
   } else {
     P = (const uint32_t*)W_or_packed;
     mulam = mu_lambda;
+    if (combo)
+      if (int e = launch_combo(nullptr, 0, nullptr, 0)) return e;
   }
   if (T == 0) {   // the weight side is still prepared, so a backward with no tokens is well defined
     if (routed)   // ... and empty expert segments are left behind for it
