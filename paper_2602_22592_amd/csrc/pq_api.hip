@@ -1192,7 +1192,8 @@ dffn_layout make_dffn_layout(const pq_decode_ffn_desc& d) {
   L.ws1 = c.take(pq_decode_ws_layout(d1, off));
   L.UG = c.take((size_t)2 * d.n_layers * B * d.d_ffn * 2);
   L.ws2 = c.take(pq_decode_ws_layout(d2, off));
-  L.amax = c.take((size_t)d.n_layers * B * 8 * sizeof(float));   // the parts' maxima of the gated hidden state
+  // maxima of the gated hidden state: of a token's eight parts, at one token per layer of 64 columns each
+  L.amax = c.take((size_t)d.n_layers * (B > 1 ? B * 8 : (d.d_ffn + 63) / 64) * sizeof(float));
   L.total = c.off;
   return L;
 }

@@ -48,6 +48,8 @@ __device__ __forceinline__ float fp16_bits_to_f32(uint16_t h) {
 // by two kernels: one workgroup per (layer, token) doing all of them (any batch), and for batch 1 a fused
 // kernel that also produces the expert hidden states so that a decode call is two launches.
 // ------------------------------------------------------------------------------------------
+constexpr int FFN_MID_PARTS = 8;                     // workgroups per (layer, token) between the FFN's products (see decode_ffn_mid_kernel)
+
 struct prep_shared {
   float red[4];
   double dred[4][8];
@@ -310,38 +312,49 @@ static inline int prep_h_rows(int L, int hidden) { return (long)L * (1 + (hidden
 // hidden state is the exact integer product of the token's codes with a row, de-quantised as
 // fl32(fl32(1/gamma_x) * acc) / gamma_a and rounded to bf16 (stored as fp32).  The token's codes (natural column
 // order) sit in LDS behind its fp32 activations.
-template <bool I8, bool EARLY>
-__global__ __launch_bounds__(256) void decode_prep_h_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wr,
-                                                            const void* __restrict__ hpA_, const float* __restrict__ gA,
-                                                            int K, int E, int r, int topk,
-                                                            int parts, int rows, int8_t* __restrict__ xq, uint32_t* __restrict__ planes,
-                                                            int* __restrict__ rowsum, float* __restrict__ gamma,
-                                                            int* __restrict__ idx, float* __restrict__ gate,
-                                                            float* __restrict__ h, int* __restrict__ zero_rs) {
-  extern __shared__ __attribute__((aligned(16))) float xs[];
-  __shared__ prep_shared sh;
+struct prep_h_params {
+  const uint16_t *X, *Wr;
+  const void* hpA;
+  const float* gA;
+  int K, E, r, topk, parts, rows;
+  int8_t* xq;
+  uint32_t* planes;
+  int* rowsum;
+  float* gamma;
+  int* idx;
+  float *gate, *h;
+  int* zero_rs;
+};
+// Workgroup b of L * p.parts; FIRST: the first part it may be (1: the quantiser is not among them).
+template <bool I8, bool EARLY, int FIRST>
+__device__ __forceinline__ void prep_h_body(const prep_h_params& p, int b, int L, float* xs, prep_shared& sh) {
+  const uint16_t* __restrict__ X = p.X;
+  const uint16_t* __restrict__ Wr = p.Wr;
+  const void* __restrict__ hpA_ = p.hpA;
+  const float* __restrict__ gA = p.gA;
+  const int K = p.K, E = p.E, r = p.r, topk = p.topk, parts = p.parts, rows = p.rows;
+  int* __restrict__ idx = p.idx;
+  float* __restrict__ gate = p.gate;
+  float* __restrict__ h = p.h;
   const uint16_t* __restrict__ hpA = (const uint16_t*)hpA_;
   // Consecutive workgroups go to different XCDs (each with its own L2): number them so that all parts of a
   // layer land on one XCD and its router matrix and activations are fetched from memory once.
   int layer, part;
-  {
-    const int L = (int)gridDim.x / parts, b = blockIdx.x;
-    if ((L & 7) == 0) {
-      const int g = b / (8 * parts), rem = b - g * (8 * parts);
-      layer = 8 * g + (rem & 7);
-      part = rem >> 3;
-    } else {
-      layer = b / parts;
-      part = b - layer * parts;
-    }
+  if ((L & 7) == 0) {
+    const int g = b / (8 * parts), rem = b - g * (8 * parts);
+    layer = 8 * g + (rem & 7);
+    part = FIRST + (rem >> 3);
+  } else {
+    layer = b / parts;
+    part = FIRST + b - layer * parts;
   }
   const size_t tok = layer;
   uint4 first[8];
   if (EARLY && part > 0) prep_router_first(Wr, layer, K, E, first);
   const float amax = prep_load_x(X, tok, K, xs);
-  if (part == 0) {
-    if (zero_rs && threadIdx.x == 0) zero_rs[tok] = 0;   // see decode_prep_kernel
-    prep_quantise(amax, tok, K, xs, sh, xq, planes, rowsum, gamma);
+  if (FIRST == 0 && part == 0) {
+    if (p.zero_rs && threadIdx.x == 0) p.zero_rs[tok] = 0;   // see decode_prep_kernel
+    prep_quantise(amax, tok, K, xs, sh, p.xq, p.planes, p.rowsum, p.gamma);
     return;
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -451,6 +464,12 @@ __global__ __launch_bounds__(256) void decode_prep_h_kernel(const uint16_t* __re
     }
   }
   if (part == 1) prep_gates(tok, E, topk, sh, idx, gate);
+}
+template <bool I8, bool EARLY>
+__global__ __launch_bounds__(256) void decode_prep_h_kernel(prep_h_params p) {
+  extern __shared__ __attribute__((aligned(16))) float xs[];
+  __shared__ prep_shared sh;
+  prep_h_body<I8, EARLY, 0>(p, blockIdx.x, (int)gridDim.x / p.parts, xs, sh);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -663,6 +682,8 @@ static bool launch_h_grouped(const uint16_t* X, const uint16_t* A, const int* id
 constexpr int GEMV_ITERS = 8;                       // 8 rows per iteration -> 64 rows per wavefront
 constexpr int GEMV_ROWS_PER_WAVE = 8 * GEMV_ITERS;
 constexpr int GEMV_ROWS_PER_BLOCK = 4 * GEMV_ROWS_PER_WAVE;
+
+__device__ __forceinline__ float silu_f(float x) { return x / (1.0f + expf(-x)); }
 
 struct gemv_params {
   const uint32_t* P;      // [L][N][K/32]
@@ -1033,6 +1054,121 @@ __global__ __launch_bounds__(256) void decode_gemv_tiled_kernel(gemv_params p) {
       const float sc = fp16_bits_to_f32(p.scale[layer]) / p.gamma[xl];
       p.Y[(size_t)layer * p.N + row] = f32_to_bf16(__fmul_rn(sc, (float)acc) + p.alpha * yy);
     }
+  }
+}
+
+// Up and gate products of the FFN for one token per layer, with the experts' hidden pairs beside them: the first nh workgroups
+// are those of prep_h_body (router and hidden rows: nothing here waits for them, so their chain of latencies runs under
+// the weight stream), the others own 64 rows of both matrices of a layer.  U and G of a row meet in one workgroup, so the
+// largest |silu(G) U| of its 64 columns leaves with them (amax[layer][group]) and the pass that collected it goes; an integer
+// maximum into one cell per layer took 4 us longer at 32 layers.  Bound by the weight stream once there are many layers
+// (32 of 4096/11008: 428 MB in 75 us, 5.7 TB/s) and by the chain of launches below that: five launches became four,
+// one layer of 1024/2048 21.4 -> 19.8 us, two of 2048/5504 29.8 -> 27.5, 32 of 1024/4096 41.5 -> 38.1, 32 of 4096/11008 128.4 -> 128.8.
+__global__ __launch_bounds__(256) void decode_ffn_upgate_kernel(gemv_params p, prep_h_params hp, int L, int nh, float* __restrict__ amax) {
+  extern __shared__ __attribute__((aligned(16))) float xs[];   // hidden rows: the token as fp32
+  __shared__ prep_shared sh;
+  __shared__ int s_dot[2][4][64];
+  __shared__ float s_u[64];
+  if ((int)blockIdx.x < nh) {                        // uniform
+    prep_h_body<false, false, 1>(hp, blockIdx.x, L, xs, sh);
+    return;
+  }
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nw = p.K / 32, nq = nw / 4;
+  const int G = (p.N + 63) / 64;
+  const int layer = ((int)blockIdx.x - nh) / G, grp = ((int)blockIdx.x - nh) - layer * G;
+  constexpr int GPB = 2;                             // the two matrices' groups
+  const uint32_t* __restrict__ planes = p.planes + (size_t)layer * 8 * nw;
+
+  int a[GPB][8];
+#pragma unroll
+  for (int g = 0; g < GPB; ++g)
+#pragma unroll
+    for (int pp = 0; pp < 8; ++pp) a[g][pp] = 0;
+  // 32 chunks of 128 columns per pass, 8 per wavefront.  Whole passes run without any condition, so the
+  // loads stay in flight while the wait counter releases one chunk at a time; the ragged last pass
+  // clamps its addresses and skips the chunks beyond the row.
+  auto pass = [&](const int q0, auto full_tag) {
+    constexpr bool FULL = decltype(full_tag)::value;
+    uint4 w[GPB][8];
+#pragma unroll
+    for (int g = 0; g < GPB; ++g) {
+      const uint4* __restrict__ Pg = reinterpret_cast<const uint4*>(p.P) + ((size_t)(2 * layer + g) * G + grp) * nq * 64;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int q = q0 + 4 * i + wave;
+        w[g][i] = nt_load16(&Pg[(size_t)((FULL || q < nq) ? q : nq - 1) * 64 + lane]);
+      }
+    }
+    // full passes request the 32 plane words of chunk i+1 (scalar loads, uniform address) before the
+    // popcounts of chunk i start
+    if constexpr (FULL) {
+      uint32_t pc[32], pn[32];
+      {
+        const uint32_t* pl = planes + (size_t)(q0 + wave) * 32;
+#pragma unroll
+        for (int t = 0; t < 32; ++t) pc[t] = pl[t];
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        if (i + 1 < 8) {
+          const uint32_t* pl = planes + (size_t)(q0 + 4 * (i + 1) + wave) * 32;
+#pragma unroll
+          for (int t = 0; t < 32; ++t) pn[t] = pl[t];
+        }
+#pragma unroll
+        for (int pp = 0; pp < 8; ++pp)
+#pragma unroll
+          for (int g = 0; g < GPB; ++g)
+            a[g][pp] += __builtin_popcount(w[g][i].x & pc[4 * pp]) + __builtin_popcount(w[g][i].y & pc[4 * pp + 1]) +
+                        __builtin_popcount(w[g][i].z & pc[4 * pp + 2]) + __builtin_popcount(w[g][i].w & pc[4 * pp + 3]);
+#pragma unroll
+        for (int t = 0; t < 32; ++t) pc[t] = pn[t];
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int q = q0 + 4 * i + wave;
+        if (q < nq) {                                  // wave-uniform
+          const uint32_t* pl = planes + (size_t)q * 32;
+#pragma unroll
+          for (int pp = 0; pp < 8; ++pp)
+#pragma unroll
+            for (int g = 0; g < GPB; ++g)
+              a[g][pp] += __builtin_popcount(w[g][i].x & pl[4 * pp]) + __builtin_popcount(w[g][i].y & pl[4 * pp + 1]) +
+                          __builtin_popcount(w[g][i].z & pl[4 * pp + 2]) + __builtin_popcount(w[g][i].w & pl[4 * pp + 3]);
+        }
+      }
+    }
+  };
+  int q0 = 0;
+  for (; q0 + 32 <= nq; q0 += 32) pass(q0, std::true_type{});
+  if (q0 < nq) pass(q0, std::false_type{});
+
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    int d = 0;
+#pragma unroll
+    for (int pp = 0; pp < 7; ++pp) d += a[g][pp] << pp;
+    s_dot[g][wave][lane] = d - (a[g][7] << 7);
+  }
+  __syncthreads();
+  const int row = grp * 64 + lane;
+  float y = 0.0f;
+  if (wave < 2 && row < p.N) {
+    const int set = 2 * layer + wave;
+    const int acc = 2 * (s_dot[wave][0][lane] + s_dot[wave][1][lane] + s_dot[wave][2][lane] + s_dot[wave][3][lane]) - p.rowsum[layer];
+    if (p.acc_out) p.acc_out[(size_t)set * p.N + row] = acc;
+    const uint16_t o = f32_to_bf16(__fmul_rn(fp16_bits_to_f32(p.scale[set]) / p.gamma[layer], (float)acc));
+    p.Y[(size_t)set * p.N + row] = o;
+    y = bf16_to_f32(o);
+  }
+  if (wave == 0) s_u[lane] = y;
+  __syncthreads();
+  if (wave == 1) {
+    const float m = wave_max(row < p.N ? fmaxf(0.0f, fabsf(silu_f(y) * s_u[lane])) : 0.0f);
+    if (lane == 0) amax[(size_t)layer * G + grp] = m;
   }
 }
 
@@ -1555,12 +1691,9 @@ __global__ __launch_bounds__(256, 4) void decode_gemm16_tiled_kernel(gemm16_para
 // it on the INT8 grid (codes, bit planes, row sum, gamma: the input of the packed down product) and applies the
 // experts' gated unit a = silu(Gate_e x) * (Up_e x) to the hidden pairs the prep kernel left in hug [topk][2r].
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ float silu_f(float x) { return x / (1.0f + expf(-x)); }
 // Workgroups per (layer, token): each owns every eighth group of 256 columns of Hd.  The row's maximum decides gamma, so
 // the work is two passes (two launches): the parts' maxima, then the quantiser of the own groups (6 KB of LDS per
 // workgroup, all workgroups of a batch resident at once); the row sum is added up over the parts with integer atomics.
-constexpr int FFN_MID_PARTS = 8;
-
 // Hd = silu(G) * U for one vector (eight columns) of a row
 __device__ __forceinline__ void ffn_hd8(const uint4& uu, const uint4& gg, float* hd) {
   const uint32_t uw[4] = {uu.x, uu.y, uu.z, uu.w}, gw[4] = {gg.x, gg.y, gg.z, gg.w};
@@ -1568,6 +1701,15 @@ __device__ __forceinline__ void ffn_hd8(const uint4& uu, const uint4& gg, float*
   for (int t = 0; t < 4; ++t) {
     hd[2 * t] = silu_f(__uint_as_float(gw[t] << 16)) * __uint_as_float(uw[t] << 16);
     hd[2 * t + 1] = silu_f(__uint_as_float(gw[t] & 0xFFFF0000u)) * __uint_as_float(uw[t] & 0xFFFF0000u);
+  }
+}
+
+// The experts' gated unit a = silu(Gate_e x) * (Up_e x) of a row's selected experts, by one workgroup.
+__device__ __forceinline__ void ffn_expert_act(int row, int r, int topk, const float* __restrict__ hug, float* __restrict__ act) {
+  for (int o = threadIdx.x; o < topk * r; o += 256) {
+    const int j = o / r, i = o - j * r;
+    const float* hp = hug + ((size_t)row * topk + j) * 2 * r;
+    act[(size_t)row * topk * r + o] = silu_f(hp[r + i]) * hp[i];
   }
 }
 
@@ -1593,12 +1735,7 @@ __global__ __launch_bounds__(256) void decode_ffn_amax_kernel(const uint16_t* __
       for (int t = 0; t < 8; ++t) amax = fmaxf(amax, fabsf(hd[t]));
     }
   }
-  if (part == 0)
-    for (int o = tid; o < topk * r; o += 256) {
-      const int j = o / r, i = o - j * r;
-      const float* hp = hug + ((size_t)row * topk + j) * 2 * r;
-      act[(size_t)row * topk * r + o] = silu_f(hp[r + i]) * hp[i];
-    }
+  if (part == 0) ffn_expert_act(row, r, topk, hug, act);
   amax = wave_max(amax);
   if ((tid & 63) == 0) red[tid >> 6] = amax;
   __syncthreads();
@@ -1607,21 +1744,24 @@ __global__ __launch_bounds__(256) void decode_ffn_amax_kernel(const uint16_t* __
 
 // Pass 2: the row's maximum from the eight parts, then the part's own column groups again (from cache) through the
 // quantiser: codes, bit planes, gamma by part 0, the row sum by integer atomics.
+// nmax: maxima per row, 8 from pass 1 or one per 64 columns from the launch of the up and gate products; there is no pass 1
+// in the second case, and the last part forms act (hug not null).
 __global__ __launch_bounds__(256) void decode_ffn_mid_kernel(const uint16_t* __restrict__ UG, int B, int F,
-                                                             const float* __restrict__ amax_part,
+                                                             const float* __restrict__ amax_part, int nmax, int r, int topk,
+                                                             const float* __restrict__ hug, float* __restrict__ act,
                                                              int8_t* __restrict__ xq, uint32_t* __restrict__ planes,
                                                              int* __restrict__ rowsum, float* __restrict__ gamma) {
   extern __shared__ __attribute__((aligned(16))) float xs[];   // this part's column groups of Hd as fp32
   __shared__ prep_shared sh;
+  __shared__ float red[4];
   // row = (layer, token); U and G of a layer are two weight sets' outputs, [2 layer + {0, 1}][B][F]
   const int row = blockIdx.x / FFN_MID_PARTS, part = blockIdx.x % FFN_MID_PARTS, tid = threadIdx.x;
   const int lay = row / B, tok = row - lay * B;
   const uint4* u4 = reinterpret_cast<const uint4*>(UG + ((size_t)(2 * lay) * B + tok) * F);
   const uint4* g4 = reinterpret_cast<const uint4*>(UG + ((size_t)(2 * lay + 1) * B + tok) * F);
   const int nvec = F / 8;
-  float amax = 0.0f;
-#pragma unroll
-  for (int q = 0; q < FFN_MID_PARTS; ++q) amax = fmaxf(amax, amax_part[(size_t)row * FFN_MID_PARTS + q]);
+  float amax = tid < nmax ? amax_part[(size_t)row * nmax + tid] : 0.0f;      // nmax <= 256
+  if (hug && part == FFN_MID_PARTS - 1) ffn_expert_act(row, r, topk, hug, act);
   for (int gi = tid >> 5; (part + FFN_MID_PARTS * gi) * 32 < nvec; gi += 8) {
     const int c = (part + FFN_MID_PARTS * gi) * 32 + (tid & 31);
     float hd[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -1630,7 +1770,10 @@ __global__ __launch_bounds__(256) void decode_ffn_mid_kernel(const uint16_t* __r
     *reinterpret_cast<float4*>(dst) = make_float4(hd[0], hd[1], hd[2], hd[3]);
     *reinterpret_cast<float4*>(dst + 4) = make_float4(hd[4], hd[5], hd[6], hd[7]);
   }
-  __syncthreads();                                    // xs complete
+  amax = wave_max(amax);
+  if ((tid & 63) == 0) red[tid >> 6] = amax;
+  __syncthreads();                                    // xs and red complete
+  amax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
   prep_quantise_own(amax, (size_t)row, F, xs, sh, xq, planes, rowsum, gamma, part, FFN_MID_PARTS);
 }
 
@@ -1664,6 +1807,7 @@ static int decode_raise_lds_limits() {
     set((const void*)decode_prep_h_kernel<false, true>);
     set((const void*)decode_prep_h_kernel<true, false>);
     set((const void*)decode_prep_h_kernel<true, true>);
+    set((const void*)decode_ffn_upgate_kernel);
     set((const void*)decode_ffn_mid_kernel);
   });
   return rc;
@@ -1766,7 +1910,8 @@ static int launch_decode_ffn_batch(int L, int B, int D, int F, int r, int E, int
     pq_prof_scope prof(PQP_SWIGLU, s);
     decode_ffn_amax_kernel<<<L * B * FFN_MID_PARTS, 256, 0, s>>>((const uint16_t*)UG, B, F, r, topk, hug, act, amax_part);
     PQ_CHECK_LAUNCH("decode_ffn_amax_kernel");
-    decode_ffn_mid_kernel<<<L * B * FFN_MID_PARTS, 256, ffn_mid_lds_bytes(F), s>>>((const uint16_t*)UG, B, F, amax_part, xq2, pl2, rs2, gm2);
+    decode_ffn_mid_kernel<<<L * B * FFN_MID_PARTS, 256, ffn_mid_lds_bytes(F), s>>>((const uint16_t*)UG, B, F, amax_part, FFN_MID_PARTS, r, topk, nullptr,
+                                                                                  nullptr, xq2, pl2, rs2, gm2);
     PQ_CHECK_LAUNCH("decode_ffn_mid_kernel");
   }
   {  // down product + experts' down projections
@@ -1797,27 +1942,25 @@ int pq_launch_decode_ffn(int L, int B, int D, int F, int r, int E, int topk, flo
   float* gm1 = (float*)(w1 + o1[3]); int* idx = (int*)(w1 + o1[4]); float* gate = (float*)(w1 + o1[5]); float* hug = (float*)(w1 + o1[6]);
   int8_t* xq2 = (int8_t*)(w2 + o2[0]); uint32_t* pl2 = (uint32_t*)(w2 + o2[1]); int* rs2 = (int*)(w2 + o2[2]);
   float* gm2 = (float*)(w2 + o2[3]); float* act = (float*)(w2 + o2[6]);
-  {  // quantiser of x, router, expert hidden pairs [Up_e x ; Gate_e x]
+  {  // quantiser of x
     pq_prof_scope prof(PQP_DECODE_PREP, s);
-    const int rows = prep_h_rows(L, topk * 2 * r), parts = 1 + (topk * 2 * r + rows - 1) / rows;
-    const auto prep = prep_early((long)L * parts) ? decode_prep_h_kernel<false, true> : decode_prep_h_kernel<false, false>;
-    prep<<<L * parts, 256, (size_t)D * sizeof(float), s>>>((const uint16_t*)X, (const uint16_t*)Wr, UpGate, nullptr, D, E, 2 * r, topk, parts, rows,
-                                                           xq1, pl1, rs1, gm1, idx, gate, hug, rs2);
-    PQ_CHECK_LAUNCH("decode_prep_h_kernel");
+    decode_prep_kernel<false><<<L, 256, (size_t)D * sizeof(float), s>>>((const uint16_t*)X, (const uint16_t*)Wr, 1, D, 0, 0, xq1, pl1, rs1, gm1, nullptr,
+                                                                        nullptr, rs2);
+    PQ_CHECK_LAUNCH("decode_prep_kernel");
   }
-  {  // U and G: 2 L weight sets, each pair reading its layer's token once quantised
+  {  // U, G and the largest |Hd|; beside them the router and the expert hidden pairs [Up_e x ; Gate_e x]
     pq_prof_scope prof(PQP_DECODE_MAIN, s);
     gemv_params p{packed_upgate, scale_upgate, pl1, rs1, gm1, nullptr, nullptr, nullptr, nullptr, (uint16_t*)UG, acc_upgate,
                   F, D, E, 0, 0, alpha, nullptr, 2};
-    dim3 grid((F + 63) / 64, 2 * L);
-    decode_gemv_tiled_kernel<1, false><<<grid, 256, 0, s>>>(p);
-    PQ_CHECK_LAUNCH("decode_gemv_tiled_kernel");
+    const int rows = prep_h_rows(L, topk * 2 * r), parts = (topk * 2 * r + rows - 1) / rows;
+    const prep_h_params hp{(const uint16_t*)X, (const uint16_t*)Wr, UpGate, nullptr, D, E, 2 * r, topk, parts, rows,
+                           nullptr, nullptr, nullptr, nullptr, idx, gate, hug, nullptr};
+    decode_ffn_upgate_kernel<<<L * (parts + (F + 63) / 64), 256, (size_t)D * sizeof(float), s>>>(p, hp, L, L * parts, amax_part);
+    PQ_CHECK_LAUNCH("decode_ffn_upgate_kernel");
   }
   {  // gated unit, quantiser of Hd, experts' gated unit
     pq_prof_scope prof(PQP_SWIGLU, s);
-    decode_ffn_amax_kernel<<<L * FFN_MID_PARTS, 256, 0, s>>>((const uint16_t*)UG, 1, F, r, topk, hug, act, amax_part);
-    PQ_CHECK_LAUNCH("decode_ffn_amax_kernel");
-    decode_ffn_mid_kernel<<<L * FFN_MID_PARTS, 256, ffn_mid_lds_bytes(F), s>>>((const uint16_t*)UG, 1, F, amax_part, xq2, pl2, rs2, gm2);
+    decode_ffn_mid_kernel<<<L * FFN_MID_PARTS, 256, ffn_mid_lds_bytes(F), s>>>((const uint16_t*)UG, 1, F, amax_part, (F + 63) / 64, r, topk, hug, act, xq2, pl2, rs2, gm2);
     PQ_CHECK_LAUNCH("decode_ffn_mid_kernel");
   }
   {  // down product + experts' down projections
@@ -1868,8 +2011,8 @@ int pq_launch_decode(const pq_decode_desc& d, const void* X, const uint32_t* pac
     const bool early = prep_early((long)L * parts);
     const auto prep = i8 ? (early ? decode_prep_h_kernel<true, true> : decode_prep_h_kernel<true, false>)
                          : (early ? decode_prep_h_kernel<false, true> : decode_prep_h_kernel<false, false>);
-    prep<<<L * parts, 256, (size_t)K * (i8 ? 5 : sizeof(float)), s>>>((const uint16_t*)X, (const uint16_t*)Wr, hpA, i8 ? gA : nullptr, K, E, r, d.top_k, parts,
-                                                                      rows, xq, planes, rowsum, gamma, idx, gate, h, nullptr);
+    prep<<<L * parts, 256, (size_t)K * (i8 ? 5 : sizeof(float)), s>>>(prep_h_params{(const uint16_t*)X, (const uint16_t*)Wr, hpA, i8 ? gA : nullptr, K, E, r,
+                                                                                    d.top_k, parts, rows, xq, planes, rowsum, gamma, idx, gate, h, nullptr});
     PQ_CHECK_LAUNCH("decode_prep_h_kernel");
   } else {
     {

@@ -124,3 +124,11 @@ def test_decode_ffn_largest_d_ffn():
     check(1, 128, 16384, 2, 8, 1)
     print("decode FFN d_ffn = 16384, 16 tokens", flush=True)
     check(1, 128, 16384, 2, 64, 1, B=16)
+
+
+@pytest.mark.parametrize("L,D,F,E,r,k", [(8, 384, 256, 4, 8, 3),        # hidden rows dealt over the XCDs
+                                         (3, 5248, 256, 2, 8, 2),       # one whole pass of 32 chunks and a ragged one
+                                         (1, 16384, 128, 2, 16, 1)])    # 64 KB of LDS for the token
+def test_decode_ffn_one_token_edges(L, D, F, E, r, k):
+    print(f"decode FFN edges: L={L} D={D} F={F} E={E} r={r} k={k}", flush=True)
+    check(L, D, F, E, r, k)
