@@ -467,11 +467,16 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
     e.C = H; e.ldc = r; e.out_kind = ok;
     H_skinny = pq_skinny_applies(T, r, K, A, B, e);
   }
+  auto H_ref = [&]() {
+    pq_epilogue e = epi_zero();
+    e.C = H; e.ldc = r; e.out_kind = PQ_OUT_F32;
+    return ref_problem(PQ_REF_CC, T, r, K, {X, K, PQ_SRC_KC32, nullptr}, {hpA, K, PQ_SRC_KC32, nullptr}, e);
+  };
   auto launch_H = [&](bool defer) -> int {
     pq_epilogue e = epi_zero();
     e.C = H; e.ldc = r; e.out_kind = ok; e.defer_reduce = defer ? 1 : 0;
     if (!bf16) {
-      pq_ref_problem p = ref_problem(PQ_REF_CC, T, r, K, {X, K, PQ_SRC_KC32, nullptr}, {hpA, K, PQ_SRC_KC32, nullptr}, e);
+      pq_ref_problem p = H_ref();
       return pq_launch_ref(&p, 1, nullptr, 0, s, PQP_GEMM_HP_H);
     }
     pq_operand A{X, K, PQ_SRC_KC16, nullptr};
@@ -510,6 +515,9 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
       const pq_quant_rows_job jobs[2] = {{hpA, d->hp_rank, K, (int8_t*)(c8 + H8.Aq), (float*)(c8 + H8.gA), (uint16_t*)(c8 + H8.At)},
                                          {hpB, N, d->hp_rank, (int8_t*)(c8 + H8.Bq), (float*)(c8 + H8.gB), (uint16_t*)(c8 + H8.Bt)}};
       if (int e = pq_launch_pack_quant_rows(W_or_packed, N, K, part, nb, (uint32_t*)(cx + L.P), Pt, (float*)(cx + L.mulam), jobs, s)) return e;
+    } else if (!bf16 && r > 0 && pq_ref_rides(T, r, K)) {   // H needs nothing of the weight: a launch less
+      if (int e = pq_launch_ref_pack(H_ref(), (const float*)W_or_packed, N, K, part, nb, (uint32_t*)(cx + L.P), Pt, (float*)(cx + L.mulam), s)) return e;
+      H_done = true;
     } else if (int e = pq_launch_pack(W_or_packed, d->io_dtype, N, K, part, nb, (uint32_t*)(cx + L.P), Pt,
                                       (float*)(cx + L.mulam), s)) return e;
     P = (const uint32_t*)(cx + L.P);
@@ -537,6 +545,9 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
                        pq_plan_fuses(pq_plan_gemm(T, N, K, true, true, PQ_PLAN_SIGNS));
   if (r > 0 && !H_done)
     if (int err = launch_H(false)) return err;
+  if (!bf16 && r > 0 && d->alpha != 0.0f && pq_ref_linear_applies(T, N, K))   // both branches in one launch
+    return pq_launch_ref_linear({Xq, P, mulam + 1, gamma, {H, r, PQ_SRC_KC32, nullptr}, {hpB, r, PQ_SRC_KC32, nullptr}, (float*)Y, T, N, K, r,
+                                 d->alpha, d->beta}, s);
   {  // 1-bit branch: Y = fl32(fl32(beta*lambda)/gamma_t) * acc   [+ alpha * H B^T when fused]
     pq_operand A{Xq, K, PQ_SRC_KC8, nullptr};
     pq_operand B{P, K / 8, PQ_SRC_BITS8, nullptr};

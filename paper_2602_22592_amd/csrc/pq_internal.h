@@ -247,6 +247,22 @@ int pq_ref_red_blocks(int M, int N, int K);   // partial sums one product leaves
 // Up to PQ_REF_MAX independent products in one launch per tile class (at most two launches); up to two scalar reductions of
 // partials that EARLIER launches left ride along.
 int pq_launch_ref(pq_ref_problem* p, int n, const pq_reduce_job* jobs, int njobs, hipStream_t s, int prof_label);
+// One product (form CC) and the packing of an fp32 weight [N][K] in one launch, where the product is small enough to share it.
+bool pq_ref_rides(int M, int N, int K);
+int pq_launch_ref_pack(const pq_ref_problem& p, const float* W, int N, int K, const double* partials, int nparts, uint32_t* P, uint32_t* Pt,
+                       float* mu_lambda, hipStream_t s);
+// Y [T][N] = (beta lambda / gamma_t) * Xq P^T + alpha * H B^T in one launch (H [T][r], B [N][r] fp32 as KC32 operands).
+struct pq_ref_linear {
+  const int8_t* Xq;             // [T][K]
+  const uint32_t* P;            // [N][K/32]
+  const float *lambda, *gamma;
+  pq_operand H, B;
+  float* Y;
+  int T, N, K, r;
+  float alpha, beta;
+};
+bool pq_ref_linear_applies(int T, int N, int K);
+int pq_launch_ref_linear(const pq_ref_linear& p, hipStream_t s);
 
 // ---- pq_fixed.hip -------------------------------------------------------------------------
 // Fixed-point form of dY for the two large contractions of the fp32 backward: row digits Drow [7][T][N] with exponents rexp [T],
@@ -267,7 +283,7 @@ int pq_launch_retile64(const uint32_t* packed, int N, int K, uint32_t* tiled, hi
 int pq_launch_decode_ffn(int L, int B, int D, int F, int r, int E, int topk, float alpha, const void* X, const uint32_t* packed_upgate,
                          const uint16_t* scale_upgate, const uint32_t* packed_down, const uint16_t* scale_down,
                          const void* UpGate, const void* Down, const void* Wr, void* Y, int32_t* acc_upgate, void* UG,
-                         void* ws1, void* ws2, float* amax_part, hipStream_t s);   // amax_part: [L][B][8] floats of scratch
+                         void* ws1, void* ws2, float* amax_part, hipStream_t s);   // amax_part: [L][B][8] floats of scratch, [L][ceil(F/64)] for one token
 
 // ---- pq_moe.hip ---------------------------------------------------------------------------
 int pq_launch_route(const int* idx, int S, int E, int* counts, int* offsets, int* perm, int* inv, hipStream_t s);

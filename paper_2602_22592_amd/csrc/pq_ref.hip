@@ -12,9 +12,10 @@
 // cost a quarter of the loop (an MFMA-only loop: 33 against 69 TFLOP/s).
 // Measured against the LDS-staged 128x128 / 64x64 kernel that this replaced, one launch per product: 2048 tokens, 2048x2048,
 // rank 128, forward and backward 2602 -> 724 us (dW 804 -> 275 us, dX with its rank-128 product 607 -> 277 us, i.e. 62 and 66
-// TFLOP/s; H 251 -> 23 us); 64 tokens, 256x256, rank 16: 176 -> 37 us (13 -> 7 launches).
+// TFLOP/s; H 251 -> 23 us); 64 tokens, 256x256, rank 16: 176 -> 37 us (13 -> 7 launches; 26 us in the 5 that are left).
 #include <string.h>
-#include "pq_internal.h"
+#include "pq_epilogue.h"
+#include "pq_pack.h"
 
 namespace {
 
@@ -477,6 +478,94 @@ __global__ __launch_bounds__(256, 2) void ref_gemm_kernel(ref_launch L) {
 #undef PQ_REF_FORMS
 }
 
+// One product of the small forms beside the packing of an fp32 weight: the first `nref` workgroups are the product's.
+// H = X A^T and the packing have no data in common and each leaves most CUs idle or waiting: forward and backward of 64 tokens, 256x256,
+// r = 16 34.9 -> 31.6 us, 2048 tokens, 2048x2048, r = 128 377 -> 371 us.
+struct ref_pack_args {
+  pq_ref_problem p;
+  const float* W;
+  const double* partials;
+  uint8_t* P;
+  uint32_t* Pt;
+  float* mu_lambda;
+  int N, K, nparts, nref, gx;
+};
+template <bool RAGGED>
+__global__ __launch_bounds__(256, 2) void ref_pack_kernel(ref_pack_args a) {
+  const int b = blockIdx.x;
+  if (b >= a.nref) {                                      // uniform
+    const int t = b - a.nref;
+    pack_sign_body<float, RAGGED>(a.W, a.N, a.K, a.partials, a.nparts, a.P, a.Pt, a.mu_lambda, t % a.gx, t / a.gx);
+    return;
+  }
+  __shared__ double red[4];
+  __shared__ double lds[3 * 16 * 64];
+  if (a.p.cfg == 1) ref_tile<PQ_REF_CC, 2, 1>(a.p, b, nullptr, red);
+  else if (a.p.cfg == 2) ref_tile<PQ_REF_CC, 2, 4>(a.p, b, lds, red);
+  else ref_tile<PQ_REF_CC, 1, 4>(a.p, b, lds, red);
+}
+
+// Y = fl32(fl32(fl32(beta lambda) / gamma_t) * acc) + alpha H B^T of the fp32 forward in one launch: acc is the exact int8
+// product of the codes with the packed signs, the rank-r product runs in fp64 and the sum is rounded once.  A workgroup owns
+// 16 x 16 outputs, its wavefronts take every fourth step of both contractions.
+// Bound by the latency of one chain of loads and by the launch itself (64 tokens, 256x256: 64 workgroups), so it is one launch of
+// small workgroups where the int8 product and the fp64 product were one each.
+// A 16x16 MFMA leaves rows 4 lk .. 4 lk + 3 in a lane in its int8 form and rows lk, lk + 4, .. in its fp64 form: the codes'
+// rows are fed permuted, so that both sums of an output meet in one register.
+__global__ __launch_bounds__(256) void ref_linear_kernel(pq_ref_linear p) {
+  __shared__ int li8[3][4][64];
+  __shared__ double lf64[3][4][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 15, lk = lane >> 4;
+  const int nbn = (p.N + 15) / 16, m0 = (int)blockIdx.x / nbn * 16, n0 = (int)blockIdx.x % nbn * 16;
+  const int n = n0 + li;
+  i32x4_t acc = {0, 0, 0, 0};
+  {
+    const int8_t* qrow = p.Xq + (size_t)min(m0 + (li >> 2) + 4 * (li & 3), p.T - 1) * p.K;
+    const uint8_t* prow = (const uint8_t*)p.P + (size_t)min(n, p.N - 1) * (p.K / 8);
+    constexpr int D = 4;                                  // steps of 64 indices in flight; K is a multiple of 32: past it, index 0 and no codes
+    for (int s0 = wave; s0 * 64 < p.K; s0 += 4 * D) {     // uniform
+      i32x4_t a[D];
+      uint32_t b[D];
+#pragma unroll
+      for (int u = 0; u < D; ++u) {
+        const int k = (s0 + 4 * u) * 64 + 16 * lk;
+        const bool in = k < p.K;
+        const i32x4_t t = *reinterpret_cast<const i32x4_t*>(qrow + (in ? k : 0));
+        a[u] = in ? t : i32x4_t{0, 0, 0, 0};
+        b[u] = *reinterpret_cast<const uint16_t*>(prow + (in ? k >> 3 : 0));
+      }
+#pragma unroll
+      for (int u = 0; u < D; ++u) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[u], pq_bits_to_i8(b[u]), acc, 0, 0, 0);
+    }
+  }
+  f64x4_t hb[1][1] = {{f64x4_t{0.0, 0.0, 0.0, 0.0}}};
+  ref_contract<PQ_SRC_KC32, PQ_SRC_KC32, 1, 4>(p.H, p.B, m0, p.T, n0, p.N, p.r, wave, 4, li, lk, hb);
+  if (wave > 0) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      li8[wave - 1][v][lane] = acc[v];
+      lf64[wave - 1][v][lane] = hb[0][0][v];
+    }
+  }
+  __syncthreads();
+  if (wave > 0 || n >= p.N) return;
+  const float sc1 = __fmul_rn(p.beta, *p.lambda);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int m = m0 + lk + 4 * v;
+    if (m >= p.T) continue;
+    int t = acc[v];
+    double h = hb[0][0][v];
+#pragma unroll
+    for (int w = 0; w < 3; ++w) {
+      t += li8[w][v][lane];
+      h += lf64[w][v][lane];
+    }
+    const float y = __fmul_rn(sc1 / p.gamma[m], (float)t);
+    p.Y[(size_t)m * p.N + n] = (float)((double)p.alpha * h + (double)y);
+  }
+}
+
 constexpr int kNB[4] = {4, 2, 2, 1}, kKS[4] = {1, 1, 4, 4};
 
 int ref_blocks(int cfg, int M, int N) {
@@ -538,5 +627,37 @@ int pq_launch_ref(pq_ref_problem* p, int n, const pq_reduce_job* jobs, int njobs
     else ref_gemm_kernel<false><<<total, 256, 0, s>>>(L);
     PQ_CHECK_LAUNCH("ref_gemm_kernel");
   }
+  return PQ_OK;
+}
+
+// The product rides along with the packing when it takes one of the small forms.
+bool pq_ref_rides(int M, int N, int K) { return M > 0 && N > 0 && ref_config(M, N, K) != 0; }
+
+int pq_launch_ref_pack(const pq_ref_problem& p, const float* W, int N, int K, const double* partials, int nparts, uint32_t* P, uint32_t* Pt,
+                       float* mu_lambda, hipStream_t s) {
+  if (p.form != PQ_REF_CC || !pq_ref_rides(p.M, p.N, p.K)) return pq_set_error(PQ_ERR_BAD_ARG, "reference engine: product cannot ride along");
+  pq_prof_scope prof(PQP_PACK, s);
+  ref_pack_args a{p, W, partials, (uint8_t*)P, Pt, mu_lambda, N, K, nparts, 0, (((K + 31) & ~31) + 511) / 512};
+  a.p.cfg = ref_config(p.M, p.N, p.K);
+  a.nref = ref_blocks(a.p.cfg, p.M, p.N);
+  const int blocks = a.nref + a.gx * ((N + 31) / 32);
+  if (K % 32 != 0 || N % 32 != 0) ref_pack_kernel<true><<<blocks, 256, 0, s>>>(a);
+  else ref_pack_kernel<false><<<blocks, 256, 0, s>>>(a);
+  PQ_CHECK_LAUNCH("ref_pack_kernel");
+  return PQ_OK;
+}
+
+// One resident round of 16x16 tiles (four workgroups on each of 256 CUs): below it the launch that goes is worth more than what
+// larger tiles save, beyond it the two launches' 64x64 and 32x32 tiles are faster; contractions beyond 4096 gain nothing either way.
+// Forward and backward, two launches against one: 64 tokens, 256x256, r = 16: 31.1 -> 26.1 us; 512 tokens (1024 tiles), 512x512, r = 64:
+// 54.0 -> 52.6; 512 tokens, 4096x512: 150.7 -> 150.6; 256 tokens, 8192x1024: 286 -> 289; 2048 tokens (2048 tiles), 256x256, r = 256: 83 -> 90;
+// 300 tokens (2432 tiles), 2048x2048: 162 -> 174.
+bool pq_ref_linear_applies(int T, int N, int K) { return (long)((T + 15) / 16) * ((N + 15) / 16) <= 1024 && K <= 4096; }
+
+int pq_launch_ref_linear(const pq_ref_linear& p, hipStream_t s) {
+  if (p.K % 32 != 0 || p.r % 4 != 0) return pq_set_error(PQ_ERR_SHAPE, "K=%d must be a multiple of 32, r=%d of 4", p.K, p.r);
+  pq_prof_scope prof(PQP_GEMM_ONEBIT, s);
+  ref_linear_kernel<<<((p.T + 15) / 16) * ((p.N + 15) / 16), 256, 0, s>>>(p);
+  PQ_CHECK_LAUNCH("ref_linear_kernel");
   return PQ_OK;
 }
