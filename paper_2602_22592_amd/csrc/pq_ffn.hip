@@ -56,22 +56,24 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   L.Xq = c.take(T * D); L.gx = c.take(T * 4); L.Xt = c.take(T * D * 2);
   L.U = c.take(T * F * 2); L.G = c.take(T * F * 2);
   L.Hq = c.take(T * F); L.gh = c.take(T * 4); L.Ht = c.take(T * F * 2);
+  // (a single branch has no slots of its own: its products read and write the token rows)
+  const size_t So = E > 1 ? S : 0;
   L.idx = c.take(S * 4); L.gate = c.take(S * 4); L.probs = c.take(T * E * 4);
   L.counts = c.take(E * 4); L.offsets = c.take((E + 1) * 4); L.perm = c.take(S * 4); L.inv = c.take(S * 4);
-  L.Xp = c.take(S * D * 2); L.ue = c.take(2 * S * r * 2); L.ge = L.ue + S * r * 2; L.a = c.take(S * r * 2);
-  L.Ys = c.take(S * D * 2);
+  L.Xp = c.take(So * D * 2); L.ue = c.take(2 * S * r * 2); L.ge = L.ue + S * r * 2; L.a = c.take(S * r * 2);
+  L.Ys = c.take(So * D * 2);
   if (d.hp_kind == PQ_HP_LOWRANK_INT8) {
     // rows of [Up_e; Gate_e] (one [2 r][D] matrix per expert, as in the bf16 form): codes, gammas, de-quantised copy
     L.UGQ = c.take(E * 2 * r * D); L.gUG = c.take(E * 2 * r * 4); L.UGT = c.take(E * 2 * r * D * 2);
     L.DownQ = c.take(E * D * r); L.gDown = c.take(E * D * 4); L.DownT = c.take(E * D * r * 2);
-    L.XqP = c.take(S * D); L.gxP = c.take(S * 4);
+    L.XqP = c.take(So * D); L.gxP = c.take(So * 4);
     L.aQ = c.take(S * r); L.gA = c.take(S * 4); L.aT = c.take(S * r * 2);
   }
   L.UG = c.take(E * 2 * r * D * 2);
   L.ctx_total = c.off;
   cursor w;
   L.stat = w.take(3 * 2 * sizeof(double) * 1024);
-  L.n_red_a = pq_rowdot_blocks((int)S);
+  L.n_red_a = E > 1 ? pq_rowdot_blocks((int)S) : S > 0 ? pq_plan_gemm((int)S, (int)r, (int)D).red_blocks : 0;   // (one branch: the da product leaves them)
   L.n_red_b = pq_plan_gemm((int)D, (int)F, (int)T, false, false, PQ_PLAN_WGRAD).red_blocks;      // dW_down GEMM
   L.red_a = w.take(sizeof(double) * (size_t)L.n_red_a);
   L.red_b = w.take(sizeof(double) * (size_t)L.n_red_b);
@@ -106,10 +108,10 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   L.splitk = w.take(sk);
   L.splitk_bytes = sk;
   L.dHd = w.take(T * F * 2); L.dU = w.take(T * F * 2); L.dG = w.take(T * F * 2);
-  L.dYp = w.take(S * D * 2); L.rd = w.take(S * 4);
+  L.dYp = w.take(So * D * 2); L.rd = w.take(So * 4);
   L.da = w.take(S * r * 2); L.du = w.take(2 * S * r * 2); L.dg = L.du + S * r * 2; L.as = w.take(S * r * 2);
-  L.dXs = w.take(S * D * 2); L.dlogit = w.take(T * E * 4);
-  L.dwr = w.take(pq_dwr_scratch_bytes((int)T, (int)D, (int)E));
+  L.dXs = w.take(So * D * 2); L.dlogit = w.take(T * E * 4);
+  L.dwr = w.take(E > 1 ? pq_dwr_scratch_bytes((int)T, (int)D, (int)E) : 0);
   L.ws_total = w.off;
   return L;
 }
@@ -221,24 +223,39 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
   int8_t* Hq = (int8_t*)(cx + L.Hq);
   float* gh = (float*)(cx + L.gh);
   if (int e = pq_launch_swiglu_quant(cx + L.U, cx + L.G, T, F, Fv, Hq, gh, cx + L.Ht, s)) return e;
-  {  // Y = beta * (lambda_d / gamma_h) * acc
+  // Y = beta * (lambda_d / gamma_h) * acc.  A single bf16 branch comes in as the second contraction of the same tile
+  // (Y = alpha * ((beta lambda_d / alpha / gamma_h) acc + a Down^T)) under the rules of the linear's dense branch.
+  const bool one = E == 1;
+  const bool fuse_y = one && !hp8 && d->alpha != 0.0f && fabsf(d->alpha) >= 9.5367431640625e-7f * fabsf(d->beta) &&
+                      pq_plan_fuses(pq_plan_gemm(T, D, F, true, true, PQ_PLAN_SIGNS));
+  auto launch_down = [&]() -> int {
     pq_operand A{Hq, F, PQ_SRC_KC8, nullptr};
     pq_operand B{cx + L.P_down, F / 8, PQ_SRC_BITS8, nullptr};
     pq_epilogue e = epi0();
-    e.C = Y; e.ldc = D; e.out_kind = PQ_OUT_BF16; e.scale = d->beta; e.dev_scale = (const float*)(cx + L.ml_down) + 1; e.row_div = gh; e.split_int8 = 1;
-    if (int err = pq_launch_gemm(T, D, F, A, B, e, s, PQP_GEMM_ONEBIT, sk)) return err;
-  }
+    e.C = Y; e.ldc = D; e.out_kind = PQ_OUT_BF16; e.split_int8 = 1;
+    if (fuse_y) {
+      pq_phase2 p2;
+      p2.A2 = pq_operand{cx + L.a, r, PQ_SRC_KC16, nullptr};
+      p2.B2 = pq_operand{Down, r, PQ_SRC_KC16, nullptr};
+      p2.K2 = r; p2.scale1 = d->beta / d->alpha; p2.dev_scale1 = (const float*)(cx + L.ml_down) + 1; p2.row_div1 = gh;
+      e.scale = d->alpha;
+      return pq_launch_gemm(T, D, F, A, B, e, s, PQP_GEMM_ONEBIT, sk, nullptr, &p2);
+    }
+    e.scale = d->beta; e.dev_scale = (const float*)(cx + L.ml_down) + 1; e.row_div = gh;
+    return pq_launch_gemm(T, D, F, A, B, e, s, PQP_GEMM_ONEBIT, sk);
+  };
+  if (!fuse_y)
+    if (int e = launch_down()) return e;
   // routed experts: router -> stable permutation by expert -> gather -> grouped GEMMs -> combine
   int* idx = (int*)(cx + L.idx);
   float* gate = (float*)(cx + L.gate);
   int* offsets = (int*)(cx + L.offsets);
   int* perm = (int*)(cx + L.perm);
   int* inv = (int*)(cx + L.inv);
-  // a single branch (the paper's default, N = 1) has nothing to route: gate 1, identity permutation, X itself in slot order
-  const bool one = E == 1;
-  if (one) {
-    if (int e = pq_launch_route_single(S, idx, gate, (float*)(cx + L.probs), (int*)(cx + L.counts), offsets, perm, inv, s)) return e;
-  } else {
+  // a single branch (the paper's default, N = 1) has nothing to route: the tokens are its slots, Ys is added to Y by the product
+  // itself.  2048 tokens 2048/5076, r = 384 INT8: five launches and two passes over the
+  // slots less, 643 -> 625 us
+  if (!one) {
     if (int e = pq_launch_router(X, Wr, PQ_BF16, T, D, E, k, idx, gate, (float*)(cx + L.probs), s)) return e;
     if (int e = pq_launch_route(idx, S, E, (int*)(cx + L.counts), offsets, perm, inv, s)) return e;
   }
@@ -268,10 +285,12 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
       pq_operand A{cx + L.aQ, r, PQ_SRC_KC8, nullptr};
       pq_operand B{cx + L.DownQ, r, PQ_SRC_KC8, nullptr};
       pq_epilogue e = epi0();
-      e.C = cx + L.Ys; e.ldc = D; e.out_kind = PQ_OUT_BF16; e.row_div = (const float*)(cx + L.gA); e.col_div = (const float*)(cx + L.gDown);
+      e.C = one ? Y : cx + L.Ys; e.ldc = D; e.out_kind = PQ_OUT_BF16; e.row_div = (const float*)(cx + L.gA); e.col_div = (const float*)(cx + L.gDown);
+      if (one) { e.accumulate = 1; e.scale = d->alpha; }
       g1.b_stride = (long)D * r; g1.coldiv_stride = D;
       if (int err = pq_launch_gemm(S, D, r, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
     }
+    if (one) return PQ_OK;
     return pq_launch_combine_fwd(Y, cx + L.Ys, inv, gate, d->alpha, T, k, D, s);
   }
   const void* xp = one ? X : cx + L.Xp;
@@ -287,14 +306,17 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
     if (int err = pq_launch_gemm(S, 2 * r, D, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
   }
   if (int e = pq_launch_expert_act(cx + L.ue, cx + L.ue + (size_t)r * 2, 2 * r, S, r, cx + L.a, s)) return e;
+  if (fuse_y) return launch_down();
   {
     pq_operand A{cx + L.a, r, PQ_SRC_KC16, nullptr};
     pq_operand B{Down, r, PQ_SRC_KC16, nullptr};
     pq_epilogue e = epi0();
-    e.C = cx + L.Ys; e.ldc = D; e.out_kind = PQ_OUT_BF16;
+    e.C = one ? Y : cx + L.Ys; e.ldc = D; e.out_kind = PQ_OUT_BF16;
+    if (one) { e.accumulate = 1; e.scale = d->alpha; }
     g1.b_stride = (long)D * r;
     if (int err = pq_launch_gemm(S, D, r, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
   }
+  if (one) return PQ_OK;
   return pq_launch_combine_fwd(Y, cx + L.Ys, inv, gate, d->alpha, T, k, D, s);
 }
 
@@ -336,6 +358,41 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
     e.sign_bytes = (const uint8_t*)(cx + L.P_down); e.ld_sign = F / 8; e.partials = red_b;
     if (int err = pq_launch_gemm(D, F, T, A, B, e, s, PQP_GEMM_DW, sk)) return err;
   }
+  // experts
+  const int* idx = (const int*)(cx + L.idx);
+  const float* gate = (const float*)(cx + L.gate);
+  const int* offsets = (const int*)(cx + L.offsets);
+  const int* perm = (const int*)(cx + L.perm);
+  const int* inv = (const int*)(cx + L.inv);
+  float* rd = (float*)(ws + L.rd);
+  const bool hp8 = d->hp_kind == PQ_HP_LOWRANK_INT8;
+  const bool one = E == 1;                           // a single branch: identity permutation, plain GEMMs over all slots (see the forward)
+  const bool fuse_dx = one && T > 0 && pq_plan_fuses(pq_plan_gemm(T, D, F, false, false, PQ_PLAN_SIGNS));
+  const void* dyp = one ? dY : ws + L.dYp;
+  // what the up and gate products multiplied: X, or with INT8 experts its de-quantised codes
+  const void* xp = one ? (hp8 ? (const void*)(cx + L.Xt) : X) : (const void*)(cx + L.Xp);
+  // row dots with the experts' outputs (d alpha, the gates' gradients) and dY in slot order
+  if (!one)
+    if (int e = pq_launch_slot_grad(dY, cx + L.Ys, perm, gate, d->alpha, false, k, S, D, ws + L.dYp, rd, red_a, s)) return e;
+  // d alpha and d beta (partials of the dW_down GEMM): both fixed-order sums ride along in the last reduction, with a single
+  // branch in the activation's backward
+  const pq_reduce_job jobs[2] = {{red_a, S > 0 ? L.n_red_a : 0, 1.0f, nullptr, dalpha_dbeta}, {red_b, L.n_red_b, 1.0f, ml_down + 1, dalpha_dbeta + 1}};
+  pq_gemm_group g1{offsets, E, 1, 0, 0, S};
+  pq_gemm_group g2{offsets, E, 2, 0, 0, S};
+  const pq_gemm_group* pg1 = one ? nullptr : &g1;
+  const pq_gemm_group* pg2 = one ? nullptr : &g2;
+  if (S > 0) {  // da = dYp Down_e  (scaled by alpha*gate inside the activation backward)
+    pq_operand A{dyp, D, PQ_SRC_KC16, nullptr};
+    pq_operand B{Down, r, PQ_SRC_KS16, nullptr};
+    pq_epilogue e = epi0();
+    e.C = ws + L.da; e.ldc = r; e.out_kind = PQ_OUT_BF16;
+    if (one) { e.dot_comp = a_fwd; e.ld_comp = r; e.comp_kind = PQ_OUT_BF16; e.partials = red_a; }   // d alpha = <a, dY Down>
+    g1.b_stride = (long)D * r;
+    if (int err = pq_launch_gemm(S, r, D, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
+  }
+  // u | g and du | dg lie side by side in [S][2 r] matrices (Up and Gate are one weight matrix per expert, in both forms)
+  if (int e = pq_launch_expert_act_bwd(ws + L.da, cx + L.ue, cx + L.ue + (size_t)r * 2, a_fwd, one ? nullptr : perm, gate, d->alpha, S, r, 2 * r,
+                                       ws + L.du, ws + L.du + (size_t)r * 2, ws + L.as, one ? dWr : nullptr, D, jobs, s)) return e;
   if (T > 0) {
     {  // dHd = beta * lambda_d * dY S_d
       pq_operand A{dY, D, PQ_SRC_KC16, nullptr};
@@ -349,8 +406,17 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
       pq_operand A{ws + L.dU, F, PQ_SRC_KC16, nullptr};
       pq_operand B{cx + L.Pt_up, F / 8, PQ_SRC_BITS16, nullptr};
       pq_epilogue e = epi0();
-      e.C = dX; e.ldc = D; e.out_kind = PQ_OUT_BF16; e.dev_scale = ml_up + 1;
-      if (int err = pq_launch_gemm(T, D, F, A, B, e, s, PQP_GEMM_DX, sk)) return err;
+      e.C = dX; e.ldc = D; e.out_kind = PQ_OUT_BF16;
+      if (fuse_dx) {   // + [du | dg] [Up; Gate] of a single branch in the same tile
+        pq_phase2 p2;
+        p2.A2 = pq_operand{ws + L.du, 2 * r, PQ_SRC_KC16, nullptr};
+        p2.B2 = pq_operand{hp8 ? cx + L.UGT : cx + L.UG, D, PQ_SRC_KS16, nullptr};
+        p2.K2 = 2 * r; p2.scale1 = 1.0f; p2.dev_scale1 = ml_up + 1; p2.row_div1 = nullptr;
+        if (int err = pq_launch_gemm(T, D, F, A, B, e, s, PQP_GEMM_DX, sk, nullptr, &p2)) return err;
+      } else {
+        e.dev_scale = ml_up + 1;
+        if (int err = pq_launch_gemm(T, D, F, A, B, e, s, PQP_GEMM_DX, sk)) return err;
+      }
       pq_operand A2{ws + L.dG, F, PQ_SRC_KC16, nullptr};
       pq_operand B2{cx + L.Pt_gate, F / 8, PQ_SRC_BITS16, nullptr};
       e.accumulate = 1; e.dev_scale = ml_gate + 1;
@@ -366,37 +432,6 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
     e.C = dW_up;
     if (int err = pq_launch_gemm_dual(F, D, T, A, B, e, A2, B, dW_gate, nullptr, s, PQP_GEMM_DW, sk)) return err;
   }
-  // experts
-  const int* idx = (const int*)(cx + L.idx);
-  const float* gate = (const float*)(cx + L.gate);
-  const int* offsets = (const int*)(cx + L.offsets);
-  const int* perm = (const int*)(cx + L.perm);
-  const int* inv = (const int*)(cx + L.inv);
-  float* rd = (float*)(ws + L.rd);
-  const bool hp8 = d->hp_kind == PQ_HP_LOWRANK_INT8;
-  const bool one = E == 1;                           // a single branch: identity permutation, plain GEMMs over all slots (see the forward)
-  const void* dyp = one ? dY : ws + L.dYp;
-  // what the up and gate products multiplied: X, or with INT8 experts its de-quantised codes
-  const void* xp = one ? (hp8 ? (const void*)(cx + L.Xt) : X) : (const void*)(cx + L.Xp);
-  // row dots with the experts' outputs (d alpha, the gates' gradients) and dY in slot order
-  if (int e = pq_launch_slot_grad(dY, cx + L.Ys, perm, gate, d->alpha, false, k, S, D, one ? nullptr : ws + L.dYp, rd, red_a, s)) return e;
-  // d alpha and d beta (partials of the dW_down GEMM): both fixed-order sums ride along in the last reduction
-  const pq_reduce_job jobs[2] = {{red_a, S > 0 ? L.n_red_a : 0, 1.0f, nullptr, dalpha_dbeta}, {red_b, L.n_red_b, 1.0f, ml_down + 1, dalpha_dbeta + 1}};
-  pq_gemm_group g1{offsets, E, 1, 0, 0, S};
-  pq_gemm_group g2{offsets, E, 2, 0, 0, S};
-  const pq_gemm_group* pg1 = one ? nullptr : &g1;
-  const pq_gemm_group* pg2 = one ? nullptr : &g2;
-  if (S > 0) {  // da = dYp Down_e  (scaled by alpha*gate inside the activation backward)
-    pq_operand A{dyp, D, PQ_SRC_KC16, nullptr};
-    pq_operand B{Down, r, PQ_SRC_KS16, nullptr};
-    pq_epilogue e = epi0();
-    e.C = ws + L.da; e.ldc = r; e.out_kind = PQ_OUT_BF16;
-    g1.b_stride = (long)D * r;
-    if (int err = pq_launch_gemm(S, r, D, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
-  }
-  // u | g and du | dg lie side by side in [S][2 r] matrices (Up and Gate are one weight matrix per expert, in both forms)
-  if (int e = pq_launch_expert_act_bwd(ws + L.da, cx + L.ue, cx + L.ue + (size_t)r * 2, a_fwd, perm, gate, d->alpha, S, r, 2 * r,
-                                       ws + L.du, ws + L.du + (size_t)r * 2, ws + L.as, s)) return e;
   {  // per-expert weight gradients: contraction over the expert's slots
     pq_operand A{dyp, D, PQ_SRC_KS16, nullptr};
     pq_operand B{ws + L.as, r, PQ_SRC_KS16, nullptr};
@@ -412,19 +447,16 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
       if (int err = pq_launch_gemm(2 * r, D, S, Aug, Bx, e, s, PQP_GEMM_EXPERT, sk, pg2)) return err;
     }
   }
-  if (S > 0) {  // dXs = [du | dg] [Up_e; Gate_e]  (INT8 experts: the de-quantised rows)
+  if (S > 0 && !fuse_dx) {  // dXs = [du | dg] [Up_e; Gate_e]  (INT8 experts: the de-quantised rows); a single branch's goes to dX itself
     pq_operand A{ws + L.du, 2 * r, PQ_SRC_KC16, nullptr};
     pq_operand B{hp8 ? cx + L.UGT : cx + L.UG, D, PQ_SRC_KS16, nullptr};
     pq_epilogue e = epi0();
-    e.C = ws + L.dXs; e.ldc = D; e.out_kind = PQ_OUT_BF16;
+    e.C = one ? dX : ws + L.dXs; e.ldc = D; e.out_kind = PQ_OUT_BF16; e.accumulate = one ? 1 : 0;
     g1.b_stride = (long)2 * r * D;
     if (int err = pq_launch_gemm(S, D, 2 * r, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
   }
+  if (one) return PQ_OK;   // softmax over one logit is constant: no gradient reaches the router
   float* dlogit = (float*)(ws + L.dlogit);
-  if (one) {   // softmax over one logit is constant: no gradient reaches the router
-    if (int e = pq_launch_dwr(nullptr, nullptr, nullptr, nullptr, 0.0f, k, nullptr, X, T, D, E, (float*)(ws + L.dwr), dWr, jobs, s)) return e;
-    return pq_launch_combine_bwd(dX, ws + L.dXs, inv, nullptr, Wr, T, k, D, 0, s);
-  }
   if (int e = pq_launch_dwr(rd, inv, idx, (const float*)(cx + L.probs), d->alpha, k, dlogit, X, T, D, E, (float*)(ws + L.dwr), dWr, jobs, s)) return e;
   return pq_launch_combine_bwd(dX, ws + L.dXs, inv, dlogit, Wr, T, k, D, E, s);
 }

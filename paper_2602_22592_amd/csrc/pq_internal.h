@@ -296,10 +296,10 @@ int pq_launch_swiglu_quant(const void* U, const void* G, int T, int F, int Fv, i
 int pq_launch_swiglu_bwd(const void* dHd, const void* U, const void* G, int T, int F, int Fv, void* dU, void* dG, hipStream_t s);
 // ue, ge (and du, dg) have a row stride of ld elements: r, or 2 r when both lie side by side in one [S][2 r] matrix
 int pq_launch_expert_act(const void* ue, const void* ge, int ld, int S, int r, void* a, hipStream_t s);
+// perm == NULL: a single branch (gate 1).  dWr != NULL: its n_wr elements are cleared and jobs[0..1] reduced in the same launch.
 int pq_launch_expert_act_bwd(const void* da, const void* ue, const void* ge, const void* a, const int* perm, const float* gate,
-                             float alpha, int S, int r, int ld, void* du, void* dg, void* as, hipStream_t s);
-// one expert, top-1: expert 0, gate 1, identity permutation, one segment (what router + counting sort would produce)
-int pq_launch_route_single(int S, int* idx, float* gate, float* probs, int* counts, int* offsets, int* perm, int* inv, hipStream_t s);
+                             float alpha, int S, int r, int ld, void* du, void* dg, void* as, float* dWr, int n_wr,
+                             const pq_reduce_job* jobs, hipStream_t s);
 int pq_rowdot_blocks(int S);
 // rd[pos] = <dY[perm[pos] / k], Ys[pos]>, partial[pq_rowdot_blocks(S)] of sum gate * rd, dst[pos] (may be NULL) = the dY row
 // [* alpha * gate]
@@ -307,7 +307,7 @@ int pq_launch_slot_grad(const void* dY, const void* Ys, const int* perm, const f
                         void* dst, float* rd, double* partial, hipStream_t s);
 int pq_launch_combine_fwd(void* Y, const void* Ys, const int* inv, const float* gate, float alpha, int T, int k, int d, hipStream_t s);
 size_t pq_dwr_scratch_bytes(int T, int d, int E);
-// router backward and dWr: dlogit [T][E] from rd and the softmax, dWr = dlogit^T X; rd == NULL: dWr = 0.  jobs: two scalar
+// router backward and dWr: dlogit [T][E] from rd and the softmax, dWr = dlogit^T X.  jobs: two scalar
 // reductions of partials that earlier launches left, in the last launch.
 int pq_launch_dwr(const float* rd, const int* inv, const int* idx, const float* probs, float alpha, int k, float* dlogit, const void* X, int T,
                   int d, int E, float* part, float* dWr, const pq_reduce_job* jobs, hipStream_t s);

@@ -118,24 +118,6 @@ __global__ __launch_bounds__(1024) void route_kernel(const int* __restrict__ idx
   }
 }
 
-// One expert (a single high-precision branch, top-1): what the router and the counting sort produce is known beforehand:
-// expert 0 with gate softmax([logit]) = 1 for every token, the identity permutation, one segment of all slots.
-__global__ __launch_bounds__(256) void route_single_kernel(int S, int* __restrict__ idx, float* __restrict__ gate, float* __restrict__ probs,
-                                                           int* __restrict__ counts, int* __restrict__ offsets, int* __restrict__ perm,
-                                                           int* __restrict__ inv) {
-  const int s = blockIdx.x * 256 + threadIdx.x;
-  if (s == 0) {
-    counts[0] = S;
-    offsets[0] = 0;
-    offsets[1] = S;
-  }
-  if (s >= S) return;
-  idx[s] = 0;
-  gate[s] = 1.0f;
-  probs[s] = 1.0f;
-  perm[s] = s;
-  inv[s] = s;
-}
 // dst[pos][:] = src[perm[pos] / k][:]   (rows of d bf16, d % 8 == 0), one wavefront per row
 __global__ __launch_bounds__(256) void gather_rows_kernel(const uint16_t* __restrict__ src, const int* __restrict__ perm, int k,
                                                           int S, int d, uint16_t* __restrict__ dst) {
@@ -293,17 +275,25 @@ __global__ __launch_bounds__(256) void expert_act_kernel(const uint16_t* __restr
   reinterpret_cast<uint4*>(a)[c] = pack8(o);
 }
 
-// with s = alpha * gate[slot]:  du = s da silu(ge), dg = s da ue silu'(ge), as = s a   (r % 8 == 0)
+// with s = alpha * gate[slot] (perm == NULL: a single branch, s = alpha):  du = s da silu(ge), dg = s da ue silu'(ge), as = s a
+// (r % 8 == 0).  The first `ride` workgroups of a single branch's launch form d alpha and d beta and clear dWr, which no gradient
+// reaches: a launch of its own took 4.6 us at the end of every backward.
 __global__ __launch_bounds__(256) void expert_act_bwd_kernel(const uint16_t* __restrict__ da, const uint16_t* __restrict__ ue,
                                                              const uint16_t* __restrict__ ge, const uint16_t* __restrict__ a,
                                                              const int* __restrict__ perm, const float* __restrict__ gate,
                                                              float alpha, int r, int ld, size_t nvec, uint16_t* __restrict__ du,
-                                                             uint16_t* __restrict__ dg, uint16_t* __restrict__ as) {
-  const size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
+                                                             uint16_t* __restrict__ dg, uint16_t* __restrict__ as, int ride,
+                                                             float* __restrict__ dWr, int n_wr, pq_reduce_job j0, pq_reduce_job j1) {
+  if ((int)blockIdx.x < ride) {                      // uniform
+    if (blockIdx.x < 2) pq_reduce_job_body(blockIdx.x == 0 ? j0 : j1);
+    else if (const int i = (blockIdx.x - 2) * 256 + threadIdx.x; i < n_wr) dWr[i] = 0.0f;
+    return;
+  }
+  const size_t c = (size_t)(blockIdx.x - ride) * 256 + threadIdx.x;
   if (c >= nvec) return;
   const int pos = (int)(c / (size_t)(r / 8));
   const size_t in = (size_t)pos * ld + (c - (size_t)pos * (r / 8)) * 8;   // ue, ge, du, dg: row stride ld (r or 2 r)
-  const float sc = alpha * gate[perm[pos]];
+  const float sc = perm ? alpha * gate[perm[pos]] : alpha;
   float d[8], uf[8], gf[8], af[8], o1[8], o2[8], o3[8];
   unpack8(reinterpret_cast<const uint4*>(da)[c], d);
   unpack8(*reinterpret_cast<const uint4*>(ue + in), uf);
@@ -715,13 +705,6 @@ int pq_launch_route(const int* idx, int S, int E, int* counts, int* offsets, int
   return PQ_OK;
 }
 
-int pq_launch_route_single(int S, int* idx, float* gate, float* probs, int* counts, int* offsets, int* perm, int* inv, hipStream_t s) {
-  pq_prof_scope prof(PQP_MOE_ROUTE, s);
-  route_single_kernel<<<(S + 256) / 256, 256, 0, s>>>(S, idx, gate, probs, counts, offsets, perm, inv);
-  PQ_CHECK_LAUNCH("route_single_kernel");
-  return PQ_OK;
-}
-
 int pq_launch_gather_rows(const void* src, const int* perm, int k, int S, int d, void* dst, hipStream_t s) {
   if (S == 0) return PQ_OK;
   pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
@@ -776,13 +759,15 @@ int pq_launch_expert_act(const void* ue, const void* ge, int ld, int S, int r, v
 }
 
 int pq_launch_expert_act_bwd(const void* da, const void* ue, const void* ge, const void* a, const int* perm, const float* gate,
-                             float alpha, int S, int r, int ld, void* du, void* dg, void* as, hipStream_t s) {
-  if (S == 0) return PQ_OK;
+                             float alpha, int S, int r, int ld, void* du, void* dg, void* as, float* dWr, int n_wr, const pq_reduce_job* jobs,
+                             hipStream_t s) {
+  const int ride = dWr ? 2 + (n_wr + 255) / 256 : 0;
+  if (S == 0 && ride == 0) return PQ_OK;
   pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
   const size_t nvec = (size_t)S * r / 8;
-  expert_act_bwd_kernel<<<(unsigned)((nvec + 255) / 256), 256, 0, s>>>((const uint16_t*)da, (const uint16_t*)ue, (const uint16_t*)ge,
+  expert_act_bwd_kernel<<<(unsigned)((nvec + 255) / 256) + ride, 256, 0, s>>>((const uint16_t*)da, (const uint16_t*)ue, (const uint16_t*)ge,
                                                                       (const uint16_t*)a, perm, gate, alpha, r, ld, nvec, (uint16_t*)du,
-                                                                      (uint16_t*)dg, (uint16_t*)as);
+                                                                      (uint16_t*)dg, (uint16_t*)as, ride, dWr, n_wr, jobs[0], jobs[1]);
   PQ_CHECK_LAUNCH("expert_act_bwd_kernel");
   return PQ_OK;
 }
@@ -813,7 +798,7 @@ size_t pq_dwr_scratch_bytes(int T, int d, int E) {
 int pq_launch_dwr(const float* rd, const int* inv, const int* idx, const float* probs, float alpha, int k, float* dlogit, const void* X, int T,
                   int d, int E, float* part, float* dWr, const pq_reduce_job* jobs, hipStream_t s) {
   pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
-  const int chunk = dwr_chunk(T, d), nchunks = rd ? (T + chunk - 1) / chunk : 0;
+  const int chunk = dwr_chunk(T, d), nchunks = (T + chunk - 1) / chunk;
   if (nchunks > 0) {
     dim3 grid((d + 255) / 256, nchunks);
     if (chunk == 32) dwr_partial_kernel<32><<<grid, 256, 0, s>>>(rd, inv, idx, probs, alpha, k, dlogit, (const uint16_t*)X, T, d, E, part);

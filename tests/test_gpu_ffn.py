@@ -140,6 +140,17 @@ def test_ffn_int8_experts(T, D, F, E, r, k):
     check_ffn(wl.ffn_case(180 + T + k + r, T, D, F, E, r), top_k=k, experts="int8")
 
 
+# single branches: their products write Y and dX directly.  One token; ragged rows on 64x64 tiles; hidden widths that are
+# padded; whole and ragged 128x256 tiles with the branch inside the tile (ranks below, at and above a step of 64); a
+# contraction that is split, where it is not
+@pytest.mark.parametrize("T,D,F,r,alpha,kind", [(1, 32, 32, 8, 2.0, "bf16"), (65, 96, 100, 24, 2.0, "bf16"), (2113, 512, 260, 40, 2.0, "bf16"),
+                                                (4096, 2048, 288, 128, 2.0, "bf16"), (4100, 2048, 100, 64, 2.0, "int8"), (300, 256, 2048, 96, 2.0, "int8"),
+                                                (520, 1024, 4096, 384, 2.0, "bf16"), (300, 256, 544, 32, 1e-8, "bf16"), (300, 256, 544, 32, 0.0, "int8")])
+def test_ffn_single_branch(T, D, F, r, alpha, kind):
+    print(f"ffn single branch T={T} d={D} F={F} r={r} alpha={alpha} {kind}", flush=True)
+    check_ffn(wl.ffn_case(260 + T + r, T, D, F, 1, r), alpha=alpha, experts=kind)
+
+
 def test_ffn_int8_experts_rejects_ranks_that_are_not_whole_words():
     with pytest.raises(pq.PQError):
         pq.FFNBuffers(pq.FFNDesc(64, 64, 64, 8, 2, 1, pq.PQ_BF16, 1.0, 1.0, pq.PQ_HP_LOWRANK_INT8))
