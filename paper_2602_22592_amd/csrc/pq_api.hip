@@ -424,8 +424,8 @@ static int hp_int8_fwd_impl(const int8_t* Xq, const float* gamma_x, const void* 
 // ---------------------------------------------------------------------------------------------
 // Forward: [stats -> pack] -> quantise -> int8 MFMA GEMM with de-quantising epilogue -> hp branch
 // ---------------------------------------------------------------------------------------------
-// prequant: the quantised activations (codes, gamma, q/gamma) are already in ctx and X is what the
-// high-precision branch reads (the normalising entry point runs the fused quantiser first)
+// prequant: the quantised activations (codes, gamma, q/gamma) are already in ctx, the weight statistics' first stage in
+// the workspace, and X is what the high-precision branch reads (the normalising entry point runs the fused quantiser first)
 static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W_or_packed,
                            const float* mu_lambda, const void* hpA, const void* hpB, const void* Wr, void* Y,
                            void* ctx, size_t ctx_bytes, void* workspace, size_t workspace_bytes, void* stream, bool prequant) {
@@ -507,7 +507,9 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
     double* part = (double*)(ws + L.stat_partials);
     if (combo) {
       if (int e = launch_combo(W_or_packed, n, part, nb)) return e;
-    } else if (int e = pq_launch_wstats_partial(W_or_packed, d->io_dtype, n, part, nb, s)) return e;
+    } else if (!prequant) {
+      if (int e = pq_launch_wstats_partial(W_or_packed, d->io_dtype, n, part, nb, s)) return e;
+    }
     uint32_t* Pt = (N % 32 == 0) ? (uint32_t*)(cx + L.Pt) : nullptr;
     if (hp8) {   // the rows of A and B on the AbsMax grid ride along
       const hp8_layout H8 = make_hp8_layout(T, K, N, d->hp_rank);
@@ -918,9 +920,9 @@ extern "C" int pq_linear_norm_fwd(const pq_linear_desc* d, const void* X, const 
   if (int e = check_desc(d, false)) return e;
   if (int e = check_norm(d, false)) return e;
   PQ_REQUIRE(d->w_kind == PQ_W_MASTER, PQ_ERR_BAD_ARG, "the normalising entry point takes latent weights");
-  PQ_REQUIRE(X && gain && ctx && workspace, PQ_ERR_BAD_ARG, "NULL buffer (X, gain, ctx or workspace)");
+  PQ_REQUIRE(X && gain && W && ctx && workspace, PQ_ERR_BAD_ARG, "NULL buffer (X, gain, W, ctx or workspace)");
   PQ_REQUIRE(eps >= 0.0f, PQ_ERR_BAD_ARG, "eps must not be negative");
-  PQ_REQUIRE(aligned16(X) && aligned16(gain) && aligned16(ctx), PQ_ERR_SHAPE, "buffers must be 16-byte aligned");
+  PQ_REQUIRE(aligned16(X) && aligned16(gain) && aligned16(W) && aligned16(ctx) && aligned16(workspace), PQ_ERR_SHAPE, "buffers must be 16-byte aligned");
   const lin_layout L = make_layout(*d);
   const norm_layout NL = make_norm_layout(*d, L);
   PQ_REQUIRE(ctx_bytes >= NL.ctx_total, PQ_ERR_WORKSPACE, "ctx too small: %zu < %zu", ctx_bytes, NL.ctx_total);
@@ -928,8 +930,10 @@ extern "C" int pq_linear_norm_fwd(const pq_linear_desc* d, const void* X, const 
   char* cx = (char*)ctx;
   const bool bf16 = d->io_dtype == PQ_BF16;
   void* Xn = cx + NL.Xn;
+  const size_t n = (size_t)d->d_out * d->d_in;
   if (int e = pq_launch_rmsnorm_quant(X, gain, d->io_dtype, d->tokens, d->d_in, eps, Xn, (int8_t*)(cx + L.Xq), (float*)(cx + L.gamma),
-                                      bf16 ? (uint16_t*)(cx + L.Xt) : nullptr, (float*)(cx + NL.rstd), (hipStream_t)stream))
+                                      bf16 ? (uint16_t*)(cx + L.Xt) : nullptr, (float*)(cx + NL.rstd), (hipStream_t)stream, W, n,
+                                      (double*)((char*)workspace + L.stat_partials), pq_stats_blocks(n)))
     return e;
   return linear_fwd_impl(d, Xn, W, nullptr, hpA, hpB, Wr, Y, ctx, L.ctx_total, workspace, L.ws_total, stream, true);
 }

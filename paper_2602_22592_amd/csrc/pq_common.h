@@ -147,6 +147,11 @@ __device__ __forceinline__ void pq_slab_sum_bf16_body(const float* __restrict__ 
       make_uint4(pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w), pack_bf16x2(b.x, b.y), pack_bf16x2(b.z, b.w));
 }
 
+// sigmoid through the hardware exponential and reciprocal (about 2 ulp each): with a correctly rounded expf and an IEEE
+// division per element the element-wise kernels of the gated unit are bound by their instruction count, not by memory
+__device__ __forceinline__ float pq_sigmoid(float x) { return __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
+__device__ __forceinline__ float pq_silu(float x) { return x * pq_sigmoid(x); }
+
 // Fixed-order final reduction of per-block fp64 partial sums to one fp32 value: out = (sum partials) * factor [* *dev_factor].
 // One workgroup of 256 threads per job.
 struct pq_reduce_job { const double* partials; int n; float factor; const float* dev_factor; float* out; };

@@ -279,8 +279,12 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
       g1.b_stride = (long)2 * r * D; g1.coldiv_stride = 2 * r;
       if (int err = pq_launch_gemm(S, 2 * r, D, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
     }
-    if (int e = pq_launch_expert_act(cx + L.ue, cx + L.ue + (size_t)r * 2, 2 * r, S, r, cx + L.a, s)) return e;
-    if (int e = pq_launch_quant_act(cx + L.a, PQ_BF16, S, r, (int8_t*)(cx + L.aQ), (float*)(cx + L.gA), (uint16_t*)(cx + L.aT), s)) return e;
+    if (pq_expert_act_quant_applies(r)) {
+      if (int e = pq_launch_expert_act_quant(cx + L.ue, cx + L.ue + (size_t)r * 2, 2 * r, S, r, (int8_t*)(cx + L.aQ), (float*)(cx + L.gA), cx + L.aT, s)) return e;
+    } else {
+      if (int e = pq_launch_expert_act(cx + L.ue, cx + L.ue + (size_t)r * 2, 2 * r, S, r, cx + L.a, s)) return e;
+      if (int e = pq_launch_quant_act(cx + L.a, PQ_BF16, S, r, (int8_t*)(cx + L.aQ), (float*)(cx + L.gA), (uint16_t*)(cx + L.aT), s)) return e;
+    }
     {
       pq_operand A{cx + L.aQ, r, PQ_SRC_KC8, nullptr};
       pq_operand B{cx + L.DownQ, r, PQ_SRC_KC8, nullptr};

@@ -21,9 +21,10 @@ int pq_launch_quant_act(const void* X, int dtype, int T, int K, int8_t* Xq, floa
                         uint16_t* Xt, hipStream_t s);
 // RMSNorm fused with the quantiser: Xn (optional, I/O type) receives the stored normalised activations,
 // Xt (optional, bf16) q/gamma, rstd (optional) the per-token reciprocal RMS.  Rows of up to 16*64 16-byte
-// vectors (8 for the backward).
+// vectors (8 for the backward).  nw > 0: nw further workgroups leave the first stage of W's statistics in partials.
 int pq_launch_rmsnorm_quant(const void* X, const void* gain, int dtype, int T, int K, float eps, void* Xn, int8_t* Xq,
-                            float* gamma, uint16_t* Xt, float* rstd, hipStream_t s);
+                            float* gamma, uint16_t* Xt, float* rstd, hipStream_t s, const void* W = nullptr, size_t w_elems = 0,
+                            double* partials = nullptr, int nw = 0);
 size_t pq_rmsnorm_bwd_scratch_bytes(int T, int K);
 int pq_launch_rmsnorm_bwd(const void* dXn, const void* X, const void* gain, const float* rstd, int dtype, int T, int K, void* dX,
                           float* dgain, float* part, hipStream_t s);
@@ -295,6 +296,9 @@ int pq_launch_gather_quant_rows(const void* xt, const int8_t* xq, const float* g
 int pq_launch_swiglu_quant(const void* U, const void* G, int T, int F, int Fv, int8_t* Hq, float* gamma, void* Ht, hipStream_t s);
 int pq_launch_swiglu_bwd(const void* dHd, const void* U, const void* G, int T, int F, int Fv, void* dU, void* dG, hipStream_t s);
 // ue, ge (and du, dg) have a row stride of ld elements: r, or 2 r when both lie side by side in one [S][2 r] matrix
+// (INT8 experts: with the quantiser of its rows, of up to 2048 elements; at the de-quantised copy)
+bool pq_expert_act_quant_applies(int r);
+int pq_launch_expert_act_quant(const void* ue, const void* ge, int ld, int S, int r, int8_t* aq, float* gamma, void* at, hipStream_t s);
 int pq_launch_expert_act(const void* ue, const void* ge, int ld, int S, int r, void* a, hipStream_t s);
 // perm == NULL: a single branch (gate 1).  dWr != NULL: its n_wr elements are cleared and jobs[0..1] reduced in the same launch.
 int pq_launch_expert_act_bwd(const void* da, const void* ue, const void* ge, const void* a, const int* perm, const float* gate,

@@ -17,12 +17,8 @@ __device__ __forceinline__ void unpack8(const uint4& u, float* f) {
 __device__ __forceinline__ uint4 pack8(const float* f) {
   return make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
 }
-// sigmoid through the hardware exponential and reciprocal (about 2 ulp each): with a correctly rounded expf and an IEEE
-// division per element the element-wise kernels of the gated unit are bound by their instruction count, not by memory
-__device__ __forceinline__ float sigmoidf_(float x) { return __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
-__device__ __forceinline__ float siluf_(float x) { return x * sigmoidf_(x); }
 __device__ __forceinline__ float dsiluf_(float x) {
-  const float s = sigmoidf_(x);
+  const float s = pq_sigmoid(x);
   return s * (1.0f + x * (1.0f - s));
 }
 
@@ -167,7 +163,7 @@ __global__ __launch_bounds__(256) void swiglu_quant_kernel(const uint16_t* __res
     unpack8(u, uf);
     unpack8(g, gf);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) h[j] = (c * 8 + j < Fv) ? siluf_(gf[j]) * uf[j] : 0.0f;
+    for (int j = 0; j < 8; ++j) h[j] = (c * 8 + j < Fv) ? pq_silu(gf[j]) * uf[j] : 0.0f;
   };
   if constexpr (NV > 0) {
     uint4 ur[NV], gr[NV];
@@ -248,7 +244,7 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(const uint16_t* __restr
       unpack8(q ? r1[2] : r0[2], gf);
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const float sg = sigmoidf_(gf[j]);
+        const float sg = pq_sigmoid(gf[j]);
         const bool ok = col + j < Fv;
         du[j] = ok ? dh[j] * (gf[j] * sg) : 0.0f;
         dg[j] = ok ? dh[j] * uf[j] * (sg * (1.0f + gf[j] * (1.0f - sg))) : 0.0f;
@@ -271,7 +267,7 @@ __global__ __launch_bounds__(256) void expert_act_kernel(const uint16_t* __restr
   unpack8(*reinterpret_cast<const uint4*>(ue + in), uf);
   unpack8(*reinterpret_cast<const uint4*>(ge + in), gf);
 #pragma unroll
-  for (int j = 0; j < 8; ++j) o[j] = siluf_(gf[j]) * uf[j];
+  for (int j = 0; j < 8; ++j) o[j] = pq_silu(gf[j]) * uf[j];
   reinterpret_cast<uint4*>(a)[c] = pack8(o);
 }
 
@@ -302,7 +298,7 @@ __global__ __launch_bounds__(256) void expert_act_bwd_kernel(const uint16_t* __r
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const float dj = sc * d[j];           // upstream of the expert output is alpha * gate * dY
-    o1[j] = dj * siluf_(gf[j]);
+    o1[j] = dj * pq_silu(gf[j]);
     o2[j] = dj * uf[j] * dsiluf_(gf[j]);
     o3[j] = sc * af[j];
   }

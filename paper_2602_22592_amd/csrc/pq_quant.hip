@@ -110,6 +110,61 @@ __global__ __launch_bounds__(256) void quant_act_kernel(const T* __restrict__ X,
   quant_act_body<T, NV>(X, Tn, K, Xq, gamma, Xt, blockIdx.x);
 }
 
+// The gated unit of INT8 experts and the quantiser of its result: a = bf16(silu(g) u) over rows of r elements (u and g of a row ld
+// elements apart from the next row's), then what quant_act_row makes of a.  Bound by its launch at most sizes; with a in memory
+// between two launches the FFN of 2048 tokens 2048/5076, r = 384 took 607.9 us, so 604.9.  Rows of up to 64 NV vectors stay in registers.
+template <int NV>
+__global__ __launch_bounds__(256) void expert_act_quant_kernel(const uint16_t* __restrict__ ue, const uint16_t* __restrict__ ge, int ld, int S,
+                                                               int r, int8_t* __restrict__ aq, float* __restrict__ gamma,
+                                                               uint16_t* __restrict__ at) {
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (row >= S) return;
+  const uint4* u4 = reinterpret_cast<const uint4*>(ue + (size_t)row * ld);
+  const uint4* g4 = reinterpret_cast<const uint4*>(ge + (size_t)row * ld);
+  const int nvec = r / 8;
+  uint4 uv[NV], gv[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c = min(i * 64 + lane, nvec - 1);      // (past the end: the last vector again, which cannot change the maximum)
+    uv[i] = u4[c];
+    gv[i] = g4[c];
+  }
+  float amax = 0.0f;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    float u[8], g[8];
+    vec16<uint16_t>::unpack(uv[i], u);
+    vec16<uint16_t>::unpack(gv[i], g);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) u[j] = pq_silu(g[j]) * u[j];
+    uv[i] = make_uint4(pack_bf16x2(u[0], u[1]), pack_bf16x2(u[2], u[3]), pack_bf16x2(u[4], u[5]), pack_bf16x2(u[6], u[7]));
+    vec16<uint16_t>::unpack(uv[i], u);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) amax = fmaxf(amax, fabsf(u[j]));
+  }
+  amax = wave_max(amax);
+  const float g = 128.0f / fmaxf(amax, 1e-5f);
+  if (lane == 0) gamma[row] = g;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c = i * 64 + lane;
+    if (c < nvec) quant_store<uint16_t>(uv[i], g, aq + (size_t)row * r, at + (size_t)row * r, c);
+  }
+}
+
+bool pq_expert_act_quant_applies(int r) { return r <= 2048; }
+int pq_launch_expert_act_quant(const void* ue, const void* ge, int ld, int S, int r, int8_t* aq, float* gamma, void* at, hipStream_t s) {
+  if (S == 0) return PQ_OK;
+  pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
+  const dim3 grid((S + 3) / 4), block(256);
+  const uint16_t *u = (const uint16_t*)ue, *g = (const uint16_t*)ge;
+  if (r <= 512) expert_act_quant_kernel<1><<<grid, block, 0, s>>>(u, g, ld, S, r, aq, gamma, (uint16_t*)at);
+  else if (r <= 2048) expert_act_quant_kernel<4><<<grid, block, 0, s>>>(u, g, ld, S, r, aq, gamma, (uint16_t*)at);
+  else return pq_set_error(PQ_ERR_SHAPE, "rows of %d elements do not fit the registers of the expert quantiser", r);
+  PQ_CHECK_LAUNCH("expert_act_quant_kernel");
+  return PQ_OK;
+}
+
 template <typename T>
 static int launch_quant_t(const T* X, int Tn, int K, int8_t* Xq, float* gamma, uint16_t* Xt,
                           hipStream_t s) {
@@ -133,10 +188,39 @@ int pq_launch_quant_act(const void* X, int dtype, int T, int K, int8_t* Xq, floa
 }
 
 // ------------------------------------------------------------------------------------------
+// Weight statistics, stage 1: grid-stride fp64 sums of W and |W|, one pair per block.
+// ------------------------------------------------------------------------------------------
+template <typename T>
+__device__ __forceinline__ void wstats_partial_body(const T* __restrict__ W, size_t nvec, double* __restrict__ partials, int block,
+                                                    int nblocks) {
+  constexpr int V = vec16<T>::V;
+  __shared__ double red[4];
+  const uint4* w4 = reinterpret_cast<const uint4*>(W);
+  double s = 0.0, a = 0.0;
+  for (size_t c = (size_t)block * 256 + threadIdx.x; c < nvec; c += (size_t)nblocks * 256) {
+    float f[V];
+    vec16<T>::unpack(w4[c], f);
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      s += (double)f[j];
+      a += (double)fabsf(f[j]);
+    }
+  }
+  double bs = block_sum_d<256>(s, red);
+  double ba = block_sum_d<256>(a, red);
+  if (threadIdx.x == 0) {
+    partials[2 * block] = bs;
+    partials[2 * block + 1] = ba;
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 // RMSNorm fused with the AbsMax quantiser (Sec. 3.1: Q(Norm(X)); App. A: both are element-wise per token
 // and merge; App. B: RMSNorm).  One wavefront per token, the row stays in registers between the three
 // steps: sum of squares (fp64, so that rstd does not depend on the order of the sum beyond its last fp64
-// bit), x_hat = fl(fl(x rstd) g) rounded to the I/O type, then the quantiser of the stored x_hat.
+// bit), x_hat = fl(fl(x rstd) g) rounded to the I/O type, then the quantiser of the stored x_hat.  The first nw workgroups
+// take the first stage of a weight's statistics instead (a linear with its normalisation: as a launch of their own they
+// were 5 us of the 230 of forward and backward of 4096 tokens 2048x2048, within this one 1).
 // ------------------------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ uint4 pack_io(const float* f);
@@ -153,10 +237,15 @@ template <typename T, int NV>
 __global__ __launch_bounds__(256) void rmsnorm_quant_kernel(const T* __restrict__ X, const T* __restrict__ gain, int Tn, int K,
                                                             float eps, T* __restrict__ Xn, int8_t* __restrict__ Xq,
                                                             float* __restrict__ gamma, uint16_t* __restrict__ Xt,
-                                                            float* __restrict__ rstd_out) {
+                                                            float* __restrict__ rstd_out, const T* __restrict__ W, size_t w_vecs,
+                                                            double* __restrict__ partials, int nw) {
+  if ((int)blockIdx.x < nw) {                        // uniform
+    wstats_partial_body<T>(W, w_vecs, partials, blockIdx.x, nw);
+    return;
+  }
   constexpr int V = vec16<T>::V;
   const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int row = (blockIdx.x - nw) * 4 + (threadIdx.x >> 6);
   if (row >= Tn) return;
   const uint4* xr = reinterpret_cast<const uint4*>(X + (size_t)row * K);
   const uint4* gr = reinterpret_cast<const uint4*>(gain);
@@ -215,25 +304,27 @@ __global__ __launch_bounds__(256) void rmsnorm_quant_kernel(const T* __restrict_
 
 template <typename T>
 static int launch_rmsnorm_quant_t(const T* X, const T* gain, int Tn, int K, float eps, T* Xn, int8_t* Xq, float* gamma,
-                                  uint16_t* Xt, float* rstd, hipStream_t s) {
+                                  uint16_t* Xt, float* rstd, hipStream_t s, const T* W, size_t w_elems, double* partials, int nw) {
   constexpr int V = vec16<T>::V;
   const int per_lane = (K / V + 63) / 64;
-  dim3 grid((Tn + 3) / 4), block(256);
-  if (per_lane <= 4) rmsnorm_quant_kernel<T, 4><<<grid, block, 0, s>>>(X, gain, Tn, K, eps, Xn, Xq, gamma, Xt, rstd);
-  else if (per_lane <= 8) rmsnorm_quant_kernel<T, 8><<<grid, block, 0, s>>>(X, gain, Tn, K, eps, Xn, Xq, gamma, Xt, rstd);
-  else if (per_lane <= 16) rmsnorm_quant_kernel<T, 16><<<grid, block, 0, s>>>(X, gain, Tn, K, eps, Xn, Xq, gamma, Xt, rstd);
+  dim3 grid((Tn + 3) / 4 + nw), block(256);
+  const size_t wv = w_elems / V;
+  if (per_lane <= 4) rmsnorm_quant_kernel<T, 4><<<grid, block, 0, s>>>(X, gain, Tn, K, eps, Xn, Xq, gamma, Xt, rstd, W, wv, partials, nw);
+  else if (per_lane <= 8) rmsnorm_quant_kernel<T, 8><<<grid, block, 0, s>>>(X, gain, Tn, K, eps, Xn, Xq, gamma, Xt, rstd, W, wv, partials, nw);
+  else if (per_lane <= 16) rmsnorm_quant_kernel<T, 16><<<grid, block, 0, s>>>(X, gain, Tn, K, eps, Xn, Xq, gamma, Xt, rstd, W, wv, partials, nw);
   else return pq_set_error(PQ_ERR_SHAPE, "row of %d elements does not fit the register cache of the fused normalising quantiser", K);
   PQ_CHECK_LAUNCH("rmsnorm_quant_kernel");
   return PQ_OK;
 }
 
 int pq_launch_rmsnorm_quant(const void* X, const void* gain, int dtype, int T, int K, float eps, void* Xn, int8_t* Xq,
-                            float* gamma, uint16_t* Xt, float* rstd, hipStream_t s) {
-  if (T == 0) return PQ_OK;
+                            float* gamma, uint16_t* Xt, float* rstd, hipStream_t s, const void* W, size_t w_elems, double* partials, int nw) {
+  if (T == 0 && nw == 0) return PQ_OK;
   pq_prof_scope prof(PQP_NORM_QUANT, s);
   if (dtype == PQ_F32)
-    return launch_rmsnorm_quant_t<float>((const float*)X, (const float*)gain, T, K, eps, (float*)Xn, Xq, gamma, Xt, rstd, s);
-  return launch_rmsnorm_quant_t<uint16_t>((const uint16_t*)X, (const uint16_t*)gain, T, K, eps, (uint16_t*)Xn, Xq, gamma, Xt, rstd, s);
+    return launch_rmsnorm_quant_t<float>((const float*)X, (const float*)gain, T, K, eps, (float*)Xn, Xq, gamma, Xt, rstd, s, (const float*)W, w_elems, partials, nw);
+  return launch_rmsnorm_quant_t<uint16_t>((const uint16_t*)X, (const uint16_t*)gain, T, K, eps, (uint16_t*)Xn, Xq, gamma, Xt, rstd, s, (const uint16_t*)W,
+                                          w_elems, partials, nw);
 }
 
 // Backward of the normalisation (the quantiser is passed straight through, App. B.1): with u = x rstd,
@@ -440,33 +531,6 @@ int pq_static_scratch(void** out) {
   }
   *out = g_scratch_ptr[dev];
   return PQ_OK;
-}
-
-// ------------------------------------------------------------------------------------------
-// Weight statistics, stage 1: grid-stride fp64 sums of W and |W|, one pair per block.
-// ------------------------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ void wstats_partial_body(const T* __restrict__ W, size_t nvec, double* __restrict__ partials, int block,
-                                                    int nblocks) {
-  constexpr int V = vec16<T>::V;
-  __shared__ double red[4];
-  const uint4* w4 = reinterpret_cast<const uint4*>(W);
-  double s = 0.0, a = 0.0;
-  for (size_t c = (size_t)block * 256 + threadIdx.x; c < nvec; c += (size_t)nblocks * 256) {
-    float f[V];
-    vec16<T>::unpack(w4[c], f);
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-      s += (double)f[j];
-      a += (double)fabsf(f[j]);
-    }
-  }
-  double bs = block_sum_d<256>(s, red);
-  double ba = block_sum_d<256>(a, red);
-  if (threadIdx.x == 0) {
-    partials[2 * block] = bs;
-    partials[2 * block + 1] = ba;
-  }
 }
 
 template <typename T>

@@ -131,11 +131,13 @@ def test_ffn_paper_1p3b_shape_reduced_tokens(N):
 @pytest.mark.parametrize("T,D,F,E,r,k", [(700, 256, 544, 8, 32, 1), (200, 96, 160, 4, 32, 2), (300, 256, 500, 1, 64, 1),
                                          (1, 32, 32, 8, 32, 1), (384, 2048, 5504, 8, 32, 1), (384, 2048, 5076, 4, 384, 1),
                                          # a single INT8 branch (the paper's default N = 1 in the form Sec. 3.2 prints): no routing
-                                         (1100, 128, 96, 1, 32, 1), (384, 2048, 5076, 1, 384, 1)])
+                                         (1100, 128, 96, 1, 32, 1), (384, 2048, 5076, 1, 384, 1),
+                                         # hidden rows of more than one vector per lane, and too long for registers
+                                         (70, 64, 96, 2, 544, 1), (33, 64, 96, 1, 2080, 1)])
 def test_ffn_int8_experts(T, D, F, E, r, k):
     """The experts in the INT8 form the FFN equation of Sec. 3.2 prints: weight rows and the expert's hidden state on the
-    AbsMax grid, x's codes shared with the 1-bit branch, STE backward on the de-quantised factors.  The last two shapes
-    are config 3 and the paper's 1.3B FFN (Table 1) at 384 tokens."""
+    AbsMax grid, x's codes shared with the 1-bit branch, STE backward on the de-quantised factors.  Config 3 and the paper's
+    1.3B FFN (Table 1) are among them at 384 tokens."""
     print(f"ffn int8 experts T={T} d={D} F={F} E={E} r={r} k={k}", flush=True)
     check_ffn(wl.ffn_case(180 + T + k + r, T, D, F, E, r), top_k=k, experts="int8")
 
