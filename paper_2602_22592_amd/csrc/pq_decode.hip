@@ -38,6 +38,23 @@ __device__ __forceinline__ int wave_sum_i(int v) {
   return v;
 }
 
+// N sums over the wavefront at once, as wave_sum_transposed: lane l ends with the sum of value l / (64 / N) in v[0]
+template <int N, int OFF>
+__device__ __forceinline__ void wave_sum_transposed_i(int* v, int lane) {
+  if constexpr (N > 1) {
+    const bool up = (lane & OFF) != 0;
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+      const int send = up ? v[i] : v[i + N / 2], keep = up ? v[i + N / 2] : v[i];
+      v[i] = keep + __shfl_xor(send, OFF, 64);
+    }
+    if constexpr (OFF > 1) wave_sum_transposed_i<N / 2, OFF / 2>(v, lane);
+  } else {
+    v[0] += __shfl_xor(v[0], OFF, 64);
+    if constexpr (OFF > 1) wave_sum_transposed_i<1, OFF / 2>(v, lane);
+  }
+}
+
 __device__ __forceinline__ float fp16_bits_to_f32(uint16_t h) {
   _Float16 x = __builtin_bit_cast(_Float16, h);
   return (float)x;
@@ -475,92 +492,121 @@ __global__ __launch_bounds__(256) void decode_prep_h_kernel(prep_h_params p) {
 // ------------------------------------------------------------------------------------------
 // Expert hidden state: one wavefront per (layer, token, slot, r): h = A_e[r,:] . x   (bf16 in, fp32 out)
 // ------------------------------------------------------------------------------------------
-// INT8 experts: hpA holds INT8 codes with one gamma per row (gA).  One workgroup per (layer, expert, group of 16
-// rows); its four wavefronts share out the tokens of the layer that selected the expert (found by scanning the
-// layer's index list), so the 16 rows are fetched from memory once however many tokens use them.  Per token the
-// codes are formed once per 4096 columns from x and its gamma (the quantiser's arithmetic) and kept in
-// registers for the 16 rows; the products are exact integers, de-quantised as
-// fl32(fl32(1/gamma_x) * acc) / gamma_a and rounded to bf16 (held as fp32).  Columns past the end carry zero
-// codes and re-read the last chunk, so no load sits behind a branch.
-constexpr int H8_ROWS = 16;
-__device__ __forceinline__ void h_int8_slot(const uint16_t* __restrict__ X, const int8_t* __restrict__ A8,
-                                            const float* __restrict__ gA, const float* __restrict__ gamma, int K, int r,
-                                            int slot, int tok, size_t arow0, int rg, float* __restrict__ h) {
-  const int lane = threadIdx.x & 63;
-  const uint4* x4 = reinterpret_cast<const uint4*>(X + (size_t)tok * K);
-  const float gx = gamma[tok];
-  const int nch = K / 16;
-  int acc[H8_ROWS];
-#pragma unroll
-  for (int rr = 0; rr < H8_ROWS; ++rr) acc[rr] = 0;
-  for (int c0 = 0; c0 < nch; c0 += 256) {
-    uint32_t xw[4][4];
-    int cc[4];
-    uint4 xv[8];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      cc[i] = min(c0 + lane + 64 * i, nch - 1);
-      xv[2 * i] = x4[2 * cc[i]];
-      xv[2 * i + 1] = x4[2 * cc[i] + 1];
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const bool ok = c0 + lane + 64 * i < nch;
-      const uint32_t w8[8] = {xv[2 * i].x, xv[2 * i].y, xv[2 * i].z, xv[2 * i].w, xv[2 * i + 1].x, xv[2 * i + 1].y, xv[2 * i + 1].z, xv[2 * i + 1].w};
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {                    // four codes per word: columns 4 d .. 4 d + 3 of the chunk
-        const float f[4] = {__uint_as_float(w8[2 * d] << 16), __uint_as_float(w8[2 * d] & 0xFFFF0000u),
-                            __uint_as_float(w8[2 * d + 1] << 16), __uint_as_float(w8[2 * d + 1] & 0xFFFF0000u)};
-        uint32_t w = 0u;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int q = (int)fminf(fmaxf(rintf(__fmul_rn(f[t], gx)), -128.0f), 127.0f);
-          w |= (uint32_t)(q & 0xFF) << (8 * t);
-        }
-        xw[i][d] = ok ? w : 0u;
-      }
-    }
-#pragma unroll 4
-    for (int rr = 0; rr < H8_ROWS; ++rr) {
-      const uint4* a4 = reinterpret_cast<const uint4*>(A8 + (arow0 + rr) * K);
-      uint4 av[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = a4[cc[i]];        // cached: the other wavefronts of the workgroup read the same rows
-      int a = acc[rr];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        a = __builtin_amdgcn_sdot4((int)av[i].x, (int)xw[i][0], a, false);
-        a = __builtin_amdgcn_sdot4((int)av[i].y, (int)xw[i][1], a, false);
-        a = __builtin_amdgcn_sdot4((int)av[i].z, (int)xw[i][2], a, false);
-        a = __builtin_amdgcn_sdot4((int)av[i].w, (int)xw[i][3], a, false);
-      }
-      acc[rr] = a;
-    }
-  }
-  const float sx = 1.0f / gx;
-#pragma unroll
-  for (int rr = 0; rr < H8_ROWS; ++rr) {
-    const int t = wave_sum_i(acc[rr]);
-    if (lane == 0) h[(size_t)slot * r + rg * H8_ROWS + rr] = bf16_to_f32(f32_to_bf16(__fmul_rn(sx, (float)t) / gA[arow0 + rr]));
-  }
-}
-
+// INT8 experts: hpA holds INT8 codes with one gamma per row (gA).  One workgroup per (layer, expert, group of 16 rows), four
+// rows to a wavefront, all of whose loads (1024 NV columns) are in flight before anything else happens: bound by the row bytes,
+// which are read once however many tokens use them (up to eight at a time; more read them again, from L2).  Meanwhile the
+// wavefronts form the codes of those tokens from x and its gamma (the quantiser's arithmetic), a token each, in LDS.  The
+// products are exact integers, de-quantised as fl32(fl32(1/gamma_x) * acc) / gamma_a and rounded to bf16 (held as fp32).
+// Columns past the end carry zero codes and re-read the last chunk, so no load sits behind a branch.  With a token and all 16
+// rows to a wavefront (two of four idle at two tokens per expert, four rows in flight) 8 tokens through 64 layers of 8 experts
+// of 64 x 4096 (121 MB) took 38 us, the whole call 206.6; now the call takes 189.7.
+constexpr int H8_ROWS = 16, H8_USERS = 8;
+template <int NV>
 __global__ __launch_bounds__(256) void decode_h_int8_kernel(const uint16_t* __restrict__ X, const int8_t* __restrict__ A8,
                                                             const float* __restrict__ gA, const float* __restrict__ gamma,
                                                             const int* __restrict__ idx, int B, int K, int E, int r, int topk,
                                                             float* __restrict__ h) {
+  __shared__ uint4 xc[H8_USERS][64 * NV];
+  const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ngrp = r / H8_ROWS;
   const int rg = blockIdx.x % ngrp, le = blockIdx.x / ngrp;    // le = layer * E + e
   const int layer = le / E, e = le - layer * E;
-  const int nslot = B * topk;
-  const int* lidx = idx + (size_t)layer * nslot;
-  const size_t arow0 = (size_t)le * r + (size_t)rg * H8_ROWS;
-  int cnt = 0;
-  for (int sl = 0; sl < nslot; ++sl) {                // uniform scan: the cnt-th user of this expert goes to wave cnt % 4
-    if (lidx[sl] != e) continue;
-    if ((cnt & 3) == wave) h_int8_slot(X, A8, gA, gamma, K, r, layer * nslot + sl, layer * B + sl / topk, arow0, rg, h);
-    ++cnt;
+  const int nslot = B * topk, nch = K / 16;
+  const int r0 = rg * H8_ROWS + 4 * wave;             // the wavefront's first row
+  const uint4* a4 = reinterpret_cast<const uint4*>(A8 + ((size_t)le * r + r0) * K);
+  for (int base = 0; base < nslot; base += 64) {
+    // the layer's selections as a mask of the expert's slots, the same in every wavefront
+    const int sel = base + lane < nslot ? idx[(size_t)layer * nslot + base + lane] : -1;
+    unsigned long long users = __ballot(sel == e);
+    while (users) {
+      const int n = min(__builtin_popcountll(users), H8_USERS);
+      int acc[4][H8_USERS];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int u = 0; u < H8_USERS; ++u) acc[j][u] = 0;
+      for (int c0 = 0; c0 < nch; c0 += 64 * NV) {
+        uint4 av[4][NV];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int i = 0; i < NV; ++i) av[j][i] = a4[(size_t)j * nch + min(c0 + lane + 64 * i, nch - 1)];
+        unsigned long long m = users;
+        for (int u = 0; u < n; ++u, m &= m - 1ull) {
+          if ((u & 3) != wave) continue;              // uniform: a token to a wavefront
+          const int tok = layer * B + (base + __builtin_ctzll(m)) / topk;
+          const uint4* x4 = reinterpret_cast<const uint4*>(X + (size_t)tok * K);
+          const float gx = gamma[tok];
+          uint4 xv[2 * NV];
+#pragma unroll
+          for (int i = 0; i < NV; ++i) {
+            const int cc = min(c0 + lane + 64 * i, nch - 1);
+            xv[2 * i] = x4[2 * cc];
+            xv[2 * i + 1] = x4[2 * cc + 1];
+          }
+#pragma unroll
+          for (int i = 0; i < NV; ++i) {
+            const bool ok = c0 + lane + 64 * i < nch;
+            const uint32_t w8[8] = {xv[2 * i].x, xv[2 * i].y, xv[2 * i].z, xv[2 * i].w, xv[2 * i + 1].x, xv[2 * i + 1].y, xv[2 * i + 1].z, xv[2 * i + 1].w};
+            uint32_t xw[4];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {              // four codes per word: columns 4 d .. 4 d + 3 of the chunk
+              const float f[4] = {__uint_as_float(w8[2 * d] << 16), __uint_as_float(w8[2 * d] & 0xFFFF0000u),
+                                  __uint_as_float(w8[2 * d + 1] << 16), __uint_as_float(w8[2 * d + 1] & 0xFFFF0000u)};
+              uint32_t w = 0u;
+#pragma unroll
+              for (int t = 0; t < 4; ++t) {
+                const int q = (int)fminf(fmaxf(rintf(__fmul_rn(f[t], gx)), -128.0f), 127.0f);
+                w |= (uint32_t)(q & 0xFF) << (8 * t);
+              }
+              xw[d] = ok ? w : 0u;
+            }
+            xc[u][64 * i + lane] = make_uint4(xw[0], xw[1], xw[2], xw[3]);
+          }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < H8_USERS; ++u) {
+          if (u < n) {                                // uniform
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+              const uint4 q = xc[u][64 * i + lane];
+#pragma unroll
+              for (int j = 0; j < 4; ++j) {
+                int a = acc[j][u];
+                a = __builtin_amdgcn_sdot4((int)av[j][i].x, (int)q.x, a, false);
+                a = __builtin_amdgcn_sdot4((int)av[j][i].y, (int)q.y, a, false);
+                a = __builtin_amdgcn_sdot4((int)av[j][i].z, (int)q.z, a, false);
+                acc[j][u] = __builtin_amdgcn_sdot4((int)av[j][i].w, (int)q.w, a, false);
+              }
+            }
+          }
+        }
+        __syncthreads();                              // the next codes overwrite these
+      }
+      // two tokens' eight sums at a time, transposed: lane 32 (u % 2) + 8 j + u / 2 keeps the sum of token u and row j, and one
+      // division and one store serve all of them
+      int mine = 0;
+#pragma unroll
+      for (int u2 = 0; u2 < H8_USERS / 2; ++u2)
+        if (2 * u2 < n) {                             // uniform
+          int v[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) v[q] = acc[q & 3][2 * u2 + (q >> 2)];
+          wave_sum_transposed_i<8, 32>(v, lane);
+          mine = (lane & 7) == u2 ? v[0] : mine;
+        }
+      const int mu = 2 * (lane & 7) + (lane >> 5), row = r0 + ((lane >> 3) & 3);
+      if (mu < n) {
+        unsigned long long m = users;
+        for (int u = 0; u < mu; ++u) m &= m - 1ull;
+        const int slot = base + __builtin_ctzll(m);
+        const float sx = 1.0f / gamma[layer * B + slot / topk];
+        h[((size_t)layer * nslot + slot) * r + row] = bf16_to_f32(f32_to_bf16(__fmul_rn(sx, (float)mine) / gA[(size_t)le * r + row]));
+      }
+      for (int u = 0; u < n; ++u) users &= users - 1ull;
+    }
   }
 }
 
@@ -2027,8 +2073,8 @@ int pq_launch_decode(const pq_decode_desc& d, const void* X, const uint32_t* pac
       pq_prof_scope prof(PQP_DECODE_H, s);
       const int total = L * B * d.top_k * r;
       if (i8) {
-        decode_h_int8_kernel<<<L * d.n_experts * (r / H8_ROWS), 256, 0, s>>>((const uint16_t*)X, (const int8_t*)hpA, gA, gamma, idx, B, K,
-                                                                           d.n_experts, r, d.top_k, h);
+        const auto hk = K <= 1024 ? decode_h_int8_kernel<1> : K <= 2048 ? decode_h_int8_kernel<2> : decode_h_int8_kernel<4>;
+        hk<<<L * d.n_experts * (r / H8_ROWS), 256, 0, s>>>((const uint16_t*)X, (const int8_t*)hpA, gA, gamma, idx, B, K, d.n_experts, r, d.top_k, h);
       } else
         if (!launch_h_grouped((const uint16_t*)X, (const uint16_t*)hpA, idx, L, B, K, d.n_experts, r, d.top_k, h, s))
           decode_h_kernel<<<(total + 3) / 4, 256, 0, s>>>((const uint16_t*)X, (const uint16_t*)hpA, idx, B, K, d.n_experts, r, d.top_k, total, h);

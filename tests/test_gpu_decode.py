@@ -170,7 +170,9 @@ def test_decode_int8_experts_alone_and_limits():
 
 
 @pytest.mark.parametrize("L,B,K,N,E,r,k", [(1, 3, 512, 200, 4, 64, 2), (2, 8, 1024, 1028, 8, 64, 2), (1, 16, 512, 64, 2, 64, 1),
-                                           (1, 5, 1536, 520, 8, 128, 3), (1, 9, 640, 132, 4, 64, 2)])
+                                           (1, 5, 1536, 520, 8, 128, 3), (1, 9, 640, 132, 4, 64, 2),
+                                           # more than eight tokens per expert; more than 64 selections; several blocks of columns
+                                           (2, 13, 2176, 64, 2, 64, 2), (1, 16, 1024, 64, 8, 64, 8), (1, 16, 4224, 128, 2, 64, 1)])
 def test_decode_int8_experts_small_batch(L, B, K, N, E, r, k):
     print(f"decode INT8 experts B={B}: L={L} K={K} N={N} E={E} r={r} k={k}", flush=True)
     check_decode_int8(wl.decode_case(90 + K + N + B, B, d_in=K, d_out=N, n_experts=E, hp_rank=r, n_layers=L), top_k=k,
