@@ -19,8 +19,8 @@
 // the bench keeps the working set larger than the Infinity Cache.
 #include <mutex>
 
-#include "pq_internal.h"
 #include <type_traits>
+#include "pq_internal.h"
 
 namespace {
 
@@ -645,18 +645,20 @@ __global__ __launch_bounds__(256) void decode_h_kernel(const uint16_t* __restric
   if (lane == 0) h[o] = acc;
 }
 
-// The same hidden states computed expert by expert (K = 512 NV <= 4096, at most 64 slots per layer): a workgroup owns
-// HG_ROWS rows of one expert of one layer, a wavefront two of them, held packed in registers (a row of 4096 bf16 is
+// The same hidden states computed expert by expert (rows of up to 512 NV <= 4096 columns, at most 64 slots per layer): a
+// workgroup owns HG_ROWS rows of one expert of one layer, a wavefront two of them, held packed in registers (a row of 4096 bf16 is
 // eight 16-byte pieces per lane); every token of the batch that selected the expert is then run against them, so an
 // expert's rows are read from memory once instead of once per selecting token.  The layer's selections are fetched with
 // one vector load and turned into a mask of the expert's slots (a scan with scalar loads is a chain of memory latencies);
 // workgroups of experts nobody selected return at once.  Per (slot, row) the sum runs in the order of decode_h_kernel.
+// TAIL: the row ends inside a lane's last piece; lanes past its end hold zeros on both sides.
 constexpr int HG_ROWS = 8;
-template <int NV>
+template <int NV, bool TAIL>
 __global__ __launch_bounds__(256) void decode_h_grouped_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ hpA,
-                                                               const int* __restrict__ idx, int B, int E, int r, int topk,
+                                                               const int* __restrict__ idx, int B, int Kt, int E, int r, int topk,
                                                                float* __restrict__ h) {
-  constexpr int K = 512 * NV;
+  constexpr int RW = HG_ROWS / 4;
+  const int K = TAIL ? Kt : 512 * NV;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ngrp = r / HG_ROWS;
@@ -666,57 +668,86 @@ __global__ __launch_bounds__(256) void decode_h_grouped_kernel(const uint16_t* _
   const int sel = lane < nslot ? idx[(size_t)layer * nslot + lane] : -1;
   unsigned long long users = __ballot(sel == e);
   if (users == 0ull) return;
-  const int r0 = rg * HG_ROWS + 2 * wave;
-  const uint4* a0 = reinterpret_cast<const uint4*>(hpA + ((size_t)le * r + r0) * K) + lane;
-  const uint4* a1 = a0 + K / 8;
-  uint4 av0[NV], av1[NV];
+  const int r0 = rg * HG_ROWS + RW * wave;
+  const int nch = K / 8;
+  auto piece = [&](int i) { return TAIL && i == NV - 1 ? min(lane + 64 * i, nch - 1) : lane + 64 * i; };
+  auto ended = [&](int i) { return TAIL && i == NV - 1 && lane + 64 * i >= nch; };
+  const uint4* a0 = reinterpret_cast<const uint4*>(hpA + ((size_t)le * r + r0) * K);
+  uint4 av[RW][NV];
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    av0[i] = nt_load16(a0 + 64 * i);
-    av1[i] = nt_load16(a1 + 64 * i);
-  }
+  for (int i = 0; i < NV; ++i)
+#pragma unroll
+    for (int q = 0; q < RW; ++q) av[q][i] = nt_load16(a0 + (size_t)q * nch + piece(i));
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+#pragma unroll
+    for (int q = 0; q < RW; ++q)
+      if (ended(i)) av[q][i] = make_uint4(0u, 0u, 0u, 0u);
   while (users) {
     const int sl = __builtin_ctzll(users);
     users &= users - 1ull;
-    const uint4* x4 = reinterpret_cast<const uint4*>(X + ((size_t)layer * B + sl / topk) * K) + lane;
+    const uint4* x4 = reinterpret_cast<const uint4*>(X + ((size_t)layer * B + sl / topk) * K);
     uint4 xv[NV];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) xv[i] = x4[64 * i];
-    float s0 = 0.0f, s1 = 0.0f;
+    for (int i = 0; i < NV; ++i) xv[i] = x4[piece(i)];
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      if (ended(i)) xv[i] = make_uint4(0u, 0u, 0u, 0u);
+    float sum[RW];
+#pragma unroll
+    for (int q = 0; q < RW; ++q) sum[q] = 0.0f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      // (the rows stay packed: without this the unpacked halves are hoisted out of the loop and held in 128 more registers)
-      asm volatile("" : "+v"(av0[i].x), "+v"(av0[i].y), "+v"(av0[i].z), "+v"(av0[i].w), "+v"(av1[i].x), "+v"(av1[i].y), "+v"(av1[i].z), "+v"(av1[i].w));
-      const uint4 x = xv[i], a = av0[i], b = av1[i];
-      s0 += __uint_as_float(a.x << 16) * __uint_as_float(x.x << 16) + __uint_as_float(a.x & 0xFFFF0000u) * __uint_as_float(x.x & 0xFFFF0000u);
-      s0 += __uint_as_float(a.y << 16) * __uint_as_float(x.y << 16) + __uint_as_float(a.y & 0xFFFF0000u) * __uint_as_float(x.y & 0xFFFF0000u);
-      s0 += __uint_as_float(a.z << 16) * __uint_as_float(x.z << 16) + __uint_as_float(a.z & 0xFFFF0000u) * __uint_as_float(x.z & 0xFFFF0000u);
-      s0 += __uint_as_float(a.w << 16) * __uint_as_float(x.w << 16) + __uint_as_float(a.w & 0xFFFF0000u) * __uint_as_float(x.w & 0xFFFF0000u);
-      s1 += __uint_as_float(b.x << 16) * __uint_as_float(x.x << 16) + __uint_as_float(b.x & 0xFFFF0000u) * __uint_as_float(x.x & 0xFFFF0000u);
-      s1 += __uint_as_float(b.y << 16) * __uint_as_float(x.y << 16) + __uint_as_float(b.y & 0xFFFF0000u) * __uint_as_float(x.y & 0xFFFF0000u);
-      s1 += __uint_as_float(b.z << 16) * __uint_as_float(x.z << 16) + __uint_as_float(b.z & 0xFFFF0000u) * __uint_as_float(x.z & 0xFFFF0000u);
-      s1 += __uint_as_float(b.w << 16) * __uint_as_float(x.w << 16) + __uint_as_float(b.w & 0xFFFF0000u) * __uint_as_float(x.w & 0xFFFF0000u);
+      const uint4 x = xv[i];
+#pragma unroll
+      for (int q = 0; q < RW; ++q) {
+        // (the rows stay packed: without this the unpacked halves are hoisted out of the loop and held in 128 more registers)
+        asm volatile("" : "+v"(av[q][i].x), "+v"(av[q][i].y), "+v"(av[q][i].z), "+v"(av[q][i].w));
+        const uint4 a = av[q][i];
+        float t = sum[q];
+        t += __uint_as_float(a.x << 16) * __uint_as_float(x.x << 16) + __uint_as_float(a.x & 0xFFFF0000u) * __uint_as_float(x.x & 0xFFFF0000u);
+        t += __uint_as_float(a.y << 16) * __uint_as_float(x.y << 16) + __uint_as_float(a.y & 0xFFFF0000u) * __uint_as_float(x.y & 0xFFFF0000u);
+        t += __uint_as_float(a.z << 16) * __uint_as_float(x.z << 16) + __uint_as_float(a.z & 0xFFFF0000u) * __uint_as_float(x.z & 0xFFFF0000u);
+        t += __uint_as_float(a.w << 16) * __uint_as_float(x.w << 16) + __uint_as_float(a.w & 0xFFFF0000u) * __uint_as_float(x.w & 0xFFFF0000u);
+        sum[q] = t;
+      }
     }
-    s0 = wave_sum(s0);
-    s1 = wave_sum(s1);
+#pragma unroll
+    for (int q = 0; q < RW; ++q) sum[q] = wave_sum(sum[q]);
     if (lane == 0) {
       float* hs = h + ((size_t)layer * nslot + sl) * r + r0;
-      hs[0] = s0;
-      hs[1] = s1;
+#pragma unroll
+      for (int q = 0; q < RW; ++q) hs[q] = sum[q];
     }
   }
 }
 
-// launches the expert-grouped kernel when the shape allows it (then returns true)
+// Launches the expert-grouped kernel when the shape allows it (then returns true).  Widths other than 512, 1024, 2048 and 4096
+// take it from 1024 workgroups on, where its one pass over the rows decides (whole calls: 13 tokens, 40 layers of 2560 63.3 -> 55.3
+// us; 8 tokens, 16 layers of 3328 50.9 -> 48.0; decode FFN of 16 tokens, 20 layers of 3584/8192 190 -> 171); with 64 the tokens of an
+// expert one after the other are the longer chain (decode FFN of 3 tokens, 2 layers of 1280/3072 26.8 -> 27.6), and a wavefront per
+// slot and row stays.  So it does past 4096 columns, where only one row to a wavefront fits the registers (4 tokens, 8 layers of
+// 6144 36.6 -> 39.9; 16 tokens, 2 layers of 7680 43 -> 57).
 static bool launch_h_grouped(const uint16_t* X, const uint16_t* A, const int* idx, int L, int B, int K, int E, int r, int topk, float* h,
                              hipStream_t s) {
-  if (r % HG_ROWS != 0 || B * topk > 64) return false;
-  const dim3 grid(L * E * (r / HG_ROWS)), block(256);
-  if (K == 4096) decode_h_grouped_kernel<8><<<grid, block, 0, s>>>(X, A, idx, B, E, r, topk, h);
-  else if (K == 2048) decode_h_grouped_kernel<4><<<grid, block, 0, s>>>(X, A, idx, B, E, r, topk, h);
-  else if (K == 1024) decode_h_grouped_kernel<2><<<grid, block, 0, s>>>(X, A, idx, B, E, r, topk, h);
-  else if (K == 512) decode_h_grouped_kernel<1><<<grid, block, 0, s>>>(X, A, idx, B, E, r, topk, h);
-  else return false;
+  if (r % HG_ROWS != 0 || B * topk > 64 || K % 8 != 0 || K > 4096) return false;
+  const long groups = (long)L * E * (r / HG_ROWS);
+  if (!(K == 512 || K == 1024 || K == 2048 || K == 4096) && groups < 1024) return false;
+  auto go = [&](auto nv) {
+    constexpr int NV = decltype(nv)::value;
+    if (K == 512 * NV) decode_h_grouped_kernel<NV, false><<<(unsigned)groups, 256, 0, s>>>(X, A, idx, B, K, E, r, topk, h);
+    else decode_h_grouped_kernel<NV, true><<<(unsigned)groups, 256, 0, s>>>(X, A, idx, B, K, E, r, topk, h);
+  };
+  switch ((K + 511) / 512) {
+    case 1: go(std::integral_constant<int, 1>()); break;
+    case 2: go(std::integral_constant<int, 2>()); break;
+    case 3: go(std::integral_constant<int, 3>()); break;
+    case 4: go(std::integral_constant<int, 4>()); break;
+    case 5: go(std::integral_constant<int, 5>()); break;
+    case 6: go(std::integral_constant<int, 6>()); break;
+    case 7: go(std::integral_constant<int, 7>()); break;
+    default: go(std::integral_constant<int, 8>()); break;
+  }
   return true;
 }
 

@@ -85,7 +85,11 @@ def test_decode_small_batch(L, B, K, N, E, r, k, tiled):
 
 @pytest.mark.parametrize("L,B,K,N,E,r,k", [(1, 4, 640, 132, 4, 32, 2), (2, 9, 1408, 260, 2, 64, 1),
                                            # the codes pass through LDS in blocks of 32 KB: three blocks, the last one ragged
-                                           (1, 16, 4352, 132, 4, 32, 2), (1, 7, 8960, 200, 2, 32, 1)])
+                                           (1, 16, 4352, 132, 4, 32, 2), (1, 7, 8960, 200, 2, 32, 1),
+                                           # 1024 workgroups of hidden states, expert by expert: rows that end inside a lane's
+                                           # last piece, in one and in eight pieces; whole pieces of another width
+                                           (32, 5, 384, 64, 8, 32, 2), (64, 3, 1152, 64, 4, 32, 2), (64, 2, 3968, 64, 4, 32, 1),
+                                           (64, 2, 1536, 64, 4, 32, 3)])
 def test_decode_small_batch_tiled_ragged_k(L, B, K, N, E, r, k):
     """Row-interleaved packing takes any d_in that is a multiple of 128 (here not of 512) and a ragged last group."""
     print(f"decode tiled B={B}: L={L} K={K} N={N} E={E} r={r} k={k}", flush=True)
