@@ -125,6 +125,12 @@ __device__ __forceinline__ void epi_vec8(const pq_epilogue& e, epi_state& st, in
     for (int j = 0; j < 8; ++j)
       if (fabs((double)w[j] - (double)st.mu) > (double)e.tau) val[j] = 0.0f;
   }
+  if (TWO && INT8 && e.C2) {                         // uniform
+    *reinterpret_cast<uint4*>((uint16_t*)e.C2 + ci) =
+        make_uint4(pack_bf16x2(val[0], val[1]), pack_bf16x2(val[2], val[3]), pack_bf16x2(val[4], val[5]), pack_bf16x2(val[6], val[7]));
+#pragma unroll
+    for (int j = 0; j < 8; ++j) val[j] = __fmul_rn(e.c2_scale, val[j]);
+  }
   if (e.accumulate) {
     float c[8];
     load_io8(e.C, e.out_kind, ci, c);

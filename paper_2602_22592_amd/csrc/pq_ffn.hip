@@ -56,13 +56,14 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   L.Xq = c.take(T * D); L.gx = c.take(T * 4); L.Xt = c.take(T * D * 2);
   L.U = c.take(T * F * 2); L.G = c.take(T * F * 2);
   L.Hq = c.take(T * F); L.gh = c.take(T * 4); L.Ht = c.take(T * F * 2);
-  // (a single branch has no slots of its own: its products read and write the token rows)
+  // (a single branch has no slots of its own: its products read and write the token rows; with INT8 experts its output is kept for d alpha)
   const size_t So = E > 1 ? S : 0;
+  const bool hp8 = d.hp_kind == PQ_HP_LOWRANK_INT8;
   L.idx = c.take(S * 4); L.gate = c.take(S * 4); L.probs = c.take(T * E * 4);
   L.counts = c.take(E * 4); L.offsets = c.take((E + 1) * 4); L.perm = c.take(S * 4); L.inv = c.take(S * 4);
   L.Xp = c.take(So * D * 2); L.ue = c.take(2 * S * r * 2); L.ge = L.ue + S * r * 2; L.a = c.take(S * r * 2);
-  L.Ys = c.take(So * D * 2);
-  if (d.hp_kind == PQ_HP_LOWRANK_INT8) {
+  L.Ys = c.take((hp8 ? S : So) * D * 2);
+  if (hp8) {
     // rows of [Up_e; Gate_e] (one [2 r][D] matrix per expert, as in the bf16 form): codes, gammas, de-quantised copy
     L.UGQ = c.take(E * 2 * r * D); L.gUG = c.take(E * 2 * r * 4); L.UGT = c.take(E * 2 * r * D * 2);
     L.DownQ = c.take(E * D * r); L.gDown = c.take(E * D * 4); L.DownT = c.take(E * D * r * 2);
@@ -73,7 +74,7 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   L.ctx_total = c.off;
   cursor w;
   L.stat = w.take(3 * 2 * sizeof(double) * 1024);
-  L.n_red_a = E > 1 ? pq_rowdot_blocks((int)S) : S > 0 ? pq_plan_gemm((int)S, (int)r, (int)D).red_blocks : 0;   // (one branch: the da product leaves them)
+  L.n_red_a = E > 1 || hp8 ? pq_rowdot_blocks((int)S) : S > 0 ? pq_plan_gemm((int)S, (int)r, (int)D).red_blocks : 0;   // (one bf16 branch: the da product leaves them)
   L.n_red_b = pq_plan_gemm((int)D, (int)F, (int)T, false, false, PQ_PLAN_WGRAD).red_blocks;      // dW_down GEMM
   L.red_a = w.take(sizeof(double) * (size_t)L.n_red_a);
   L.red_b = w.take(sizeof(double) * (size_t)L.n_red_b);
@@ -253,8 +254,8 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
   int* perm = (int*)(cx + L.perm);
   int* inv = (int*)(cx + L.inv);
   // a single branch (the paper's default, N = 1) has nothing to route: the tokens are its slots, Ys is added to Y by the product
-  // itself.  2048 tokens 2048/5076, r = 384 INT8: five launches and two passes over the
-  // slots less, 643 -> 625 us
+  // itself (which leaves the INT8 form's in ctx, see the backward).  2048 tokens 2048/5076, r = 384 INT8: five launches and a pass over the
+  // slots less, 643 -> 635 us
   if (!one) {
     if (int e = pq_launch_router(X, Wr, PQ_BF16, T, D, E, k, idx, gate, (float*)(cx + L.probs), s)) return e;
     if (int e = pq_launch_route(idx, S, E, (int*)(cx + L.counts), offsets, perm, inv, s)) return e;
@@ -290,7 +291,7 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
       pq_operand B{cx + L.DownQ, r, PQ_SRC_KC8, nullptr};
       pq_epilogue e = epi0();
       e.C = one ? Y : cx + L.Ys; e.ldc = D; e.out_kind = PQ_OUT_BF16; e.row_div = (const float*)(cx + L.gA); e.col_div = (const float*)(cx + L.gDown);
-      if (one) { e.accumulate = 1; e.scale = d->alpha; }
+      if (one) { e.accumulate = 1; e.C2 = cx + L.Ys; e.c2_scale = d->alpha; }
       g1.b_stride = (long)D * r; g1.coldiv_stride = D;
       if (int err = pq_launch_gemm(S, D, r, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
     }
@@ -375,9 +376,16 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
   const void* dyp = one ? dY : ws + L.dYp;
   // what the up and gate products multiplied: X, or with INT8 experts its de-quantised codes
   const void* xp = one ? (hp8 ? (const void*)(cx + L.Xt) : X) : (const void*)(cx + L.Xp);
-  // row dots with the experts' outputs (d alpha, the gates' gradients) and dY in slot order
-  if (!one)
+  // Row dots with the experts' outputs (d alpha, the gates' gradients) and dY in slot order.  d alpha = <Ys, dY> is a sum of terms of
+  // either sign.  Of a single bf16 branch it is <a, dY Down>, formed in the da product from the same bf16 factors as Ys and from
+  // unrounded sums.  The factors of an INT8 branch are codes over gammas, which bf16 rounds (one step for every element of equal code
+  // in a row, so the errors add up): there Ys, whose product is exact, is read.  Error over sqrt(sum (Ys dY)^2), 2048 tokens 2048/5076,
+  // r = 384: INT8 3.2e-3 from the factors, 1.1e-3 from Ys.
+  if (!one) {
     if (int e = pq_launch_slot_grad(dY, cx + L.Ys, perm, gate, d->alpha, false, k, S, D, ws + L.dYp, rd, red_a, s)) return e;
+  } else if (hp8) {
+    if (int e = pq_launch_slot_grad(dY, cx + L.Ys, nullptr, nullptr, d->alpha, false, 1, S, D, nullptr, nullptr, red_a, s)) return e;
+  }
   // d alpha and d beta (partials of the dW_down GEMM): both fixed-order sums ride along in the last reduction, with a single
   // branch in the activation's backward
   const pq_reduce_job jobs[2] = {{red_a, S > 0 ? L.n_red_a : 0, 1.0f, nullptr, dalpha_dbeta}, {red_b, L.n_red_b, 1.0f, ml_down + 1, dalpha_dbeta + 1}};
@@ -390,7 +398,7 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
     pq_operand B{Down, r, PQ_SRC_KS16, nullptr};
     pq_epilogue e = epi0();
     e.C = ws + L.da; e.ldc = r; e.out_kind = PQ_OUT_BF16;
-    if (one) { e.dot_comp = a_fwd; e.ld_comp = r; e.comp_kind = PQ_OUT_BF16; e.partials = red_a; }   // d alpha = <a, dY Down>
+    if (one && !hp8) { e.dot_comp = a_fwd; e.ld_comp = r; e.comp_kind = PQ_OUT_BF16; e.partials = red_a; }   // d alpha = <a, dY Down>
     g1.b_stride = (long)D * r;
     if (int err = pq_launch_gemm(S, r, D, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
   }

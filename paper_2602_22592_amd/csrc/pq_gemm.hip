@@ -899,7 +899,7 @@ __global__ __launch_bounds__(WGM * WGN * 64, 2) void mfma_gemm_kernel(int M, int
             *reinterpret_cast<uint4*>(slab + (size_t)m * N + n) = r0;
             *reinterpret_cast<uint4*>(slab + (size_t)m * N + n + 4) = r1;
           } else {
-            epi_vec8<ACC_INT>(epi, st, m, n, r0, r1, rs);
+            epi_vec8<ACC_INT, BKIND == PQ_SRC_KC8>(epi, st, m, n, r0, r1, rs);
           }
         }
       }
@@ -2014,6 +2014,9 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
   if (epi.m_split > 0 && (A.kind != PQ_SRC_KS16 || B.kind != PQ_SRC_KS16 || epi.out_kind != PQ_OUT_F32 || epi.accumulate || epi.maskW || epi.dot_comp ||
                           epi.m_limit || epi.n_limit || M % (2 * epi.m_split) != 0))
     return pq_set_error(PQ_ERR_BAD_ARG, "a second destination goes with plain fp32 weight gradients");
+  if (epi.C2 && epi.m_split == 0 && (A.kind != PQ_SRC_KC8 || B.kind != PQ_SRC_KC8 || epi.out_kind != PQ_OUT_BF16 || !epi.accumulate || epi.split_int8 ||
+                                     epi.m_limit || epi.n_limit))
+    return pq_set_error(PQ_ERR_BAD_ARG, "a copy of the value goes with int8 products that accumulate");
   // plain rank-128 products over many rows: the streaming kernel (callers that want per-block partial sums or the
   // slabs of a split contraction choose it themselves, since it changes how many of those there are)
   if (!grp.mode && ph2.K2 == 0 && !epi.partials && !epi.defer_reduce && pq_skinny_applies(M, N, K, A, B, epi))

@@ -124,8 +124,10 @@ struct pq_epilogue {
   int m_limit, n_limit;
   // optional second destination: of every 2 * m_split rows the first m_split go to C, the others to C2 (both with their rows
   // closed up): the gradients of matrices that are multiplied as one.  fp32, plain stores only.
+  // m_split == 0 (int8 x int8, bf16 outputs that accumulate): C2 [M][ldc] receives the value itself and C then adds c2_scale times it.
   void* C2;
   int m_split;
+  float c2_scale;
 };
 
 // Optional second contraction accumulated into the same output tile (the rank-r branch fused into

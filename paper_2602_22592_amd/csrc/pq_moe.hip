@@ -308,8 +308,9 @@ __global__ __launch_bounds__(256) void expert_act_bwd_kernel(const uint16_t* __r
 }
 
 // One pass over the upstream gradient in slot order: rd[pos] = <dY[t], Ys[pos]> (fp32) with t = perm[pos] / k,
-// partial[block] = sum gate[perm[pos]] * rd[pos] (for d alpha), and, unless dst is NULL, dst[pos] = dY[t], with SCALE times
-// alpha * gate (the upstream gradient of an expert's output).  Gather, dot and scaling in passes of their own read and wrote
+// partial[block] = sum gate[perm[pos]] * rd[pos] (for d alpha), and dst[pos] = dY[t], with SCALE times
+// alpha * gate (the upstream gradient of an expert's output).  perm NULL: a single branch (slot pos is token pos, gate 1), of
+// which the sum alone is wanted: gate, rd and dst are NULL too.  Gather, dot and scaling in passes of their own read and wrote
 // the slot rows three times: routed linear of 1531 tokens 1056 -> 3104, two experts each, 6.9 + 8.2 + 6.8 us.
 template <bool SCALE>
 __global__ __launch_bounds__(256) void slot_grad_kernel(const uint16_t* __restrict__ dY, const uint16_t* __restrict__ Ys,
@@ -320,8 +321,8 @@ __global__ __launch_bounds__(256) void slot_grad_kernel(const uint16_t* __restri
   const int pos = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   double contrib = 0.0;
   if (pos < S) {
-    const int slot = perm[pos];
-    const float gt = gate[slot], sc = alpha * gt;
+    const int slot = perm ? perm[pos] : pos;
+    const float gt = perm ? gate[slot] : 1.0f, sc = alpha * gt;
     const uint4* a4 = reinterpret_cast<const uint4*>(dY + (size_t)(slot / k) * d);
     const uint4* b4 = reinterpret_cast<const uint4*>(Ys + (size_t)pos * d);
     uint4* o4 = reinterpret_cast<uint4*>(dst + (size_t)pos * d);
@@ -355,7 +356,7 @@ __global__ __launch_bounds__(256) void slot_grad_kernel(const uint16_t* __restri
     }
     acc = wave_sum(acc);
     if (lane == 0) {
-      rd[pos] = acc;
+      if (rd) rd[pos] = acc;
       contrib = (double)gt * (double)acc;
     }
   }

@@ -412,7 +412,7 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_
             *reinterpret_cast<uint4*>(slab + (size_t)m * N + n) = r0;
             *reinterpret_cast<uint4*>(slab + (size_t)m * N + n + 4) = r1;
           } else {
-            epi_vec8<INT8 && !PH2, AK == PQ_SRC_KS16>(epi, st, m, n, r0, r1, rs);
+            epi_vec8<INT8 && !PH2, AK == PQ_SRC_KS16 || BK == PQ_SRC_KC8>(epi, st, m, n, r0, r1, rs);
           }
         }
       }
@@ -735,7 +735,7 @@ __global__ __launch_bounds__(256) void tile64_gemm_kernel(int M, int N, int K, p
         *reinterpret_cast<uint4*>(slab + (size_t)m * N + n) = r0;
         *reinterpret_cast<uint4*>(slab + (size_t)m * N + n + 4) = r1;
       } else {
-        epi_vec8<INT8 && !PH2, AK == PQ_SRC_KS16>(epi, st, m, n, r0, r1);
+        epi_vec8<INT8 && !PH2, AK == PQ_SRC_KS16 || BK == PQ_SRC_KC8>(epi, st, m, n, r0, r1);
       }
     }
   }

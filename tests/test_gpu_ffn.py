@@ -153,6 +153,22 @@ def test_ffn_single_branch(T, D, F, r, alpha, kind):
     check_ffn(wl.ffn_case(260 + T + r, T, D, F, 1, r), alpha=alpha, experts=kind)
 
 
+def test_ffn_single_int8_branch_dalpha_reads_exact_products():
+    """d alpha = <Ys, dY> of a single INT8 branch when every de-quantised weight rounds the same way in bf16 (codes 127 of rows with
+    the largest element 0.023: 2.5e-3 each) and no term cancels (dY = Ys): the exact integer product rounded once per output loses
+    about 2^-9 / sqrt(tokens * d) of it, a product of the rounded factors 2.5e-3.  Bar: 2^-12."""
+    c = wl.ffn_case(77, 96, 128, 64, 1, 64)
+    rng = np.random.default_rng(78)
+    c["Down"] = np.where(rng.random(c["Down"].shape) < 0.5, np.float32(0.02294921875), np.float32(0)).astype(np.float32)
+    f = po.ffn_fwd(c["X"], c["W_up"], c["W_gate"], c["W_down"], c["Up"], c["Gate"], c["Down"], c["Wr"], 2.0, 0.2, top_k=1, bf16=True,
+                   experts="int8")
+    c["dY"] = torch.from_numpy(np.ascontiguousarray(f["Yhp"]).astype(np.float32)).to(torch.bfloat16).float().numpy()
+    g = po.ffn_bwd(c["dY"], c["X"], c["Up"], c["Gate"], c["Down"], c["Wr"], 2.0, 0.2, f)
+    err = abs(run_ffn(c, 1, 2.0, 0.2, "int8")["dab"][0] - g["dalpha"]) / abs(g["dalpha"])
+    print(f"  relative error of d alpha {err:.2e}", flush=True)
+    assert err <= 2.0 ** -12
+
+
 def test_ffn_int8_experts_rejects_ranks_that_are_not_whole_words():
     with pytest.raises(pq.PQError):
         pq.FFNBuffers(pq.FFNDesc(64, 64, 64, 8, 2, 1, pq.PQ_BF16, 1.0, 1.0, pq.PQ_HP_LOWRANK_INT8))
