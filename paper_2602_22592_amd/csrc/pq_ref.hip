@@ -264,9 +264,10 @@ __device__ __forceinline__ void ref_direct(const pq_ref_problem& p, int m, int n
   }
 }
 
-// The sums of a SUM form: sum_d 256^d acc_d 2^(E - 54), from the top digit down.  (A lane's NB columns of a row are one load a plane.)
-template <int FORM, int NB>
-__device__ __forceinline__ void ref_planes(const pq_ref_problem& p, int m0, int n0, int li, int lk, f64x4_t (&acc)[NB][NB]) {
+// The sums of a SUM form: sum_d 256^d acc_d 2^(E - 54), from the top digit down.  (A lane's two columns of a row are one load a plane.)
+template <int FORM>
+__device__ __forceinline__ void ref_planes(const pq_ref_problem& p, int m0, int n0, int li, int lk, f64x4_t (&acc)[2][2]) {
+  constexpr int NB = 2;
   const size_t stride = (size_t)p.M * p.N;
   const int n = min(n0 + NB * li, p.N - NB);
   bool marked = false;
@@ -279,13 +280,8 @@ __device__ __forceinline__ void ref_planes(const pq_ref_problem& p, int m0, int 
       int x[PQ_FIXED_DIGITS][NB];
 #pragma unroll
       for (int d = 0; d < PQ_FIXED_DIGITS; ++d) {
-        if constexpr (NB == 4) {
-          const int4 t = *reinterpret_cast<const int4*>(src + d * stride);
-          x[d][0] = t.x; x[d][1] = t.y; x[d][2] = t.z; x[d][3] = t.w;
-        } else if constexpr (NB == 2) {
-          const int2 t = *reinterpret_cast<const int2*>(src + d * stride);
-          x[d][0] = t.x; x[d][1] = t.y;
-        } else x[d][0] = src[d * stride];
+        const int2 t = *reinterpret_cast<const int2*>(src + d * stride);
+        x[d][0] = t.x; x[d][1] = t.y;
       }
       const int e = p.exps[m];
       const double sc = ldexp(1.0, e - 54);
@@ -321,6 +317,7 @@ template <int FORM, int NB, int KS>
 __device__ __forceinline__ void ref_tile(const pq_ref_problem& p, int block, double* lds, double* red) {
   constexpr int WT = 16 * NB, DEPTH = NB == 4 ? 2 : NB == 2 ? 3 : 4;
   constexpr bool SUM = FORM == PQ_REF_SUM_CBITS || FORM == PQ_REF_SUM_SS8;
+  static_assert(!SUM || (NB == 2 && KS == 1), "the SUM forms take 32x32 wavefront tiles");
   constexpr int AK = (FORM == PQ_REF_SS8 || FORM == PQ_REF_SS) ? PQ_SRC_KS32 : PQ_SRC_KC32;
   constexpr int BK = FORM == PQ_REF_CC ? PQ_SRC_KC32 : FORM == PQ_REF_CBITS ? PQ_SRC_BITSF : FORM == PQ_REF_SS8 ? PQ_SRC_KS8 : PQ_SRC_KS32;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 15, lk = lane >> 4;
@@ -335,8 +332,8 @@ __device__ __forceinline__ void ref_tile(const pq_ref_problem& p, int block, dou
   const int first = KS == 1 ? 0 : wave;
   const bool live = KS == 4 || (m0 < p.M && n0 < p.N);    // uniform for the wavefront
   if (live) {
-    if constexpr (!SUM) ref_contract<AK, BK, NB, DEPTH>(p.A, p.B, m0, p.M, n0, p.N, p.K, first, KS, li, lk, acc);
-    else if (KS == 1 || wave == 0) ref_planes<FORM, NB>(p, m0, n0, li, lk, acc);
+    if constexpr (SUM) ref_planes<FORM>(p, m0, n0, li, lk, acc);
+    else ref_contract<AK, BK, NB, DEPTH>(p.A, p.B, m0, p.M, n0, p.N, p.K, first, KS, li, lk, acc);
     if constexpr (FORM == PQ_REF_CBITS || FORM == PQ_REF_SUM_CBITS) {
       // the rank-r product rides in the same accumulators; the 1-bit sum carries its scale from here on
       const double sc1 = (double)(p.dev_scale1 ? __fmul_rn(p.scale1, *p.dev_scale1) : p.scale1);
@@ -463,15 +460,17 @@ __global__ __launch_bounds__(256, 2) void ref_gemm_kernel(ref_launch L) {
     case PQ_REF_CS: ref_tile<PQ_REF_CS, NB, KS>(p, blk, LDS, red); break;              \
     case PQ_REF_CBITS: ref_tile<PQ_REF_CBITS, NB, KS>(p, blk, LDS, red); break;          \
     case PQ_REF_SS8: ref_tile<PQ_REF_SS8, NB, KS>(p, blk, LDS, red); break;        \
-    case PQ_REF_SUM_CBITS: ref_tile<PQ_REF_SUM_CBITS, NB, KS>(p, blk, LDS, red); break;   \
-    case PQ_REF_SUM_SS8: ref_tile<PQ_REF_SUM_SS8, NB, KS>(p, blk, LDS, red); break;       \
     default: ref_tile<PQ_REF_SS, NB, KS>(p, blk, LDS, red);                            \
   }
   if constexpr (BIG) {
     PQ_REF_FORMS(4, 1, nullptr)
   } else {
     __shared__ double lds[3 * 16 * 64];
-    if (p.cfg == 1) { PQ_REF_FORMS(2, 1, nullptr) }
+    if (p.cfg == 1) {
+      if (p.form == PQ_REF_SUM_CBITS) ref_tile<PQ_REF_SUM_CBITS, 2, 1>(p, blk, nullptr, red);   // (the SUM forms: always this one)
+      else if (p.form == PQ_REF_SUM_SS8) ref_tile<PQ_REF_SUM_SS8, 2, 1>(p, blk, nullptr, red);
+      else { PQ_REF_FORMS(2, 1, nullptr) }
+    }
     else if (p.cfg == 2) { PQ_REF_FORMS(2, 4, lds) }
     else { PQ_REF_FORMS(1, 4, lds) }
   }
