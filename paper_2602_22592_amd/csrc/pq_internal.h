@@ -232,7 +232,7 @@ enum pq_ref_form {
   PQ_REF_SS8 = 3,     // A KS32, B KS8 divided by its kdiv
   PQ_REF_SS = 4,      // A KS32, B KS32
   // the same with the first contraction already done in fixed point (pq_fixed.hip): its sums are read from `planes` and A, B are
-  // looked at only for rows that are not finite
+  // looked at only for tiles with rows that are not finite
   PQ_REF_SUM_CBITS = 5,
   PQ_REF_SUM_SS8 = 6
 };

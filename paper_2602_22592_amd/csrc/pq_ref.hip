@@ -242,35 +242,13 @@ __device__ __forceinline__ void ref_contract(const pq_operand& A, const pq_opera
   }
 }
 
-// NB columns of one row of a SUM form's first contraction the long way, for rows with infinities or NaN.
-template <int FORM, int NB>
-__device__ __forceinline__ void ref_direct(const pq_ref_problem& p, int m, int n, double (&s)[NB]) {
-#pragma unroll
-  for (int j = 0; j < NB; ++j) s[j] = 0.0;
-#pragma unroll 1
-  for (int k = 0; k < p.K; ++k) {
-    if constexpr (FORM == PQ_REF_SUM_CBITS) {
-      const double a = (double)((const float*)p.A.p)[(size_t)m * p.A.ld + k];
-#pragma unroll
-      for (int j = 0; j < NB; ++j) s[j] += ((((const uint8_t*)p.B.p)[(size_t)(n + j) * p.B.ld + (k >> 3)] >> (k & 7)) & 1) ? a : -a;
-    } else {
-      const double d = (double)p.B.kdiv[k], a = (double)((const float*)p.A.p)[(size_t)k * p.A.ld + m];
-      double r = __builtin_amdgcn_rcp(d);
-      r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
-      r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
-#pragma unroll
-      for (int j = 0; j < NB; ++j) s[j] = __builtin_fma(a, (double)((const int8_t*)p.B.p)[(size_t)k * p.B.ld + n + j] * r, s[j]);
-    }
-  }
-}
-
-// The sums of a SUM form: sum_d 256^d acc_d 2^(E - 54), from the top digit down.  (A lane's two columns of a row are one load a plane.)
-template <int FORM>
-__device__ __forceinline__ void ref_planes(const pq_ref_problem& p, int m0, int n0, int li, int lk, f64x4_t (&acc)[2][2]) {
+// The sums of a SUM form: sum_d 256^d acc_d 2^(E - 54), from the top digit down (a lane's two columns of a row are one load a plane).
+// False for the whole wavefront when one of its rows has no digits: the tile is then to be formed as the fp64 product it stands for.
+__device__ __forceinline__ bool ref_planes(const pq_ref_problem& p, int m0, int n0, int li, int lk, f64x4_t (&acc)[2][2]) {
   constexpr int NB = 2;
   const size_t stride = (size_t)p.M * p.N;
   const int n = min(n0 + NB * li, p.N - NB);
-  bool marked = false;
+  if (__any(p.exps[min(m0 + ((int)threadIdx.x & 31), p.M - 1)] == PQ_FIXED_NOT_FINITE)) return false;
 #pragma unroll
   for (int i = 0; i < NB; ++i)
 #pragma unroll
@@ -283,8 +261,7 @@ __device__ __forceinline__ void ref_planes(const pq_ref_problem& p, int m0, int 
         const int2 t = *reinterpret_cast<const int2*>(src + d * stride);
         x[d][0] = t.x; x[d][1] = t.y;
       }
-      const int e = p.exps[m];
-      const double sc = ldexp(1.0, e - 54);
+      const double sc = ldexp(1.0, p.exps[m] - 54);
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
         double s = 0.0;
@@ -292,49 +269,42 @@ __device__ __forceinline__ void ref_planes(const pq_ref_problem& p, int m0, int 
         for (int d = PQ_FIXED_DIGITS - 1; d >= 0; --d) s = __builtin_fma(s, 256.0, (double)x[d][j]);
         acc[i][j][v] = s * sc;
       }
-      marked |= e == PQ_FIXED_NOT_FINITE;
     }
-  if (__any(marked)) {
-#pragma unroll 1
-    for (int q = 0; q < 4 * NB; ++q) {
-      const int m = min(m0 + NB * (lk + 4 * (q & 3)) + (q >> 2), p.M - 1);
-      if (p.exps[m] != PQ_FIXED_NOT_FINITE) continue;
-      double s[NB];
-      ref_direct<FORM, NB>(p, m, n, s);
-#pragma unroll
-      for (int i = 0; i < NB; ++i)                   // (static indices: the accumulators stay in registers)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-#pragma unroll
-          for (int j = 0; j < NB; ++j) acc[i][j][v] = q == 4 * i + v ? s[j] : acc[i][j][v];
-    }
-  }
+  return true;
 }
 
 // One workgroup's tile of one product.  KS = 1: the four wavefronts own a 2 x 2 arrangement of tiles; KS = 4: they share one
 // tile, wavefront w taking every fourth step, and wavefront 0 adds their sums in order.
 template <int FORM, int NB, int KS>
 __device__ __forceinline__ void ref_tile(const pq_ref_problem& p, int block, double* lds, double* red) {
-  constexpr int WT = 16 * NB, DEPTH = NB == 4 ? 2 : NB == 2 ? 3 : 4;
   constexpr bool SUM = FORM == PQ_REF_SUM_CBITS || FORM == PQ_REF_SUM_SS8;
+  constexpr int WT = 16 * NB, DEPTH = NB == 4 ? 2 : NB == 2 ? 3 : 4;
   static_assert(!SUM || (NB == 2 && KS == 1), "the SUM forms take 32x32 wavefront tiles");
-  constexpr int AK = (FORM == PQ_REF_SS8 || FORM == PQ_REF_SS) ? PQ_SRC_KS32 : PQ_SRC_KC32;
-  constexpr int BK = FORM == PQ_REF_CC ? PQ_SRC_KC32 : FORM == PQ_REF_CBITS ? PQ_SRC_BITSF : FORM == PQ_REF_SS8 ? PQ_SRC_KS8 : PQ_SRC_KS32;
+  constexpr bool BITS = FORM == PQ_REF_CBITS || FORM == PQ_REF_SUM_CBITS, CODES = FORM == PQ_REF_SS8 || FORM == PQ_REF_SUM_SS8;
+  constexpr int AK = (CODES || FORM == PQ_REF_SS) ? PQ_SRC_KS32 : PQ_SRC_KC32;
+  constexpr int BK = FORM == PQ_REF_CC ? PQ_SRC_KC32 : BITS ? PQ_SRC_BITSF : CODES ? PQ_SRC_KS8 : PQ_SRC_KS32;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 15, lk = lane >> 4;
   const int nbn = (p.N + WT * (KS == 1 ? 2 : 1) - 1) / (WT * (KS == 1 ? 2 : 1));
   const int bm = block / nbn, bn = block % nbn;
   const int m0 = KS == 1 ? (2 * bm + (wave >> 1)) * WT : bm * WT, n0 = KS == 1 ? (2 * bn + (wave & 1)) * WT : bn * WT;
   f64x4_t acc[NB][NB];
+  auto clear = [&] {
 #pragma unroll
-  for (int i = 0; i < NB; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+      for (int j = 0; j < NB; ++j) acc[i][j] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  };
+  if constexpr (!SUM) clear();
   const int first = KS == 1 ? 0 : wave;
   const bool live = KS == 4 || (m0 < p.M && n0 < p.N);    // uniform for the wavefront
   if (live) {
-    if constexpr (SUM) ref_planes<FORM>(p, m0, n0, li, lk, acc);
-    else ref_contract<AK, BK, NB, DEPTH>(p.A, p.B, m0, p.M, n0, p.N, p.K, first, KS, li, lk, acc);
-    if constexpr (FORM == PQ_REF_CBITS || FORM == PQ_REF_SUM_CBITS) {
+    bool contract = true;                                 // uniform
+    if constexpr (SUM) {
+      contract = !ref_planes(p, m0, n0, li, lk, acc);
+      if (contract) clear();
+    }
+    if (contract) ref_contract<AK, BK, NB, DEPTH>(p.A, p.B, m0, p.M, n0, p.N, p.K, first, KS, li, lk, acc);
+    if constexpr (BITS) {
       // the rank-r product rides in the same accumulators; the 1-bit sum carries its scale from here on
       const double sc1 = (double)(p.dev_scale1 ? __fmul_rn(p.scale1, *p.dev_scale1) : p.scale1);
 #pragma unroll
