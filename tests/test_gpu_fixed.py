@@ -20,6 +20,14 @@ def test_shapes_take_the_form(T, K, N, r, tau):
     assert len(kernels(res, "fixed_rows_kernel")) == 1 and len(kernels(res, "fixed_cols_kernel")) == 1
 
 
+@pytest.mark.parametrize("T", [2048, 65536])
+def test_column_maxima_are_reduced_once(T):
+    """... in a launch of ceil(d_out / 64) workgroups whatever the tokens, not by every workgroup of the column pass."""
+    res = trace([dict(op="linear", tokens=T, d_in=1024, d_out=1056, io_dtype=0)])[0]
+    assert res["rc"] == 0, res["error"]
+    assert [grid[0] for _, grid in kernels(res, "fixed_exps_kernel")] == [17]
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("T,K,N,r,tau", SHAPES)
 def test_against_the_oracle(T, K, N, r, tau):
