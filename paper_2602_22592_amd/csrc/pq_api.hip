@@ -128,11 +128,15 @@ struct cursor {
 };
 
 inline int fixed_Tp(int T) { return (T + 15) / 16 * 16; }
-// The two large contractions of the fp32 backward in fixed point: four more launches (about 40 us) and passes over dY and the
-// sums, a fifth of the time of the products.  44 shapes of 64 to 2048 tokens: 0.55-0.9 x up to tokens * d_in * d_out = 0.54e9,
-// 0.96-1.11 x at 1.07e9, 1.2-1.4 x from 1.9e9 on, 1.75 x at 8.6e9 (2048 tokens 2048x2048 r=128: 716 -> 410 us).  The int32 sums of dW hold
-// tokens * 2^14, those of dX d_out * 2^7.
-bool fixed_applies(int T, int K, int N) { return T >= 64 && T <= 65536 && N <= 65536 && (double)T * K * N >= 1.2e9; }
+// The two large contractions of the fp32 backward in fixed point: seven int8 products of one in fp64, a tenth of its time, but five
+// more launches (some 20 us) and 56 bytes of planes per output and 22 of digits per element of dY, written and read, i.e. 56 (1 / d_out +
+// 1 / tokens) + 22 / d_in bytes per product.  Backward against the fp64 products, 49 shapes of 64 to 65536 tokens and widths of 128 to 16384:
+// with 1 / tokens + 1 / d_out + 0.4 / d_in up to 1 / 320 1.17 x (512 tokens 1024->4096, 65536 512->512 1.19) to 2.77 x (2048 tokens
+// 4096->4096), beyond it 1.14 x (16384 256->512) down to 0.39 x (64 tokens 8192->8192); below tokens * d_in * d_out = 1.2e9 0.55 to 1.1 x.
+// The int32 sums of dW hold tokens * 2^14, those of dX d_out * 2^7.
+bool fixed_applies(int T, int K, int N) {
+  return T <= 65536 && N <= 65536 && (double)T * K * N >= 1.2e9 && 1.0 / T + 1.0 / N + 0.4 / K <= 1.0 / 320;
+}
 
 lin_layout make_layout(const pq_linear_desc& d) {
   lin_layout L;

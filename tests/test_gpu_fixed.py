@@ -10,7 +10,8 @@ from paper_2602_22592_amd import binding as pq
 from paper_2602_22592_amd import workloads as wl
 from test_gpu_ref import test_fp32_products_at_tile_edges as check_fp32
 
-SHAPES = [(1037, 1056, 1120, 40, None), (517, 1568, 1504, 0, 0.02), (2049, 544, 1312, 8, None), (64, 4640, 4096, 16, None)]
+SHAPES = [(1037, 1056, 1120, 40, None), (517, 1568, 1504, 0, 0.02), (2049, 544, 1312, 8, None), (409, 2080, 2080, 16, None),
+          (2050, 288, 2400, 16, None)]
 
 
 @pytest.mark.parametrize("T,K,N,r,tau", SHAPES)
@@ -18,6 +19,14 @@ def test_shapes_take_the_form(T, K, N, r, tau):
     res = trace([dict(op="linear", tokens=T, d_in=K, d_out=N, hp_rank=r, io_dtype=0)])[0]
     assert res["rc"] == 0, res["error"]
     assert len(kernels(res, "fixed_rows_kernel")) == 1 and len(kernels(res, "fixed_cols_kernel")) == 1
+
+
+# few tokens or narrow layers: the planes' traffic outweighs the products (fp64 backward 157 / 368 / 173 / 170 / 816 us, digits 307 / 943 / 287 / 216 / 820)
+@pytest.mark.parametrize("T,K,N", [(64, 4640, 4096), (64, 8192, 8192), (2048, 8192, 128), (2048, 128, 8192), (65536, 512, 256)])
+def test_shapes_that_digits_would_slow_down_do_not(T, K, N):
+    res = trace([dict(op="linear", tokens=T, d_in=K, d_out=N, io_dtype=0)])[0]
+    assert res["rc"] == 0, res["error"]
+    assert not kernels(res, "fixed_rows_kernel")
 
 
 @pytest.mark.parametrize("T", [2048, 65536])
