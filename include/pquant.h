@@ -137,7 +137,11 @@ int pq_onebit_acc(const int8_t* Xq, const uint32_t* packed, int32_t T, int32_t K
 /* Sizes of the caller-owned buffers of pq_linear_fwd / pq_linear_bwd for a descriptor.
  * ctx holds what forward saves for backward (packed bits in both orientations, mu/lambda, the
  * quantised activations and gamma, the hp hidden state, routing decisions); workspace is scratch
- * whose contents need not survive between calls.  Both sizes cover forward and backward. */
+ * whose contents need not survive between calls.  Both sizes cover forward and backward.
+ * fp32 I/O, latent weights: the workspace of a large call ends with the digits that its backward forms the products of
+ * dX and dW from (up to 2 GiB; 14 tokens * d_out + 28 d_in * max(tokens, d_out) bytes).  A workspace without them, i.e. of the size
+ * that the same descriptor with PQ_W_PACKED asks for, is accepted by both calls; the backward then runs fp64 products
+ * (about twice its time). */
 size_t pq_linear_ctx_bytes(const pq_linear_desc* desc);
 size_t pq_linear_workspace_bytes(const pq_linear_desc* desc);
 
@@ -180,7 +184,8 @@ int pq_linear_bwd(const pq_linear_desc* desc, const void* dY, const void* X, con
  *   X [T][K], gain [K] io_dtype; eps >= 0; W latent weights (PQ_W_MASTER); the other arguments as in pq_linear_fwd.
  *   Backward: dX [T][K] io_dtype is the gradient with respect to X; dgain [K] fp32.
  *   ctx / workspace: pq_linear_norm_ctx_bytes() / pq_linear_norm_workspace_bytes() bytes (ctx is required).
- *   d_in <= 8192 (bf16) / 4096 (fp32) for the forward, 4096 / 2048 for the backward. */
+ *   d_in <= 8192 (bf16) / 4096 (fp32) for the forward, 4096 / 2048 for the backward.
+ *   (fp32: a workspace without the digits is accepted here too; for the norm's size query PQ_W_PACKED leaves them out likewise.) */
 size_t pq_linear_norm_ctx_bytes(const pq_linear_desc* desc);
 size_t pq_linear_norm_workspace_bytes(const pq_linear_desc* desc);
 int pq_linear_norm_fwd(const pq_linear_desc* desc, const void* X, const void* gain, float eps, const void* W,

@@ -110,11 +110,11 @@ struct lin_layout {
   // INT8 form of the dense branch: the ctx of pq_hp_int8_* behind the linear's own
   size_t hp8, hp8_bytes;
   // workspace (scratch)
-  size_t stat_partials, red_a, red_b, dH, w_Xq, w_gamma, w_H, splitk, splitk2, splitk_bytes, splitk2_bytes, ws_total;
+  size_t stat_partials, red_a, red_b, dH, w_Xq, w_gamma, w_H, splitk, splitk2, splitk_bytes, splitk2_bytes, ws_base, ws_total;
   size_t dYp, rd, dHs, dXs, dlogit, dwr, hp8_ws, hp8_ws_bytes;
-  // fp32 I/O in fixed point (pq_fixed.hip)
-  bool fixed;
-  size_t fx_drow, fx_rexp, fx_dcol, fx_cexp, fx_qT, fx_colmax, fx_planes;
+  // fp32 I/O in fixed point (pq_fixed.hip): a region of fx_bytes (0: the call has none) behind everything else, which only a backward
+  // uses, and only if the workspace holds it
+  size_t fx_drow, fx_rexp, fx_dcol, fx_cexp, fx_qT, fx_colmax, fx_red_b, fx_planes, fx_bytes;
   int n_red_a, n_red_b;
 };
 
@@ -133,7 +133,10 @@ inline int fixed_Tp(int T) { return (T + 15) / 16 * 16; }
 // 1 / tokens) + 22 / d_in bytes per product.  Backward against the fp64 products, 49 shapes of 64 to 65536 tokens and widths of 128 to 16384:
 // with 1 / tokens + 1 / d_out + 0.4 / d_in up to 1 / 320 1.17 x (512 tokens 1024->4096, 65536 512->512 1.19) to 2.77 x (2048 tokens
 // 4096->4096), beyond it 1.14 x (16384 256->512) down to 0.39 x (64 tokens 8192->8192); below tokens * d_in * d_out = 1.2e9 0.55 to 1.1 x.
-// The int32 sums of dW hold tokens * 2^14, those of dX d_out * 2^7.
+// The int32 sums of dW hold tokens * 2^14, those of dX d_out * 2^7.  Calls whose digits and planes would take more than FIXED_MAX_BYTES
+// (14 tokens * d_out + 28 d_in * max(tokens, d_out) bytes: 176 MiB at 2048 tokens 2048x2048, 1.9 GiB at 4096 tokens 4096x11008) keep
+// the fp64 products.
+constexpr size_t FIXED_MAX_BYTES = (size_t)2 << 30;
 bool fixed_applies(int T, int K, int N) {
   return T <= 65536 && N <= 65536 && (double)T * K * N >= 1.2e9 && 1.0 / T + 1.0 / N + 0.4 / K <= 1.0 / 320;
 }
@@ -168,10 +171,9 @@ lin_layout make_layout(const pq_linear_desc& d) {
   cursor w;
   L.stat_partials = w.take(2 * sizeof(double) * 1024);
   const int Ti = d.tokens, Ki = d.d_in, Ni = d.d_out, ri = (int)r;
-  L.fixed = !bf16 && fixed_applies(Ti, Ki, Ni);
   L.n_red_a = r ? (bf16 ? pq_plan_gemm(Ti, ri, Ni).red_blocks : pq_ref_red_blocks(Ti, ri, Ni)) : 0;   // dH GEMM
   if (r && pq_skinny_blocks(Ti) > L.n_red_a) L.n_red_a = pq_skinny_blocks(Ti);   // room for the streaming rank-r kernel's partials
-  L.n_red_b = bf16 ? pq_plan_gemm(Ni, Ki, Ti, false, false, PQ_PLAN_WGRAD).red_blocks : pq_ref_red_blocks(Ni, Ki, L.fixed ? -1 : Ti);              // dW GEMM
+  L.n_red_b = bf16 ? pq_plan_gemm(Ni, Ki, Ti, false, false, PQ_PLAN_WGRAD).red_blocks : pq_ref_red_blocks(Ni, Ki, Ti);              // dW GEMM
   size_t sk = 0;
   const int shapes[7][3] = {{Ti, ri, Ki}, {Ti, Ni, ri}, {Ti, ri, Ni}, {Ti, Ki, ri}, {Ni, Ki, Ti}, {Ni, ri, Ti}, {ri, Ki, Ti}};
   for (const auto& sh : shapes) {
@@ -200,13 +202,6 @@ lin_layout make_layout(const pq_linear_desc& d) {
   L.w_Xq = w.take(T * K);          // used when forward runs without a ctx (inference)
   L.w_gamma = w.take(T * sizeof(float));
   L.w_H = w.take(T * r * es);
-  if (L.fixed) {
-    const size_t Tp = fixed_Tp(Ti), pl = PQ_FIXED_DIGITS * K * (T > N ? T : N) * sizeof(int);   // (dW's planes, then dX's)
-    L.fx_drow = w.take(PQ_FIXED_DIGITS * T * N); L.fx_rexp = w.take(T * sizeof(int));
-    L.fx_dcol = w.take(PQ_FIXED_DIGITS * N * Tp); L.fx_cexp = w.take(N * sizeof(int));
-    L.fx_qT = w.take(K * Tp); L.fx_colmax = w.take(pq_fixed_max_rows(Ti) * N * sizeof(uint32_t));
-    L.fx_planes = w.take(pl);
-  }
   L.splitk = w.take(sk);
   L.splitk_bytes = sk;
   // slabs of dA, which shares a launch with dB (whose slabs are in the region above)
@@ -222,7 +217,20 @@ lin_layout make_layout(const pq_linear_desc& d) {
     L.hp8_ws_bytes = pq_hp_int8_workspace_bytes(d.tokens, d.d_in, d.d_out, d.hp_rank);
     L.hp8_ws = w.take(L.hp8_ws_bytes);
   }
-  L.ws_total = w.off;
+  L.ws_base = L.ws_total = w.off;
+  if (!bf16 && d.w_kind == PQ_W_MASTER && Ni % 32 == 0 && fixed_applies(Ti, Ki, Ni)) {   // (what a backward takes)
+    const size_t Tp = fixed_Tp(Ti), pl = PQ_FIXED_DIGITS * K * (T > N ? T : N) * sizeof(int);   // (dW's planes, then dX's)
+    cursor x;
+    L.fx_drow = x.take(PQ_FIXED_DIGITS * T * N); L.fx_rexp = x.take(T * sizeof(int));
+    L.fx_dcol = x.take(PQ_FIXED_DIGITS * N * Tp); L.fx_cexp = x.take(N * sizeof(int));
+    L.fx_qT = x.take(K * Tp); L.fx_colmax = x.take(pq_fixed_max_rows(Ti) * N * sizeof(uint32_t));
+    L.fx_red_b = x.take(sizeof(double) * (size_t)pq_ref_red_blocks(Ni, Ki, -1));
+    L.fx_planes = x.take(pl);
+    if (x.off <= FIXED_MAX_BYTES) {
+      L.fx_bytes = x.off;
+      L.ws_total += x.off;
+    }
+  }
   return L;
 }
 
@@ -448,7 +456,7 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
   PQ_REQUIRE(d->w_kind == PQ_W_PACKED || ctx, PQ_ERR_BAD_ARG, "latent weights need a ctx to hold the packed bits");
   PQ_REQUIRE(aligned16(X) && aligned16(W_or_packed) && aligned16(Y) && aligned16(workspace) && aligned16(ctx) &&
                  aligned16(hpA) && aligned16(hpB), PQ_ERR_SHAPE, "buffers must be 16-byte aligned");
-  PQ_REQUIRE(workspace_bytes >= L.ws_total, PQ_ERR_WORKSPACE, "workspace too small: %zu < %zu", workspace_bytes, L.ws_total);
+  PQ_REQUIRE(workspace_bytes >= L.ws_base, PQ_ERR_WORKSPACE, "workspace too small: %zu < %zu", workspace_bytes, L.ws_base);
   PQ_REQUIRE(!ctx || ctx_bytes >= L.ctx_total, PQ_ERR_WORKSPACE, "ctx too small: %zu < %zu", ctx_bytes, L.ctx_total);
   hipStream_t s = (hipStream_t)stream;
   char* cx = (char*)ctx;
@@ -639,26 +647,27 @@ static int hp_int8_factor_grads(const void* dY, const void* Xt, int T, int K, in
 // (pq_fixed.hip), whose sums the launches below finish.  What depends on nothing (dW, dH, dB) is one launch, what needs dH
 // (dX with dH A in the same sums, dA) and the two scalar reductions a second one: six products and a reduction in a row
 // left most of the chip idle at every size, and at 64 tokens their starts were most of the time.
+// fx: the region of the digits and planes, or NULL for the fp64 products alone.
 static int linear_bwd_f32(const pq_linear_desc* d, const lin_layout& L, const void* dY, const void* X, const void* W, const void* hpA,
-                          const void* hpB, const char* cx, void* dX, float* dW, float* dhpA, float* dhpB, float* dalpha_dbeta, char* ws,
+                          const void* hpB, const char* cx, void* dX, float* dW, float* dhpA, float* dhpB, float* dalpha_dbeta, char* ws, char* fx,
                           hipStream_t s) {
   const int T = d->tokens, K = d->d_in, N = d->d_out, r = d->hp_rank;
   const float* mulam = (const float*)(cx + L.mulam);
   double* red_a = (double*)(ws + L.red_a);
-  double* red_b = (double*)(ws + L.red_b);
+  double* red_b = (double*)(fx ? fx + L.fx_red_b : ws + L.red_b);
   const void* H = cx + L.H;
   void* dH = ws + L.dH;
   pq_ref_problem p[PQ_REF_MAX];
   int n = 0;
-  int* planes = (int*)(ws + L.fx_planes);
+  int* planes = fx ? (int*)(fx + L.fx_planes) : nullptr;
   const int Tp = fixed_Tp(T);
-  if (L.fixed) {                     // (dY / gamma)^T q: the digits of dY's columns, one behind the other, times q
-    if (int err = pq_launch_fixed_split((const float*)dY, (const float*)(cx + L.gamma), (const int8_t*)(cx + L.Xq), T, Tp, N, K, (int8_t*)(ws + L.fx_drow),
-                                        (int*)(ws + L.fx_rexp), (int8_t*)(ws + L.fx_dcol), (int*)(ws + L.fx_cexp), (int8_t*)(ws + L.fx_qT),
-                                        (uint32_t*)(ws + L.fx_colmax), s)) return err;
+  if (fx) {                          // (dY / gamma)^T q: the digits of dY's columns, one behind the other, times q
+    if (int err = pq_launch_fixed_split((const float*)dY, (const float*)(cx + L.gamma), (const int8_t*)(cx + L.Xq), T, Tp, N, K, (int8_t*)(fx + L.fx_drow),
+                                        (int*)(fx + L.fx_rexp), (int8_t*)(fx + L.fx_dcol), (int*)(fx + L.fx_cexp), (int8_t*)(fx + L.fx_qT),
+                                        (uint32_t*)(fx + L.fx_colmax), s)) return err;
     pq_epilogue e = epi_zero();
     e.C = planes; e.ldc = K; e.out_kind = PQ_OUT_I32;
-    if (int err = pq_launch_gemm(PQ_FIXED_DIGITS * N, K, Tp, {ws + L.fx_dcol, Tp, PQ_SRC_KC8, nullptr}, {ws + L.fx_qT, Tp, PQ_SRC_KC8, nullptr}, e, s,
+    if (int err = pq_launch_gemm(PQ_FIXED_DIGITS * N, K, Tp, {fx + L.fx_dcol, Tp, PQ_SRC_KC8, nullptr}, {fx + L.fx_qT, Tp, PQ_SRC_KC8, nullptr}, e, s,
                                  PQP_GEMM_DW)) return err;
   }
   auto add_dW = [&] {  // dW = beta * dY^T (q / gamma)  [masked];  d beta = lambda * sum S .* (dY^T (q / gamma))
@@ -666,12 +675,12 @@ static int linear_bwd_f32(const pq_linear_desc* d, const lin_layout& L, const vo
     e.C = dW; e.ldc = K; e.scale = d->beta;
     e.sign_bytes = (const uint8_t*)(cx + L.P); e.ld_sign = K / 8; e.partials = red_b;
     if (d->ste_mode == PQ_STE_CLIP) { e.maskW = W; e.mu_dev = mulam; e.tau = d->ste_tau; }
-    p[n] = ref_problem(L.fixed ? PQ_REF_SUM_SS8 : PQ_REF_SS8, N, K, T, {dY, N, PQ_SRC_KS32, nullptr},
+    p[n] = ref_problem(fx ? PQ_REF_SUM_SS8 : PQ_REF_SS8, N, K, T, {dY, N, PQ_SRC_KS32, nullptr},
                        {cx + L.Xq, K, PQ_SRC_KS8, (const float*)(cx + L.gamma)}, e);
-    p[n].planes = planes; p[n].exps = (const int*)(ws + L.fx_cexp);
+    p[n].planes = planes; p[n].exps = fx ? (const int*)(fx + L.fx_cexp) : nullptr;
     ++n;
   };
-  if (!L.fixed) add_dW();            // (the longest first: products before sums of planes)
+  if (!fx) add_dW();                 // (the longest first: products before sums of planes)
   if (r > 0) {
     pq_epilogue e = epi_zero();      // dB = alpha * dY^T H
     e.C = dhpB; e.ldc = r; e.scale = d->alpha;
@@ -680,40 +689,41 @@ static int linear_bwd_f32(const pq_linear_desc* d, const lin_layout& L, const vo
     e.C = dH; e.ldc = r; e.scale = d->alpha; e.dot_comp = H; e.ld_comp = r; e.partials = red_a;
     p[n++] = ref_problem(PQ_REF_CS, T, r, N, {dY, N, PQ_SRC_KC32, nullptr}, {hpB, r, PQ_SRC_KS32, nullptr}, e);
   }
-  if (L.fixed) add_dW();
+  if (fx) add_dW();
   if (int err = pq_launch_ref(p, n, nullptr, 0, s, PQP_GEMM_DW)) return err;
-  if (L.fixed) {                     // dY S: the digits of dY's rows, one behind the other, times the signs
+  if (fx) {                          // dY S: the digits of dY's rows, one behind the other, times the signs
     pq_epilogue e = epi_zero();
     e.C = planes; e.ldc = K; e.out_kind = PQ_OUT_I32;
-    if (int err = pq_launch_gemm(PQ_FIXED_DIGITS * T, K, N, {ws + L.fx_drow, N, PQ_SRC_KC8, nullptr}, {cx + L.Pt, N / 8, PQ_SRC_BITS8, nullptr}, e, s,
+    if (int err = pq_launch_gemm(PQ_FIXED_DIGITS * T, K, N, {fx + L.fx_drow, N, PQ_SRC_KC8, nullptr}, {cx + L.Pt, N / 8, PQ_SRC_BITS8, nullptr}, e, s,
                                  PQP_GEMM_DX)) return err;
   }
   const pq_reduce_job jobs[2] = {{red_a, (T > 0 && r > 0) ? pq_ref_red_blocks(T, r, N) : 0, 1.0f, nullptr, dalpha_dbeta},
-                                 {red_b, L.n_red_b, 1.0f, mulam + 1, dalpha_dbeta + 1}};
+                                 {red_b, fx ? pq_ref_red_blocks(N, K, -1) : L.n_red_b, 1.0f, mulam + 1, dalpha_dbeta + 1}};
   n = 0;
   auto add_dX = [&] {                // dX = beta * lambda * dY S + dH A
     pq_epilogue e = epi_zero();
     e.C = dX; e.ldc = K;
-    p[n] = ref_problem(L.fixed ? PQ_REF_SUM_CBITS : PQ_REF_CBITS, T, K, N, {dY, N, PQ_SRC_KC32, nullptr}, {cx + L.Pt, N / 8, PQ_SRC_BITSF, nullptr}, e);
-    p[n].planes = planes; p[n].exps = (const int*)(ws + L.fx_rexp);
+    p[n] = ref_problem(fx ? PQ_REF_SUM_CBITS : PQ_REF_CBITS, T, K, N, {dY, N, PQ_SRC_KC32, nullptr}, {cx + L.Pt, N / 8, PQ_SRC_BITSF, nullptr}, e);
+    p[n].planes = planes; p[n].exps = fx ? (const int*)(fx + L.fx_rexp) : nullptr;
     p[n].scale1 = d->beta; p[n].dev_scale1 = mulam + 1;
     if (r > 0) { p[n].K2 = r; p[n].A2 = pq_operand{dH, r, PQ_SRC_KC32, nullptr}; p[n].B2 = pq_operand{hpA, K, PQ_SRC_KS32, nullptr}; }
     ++n;
   };
-  if (!L.fixed) add_dX();
+  if (!fx) add_dX();
   if (r > 0) {                       // dA = dH^T X   (dH already carries alpha)
     pq_epilogue e = epi_zero();
     e.C = dhpA; e.ldc = K;
     p[n++] = ref_problem(PQ_REF_SS, r, K, T, {dH, r, PQ_SRC_KS32, nullptr}, {X, K, PQ_SRC_KS32, nullptr}, e);
   }
-  if (L.fixed) add_dX();
+  if (fx) add_dX();
   return pq_launch_ref(p, n, jobs, 2, s, PQP_GEMM_DX);
 }
 
-extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void* X, const void* W,
-                             const void* hpA, const void* hpB, const void* Wr, const void* ctx, size_t ctx_bytes,
-                             void* dX, float* dW, float* dhpA, float* dhpB, float* dWr, float* dalpha_dbeta,
-                             void* workspace, size_t workspace_bytes, void* stream) {
+// fx_at: where the region of fp32 digits lies when it does not follow ws_base in the workspace.
+static int linear_bwd_impl(const pq_linear_desc* d, const void* dY, const void* X, const void* W,
+                           const void* hpA, const void* hpB, const void* Wr, const void* ctx, size_t ctx_bytes,
+                           void* dX, float* dW, float* dhpA, float* dhpB, float* dWr, float* dalpha_dbeta,
+                           void* workspace, size_t workspace_bytes, void* stream, char* fx_at) {
   if (int e = check_desc(d, true)) return e;
   const lin_layout L = make_layout(*d);
   const bool routed = d->n_experts > 1 && d->hp_rank > 0;
@@ -726,7 +736,7 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
   PQ_REQUIRE(d->ste_mode == PQ_STE_IDENTITY || W, PQ_ERR_BAD_ARG, "PQ_STE_CLIP needs the latent W");
   PQ_REQUIRE(aligned16(dY) && aligned16(X) && aligned16(ctx) && aligned16(dX) && aligned16(dW) && aligned16(workspace) &&
                  aligned16(hpA) && aligned16(hpB) && aligned16(W), PQ_ERR_SHAPE, "buffers must be 16-byte aligned");
-  PQ_REQUIRE(workspace_bytes >= L.ws_total, PQ_ERR_WORKSPACE, "workspace too small: %zu < %zu", workspace_bytes, L.ws_total);
+  PQ_REQUIRE(workspace_bytes >= L.ws_base, PQ_ERR_WORKSPACE, "workspace too small: %zu < %zu", workspace_bytes, L.ws_base);
   PQ_REQUIRE(ctx_bytes >= L.ctx_total, PQ_ERR_WORKSPACE, "ctx too small: %zu < %zu", ctx_bytes, L.ctx_total);
   hipStream_t s = (hipStream_t)stream;
   const char* cx = (const char*)ctx;
@@ -739,7 +749,10 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
   void* dH = ws + L.dH;
   double* red_a = (double*)(ws + L.red_a);
   double* red_b = (double*)(ws + L.red_b);
-  if (!bf16) return linear_bwd_f32(d, L, dY, X, W, hpA, hpB, cx, dX, dW, dhpA, dhpB, dalpha_dbeta, ws, s);
+  if (!bf16) {
+    char* fx = L.fx_bytes == 0 ? nullptr : fx_at ? fx_at : workspace_bytes >= L.ws_total ? ws + L.ws_base : nullptr;
+    return linear_bwd_f32(d, L, dY, X, W, hpA, hpB, cx, dX, dW, dhpA, dhpB, dalpha_dbeta, ws, fx, s);
+  }
   int n_red_a = r > 0 ? pq_plan_gemm(T, r, N).red_blocks : 0;   // partial sums of d alpha that the dH GEMM leaves
 
   if (T > 0 && r > 0) {  // dH = alpha * dY B ; d alpha = <H, dY B>
@@ -881,14 +894,21 @@ extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void
   return PQ_OK;
 }
 
+extern "C" int pq_linear_bwd(const pq_linear_desc* d, const void* dY, const void* X, const void* W,
+                             const void* hpA, const void* hpB, const void* Wr, const void* ctx, size_t ctx_bytes,
+                             void* dX, float* dW, float* dhpA, float* dhpB, float* dWr, float* dalpha_dbeta,
+                             void* workspace, size_t workspace_bytes, void* stream) {
+  return linear_bwd_impl(d, dY, X, W, hpA, hpB, Wr, ctx, ctx_bytes, dX, dW, dhpA, dhpB, dWr, dalpha_dbeta, workspace, workspace_bytes, stream, nullptr);
+}
+
 // ---------------------------------------------------------------------------------------------
 // The linear with its normalisation (Sec. 3.1: Y = (lambda/gamma) W Q(Norm(X))): the fused normalising
 // quantiser writes codes, gamma and q/gamma straight into the linear's ctx, the high-precision branch reads
 // the stored normalised activations, and the backward chains the linear's dX into the normalisation backward.
-// ctx = [linear ctx][x_hat T*K][rstd T]; workspace = [linear workspace][d x_hat T*K][dgain partial rows].
+// ctx = [linear ctx][x_hat T*K][rstd T]; workspace = [linear workspace][d x_hat T*K][dgain partial rows][fp32 digits].
 // ---------------------------------------------------------------------------------------------
 namespace {
-struct norm_layout { size_t Xn, rstd, ctx_total, dXn, part, ws_total; };
+struct norm_layout { size_t Xn, rstd, ctx_total, dXn, part, ws_base, ws_total; };
 norm_layout make_norm_layout(const pq_linear_desc& d, const lin_layout& L) {
   norm_layout n;
   const size_t T = d.tokens, K = d.d_in, es = esize(d.io_dtype);
@@ -896,10 +916,11 @@ norm_layout make_norm_layout(const pq_linear_desc& d, const lin_layout& L) {
   n.Xn = c.take(T * K * es);
   n.rstd = c.take(T * sizeof(float));
   n.ctx_total = c.off;
-  cursor w; w.off = pq_align_up(L.ws_total, 256);
+  cursor w; w.off = L.ws_base;
   n.dXn = w.take(T * K * es);
   n.part = w.take(pq_rmsnorm_bwd_scratch_bytes(d.tokens, d.d_in) + 256);
-  n.ws_total = w.off;
+  n.ws_base = w.off;
+  n.ws_total = w.off + L.fx_bytes;
   return n;
 }
 int check_norm(const pq_linear_desc* d, bool bwd) {
@@ -930,7 +951,7 @@ extern "C" int pq_linear_norm_fwd(const pq_linear_desc* d, const void* X, const 
   const lin_layout L = make_layout(*d);
   const norm_layout NL = make_norm_layout(*d, L);
   PQ_REQUIRE(ctx_bytes >= NL.ctx_total, PQ_ERR_WORKSPACE, "ctx too small: %zu < %zu", ctx_bytes, NL.ctx_total);
-  PQ_REQUIRE(workspace_bytes >= NL.ws_total, PQ_ERR_WORKSPACE, "workspace too small: %zu < %zu", workspace_bytes, NL.ws_total);
+  PQ_REQUIRE(workspace_bytes >= NL.ws_base, PQ_ERR_WORKSPACE, "workspace too small: %zu < %zu", workspace_bytes, NL.ws_base);
   char* cx = (char*)ctx;
   const bool bf16 = d->io_dtype == PQ_BF16;
   void* Xn = cx + NL.Xn;
@@ -939,7 +960,7 @@ extern "C" int pq_linear_norm_fwd(const pq_linear_desc* d, const void* X, const 
                                       bf16 ? (uint16_t*)(cx + L.Xt) : nullptr, (float*)(cx + NL.rstd), (hipStream_t)stream, W, n,
                                       (double*)((char*)workspace + L.stat_partials), pq_stats_blocks(n)))
     return e;
-  return linear_fwd_impl(d, Xn, W, nullptr, hpA, hpB, Wr, Y, ctx, L.ctx_total, workspace, L.ws_total, stream, true);
+  return linear_fwd_impl(d, Xn, W, nullptr, hpA, hpB, Wr, Y, ctx, L.ctx_total, workspace, L.ws_base, stream, true);
 }
 
 extern "C" int pq_linear_norm_bwd(const pq_linear_desc* d, const void* dY, const void* X, const void* gain, const void* W,
@@ -953,12 +974,12 @@ extern "C" int pq_linear_norm_bwd(const pq_linear_desc* d, const void* dY, const
   const lin_layout L = make_layout(*d);
   const norm_layout NL = make_norm_layout(*d, L);
   PQ_REQUIRE(ctx_bytes >= NL.ctx_total, PQ_ERR_WORKSPACE, "ctx too small: %zu < %zu", ctx_bytes, NL.ctx_total);
-  PQ_REQUIRE(workspace_bytes >= NL.ws_total, PQ_ERR_WORKSPACE, "workspace too small: %zu < %zu", workspace_bytes, NL.ws_total);
+  PQ_REQUIRE(workspace_bytes >= NL.ws_base, PQ_ERR_WORKSPACE, "workspace too small: %zu < %zu", workspace_bytes, NL.ws_base);
   const char* cx = (const char*)ctx;
   char* ws = (char*)workspace;
   void* dXn = ws + NL.dXn;
-  if (int e = pq_linear_bwd(d, dY, cx + NL.Xn, W, hpA, hpB, Wr, ctx, L.ctx_total, dXn, dW, dhpA, dhpB, dWr, dalpha_dbeta, workspace,
-                            L.ws_total, stream))
+  if (int e = linear_bwd_impl(d, dY, cx + NL.Xn, W, hpA, hpB, Wr, ctx, L.ctx_total, dXn, dW, dhpA, dhpB, dWr, dalpha_dbeta, workspace,
+                              L.ws_base, stream, workspace_bytes >= NL.ws_total ? ws + NL.ws_base : nullptr))
     return e;
   float* part = (float*)(((uintptr_t)(ws + NL.part) + 255) & ~(uintptr_t)255);
   return pq_launch_rmsnorm_bwd(dXn, X, gain, (const float*)(cx + NL.rstd), d->io_dtype, d->tokens, d->d_in, dX, dgain, part,

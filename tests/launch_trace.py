@@ -3,7 +3,7 @@
 `trace(calls)` runs the calls in a child process in which the HIP runtime's symbols are those of host_launches.c (a launch
 records the kernel's name and grid and does nothing).  Buffers are addresses that nobody reads; workspace and ctx sizes are
 exactly what the library's own queries say.  A call is a dict: `op` (linear, linear_norm, prefill, ffn, hp_int8, decode) and the
-fields of its descriptor.  The result is one dict per call: `rc`, `error`, `launches`, a list of [kernel, template
+fields of its descriptor; for the linears also `workspace_bytes`, another size than the query's.  The result is one dict per call: `rc`, `error`, `launches`, a list of [kernel, template
 arguments, grid], and `symbols`, the launches' mangled kernel names."""
 import ctypes as C
 import json
@@ -103,10 +103,11 @@ def _child(shim_path, lib_path):
             if i8:
                 return lib.pq_decode_gemv_int8(p, *map(buf, range(9)), None, buf(9), size(nw), None)
             return lib.pq_decode_gemv(p, *map(buf, range(7)), None, buf(9), size(nw), None)
+        given = c.pop("workspace_bytes", 0)
         d = Linear(**{**dict(hp_rank=0, n_experts=1, top_k=1, io_dtype=1, w_kind=1 if op == "prefill" else 0, alpha=2.0, beta=0.2), **c})
         p = C.byref(d)
         kind = "pq_linear_norm" if op == "linear_norm" else "pq_linear"
-        nc, nw = query(kind + "_ctx_bytes", p), query(kind + "_workspace_bytes", p)
+        nc, nw = query(kind + "_ctx_bytes", p), given or query(kind + "_workspace_bytes", p)
         hp = [buf(2), buf(3), buf(4)] if d.hp_rank else [None, None, None]
         dhp = [buf(5), buf(6), buf(7)] if d.hp_rank else [None, None, None]
         if op == "prefill":

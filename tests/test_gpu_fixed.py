@@ -1,6 +1,8 @@
 """fp32 I/O, calls large enough for the fixed-point form of dX and dW: against the fp64 oracle at sizes where rows, tokens and tiles end
 inside their blocks (bound as for the fp64 products: one rounding to fp32), rows whose elements span the whole range of fp32 and
 cancel (an fp64 sum's own rounding is the bound), and infinities and NaN, which must come out where plain arithmetic has them."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -29,12 +31,55 @@ def test_shapes_that_digits_would_slow_down_do_not(T, K, N):
     assert not kernels(res, "fixed_rows_kernel")
 
 
-@pytest.mark.parametrize("T", [2048, 65536])
+@pytest.mark.parametrize("T", [2048, 32768])
 def test_column_maxima_are_reduced_once(T):
     """... in a launch of ceil(d_out / 64) workgroups whatever the tokens, not by every workgroup of the column pass."""
     res = trace([dict(op="linear", tokens=T, d_in=1024, d_out=1056, io_dtype=0)])[0]
     assert res["rc"] == 0, res["error"]
     assert [grid[0] for _, grid in kernels(res, "fixed_exps_kernel")] == [17]
+
+
+def _workspace(kind, T, K, N, w_kind=pq.PQ_W_MASTER, r=16):
+    return getattr(pq.lib(), kind + "_workspace_bytes")(C.byref(pq.make_desc(T, K, N, hp_rank=r, io_dtype=pq.PQ_F32, w_kind=w_kind)))
+
+
+@pytest.mark.parametrize("op", ["linear", "linear_norm"])
+def test_workspace_without_digits_is_accepted(op):
+    """The digits are a region behind everything else: forward and backward take a workspace that ends in front of it (the size of the
+    packed descriptor, which cannot have a backward), and the backward then runs fp64 products."""
+    T, K, N, r = 1037, 1056, 1120, 16
+    small, full = (_workspace("pq_" + op, T, K, N, w) for w in (pq.PQ_W_PACKED, pq.PQ_W_MASTER))
+    assert 0 < full - small - (14 * T * N + 28 * N * K) < 4 << 20
+    calls = [dict(op=op, tokens=T, d_in=K, d_out=N, hp_rank=r, io_dtype=0, workspace_bytes=n) for n in (full, full - 1, small, small - 1)]
+    res = trace(calls)
+    assert [x["rc"] for x in res] == [0, 0, 0, -4], [x["error"] for x in res]      # PQ_ERR_WORKSPACE
+    assert [len(kernels(x, "fixed_rows_kernel")) for x in res] == [1, 0, 0, 0]
+    assert not res[3]["launches"]
+
+
+@pytest.mark.parametrize("T,K,N", [(65536, 8192, 8192), (8192, 4096, 11008), (4096, 2048, 2040)])
+def test_workspace_of_digits_is_bounded(T, K, N):
+    """Beyond 2 GiB, and for d_out that no backward takes, there are no digits."""
+    assert _workspace("pq_linear", T, K, N) == _workspace("pq_linear", T, K, N, pq.PQ_W_PACKED) < 1 << 30
+
+
+@pytest.mark.gpu
+def test_workspace_without_digits_gives_the_same_gradients():
+    T, K, N, r = 517, 1568, 1504, 24
+    c = wl.linear_case(9, T, K, N, hp_rank=r, bf16=False, outlier_count=2, outlier_scale=10.0)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    t = {k: dev(c[k]) for k in ("X", "W", "dY", "A", "B")}
+    desc = pq.make_desc(T, K, N, hp_rank=r, io_dtype=pq.PQ_F32)
+    out = []
+    for ws in (None, torch.empty(_workspace("pq_linear", T, K, N, pq.PQ_W_PACKED, r), dtype=torch.uint8, device="cuda")):
+        bufs = pq.LinearBuffers(desc, ws=ws)
+        Y, dX, dW, dA, dB, dab = (torch.empty(s, device="cuda") for s in ((T, N), (T, K), (N, K), (r, K), (N, r), (2,)))
+        pq.linear_fwd(desc, t["X"], t["W"], Y, bufs, A=t["A"], B=t["B"])
+        pq.linear_bwd(desc, t["dY"], t["X"], t["W"], bufs, dX, dW, dab, A=t["A"], B=t["B"], dA=dA, dB=dB)
+        torch.cuda.synchronize()
+        out.append([x.cpu().numpy().astype(np.float64) for x in (Y, dX, dW, dA, dB, dab)])
+    for a, b in zip(*out):                            # sums that agree to fp64, each rounded to fp32
+        assert np.abs(a - b).max() <= 2.0**-23 * np.abs(a).max()
 
 
 @pytest.mark.gpu
