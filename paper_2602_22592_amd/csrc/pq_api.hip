@@ -114,7 +114,7 @@ struct lin_layout {
   size_t dYp, rd, dHs, dXs, dlogit, dwr, hp8_ws, hp8_ws_bytes;
   // fp32 I/O in fixed point (pq_fixed.hip): a region of fx_bytes (0: the call has none) behind everything else, which only a backward
   // uses, and only if the workspace holds it
-  size_t fx_drow, fx_rexp, fx_dcol, fx_cexp, fx_qT, fx_colmax, fx_red_b, fx_planes, fx_bytes;
+  size_t fx_drow, fx_rexp, fx_dcol, fx_cexp, fx_qT, fx_colmax, fx_counts, fx_red_b, fx_planes, fx_bytes;
   int n_red_a, n_red_b;
 };
 
@@ -224,6 +224,7 @@ lin_layout make_layout(const pq_linear_desc& d) {
     L.fx_drow = x.take(PQ_FIXED_DIGITS * T * N); L.fx_rexp = x.take(T * sizeof(int));
     L.fx_dcol = x.take(PQ_FIXED_DIGITS * N * Tp); L.fx_cexp = x.take(N * sizeof(int));
     L.fx_qT = x.take(K * Tp); L.fx_colmax = x.take(pq_fixed_max_rows(Ti) * N * sizeof(uint32_t));
+    L.fx_counts = x.take((2 * N + K) * sizeof(int));
     L.fx_red_b = x.take(sizeof(double) * (size_t)pq_ref_red_blocks(Ni, Ki, -1));
     L.fx_planes = x.take(pl);
     if (x.off <= FIXED_MAX_BYTES) {
@@ -664,7 +665,7 @@ static int linear_bwd_f32(const pq_linear_desc* d, const lin_layout& L, const vo
   if (fx) {                          // (dY / gamma)^T q: the digits of dY's columns, one behind the other, times q
     if (int err = pq_launch_fixed_split((const float*)dY, (const float*)(cx + L.gamma), (const int8_t*)(cx + L.Xq), T, Tp, N, K, (int8_t*)(fx + L.fx_drow),
                                         (int*)(fx + L.fx_rexp), (int8_t*)(fx + L.fx_dcol), (int*)(fx + L.fx_cexp), (int8_t*)(fx + L.fx_qT),
-                                        (uint32_t*)(fx + L.fx_colmax), s)) return err;
+                                        (uint32_t*)(fx + L.fx_colmax), (int*)(fx + L.fx_counts), s)) return err;
     pq_epilogue e = epi_zero();
     e.C = planes; e.ldc = K; e.out_kind = PQ_OUT_I32;
     if (int err = pq_launch_gemm(PQ_FIXED_DIGITS * N, K, Tp, {fx + L.fx_dcol, Tp, PQ_SRC_KC8, nullptr}, {fx + L.fx_qT, Tp, PQ_SRC_KC8, nullptr}, e, s,
@@ -678,6 +679,7 @@ static int linear_bwd_f32(const pq_linear_desc* d, const lin_layout& L, const vo
     p[n] = ref_problem(fx ? PQ_REF_SUM_SS8 : PQ_REF_SS8, N, K, T, {dY, N, PQ_SRC_KS32, nullptr},
                        {cx + L.Xq, K, PQ_SRC_KS8, (const float*)(cx + L.gamma)}, e);
     p[n].planes = planes; p[n].exps = fx ? (const int*)(fx + L.fx_cexp) : nullptr;
+    p[n].counts = fx ? (const int*)(fx + L.fx_counts) : nullptr;
     ++n;
   };
   if (!fx) add_dW();                 // (the longest first: products before sums of planes)

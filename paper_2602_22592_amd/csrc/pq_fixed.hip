@@ -6,8 +6,17 @@
 // element, X = rint(x 2^(54 - E)), max |x| < 2^E, and those as seven signed digits of base 256, each a plane of int8 (the
 // splitting of operands into slices whose products are exact: Ozaki, Ogita, Oishi, Rump, "Error-free transformations of matrix
 // multiplication", 2012).  Seven int8 products with int32 sums are exact; their sum sum_d 256^d acc_d 2^(E - 54) is formed in fp64
-// (pq_ref.hip, the SUM forms).  What is lost is the rounding of an element to 2^-55 of its row's largest, less than the
-// rounding that every addition of an fp64 sum of such a row makes.
+// (pq_ref.hip, the SUM forms).  What is lost is the rounding of an element to 2^(E - 55).  In dX every element of a row enters every
+// sum, and the additions behind the largest one round as much in fp64.  In dW a token whose code is zero stays out of a sum, and the
+// largest element may be such a token's.  The column pass therefore counts the small elements, below 2^(E - 17), the zero ones and,
+// per channel, the zero codes; a sum is taken from the planes only if, with l = tokens - small - zero ones and z the zero codes,
+//     8 max(l - z, 0) >= min(small, tokens - z):
+// at least l - z larger elements enter it then and at most eight times as many small ones, so that it is off by at most 2^-28 of
+// sum |x q|, a sixteenth of the rounding to fp32.  A 32x32 tile with another sum in it
+// is formed as the fp64 product it stands for.  One token 1e9 / 1e12 / 1e16 times the others: relative error of the sums that its zero
+// codes leave out 3.2e-8 / 1.9e-5 / 0.2 from the planes, 2.6e-8 now.  Backward of 2048 tokens 2048x2048 (us): 248 with normal data; 218 to
+// 249 with 95 % zero codes, half of the tokens masked, token scales of e^+-6 or elements of e^+-10; 538 with one token 1e6 times the others
+// (all tiles fp64).
 // What it is for: the fp64 matrix rate is 78.6 TFLOP/s, the int8 one 5 POP/s nominal and 2 on real data, so seven products cost a
 // fifth of one fp64 product.  2048 tokens, 2048x2048 (us): dX 277 -> 74 + 57 (with the rank-128 product and dA), dW 275 -> 80 + 65 (with dB
 // and dH); the two passes below 14 and 23, one over dY each: 4 bytes read and 7 written per element; whole step 718 -> 388.
@@ -21,6 +30,7 @@ namespace {
 
 constexpr int ND = PQ_FIXED_DIGITS;
 constexpr int COLT = 128;                            // tokens per workgroup of the column pass
+constexpr int SMALL = 37;                            // digits below 2^37: elements below 2^(E - 17)
 constexpr int ROWS = 8;                              // rows of dY per workgroup of the row pass, four to a half of it
 
 // 1 / gamma in fp64, as the fp64 products form it (pq_ref.hip)
@@ -60,9 +70,11 @@ __device__ __forceinline__ int exp_f32(uint32_t u) { return u >= 0x7F800000u ? P
 __device__ __forceinline__ int exp_f64(uint32_t u) { return u >= 0x7FF00000u ? PQ_FIXED_NOT_FINITE : max((int)(u >> 20), 1) - 1022; }
 
 // Rows of dY: digits [ND][T][N] and exponents [T]; colmax [ceil(T / ROWS)][N]: the largest |dY / gamma| of the workgroup's rows, as
-// the upper half of the double.
+// the upper half of the double.  counts: cleared for the column pass.
 __global__ __launch_bounds__(512) void fixed_rows_kernel(const float* __restrict__ dY, const float* __restrict__ gamma, int T, int N,
-                                                         int8_t* __restrict__ D, int* __restrict__ rexp, uint32_t* __restrict__ colmax) {
+                                                         int8_t* __restrict__ D, int* __restrict__ rexp, uint32_t* __restrict__ colmax,
+                                                         int* __restrict__ counts, int ncounts) {
+  for (int i = blockIdx.x * 512 + threadIdx.x; i < ncounts; i += gridDim.x * 512) counts[i] = 0;
   constexpr int R = ROWS / 2;
   __shared__ uint32_t wmax[8][R];
   __shared__ uint4 cmax[256];
@@ -152,15 +164,17 @@ __global__ __launch_bounds__(1024) void fixed_exps_kernel(const uint32_t* __rest
 }
 
 // Columns of dY / gamma over the tokens: digits [ND][N][Tp]; and q transposed, [K][Tp].  Tp: T rounded up to whole
-// 16 bytes, the rest zero.  Workgroups (column block, token block of COLT): N / 64 of digits, then K / 256 of codes.
+// 16 bytes, the rest zero.  counts: small elements [N], zero ones [N], zero codes [K].  Workgroups (column block, token block of COLT): N / 64 of digits, then K / 256 of codes.
 __global__ __launch_bounds__(256) void fixed_cols_kernel(const float* __restrict__ dY, const float* __restrict__ gamma, const int8_t* __restrict__ q,
                                                          int T, int Tp, int N, int K, const int* __restrict__ cexp, int8_t* __restrict__ D,
-                                                         int8_t* __restrict__ qT, int nblk) {
+                                                         int8_t* __restrict__ qT, int* __restrict__ counts, int nblk) {
+  __shared__ int zero_codes[256];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   if ((int)blockIdx.x >= nblk) {                     // uniform: four columns of codes per lane, sixteen tokens per wavefront
-    const int k = ((int)blockIdx.x - nblk) * 256 + 4 * lane;
-    if (k >= K) return;
-    const int tend = min(Tp, (int)(blockIdx.y + 1) * COLT);
+    const int k0 = ((int)blockIdx.x - nblk) * 256, k = k0 + 4 * lane;
+    zero_codes[threadIdx.x] = 0;
+    __syncthreads();
+    const int tend = k < K ? min(Tp, (int)(blockIdx.y + 1) * COLT) : 0;
     for (int t0 = blockIdx.y * COLT + wv * 16; t0 < tend; t0 += 64) {
       uint32_t w[16];
 #pragma unroll
@@ -171,8 +185,15 @@ __global__ __launch_bounds__(256) void fixed_cols_kernel(const float* __restrict
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[i >> 2] |= (t0 + i < T ? (w[i] >> (8 * j)) & 0xFFu : 0u) << (8 * (i & 3));
         *reinterpret_cast<uint4*>(qT + (size_t)(k + j) * Tp + t0) = make_uint4(o[0], o[1], o[2], o[3]);
+        int z = -max(t0 + 16 - T, 0);                // (not the padding)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) z += __builtin_popcount(~(((o[i] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | o[i] | 0x7F7F7F7Fu));
+        atomicAdd(&zero_codes[4 * lane + j], z);
       }
     }
+    __syncthreads();
+    const int kk = k0 + threadIdx.x;
+    if (kk < K && zero_codes[threadIdx.x] > 0) atomicAdd(counts + 2 * N + kk, zero_codes[threadIdx.x]);
     return;
   }
   const int n = blockIdx.x * 64 + lane;
@@ -181,6 +202,7 @@ __global__ __launch_bounds__(256) void fixed_cols_kernel(const float* __restrict
   const bool ok = e != PQ_FIXED_NOT_FINITE;
   const double s = ok ? pow2(min(54 - e, 1023)) : 0.0;
   const int tend = min(Tp, (int)(blockIdx.y + 1) * COLT);
+  int small = 0, zero = 0;
   for (int t0 = blockIdx.y * COLT + wv * 16; t0 < tend; t0 += 64) {
     float v[16];
 #pragma unroll
@@ -192,7 +214,11 @@ __global__ __launch_bounds__(256) void fixed_cols_kernel(const float* __restrict
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int t = t0 + 4 * h + i;
-        w[i] = ok && t < T ? digits((double)v[4 * h + i] * recip(gamma[min(t, T - 1)]) * s) : 0;
+        const double x = (double)v[4 * h + i] * recip(gamma[min(t, T - 1)]) * s;
+        w[i] = ok && t < T ? digits(x) : 0;
+        const bool is0 = t < T && v[4 * h + i] == 0.0f;
+        zero += is0 ? 1 : 0;
+        small += t < T && !is0 && fabs(x) < (double)(1ull << SMALL) ? 1 : 0;
       }
       planes_of(w, o[h]);
     }
@@ -200,6 +226,8 @@ __global__ __launch_bounds__(256) void fixed_cols_kernel(const float* __restrict
     for (int d = 0; d < ND; ++d)
       *reinterpret_cast<uint4*>(D + ((size_t)d * N + n) * Tp + t0) = make_uint4(o[0][d], o[1][d], o[2][d], o[3][d]);
   }
+  if (small > 0) atomicAdd(counts + n, small);       // (rare on both counts)
+  if (zero > 0) atomicAdd(counts + N + n, zero);
 }
 
 }  // namespace
@@ -207,14 +235,14 @@ __global__ __launch_bounds__(256) void fixed_cols_kernel(const float* __restrict
 int pq_fixed_max_rows(int T) { return (T + ROWS - 1) / ROWS; }
 
 int pq_launch_fixed_split(const float* dY, const float* gamma, const int8_t* q, int T, int Tp, int N, int K, int8_t* Drow, int* rexp, int8_t* Dcol,
-                          int* cexp, int8_t* qT, uint32_t* colmax, hipStream_t s) {
+                          int* cexp, int8_t* qT, uint32_t* colmax, int* counts, hipStream_t s) {
   pq_prof_scope prof(PQP_QUANT, s);
-  fixed_rows_kernel<<<pq_fixed_max_rows(T), 512, 0, s>>>(dY, gamma, T, N, Drow, rexp, colmax);
+  fixed_rows_kernel<<<pq_fixed_max_rows(T), 512, 0, s>>>(dY, gamma, T, N, Drow, rexp, colmax, counts, 2 * N + K);
   PQ_CHECK_LAUNCH("fixed_rows_kernel");
   const int nblk = (N + 63) / 64;
   fixed_exps_kernel<<<nblk, 1024, 0, s>>>(colmax, pq_fixed_max_rows(T), N, cexp);
   PQ_CHECK_LAUNCH("fixed_exps_kernel");
-  fixed_cols_kernel<<<dim3(nblk + (K + 255) / 256, (Tp + COLT - 1) / COLT), 256, 0, s>>>(dY, gamma, q, T, Tp, N, K, cexp, Dcol, qT, nblk);
+  fixed_cols_kernel<<<dim3(nblk + (K + 255) / 256, (Tp + COLT - 1) / COLT), 256, 0, s>>>(dY, gamma, q, T, Tp, N, K, cexp, Dcol, qT, counts, nblk);
   PQ_CHECK_LAUNCH("fixed_cols_kernel");
   return PQ_OK;
 }

@@ -243,12 +243,24 @@ __device__ __forceinline__ void ref_contract(const pq_operand& A, const pq_opera
 }
 
 // The sums of a SUM form: sum_d 256^d acc_d 2^(E - 54), from the top digit down (a lane's two columns of a row are one load a plane).
-// False for the whole wavefront when one of its rows has no digits: the tile is then to be formed as the fp64 product it stands for.
+// False for the whole wavefront when one of its rows has no digits, or (FORM SUM_SS8, see pq_fixed.hip) one of its sums may consist
+// of elements that the digits hold too coarsely: the tile is then to be formed as the fp64 product it stands for.
+template <int FORM>
 __device__ __forceinline__ bool ref_planes(const pq_ref_problem& p, int m0, int n0, int li, int lk, f64x4_t (&acc)[2][2]) {
   constexpr int NB = 2;
   const size_t stride = (size_t)p.M * p.N;
   const int n = min(n0 + NB * li, p.N - NB);
-  if (__any(p.exps[min(m0 + ((int)threadIdx.x & 31), p.M - 1)] == PQ_FIXED_NOT_FINITE)) return false;
+  const int rm = min(m0 + ((int)threadIdx.x & 31), p.M - 1);
+  bool leave = p.exps[rm] == PQ_FIXED_NOT_FINITE;
+  if constexpr (FORM == PQ_REF_SUM_SS8) {
+    const int small = p.counts[rm], l = p.K - small - p.counts[p.M + rm];
+    int z = p.counts[2 * p.M + min(n0 + ((int)threadIdx.x & 31), p.N - 1)];
+    z = z == p.K ? 0 : z;                            // (a channel of zeros has no sum; of the others the one with the most zeros decides)
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) z = max(z, __shfl_xor(z, o, 64));
+    leave |= 8 * max(l - z, 0) < min(small, p.K - z);
+  }
+  if (__any(leave)) return false;
 #pragma unroll
   for (int i = 0; i < NB; ++i)
 #pragma unroll
@@ -300,7 +312,7 @@ __device__ __forceinline__ void ref_tile(const pq_ref_problem& p, int block, dou
   if (live) {
     bool contract = true;                                 // uniform
     if constexpr (SUM) {
-      contract = !ref_planes(p, m0, n0, li, lk, acc);
+      contract = !ref_planes<FORM>(p, m0, n0, li, lk, acc);
       if (contract) clear();
     }
     if (contract) ref_contract<AK, BK, NB, DEPTH>(p.A, p.B, m0, p.M, n0, p.N, p.K, first, KS, li, lk, acc);
