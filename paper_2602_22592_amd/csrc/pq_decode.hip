@@ -777,7 +777,6 @@ struct gemv_params {
   int N, K, E, r, topk;
   float alpha;
   const float* gB;        // INT8 experts: [L][E][N] gammas of the rows of hpB (then hpB is int8 [L][E][N][r])
-  int xshare;             // > 1: that many consecutive weight sets read the same token (planes, row sum, gamma of set / xshare)
 };
 
 // INT8 experts: the hidden state of every selected expert (bf16 values held as fp32) is put on the INT8 grid
@@ -962,8 +961,7 @@ __global__ __launch_bounds__(256) void decode_gemv_tiled_kernel(gemv_params p) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nw = p.K / 32, nq = nw / 4;
   const int G = (p.N + 63) / 64;
-  const int xl = p.xshare > 1 ? layer / p.xshare : layer;   // the token this weight set reads
-  const uint32_t* __restrict__ planes = p.planes + (size_t)xl * 8 * nw;
+  const uint32_t* __restrict__ planes = p.planes + (size_t)layer * 8 * nw;
 
   int a[GPB][8];
 #pragma unroll
@@ -1126,9 +1124,9 @@ __global__ __launch_bounds__(256) void decode_gemv_tiled_kernel(gemv_params p) {
     if (row < p.N) {
       const int dd = s_dot[g][0][lane] + s_dot[g][1][lane] + s_dot[g][2][lane] + s_dot[g][3][lane];
       const float yy = p.r > 0 ? s_yh[g][lane] : 0.0f;
-      const int acc = 2 * dd - p.rowsum[xl];
+      const int acc = 2 * dd - p.rowsum[layer];
       if (p.acc_out) p.acc_out[(size_t)layer * p.N + row] = acc;
-      const float sc = fp16_bits_to_f32(p.scale[layer]) / p.gamma[xl];
+      const float sc = fp16_bits_to_f32(p.scale[layer]) / p.gamma[layer];
       p.Y[(size_t)layer * p.N + row] = f32_to_bf16(__fmul_rn(sc, (float)acc) + p.alpha * yy);
     }
   }
@@ -2028,7 +2026,7 @@ int pq_launch_decode_ffn(int L, int B, int D, int F, int r, int E, int topk, flo
   {  // U, G and the largest |Hd|; beside them the router and the expert hidden pairs [Up_e x ; Gate_e x]
     pq_prof_scope prof(PQP_DECODE_MAIN, s);
     gemv_params p{packed_upgate, scale_upgate, pl1, rs1, gm1, nullptr, nullptr, nullptr, nullptr, (uint16_t*)UG, acc_upgate,
-                  F, D, E, 0, 0, alpha, nullptr, 2};
+                  F, D, E, 0, 0, alpha, nullptr};
     const int rows = prep_h_rows(L, topk * 2 * r), parts = (topk * 2 * r + rows - 1) / rows;
     const prep_h_params hp{(const uint16_t*)X, (const uint16_t*)Wr, UpGate, nullptr, D, E, 2 * r, topk, parts, rows,
                            nullptr, nullptr, nullptr, nullptr, idx, gate, hug, nullptr};
@@ -2043,7 +2041,7 @@ int pq_launch_decode_ffn(int L, int B, int D, int F, int r, int E, int topk, flo
   {  // down product + experts' down projections
     pq_prof_scope prof(PQP_DECODE_MAIN, s);
     gemv_params p{packed_down, scale_down, pl2, rs2, gm2, (const uint16_t*)Down, idx, gate, act, (uint16_t*)Y, nullptr,
-                  D, F, E, r, topk, alpha, nullptr, 1};
+                  D, F, E, r, topk, alpha, nullptr};
     dim3 grid((D + 63) / 64, L);
     decode_gemv_tiled_kernel<1, false><<<grid, 256, 0, s>>>(p);
     PQ_CHECK_LAUNCH("decode_gemv_tiled_kernel");

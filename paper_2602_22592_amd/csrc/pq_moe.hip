@@ -579,8 +579,7 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(uint16_t* __restrict__
 
 // The same with the router matrix in LDS (E * d bf16 <= 64 KB, E <= 64) and a token's pieces requested together: NC
 // 16-byte pieces per lane (d = 512 NC), up to KMAX slots per token; lane e fetches dlogit[t][e] once and hands it round.
-// (In the loop above every dlogit and router piece is a load of its own with a wait behind it: 32 cache round trips
-// per lane and token at 8 experts.)  A workgroup takes CB_TOK tokens per wavefront, so the router matrix is staged once
+// A workgroup takes CB_TOK tokens per wavefront, so the router matrix is staged once
 // per 4 * CB_TOK tokens.  Same sums in the same order as above.
 constexpr int CB_TOK = 4;
 template <int NC, int KMAX>
@@ -813,9 +812,9 @@ int pq_launch_combine_bwd(void* dX, const void* dXs, const int* inv, const float
   pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
   const size_t wr_bytes = (size_t)E * d * 2;
   const int grid_l = (T + 4 * CB_TOK - 1) / (4 * CB_TOK);
-  if (E > 0 && E <= 64 && k <= 2 && wr_bytes <= 64 * 1024 && d == 2048)
+  if (E <= 64 && k <= 2 && wr_bytes <= 64 * 1024 && d == 2048)
     combine_bwd_lds_kernel<4, 2><<<grid_l, 256, wr_bytes, s>>>((uint16_t*)dX, (const uint16_t*)dXs, inv, dlogit, (const uint16_t*)Wr, T, k, E);
-  else if (E > 0 && E <= 64 && k <= 2 && wr_bytes <= 64 * 1024 && d == 4096)
+  else if (E <= 64 && k <= 2 && wr_bytes <= 64 * 1024 && d == 4096)
     combine_bwd_lds_kernel<8, 2><<<grid_l, 256, wr_bytes, s>>>((uint16_t*)dX, (const uint16_t*)dXs, inv, dlogit, (const uint16_t*)Wr, T, k, E);
   else
     combine_bwd_kernel<<<(T + 3) / 4, 256, 0, s>>>((uint16_t*)dX, (const uint16_t*)dXs, inv, dlogit, (const uint16_t*)Wr, T, k, d, E);
