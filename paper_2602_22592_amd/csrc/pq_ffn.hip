@@ -56,12 +56,14 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   L.Xq = c.take(T * D); L.gx = c.take(T * 4); L.Xt = c.take(T * D * 2);
   L.U = c.take(T * F * 2); L.G = c.take(T * F * 2);
   L.Hq = c.take(T * F); L.gh = c.take(T * 4); L.Ht = c.take(T * F * 2);
-  // (a single branch has no slots of its own: its products read and write the token rows; with INT8 experts its output is kept for d alpha)
+  // (a single branch has no routing and no slots of its own: its products read and write the token rows; with INT8 experts its output
+  // is kept for d alpha)
   const size_t So = E > 1 ? S : 0;
   const bool hp8 = d.hp_kind == PQ_HP_LOWRANK_INT8;
-  L.idx = c.take(S * 4); L.gate = c.take(S * 4); L.probs = c.take(T * E * 4);
-  L.counts = c.take(E * 4); L.offsets = c.take((E + 1) * 4); L.perm = c.take(S * 4); L.inv = c.take(S * 4);
-  L.Xp = c.take(So * D * 2); L.ue = c.take(2 * S * r * 2); L.ge = L.ue + S * r * 2; L.a = c.take(S * r * 2);
+  L.idx = c.take(So * 4); L.gate = c.take(So * 4); L.probs = c.take(E > 1 ? T * E * 4 : 0);
+  L.counts = c.take(E > 1 ? E * 4 : 0); L.offsets = c.take(E > 1 ? (E + 1) * 4 : 0); L.perm = c.take(So * 4); L.inv = c.take(So * 4);
+  L.Xp = c.take(So * D * 2); L.ue = c.take(2 * S * r * 2); L.ge = L.ue + S * r * 2;
+  L.a = c.take(hp8 && pq_expert_act_quant_applies((int)r) ? 0 : S * r * 2);   // (INT8: with the quantiser in the same launch only aT stays)
   L.Ys = c.take((hp8 ? S : So) * D * 2);
   if (hp8) {
     // rows of [Up_e; Gate_e] (one [2 r][D] matrix per expert, as in the bf16 form): codes, gammas, de-quantised copy
@@ -111,7 +113,7 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   L.dHd = w.take(T * F * 2); L.dU = w.take(T * F * 2); L.dG = w.take(T * F * 2);
   L.dYp = w.take(So * D * 2); L.rd = w.take(So * 4);
   L.da = w.take(S * r * 2); L.du = w.take(2 * S * r * 2); L.dg = L.du + S * r * 2; L.as = w.take(S * r * 2);
-  L.dXs = w.take(So * D * 2); L.dlogit = w.take(T * E * 4);
+  L.dXs = w.take(So * D * 2); L.dlogit = w.take(E > 1 ? T * E * 4 : 0);
   L.dwr = w.take(E > 1 ? pq_dwr_scratch_bytes((int)T, (int)D, (int)E) : 0);
   L.ws_total = w.off;
   return L;
@@ -210,9 +212,10 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
   }
   if (int e = pq_launch_ffn_prep(p, s)) return e;
   if (int e = pq_launch_pack3(p.w, s)) return e;
+  const bool one = E == 1;
   if (T == 0)  // no tokens: leave empty expert segments behind so that a backward call is well defined
-    return pq_launch_route((const int*)(cx + L.idx), 0, E, (int*)(cx + L.counts), (int*)(cx + L.offsets), (int*)(cx + L.perm),
-                           (int*)(cx + L.inv), s);
+    return one ? PQ_OK : pq_launch_route((const int*)(cx + L.idx), 0, E, (int*)(cx + L.counts), (int*)(cx + L.offsets), (int*)(cx + L.perm),
+                                         (int*)(cx + L.inv), s);
 
   {  // U and G: pure 1-bit linears (no feature scale of their own), one launch
     pq_operand A{Xq, D, PQ_SRC_KC8, nullptr};
@@ -226,7 +229,6 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
   if (int e = pq_launch_swiglu_quant(cx + L.U, cx + L.G, T, F, Fv, Hq, gh, cx + L.Ht, s)) return e;
   // Y = beta * (lambda_d / gamma_h) * acc.  A single bf16 branch comes in as the second contraction of the same tile
   // (Y = alpha * ((beta lambda_d / alpha / gamma_h) acc + a Down^T)) under the rules of the linear's dense branch.
-  const bool one = E == 1;
   const bool fuse_y = one && !hp8 && d->alpha != 0.0f && fabsf(d->alpha) >= 9.5367431640625e-7f * fabsf(d->beta) &&
                       pq_plan_fuses(pq_plan_gemm(T, D, F, true, true, PQ_PLAN_SIGNS));
   auto launch_down = [&]() -> int {
