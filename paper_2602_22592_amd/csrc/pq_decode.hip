@@ -722,17 +722,21 @@ __global__ __launch_bounds__(256) void decode_h_grouped_kernel(const uint16_t* _
   }
 }
 
-// Launches the expert-grouped kernel when the shape allows it (then returns true).  Widths other than 512, 1024, 2048 and 4096
-// take it from 1024 workgroups on, where its one pass over the rows decides (whole calls: 13 tokens, 40 layers of 2560 63.3 -> 55.3
-// us; 8 tokens, 16 layers of 3328 50.9 -> 48.0; decode FFN of 16 tokens, 20 layers of 3584/8192 190 -> 171); with 64 the tokens of an
-// expert one after the other are the longer chain (decode FFN of 3 tokens, 2 layers of 1280/3072 26.8 -> 27.6), and a wavefront per
-// slot and row stays.  So it does past 4096 columns, where only one row to a wavefront fits the registers (4 tokens, 8 layers of
-// 6144 36.6 -> 39.9; 16 tokens, 2 layers of 7680 43 -> 57).
+// Launches the expert-grouped kernel when the shape allows it and it pays (then returns true).  Its gain is one pass over the rows of an
+// expert for all its tokens, its price that the tokens follow one another in a workgroup that holds two rows to a wavefront: from
+// 1024 workgroups on (four to a CU) and with at least d_in / 4096 selections per expert.  Whole calls on weights that no cache holds,
+// a wavefront per slot and row against grouped, eight experts of rank 64, us: 16 layers (1024 workgroups), 1 selection per expert (8 tokens, top-1): 1024 wide
+// 20.9 / 18.4, 2560 27.4 / 26.8, 4096 34.0 / 34.1; 2 per expert 27.6 / 22.1, 34.5 / 29.4, 42.2 / 40.8; 0.25 per expert (2 tokens) 15.8 / 14.7,
+// 18.9 / 21.3, 23.6 / 26.2.  One layer (64 workgroups), 2 per expert: 16.9 / 17.8, 20.6 / 23.6, 24.4 / 28.4.  Rows of up to 1024 columns
+// gain from 8192 workgroups times selections on (1024 wide, 4 layers of 16 tokens, top-2: 23.7 / 22.7; 2048 wide 26.7 / 28.4).  (The same lines
+// fit 4, 16, 32 and 64 experts.)  Past 4096 columns only one row to a wavefront fits the registers and a wavefront per slot and row stays (4 tokens, 8 layers of 6144
+// 36.6 -> 39.9; 16 tokens, 2 layers of 7680 43 -> 57).
 static bool launch_h_grouped(const uint16_t* X, const uint16_t* A, const int* idx, int L, int B, int K, int E, int r, int topk, float* h,
                              hipStream_t s) {
   if (r % HG_ROWS != 0 || B * topk > 64 || K % 8 != 0 || K > 4096) return false;
   const long groups = (long)L * E * (r / HG_ROWS);
-  if (!(K == 512 || K == 1024 || K == 2048 || K == 4096) && groups < 1024) return false;
+  const int slots = B * topk;
+  if ((groups < 1024 && !(K <= 1024 && groups * slots >= 8192)) || 4096L * slots < (long)K * E) return false;
   auto go = [&](auto nv) {
     constexpr int NV = decltype(nv)::value;
     if (K == 512 * NV) decode_h_grouped_kernel<NV, false><<<(unsigned)groups, 256, 0, s>>>(X, A, idx, B, K, E, r, topk, h);

@@ -89,7 +89,9 @@ def test_decode_small_batch(L, B, K, N, E, r, k, tiled):
                                            # 1024 workgroups of hidden states, expert by expert: rows that end inside a lane's
                                            # last piece, in one and in eight pieces; whole pieces of another width
                                            (32, 5, 384, 64, 8, 32, 2), (64, 3, 1152, 64, 4, 32, 2), (64, 2, 3968, 64, 4, 32, 1),
-                                           (64, 2, 1536, 64, 4, 32, 3)])
+                                           (64, 2, 1536, 64, 4, 32, 3), (64, 2, 3968, 64, 4, 32, 2),
+                                           # ... and whole rows of one, two, four and eight pieces
+                                           (64, 3, 512, 64, 4, 32, 1), (64, 3, 1024, 64, 4, 32, 1), (32, 9, 2048, 64, 8, 32, 1), (64, 5, 4096, 64, 4, 32, 2)])
 def test_decode_small_batch_tiled_ragged_k(L, B, K, N, E, r, k):
     """Row-interleaved packing takes any d_in that is a multiple of 128 (here not of 512) and a ragged last group."""
     print(f"decode tiled B={B}: L={L} K={K} N={N} E={E} r={r} k={k}", flush=True)

@@ -85,3 +85,16 @@ def test_single_branch_of_large_rank_takes_split_256_tiles(T, D, F, r):
     (args, grid), = [k for k in kernels(res, "gemm_tn_w4_kernel") if k[0][2]]
     assert args == [int(T % 32 != 0), 0, 1] and grid[1] > 1
     assert [0, 1] in [a for a, _ in kernels(res, "splitk_reduce_kernel")]
+
+
+@pytest.mark.parametrize("batch,d_in,experts,rank,layers,top_k,grouped", [(8, 2560, 8, 64, 16, 1, True), (4, 2560, 8, 64, 16, 1, False), (8, 2560, 8, 64, 8, 2, False),
+                                                                          (8, 4096, 8, 64, 16, 1, True), (4, 4096, 8, 64, 16, 1, False), (16, 4096, 8, 64, 1, 2, False),
+                                                                          (2, 1024, 8, 64, 64, 1, True), (8, 1024, 64, 64, 4, 1, False), (8, 3328, 4, 32, 64, 1, True),
+                                                                          (16, 4224, 8, 64, 16, 2, False), (16, 1024, 8, 64, 4, 2, True),
+                                                                          (16, 1152, 8, 64, 4, 2, False), (8, 1024, 8, 64, 4, 2, False)])
+def test_decode_hidden_states_expert_by_expert_where_tokens_share_experts(batch, d_in, experts, rank, layers, top_k, grouped):
+    """From 1024 workgroups of eight rows (rows of up to 1024 columns: 8192 workgroups times selections) and d_in / 4096 selections per
+    expert on, whatever the width up to 4096."""
+    r = trace([dict(op="decode", batch=batch, d_in=d_in, d_out=512, hp_rank=rank, n_experts=experts, top_k=top_k, n_layers=layers)])[0]
+    assert r["rc"] == 0, r["error"]
+    assert len(kernels(r, "decode_h_grouped_kernel")) == int(grouped) and len(kernels(r, "decode_h_kernel")) == int(not grouped)
