@@ -338,8 +338,9 @@ def fp32_io_bench(pq, torch, c, steps=5, warmup=2):
     big = 2.0 * T * K * N
     return {"workload": "tokens=%d, d_in=%d, d_out=%d, r=%d, fp32 I/O, fwd+bwd" % (T, K, N, r), "ms_per_step": round(ms, 3),
             "tokens_per_s": round(T / (ms * 1e-3), 1),
-            "gemm_dX_fp64_TFLOPs": round(big / (k_us["gemm_dX"] * 1e-6) / 1e12, 1) if "gemm_dX" in k_us else None,
-            "gemm_dW_fp64_TFLOPs": round(big / (k_us["gemm_dW"] * 1e-6) / 1e12, 1) if "gemm_dW" in k_us else None,
+            # operations of the one fp64 product over everything a step spends under its label: the int8 product of its digits, the
+            # launch that sums them and what shares it (dX: the rank-r product and dA; dW: dB and dH)
+            **{f"{n}_fp64_equivalent_TFLOPs": round(big / (1e-3 * prof[n][0] / steps) / 1e12, 1) for n in ("gemm_dX", "gemm_dW") if n in prof},
             "kernels_us": k_us}
 
 
