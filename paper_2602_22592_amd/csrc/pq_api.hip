@@ -128,7 +128,7 @@ struct cursor {
 };
 
 inline int fixed_Tp(int T) { return (T + 15) / 16 * 16; }
-// The two large contractions of the fp32 backward in fixed point: seven int8 products of one in fp64, a tenth of its time, but five
+// The two large contractions of the fp32 backward in fixed point: seven int8 products of one in fp64, a quarter of its time, but five
 // more launches (some 20 us) and 56 bytes of planes per output and 22 of digits per element of dY, written and read, i.e. 56 (1 / d_out +
 // 1 / tokens) + 22 / d_in bytes per product.  Backward against the fp64 products, 49 shapes of 64 to 65536 tokens and widths of 128 to 16384:
 // with 1 / tokens + 1 / d_out + 0.4 / d_in up to 1 / 320 1.17 x (512 tokens 1024->4096, 65536 512->512 1.19) to 2.77 x (2048 tokens

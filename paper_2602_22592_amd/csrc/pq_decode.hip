@@ -1142,7 +1142,7 @@ __global__ __launch_bounds__(256) void decode_gemv_tiled_kernel(gemv_params p) {
 // largest |silu(G) U| of its 64 columns leaves with them (amax[layer][group]) and the pass that collected it goes; an integer
 // maximum into one cell per layer took 4 us longer at 32 layers.  Bound by the weight stream once there are many layers
 // (32 of 4096/11008: 428 MB in 75 us, 5.7 TB/s) and by the chain of launches below that: five launches became four,
-// one layer of 1024/2048 21.4 -> 19.8 us, two of 2048/5504 29.8 -> 27.5, 32 of 1024/4096 41.5 -> 38.1, 32 of 4096/11008 128.4 -> 128.8.
+// one layer of 1024/2048 21.4 -> 19.8 us, two of 2048/5504 29.8 -> 27.5, 32 of 1024/4096 41.5 -> 38.1, 32 of 4096/11008 128.2 -> 127.1.
 __global__ __launch_bounds__(256) void decode_ffn_upgate_kernel(gemv_params p, prep_h_params hp, int L, int nh, float* __restrict__ amax) {
   extern __shared__ __attribute__((aligned(16))) float xs[];   // hidden rows: the token as fp32
   __shared__ prep_shared sh;

@@ -18,8 +18,8 @@
 // 249 with 95 % zero codes, half of the tokens masked, token scales of e^+-6 or elements of e^+-10; 538 with one token 1e6 times the others
 // (all tiles fp64).
 // What it is for: the fp64 matrix rate is 78.6 TFLOP/s, the int8 one 5 POP/s nominal and 2 on real data, so seven products cost a
-// fifth of one fp64 product.  2048 tokens, 2048x2048 (us): dX 277 -> 74 + 57 (with the rank-128 product and dA), dW 275 -> 80 + 65 (with dB
-// and dH); the two passes below 14 and 23, one over dY each: 4 bytes read and 7 written per element; whole step 718 -> 388.
+// quarter of one fp64 product.  2048 tokens, 2048x2048, r = 128 (us): dX 277 -> 74 + 55 (with the rank-128 product and dA), dW 275 -> 77 + 63 (with
+// dB and dH); the passes below 13, 5 and 20, two of them over dY, 4 bytes read and 7 written per element; whole step 718 -> 380.
 // Infinities and NaN have no fixed-point form: their rows get no digits and are marked, and the SUM forms compute a 32x32 tile that
 // a marked row reaches as the fp64 product it stands for.  Step of 2048 tokens 2048x2048 (us): finite 300; one NaN in dY 443; an infinity in X, which marks every
 // row of dW, 604 (one element after the other: 1115 and 5368; fp64 products alone 600).

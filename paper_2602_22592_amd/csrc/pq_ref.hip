@@ -1,5 +1,6 @@
 // Reference-precision engine (fp32 I/O): products and sums in fp64 on the matrix pipe (v_mfma_f64_16x16x4_f64), for every
-// GEMM of the linear whose operands are fp32 except the exact int8 one.
+// GEMM of the linear whose operands are fp32 but these: the 1-bit product of the forward, exact in int8, and the contractions of dX and dW
+// of large calls, which come as int32 sums of digit products (pq_fixed.hip) that the SUM forms below add up in fp64.
 //
 // What bounds it: the instruction itself, 64 cycles per 2048 flops and SIMD (78.6 TFLOP/s over the chip; the vendor's fp64
 // product reaches 71.8 on 4096^3).  A wavefront needs so little operand data per instruction (two 8-byte values per lane and
