@@ -114,7 +114,7 @@ struct lin_layout {
   size_t dYp, rd, dHs, dXs, dlogit, dwr, hp8_ws, hp8_ws_bytes;
   // fp32 I/O in fixed point (pq_fixed.hip): a region of fx_bytes (0: the call has none) behind everything else, which only a backward
   // uses, and only if the workspace holds it
-  size_t fx_drow, fx_rexp, fx_dcol, fx_cexp, fx_qT, fx_colmax, fx_counts, fx_red_b, fx_planes, fx_bytes;
+  size_t fx_drow, fx_rexp, fx_dcol, fx_cexp, fx_qT, fx_colmax, fx_counts, fx_red_b, fx_signs, fx_SW, fx_SX, fx_bytes;
   int n_red_a, n_red_b;
 };
 
@@ -127,7 +127,6 @@ struct cursor {
   }
 };
 
-inline int fixed_Tp(int T) { return (T + 15) / 16 * 16; }
 // The two large contractions of the fp32 backward in fixed point: seven int8 products of one in fp64, a quarter of its time, but five
 // more launches (some 20 us) and 56 bytes of planes per output and 22 of digits per element of dY, written and read, i.e. 56 (1 / d_out +
 // 1 / tokens) + 22 / d_in bytes per product.  Backward against the fp64 products, 49 shapes of 64 to 65536 tokens and widths of 128 to 16384:
@@ -219,14 +218,18 @@ lin_layout make_layout(const pq_linear_desc& d) {
   }
   L.ws_base = L.ws_total = w.off;
   if (!bf16 && d.w_kind == PQ_W_MASTER && Ni % 32 == 0 && fixed_applies(Ti, Ki, Ni)) {   // (what a backward takes)
-    const size_t Tp = fixed_Tp(Ti), pl = PQ_FIXED_DIGITS * K * (T > N ? T : N) * sizeof(int);   // (dW's planes, then dX's)
+    const size_t T64 = pq_align_up(T, 64), N64 = pq_align_up(N, 64), Kp = pq_align_up(K, PQ_FIXED_N);
     cursor x;
-    L.fx_drow = x.take(PQ_FIXED_DIGITS * T * N); L.fx_rexp = x.take(T * sizeof(int));
-    L.fx_dcol = x.take(PQ_FIXED_DIGITS * N * Tp); L.fx_cexp = x.take(N * sizeof(int));
-    L.fx_qT = x.take(K * Tp); L.fx_colmax = x.take(pq_fixed_max_rows(Ti) * N * sizeof(uint32_t));
+    L.fx_drow = x.take(PQ_FIXED_DIGITS * T64 * N64); L.fx_rexp = x.take(T * sizeof(int));
+    L.fx_dcol = x.take(PQ_FIXED_DIGITS * N64 * T64); L.fx_cexp = x.take(N * sizeof(int));
+    L.fx_qT = x.take(Kp * T64); L.fx_signs = x.take(Kp * N64);
+    L.fx_colmax = x.take(pq_fixed_max_rows(Ti) * N * sizeof(uint32_t));
     L.fx_counts = x.take((2 * N + K) * sizeof(int));
     L.fx_red_b = x.take(sizeof(double) * (size_t)pq_ref_red_blocks(Ni, Ki, -1));
-    L.fx_planes = x.take(pl);
+    L.fx_SW = x.take(N * K * sizeof(double)); L.fx_SX = x.take(T * K * sizeof(double));
+    // (the region is never smaller than 14 T N + K T + 28 K max(T, N) bytes, what callers have sized it by)
+    const size_t least = 14 * T * N + K * T + 28 * K * (T > N ? T : N);
+    if (x.off < least) x.take(least - x.off);
     if (x.off <= FIXED_MAX_BYTES) {
       L.fx_bytes = x.off;
       L.ws_total += x.off;
@@ -660,16 +663,13 @@ static int linear_bwd_f32(const pq_linear_desc* d, const lin_layout& L, const vo
   void* dH = ws + L.dH;
   pq_ref_problem p[PQ_REF_MAX];
   int n = 0;
-  int* planes = fx ? (int*)(fx + L.fx_planes) : nullptr;
-  const int Tp = fixed_Tp(T);
-  if (fx) {                          // (dY / gamma)^T q: the digits of dY's columns, one behind the other, times q
-    if (int err = pq_launch_fixed_split((const float*)dY, (const float*)(cx + L.gamma), (const int8_t*)(cx + L.Xq), T, Tp, N, K, (int8_t*)(fx + L.fx_drow),
-                                        (int*)(fx + L.fx_rexp), (int8_t*)(fx + L.fx_dcol), (int*)(fx + L.fx_cexp), (int8_t*)(fx + L.fx_qT),
-                                        (uint32_t*)(fx + L.fx_colmax), (int*)(fx + L.fx_counts), s)) return err;
-    pq_epilogue e = epi_zero();
-    e.C = planes; e.ldc = K; e.out_kind = PQ_OUT_I32;
-    if (int err = pq_launch_gemm(PQ_FIXED_DIGITS * N, K, Tp, {fx + L.fx_dcol, Tp, PQ_SRC_KC8, nullptr}, {fx + L.fx_qT, Tp, PQ_SRC_KC8, nullptr}, e, s,
-                                 PQP_GEMM_DW)) return err;
+  double *SW = fx ? (double*)(fx + L.fx_SW) : nullptr, *SX = fx ? (double*)(fx + L.fx_SX) : nullptr;
+  if (fx) {                          // dY S and (dY / gamma)^T q from the digits of dY's rows and columns
+    int8_t *drow = (int8_t*)(fx + L.fx_drow), *dcol = (int8_t*)(fx + L.fx_dcol), *qT = (int8_t*)(fx + L.fx_qT), *signs = (int8_t*)(fx + L.fx_signs);
+    int *rexp = (int*)(fx + L.fx_rexp), *cexp = (int*)(fx + L.fx_cexp);
+    if (int err = pq_launch_fixed_split((const float*)dY, (const float*)(cx + L.gamma), (const int8_t*)(cx + L.Xq), T, N, K, drow, rexp, dcol, cexp, qT,
+                                        (uint32_t*)(fx + L.fx_colmax), (int*)(fx + L.fx_counts), (const uint32_t*)(cx + L.Pt), signs, s)) return err;
+    if (int err = pq_launch_fixed_products(drow, rexp, signs, SX, dcol, cexp, qT, SW, T, N, K, s)) return err;
   }
   auto add_dW = [&] {  // dW = beta * dY^T (q / gamma)  [masked];  d beta = lambda * sum S .* (dY^T (q / gamma))
     pq_epilogue e = epi_zero();
@@ -678,7 +678,7 @@ static int linear_bwd_f32(const pq_linear_desc* d, const lin_layout& L, const vo
     if (d->ste_mode == PQ_STE_CLIP) { e.maskW = W; e.mu_dev = mulam; e.tau = d->ste_tau; }
     p[n] = ref_problem(fx ? PQ_REF_SUM_SS8 : PQ_REF_SS8, N, K, T, {dY, N, PQ_SRC_KS32, nullptr},
                        {cx + L.Xq, K, PQ_SRC_KS8, (const float*)(cx + L.gamma)}, e);
-    p[n].planes = planes; p[n].exps = fx ? (const int*)(fx + L.fx_cexp) : nullptr;
+    p[n].sums = SW; p[n].exps = fx ? (const int*)(fx + L.fx_cexp) : nullptr;
     p[n].counts = fx ? (const int*)(fx + L.fx_counts) : nullptr;
     ++n;
   };
@@ -693,12 +693,6 @@ static int linear_bwd_f32(const pq_linear_desc* d, const lin_layout& L, const vo
   }
   if (fx) add_dW();
   if (int err = pq_launch_ref(p, n, nullptr, 0, s, PQP_GEMM_DW)) return err;
-  if (fx) {                          // dY S: the digits of dY's rows, one behind the other, times the signs
-    pq_epilogue e = epi_zero();
-    e.C = planes; e.ldc = K; e.out_kind = PQ_OUT_I32;
-    if (int err = pq_launch_gemm(PQ_FIXED_DIGITS * T, K, N, {fx + L.fx_drow, N, PQ_SRC_KC8, nullptr}, {cx + L.Pt, N / 8, PQ_SRC_BITS8, nullptr}, e, s,
-                                 PQP_GEMM_DX)) return err;
-  }
   const pq_reduce_job jobs[2] = {{red_a, (T > 0 && r > 0) ? pq_ref_red_blocks(T, r, N) : 0, 1.0f, nullptr, dalpha_dbeta},
                                  {red_b, fx ? pq_ref_red_blocks(N, K, -1) : L.n_red_b, 1.0f, mulam + 1, dalpha_dbeta + 1}};
   n = 0;
@@ -706,7 +700,7 @@ static int linear_bwd_f32(const pq_linear_desc* d, const lin_layout& L, const vo
     pq_epilogue e = epi_zero();
     e.C = dX; e.ldc = K;
     p[n] = ref_problem(fx ? PQ_REF_SUM_CBITS : PQ_REF_CBITS, T, K, N, {dY, N, PQ_SRC_KC32, nullptr}, {cx + L.Pt, N / 8, PQ_SRC_BITSF, nullptr}, e);
-    p[n].planes = planes; p[n].exps = fx ? (const int*)(fx + L.fx_rexp) : nullptr;
+    p[n].sums = SX; p[n].exps = fx ? (const int*)(fx + L.fx_rexp) : nullptr;
     p[n].scale1 = d->beta; p[n].dev_scale1 = mulam + 1;
     if (r > 0) { p[n].K2 = r; p[n].A2 = pq_operand{dH, r, PQ_SRC_KC32, nullptr}; p[n].B2 = pq_operand{hpA, K, PQ_SRC_KS32, nullptr}; }
     ++n;

@@ -24,7 +24,8 @@
 // a marked row reaches as the fp64 product it stands for.  Step of 2048 tokens 2048x2048 (us): finite 300; one NaN in dY 443; an infinity in X, which marks every
 // row of dW, 604 (one element after the other: 1115 and 5368; fp64 products alone 600).
 #include <string.h>
-#include "pq_internal.h"
+#include <type_traits>
+#include "pq_epilogue.h"
 
 namespace {
 
@@ -32,6 +33,7 @@ constexpr int ND = PQ_FIXED_DIGITS;
 constexpr int COLT = 128;                            // tokens per workgroup of the column pass
 constexpr int SMALL = 37;                            // digits below 2^37: elements below 2^(E - 17)
 constexpr int ROWS = 8;                              // rows of dY per workgroup of the row pass, four to a half of it
+constexpr int FXM = PQ_FIXED_M, FXN = PQ_FIXED_N;    // the products' tiles
 
 // 1 / gamma in fp64, as the fp64 products form it (pq_ref.hip)
 __device__ __forceinline__ double recip(float g) {
@@ -69,12 +71,29 @@ __device__ __forceinline__ int exp_f32(uint32_t u) { return u >= 0x7F800000u ? P
 // the same from the upper half of a double's bits
 __device__ __forceinline__ int exp_f64(uint32_t u) { return u >= 0x7FF00000u ? PQ_FIXED_NOT_FINITE : max((int)(u >> 20), 1) - 1022; }
 
-// Rows of dY: digits [ND][T][N] and exponents [T]; colmax [ceil(T / ROWS)][N]: the largest |dY / gamma| of the workgroup's rows, as
+// What the products read lies in memory as the tiles that they stream: panels of FXM rows (digits) or FXN rows (signs, codes), stages of 64
+// contraction indices, and in a stage [digit][row][64 B] with the row's 16-byte chunks swizzled, so that every direct load is 1 KB of
+// consecutive memory and lands where the operand reads want it.  (As plain rows the loads took 64 bytes of sixteen rows: 103 us for the
+// stream of 2048 tokens 2048x2048 alone; and the column pass below stored 16-byte pieces a row apart.)  Bytes of chunk c of row r:
+__device__ __forceinline__ int tile_off(int r, int c) { return r * 64 + (((c ^ (r >> 1) ^ (r >> 3)) & 3) << 4); }
+
+// Rows of dY: digits (panels of 64 tokens) and exponents [T]; colmax [ceil(T / ROWS)][N]: the largest |dY / gamma| of the workgroup's rows, as
 // the upper half of the double.  counts: cleared for the column pass.
 __global__ __launch_bounds__(512) void fixed_rows_kernel(const float* __restrict__ dY, const float* __restrict__ gamma, int T, int N,
                                                          int8_t* __restrict__ D, int* __restrict__ rexp, uint32_t* __restrict__ colmax,
-                                                         int* __restrict__ counts, int ncounts) {
-  for (int i = blockIdx.x * 512 + threadIdx.x; i < ncounts; i += gridDim.x * 512) counts[i] = 0;
+                                                         int* __restrict__ counts, int ncounts, const uint16_t* __restrict__ bits,
+                                                         int8_t* __restrict__ signs, int K, int nrow) {
+  const int nk = (N + 63) >> 6;                      // stages of a contraction over the columns
+  if ((int)blockIdx.x >= nrow) {                     // uniform: the packed signs [K][N] as bytes, a chunk per thread and turn, zeros behind a row's end
+    const size_t total = (size_t)K * nk * 4;
+    for (size_t i = (size_t)((int)blockIdx.x - nrow) * 512 + threadIdx.x; i < total; i += (size_t)((int)gridDim.x - nrow) * 512) {
+      const int k = (int)(i / (unsigned)(nk * 4)), ch = (int)(i - (size_t)k * (nk * 4));
+      const i32x4_t o = ch * 16 < N ? pq_bits_to_i8(bits[(size_t)k * (N >> 4) + ch]) : i32x4_t{0, 0, 0, 0};
+      *reinterpret_cast<i32x4_t*>(signs + ((size_t)(k / FXN) * nk + (ch >> 2)) * (FXN * 64) + tile_off(k % FXN, ch & 3)) = o;
+    }
+    return;
+  }
+  for (int i = blockIdx.x * 512 + threadIdx.x; i < ncounts; i += nrow * 512) counts[i] = 0;
   constexpr int R = ROWS / 2;
   __shared__ uint32_t wmax[8][R];
   __shared__ uint4 cmax[256];
@@ -136,7 +155,8 @@ __global__ __launch_bounds__(512) void fixed_rows_kernel(const float* __restrict
       uint32_t o[ND];
       planes_of(w, o);
 #pragma unroll
-      for (int d = 0; d < ND; ++d) *reinterpret_cast<uint32_t*>(D + ((size_t)d * T + t0 + r) * N + c) = o[d];
+      for (int d = 0; d < ND; ++d)
+        *reinterpret_cast<uint32_t*>(D + (((size_t)((t0 + r) / FXM) * nk + (c >> 6)) * ND + d) * (FXM * 64) + tile_off((t0 + r) % FXM, (c >> 4) & 3) + (c & 15)) = o[d];
     }
   }
 }
@@ -163,8 +183,8 @@ __global__ __launch_bounds__(1024) void fixed_exps_kernel(const uint32_t* __rest
   cexp[n] = exp_f64(m);
 }
 
-// Columns of dY / gamma over the tokens: digits [ND][N][Tp]; and q transposed, [K][Tp].  Tp: T rounded up to whole
-// 16 bytes, the rest zero.  counts: small elements [N], zero ones [N], zero codes [K].  Workgroups (column block, token block of COLT): N / 64 of digits, then K / 256 of codes.
+// Columns of dY / gamma over the tokens: digits (panels of 64 columns); and q transposed (panels of 128 channels).  Tp: T rounded up to
+// whole stages, the rest zero.  counts: small elements [N], zero ones [N], zero codes [K].  Workgroups (column block, token block of COLT): N / 64 of digits, then K / 256 of codes.
 __global__ __launch_bounds__(256) void fixed_cols_kernel(const float* __restrict__ dY, const float* __restrict__ gamma, const int8_t* __restrict__ q,
                                                          int T, int Tp, int N, int K, const int* __restrict__ cexp, int8_t* __restrict__ D,
                                                          int8_t* __restrict__ qT, int* __restrict__ counts, int nblk) {
@@ -184,8 +204,9 @@ __global__ __launch_bounds__(256) void fixed_cols_kernel(const float* __restrict
         uint32_t o[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[i >> 2] |= (t0 + i < T ? (w[i] >> (8 * j)) & 0xFFu : 0u) << (8 * (i & 3));
-        *reinterpret_cast<uint4*>(qT + (size_t)(k + j) * Tp + t0) = make_uint4(o[0], o[1], o[2], o[3]);
-        int z = -max(t0 + 16 - T, 0);                // (not the padding)
+        *reinterpret_cast<uint4*>(qT + ((size_t)((k + j) / FXN) * (Tp >> 6) + (t0 >> 6)) * (FXN * 64) + tile_off((k + j) % FXN, (t0 >> 4) & 3)) =
+            make_uint4(o[0], o[1], o[2], o[3]);
+        int z = -min(max(t0 + 16 - T, 0), 16);       // (not the padding)
 #pragma unroll
         for (int i = 0; i < 4; ++i) z += __builtin_popcount(~(((o[i] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | o[i] | 0x7F7F7F7Fu));
         atomicAdd(&zero_codes[4 * lane + j], z);
@@ -224,25 +245,252 @@ __global__ __launch_bounds__(256) void fixed_cols_kernel(const float* __restrict
     }
 #pragma unroll
     for (int d = 0; d < ND; ++d)
-      *reinterpret_cast<uint4*>(D + ((size_t)d * N + n) * Tp + t0) = make_uint4(o[0][d], o[1][d], o[2][d], o[3][d]);
+      *reinterpret_cast<uint4*>(D + (((size_t)blockIdx.x * (Tp >> 6) + (t0 >> 6)) * ND + d) * (FXM * 64) + tile_off(lane, (t0 >> 4) & 3)) =
+          make_uint4(o[0][d], o[1][d], o[2][d], o[3][d]);
   }
   if (small > 0) atomicAdd(counts + n, small);       // (rare on both counts)
   if (zero > 0) atomicAdd(counts + N + n, zero);
+}
+
+// ---------------------------------------------------------------------------------------------
+// The sums of the digit products: S[m][n] = sum_d 256^d (sum_k A_d(m,k) B(n,k)) 2^(E_m - 54) (A_d: the d-th digits of dY's rows or
+// columns; B: signs or transposed codes).
+// ---------------------------------------------------------------------------------------------
+// A wavefront multiplies 32 rows of all seven digits with 64 columns: fourteen 32x32 blocks of int32 sums (224 AGPRs, one wavefront
+// per SIMD), which meet in fp64 in its own registers.  As one product of 7 M rows with its int32 planes in memory the same work wrote and
+// read 56 bytes per output and fetched the operand B once per digit; here a B operand read from LDS serves seven MFMAs (nine operand
+// reads to fourteen MFMAs) and an output leaves as 8 bytes.  A workgroup is 64x128 outputs on four wavefronts (2 x 2); a stage is 64
+// contraction indices (36 KB), the ring has four.  The order of a stage is fixed, as in the weight-gradient products: behind the MFMAs of
+// the first half go the operand reads of the second, then the barrier, then the direct loads of the stage three ahead; behind those of
+// the second half the operand reads of the next stage, which that barrier has let in.
+// One workgroup per CU walks over tiles, and its loads run on into the next tile: the conversion and the stores of a tile (6 us where a
+// tile was a workgroup, against 19 of MFMAs) have the next one's first three stages under way.
+constexpr int FX_A = ND * FXM * 64, FX_STAGE = FX_A + FXN * 64, FX_OUT = 4096;   // bytes of a stage, and of a wavefront's share of the output's patch
+
+struct fixed_product {
+  const int8_t* A;      // [M / 64][nkt][ND][64][64 B]
+  const int8_t* B;      // [N / 128][nkt][128][64 B]
+  const int* exps;      // [M]
+  double* S;            // [M][N]
+  int M, N, nkt, nbn;
+};
+
+#define FX_MFMA(acc, a, b) asm volatile("v_mfma_i32_32x32x32_i8 %0, %2, %1, %0" : "+a"(acc) : "v"(a), "v"(b))
+#define FX_MFMA0(acc, a, b) asm volatile("v_mfma_i32_32x32x32_i8 %0, %2, %1, 0" : "=a"(acc) : "v"(a), "v"(b))
+#define FX_READ(dst, addr, off) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(off) : "memory")
+struct fixed_frags {
+  i32x4_t q[ND + 2];    // the digits' operands, then the two of B
+  __device__ __forceinline__ void wait_all() {
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]), "+v"(q[4]), "+v"(q[5]), "+v"(q[6]), "+v"(q[7]), "+v"(q[8]));
+  }
+};
+
+__global__ __launch_bounds__(256, 1) void fixed_gemm_kernel(fixed_product p0, fixed_product p1, int tiles0, int tiles) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  static_assert(ND == 7 && FXM == 64 && FXN == 128, "nine load instructions per wavefront and stage");
+  constexpr int IPS = FX_STAGE / 4096;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[4 * FX_STAGE + 4 * FX_OUT];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wv >> 1, wn = wv & 1;
+  // tiles of this workgroup: every gridDim.x-th; of each round an XCD (workgroups c, c + 8, ..) takes consecutive ones
+  const int per = (int)gridDim.x >> 3;
+  const int tile_first = ((int)gridDim.x & 7) == 0 ? ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
+  if (tile_first >= tiles) return;                              // uniform
+
+  // ---- the load stream: stage after stage, tile after tile ----
+  const int8_t *la, *lb;                                        // of the next stage to request
+  int lt = tile_first, lk = 0, lnkt = 0;
+  auto load_tile = [&] {
+    const bool sec = lt >= tiles0;
+    const int t = sec ? lt - tiles0 : lt, nbn = sec ? p1.nbn : p0.nbn;
+    lnkt = sec ? p1.nkt : p0.nkt;
+    la = (sec ? p1.A : p0.A) + (size_t)(t / nbn) * lnkt * FX_A;
+    lb = (sec ? p1.B : p0.B) + (size_t)(t % nbn) * lnkt * (FXN * 64);
+  };
+  load_tile();
+  auto issue1 = [&](int slot, int i) {
+    const int qi = wv * IPS + i;                                // 1 KB block of the stage
+    const int8_t* g = (qi < ND * 4 ? la + qi * 1024 : lb + (qi - ND * 4) * 1024) + lane * 16;
+    __builtin_amdgcn_global_load_lds(g, PQ_LDS_PTR(smem + slot * FX_STAGE + qi * 1024), 16, 0, 0);
+  };
+  auto advance = [&] {                                          // past the last stage: it again, into a slot nobody reads
+    if (++lk < lnkt) {
+      la += FX_A;
+      lb += FXN * 64;
+    } else if (lt + (int)gridDim.x < tiles) {
+      lt += (int)gridDim.x;
+      lk = 0;
+      load_tile();
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < 3; ++u) {
+#pragma unroll
+    for (int i = 0; i < IPS; ++i) issue1(u, i);
+    advance();
+  }
+
+  // operand reads (slot 0): lane l takes row l & 31, chunk 2 ks + (l >> 5); 32 rows further the swizzle is the same
+  const uint32_t lds0 = (uint32_t)(size_t)smem;
+  uint32_t adA[2], adB[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const int o = tile_off(lane & 31, 2 * ks + (lane >> 5));
+    adA[ks] = lds0 + wm * 2048 + o;
+    adB[ks] = lds0 + FX_A + wn * 4096 + o;
+  }
+  fixed_frags F0, F1;
+  auto rd = [&](fixed_frags& F, int n, uint32_t so, int ks) {   // B first: every MFMA needs one of them
+    if (n < 2) {
+      const uint32_t pb = adB[ks] + so;
+      if (n == 0) FX_READ(F.q[ND], pb, 0);
+      else FX_READ(F.q[ND + 1], pb, 2048);
+    } else {
+      const uint32_t pa = adA[ks] + so;
+      switch (n - 2) {                                          // (constant after unrolling)
+        case 0: FX_READ(F.q[0], pa, 0); break;
+        case 1: FX_READ(F.q[1], pa, 4096); break;
+        case 2: FX_READ(F.q[2], pa, 8192); break;
+        case 3: FX_READ(F.q[3], pa, 12288); break;
+        case 4: FX_READ(F.q[4], pa, 16384); break;
+        case 5: FX_READ(F.q[5], pa, 20480); break;
+        default: FX_READ(F.q[6], pa, 24576);
+      }
+    }
+  };
+  i32x16_t acc[ND][2];
+  auto mf = [&acc](const fixed_frags& X, int n, auto first_c) {    // an operand of A stays for two MFMAs
+    const int d = n >> 1, j = (n & 1) ^ (d & 1);
+    if constexpr (decltype(first_c)::value) FX_MFMA0(acc[d][j], X.q[d], X.q[ND + j]);
+    else FX_MFMA(acc[d][j], X.q[d], X.q[ND + j]);
+  };
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+  for (int n = 0; n < ND + 2; ++n) rd(F0, n, 0u, 0);
+
+  int slot = 0;
+  for (int tile = tile_first; tile < tiles; tile += (int)gridDim.x) {
+    const bool sec = tile >= tiles0;                            // uniform
+    const int nkt = sec ? p1.nkt : p0.nkt;
+    for (int kt = 0; kt < nkt; ++kt) {
+      const uint32_t so = (uint32_t)slot * FX_STAGE, sn = (uint32_t)((slot + 1) & 3) * FX_STAGE;
+      const int sl = (slot + 3) & 3;
+      F0.wait_all();
+      auto half = [&](auto first_c) {
+#pragma unroll
+        for (int n = 0; n < ND; ++n) {
+          mf(F0, n, first_c);
+          rd(F1, n, so, 1);
+          if (n < 2) rd(F1, n + ND, so, 1);
+        }
+        // The wavefront's own loads of the next stage have landed.  (At a tile's start there are three stages that the end of the
+        // tile before, or the start, has waited for, and stores behind them that nothing here need wait for.)
+        if constexpr (!decltype(first_c)::value)
+          if (kt > 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(IPS) : "memory");
+        asm volatile("s_barrier" ::: "memory");                 // everybody's have; nobody reads the stage before this one any more
+#pragma unroll
+        for (int n = ND; n < 2 * ND; ++n) {
+          mf(F0, n, first_c);
+          issue1(sl, n - ND);
+          if (n < ND + 2) issue1(sl, n);
+        }
+      };
+      if (kt == 0) half(std::true_type{});
+      else half(std::false_type{});
+      advance();
+      F1.wait_all();
+#pragma unroll
+      for (int n = 0; n < 2 * ND; ++n) {
+        mf(F1, n, std::false_type{});
+        if (n < ND + 2) rd(F0, n, sn, 0);                       // past the last stage: a slot nobody uses
+      }
+      slot = (slot + 1) & 3;
+    }
+    // (an asm MFMA's registers may be read when the matrix pipe has written them: the compiler does not know)
+    asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) asm volatile("" : "+a"(acc[d][j]));
+
+    // In a block lane l holds row l & 31, register v column 8 (v >> 2) + 4 (l >> 5) + (v & 3).  Sixteen columns at a time pass through
+    // the wavefront's patch, [32 rows][128 B], and leave as whole lines.
+    const fixed_product& p = sec ? p1 : p0;
+    const int t = sec ? tile - tiles0 : tile;
+    const int m0 = t / p.nbn * FXM + wm * 32, n0 = t % p.nbn * FXN + wn * 64;
+    const int row = lane & 31;
+    const int e = p.exps[min(m0 + row, p.M - 1)];
+    const double sc = e == PQ_FIXED_NOT_FINITE ? 0.0 : ldexp(1.0, e - 54);
+    unsigned char* const mine = smem + 4 * FX_STAGE + wv * FX_OUT;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {                               // columns 16 c .. 16 c + 15
+      double2 o[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const int j = c >> 1, v = 8 * (c & 1) + 2 * x;
+        double s[2] = {0.0, 0.0};
+#pragma unroll
+        for (int d = ND - 1; d >= 0; --d)
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const int a = acc[d][j][v + u];
+            s[u] = __builtin_fma(s[u], 256.0, (double)a);
+          }
+        o[x] = make_double2(s[0] * sc, s[1] * sc);
+      }
+      if (c == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the next tile's stages, ahead of the stores
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const int ch = (x >> 1) * 4 + (lane >> 5) * 2 + (x & 1);     // 16-byte chunk of the row's 128 bytes
+        *reinterpret_cast<double2*>(mine + row * 128 + ((ch ^ (row & 7)) << 4)) = o[x];
+      }
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int it = 0; it < 4; ++it) {
+        const int r = it * 8 + (lane >> 3), ch = lane & 7;
+        const double2 w = *reinterpret_cast<const double2*>(mine + r * 128 + ((ch ^ (r & 7)) << 4));
+        const int m = m0 + r, n = n0 + c * 16 + ch * 2;
+        if (m < p.M && n < p.N) *reinterpret_cast<double2*>(p.S + (size_t)m * p.N + n) = w;   // (N is even)
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
 }
 
 }  // namespace
 
 int pq_fixed_max_rows(int T) { return (T + ROWS - 1) / ROWS; }
 
-int pq_launch_fixed_split(const float* dY, const float* gamma, const int8_t* q, int T, int Tp, int N, int K, int8_t* Drow, int* rexp, int8_t* Dcol,
-                          int* cexp, int8_t* qT, uint32_t* colmax, int* counts, hipStream_t s) {
+int pq_launch_fixed_split(const float* dY, const float* gamma, const int8_t* q, int T, int N, int K, int8_t* Drow, int* rexp, int8_t* Dcol,
+                          int* cexp, int8_t* qT, uint32_t* colmax, int* counts, const uint32_t* Pt, int8_t* signs, hipStream_t s) {
   pq_prof_scope prof(PQP_QUANT, s);
-  fixed_rows_kernel<<<pq_fixed_max_rows(T), 512, 0, s>>>(dY, gamma, T, N, Drow, rexp, colmax, counts, 2 * N + K);
+  const int nrow = pq_fixed_max_rows(T), Tp = (T + 63) / 64 * 64;
+  const size_t chunks = (size_t)K * ((N + 63) / 64) * 4;
+  const int nsign = (int)((chunks + 2047) / 2048 < 1024 ? (chunks + 2047) / 2048 : 1024);
+  fixed_rows_kernel<<<nrow + nsign, 512, 0, s>>>(dY, gamma, T, N, Drow, rexp, colmax, counts, 2 * N + K, (const uint16_t*)Pt, signs, K, nrow);
   PQ_CHECK_LAUNCH("fixed_rows_kernel");
   const int nblk = (N + 63) / 64;
   fixed_exps_kernel<<<nblk, 1024, 0, s>>>(colmax, pq_fixed_max_rows(T), N, cexp);
   PQ_CHECK_LAUNCH("fixed_exps_kernel");
   fixed_cols_kernel<<<dim3(nblk + (K + 255) / 256, (Tp + COLT - 1) / COLT), 256, 0, s>>>(dY, gamma, q, T, Tp, N, K, cexp, Dcol, qT, counts, nblk);
   PQ_CHECK_LAUNCH("fixed_cols_kernel");
+  return PQ_OK;
+}
+
+int pq_launch_fixed_products(const int8_t* Drow, const int* rexp, const int8_t* signs, double* SX, const int8_t* Dcol, const int* cexp, const int8_t* qT,
+                             double* SW, int T, int N, int K, hipStream_t s) {
+  if (T <= 0 || N <= 0 || N % 32 != 0 || K <= 0 || K % 32 != 0) return pq_set_error(PQ_ERR_SHAPE, "digit products: T=%d d_in=%d d_out=%d", T, K, N);
+  pq_prof_scope prof(PQP_GEMM_DX, s);
+  const int nbn = (K + FXN - 1) / FXN;
+  const fixed_product x{Drow, signs, rexp, SX, T, K, (N + 63) / 64, nbn}, w{Dcol, qT, cexp, SW, N, K, (T + 63) / 64, nbn};
+  const int tx = (T + FXM - 1) / FXM * nbn, tw = (N + FXM - 1) / FXM * nbn, tiles = tx + tw;
+  const bool w_first = T >= N;                       // the longer contraction first
+  fixed_gemm_kernel<<<tiles < 256 ? tiles : 256, 256, 0, s>>>(w_first ? w : x, w_first ? x : w, w_first ? tw : tx, tiles);
+  PQ_CHECK_LAUNCH("fixed_gemm_kernel");
   return PQ_OK;
 }

@@ -231,7 +231,7 @@ enum pq_ref_form {
                       // (scale1 [* *dev_scale1]) * sum_k A B + sum_k2 A2 B2
   PQ_REF_SS8 = 3,     // A KS32, B KS8 divided by its kdiv
   PQ_REF_SS = 4,      // A KS32, B KS32
-  // the same with the first contraction already done in fixed point (pq_fixed.hip): its sums are read from `planes` and A, B are
+  // the same with the first contraction already done in fixed point (pq_fixed.hip): its sums are read from `sums` and A, B are
   // looked at only for tiles with rows that are not finite or sums that their elements' range leaves out
   PQ_REF_SUM_CBITS = 5,
   PQ_REF_SUM_SS8 = 6
@@ -241,9 +241,9 @@ struct pq_ref_problem {
   pq_operand A, B, A2, B2;
   float scale1;
   const float* dev_scale1;
-  const int* planes;            // SUM forms: [PQ_FIXED_DIGITS][M][N] int32 sums of the digit products, lowest digit first
+  const double* sums;           // SUM forms: [M][N] sums of the digit products
   const int* exps;              // ... and the rows' exponents
-  const int* counts;            // SUM_SS8: [2 M + N], what decides whether a sum may be taken from the planes (pq_fixed.hip)
+  const int* counts;            // SUM_SS8: [2 M + N], what decides whether a sum of digits may be taken (pq_fixed.hip)
   pq_epilogue epi;              // scale, dev_scale, accumulate, dot_comp, sign_bytes, partials and the clip mask; C is fp32
 };
 constexpr int PQ_REF_MAX = 3;
@@ -269,15 +269,20 @@ bool pq_ref_linear_applies(int T, int N, int K);
 int pq_launch_ref_linear(const pq_ref_linear& p, hipStream_t s);
 
 // ---- pq_fixed.hip -------------------------------------------------------------------------
-// Fixed-point form of dY for the two large contractions of the fp32 backward: row digits Drow [7][T][N] with exponents rexp [T],
-// digits of the columns of dY / gamma Dcol [7][N][Tp] with exponents cexp [N], q transposed qT [K][Tp]; Tp = T rounded up to a
-// multiple of 16.  colmax: [pq_fixed_max_rows(T)][N] words of scratch.  counts [2 N + K]: small and zero elements of the columns, zero
-// codes of the channels.
+// Fixed-point form of dY for the two large contractions of the fp32 backward: digits Drow of dY's rows with exponents rexp [T], digits
+// Dcol of the columns of dY / gamma with exponents cexp [N], the codes transposed (qT) and the signs as bytes (from Pt [K][N/32]), each in
+// the tiles that the products stream (pq_fixed.hip): rows rounded up to whole panels, PQ_FIXED_M of digits, PQ_FIXED_N of signs and codes,
+// the contraction to whole 64.  colmax: [pq_fixed_max_rows(T)][N] words of scratch.  counts [2 N + K]: small and zero elements of the
+// columns, zero codes of the channels.
 constexpr int PQ_FIXED_DIGITS = 7;
+constexpr int PQ_FIXED_M = 64, PQ_FIXED_N = 128;
 constexpr int PQ_FIXED_NOT_FINITE = 1 << 20;         // the exponent of a row with infinities or NaN (its digits are zero)
 int pq_fixed_max_rows(int T);
-int pq_launch_fixed_split(const float* dY, const float* gamma, const int8_t* q, int T, int Tp, int N, int K, int8_t* Drow, int* rexp, int8_t* Dcol,
-                          int* cexp, int8_t* qT, uint32_t* colmax, int* counts, hipStream_t s);
+int pq_launch_fixed_split(const float* dY, const float* gamma, const int8_t* q, int T, int N, int K, int8_t* Drow, int* rexp, int8_t* Dcol,
+                          int* cexp, int8_t* qT, uint32_t* colmax, int* counts, const uint32_t* Pt, int8_t* signs, hipStream_t s);
+// SX [T][K] = dY S and SW [N][K] = (dY / gamma)^T q from those digits
+int pq_launch_fixed_products(const int8_t* Drow, const int* rexp, const int8_t* signs, double* SX, const int8_t* Dcol, const int* cexp, const int8_t* qT,
+                             double* SW, int T, int N, int K, hipStream_t s);
 
 // ---- pq_decode.hip ------------------------------------------------------------------------
 size_t pq_decode_ws_layout(const pq_decode_desc& d, size_t* off);

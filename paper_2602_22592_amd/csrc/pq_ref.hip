@@ -243,13 +243,12 @@ __device__ __forceinline__ void ref_contract(const pq_operand& A, const pq_opera
   }
 }
 
-// The sums of a SUM form: sum_d 256^d acc_d 2^(E - 54), from the top digit down (a lane's two columns of a row are one load a plane).
+// The sums of a SUM form (a lane's two columns of a row are one load).
 // False for the whole wavefront when one of its rows has no digits, or (FORM SUM_SS8, see pq_fixed.hip) one of its sums may consist
 // of elements that the digits hold too coarsely: the tile is then to be formed as the fp64 product it stands for.
 template <int FORM>
-__device__ __forceinline__ bool ref_planes(const pq_ref_problem& p, int m0, int n0, int li, int lk, f64x4_t (&acc)[2][2]) {
+__device__ __forceinline__ bool ref_sums(const pq_ref_problem& p, int m0, int n0, int li, int lk, f64x4_t (&acc)[2][2]) {
   constexpr int NB = 2;
-  const size_t stride = (size_t)p.M * p.N;
   const int n = min(n0 + NB * li, p.N - NB);
   const int rm = min(m0 + ((int)threadIdx.x & 31), p.M - 1);
   bool leave = p.exps[rm] == PQ_FIXED_NOT_FINITE;
@@ -267,21 +266,9 @@ __device__ __forceinline__ bool ref_planes(const pq_ref_problem& p, int m0, int 
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int m = min(m0 + NB * (lk + 4 * v) + i, p.M - 1);
-      const int* src = p.planes + (size_t)m * p.N + n;
-      int x[PQ_FIXED_DIGITS][NB];
-#pragma unroll
-      for (int d = 0; d < PQ_FIXED_DIGITS; ++d) {
-        const int2 t = *reinterpret_cast<const int2*>(src + d * stride);
-        x[d][0] = t.x; x[d][1] = t.y;
-      }
-      const double sc = ldexp(1.0, p.exps[m] - 54);
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        double s = 0.0;
-#pragma unroll
-        for (int d = PQ_FIXED_DIGITS - 1; d >= 0; --d) s = __builtin_fma(s, 256.0, (double)x[d][j]);
-        acc[i][j][v] = s * sc;
-      }
+      const double2 t = *reinterpret_cast<const double2*>(p.sums + (size_t)m * p.N + n);
+      acc[i][0][v] = t.x;
+      acc[i][1][v] = t.y;
     }
   return true;
 }
@@ -313,7 +300,7 @@ __device__ __forceinline__ void ref_tile(const pq_ref_problem& p, int block, dou
   if (live) {
     bool contract = true;                                 // uniform
     if constexpr (SUM) {
-      contract = !ref_planes<FORM>(p, m0, n0, li, lk, acc);
+      contract = !ref_sums<FORM>(p, m0, n0, li, lk, acc);
       if (contract) clear();
     }
     if (contract) ref_contract<AK, BK, NB, DEPTH>(p.A, p.B, m0, p.M, n0, p.N, p.K, first, KS, li, lk, acc);
