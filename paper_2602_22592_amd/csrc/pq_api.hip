@@ -771,6 +771,8 @@ static int linear_bwd_impl(const pq_linear_desc* d, const void* dY, const void* 
     n_red_a = pq_plan_gemm(T, d->hp_rank, N).red_blocks;
     if (int e = hp_int8_dh(dY, T, N, d->hp_rank, d->alpha, cx + L.hp8, H8, ws + L.hp8_ws, red_a, s)) return e;
   }
+  pq_gemm_call set[2];
+  int n_set = 1;
   if (T > 0) {  // dX = beta*lambda * dY S  (+ dH A, fused into the same tile)
     pq_operand A{dY, N, PQ_SRC_KC16, nullptr};
     pq_operand B{cx + L.Pt, N / 8, PQ_SRC_BITS16, nullptr};
@@ -789,7 +791,10 @@ static int linear_bwd_impl(const pq_linear_desc* d, const void* dY, const void* 
       if (int err = pq_launch_gemm(T, K, N, A, B, e, s, PQP_GEMM_DX, sk_ws, nullptr, &p2)) return err;
     } else {
       e.scale = d->beta; e.dev_scale = mulam + 1;
-      if (int err = pq_launch_gemm(T, K, N, A, B, e, s, PQP_GEMM_DX, sk_ws)) return err;
+      if (r2 == 0) {                 // nothing between it and dW: they go together
+        set[1] = pq_gemm_call{T, K, N, A, B, e, nullptr, PQP_GEMM_DX};
+        n_set = 2;
+      } else if (int err = pq_launch_gemm(T, K, N, A, B, e, s, PQP_GEMM_DX, sk_ws)) return err;
       if (r2 > 0) {
         pq_operand A2{dH2, r2, PQ_SRC_KC16, nullptr};
         pq_operand B2{A2p, K, PQ_SRC_KS16, nullptr};
@@ -810,7 +815,10 @@ static int linear_bwd_impl(const pq_linear_desc* d, const void* dY, const void* 
     if (d->ste_mode == PQ_STE_CLIP) {
       e.maskW = W; e.mask_kind = ok; e.mu_dev = mulam; e.tau = d->ste_tau;
     }
-    if (int err = pq_launch_gemm(N, K, T, A, B, e, s, PQP_GEMM_DW, sk_ws)) return err;
+    set[0] = pq_gemm_call{N, K, T, A, B, e, nullptr, PQP_GEMM_DW};
+    if (n_set == 2) {
+      if (int err = pq_launch_gemm_set(set, 2, s, sk_ws)) return err;
+    } else if (int err = pq_launch_gemm(N, K, T, A, B, e, s, PQP_GEMM_DW, sk_ws)) return err;
   }
   if (routed) {
     // Sec. 3.3 backward: upstream of expert e's output for slot (t, j) is alpha gate_tj dY_t; the gate itself
@@ -835,27 +843,23 @@ static int linear_bwd_impl(const pq_linear_desc* d, const void* dY, const void* 
       g1.b_stride = (long)N * re;
       if (int err = pq_launch_gemm(S, re, N, A, B, e, s, PQP_GEMM_EXPERT, sk_ws, &g1)) return err;
     }
-    {  // per-expert weight gradients: the contraction runs over the expert's slots
-      pq_operand A{ws + L.dYp, N, PQ_SRC_KS16, nullptr};
-      pq_operand B{cx + L.Hs, re, PQ_SRC_KS16, nullptr};
+    // per-expert weight gradients (the contraction runs over the expert's slots), and dXs = dH_e A_e in slot order, which the
+    // combination scatters back with the router's share
+    pq_gemm_call c[3];
+    pq_gemm_group gB = g2, gA = g2;
+    {
       pq_epilogue e = epi_zero();
       e.C = dhpB; e.ldc = re; e.out_kind = PQ_OUT_F32;
-      g2.c_stride = (long)N * re;
-      if (int err = pq_launch_gemm(N, re, S, A, B, e, s, PQP_GEMM_EXPERT, sk_ws, &g2)) return err;
-      pq_operand A2{ws + L.dHs, re, PQ_SRC_KS16, nullptr};
-      pq_operand B2{cx + L.Xp, K, PQ_SRC_KS16, nullptr};
+      gB.c_stride = (long)N * re;
+      c[0] = pq_gemm_call{N, re, S, {ws + L.dYp, N, PQ_SRC_KS16, nullptr}, {cx + L.Hs, re, PQ_SRC_KS16, nullptr}, e, &gB, PQP_GEMM_EXPERT};
       e.C = dhpA; e.ldc = K;
-      g2.c_stride = (long)re * K;
-      if (int err = pq_launch_gemm(re, K, S, A2, B2, e, s, PQP_GEMM_EXPERT, sk_ws, &g2)) return err;
-    }
-    if (S > 0) {  // dXs = dH_e A_e (slot order), then scattered back with the router's share
-      pq_operand A{ws + L.dHs, re, PQ_SRC_KC16, nullptr};
-      pq_operand B{hpA, K, PQ_SRC_KS16, nullptr};
-      pq_epilogue e = epi_zero();
-      e.C = ws + L.dXs; e.ldc = K; e.out_kind = PQ_OUT_BF16;
+      gA.c_stride = (long)re * K;
+      c[1] = pq_gemm_call{re, K, S, {ws + L.dHs, re, PQ_SRC_KS16, nullptr}, {cx + L.Xp, K, PQ_SRC_KS16, nullptr}, e, &gA, PQP_GEMM_EXPERT};
+      e.C = ws + L.dXs; e.out_kind = PQ_OUT_BF16;
       g1.b_stride = (long)re * K;
-      if (int err = pq_launch_gemm(S, K, re, A, B, e, s, PQP_GEMM_EXPERT, sk_ws, &g1)) return err;
+      c[2] = pq_gemm_call{S, K, re, {ws + L.dHs, re, PQ_SRC_KC16, nullptr}, {hpA, K, PQ_SRC_KS16, nullptr}, e, &g1, PQP_GEMM_EXPERT};
     }
+    if (int err = pq_launch_gemm_set(c, 3, s, sk_ws)) return err;
     float* dlogit = (float*)(ws + L.dlogit);
     const pq_reduce_job rj[2] = {{red_a, n_red_a, 1.0f, nullptr, dalpha_dbeta}, {red_b, L.n_red_b, 1.0f, mulam + 1, dalpha_dbeta + 1}};
     if (int e = pq_launch_dwr(rd, inv, idx, (const float*)(cx + L.probs), d->alpha, k, dlogit, X, T, K, E, (float*)(ws + L.dwr), dWr, rj, s)) return e;

@@ -394,7 +394,6 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
   pq_gemm_group g1{offsets, E, 1, 0, 0, S};
   pq_gemm_group g2{offsets, E, 2, 0, 0, S};
   const pq_gemm_group* pg1 = one ? nullptr : &g1;
-  const pq_gemm_group* pg2 = one ? nullptr : &g2;
   if (S > 0) {  // da = dYp Down_e  (scaled by alpha*gate inside the activation backward)
     pq_operand A{dyp, D, PQ_SRC_KC16, nullptr};
     pq_operand B{Down, r, PQ_SRC_KS16, nullptr};
@@ -446,29 +445,30 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
     e.C = dW_up;
     if (int err = pq_launch_gemm_dual(F, D, T, A, B, e, A2, B, dW_gate, nullptr, s, PQP_GEMM_DW, sk)) return err;
   }
-  {  // per-expert weight gradients: contraction over the expert's slots
-    pq_operand A{dyp, D, PQ_SRC_KS16, nullptr};
-    pq_operand B{ws + L.as, r, PQ_SRC_KS16, nullptr};
+  // per-expert weight gradients, contractions over the expert's slots: dDown, and d[Up_e; Gate_e] = [du | dg]^T Xp, the halves of whose
+  // rows are stored to the caller's two gradients.  dXs = [du | dg] [Up_e; Gate_e] (INT8 experts: the de-quantised rows); a single
+  // branch's goes to dX itself.
+  pq_gemm_call c[3];
+  pq_gemm_group gD = g2, gU = g2;
+  {
     pq_epilogue e = epi0();
     e.C = dDown; e.ldc = r; e.out_kind = PQ_OUT_F32;
-    g2.c_stride = (long)D * r;
-    if (int err = pq_launch_gemm(D, r, S, A, B, e, s, PQP_GEMM_EXPERT, sk, pg2)) return err;
-    pq_operand Bx{xp, D, PQ_SRC_KS16, nullptr};
-    {   // d[Up_e; Gate_e] = [du | dg]^T Xp, the halves of its rows stored to the caller's two gradients
-      pq_operand Aug{ws + L.du, 2 * r, PQ_SRC_KS16, nullptr};
-      e.C = dUp; e.C2 = dGate; e.m_split = r; e.ldc = D;
-      g2.c_stride = (long)r * D;
-      if (int err = pq_launch_gemm(2 * r, D, S, Aug, Bx, e, s, PQP_GEMM_EXPERT, sk, pg2)) return err;
-    }
-  }
-  if (S > 0 && !fuse_dx) {  // dXs = [du | dg] [Up_e; Gate_e]  (INT8 experts: the de-quantised rows); a single branch's goes to dX itself
-    pq_operand A{ws + L.du, 2 * r, PQ_SRC_KC16, nullptr};
-    pq_operand B{hp8 ? cx + L.UGT : cx + L.UG, D, PQ_SRC_KS16, nullptr};
-    pq_epilogue e = epi0();
+    gD.c_stride = (long)D * r;
+    c[0] = pq_gemm_call{D, r, S, {dyp, D, PQ_SRC_KS16, nullptr}, {ws + L.as, r, PQ_SRC_KS16, nullptr}, e, one ? nullptr : &gD, PQP_GEMM_EXPERT};
+    e.C = dUp; e.C2 = dGate; e.m_split = r; e.ldc = D;
+    gU.c_stride = (long)r * D;
+    c[1] = pq_gemm_call{2 * r, D, S, {ws + L.du, 2 * r, PQ_SRC_KS16, nullptr}, {xp, D, PQ_SRC_KS16, nullptr}, e, one ? nullptr : &gU, PQP_GEMM_EXPERT};
+    e = epi0();
     e.C = one ? dX : ws + L.dXs; e.ldc = D; e.out_kind = PQ_OUT_BF16; e.accumulate = one ? 1 : 0;
     g1.b_stride = (long)2 * r * D;
-    if (int err = pq_launch_gemm(S, D, 2 * r, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
+    c[2] = pq_gemm_call{S, D, 2 * r, {ws + L.du, 2 * r, PQ_SRC_KC16, nullptr}, {hp8 ? cx + L.UGT : cx + L.UG, D, PQ_SRC_KS16, nullptr}, e, pg1,
+                        PQP_GEMM_EXPERT};
   }
+  if (S > 0 && !fuse_dx) {
+    if (int err = pq_launch_gemm_set(c, 3, s, sk)) return err;
+  } else
+    for (int i = 0; i < 2; ++i)
+      if (int err = pq_launch_gemm(c[i].M, c[i].N, c[i].K, c[i].A, c[i].B, c[i].epi, s, PQP_GEMM_EXPERT, sk, c[i].grp)) return err;
   if (one) return PQ_OK;   // softmax over one logit is constant: no gradient reaches the router
   float* dlogit = (float*)(ws + L.dlogit);
   if (int e = pq_launch_dwr(rd, inv, idx, (const float*)(cx + L.probs), d->alpha, k, dlogit, X, T, D, E, (float*)(ws + L.dwr), dWr, jobs, s)) return e;

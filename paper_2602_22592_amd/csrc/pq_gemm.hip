@@ -1998,17 +1998,8 @@ size_t pq_mode2_ws_bytes(int M, int N, int n_groups, int total_k) {
   return sp > 1 ? (size_t)sp * n_groups * M * N * sizeof(float) : 0;
 }
 
-int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B,
-                   const pq_epilogue& epi, hipStream_t s, int prof_label, pq_scratch sk,
-                   const pq_gemm_group* group, const pq_phase2* phase2) {
-  if (M <= 0 || N <= 0) return PQ_OK;
-  pq_gemm_group grp;
-  memset(&grp, 0, sizeof(grp));
-  if (group) grp = *group;
-  pq_phase2 ph2;
-  memset(&ph2, 0, sizeof(ph2));
-  if (phase2) ph2 = *phase2;
-  if (ph2.K2 > 0 && grp.mode) return pq_set_error(PQ_ERR_BAD_ARG, "a fused second contraction needs the plain MFMA engine");
+// what an epilogue asks for that no kernel does
+static int check_epilogue(int M, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi) {
   if ((epi.n_limit > 0 || epi.m_limit > 0) && (epi.accumulate || epi.maskW || epi.dot_comp || epi.n_limit % 4 != 0))
     return pq_set_error(PQ_ERR_BAD_ARG, "store limits go with plain stores and a column limit that is a multiple of 4");
   if (epi.m_split > 0 && (A.kind != PQ_SRC_KS16 || B.kind != PQ_SRC_KS16 || epi.out_kind != PQ_OUT_F32 || epi.accumulate || epi.maskW || epi.dot_comp ||
@@ -2017,10 +2008,12 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
   if (epi.C2 && epi.m_split == 0 && (A.kind != PQ_SRC_KC8 || B.kind != PQ_SRC_KC8 || epi.out_kind != PQ_OUT_BF16 || !epi.accumulate || epi.split_int8 ||
                                      epi.m_limit || epi.n_limit))
     return pq_set_error(PQ_ERR_BAD_ARG, "a copy of the value goes with int8 products that accumulate");
-  // plain rank-128 products over many rows: the streaming kernel (callers that want per-block partial sums or the
-  // slabs of a split contraction choose it themselves, since it changes how many of those there are)
-  if (!grp.mode && ph2.K2 == 0 && !epi.partials && !epi.defer_reduce && pq_skinny_applies(M, N, K, A, B, epi))
-    return pq_launch_skinny(M, K, A, B, epi, s, prof_label);
+  return PQ_OK;
+}
+
+// Tile, contraction split and scratch of a product; grp: plain (mode 0), row groups or contraction ranges.
+static pq_gemm_plan plan_call(int M, int N, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi, const pq_gemm_group& grp,
+                              pq_scratch sk) {
   const int ak = A.kind, bk = B.kind;
   const bool int8 = (ak == PQ_SRC_KC8);
   pq_gemm_plan pl = pq_plan_gemm(M, N, K, int8, epi.split_int8 != 0,
@@ -2070,6 +2063,42 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
       }
     }
   }
+  return pl;
+}
+
+// The sum of a split contraction's slabs.  raw_int: the slabs are int32 accumulators.
+static int reduce_call(int M, int N, const pq_epilogue& epi, const pq_gemm_group& grp, const pq_gemm_plan& pl, const float* part, bool raw_int,
+                       hipStream_t s) {
+  if (pl.splits > 1 && !epi.defer_reduce) {
+    pq_prof_scope prof(PQP_SPLITK_REDUCE, s);
+    const int Mred = grp.mode == 2 ? grp.n_groups * M : M;   // grouped ranges: the groups' outputs as one matrix
+    if (raw_int) splitk_reduce_kernel<true, false><<<pl.red_blocks, 256, 0, s>>>(Mred, N, pl.splits, part, epi);
+    else if (epi.m_split > 0) splitk_reduce_kernel<false, true><<<pl.red_blocks, 256, 0, s>>>(Mred, N, pl.splits, part, epi);
+    else splitk_reduce_kernel<false, false><<<pl.red_blocks, 256, 0, s>>>(Mred, N, pl.splits, part, epi);
+    PQ_CHECK_LAUNCH("splitk_reduce_kernel");
+  }
+  return PQ_OK;
+}
+
+int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B,
+                   const pq_epilogue& epi, hipStream_t s, int prof_label, pq_scratch sk,
+                   const pq_gemm_group* group, const pq_phase2* phase2) {
+  if (M <= 0 || N <= 0) return PQ_OK;
+  pq_gemm_group grp;
+  memset(&grp, 0, sizeof(grp));
+  if (group) grp = *group;
+  pq_phase2 ph2;
+  memset(&ph2, 0, sizeof(ph2));
+  if (phase2) ph2 = *phase2;
+  if (ph2.K2 > 0 && grp.mode) return pq_set_error(PQ_ERR_BAD_ARG, "a fused second contraction needs the plain MFMA engine");
+  if (int rc = check_epilogue(M, A, B, epi)) return rc;
+  // plain rank-128 products over many rows: the streaming kernel (callers that want per-block partial sums or the
+  // slabs of a split contraction choose it themselves, since it changes how many of those there are)
+  if (!grp.mode && ph2.K2 == 0 && !epi.partials && !epi.defer_reduce && pq_skinny_applies(M, N, K, A, B, epi))
+    return pq_launch_skinny(M, K, A, B, epi, s, prof_label);
+  const int ak = A.kind, bk = B.kind;
+  const bool int8 = (ak == PQ_SRC_KC8);
+  const pq_gemm_plan pl = plan_call(M, N, K, A, B, epi, grp, sk);
   if (int rc = check_scratch(pl.ws_bytes, sk)) return rc;
   float* part = (float*)sk.p;
   int rc;
@@ -2091,14 +2120,37 @@ int pq_launch_gemm(int M, int N, int K, const pq_operand& A, const pq_operand& B
     else return pq_set_error(PQ_ERR_BAD_ARG, "no MFMA kernel for operand kinds (%d, %d)", ak, bk);
   }
   if (rc != PQ_OK) return rc;
-  if (pl.splits > 1 && !epi.defer_reduce) {
-    pq_prof_scope prof(PQP_SPLITK_REDUCE, s);
-    const int Mred = grp.mode == 2 ? grp.n_groups * M : M;   // grouped ranges: the groups' outputs as one matrix
-    // (with a second contraction the slabs are already floating-point numbers)
-    if (int8 && ph2.K2 == 0) splitk_reduce_kernel<true, false><<<pl.red_blocks, 256, 0, s>>>(Mred, N, pl.splits, part, epi);
-    else if (epi.m_split > 0) splitk_reduce_kernel<false, true><<<pl.red_blocks, 256, 0, s>>>(Mred, N, pl.splits, part, epi);
-    else splitk_reduce_kernel<false, false><<<pl.red_blocks, 256, 0, s>>>(Mred, N, pl.splits, part, epi);
-    PQ_CHECK_LAUNCH("splitk_reduce_kernel");
+  // (with a second contraction the slabs are already floating-point numbers)
+  return reduce_call(M, N, epi, grp, pl, part, int8 && ph2.K2 == 0, s);
+}
+
+int pq_launch_gemm_set(const pq_gemm_call* c, int n, hipStream_t s, pq_scratch sk) {
+  pq_tile_call t[3];
+  bool together = n == 2 || n == 3;
+  size_t used = 0;
+  for (int i = 0; i < n && together; ++i) {
+    if (c[i].M <= 0 || c[i].N <= 0) { together = false; break; }
+    if (int rc = check_epilogue(c[i].M, c[i].A, c[i].B, c[i].epi)) return rc;
+    t[i] = pq_tile_call{c[i].M, c[i].N, c[i].K, c[i].A, c[i].B, c[i].epi, {}, {}, nullptr};
+    if (c[i].grp) t[i].grp = *c[i].grp;
+    t[i].pl = plan_call(c[i].M, c[i].N, c[i].K, c[i].A, c[i].B, c[i].epi, t[i].grp, sk);
+    if (t[i].pl.splits > 1) {
+      t[i].part = (float*)((char*)sk.p + used);
+      used += pq_align_up(t[i].pl.ws_bytes, 256);
+    }
   }
+  together = together && used <= sk.bytes && pq_tile_set_applies(&t[0], n == 3 ? &t[1] : nullptr, t[n - 1]);
+  if (!together) {
+    for (int i = 0; i < n; ++i)
+      if (int rc = pq_launch_gemm(c[i].M, c[i].N, c[i].K, c[i].A, c[i].B, c[i].epi, s, c[i].prof_label, sk, c[i].grp)) return rc;
+    return PQ_OK;
+  }
+  {
+    pq_prof_scope prof(c[0].prof_label, s);
+    if (int rc = pq_launch_tile_set(&t[0], n == 3 ? &t[1] : nullptr, t[n - 1], s)) return rc;
+  }
+  for (int i = 0; i < n; ++i)
+    if (int rc = reduce_call(t[i].M, t[i].N, t[i].epi, t[i].grp, t[i].pl, t[i].part, false, s)) return rc;
   return PQ_OK;
 }
+

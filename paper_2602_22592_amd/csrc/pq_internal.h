@@ -214,6 +214,28 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
 // ---- pq_tile.hip: the 64x64 and 128x128 streaming tiles (pl.bm; the contraction split is the caller's plan) ----
 int pq_launch_tile(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi, hipStream_t s,
                    float* part, const pq_gemm_group& grp, const pq_phase2& ph2, const pq_gemm_second* second = nullptr);
+// a product as its launch takes it
+struct pq_tile_call {
+  int M, N, K;
+  pq_operand A, B;
+  pq_epilogue epi;
+  pq_gemm_group grp;
+  pq_gemm_plan pl;
+  float* part;
+};
+bool pq_tile_set_applies(const pq_tile_call* w0, const pq_tile_call* w1, const pq_tile_call& x);   // (w1 may be NULL)
+int pq_launch_tile_set(const pq_tile_call* w0, const pq_tile_call* w1, const pq_tile_call& x, hipStream_t s);
+// Up to three products that do not depend on each other: n - 1 weight gradients (one or two), then a product of a contraction-contiguous
+// operand with signs or a contraction-strided one.  One launch where they all take small tiles and their slabs fit side by side
+// in the scratch, otherwise one after the other.
+struct pq_gemm_call {
+  int M, N, K;
+  pq_operand A, B;
+  pq_epilogue epi;
+  const pq_gemm_group* grp;
+  int prof_label;
+};
+int pq_launch_gemm_set(const pq_gemm_call* c, int n, hipStream_t s, pq_scratch sk);
 pq_gemm_plan pq_plan_dual(int M, int N, int K, bool int8);   // (its ws_bytes: the slabs of both)
 int pq_launch_gemm_dual(int M, int N, int K, const pq_operand& A0, const pq_operand& B0, const pq_epilogue& e0, const pq_operand& A1,
                         const pq_operand& B1, void* C1, const float* dev_scale1, hipStream_t s, int prof_label, pq_scratch sk);

@@ -207,10 +207,16 @@ __device__ __forceinline__ void tile_step(const FA& fa, const FB& fb, uint32_t s
 }
 
 // 128x128 tiles: wavefront (wv >> 1, wv & 1) multiplies a 64x64 quadrant.  NST: ring stages.
+template <int NST, int AK, int BK, int BK2>
+constexpr int tile_lds() {   // (the second contraction's stages follow in the ring's place)
+  constexpr int ring = NST * (tile_src<AK, 128>::BYTES + tile_src<BK, 128>::BYTES), two = BK2 >= 0 ? 2 * 256 * 128 : 0;
+  return ring > two ? ring : two;
+}
+// (bx, by, bz) of a grid of gy rows: the workgroup's place in its own product's launch
 template <int NST, bool INT8, int AK, int BK, int BK2>
-__global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn,
-                                                        int total_tiles, int kchunk, float* splitk_part, pq_gemm_group grp, pq_phase2 ph2,
-                                                        pq_second_arg<pair_kinds<AK, BK, BK2>()> second) {
+__device__ __forceinline__ void tile_body(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn, int total_tiles, int kchunk,
+                                          float* splitk_part, const pq_gemm_group& grp, const pq_phase2& ph2, int bx, int by, int bz, int gy,
+                                          unsigned char* smem, double* red) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int BM = 128, BN = 128, WM = 64, WN = 64, TM = 2, TN = 2;
   constexpr int EPB = INT8 ? 128 : 64;
@@ -220,26 +226,14 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_
   constexpr int STG = SA::BYTES + SB::BYTES;
   constexpr bool PH2 = BK2 >= 0;
   constexpr int STG2 = PH2 ? (BM + BN) * 128 : 0;
-  constexpr int RING = NST * STG;
-  constexpr int SMEM = RING > 2 * STG2 ? RING : 2 * STG2;   // (the second contraction's stages follow in the same place)
   using acc_t = typename std::conditional<INT8, i32x16_t, f32x16_t>::type;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
-  __shared__ double red[4];
-
   constexpr bool PAIR = pair_kinds<AK, BK, BK2>();
-  if constexpr (PAIR)
-    if (grp.mode == 3 && blockIdx.z == 1) {          // uniform: the second problem of a paired launch
-      A = second.A; B = second.B;
-      M = second.M; N = second.N; nbn = second.nbn;
-      splitk_part = second.part;
-      epi.C = second.C; epi.ldc = second.ldc; epi.scale = second.scale; epi.dev_scale = second.dev_scale;
-    }
   // XCD-aware order: XCD c takes the c-th eighth of the (contraction split, tile row, tile column) order
-  int pid = blockIdx.x, split = blockIdx.y;
+  int pid = bx, split = by;
   {
-    const int nb = total_tiles * (int)gridDim.y;
+    const int nb = total_tiles * gy;
     if ((nb & 7) == 0) {
-      const int lin = blockIdx.x + total_tiles * blockIdx.y;
+      const int lin = bx + total_tiles * by;
       const int w = (lin & 7) * (nb >> 3) + (lin >> 3);
       split = w / total_tiles;
       pid = w - split * total_tiles;
@@ -265,12 +259,12 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_
     M = grp.offsets[z + 1];
     B.p = (const char*)B.p + (size_t)z * grp.b_stride * (BK == PQ_SRC_KC8 ? 1 : 2);
     if (epi.col_div) epi.col_div += (size_t)z * grp.coldiv_stride;
-  } else if (grp.mode == 2) {   // contraction range of group z, in gridDim.y pieces of whole 64-element steps
-    const int z = blockIdx.z;
+  } else if (grp.mode == 2) {   // contraction range of group z, in gy pieces of whole 64-element steps
+    const int z = bz;
     kb = grp.offsets[z];
     ke = grp.offsets[z + 1];
-    if (gridDim.y > 1) {
-      int chunk = (ke - kb + (int)gridDim.y - 1) / (int)gridDim.y;
+    if (gy > 1) {
+      int chunk = (ke - kb + gy - 1) / gy;
       chunk = (chunk + 63) & ~63;
       kb = min(ke, kb + split * chunk);
       ke = min(ke, kb + chunk);
@@ -417,8 +411,25 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_
         }
       }
   }
-  if (!slab) epi_end<256>(epi, st, red, blockIdx.x);
+  if (!slab) epi_end<256>(epi, st, red, bx);
 #endif
+}
+
+template <int NST, bool INT8, int AK, int BK, int BK2>
+__global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn,
+                                                        int total_tiles, int kchunk, float* splitk_part, pq_gemm_group grp, pq_phase2 ph2,
+                                                        pq_second_arg<pair_kinds<AK, BK, BK2>()> second) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[tile_lds<NST, AK, BK, BK2>()];
+  __shared__ double red[4];
+  if constexpr (pair_kinds<AK, BK, BK2>())
+    if (grp.mode == 3 && blockIdx.z == 1) {          // uniform: the second problem of a paired launch
+      A = second.A; B = second.B;
+      M = second.M; N = second.N; nbn = second.nbn;
+      splitk_part = second.part;
+      epi.C = second.C; epi.ldc = second.ldc; epi.scale = second.scale; epi.dev_scale = second.dev_scale;
+    }
+  tile_body<NST, INT8, AK, BK, BK2>(M, N, K, A, B, epi, nbn, total_tiles, kchunk, splitk_part, grp, ph2, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y,
+                                    smem, red);
 }
 
 // 64x64 tiles, the contraction shared out over the wavefronts: wavefront w multiplies the w-th quarter of every 128-byte
@@ -494,10 +505,16 @@ __device__ __forceinline__ void rd64_pair(const rd64<AK>& fa, const rd64<BK>& fb
 #undef W0
 
 // NG: groups of two stages in the ring (NG - 1 of them in flight ahead of the MFMAs)
+template <int NG, int AK, int BK, int BK2>
+constexpr int tile64_lds() {
+  constexpr int need = NG * 2 * (tile_src<AK, 64>::BYTES + tile_src<BK, 64>::BYTES) + (BK2 >= 0 ? 2 * 128 * 128 : 0);
+  static_assert(need <= 150 * 1024, "LDS");
+  return need > 65536 ? need : 65536;                // four partial tiles at the end
+}
 template <int NG, bool INT8, int AK, int BK, int BK2>
-__global__ __launch_bounds__(256) void tile64_gemm_kernel(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn,
-                                                          int total_tiles, int kchunk, float* splitk_part, pq_gemm_group grp, pq_phase2 ph2,
-                                                        pq_second_arg<pair_kinds<AK, BK, BK2>()> second) {
+__device__ __forceinline__ void tile64_body(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn, int total_tiles, int kchunk,
+                                            float* splitk_part, const pq_gemm_group& grp, const pq_phase2& ph2, int bx, int by, int bz, int gy,
+                                            unsigned char* smem, double* red) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int EPB = INT8 ? 128 : 64;
   using SA = tile_src<AK, 64>;
@@ -509,26 +526,14 @@ __global__ __launch_bounds__(256) void tile64_gemm_kernel(int M, int N, int K, p
   constexpr int STG2 = 128 * 128;
   constexpr int RING = NG * 2 * STG;
   constexpr int OFF2 = RING;                         // the second contraction's first two steps have LDS of their own
-  constexpr int NEED = RING + (PH2 ? 2 * STG2 : 0);
-  constexpr int SMEM = NEED > 65536 ? NEED : 65536;  // four partial tiles at the end
-  static_assert(SMEM <= 150 * 1024, "LDS");
   using acc_t = typename std::conditional<INT8, i32x16_t, f32x16_t>::type;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
-  __shared__ double red[4];
   constexpr bool PAIR = pair_kinds<AK, BK, BK2>();
-  if constexpr (PAIR)
-    if (grp.mode == 3 && blockIdx.z == 1) {          // uniform: the second problem of a paired launch
-      A = second.A; B = second.B;
-      M = second.M; N = second.N; nbn = second.nbn;
-      splitk_part = second.part;
-      epi.C = second.C; epi.ldc = second.ldc; epi.scale = second.scale; epi.dev_scale = second.dev_scale;
-    }
   // XCD-aware order: XCD c takes the c-th eighth of the (contraction split, tile row, tile column) order
-  int pid = blockIdx.x, split = blockIdx.y;
+  int pid = bx, split = by;
   {
-    const int nb = total_tiles * (int)gridDim.y;
+    const int nb = total_tiles * gy;
     if ((nb & 7) == 0) {
-      const int lin = blockIdx.x + total_tiles * blockIdx.y;
+      const int lin = bx + total_tiles * by;
       const int w = (lin & 7) * (nb >> 3) + (lin >> 3);
       split = w / total_tiles;
       pid = w - split * total_tiles;
@@ -554,12 +559,12 @@ __global__ __launch_bounds__(256) void tile64_gemm_kernel(int M, int N, int K, p
     M = grp.offsets[z + 1];
     B.p = (const char*)B.p + (size_t)z * grp.b_stride * (BK == PQ_SRC_KC8 ? 1 : 2);
     if (epi.col_div) epi.col_div += (size_t)z * grp.coldiv_stride;
-  } else if (grp.mode == 2) {   // contraction range of group z, in gridDim.y pieces of whole 64-element steps
-    const int z = blockIdx.z;
+  } else if (grp.mode == 2) {   // contraction range of group z, in gy pieces of whole 64-element steps
+    const int z = bz;
     kb = grp.offsets[z];
     ke = grp.offsets[z + 1];
-    if (gridDim.y > 1) {
-      int chunk = (ke - kb + (int)gridDim.y - 1) / (int)gridDim.y;
+    if (gy > 1) {
+      int chunk = (ke - kb + gy - 1) / gy;
       chunk = (chunk + 63) & ~63;
       kb = min(ke, kb + split * chunk);
       ke = min(ke, kb + chunk);
@@ -739,8 +744,25 @@ __global__ __launch_bounds__(256) void tile64_gemm_kernel(int M, int N, int K, p
       }
     }
   }
-  if (!slab) epi_end<256>(epi, st, red, blockIdx.x);
+  if (!slab) epi_end<256>(epi, st, red, bx);
 #endif
+}
+
+template <int NG, bool INT8, int AK, int BK, int BK2>
+__global__ __launch_bounds__(256) void tile64_gemm_kernel(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn,
+                                                          int total_tiles, int kchunk, float* splitk_part, pq_gemm_group grp, pq_phase2 ph2,
+                                                          pq_second_arg<pair_kinds<AK, BK, BK2>()> second) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[tile64_lds<NG, AK, BK, BK2>()];
+  __shared__ double red[4];
+  if constexpr (pair_kinds<AK, BK, BK2>())
+    if (grp.mode == 3 && blockIdx.z == 1) {          // uniform: the second problem of a paired launch
+      A = second.A; B = second.B;
+      M = second.M; N = second.N; nbn = second.nbn;
+      splitk_part = second.part;
+      epi.C = second.C; epi.ldc = second.ldc; epi.scale = second.scale; epi.dev_scale = second.dev_scale;
+    }
+  tile64_body<NG, INT8, AK, BK, BK2>(M, N, K, A, B, epi, nbn, total_tiles, kchunk, splitk_part, grp, ph2, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y,
+                                     smem, red);
 }
 
 #ifndef PQ_NG_DEEP
@@ -789,7 +811,80 @@ int launch_kinds(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& 
   return launch_tile<128, bits ? PQ_NST128B : PQ_NST128, INT8, AK, BK, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2, second);
 }
 
+// Up to two weight gradients (w0, w1) and a product of their input's size (x: its input gradient, or an expert's) that do not depend
+// on each other, in one launch: workgroups of w0, then of w1, then of x.  Alone each leaves CUs idle (one wave of small tiles, or
+// less) and is bound by its own chain of latencies and its launch.
+struct tile_job {
+  int M, N, K, nbn, tiles, kchunk, gy, blocks;       // blocks: tiles * splits * groups
+  pq_operand A, B;
+  pq_epilogue epi;
+  float* part;
+  pq_gemm_group grp;
+};
+template <int BM, int NST, int AK, int BK>
+struct tile_kind {
+  static constexpr int LDS = BM == 64 ? tile64_lds<NST, AK, BK, -1>() : tile_lds<NST, AK, BK, -1>();
+  static __device__ __forceinline__ void run(const tile_job& j, int b, unsigned char* smem, double* red) {
+    pq_phase2 none;
+    none.K2 = 0;
+    const int bx = b % j.tiles, by = b / j.tiles % j.gy, bz = b / (j.tiles * j.gy);
+    if constexpr (BM == 64) tile64_body<NST, false, AK, BK, -1>(j.M, j.N, j.K, j.A, j.B, j.epi, j.nbn, j.tiles, j.kchunk, j.part, j.grp, none, bx, by, bz, j.gy, smem, red);
+    else tile_body<NST, false, AK, BK, -1>(j.M, j.N, j.K, j.A, j.B, j.epi, j.nbn, j.tiles, j.kchunk, j.part, j.grp, none, bx, by, bz, j.gy, smem, red);
+  }
+};
+template <int BM, int AK, int BK>
+using tile_in_set = tile_kind<BM, BM == 64 ? PQ_NG : BK == PQ_SRC_BITS16 ? PQ_NST128B : PQ_NST128, AK, BK>;
+template <int WBM, int XBM, int XBK>
+__global__ __launch_bounds__(256) void tile_set_kernel(tile_job w0, tile_job w1, tile_job x) {
+  using W = tile_in_set<WBM, PQ_SRC_KS16, PQ_SRC_KS16>;
+  using X = tile_in_set<XBM, PQ_SRC_KC16, XBK>;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[W::LDS > X::LDS ? W::LDS : X::LDS];
+  __shared__ double red[4];
+  const int b = blockIdx.x, nw = w0.blocks + w1.blocks;
+  if (b >= nw) {                                     // uniform
+    X::run(x, b - nw, smem, red);
+    return;
+  }
+  const bool second = b >= w0.blocks;
+  const tile_job& w = second ? w1 : w0;
+  W::run(w, second ? b - w0.blocks : b, smem, red);
+}
+
+template <int WBM, int XBM, int XBK>
+int launch_set(const tile_job& w0, const tile_job& w1, const tile_job& x, hipStream_t s) {
+  tile_set_kernel<WBM, XBM, XBK><<<w0.blocks + w1.blocks + x.blocks, 256, 0, s>>>(w0, w1, x);
+  PQ_CHECK_LAUNCH("tile_set_kernel");
+  return PQ_OK;
+}
+
+tile_job job_of(const pq_tile_call* c) {
+  tile_job j;
+  memset(&j, 0, sizeof(j));
+  if (!c) return j;
+  const int bm = c->pl.bm, nbm = c->grp.mode == 1 ? (c->grp.max_rows + bm - 1) / bm + c->grp.n_groups : (c->M + bm - 1) / bm;
+  j.M = c->M; j.N = c->N; j.K = c->K; j.nbn = (c->N + bm - 1) / bm; j.tiles = nbm * j.nbn; j.kchunk = c->pl.kchunk;
+  j.gy = c->pl.splits; j.blocks = j.tiles * j.gy * (c->grp.mode == 2 ? c->grp.n_groups : 1);
+  j.A = c->A; j.B = c->B; j.epi = c->epi; j.part = c->pl.splits > 1 ? c->part : nullptr; j.grp = c->grp;
+  return j;
+}
+
 }  // namespace
+
+bool pq_tile_set_applies(const pq_tile_call* w0, const pq_tile_call* w1, const pq_tile_call& x) {
+  for (const pq_tile_call* w : {w0, w1})
+    if (w && (w->A.kind != PQ_SRC_KS16 || w->B.kind != PQ_SRC_KS16 || w->pl.bn > 128 || w->pl.bm != w0->pl.bm)) return false;
+  return x.A.kind == PQ_SRC_KC16 && (x.B.kind == PQ_SRC_BITS16 || x.B.kind == PQ_SRC_KS16) && x.pl.bn <= 128;
+}
+
+int pq_launch_tile_set(const pq_tile_call* w0, const pq_tile_call* w1, const pq_tile_call& x, hipStream_t s) {
+  if (!w0 || !pq_tile_set_applies(w0, w1, x)) return pq_set_error(PQ_ERR_BAD_ARG, "products that cannot share a launch");
+  const tile_job j0 = job_of(w0), j1 = job_of(w1), jx = job_of(&x);
+#define PQ_SET(WBM, XBM, XBK) if (w0->pl.bm == WBM && x.pl.bm == XBM && x.B.kind == XBK) return launch_set<WBM, XBM, XBK>(j0, j1, jx, s)
+  PQ_SET(64, 64, PQ_SRC_BITS16); PQ_SET(64, 128, PQ_SRC_BITS16); PQ_SET(128, 64, PQ_SRC_BITS16); PQ_SET(128, 128, PQ_SRC_BITS16);
+  PQ_SET(64, 64, PQ_SRC_KS16); PQ_SET(64, 128, PQ_SRC_KS16); PQ_SET(128, 64, PQ_SRC_KS16); PQ_SET(128, 128, PQ_SRC_KS16);
+#undef PQ_SET
+  return pq_set_error(PQ_ERR_BAD_ARG, "no launch for these tiles");
+}
 
 int pq_launch_tile(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi, hipStream_t s,
                    float* part, const pq_gemm_group& grp, const pq_phase2& ph2, const pq_gemm_second* second) {
