@@ -111,7 +111,7 @@ struct lin_layout {
   size_t hp8, hp8_bytes;
   // workspace (scratch)
   size_t stat_partials, red_a, red_b, dH, w_Xq, w_gamma, w_H, splitk, splitk2, splitk_bytes, splitk2_bytes, ws_base, ws_total;
-  size_t dYp, rd, dHs, dXs, dlogit, dwr, hp8_ws, hp8_ws_bytes;
+  size_t hist, dYp, rd, dHs, dXs, dlogit, dwr, hp8_ws, hp8_ws_bytes;
   // fp32 I/O in fixed point (pq_fixed.hip): a region of fx_bytes (0: the call has none) behind everything else, which only a backward
   // uses, and only if the workspace holds it
   size_t fx_drow, fx_rexp, fx_dcol, fx_cexp, fx_qT, fx_colmax, fx_counts, fx_red_b, fx_signs, fx_SW, fx_SX, fx_bytes;
@@ -208,6 +208,7 @@ lin_layout make_layout(const pq_linear_desc& d) {
   L.splitk2_bytes = sk2a > sk2b ? sk2a : sk2b;
   L.splitk2 = w.take(L.splitk2_bytes);
   if (routed) {
+    L.hist = w.take((T + pq_router_tokens((int)E) - 1) / pq_router_tokens((int)E) * E * sizeof(int));
     L.dYp = w.take(S * N * 2); L.rd = w.take(S * 4); L.dHs = w.take(S * re * 2); L.dXs = w.take(S * K * 2);
     L.dlogit = w.take(T * E * 4);
     L.dwr = w.take(pq_dwr_scratch_bytes(d.tokens, d.d_in, d.n_experts));
@@ -510,7 +511,23 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
     if (int e = launch_H(H_splits > 1)) return e;
     H_done = true;
   }
+  // routed experts: the router (with the statistics and the quantiser where they take it), and what orders its slots
+  pq_router_job route;
+  pq_place place;
+  memset(&route, 0, sizeof(route));
+  memset(&place, 0, sizeof(place));
+  bool routed_done = false;
+  if (routed) {
+    const int E = d->n_experts, rt = pq_router_tokens(E);
+    route = pq_router_job{Wr, E, d->top_k, (int*)(cx + L.idx), (float*)(cx + L.gate), (float*)(cx + L.probs), (int*)(ws + L.hist)};
+    place = pq_place{route.hist, (T + rt - 1) / rt, rt, T, d->top_k, E, K, route.idx, (int*)(cx + L.counts), (int*)(cx + L.offsets), (int*)(cx + L.perm),
+                     (int*)(cx + L.inv), (const uint16_t*)X, (uint16_t*)(cx + L.Xp), nullptr, nullptr, nullptr, nullptr};
+  }
   auto launch_combo = [&](const void* w, size_t n, double* part, int nb) -> int {
+    if (routed && pq_wstats_quant_router_applies(d->n_experts, K, nb + (T + 3) / 4)) {
+      quant_done = routed_done = true;
+      return pq_launch_wstats_quant_router(w, n, part, nb, X, T, K, Xq, gamma, Xt, route, s);
+    }
     const bool sum = H_done && H_splits > 1;
     quant_done = true;
     return pq_launch_wstats_quant(w, d->io_dtype, n, part, nb, X, T, K, Xq, gamma, Xt, s, sum ? (const float*)sk_ws.p : nullptr, H_splits, T, r, H, r);
@@ -527,7 +544,11 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
       if (int e = pq_launch_wstats_partial(W_or_packed, d->io_dtype, n, part, nb, s)) return e;
     }
     uint32_t* Pt = (N % 32 == 0) ? (uint32_t*)(cx + L.Pt) : nullptr;
-    if (hp8) {   // the rows of A and B on the AbsMax grid ride along
+    if (routed && !routed_done)
+      if (int e = pq_launch_router(X, Wr, PQ_BF16, T, K, route.E, route.k, route.idx, route.gate, route.probs, s, route.hist)) return e;
+    if (routed) {   // the slots' order rides along (with no tokens: empty expert segments for a backward)
+      if (int e = pq_launch_pack_place(W_or_packed, N, K, part, nb, (uint32_t*)(cx + L.P), Pt, (float*)(cx + L.mulam), place, s)) return e;
+    } else if (hp8) {   // the rows of A and B on the AbsMax grid ride along
       const hp8_layout H8 = make_hp8_layout(T, K, N, d->hp_rank);
       char* c8 = cx + L.hp8;
       const pq_quant_rows_job jobs[2] = {{hpA, d->hp_rank, K, (int8_t*)(c8 + H8.Aq), (float*)(c8 + H8.gA), (uint16_t*)(c8 + H8.At)},
@@ -545,13 +566,12 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
     mulam = mu_lambda;
     if (combo)
       if (int e = launch_combo(nullptr, 0, nullptr, 0)) return e;
+    if (routed) {
+      if (int e = pq_launch_router(X, Wr, PQ_BF16, T, K, route.E, route.k, route.idx, route.gate, route.probs, s, route.hist)) return e;
+      if (int e = pq_launch_pack_place(nullptr, N, K, nullptr, 0, nullptr, nullptr, nullptr, place, s)) return e;
+    }
   }
-  if (T == 0) {   // the weight side is still prepared, so a backward with no tokens is well defined
-    if (routed)   // ... and empty expert segments are left behind for it
-      return pq_launch_route((const int*)(cx + L.idx), 0, d->n_experts, (int*)(cx + L.counts), (int*)(cx + L.offsets),
-                             (int*)(cx + L.perm), (int*)(cx + L.inv), s);
-    return PQ_OK;
-  }
+  if (T == 0) return PQ_OK;   // the weight side is prepared, so a backward with no tokens is well defined
 
   if (!quant_done)
     if (int e = pq_launch_quant_act(X, d->io_dtype, T, K, Xq, gamma, Xt, s)) return e;
@@ -599,17 +619,9 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
     return hp_int8_fwd_impl(Xq, gamma, hpA, hpB, PQ_BF16, T, K, N, d->hp_rank, d->alpha, Y, 1, cx + L.hp8, L.hp8_bytes,
                             ws + L.hp8_ws, L.hp8_ws_bytes, stream, d->w_kind == PQ_W_MASTER);
   if (routed) {
-    // router -> stable permutation by expert -> gather -> H_e = X_e A_e^T -> Y_e = H_e B_e^T -> gate-weighted combine
+    // slots in expert order (above) -> H_e = X_e A_e^T -> Y_e = H_e B_e^T -> gate-weighted combine
     const int E = d->n_experts, k = d->top_k, S = T * k, re = d->hp_rank;
-    int* idx = (int*)(cx + L.idx);
-    float* gate = (float*)(cx + L.gate);
-    int* offsets = (int*)(cx + L.offsets);
-    int* perm = (int*)(cx + L.perm);
-    int* inv = (int*)(cx + L.inv);
-    if (int e = pq_launch_router(X, Wr, PQ_BF16, T, K, E, k, idx, gate, (float*)(cx + L.probs), s)) return e;
-    if (int e = pq_launch_route(idx, S, E, (int*)(cx + L.counts), offsets, perm, inv, s)) return e;
-    if (int e = pq_launch_gather_rows(X, perm, k, S, K, cx + L.Xp, s)) return e;
-    pq_gemm_group g1{offsets, E, 1, 0, 0, S};
+    pq_gemm_group g1{place.offsets, E, 1, 0, 0, S};
     {
       pq_operand A{cx + L.Xp, K, PQ_SRC_KC16, nullptr};
       pq_operand B{hpA, K, PQ_SRC_KC16, nullptr};
@@ -626,7 +638,7 @@ static int linear_fwd_impl(const pq_linear_desc* d, const void* X, const void* W
       g1.b_stride = (long)N * re;
       if (int err = pq_launch_gemm(S, N, re, A, B, e, s, PQP_GEMM_EXPERT, sk_ws, &g1)) return err;
     }
-    return pq_launch_combine_fwd(Y, cx + L.Ys, inv, gate, d->alpha, T, k, N, s);
+    return pq_launch_combine_fwd(Y, cx + L.Ys, place.inv, route.gate, d->alpha, T, k, N, s);
   }
   return PQ_OK;
 }

@@ -38,7 +38,7 @@ struct ffn_layout {
   // X~ instead of X)
   size_t UGQ, gUG, UGT, DownQ, gDown, DownT, XqP, gxP, aQ, gA, aT, ctx_total;
   // workspace
-  size_t stat, red_a, red_b, splitk, dHd, dU, dG, dYp, rd, da, du, dg, as, dXs, dlogit, dwr, splitk_bytes, ws_total;
+  size_t stat, red_a, red_b, splitk, dHd, dU, dG, hist, dYp, rd, da, du, dg, as, dXs, dlogit, dwr, splitk_bytes, ws_total;
   int n_red_a, n_red_b;
 };
 
@@ -111,6 +111,7 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   L.splitk = w.take(sk);
   L.splitk_bytes = sk;
   L.dHd = w.take(T * F * 2); L.dU = w.take(T * F * 2); L.dG = w.take(T * F * 2);
+  L.hist = w.take(E > 1 ? (T + pq_router_tokens((int)E) - 1) / pq_router_tokens((int)E) * E * sizeof(int) : 0);
   L.dYp = w.take(So * D * 2); L.rd = w.take(So * 4);
   L.da = w.take(S * r * 2); L.du = w.take(2 * S * r * 2); L.dg = L.du + S * r * 2; L.as = w.take(S * r * 2);
   L.dXs = w.take(So * D * 2); L.dlogit = w.take(E > 1 ? T * E * 4 : 0);
@@ -210,12 +211,24 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
     p.UGQ = (int8_t*)(cx + L.UGQ); p.gUG = (float*)(cx + L.gUG); p.UGT = (uint16_t*)(cx + L.UGT);
     p.DownQ = (int8_t*)(cx + L.DownQ); p.gDown = (float*)(cx + L.gDown); p.DownT = (uint16_t*)(cx + L.DownT);
   }
-  if (int e = pq_launch_ffn_prep(p, s)) return e;
-  if (int e = pq_launch_pack3(p.w, s)) return e;
+  // routed experts: router -> slots in expert order, their rows copied -> grouped GEMMs -> combine.  The router goes with the statistics
+  // where they take it, the order with the packing (with no tokens: empty expert segments, so that a backward is well defined).
   const bool one = E == 1;
-  if (T == 0)  // no tokens: leave empty expert segments behind so that a backward call is well defined
-    return one ? PQ_OK : pq_launch_route((const int*)(cx + L.idx), 0, E, (int*)(cx + L.counts), (int*)(cx + L.offsets), (int*)(cx + L.perm),
-                                         (int*)(cx + L.inv), s);
+  const pq_router_job route{Wr, E, k, (int*)(cx + L.idx), (float*)(cx + L.gate), (float*)(cx + L.probs), (int*)(ws + L.hist)};
+  const bool route_rides = !one && T > 0 && pq_wstats_quant_router_applies(E, D, p.w[0].nblocks + p.w[1].nblocks + p.w[2].nblocks + (T + 3) / 4);
+  if (route_rides) p.route = route;
+  if (int e = pq_launch_ffn_prep(p, s)) return e;
+  if (!one && !route_rides)
+    if (int e = pq_launch_router(X, Wr, PQ_BF16, T, D, E, k, route.idx, route.gate, route.probs, s, route.hist)) return e;
+  const int rt = pq_router_tokens(E);
+  pq_place place{route.hist, (T + rt - 1) / rt, rt, T, k, E, D, route.idx, (int*)(cx + L.counts), (int*)(cx + L.offsets), (int*)(cx + L.perm),
+                 (int*)(cx + L.inv), (const uint16_t*)X, (uint16_t*)(cx + L.Xp), nullptr, nullptr, nullptr, nullptr};
+  if (hp8) {   // slot-ordered X~ (for the backward), codes and gamma of x
+    place.src = (const uint16_t*)(cx + L.Xt);
+    place.codes = Xq; place.gamma = gx; place.codes_out = (int8_t*)(cx + L.XqP); place.gamma_out = (float*)(cx + L.gxP);
+  }
+  if (int e = pq_launch_pack3(p.w, one ? nullptr : &place, s)) return e;
+  if (T == 0) return PQ_OK;
 
   {  // U and G: pure 1-bit linears (no feature scale of their own), one launch
     pq_operand A{Xq, D, PQ_SRC_KC8, nullptr};
@@ -249,31 +262,19 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
   };
   if (!fuse_y)
     if (int e = launch_down()) return e;
-  // routed experts: router -> stable permutation by expert -> gather -> grouped GEMMs -> combine
-  int* idx = (int*)(cx + L.idx);
-  float* gate = (float*)(cx + L.gate);
-  int* offsets = (int*)(cx + L.offsets);
-  int* perm = (int*)(cx + L.perm);
-  int* inv = (int*)(cx + L.inv);
   // a single branch (the paper's default, N = 1) has nothing to route: the tokens are its slots, Ys is added to Y by the product
   // itself (which leaves the INT8 form's in ctx, see the backward).  2048 tokens 2048/5076, r = 384 INT8: five launches and a pass over the
   // slots less, 643 -> 635 us
-  if (!one) {
-    if (int e = pq_launch_router(X, Wr, PQ_BF16, T, D, E, k, idx, gate, (float*)(cx + L.probs), s)) return e;
-    if (int e = pq_launch_route(idx, S, E, (int*)(cx + L.counts), offsets, perm, inv, s)) return e;
-  }
+  const int *offsets = place.offsets, *inv = place.inv;
+  const float* gate = route.gate;
   pq_gemm_group g1{offsets, E, 1, 0, 0, S};
   // a single branch (the paper's default, N = 1): every slot belongs to it, so its products are plain GEMMs over all slots
   // (they then take the split rules and kernels of plain GEMMs, the four-wavefront weight-gradient kernel among them)
   const pq_gemm_group* pg1 = one ? nullptr : &g1;
   if (hp8) {
-    // slot-ordered X~ (for the backward), codes and gamma of x; with a single branch the slot order is the token order and
-    // the originals serve
+    // with a single branch the slot order is the token order and the originals serve
     const void* xqp = one ? (const void*)Xq : (const void*)(cx + L.XqP);
     const float* gxp = one ? (const float*)gx : (const float*)(cx + L.gxP);
-    if (!one) {
-      if (int e = pq_launch_gather_quant_rows(cx + L.Xt, Xq, gx, perm, k, S, D, cx + L.Xp, (int8_t*)(cx + L.XqP), (float*)(cx + L.gxP), s)) return e;
-    }
     {  // [u | g] = (q_x q_w^T) / (gamma_x gamma_w), bf16: both projections as one product with 2 r outputs per slot
       pq_operand A{xqp, D, PQ_SRC_KC8, nullptr};
       pq_operand B{cx + L.UGQ, D, PQ_SRC_KC8, nullptr};
@@ -301,8 +302,6 @@ extern "C" int pq_ffn_fwd(const pq_ffn_desc* d, const void* X, const void* W_up,
     return pq_launch_combine_fwd(Y, cx + L.Ys, inv, gate, d->alpha, T, k, D, s);
   }
   const void* xp = one ? X : cx + L.Xp;
-  if (!one)
-    if (int e = pq_launch_gather_rows(X, perm, k, S, D, cx + L.Xp, s)) return e;
   // [u | g] = Xp [Up_e; Gate_e]^T: both projections as one product with 2 r outputs per slot
   {
     pq_operand A{xp, D, PQ_SRC_KC16, nullptr};

@@ -49,6 +49,21 @@ int pq_launch_pack(const void* W, int dtype, int N, int K, const double* partial
 // pq_stats_blocks), the quantiser of X (T rows of D; T may be 0), and the expert rows [Up_e; Gate_e] as one [E][2 r][D]
 // matrix: copied to UG, or with UGQ set (INT8 experts) quantised to UGQ / gUG / UGT, with the E * D rows of Down to DownQ /
 // gDown / DownT; then the packing of the three.
+struct pq_router_job { const void* Wr; int E, k; int* idx; float *gate, *probs; int* hist; };   // (Wr NULL: none)
+// The slots of a routed call in expert order, from the router's counts, and their rows in that order (pq_quant.hip).
+struct pq_place {
+  const int* hist;              // [nblk][E], of `tokens` tokens each
+  int nblk, tokens, T, k, E, d;
+  const int* idx;
+  int *counts, *offsets, *perm, *inv;
+  const uint16_t* src;          // [T][d] bf16
+  uint16_t* dst;                // [T k][d]
+  const int8_t* codes;          // INT8 experts (otherwise NULL): codes [T][d] and gammas [T] go along
+  const float* gamma;
+  int8_t* codes_out;
+  float* gamma_out;
+};
+int pq_router_tokens(int E);    // tokens per row of hist
 struct pq_weight_job { const void* W; int N, K; double* partials; int nblocks; uint32_t* P; uint32_t* Pt; float* mu_lambda; };
 struct pq_ffn_prep {
   pq_weight_job w[3];
@@ -57,15 +72,23 @@ struct pq_ffn_prep {
   void* UG;
   int8_t* UGQ; float* gUG; uint16_t* UGT;
   int8_t* DownQ; float* gDown; uint16_t* DownT;
+  pq_router_job route;          // (where pq_wstats_quant_router_applies)
 };
 int pq_launch_ffn_prep(const pq_ffn_prep& p, hipStream_t s);
-int pq_launch_pack3(const pq_weight_job* w, hipStream_t s);
+int pq_launch_pack3(const pq_weight_job* w, const pq_place* place, hipStream_t s);   // place may be NULL
+// pq_launch_pack of a bf16 weight (N, K multiples of 32; W NULL: no weight) with the ordering of the slots in the launch
+int pq_launch_pack_place(const void* W, int N, int K, const double* partials, int nblocks, uint32_t* P, uint32_t* Pt, float* mu_lambda,
+                         const pq_place& place, hipStream_t s);
+// pq_launch_wstats_quant (bf16) with the router in the launch
+bool pq_wstats_quant_router_applies(int E, int K, long blocks);   // blocks: workgroups of the launch without it
+int pq_launch_wstats_quant_router(const void* W, size_t n_elems, double* partials, int nblocks, const void* X, int T, int K, int8_t* Xq, float* gamma,
+                                  uint16_t* Xt, const pq_router_job& r, hipStream_t s);
 // pq_launch_pack of a bf16 weight (N, K multiples of 32) with the AbsMax quantiser of the rows of two more bf16 matrices in the launch
 struct pq_quant_rows_job { const void* src; int rows, cols; int8_t* codes; float* gamma; uint16_t* deq; };
 int pq_launch_pack_quant_rows(const void* W, int N, int K, const double* partials, int nblocks, uint32_t* P, uint32_t* Pt, float* mu_lambda,
                               const pq_quant_rows_job* jobs, hipStream_t s);
 int pq_launch_router(const void* X, const void* Wr, int dtype, int T, int K, int E, int k, int* idx,
-                     float* gate, float* probs, hipStream_t s);
+                     float* gate, float* probs, hipStream_t s, int* hist = nullptr);
 // two sums of partials in one launch: out[0] = factor [* *dev_factor] * sum(partials[0..n))
 int pq_launch_reduce_partials2(const double* pa, int na, float fa, const float* dfa, float* oa, const double* pb, int nb, float fb,
                                const float* dfb, float* ob, hipStream_t s);
@@ -318,12 +341,7 @@ int pq_launch_decode_ffn(int L, int B, int D, int F, int r, int E, int topk, flo
                          void* ws1, void* ws2, float* amax_part, hipStream_t s);   // amax_part: [L][B][8] floats of scratch, [L][ceil(F/64)] for one token
 
 // ---- pq_moe.hip ---------------------------------------------------------------------------
-int pq_launch_route(const int* idx, int S, int E, int* counts, int* offsets, int* perm, int* inv, hipStream_t s);
 int pq_launch_gather_rows(const void* src, const int* perm, int k, int S, int d, void* dst, hipStream_t s);
-// the same for rows of bf16 with their INT8 codes and gammas (d % 16 == 0)
-int pq_launch_gather_quant_rows(const void* xt, const int8_t* xq, const float* gx, const int* perm, int k, int S, int d, void* xt_out,
-                                int8_t* xq_out, float* gx_out, hipStream_t s);
-// rows of F elements of which the first Fv exist (padded widths): the rest is written as zero
 int pq_launch_swiglu_quant(const void* U, const void* G, int T, int F, int Fv, int8_t* Hq, float* gamma, void* Ht, hipStream_t s);
 int pq_launch_swiglu_bwd(const void* dHd, const void* U, const void* G, int T, int F, int Fv, void* dU, void* dG, hipStream_t s);
 // ue, ge (and du, dg) have a row stride of ld elements: r, or 2 r when both lie side by side in one [S][2 r] matrix

@@ -1,9 +1,6 @@
-// Routing bookkeeping and element-wise kernels of the decoupled FFN (Sec. 3.2, 3.3): expert
-// histogram and stable permutation, row gather, the gated unit with fused AbsMax re-quantisation,
+// Element-wise kernels of the decoupled FFN and the routed experts (Sec. 3.2, 3.3): row gather, the gated unit with fused AbsMax re-quantisation,
 // expert activation forward/backward, gate/alpha reductions, router backward, scatter-combine.
 // All tensors here are bf16 unless noted; every reduction has a fixed order.
-#include <mutex>
-
 #include "pq_internal.h"
 
 namespace {
@@ -22,98 +19,6 @@ __device__ __forceinline__ float dsiluf_(float x) {
   return s * (1.0f + x * (1.0f - s));
 }
 
-// Stable counting sort of the slots (slot = token * k + j) by expert: perm[pos] = slot, inv[slot] = pos,
-// offsets[e] = first position of expert e.  One workgroup of 16 wavefronts, each owning a contiguous range of whole
-// 64-slot batches.  The expert ids (< 64) are first copied into LDS as bytes (LDS_IDS; otherwise both passes read them
-// from global memory).  Pass 1: lane e of a wavefront counts expert e in the wavefront's range (one ballot per batch and
-// expert).  The counts are scanned over (expert, wavefront), which gives every wavefront the first position of each
-// expert's slots inside its range.  Pass 2: the same walk assigns positions in slot order (rank inside a batch by
-// ballot prefix), lane e carrying expert e's running position.
-template <bool LDS_IDS>
-__global__ __launch_bounds__(1024) void route_kernel(const int* __restrict__ idx, int S, int E, int* __restrict__ counts,
-                                                     int* __restrict__ offsets, int* __restrict__ perm,
-                                                     int* __restrict__ inv) {
-  extern __shared__ unsigned char s_ids[];
-  __shared__ int s_cnt[16][64], s_off[65];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if constexpr (LDS_IDS) {
-    // eight loads per thread in flight (indices clamped, the store conditional): one memory latency per 8192 slots
-    for (int s0 = 0; s0 < S; s0 += 8192) {
-      int v[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = idx[min(s0 + q * 1024 + (int)threadIdx.x, S - 1)];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int s = s0 + q * 1024 + (int)threadIdx.x;
-        if (s < S) s_ids[s] = (unsigned char)v[q];
-      }
-    }
-    __syncthreads();
-  }
-  auto id_at = [&](int s) -> int {
-    if (s >= S) return -1;
-    if constexpr (LDS_IDS) return s_ids[s];
-    else return idx[s];
-  };
-  const int nb = (S + 63) / 64, per = (nb + 15) / 16;
-  const int b0 = min(nb, wave * per), b1 = min(nb, b0 + per);
-  int cnt = 0;                                      // lane e: slots of expert e in this wavefront's range
-  for (int b = b0; b < b1; ++b) {
-    const int id = id_at(b * 64 + lane);
-    for (int e = 0; e < E; ++e) {
-      const int c = __builtin_popcountll(__ballot(id == e));
-      if (lane == e) cnt += c;
-    }
-  }
-  s_cnt[wave][lane] = cnt;
-  __syncthreads();
-  if (wave == 0) {                                  // lane e: expert e's total, then the exclusive prefix over the experts (E <= 64)
-    int tot = 0;
-    if (lane < E) {
-#pragma unroll
-      for (int w = 0; w < 16; ++w) tot += s_cnt[w][lane];
-    }
-    int incl = tot;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int up = __shfl_up(incl, d);
-      if (lane >= d) incl += up;
-    }
-    if (lane < E) {
-      s_off[lane] = incl - tot;
-      offsets[lane] = incl - tot;
-      counts[lane] = tot;
-    }
-    if (lane == E - 1) {
-      s_off[E] = incl;
-      offsets[E] = incl;
-    }
-  }
-  __syncthreads();
-  int running = 0;                                  // lane e: next position of expert e for this wavefront
-  if (lane < E) {
-    running = s_off[lane];
-    for (int w = 0; w < wave; ++w) running += s_cnt[w][lane];
-  }
-  for (int b = b0; b < b1; ++b) {
-    const int s = b * 64 + lane;
-    const int id = id_at(s);
-    int pos = 0;
-    for (int e = 0; e < E; ++e) {
-      const unsigned long long m = __ballot(id == e);
-      const int base = __builtin_amdgcn_readlane(running, e);   // e is uniform: a scalar read, not a trip through LDS
-      if (id == e) pos = base + __builtin_popcountll(m & ((1ull << lane) - 1ull));
-      if (lane == e) running += __builtin_popcountll(m);
-    }
-    // one pair of stores per 64 slots (a store under each expert's branch made the single CU's memory pipe the bottleneck:
-    // 2 E store instructions per block and wavefront)
-    if (id >= 0) {
-      perm[pos] = s;
-      inv[s] = pos;
-    }
-  }
-}
-
 // dst[pos][:] = src[perm[pos] / k][:]   (rows of d bf16, d % 8 == 0), one wavefront per row
 __global__ __launch_bounds__(256) void gather_rows_kernel(const uint16_t* __restrict__ src, const int* __restrict__ perm, int k,
                                                           int S, int d, uint16_t* __restrict__ dst) {
@@ -123,23 +28,6 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint16_t* __rest
   const uint4* s4 = reinterpret_cast<const uint4*>(src + (size_t)t * d);
   uint4* d4 = reinterpret_cast<uint4*>(dst + (size_t)pos * d);
   for (int c = lane; c < d / 8; c += 64) d4[c] = s4[c];
-}
-
-// the same for a row of bf16, its INT8 codes and its gamma (INT8 experts), one wavefront per slot
-__global__ __launch_bounds__(256) void gather_quant_rows_kernel(const uint16_t* __restrict__ xt, const int8_t* __restrict__ xq,
-                                                                const float* __restrict__ gx, const int* __restrict__ perm, int k, int S,
-                                                                int d, uint16_t* __restrict__ xt_out, int8_t* __restrict__ xq_out,
-                                                                float* __restrict__ gx_out) {
-  const int pos = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (pos >= S) return;
-  const int t = perm[pos] / k;
-  const uint4* a = reinterpret_cast<const uint4*>(xt + (size_t)t * d);
-  const uint4* q = reinterpret_cast<const uint4*>(xq + (size_t)t * d);
-  uint4* ao = reinterpret_cast<uint4*>(xt_out + (size_t)pos * d);
-  uint4* qo = reinterpret_cast<uint4*>(xq_out + (size_t)pos * d);
-  for (int c = lane; c < d / 8; c += 64) ao[c] = a[c];
-  for (int c = lane; c < d / 16; c += 64) qo[c] = q[c];
-  if (lane == 0) gx_out[pos] = gx[t];
 }
 
 // ---- the gated unit with fused AbsMax re-quantisation (one wavefront per token) -------------
@@ -683,38 +571,11 @@ int pq_launch_lincomb(void* out, const void* x0, const void* x1, const void* x2,
 }
 
 // ---------------------------------------------------------------------------------------------
-int pq_launch_route(const int* idx, int S, int E, int* counts, int* offsets, int* perm, int* inv, hipStream_t s) {
-  pq_prof_scope prof(PQP_MOE_ROUTE, s);
-  if (S <= 96 * 1024) {
-    static std::once_flag once;
-    static int rc = PQ_OK;
-    std::call_once(once, [] {
-      if (hipFuncSetAttribute((const void*)route_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024) != hipSuccess)
-        rc = pq_set_error(PQ_ERR_HIP, "hipFuncSetAttribute failed for route_kernel");
-    });
-    if (rc != PQ_OK) return rc;
-    route_kernel<true><<<1, 1024, (size_t)((S + 15) / 16 * 16), s>>>(idx, S, E, counts, offsets, perm, inv);
-  } else {
-    route_kernel<false><<<1, 1024, 0, s>>>(idx, S, E, counts, offsets, perm, inv);
-  }
-  PQ_CHECK_LAUNCH("route_kernel");
-  return PQ_OK;
-}
-
 int pq_launch_gather_rows(const void* src, const int* perm, int k, int S, int d, void* dst, hipStream_t s) {
   if (S == 0) return PQ_OK;
   pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
   gather_rows_kernel<<<(S + 3) / 4, 256, 0, s>>>((const uint16_t*)src, perm, k, S, d, (uint16_t*)dst);
   PQ_CHECK_LAUNCH("gather_rows_kernel");
-  return PQ_OK;
-}
-
-int pq_launch_gather_quant_rows(const void* xt, const int8_t* xq, const float* gx, const int* perm, int k, int S, int d, void* xt_out,
-                                int8_t* xq_out, float* gx_out, hipStream_t s) {
-  if (S == 0) return PQ_OK;
-  pq_prof_scope prof(PQP_MOE_ELEMENTWISE, s);
-  gather_quant_rows_kernel<<<(S + 3) / 4, 256, 0, s>>>((const uint16_t*)xt, xq, gx, perm, k, S, d, (uint16_t*)xt_out, xq_out, gx_out);
-  PQ_CHECK_LAUNCH("gather_quant_rows_kernel");
   return PQ_OK;
 }
 

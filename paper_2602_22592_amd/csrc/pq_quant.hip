@@ -1,6 +1,7 @@
 // Bandwidth-bound element kernels: AbsMax INT8 activation quantiser (Sec. 3.1), weight statistics
 // mu/lambda and the sign binariser/packer (Sec. 3.1, App. A), the router (Sec. 3.3).
 #include <mutex>
+#include <string.h>
 #include "pq_internal.h"
 #include "pq_pack.h"
 
@@ -539,6 +540,231 @@ __global__ __launch_bounds__(256) void wstats_partial_kernel(const T* __restrict
   wstats_partial_body<T>(W, nvec, partials, blockIdx.x, gridDim.x);
 }
 
+// ------------------------------------------------------------------------------------------
+// Router: a wavefront takes TB tokens at once (a router row converted to fp64 serves all of them): fp64 dot products
+// against all E router rows, lane l accumulating the 16-byte chunks l, l + 64, ... of a token row in order, then the
+// wave sums, which leave one (token, expert) pair per lane; that lane rounds the logit to fp32 and evaluates its term
+// of the softmax in fp64; the first lane of a token's group selects the top-k (ties to the lower index).
+// ------------------------------------------------------------------------------------------
+// hist (may be NULL): [workgroups][E], how many slots of the workgroup's 4 TB tokens each expert got (what the permutation starts from).
+template <typename T, int EMAX, int TB>
+__device__ __forceinline__ void router_body(const T* __restrict__ X, const T* __restrict__ Wr, int Tn, int K, int E, int k, int* __restrict__ idx,
+                                            float* __restrict__ gate, float* __restrict__ probs, int* __restrict__ hist, int block) {
+  constexpr int V = vec16<T>::V;
+  __shared__ int s_hist[64];
+  const int lane = threadIdx.x & 63;
+  const int t0 = (block * 4 + (threadIdx.x >> 6)) * TB;
+  if (hist) {                                        // uniform
+    if (threadIdx.x < 64) s_hist[threadIdx.x] = 0;
+    __syncthreads();
+  } else if (t0 >= Tn) return;
+  const int nvec = K / V;
+  double acc[TB][EMAX];
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+    for (int e = 0; e < EMAX; ++e) acc[tb][e] = 0.0;
+  // Router rows are requested unconditionally, eight at a time (rows past E repeat the last one and their sums
+  // are never used; tokens past the end repeat the last token): a load under a branch gets a wait of its own, which
+  // made this loop a chain of latencies.
+  for (int c = lane; c < nvec; c += 64) {
+    double xd[TB][V];
+    uint4 xv[TB];
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) xv[tb] = reinterpret_cast<const uint4*>(X + (size_t)min(t0 + tb, Tn - 1) * K)[c];
+#pragma unroll
+    for (int e0 = 0; e0 < EMAX; e0 += 8) {
+      uint4 wv[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) wv[u] = reinterpret_cast<const uint4*>(Wr + (size_t)min(e0 + u, E - 1) * K)[c];
+      if (e0 == 0) {
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) {
+          float xf[V];
+          vec16<T>::unpack(xv[tb], xf);
+#pragma unroll
+          for (int j = 0; j < V; ++j) xd[tb][j] = (double)xf[j];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        float wf[V];
+        vec16<T>::unpack(wv[u], wf);
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+          const double wd = (double)wf[j];
+#pragma unroll
+          for (int tb = 0; tb < TB; ++tb) acc[tb][e0 + u] += xd[tb][j] * wd;
+        }
+      }
+    }
+  }
+  // Sums over the wavefront, transposed (see wave_sum_transposed): lane l ends with the sum of value l / ST.
+  constexpr int NV = TB * EMAX, ST = 64 / NV;
+  static_assert(NV == 32 || NV == 64, "a wavefront carries 32 or 64 (token, expert) sums");
+  double v[NV];
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+    for (int e = 0; e < EMAX; ++e) v[tb * EMAX + e] = acc[tb][e];
+  wave_sum_transposed<NV, 32>(v, lane);
+  // lane l: pair (token tb, expert e); one exponential and one division per lane
+  const int vi = lane / ST, tb = vi / EMAX, e = vi % EMAX;
+  const double lg = (double)(float)v[0];              // one rounding to fp32
+  const bool live = e < E;
+  double mx = live ? lg : -1e300;
+#pragma unroll
+  for (int off = ST; off < ST * EMAX; off <<= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+  double pr = live ? exp(lg - mx) : 0.0;
+  double den = pr;
+#pragma unroll
+  for (int off = ST; off < ST * EMAX; off <<= 1) den += __shfl_xor(den, off, 64);
+  pr /= den;
+  const int t = t0 + tb;
+  if (probs && live && t < Tn && lane % ST == 0) probs[(size_t)t * E + e] = (float)pr;
+  // the token's logits and probabilities into every lane of its group, then the top-k (ties to the lower index)
+  double logit[EMAX], p[EMAX];
+#pragma unroll
+  for (int ee = 0; ee < EMAX; ++ee) {
+    logit[ee] = __shfl(lg, (tb * EMAX + ee) * ST, 64);
+    p[ee] = __shfl(pr, (tb * EMAX + ee) * ST, 64);
+  }
+  if (lane % (ST * EMAX) == 0 && t < Tn) {            // the group's first lane writes the token's choice
+    unsigned long long taken = 0ull;
+    for (int j = 0; j < k; ++j) {
+      int best = -1;
+      double bv = 0.0, bp = 0.0;
+#pragma unroll
+      for (int ee = 0; ee < EMAX; ++ee) {
+        if (ee < E && !((taken >> ee) & 1ull) && (best < 0 || logit[ee] > bv)) {
+          best = ee; bv = logit[ee]; bp = p[ee];
+        }
+      }
+      taken |= 1ull << best;
+      idx[(size_t)t * k + j] = best;
+      gate[(size_t)t * k + j] = (float)bp;
+      if (hist) atomicAdd(&s_hist[best], 1);
+    }
+  }
+  if (hist) {
+    __syncthreads();
+    if ((int)threadIdx.x < E) hist[(size_t)block * E + threadIdx.x] = s_hist[threadIdx.x];
+  }
+}
+template <typename T, int EMAX, int TB>
+__global__ __launch_bounds__(256) void router_kernel(const T* __restrict__ X, const T* __restrict__ Wr, int Tn, int K, int E, int k,
+                                                     int* __restrict__ idx, float* __restrict__ gate, float* __restrict__ probs, int* __restrict__ hist) {
+  router_body<T, EMAX, TB>(X, Wr, Tn, K, E, k, idx, gate, probs, hist, blockIdx.x);
+}
+// tokens of a router workgroup
+int pq_router_tokens(int E) { return E <= 8 ? 16 : E <= 16 ? 8 : 4; }
+
+
+// ------------------------------------------------------------------------------------------
+// The slots (slot = token * k + j) ordered by expert, slots of one expert in their own order: perm[pos] = slot, inv[slot] = pos,
+// offsets[e] = first position of expert e, and with it the slots' rows of the activations, copied to dst[pos].
+// The router's workgroups have counted their experts (hist).  A workgroup here owns a run of them: it sums what lies before it and in
+// all, per expert, which gives it the first position of each expert's slots, walks its own slots 64 at a time (rank inside a batch by
+// ballot prefix, lane e carrying expert e's running position) and copies their rows.  Any number of workgroups: as a counting sort on
+// one workgroup and a gather in a launch of its own the two took 15 + 12 us for 8192 tokens, 25 + 22 for 16384 (2048 wide).
+// ------------------------------------------------------------------------------------------
+constexpr int PLACE_GROUPS = 512;                    // workgroups at most (each reads all of hist)
+// sub of subs: while there are few runs each goes to several workgroups, which all find its positions and copy every subs-th row
+__device__ __forceinline__ void place_body(const pq_place p, int wg, int groups, int subs) {
+  const int g = wg / subs, sub = wg - g * subs;
+  constexpr int SMAX = 256;                          // slots of a router workgroup: 16 tokens x 8, 8 x 16 or 4 x 64 experts
+  __shared__ int s_pre[256], s_all[256], s_run[64], s_pos[SMAX];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, E = p.E;
+  const int per = (p.nblk + groups - 1) / groups, b0 = min(g * per, p.nblk), b1 = min(b0 + per, p.nblk);
+  {  // thread (e, j): expert e over every J-th workgroup of the router
+    const int J = 256 / E, e = tid % E, j = tid / E;
+    int pre = 0, all = 0;
+    if (j < J) {
+      for (int w0 = j; w0 < p.nblk; w0 += 8 * J) {   // (eight loads in flight, clamped)
+        int v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = p.hist[(size_t)min(w0 + u * J, p.nblk - 1) * E + e];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int w = w0 + u * J;
+          all += w < p.nblk ? v[u] : 0;
+          pre += w < b0 ? v[u] : 0;
+        }
+      }
+    }
+    s_pre[tid] = pre;
+    s_all[tid] = all;
+    __syncthreads();
+    if (wave == 0) {                                 // lane e: expert e
+      int before = 0, total = 0;
+      if (lane < E)
+        for (int q = 0; q < J; ++q) { before += s_pre[q * E + lane]; total += s_all[q * E + lane]; }
+      int incl = total;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int up = __shfl_up(incl, d);
+        if (lane >= d) incl += up;
+      }
+      s_run[lane] = incl - total + before;
+      if (wg == 0) {
+        if (lane < E) {
+          p.offsets[lane] = incl - total;
+          p.counts[lane] = total;
+        }
+        if (lane == E - 1) p.offsets[E] = incl;
+      }
+    }
+    __syncthreads();
+  }
+  for (int b = b0; b < b1; ++b) {                    // uniform
+    const int t0 = b * p.tokens, n = min(p.tokens, p.T - t0) * p.k, slot0 = t0 * p.k;
+    if (wave == 0) {
+      int running = s_run[lane];
+      for (int s0 = 0; s0 < n; s0 += 64) {
+        const int s = s0 + lane, id = s < n ? p.idx[slot0 + s] : -1;
+        int pos = 0;
+        for (int e = 0; e < E; ++e) {
+          const unsigned long long m = __ballot(id == e);
+          const int base = __builtin_amdgcn_readlane(running, e);   // (e is uniform)
+          if (id == e) pos = base + __builtin_popcountll(m & ((1ull << lane) - 1ull));
+          if (lane == e) running += __builtin_popcountll(m);
+        }
+        if (s < n) {
+          s_pos[s] = pos;
+          if (sub == 0) {
+            p.perm[pos] = slot0 + s;
+            p.inv[slot0 + s] = pos;
+          }
+        }
+      }
+      s_run[lane] = running;
+    }
+    __syncthreads();
+    const int nv = p.d / 8;
+    for (int i = wave * subs + sub; i < n; i += 4 * subs) {   // a wavefront copies a row, up to four vectors of a lane in flight
+      const size_t t = (size_t)(t0 + i / p.k), pos = (size_t)s_pos[i];
+      const uint4* src = reinterpret_cast<const uint4*>(p.src + t * p.d);
+      uint4* dst = reinterpret_cast<uint4*>(p.dst + pos * p.d);
+      for (int c0 = lane; c0 < nv; c0 += 256) {
+        const uint4 v0 = src[c0], v1 = src[min(c0 + 64, nv - 1)], v2 = src[min(c0 + 128, nv - 1)], v3 = src[min(c0 + 192, nv - 1)];
+        dst[c0] = v0;
+        if (c0 + 64 < nv) dst[c0 + 64] = v1;
+        if (c0 + 128 < nv) dst[c0 + 128] = v2;
+        if (c0 + 192 < nv) dst[c0 + 192] = v3;
+      }
+      if (p.codes) {                                 // uniform: INT8 experts, the row's codes and gamma too (d % 16 == 0)
+        const uint4* q = reinterpret_cast<const uint4*>(p.codes + t * p.d);
+        uint4* qo = reinterpret_cast<uint4*>(p.codes_out + pos * p.d);
+        for (int c = lane; c < p.d / 16; c += 64) qo[c] = q[c];
+        if (lane == 0) p.gamma_out[pos] = p.gamma[t];
+      }
+    }
+    __syncthreads();
+  }
+}
+static int place_groups(int nblk) { return nblk < 1 ? 1 : nblk < PLACE_GROUPS ? nblk : PLACE_GROUPS; }
+static int place_subs(int nblk) { return nblk <= PLACE_GROUPS / 4 ? 4 : nblk <= PLACE_GROUPS / 2 ? 2 : 1; }
+
 // The first stage of the weight statistics and the activation quantiser of one forward call are independent and
 // each too short to fill its own launch well: one launch, the first nw workgroups take the weights.
 struct slab_sum_job { const float* part; int splits, M, N; uint16_t* C; int ldc; };
@@ -553,15 +779,52 @@ __global__ __launch_bounds__(256) void wstats_quant_kernel(const T* __restrict__
   else pq_slab_sum_bf16_body(sj.part, sj.splits, sj.M, sj.N, sj.C, sj.ldc, (size_t)(b - nw - nq) * 256 + threadIdx.x);
 }
 
+// ... and the router of a call with up to eight experts, which reads the same activations (its workgroups, bound by fp64 sums, first).
+template <int NV>
+__global__ __launch_bounds__(256) void wstats_quant_router_kernel(const uint16_t* __restrict__ W, size_t nvec, double* __restrict__ partials,
+                                                                  int nw, const uint16_t* __restrict__ X, int Tn, int K, int8_t* __restrict__ Xq,
+                                                                  float* __restrict__ gamma, uint16_t* __restrict__ Xt, pq_router_job r, int nr) {
+  const int b = blockIdx.x;
+  if (b < nr) router_body<uint16_t, 8, 4>(X, (const uint16_t*)r.Wr, Tn, K, r.E, r.k, r.idx, r.gate, r.probs, r.hist, b);
+  else if (b < nr + nw) wstats_partial_body<uint16_t>(W, nvec, partials, b - nr, nw);
+  else quant_act_body<uint16_t, NV>(X, Tn, K, Xq, gamma, Xt, b - nr - nw);
+}
+// The router's registers leave two wavefronts to a SIMD, which the quantiser feels where it is bound by memory rather than by its
+// launch.  Forward and backward with the router in a launch of its own / with it here (us): routed linears 2048x2048 of 256 tokens
+// (320 workgroups of statistics and rows) 126.7 / 121.7, 2048 tokens (768) 206.1 / 200.0, 8192 tokens (2304) 404.1 / 401.0; FFNs
+// 2048/5504 of 1024 tokens (2320) 433.5 / 433.4, 4096 tokens (3088) 919.6 / 924.0.
+bool pq_wstats_quant_router_applies(int E, int K, long blocks) { return E <= 8 && K <= 4096 && blocks <= 2304; }
+int pq_launch_wstats_quant_router(const void* W, size_t n_elems, double* partials, int nblocks, const void* X, int T, int K, int8_t* Xq, float* gamma,
+                                  uint16_t* Xt, const pq_router_job& r, hipStream_t s) {
+  if (T <= 0 || r.E > 8 || K > 4096) return pq_set_error(PQ_ERR_SHAPE, "combined statistics/quantiser/router launch: T=%d K=%d E=%d", T, K, r.E);
+  pq_prof_scope prof(PQP_QUANT, s);
+  const int nr = (T + 15) / 16, grid = nr + nblocks + (T + 3) / 4;
+  const uint16_t *w = (const uint16_t*)W, *x = (const uint16_t*)X;
+  if (K <= 2048) wstats_quant_router_kernel<4><<<grid, 256, 0, s>>>(w, n_elems / 8, partials, nblocks, x, T, K, Xq, gamma, Xt, r, nr);
+  else wstats_quant_router_kernel<8><<<grid, 256, 0, s>>>(w, n_elems / 8, partials, nblocks, x, T, K, Xq, gamma, Xt, r, nr);
+  PQ_CHECK_LAUNCH("wstats_quant_router_kernel");
+  return PQ_OK;
+}
+
 // The weight side of the FFN's forward ahead of the packing, and the quantiser of its activations, as one launch (bf16): the
 // statistics of up to three weights, the rows of X, the expert rows [Up_e; Gate_e] of every expert as one matrix, copied or
 // (INT8 experts) put on the AbsMax grid, and the rows of Down_e likewise.  All independent and short: one after the other
 // they were up to seven launches of which each costs a launch of about 5 us whatever it does.  With the packing in one launch and
 // U, G and dW_up, dW_gate paired: FFN step at 153 tokens 992/2136 244 -> 203 us, 3135 tokens 320/924 249 -> 201 us, 4284 tokens
 // 1728/2336 716 -> 668 us, 2048 tokens 2048/5076 703 -> 678 us.
-template <int NV>
+// ROUTE: with the router of up to eight experts, whose workgroups come first.
+template <int NV, bool ROUTE>
 __global__ __launch_bounds__(256) void ffn_prep_kernel(pq_ffn_prep p) {
   int b = blockIdx.x;
+  if constexpr (ROUTE) {
+    const int nr = (p.T + 15) / 16;
+    if (b < nr) {                                    // uniform
+      router_body<uint16_t, 8, 4>((const uint16_t*)p.X, (const uint16_t*)p.route.Wr, p.T, p.D, p.E, p.route.k, p.route.idx, p.route.gate, p.route.probs,
+                                  p.route.hist, b);
+      return;
+    }
+    b -= nr;
+  }
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     if (b < p.w[i].nblocks) {                        // uniform
@@ -605,10 +868,15 @@ int pq_launch_ffn_prep(const pq_ffn_prep& p, hipStream_t s) {
   for (const pq_weight_job& w : p.w) blocks += w.nblocks;
   if (p.UGQ) blocks += (nug + 3) / 4 + ((long)p.E * p.D + 3) / 4;
   else blocks += ((long)nug * (p.D / 8) + 255) / 256;
-  if (per_lane <= 4) ffn_prep_kernel<4><<<(unsigned)blocks, 256, 0, s>>>(p);
-  else if (per_lane <= 8) ffn_prep_kernel<8><<<(unsigned)blocks, 256, 0, s>>>(p);
-  else if (per_lane <= 16) ffn_prep_kernel<16><<<(unsigned)blocks, 256, 0, s>>>(p);
-  else ffn_prep_kernel<0><<<(unsigned)blocks, 256, 0, s>>>(p);
+  if (p.route.Wr) {
+    if (p.E > 8 || p.D > 4096) return pq_set_error(PQ_ERR_SHAPE, "router of %d experts in the launch of the statistics", p.E);
+    blocks += (p.T + 15) / 16;
+    if (per_lane <= 4) ffn_prep_kernel<4, true><<<(unsigned)blocks, 256, 0, s>>>(p);
+    else ffn_prep_kernel<8, true><<<(unsigned)blocks, 256, 0, s>>>(p);
+  } else if (per_lane <= 4) ffn_prep_kernel<4, false><<<(unsigned)blocks, 256, 0, s>>>(p);
+  else if (per_lane <= 8) ffn_prep_kernel<8, false><<<(unsigned)blocks, 256, 0, s>>>(p);
+  else if (per_lane <= 16) ffn_prep_kernel<16, false><<<(unsigned)blocks, 256, 0, s>>>(p);
+  else ffn_prep_kernel<0, false><<<(unsigned)blocks, 256, 0, s>>>(p);
   PQ_CHECK_LAUNCH("ffn_prep_kernel");
   return PQ_OK;
 }
@@ -693,11 +961,40 @@ int pq_launch_pack_quant_rows(const void* W, int N, int K, const double* partial
   PQ_CHECK_LAUNCH("pack_quant_rows_kernel");
   return PQ_OK;
 }
-// three bf16 weights in one launch, the tiles of one after those of the other
-struct pack3_args { pq_weight_job w[3]; };
-template <bool RAGGED>
+// one bf16 weight (npack workgroups, none where it is packed already) behind the ordering of a routed call's slots
+__global__ __launch_bounds__(256) void pack_place_kernel(const uint16_t* __restrict__ W, int N, int K, const double* __restrict__ partials,
+                                                         int G, uint8_t* __restrict__ Pbytes, uint32_t* __restrict__ Pt,
+                                                         float* __restrict__ mu_lambda, int gx, pq_place place, int groups, int subs) {
+  const int b = blockIdx.x;
+  const int np = groups * subs;
+  if (b < np) {                                      // uniform
+    place_body(place, b, groups, subs);
+    return;
+  }
+  pack_sign_body<uint16_t, false>(W, N, K, partials, G, Pbytes, Pt, mu_lambda, (b - np) % gx, (b - np) / gx);
+}
+int pq_launch_pack_place(const void* W, int N, int K, const double* partials, int nblocks, uint32_t* P, uint32_t* Pt, float* mu_lambda,
+                         const pq_place& place, hipStream_t s) {
+  if (N % 32 != 0 || K % 32 != 0) return pq_set_error(PQ_ERR_SHAPE, "N=%d and K=%d must be multiples of 32", N, K);
+  pq_prof_scope prof(PQP_PACK, s);
+  const int gx = (K + 511) / 512, groups = place_groups(place.nblk), subs = place_subs(place.nblk);
+  pack_place_kernel<<<groups * subs + (W ? gx * (N / 32) : 0), 256, 0, s>>>((const uint16_t*)W, N, K, partials, nblocks, (uint8_t*)P, Pt, mu_lambda, gx, place,
+                                                                          groups, subs);
+  PQ_CHECK_LAUNCH("pack_place_kernel");
+  return PQ_OK;
+}
+// three bf16 weights in one launch, the tiles of one after those of the other (PLACE: behind the ordering of the slots)
+struct pack3_args { pq_weight_job w[3]; pq_place place; int groups, subs; };
+template <bool RAGGED, bool PLACE>
 __global__ __launch_bounds__(256) void pack_sign3_kernel(pack3_args a) {
   int b = blockIdx.x, i = 0;
+  if constexpr (PLACE) {
+    if (b < a.groups * a.subs) {                     // uniform
+      place_body(a.place, b, a.groups, a.subs);
+      return;
+    }
+    b -= a.groups * a.subs;
+  }
   int gx = (((a.w[0].K + 31) & ~31) + 511) / 512, n = gx * ((a.w[0].N + 31) / 32);
   while (i < 2 && b >= n) {                          // uniform
     b -= n;
@@ -708,18 +1005,28 @@ __global__ __launch_bounds__(256) void pack_sign3_kernel(pack3_args a) {
   const pq_weight_job& w = a.w[i];
   pack_sign_body<uint16_t, RAGGED>((const uint16_t*)w.W, w.N, w.K, w.partials, w.nblocks, (uint8_t*)w.P, w.Pt, w.mu_lambda, b % gx, b / gx);
 }
-int pq_launch_pack3(const pq_weight_job* w, hipStream_t s) {
+int pq_launch_pack3(const pq_weight_job* w, const pq_place* place, hipStream_t s) {
   pq_prof_scope prof(PQP_PACK, s);
   pack3_args a;
+  memset(&a, 0, sizeof(a));
   bool ragged = false;
   unsigned blocks = 0;
+  if (place) {
+    a.place = *place;
+    a.groups = place_groups(place->nblk);
+    a.subs = place_subs(place->nblk);
+    blocks = (unsigned)(a.groups * a.subs);
+  }
   for (int i = 0; i < 3; ++i) {
     a.w[i] = w[i];
     ragged = ragged || w[i].K % 32 || w[i].N % 32;
     blocks += (unsigned)((((w[i].K + 31) & ~31) + 511) / 512) * ((w[i].N + 31) / 32);
   }
-  if (ragged) pack_sign3_kernel<true><<<blocks, 256, 0, s>>>(a);
-  else pack_sign3_kernel<false><<<blocks, 256, 0, s>>>(a);
+  if (place) {
+    if (ragged) pack_sign3_kernel<true, true><<<blocks, 256, 0, s>>>(a);
+    else pack_sign3_kernel<false, true><<<blocks, 256, 0, s>>>(a);
+  } else if (ragged) pack_sign3_kernel<true, false><<<blocks, 256, 0, s>>>(a);
+  else pack_sign3_kernel<false, false><<<blocks, 256, 0, s>>>(a);
   PQ_CHECK_LAUNCH("pack_sign3_kernel");
   return PQ_OK;
 }
@@ -741,126 +1048,24 @@ int pq_launch_pack(const void* W, int dtype, int N, int K, const double* partial
   return PQ_OK;
 }
 
-// ------------------------------------------------------------------------------------------
-// Router: a wavefront takes TB tokens at once (a router row converted to fp64 serves all of them): fp64 dot products
-// against all E router rows, lane l accumulating the 16-byte chunks l, l + 64, ... of a token row in order, then the
-// wave sums, which leave one (token, expert) pair per lane; that lane rounds the logit to fp32 and evaluates its term
-// of the softmax in fp64; the first lane of a token's group selects the top-k (ties to the lower index).
-// ------------------------------------------------------------------------------------------
-template <typename T, int EMAX, int TB>
-__global__ __launch_bounds__(256) void router_kernel(const T* __restrict__ X, const T* __restrict__ Wr,
-                                                     int Tn, int K, int E, int k, int* __restrict__ idx,
-                                                     float* __restrict__ gate, float* __restrict__ probs) {
-  constexpr int V = vec16<T>::V;
-  const int lane = threadIdx.x & 63;
-  const int t0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * TB;
-  if (t0 >= Tn) return;
-  const int nvec = K / V;
-  double acc[TB][EMAX];
-#pragma unroll
-  for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-    for (int e = 0; e < EMAX; ++e) acc[tb][e] = 0.0;
-  // Router rows are requested unconditionally, eight at a time (rows past E repeat the last one and their sums
-  // are never used; tokens past the end repeat the last token): a load under a branch gets a wait of its own, which
-  // made this loop a chain of latencies.
-  for (int c = lane; c < nvec; c += 64) {
-    double xd[TB][V];
-    uint4 xv[TB];
-#pragma unroll
-    for (int tb = 0; tb < TB; ++tb) xv[tb] = reinterpret_cast<const uint4*>(X + (size_t)min(t0 + tb, Tn - 1) * K)[c];
-#pragma unroll
-    for (int e0 = 0; e0 < EMAX; e0 += 8) {
-      uint4 wv[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) wv[u] = reinterpret_cast<const uint4*>(Wr + (size_t)min(e0 + u, E - 1) * K)[c];
-      if (e0 == 0) {
-#pragma unroll
-        for (int tb = 0; tb < TB; ++tb) {
-          float xf[V];
-          vec16<T>::unpack(xv[tb], xf);
-#pragma unroll
-          for (int j = 0; j < V; ++j) xd[tb][j] = (double)xf[j];
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        float wf[V];
-        vec16<T>::unpack(wv[u], wf);
-#pragma unroll
-        for (int j = 0; j < V; ++j) {
-          const double wd = (double)wf[j];
-#pragma unroll
-          for (int tb = 0; tb < TB; ++tb) acc[tb][e0 + u] += xd[tb][j] * wd;
-        }
-      }
-    }
-  }
-  // Sums over the wavefront, transposed (see wave_sum_transposed): lane l ends with the sum of value l / ST.
-  constexpr int NV = TB * EMAX, ST = 64 / NV;
-  static_assert(NV == 32 || NV == 64, "a wavefront carries 32 or 64 (token, expert) sums");
-  double v[NV];
-#pragma unroll
-  for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-    for (int e = 0; e < EMAX; ++e) v[tb * EMAX + e] = acc[tb][e];
-  wave_sum_transposed<NV, 32>(v, lane);
-  // lane l: pair (token tb, expert e); one exponential and one division per lane
-  const int vi = lane / ST, tb = vi / EMAX, e = vi % EMAX;
-  const double lg = (double)(float)v[0];              // one rounding to fp32
-  const bool live = e < E;
-  double mx = live ? lg : -1e300;
-#pragma unroll
-  for (int off = ST; off < ST * EMAX; off <<= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
-  double pr = live ? exp(lg - mx) : 0.0;
-  double den = pr;
-#pragma unroll
-  for (int off = ST; off < ST * EMAX; off <<= 1) den += __shfl_xor(den, off, 64);
-  pr /= den;
-  const int t = t0 + tb;
-  if (probs && live && t < Tn && lane % ST == 0) probs[(size_t)t * E + e] = (float)pr;
-  // the token's logits and probabilities into every lane of its group, then the top-k (ties to the lower index)
-  double logit[EMAX], p[EMAX];
-#pragma unroll
-  for (int ee = 0; ee < EMAX; ++ee) {
-    logit[ee] = __shfl(lg, (tb * EMAX + ee) * ST, 64);
-    p[ee] = __shfl(pr, (tb * EMAX + ee) * ST, 64);
-  }
-  if (lane % (ST * EMAX) != 0 || t >= Tn) return;     // the group's first lane writes the token's choice
-  unsigned long long taken = 0ull;
-  for (int j = 0; j < k; ++j) {
-    int best = -1;
-    double bv = 0.0, bp = 0.0;
-#pragma unroll
-    for (int ee = 0; ee < EMAX; ++ee) {
-      if (ee < E && !((taken >> ee) & 1ull) && (best < 0 || logit[ee] > bv)) {
-        best = ee; bv = logit[ee]; bp = p[ee];
-      }
-    }
-    taken |= 1ull << best;
-    idx[(size_t)t * k + j] = best;
-    gate[(size_t)t * k + j] = (float)bp;
-  }
-}
-
 template <typename T>
 static int launch_router_t(const T* X, const T* Wr, int Tn, int K, int E, int k, int* idx, float* gate,
-                           float* probs, hipStream_t s) {
-  dim3 block(256);
-  if (E <= 8) router_kernel<T, 8, 4><<<dim3((Tn + 15) / 16), block, 0, s>>>(X, Wr, Tn, K, E, k, idx, gate, probs);
-  else if (E <= 16) router_kernel<T, 16, 2><<<dim3((Tn + 7) / 8), block, 0, s>>>(X, Wr, Tn, K, E, k, idx, gate, probs);
-  else router_kernel<T, 64, 1><<<dim3((Tn + 3) / 4), block, 0, s>>>(X, Wr, Tn, K, E, k, idx, gate, probs);
+                           float* probs, hipStream_t s, int* hist) {
+  const dim3 block(256), grid((Tn + pq_router_tokens(E) - 1) / pq_router_tokens(E));
+  if (E <= 8) router_kernel<T, 8, 4><<<grid, block, 0, s>>>(X, Wr, Tn, K, E, k, idx, gate, probs, hist);
+  else if (E <= 16) router_kernel<T, 16, 2><<<grid, block, 0, s>>>(X, Wr, Tn, K, E, k, idx, gate, probs, hist);
+  else router_kernel<T, 64, 1><<<grid, block, 0, s>>>(X, Wr, Tn, K, E, k, idx, gate, probs, hist);
   PQ_CHECK_LAUNCH("router_kernel");
   return PQ_OK;
 }
 
 int pq_launch_router(const void* X, const void* Wr, int dtype, int T, int K, int E, int k, int* idx,
-                     float* gate, float* probs, hipStream_t s) {
+                     float* gate, float* probs, hipStream_t s, int* hist) {
   if (T == 0) return PQ_OK;
   pq_prof_scope prof(PQP_ROUTER, s);
   if (dtype == PQ_F32)
-    return launch_router_t<float>((const float*)X, (const float*)Wr, T, K, E, k, idx, gate, probs, s);
-  return launch_router_t<uint16_t>((const uint16_t*)X, (const uint16_t*)Wr, T, K, E, k, idx, gate, probs, s);
+    return launch_router_t<float>((const float*)X, (const float*)Wr, T, K, E, k, idx, gate, probs, s, hist);
+  return launch_router_t<uint16_t>((const uint16_t*)X, (const uint16_t*)Wr, T, K, E, k, idx, gate, probs, s, hist);
 }
 
 // ------------------------------------------------------------------------------------------
