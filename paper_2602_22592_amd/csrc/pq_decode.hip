@@ -1297,24 +1297,14 @@ constexpr int G16_ROWS_PER_BLOCK = 4 * G16_ROWS_PER_WAVE;
 // selected (token, expert) hidden state is put on the INT8 grid with its own gamma (Sec. 3.1 quantiser), one
 // wavefront per slot; behind the codes sit 1/gamma_h and the gate per (token, expert), zero where not selected.
 // Columns [k0, k0 + kcols) of the batch's codes into xs, rows `stride` bytes apart (kcols and stride multiples of 128)
-// (All loads below are unconditional, with clamped indices, and in batches ahead of the stores that use them: a load under a branch, or
-// behind a store to LDS, waits for its own latency, and a workgroup's start was a chain of some twenty of them.)
 template <int TOKS>
 __device__ __forceinline__ void g16_stage_codes(const gemm16_params& p, int layer, unsigned char* xs, int k0, int kcols, int stride) {
-  const int kch = kcols / 16, total = TOKS * kch;
-  const int8_t* src = p.xq + (size_t)layer * p.B * p.K + k0;
-  for (int c0 = threadIdx.x; c0 < total; c0 += 2048) {   // (one turn for a block of the codes)
-    uint4 v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int c = min(c0 + 256 * u, total - 1), j = c / kch;
-      v[u] = *reinterpret_cast<const uint4*>(src + (size_t)min(j, p.B - 1) * p.K + (c - j * kch) * 16);
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int c = c0 + 256 * u, j = c / kch, cc = c - j * kch;
-      if (c < total) *reinterpret_cast<uint4*>(xs + (size_t)j * stride + ((cc ^ (j & 7)) << 4)) = j < p.B ? v[u] : make_uint4(0, 0, 0, 0);
-    }
+  const int kch = kcols / 16;
+  for (int c = threadIdx.x; c < TOKS * kch; c += 256) {
+    const int j = c / kch, cc = c % kch;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (j < p.B) v = *reinterpret_cast<const uint4*>(p.xq + ((size_t)layer * p.B + j) * p.K + k0 + cc * 16);
+    *reinterpret_cast<uint4*>(xs + (size_t)j * stride + ((cc ^ (j & 7)) << 4)) = v;
   }
 }
 
@@ -1322,58 +1312,50 @@ __device__ __forceinline__ void g16_stage_codes(const gemm16_params& p, int laye
 template <int TOKS, bool I8 = false>
 __device__ __forceinline__ unsigned long long g16_stage_inputs(const gemm16_params& p, int layer, unsigned char* xs,
                                                                uint16_t* hm, int kcols) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x;
   const int Er = p.E * p.r;
-  const int nslot = p.r > 0 ? p.B * p.topk : 0;       // <= 16 * 64
-  const int* idx = p.idx + (size_t)layer * nslot;
-  const float* gate = p.gate + (size_t)layer * nslot;
-  const float* hs = p.h + (size_t)layer * nslot * p.r;
-  int e_lane = -1;                                    // lane s: slot s's expert (the first 64 slots)
-  if (nslot > 0) {
-    const int e = idx[min(lane, nslot - 1)];
-    e_lane = lane < nslot ? e : -1;
-  }
   g16_stage_codes<TOKS>(p, layer, xs, 0, kcols, kcols);
   for (int c = tid; c < TOKS * Er / 8; c += 256) reinterpret_cast<uint4*>(hm)[c] = make_uint4(0, 0, 0, 0);
-  float* inv = nullptr;                               // INT8: [TOKS][E] 1/gamma_h, then [TOKS][E] gates
-  if constexpr (I8) {
-    inv = reinterpret_cast<float*>(reinterpret_cast<int8_t*>(hm) + (size_t)TOKS * Er);
-    for (int c = tid; c < 2 * TOKS * p.E; c += 256) inv[c] = 0.0f;
-  }
   __syncthreads();
   unsigned long long used = 0ull;
-  if (nslot > 0) {
-    // every wavefront builds the mask of selected experts: lane s holds slot s, a ballot per expert bit
+  if (p.r > 0) {
+    // every wavefront builds the mask of selected experts: lane s reads slot s, a ballot per expert bit
+    const int nslot = p.B * p.topk;                  // <= 16 * 64
     for (int s0 = 0; s0 < nslot; s0 += 64) {
-      const int e = s0 == 0 ? e_lane : s0 + lane < nslot ? idx[s0 + lane] : -1;
+      const int s = s0 + (tid & 63);
+      const int e = s < nslot ? p.idx[(size_t)layer * nslot + s] : -1;
       for (int ee = 0; ee < p.E; ++ee) used |= (__ballot(e == ee) != 0ull) ? (1ull << ee) : 0ull;
     }
     if constexpr (I8) {
       int8_t* hq = reinterpret_cast<int8_t*>(hm);
+      float* inv = reinterpret_cast<float*>(hq + (size_t)TOKS * Er);      // [TOKS][E] 1/gamma_h, then [TOKS][E] gates
       float* gts = inv + TOKS * p.E;
-      for (int s0 = wave; s0 < nslot; s0 += 16) {     // wave-uniform: four slots at a time
-        float v[4][2], gt[4], amax[4];
-        int e[4];
+      for (int c = tid; c < 2 * TOKS * p.E; c += 256) inv[c] = 0.0f;
+      __syncthreads();
+      const int lane = tid & 63, wave = tid >> 6;
+      // Four slots at a time where a wavefront has them: one after the other they were a chain of eight memory latencies (8 tokens, two
+      // experts each).  The codes' staging stays as it is: its loads in batches of eight or four were spills beside the weights in
+      // flight, 64 layers 4096 -> 11008 with bf16 experts 239 -> 251 us.
+      auto slots = [&](auto n_c, int s0) {
+        constexpr int U = decltype(n_c)::value;
+        float v[U][2], gt[U];
+        int e[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int s = min(s0 + 4 * u, nslot - 1);
-          e[u] = idx[s];
-          gt[u] = gate[s];
+        for (int u = 0; u < U; ++u) {
+          const int s = s0 + 4 * u;
+          e[u] = p.idx[(size_t)layer * nslot + s];
+          gt[u] = p.gate[(size_t)layer * nslot + s];
 #pragma unroll
-          for (int q = 0; q < 2; ++q) v[u][q] = hs[(size_t)s * p.r + min(lane + 64 * q, p.r - 1)];   // (past the end: the last one again)
+          for (int q = 0; q < 2; ++q) v[u][q] = p.h[((size_t)layer * nslot + s) * p.r + min(lane + 64 * q, p.r - 1)];   // (past the end: the last one again)
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int s = min(s0 + 4 * u, nslot - 1);
-          amax[u] = fmaxf(fabsf(v[u][0]), fabsf(v[u][1]));
-          for (int rr = lane + 128; rr < p.r; rr += 64) amax[u] = fmaxf(amax[u], fabsf(hs[(size_t)s * p.r + rr]));
-          amax[u] = wave_max(amax[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < U; ++u) {
           const int s = s0 + 4 * u, j = s / p.topk;
-          if (s >= nslot) break;                      // wave-uniform
-          const float gh = 128.0f / fmaxf(amax[u], 1e-5f);
+          const float* hs = p.h + ((size_t)layer * nslot + s) * p.r;
+          float amax = fmaxf(fabsf(v[u][0]), fabsf(v[u][1]));
+          for (int rr = lane + 128; rr < p.r; rr += 64) amax = fmaxf(amax, fabsf(hs[rr]));
+          amax = wave_max(amax);
+          const float gh = 128.0f / fmaxf(amax, 1e-5f);
           auto put = [&](int rr, float x) {
             const int q = (int)fminf(fmaxf(rintf(__fmul_rn(x, gh)), -128.0f), 127.0f);
             const int col = e[u] * p.r + rr;
@@ -1381,32 +1363,25 @@ __device__ __forceinline__ unsigned long long g16_stage_inputs(const gemm16_para
           };
           if (lane < p.r) put(lane, v[u][0]);
           if (lane + 64 < p.r) put(lane + 64, v[u][1]);
-          for (int rr = lane + 128; rr < p.r; rr += 64) put(rr, hs[(size_t)s * p.r + rr]);
+          for (int rr = lane + 128; rr < p.r; rr += 64) put(rr, hs[rr]);
           if (lane == 0) {
             inv[j * p.E + e[u]] = 1.0f / gh;
             gts[j * p.E + e[u]] = gt[u];
           }
         }
+      };
+      for (int s = wave; s < nslot;) {                // wave-uniform
+        if (s + 12 < nslot) { slots(std::integral_constant<int, 4>{}, s); s += 16; }
+        else { slots(std::integral_constant<int, 1>{}, s); s += 4; }
       }
     } else {
-      const int total = nslot * p.r;
-      for (int c0 = tid; c0 < total; c0 += 1024) {
-        float h[4], gt[4];
-        int e[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int c = min(c0 + 256 * u, total - 1), s = c / p.r;
-          e[u] = idx[s];
-          gt[u] = gate[s];
-          h[u] = hs[c];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int c = c0 + 256 * u, s = c / p.r, rr = c - s * p.r, j = s / p.topk;
-          const int col = e[u] * p.r + rr;            // 16-byte chunk (col/8) stored at chunk ^ (j & 7)
-          if (c < total) hm[(size_t)j * Er + ((((col >> 3) ^ (j & 7)) << 3) | (col & 7))] = f32_to_bf16(gt[u] * h[u]);
-        }
-      }
+    for (int c = tid; c < p.B * p.topk * p.r; c += 256) {
+      const int rr = c % p.r, s = c / p.r, j = s / p.topk;
+      const int e = p.idx[(size_t)layer * p.B * p.topk + s];
+      const float v = p.gate[(size_t)layer * p.B * p.topk + s] * p.h[((size_t)layer * p.B * p.topk + s) * p.r + rr];
+      const int col = e * p.r + rr;                  // 16-byte chunk (col/8) stored at chunk ^ (j & 7)
+      hm[(size_t)j * Er + ((((col >> 3) ^ (j & 7)) << 3) | (col & 7))] = f32_to_bf16(v);
+    }
     }
   }
   __syncthreads();
