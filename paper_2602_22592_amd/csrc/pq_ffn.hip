@@ -406,14 +406,18 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
   if (int e = pq_launch_expert_act_bwd(ws + L.da, cx + L.ue, cx + L.ue + (size_t)r * 2, a_fwd, one ? nullptr : perm, gate, d->alpha, S, r, 2 * r,
                                        ws + L.du, ws + L.du + (size_t)r * 2, ws + L.as, one ? dWr : nullptr, D, jobs, s)) return e;
   if (T > 0) {
-    {  // dHd = beta * lambda_d * dY S_d
+    {  // dHd = beta * lambda_d * dY S_d, and through the gated unit: dU = dHd silu(G), dG = dHd U silu'(G)
       pq_operand A{dY, D, PQ_SRC_KC16, nullptr};
       pq_operand B{cx + L.Pt_down, D / 8, PQ_SRC_BITS16, nullptr};
-      pq_epilogue e = epi0();
-      e.C = ws + L.dHd; e.ldc = F; e.out_kind = PQ_OUT_BF16; e.scale = d->beta; e.dev_scale = ml_down + 1;
-      if (int err = pq_launch_gemm(T, F, D, A, B, e, s, PQP_GEMM_DX, sk)) return err;
+      if (pq_gemm_swiglu_applies(T, F, D)) {
+        if (int err = pq_launch_gemm_swiglu(T, F, D, A, B, d->beta, ml_down + 1, {cx + L.U, cx + L.G, ws + L.dU, ws + L.dG, Fv}, s, PQP_GEMM_DX)) return err;
+      } else {
+        pq_epilogue e = epi0();
+        e.C = ws + L.dHd; e.ldc = F; e.out_kind = PQ_OUT_BF16; e.scale = d->beta; e.dev_scale = ml_down + 1;
+        if (int err = pq_launch_gemm(T, F, D, A, B, e, s, PQP_GEMM_DX, sk)) return err;
+        if (int err = pq_launch_swiglu_bwd(ws + L.dHd, cx + L.U, cx + L.G, T, F, Fv, ws + L.dU, ws + L.dG, s)) return err;
+      }
     }
-    if (int err = pq_launch_swiglu_bwd(ws + L.dHd, cx + L.U, cx + L.G, T, F, Fv, ws + L.dU, ws + L.dG, s)) return err;
     {  // dX = lambda_u dU S_u + lambda_g dG S_g
       pq_operand A{ws + L.dU, F, PQ_SRC_KC16, nullptr};
       pq_operand B{cx + L.Pt_up, F / 8, PQ_SRC_BITS16, nullptr};

@@ -237,6 +237,12 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
 // ---- pq_tile.hip: the 64x64 and 128x128 streaming tiles (pl.bm; the contraction split is the caller's plan) ----
 int pq_launch_tile(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi, hipStream_t s,
                    float* part, const pq_gemm_group& grp, const pq_phase2& ph2, const pq_gemm_second* second = nullptr);
+// dHd [M][N] = scale [* *dev_scale] * A B^T, rounded to bf16, straight into dU and dG of the gated unit Hd = silu(G) U (all [M][N] bf16, columns
+// from Fv on written as zeros)
+struct pq_gemm_act { const void *U, *G; void *dU, *dG; int Fv; };
+bool pq_gemm_swiglu_applies(int M, int N, int K);
+int pq_launch_gemm_swiglu(int M, int N, int K, const pq_operand& A, const pq_operand& B, float scale, const float* dev_scale, const pq_gemm_act& act,
+                          hipStream_t s, int prof_label);
 // a product as its launch takes it
 struct pq_tile_call {
   int M, N, K;

@@ -1,7 +1,7 @@
 // Element-wise kernels of the decoupled FFN and the routed experts (Sec. 3.2, 3.3): row gather, the gated unit with fused AbsMax re-quantisation,
 // expert activation forward/backward, gate/alpha reductions, router backward, scatter-combine.
 // All tensors here are bf16 unless noted; every reduction has a fixed order.
-#include "pq_internal.h"
+#include "pq_epilogue.h"
 
 namespace {
 
@@ -126,19 +126,10 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(const uint16_t* __restr
       if (q == 1 && !two) break;
       const size_t c = q ? c1 : c0;
       const int col = (int)(c % (size_t)vpr) * 8;
-      float dh[8], uf[8], gf[8], du[8], dg[8];
-      unpack8(q ? r1[0] : r0[0], dh);
-      unpack8(q ? r1[1] : r0[1], uf);
-      unpack8(q ? r1[2] : r0[2], gf);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float sg = pq_sigmoid(gf[j]);
-        const bool ok = col + j < Fv;
-        du[j] = ok ? dh[j] * (gf[j] * sg) : 0.0f;
-        dg[j] = ok ? dh[j] * uf[j] * (sg * (1.0f + gf[j] * (1.0f - sg))) : 0.0f;
-      }
-      reinterpret_cast<uint4*>(dU)[c] = pack8(du);
-      reinterpret_cast<uint4*>(dG)[c] = pack8(dg);
+      uint4 du, dg;
+      pq_swiglu_bwd8(q ? r1[0] : r0[0], q ? r1[1] : r0[1], q ? r1[2] : r0[2], col, Fv, du, dg);
+      reinterpret_cast<uint4*>(dU)[c] = du;
+      reinterpret_cast<uint4*>(dG)[c] = dg;
     }
   }
 }
