@@ -657,7 +657,8 @@ extern "C" int pq_linear_fwd(const pq_linear_desc* d, const void* X, const void*
 // along where the launch has room for them.
 static int hp_int8_dh(const void* dY, int T, int N, int r, float alpha, const char* cx, const hp8_layout& L, char* ws, double* red_a, hipStream_t s);
 static int hp_int8_factor_grads(const void* dY, const void* Xt, int T, int K, int N, int r, float alpha, const char* cx, const hp8_layout& L,
-                                float* dA, float* dB, char* ws, const pq_reduce_job* jobs, bool* jobs_done, hipStream_t s);
+                                float* dA, float* dB, char* ws, const pq_reduce_job* jobs, bool* jobs_done, hipStream_t s,
+                                const pq_grads* along);
 
 // fp32 I/O: the same products at reference precision; large ones of dX and dW as exact integer products of fixed-point digits
 // (pq_fixed.hip), whose sums the launches below finish.  What depends on nothing (dW, dH, dB) is one launch, what needs dH
@@ -785,6 +786,10 @@ static int linear_bwd_impl(const pq_linear_desc* d, const void* dY, const void* 
   }
   pq_gemm_call set[2];
   int n_set = 1;
+  pq_grads grads;                                    // what is left to the launch of the factor gradients
+  grads.has_x = false;
+  grads.sk = sk_ws;
+  const bool dW_last = T > 0 && (hp8 || r > 0);
   if (T > 0) {  // dX = beta*lambda * dY S  (+ dH A, fused into the same tile)
     pq_operand A{dY, N, PQ_SRC_KC16, nullptr};
     pq_operand B{cx + L.Pt, N / 8, PQ_SRC_BITS16, nullptr};
@@ -796,11 +801,12 @@ static int linear_bwd_impl(const pq_linear_desc* d, const void* dY, const void* 
     const void* A2p = hp8 ? (const void*)(cx + L.hp8 + H8.At) : hpA;
     const bool fuse = r2 > 0 && pq_plan_fuses(pq_plan_gemm(T, K, N, false, false, PQ_PLAN_SIGNS));
     if (fuse) {
-      pq_phase2 p2;
+      pq_phase2& p2 = grads.p2;
       p2.A2 = pq_operand{dH2, r2, PQ_SRC_KC16, nullptr};
       p2.B2 = pq_operand{A2p, K, PQ_SRC_KS16, nullptr};
       p2.K2 = r2; p2.scale1 = d->beta; p2.dev_scale1 = mulam + 1; p2.row_div1 = nullptr;
-      if (int err = pq_launch_gemm(T, K, N, A, B, e, s, PQP_GEMM_DX, sk_ws, nullptr, &p2)) return err;
+      grads.x = pq_gemm_call{T, K, N, A, B, e, nullptr, PQP_GEMM_DX};
+      grads.has_x = true;
     } else {
       e.scale = d->beta; e.dev_scale = mulam + 1;
       if (r2 == 0) {                 // nothing between it and dW: they go together
@@ -828,7 +834,9 @@ static int linear_bwd_impl(const pq_linear_desc* d, const void* dY, const void* 
       e.maskW = W; e.mask_kind = ok; e.mu_dev = mulam; e.tau = d->ste_tau;
     }
     set[0] = pq_gemm_call{N, K, T, A, B, e, nullptr, PQP_GEMM_DW};
-    if (n_set == 2) {
+    grads.w = set[0];
+    if (dW_last) {                   // with the factor gradients below
+    } else if (n_set == 2) {
       if (int err = pq_launch_gemm_set(set, 2, s, sk_ws)) return err;
     } else if (int err = pq_launch_gemm(N, K, T, A, B, e, s, PQP_GEMM_DW, sk_ws)) return err;
   }
@@ -882,14 +890,15 @@ static int linear_bwd_impl(const pq_linear_desc* d, const void* dY, const void* 
                                  {red_b, L.n_red_b, 1.0f, mulam + 1, dalpha_dbeta + 1}};
   bool jobs_done = routed;   // (the routed path's own last reduction carries them)
   if (hp8)
-    if (int e = hp_int8_factor_grads(dY, cx + L.Xt, T, K, N, d->hp_rank, d->alpha, cx + L.hp8, H8, dhpA, dhpB, ws + L.hp8_ws, jobs, &jobs_done, s)) return e;
+    if (int e = hp_int8_factor_grads(dY, cx + L.Xt, T, K, N, d->hp_rank, d->alpha, cx + L.hp8, H8, dhpA, dhpB, ws + L.hp8_ws, jobs, &jobs_done, s,
+                                     dW_last ? &grads : nullptr)) return e;
   if (r > 0 && T > 0) {
     // dB = alpha * dY^T H and dA = dH^T X (dH already carries alpha): two narrow GEMMs over the same contraction,
     // one launch when their plans agree; the two scalar reductions then ride along with their split reduction
     pq_operand A0{dY, N, PQ_SRC_KS16, nullptr}, B0{H, r, PQ_SRC_KS16, nullptr};
     pq_operand A1{dH, r, PQ_SRC_KS16, nullptr}, B1{X, K, PQ_SRC_KS16, nullptr};
     if (int err = pq_launch_gemm_pair_ks16(T, N, r, A0, B0, dhpB, r, d->alpha, r, K, A1, B1, dhpA, K, 1.0f, s, PQP_GEMM_DB, PQP_GEMM_DA,
-                                           sk_ws, {ws + L.splitk2, L.splitk2_bytes}, jobs, &jobs_done)) return err;
+                                           sk_ws, {ws + L.splitk2, L.splitk2_bytes}, jobs, &jobs_done, &grads)) return err;
   }
   if (!jobs_done)
     if (int err = pq_launch_reduce_partials2(jobs[0].partials, jobs[0].n, 1.0f, nullptr, jobs[0].out, jobs[1].partials, jobs[1].n, 1.0f,
@@ -1086,7 +1095,7 @@ extern "C" int pq_hp_int8_bwd(const void* dY, const void* Xt, int32_t dtype, int
   char* ws = (char*)workspace;
   if (T > 0)
     if (int e = hp_int8_dh(dY, T, N, r, alpha, cx, L, ws, nullptr, s)) return e;
-  if (int e = hp_int8_factor_grads(dY, Xt, T, K, N, r, alpha, cx, L, dA, dB, ws, nullptr, nullptr, s)) return e;
+  if (int e = hp_int8_factor_grads(dY, Xt, T, K, N, r, alpha, cx, L, dA, dB, ws, nullptr, nullptr, s, nullptr)) return e;
   if (T > 0) {  // dX (+)= dH A~
     pq_operand a{ws + L.dH, r, PQ_SRC_KC16, nullptr};
     pq_operand b{cx + L.At, K, PQ_SRC_KS16, nullptr};
@@ -1109,13 +1118,14 @@ static int hp_int8_dh(const void* dY, int T, int N, int r, float alpha, const ch
 }
 
 static int hp_int8_factor_grads(const void* dY, const void* Xt, int T, int K, int N, int r, float alpha, const char* cx, const hp8_layout& L,
-                                float* dA, float* dB, char* ws, const pq_reduce_job* jobs, bool* jobs_done, hipStream_t s) {
+                                float* dA, float* dB, char* ws, const pq_reduce_job* jobs, bool* jobs_done, hipStream_t s,
+                                const pq_grads* along) {
   // dB = alpha * dY^T H~ and dA = dH^T X~ (dH already carries alpha): one launch when their shapes allow it
   const void* dH = ws + L.dH;
   pq_operand a0{dY, N, PQ_SRC_KS16, nullptr}, b0{cx + L.Ht, r, PQ_SRC_KS16, nullptr};
   pq_operand a1{dH, r, PQ_SRC_KS16, nullptr}, b1{Xt, K, PQ_SRC_KS16, nullptr};
   return pq_launch_gemm_pair_ks16(T, N, r, a0, b0, dB, r, alpha, r, K, a1, b1, dA, K, 1.0f, s, PQP_GEMM_DB, PQP_GEMM_DA, {ws + L.splitk, L.splitk_bytes},
-                                  {ws + L.splitk2, L.splitk2_bytes}, jobs, jobs_done);
+                                  {ws + L.splitk2, L.splitk2_bytes}, jobs, jobs_done, along);
 }
 
 // ---------------------------------------------------------------------------------------------

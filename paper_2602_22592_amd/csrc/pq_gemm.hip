@@ -1909,10 +1909,20 @@ pq_pair_plan pq_plan_pair(int K, int M0, int N0, int M1, int N1) {
   return p;
 }
 
+static int check_epilogue(int M, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi);
+static pq_gemm_plan plan_call(int M, int N, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi, const pq_gemm_group& grp,
+                              pq_scratch sk);
+// A product on 64x64 tiles, not split: c is its launch.
+static bool pq_plain_64(const pq_gemm_call& w, pq_scratch sk, pq_tile_call* c) {
+  if (w.M <= 0 || w.N <= 0 || w.K <= 0 || check_epilogue(w.M, w.A, w.B, w.epi)) return false;
+  *c = pq_tile_call{w.M, w.N, w.K, w.A, w.B, w.epi, {}, {}, nullptr};
+  c->pl = plan_call(w.M, w.N, w.K, w.A, w.B, w.epi, c->grp, sk);
+  return c->pl.bm == 64 && c->pl.bn == 64 && c->pl.splits == 1;
+}
 int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const pq_operand& B0, float* C0, int ldc0, float scale0,
                              int M1, int N1, const pq_operand& A1, const pq_operand& B1, float* C1, int ldc1, float scale1,
                              hipStream_t s, int prof_label0, int prof_label1, pq_scratch sk0, pq_scratch sk1,
-                             const pq_reduce_job* jobs, bool* jobs_done) {
+                             const pq_reduce_job* jobs, bool* jobs_done, const pq_grads* along) {
   if (jobs_done) *jobs_done = false;
   pq_epilogue e0;
   memset(&e0, 0, sizeof(e0));
@@ -1927,6 +1937,21 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
   const bool one = M0 > 0 && N0 > 0 && M1 > 0 && N1 > 0 && K > 0 && al(A0) && al(B0) && al(A1) && al(B1) && A0.ld >= M0 && B0.ld >= N0 &&
                    A1.ld >= M1 && B1.ld >= N1 &&
                    (pp.splits == 1 || (sk0.p && sk1.p && ((uintptr_t)sk0.p % 16) == 0 && ((uintptr_t)sk1.p % 16) == 0));
+  if (along) {
+    // where dW takes 64x64 tiles and is not split, those of dB and dA, not split either, end with its own
+    pq_tile_call c[3], x;
+    const pq_gemm_call &w = along->w, &xc = along->x;
+    const bool w_too = one && !pp.apart && !pp.tn && pq_plain_64(w, along->sk, &c[0]), x_too = w_too && along->has_x && pq_plain_64(xc, along->sk, &x);
+    if (along->has_x && !x_too)
+      if (int rc = pq_launch_gemm(xc.M, xc.N, xc.K, xc.A, xc.B, xc.epi, s, xc.prof_label, along->sk, nullptr, &along->p2)) return rc;
+    if (w_too) {
+      c[1] = pq_tile_call{M0, N0, K, A0, B0, e0, c[0].grp, c[0].pl, nullptr};
+      c[2] = pq_tile_call{M1, N1, K, A1, B1, e1, c[0].grp, c[0].pl, nullptr};
+      pq_prof_scope prof(w.prof_label, s);
+      return pq_launch_tile_grads(c, x_too ? &x : nullptr, x_too ? &along->p2 : nullptr, s);
+    }
+    if (int rc = pq_launch_gemm(w.M, w.N, w.K, w.A, w.B, w.epi, s, w.prof_label, along->sk)) return rc;
+  }
   if (!one || pp.apart) {
     if (int rc = pq_launch_gemm(M0, N0, K, A0, B0, e0, s, prof_label0, sk0)) return rc;
     return pq_launch_gemm(M1, N1, K, A1, B1, e1, s, prof_label1, sk1);

@@ -230,10 +230,13 @@ int pq_launch_skinny(int M, int K, const pq_operand& A, const pq_operand& B, con
 
 // Two bf16 GEMMs with contraction-strided operands on both sides (the rank-r weight gradients dA and dB), in one launch where
 // pq_plan_pair finds that better.  Both have plain epilogues: C (fp32) = scale * acc.
+// along (may be NULL): the rest of a linear's backward behind dH, which goes before them or in their launch: dW (the same kinds and
+// contraction) and, if has_x, dX with the branch's share as its second contraction.
 int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const pq_operand& B0, float* C0, int ldc0, float scale0,
                              int M1, int N1, const pq_operand& A1, const pq_operand& B1, float* C1, int ldc1, float scale1,
                              hipStream_t s, int prof_label0, int prof_label1, pq_scratch sk0, pq_scratch sk1,
-                             const pq_reduce_job* jobs = nullptr, bool* jobs_done = nullptr);   // jobs: two scalar reductions to ride along
+                             const pq_reduce_job* jobs = nullptr, bool* jobs_done = nullptr,   // jobs: two scalar reductions to ride along
+                             const struct pq_grads* along = nullptr);
 // ---- pq_tile.hip: the 64x64 and 128x128 streaming tiles (pl.bm; the contraction split is the caller's plan) ----
 int pq_launch_tile(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi, hipStream_t s,
                    float* part, const pq_gemm_group& grp, const pq_phase2& ph2, const pq_gemm_second* second = nullptr);
@@ -253,6 +256,8 @@ struct pq_tile_call {
   float* part;
 };
 bool pq_tile_set_applies(const pq_tile_call* w0, const pq_tile_call* w1, const pq_tile_call& x);   // (w1 may be NULL)
+// 64x64 tiles, nothing split: three products of contraction-strided operands and, with x, one of packed signs with a second contraction
+int pq_launch_tile_grads(const pq_tile_call (&c)[3], const pq_tile_call* x, const pq_phase2* p2, hipStream_t s);
 int pq_launch_tile_set(const pq_tile_call* w0, const pq_tile_call* w1, const pq_tile_call& x, hipStream_t s);
 // Up to three products that do not depend on each other: n - 1 weight gradients (one or two), then a product of a contraction-contiguous
 // operand with signs or a contraction-strided one.  One launch where they all take small tiles and their slabs fit side by side
@@ -263,6 +268,12 @@ struct pq_gemm_call {
   pq_epilogue epi;
   const pq_gemm_group* grp;
   int prof_label;
+};
+struct pq_grads {
+  pq_gemm_call w, x;
+  pq_phase2 p2;
+  bool has_x;
+  pq_scratch sk;
 };
 int pq_launch_gemm_set(const pq_gemm_call* c, int n, hipStream_t s, pq_scratch sk);
 pq_gemm_plan pq_plan_dual(int M, int N, int K, bool int8);   // (its ws_bytes: the slabs of both)

@@ -850,6 +850,34 @@ __global__ __launch_bounds__(256) void tile_set_kernel(tile_job w0, tile_job w1,
   W::run(w, second ? b - w0.blocks : b, smem, red);
 }
 
+// What follows dH in the backward of a linear with a dense branch, where all of it takes 64x64 tiles and nothing is split: workgroups of
+// dX (with X), then of dW, dB and dA (j0, j1, j2), which share a contraction.  Each is one chain of latencies; the branch's gradients
+// alone fill a fraction of the chip (32 to 70 tiles) and were split and added where that paid.  In one launch instead of three or four
+// (whole call, forward and backward): 64 tokens 256 -> 256, r = 16, 47.8 -> 37.5 us; 512 tokens 512 -> 512, r = 64, 56.7 -> 43.0; 701 tokens
+// 608 -> 2048, r = 40, 77.4 -> 61.0; 236 tokens 2560 -> 672, r = 160, INT8 branch, 84.4 -> 72.5; without dX, which takes other tiles there: 3032
+// tokens 1504 -> 480, r = 16, 111.0 -> 102.5; 1724 tokens 1984 -> 736, r = 32, INT8 branch, 107.1 -> 99.2.
+template <int NG, bool X>
+__global__ __launch_bounds__(256) void tile64_grads_kernel(tile_job x, pq_phase2 p2, tile_job j0, tile_job j1, tile_job j2) {
+  constexpr int LW = tile64_lds<NG, PQ_SRC_KS16, PQ_SRC_KS16, -1>(), LX = X ? tile64_lds<NG, PQ_SRC_KC16, PQ_SRC_BITS16, PQ_SRC_KS16>() : 0;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[LW > LX ? LW : LX];
+  __shared__ double red[4];
+  int b = blockIdx.x;
+  if constexpr (X) {
+    if (b < x.blocks) {                              // uniform
+      tile64_body<NG, false, PQ_SRC_KC16, PQ_SRC_BITS16, PQ_SRC_KS16>(x.M, x.N, x.K, x.A, x.B, x.epi, x.nbn, x.tiles, x.kchunk, nullptr, x.grp, p2, b, 0, 0,
+                                                                      1, smem, red);
+      return;
+    }
+    b -= x.blocks;
+  }
+  const int n1 = j0.blocks + j1.blocks;
+  const tile_job& j = b < j0.blocks ? j0 : b < n1 ? j1 : j2;   // uniform
+  pq_phase2 none;
+  none.K2 = 0;
+  tile64_body<NG, false, PQ_SRC_KS16, PQ_SRC_KS16, -1>(j.M, j.N, j.K, j.A, j.B, j.epi, j.nbn, j.tiles, j.kchunk, nullptr, j.grp, none,
+                                                       b < j0.blocks ? b : b < n1 ? b - j0.blocks : b - n1, 0, 0, 1, smem, red);
+}
+
 template <int WBM, int XBM, int XBK>
 int launch_set(const tile_job& w0, const tile_job& w1, const tile_job& x, hipStream_t s) {
   tile_set_kernel<WBM, XBM, XBK><<<w0.blocks + w1.blocks + x.blocks, 256, 0, s>>>(w0, w1, x);
@@ -884,6 +912,26 @@ int pq_launch_tile_set(const pq_tile_call* w0, const pq_tile_call* w1, const pq_
   PQ_SET(64, 64, PQ_SRC_KS16); PQ_SET(64, 128, PQ_SRC_KS16); PQ_SET(128, 64, PQ_SRC_KS16); PQ_SET(128, 128, PQ_SRC_KS16);
 #undef PQ_SET
   return pq_set_error(PQ_ERR_BAD_ARG, "no launch for these tiles");
+}
+
+int pq_launch_tile_grads(const pq_tile_call (&c)[3], const pq_tile_call* x, const pq_phase2* p2, hipStream_t s) {
+  auto plain64 = [](const pq_tile_call& q) { return q.pl.bm == 64 && q.pl.splits == 1 && q.grp.mode == 0 && q.M > 0 && q.N > 0; };
+  for (const pq_tile_call& q : c)
+    if (!plain64(q) || q.A.kind != PQ_SRC_KS16 || q.B.kind != PQ_SRC_KS16) return pq_set_error(PQ_ERR_BAD_ARG, "products that cannot share a launch");
+  if (x && (!p2 || !plain64(*x) || x->A.kind != PQ_SRC_KC16 || x->B.kind != PQ_SRC_BITS16 || p2->A2.kind != PQ_SRC_KC16 || p2->B2.kind != PQ_SRC_KS16))
+    return pq_set_error(PQ_ERR_BAD_ARG, "products that cannot share a launch");
+  const tile_job jx = job_of(x), j0 = job_of(&c[0]), j1 = job_of(&c[1]), j2 = job_of(&c[2]);
+  const int blocks = jx.blocks + j0.blocks + j1.blocks + j2.blocks;
+  const bool deep = blocks <= 256;                   // (rings as in launch_tile)
+  pq_phase2 ph2;
+  memset(&ph2, 0, sizeof(ph2));
+  if (x) ph2 = *p2;
+  if (x && deep) tile64_grads_kernel<PQ_NG_DEEP, true><<<blocks, 256, 0, s>>>(jx, ph2, j0, j1, j2);
+  else if (x) tile64_grads_kernel<PQ_NG, true><<<blocks, 256, 0, s>>>(jx, ph2, j0, j1, j2);
+  else if (deep) tile64_grads_kernel<PQ_NG_DEEP, false><<<blocks, 256, 0, s>>>(jx, ph2, j0, j1, j2);
+  else tile64_grads_kernel<PQ_NG, false><<<blocks, 256, 0, s>>>(jx, ph2, j0, j1, j2);
+  PQ_CHECK_LAUNCH("tile64_grads_kernel");
+  return PQ_OK;
 }
 
 int pq_launch_tile(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& A, const pq_operand& B, const pq_epilogue& epi, hipStream_t s,
