@@ -355,6 +355,7 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
   double* red_a = (double*)(ws + L.red_a);
   double* red_b = (double*)(ws + L.red_b);
 
+  pq_gemm_call first[2];                             // dW_down and da
   {  // dW_down = beta * dY^T Ht ;  d beta = lambda_d * sum S_d .* (dY^T Ht)
     pq_operand A{dY, D, PQ_SRC_KS16, nullptr};
     pq_operand B{cx + L.Ht, F, PQ_SRC_KS16, nullptr};
@@ -362,7 +363,7 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
     e.C = dW_down; e.ldc = Fv; e.out_kind = PQ_OUT_F32; e.scale = d->beta;
     if (Fv != F) e.n_limit = Fv;                     // the padded columns (zero: Ht is zero there) are not part of dW_down
     e.sign_bytes = (const uint8_t*)(cx + L.P_down); e.ld_sign = F / 8; e.partials = red_b;
-    if (int err = pq_launch_gemm(D, F, T, A, B, e, s, PQP_GEMM_DW, sk)) return err;
+    first[0] = pq_gemm_call{D, F, T, A, B, e, nullptr, PQP_GEMM_DW};
   }
   // experts
   const int* idx = (const int*)(cx + L.idx);
@@ -377,6 +378,24 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
   const void* dyp = one ? dY : ws + L.dYp;
   // what the up and gate products multiplied: X, or with INT8 experts its de-quantised codes
   const void* xp = one ? (hp8 ? (const void*)(cx + L.Xt) : X) : (const void*)(cx + L.Xp);
+  pq_gemm_group g1{offsets, E, 1, 0, 0, S};
+  pq_gemm_group g2{offsets, E, 2, 0, 0, S};
+  const pq_gemm_group* pg1 = one ? nullptr : &g1;
+  if (S > 0) {  // da = dYp Down_e  (scaled by alpha*gate inside the activation backward)
+    pq_operand A{dyp, D, PQ_SRC_KC16, nullptr};
+    pq_operand B{Down, r, PQ_SRC_KS16, nullptr};
+    pq_epilogue e = epi0();
+    e.C = ws + L.da; e.ldc = r; e.out_kind = PQ_OUT_BF16;
+    if (one && !hp8) { e.dot_comp = a_fwd; e.ld_comp = r; e.comp_kind = PQ_OUT_BF16; e.partials = red_a; }   // d alpha = <a, dY Down>
+    g1.b_stride = (long)D * r;
+    first[1] = pq_gemm_call{S, r, D, A, B, e, pg1, PQP_GEMM_EXPERT};
+  }
+  // Together on small tiles (6361 tokens 768/584, r = 384, INT8: 325 -> 314 us the whole call, 106 tokens 1472/608, r = 32, four experts:
+  // 137 -> 128 with the gradients below); otherwise dW_down goes first, and da reads rows that have just been written (8192 tokens
+  // 2048/5504, eight experts: 1535 us, with dW_down between the two 1537).
+  const bool da_too = S > 0 && pq_gemm_set_shares(first, 2, sk, true);
+  if (!da_too)
+    if (int err = pq_launch_gemm(D, F, T, first[0].A, first[0].B, first[0].epi, s, PQP_GEMM_DW, sk)) return err;
   // Row dots with the experts' outputs (d alpha, the gates' gradients) and dY in slot order.  d alpha = <Ys, dY> is a sum of terms of
   // either sign.  Of a single bf16 branch it is <a, dY Down>, formed in the da product from the same bf16 factors as Ys and from
   // unrounded sums.  The factors of an INT8 branch are codes over gammas, which bf16 rounds (one step for every element of equal code
@@ -390,17 +409,11 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
   // d alpha and d beta (partials of the dW_down GEMM): both fixed-order sums ride along in the last reduction, with a single
   // branch in the activation's backward
   const pq_reduce_job jobs[2] = {{red_a, S > 0 ? L.n_red_a : 0, 1.0f, nullptr, dalpha_dbeta}, {red_b, L.n_red_b, 1.0f, ml_down + 1, dalpha_dbeta + 1}};
-  pq_gemm_group g1{offsets, E, 1, 0, 0, S};
-  pq_gemm_group g2{offsets, E, 2, 0, 0, S};
-  const pq_gemm_group* pg1 = one ? nullptr : &g1;
-  if (S > 0) {  // da = dYp Down_e  (scaled by alpha*gate inside the activation backward)
-    pq_operand A{dyp, D, PQ_SRC_KC16, nullptr};
-    pq_operand B{Down, r, PQ_SRC_KS16, nullptr};
-    pq_epilogue e = epi0();
-    e.C = ws + L.da; e.ldc = r; e.out_kind = PQ_OUT_BF16;
-    if (one && !hp8) { e.dot_comp = a_fwd; e.ld_comp = r; e.comp_kind = PQ_OUT_BF16; e.partials = red_a; }   // d alpha = <a, dY Down>
-    g1.b_stride = (long)D * r;
-    if (int err = pq_launch_gemm(S, r, D, A, B, e, s, PQP_GEMM_EXPERT, sk, pg1)) return err;
+  if (da_too) {
+    if (int err = pq_launch_gemm_set(first, 2, s, sk)) return err;
+  } else if (S > 0) {
+    const pq_gemm_call& q = first[1];
+    if (int err = pq_launch_gemm(q.M, q.N, q.K, q.A, q.B, q.epi, s, q.prof_label, sk, q.grp)) return err;
   }
   // u | g and du | dg lie side by side in [S][2 r] matrices (Up and Gate are one weight matrix per expert, in both forms)
   if (int e = pq_launch_expert_act_bwd(ws + L.da, cx + L.ue, cx + L.ue + (size_t)r * 2, a_fwd, one ? nullptr : perm, gate, d->alpha, S, r, 2 * r,
@@ -439,39 +452,49 @@ extern "C" int pq_ffn_bwd(const pq_ffn_desc* d, const void* dY, const void* X, c
       if (int err = pq_launch_gemm(T, D, F, A2, B2, e, s, PQP_GEMM_DX, sk)) return err;
     }
   }
+  pq_gemm_call c[5];
   {  // dW_up = dU^T Xt, dW_gate = dG^T Xt
     pq_operand B{cx + L.Xt, D, PQ_SRC_KS16, nullptr};
     pq_epilogue e = epi0();
-    e.ldc = D; e.out_kind = PQ_OUT_F32;
+    e.ldc = D; e.out_kind = PQ_OUT_F32; e.scale = 1.0f;
     if (Fv != F) e.m_limit = Fv;                     // rows Fv.. of the padded product do not exist in dW_up / dW_gate
-    pq_operand A{ws + L.dU, F, PQ_SRC_KS16, nullptr}, A2{ws + L.dG, F, PQ_SRC_KS16, nullptr};
     e.C = dW_up;
-    if (int err = pq_launch_gemm_dual(F, D, T, A, B, e, A2, B, dW_gate, nullptr, s, PQP_GEMM_DW, sk)) return err;
+    c[0] = pq_gemm_call{F, D, T, {ws + L.dU, F, PQ_SRC_KS16, nullptr}, B, e, nullptr, PQP_GEMM_DW};
+    e.C = dW_gate;
+    c[1] = pq_gemm_call{F, D, T, {ws + L.dG, F, PQ_SRC_KS16, nullptr}, B, e, nullptr, PQP_GEMM_DW};
   }
   // per-expert weight gradients, contractions over the expert's slots: dDown, and d[Up_e; Gate_e] = [du | dg]^T Xp, the halves of whose
   // rows are stored to the caller's two gradients.  dXs = [du | dg] [Up_e; Gate_e] (INT8 experts: the de-quantised rows); a single
   // branch's goes to dX itself.
-  pq_gemm_call c[3];
   pq_gemm_group gD = g2, gU = g2;
   {
     pq_epilogue e = epi0();
     e.C = dDown; e.ldc = r; e.out_kind = PQ_OUT_F32;
     gD.c_stride = (long)D * r;
-    c[0] = pq_gemm_call{D, r, S, {dyp, D, PQ_SRC_KS16, nullptr}, {ws + L.as, r, PQ_SRC_KS16, nullptr}, e, one ? nullptr : &gD, PQP_GEMM_EXPERT};
+    c[2] = pq_gemm_call{D, r, S, {dyp, D, PQ_SRC_KS16, nullptr}, {ws + L.as, r, PQ_SRC_KS16, nullptr}, e, one ? nullptr : &gD, PQP_GEMM_EXPERT};
     e.C = dUp; e.C2 = dGate; e.m_split = r; e.ldc = D;
     gU.c_stride = (long)r * D;
-    c[1] = pq_gemm_call{2 * r, D, S, {ws + L.du, 2 * r, PQ_SRC_KS16, nullptr}, {xp, D, PQ_SRC_KS16, nullptr}, e, one ? nullptr : &gU, PQP_GEMM_EXPERT};
+    c[3] = pq_gemm_call{2 * r, D, S, {ws + L.du, 2 * r, PQ_SRC_KS16, nullptr}, {xp, D, PQ_SRC_KS16, nullptr}, e, one ? nullptr : &gU, PQP_GEMM_EXPERT};
     e = epi0();
     e.C = one ? dX : ws + L.dXs; e.ldc = D; e.out_kind = PQ_OUT_BF16; e.accumulate = one ? 1 : 0;
     g1.b_stride = (long)2 * r * D;
-    c[2] = pq_gemm_call{S, D, 2 * r, {ws + L.du, 2 * r, PQ_SRC_KC16, nullptr}, {hp8 ? cx + L.UGT : cx + L.UG, D, PQ_SRC_KS16, nullptr}, e, pg1,
+    c[4] = pq_gemm_call{S, D, 2 * r, {ws + L.du, 2 * r, PQ_SRC_KC16, nullptr}, {hp8 ? cx + L.UGT : cx + L.UG, D, PQ_SRC_KS16, nullptr}, e, pg1,
                         PQP_GEMM_EXPERT};
   }
-  if (S > 0 && !fuse_dx) {
-    if (int err = pq_launch_gemm_set(c, 3, s, sk)) return err;
-  } else
-    for (int i = 0; i < 2; ++i)
-      if (int err = pq_launch_gemm(c[i].M, c[i].N, c[i].K, c[i].A, c[i].B, c[i].epi, s, PQP_GEMM_EXPERT, sk, c[i].grp)) return err;
+  const bool dxs = S > 0 && !fuse_dx;
+  const pq_gemm_plan dual = pq_plan_dual(F, D, T, false);
+  if (T > 0 && dual.bm == 64 && dual.splits == 1 && pq_gemm_set_shares(c, 4 + dxs, sk, dxs)) {
+    // all of it: on 64x64 tiles, not split, each is one wave or less (1257 tokens 320/912, r = 256: 139 -> 116 us the whole call, 64 tokens
+    // 256/512, r = 128: 92 -> 79, 1189 tokens 960/704, r = 32, four experts: 160 -> 148)
+    if (int err = pq_launch_gemm_set(c, 4 + dxs, s, sk, dxs)) return err;
+  } else {
+    if (int err = pq_launch_gemm_dual(F, D, T, c[0].A, c[0].B, c[0].epi, c[1].A, c[1].B, dW_gate, nullptr, s, PQP_GEMM_DW, sk)) return err;
+    if (dxs) {
+      if (int err = pq_launch_gemm_set(c + 2, 3, s, sk)) return err;
+    } else
+      for (int i = 2; i < 4; ++i)
+        if (int err = pq_launch_gemm(c[i].M, c[i].N, c[i].K, c[i].A, c[i].B, c[i].epi, s, PQP_GEMM_EXPERT, sk, c[i].grp)) return err;
+  }
   if (one) return PQ_OK;   // softmax over one logit is constant: no gradient reaches the router
   float* dlogit = (float*)(ws + L.dlogit);
   if (int e = pq_launch_dwr(rd, inv, idx, (const float*)(cx + L.probs), d->alpha, k, dlogit, X, T, D, E, (float*)(ws + L.dwr), dWr, jobs, s)) return e;

@@ -2211,13 +2211,15 @@ int pq_launch_gemm_swiglu(int M, int N, int K, const pq_operand& A, const pq_ope
   return PQ_OK;
 }
 
-int pq_launch_gemm_set(const pq_gemm_call* c, int n, hipStream_t s, pq_scratch sk) {
-  pq_tile_call t[3];
-  bool together = n == 2 || n == 3;
+// their launches (t, slabs side by side) and whether those can be one
+static int plan_set(const pq_gemm_call* c, int n, pq_scratch sk, bool has_x, pq_tile_call* t, bool* together) {
+  *together = false;
+  if (n < 2 || n > 4 + has_x) return PQ_OK;
   size_t used = 0;
-  for (int i = 0; i < n && together; ++i) {
-    if (c[i].M <= 0 || c[i].N <= 0) { together = false; break; }
+  for (int i = 0; i < n; ++i) {
+    if (c[i].M <= 0 || c[i].N <= 0) return PQ_OK;
     if (int rc = check_epilogue(c[i].M, c[i].A, c[i].B, c[i].epi)) return rc;
+    if (!c[i].grp && !c[i].epi.partials && pq_skinny_applies(c[i].M, c[i].N, c[i].K, c[i].A, c[i].B, c[i].epi)) return PQ_OK;   // (see pq_launch_gemm)
     t[i] = pq_tile_call{c[i].M, c[i].N, c[i].K, c[i].A, c[i].B, c[i].epi, {}, {}, nullptr};
     if (c[i].grp) t[i].grp = *c[i].grp;
     t[i].pl = plan_call(c[i].M, c[i].N, c[i].K, c[i].A, c[i].B, c[i].epi, t[i].grp, sk);
@@ -2226,7 +2228,19 @@ int pq_launch_gemm_set(const pq_gemm_call* c, int n, hipStream_t s, pq_scratch s
       used += pq_align_up(t[i].pl.ws_bytes, 256);
     }
   }
-  together = together && used <= sk.bytes && pq_tile_set_applies(&t[0], n == 3 ? &t[1] : nullptr, t[n - 1]);
+  *together = used <= sk.bytes && pq_tile_set_applies(t, n - has_x, has_x ? &t[n - 1] : nullptr);
+  return PQ_OK;
+}
+bool pq_gemm_set_shares(const pq_gemm_call* c, int n, pq_scratch sk, bool has_x) {
+  pq_tile_call t[5];
+  bool together;
+  return plan_set(c, n, sk, has_x, t, &together) == PQ_OK && together;
+}
+
+int pq_launch_gemm_set(const pq_gemm_call* c, int n, hipStream_t s, pq_scratch sk, bool has_x) {
+  pq_tile_call t[5];
+  bool together;
+  if (int rc = plan_set(c, n, sk, has_x, t, &together)) return rc;
   if (!together) {
     for (int i = 0; i < n; ++i)
       if (int rc = pq_launch_gemm(c[i].M, c[i].N, c[i].K, c[i].A, c[i].B, c[i].epi, s, c[i].prof_label, sk, c[i].grp)) return rc;
@@ -2234,7 +2248,7 @@ int pq_launch_gemm_set(const pq_gemm_call* c, int n, hipStream_t s, pq_scratch s
   }
   {
     pq_prof_scope prof(c[0].prof_label, s);
-    if (int rc = pq_launch_tile_set(&t[0], n == 3 ? &t[1] : nullptr, t[n - 1], s)) return rc;
+    if (int rc = pq_launch_tile_set(t, n - has_x, has_x ? &t[n - 1] : nullptr, s)) return rc;
   }
   for (int i = 0; i < n; ++i)
     if (int rc = reduce_call(t[i].M, t[i].N, t[i].epi, t[i].grp, t[i].pl, t[i].part, false, s)) return rc;

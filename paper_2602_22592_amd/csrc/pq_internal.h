@@ -255,11 +255,11 @@ struct pq_tile_call {
   pq_gemm_plan pl;
   float* part;
 };
-bool pq_tile_set_applies(const pq_tile_call* w0, const pq_tile_call* w1, const pq_tile_call& x);   // (w1 may be NULL)
+bool pq_tile_set_applies(const pq_tile_call* w, int nw, const pq_tile_call* x);   // (x may be NULL)
 // 64x64 tiles, nothing split: three products of contraction-strided operands and, with x, one of packed signs with a second contraction
 int pq_launch_tile_grads(const pq_tile_call (&c)[3], const pq_tile_call* x, const pq_phase2* p2, hipStream_t s);
-int pq_launch_tile_set(const pq_tile_call* w0, const pq_tile_call* w1, const pq_tile_call& x, hipStream_t s);
-// Up to three products that do not depend on each other: n - 1 weight gradients (one or two), then a product of a contraction-contiguous
+int pq_launch_tile_set(const pq_tile_call* w, int nw, const pq_tile_call* x, hipStream_t s);
+// Products that do not depend on each other: up to four weight gradients and, with has_x, at the end one of a contraction-contiguous
 // operand with signs or a contraction-strided one.  One launch where they all take small tiles and their slabs fit side by side
 // in the scratch, otherwise one after the other.
 struct pq_gemm_call {
@@ -275,7 +275,8 @@ struct pq_grads {
   bool has_x;
   pq_scratch sk;
 };
-int pq_launch_gemm_set(const pq_gemm_call* c, int n, hipStream_t s, pq_scratch sk);
+int pq_launch_gemm_set(const pq_gemm_call* c, int n, hipStream_t s, pq_scratch sk, bool has_x = true);
+bool pq_gemm_set_shares(const pq_gemm_call* c, int n, pq_scratch sk, bool has_x);   // (in one launch)
 pq_gemm_plan pq_plan_dual(int M, int N, int K, bool int8);   // (its ws_bytes: the slabs of both)
 int pq_launch_gemm_dual(int M, int N, int K, const pq_operand& A0, const pq_operand& B0, const pq_epilogue& e0, const pq_operand& A1,
                         const pq_operand& B1, void* C1, const float* dev_scale1, hipStream_t s, int prof_label, pq_scratch sk);

@@ -811,8 +811,8 @@ int launch_kinds(const pq_gemm_plan& pl, int M, int N, int K, const pq_operand& 
   return launch_tile<128, bits ? PQ_NST128B : PQ_NST128, INT8, AK, BK, BK2>(pl, M, N, K, A, B, epi, s, part, grp, ph2, second);
 }
 
-// Up to two weight gradients (w0, w1) and a product of their input's size (x: its input gradient, or an expert's) that do not depend
-// on each other, in one launch: workgroups of w0, then of w1, then of x.  Alone each leaves CUs idle (one wave of small tiles, or
+// Up to four weight gradients (w) and a product of their input's size (x: an input gradient, or an expert's; may be none) that do not
+// depend on each other, in one launch: workgroups of w[0], w[1], ..., then of x.  Alone each leaves CUs idle (one wave of small tiles, or
 // less) and is bound by its own chain of latencies and its launch.
 struct tile_job {
   int M, N, K, nbn, tiles, kchunk, gy, blocks;       // blocks: tiles * splits * groups
@@ -834,20 +834,19 @@ struct tile_kind {
 };
 template <int BM, int AK, int BK>
 using tile_in_set = tile_kind<BM, BM == 64 ? PQ_NG : BK == PQ_SRC_BITS16 ? PQ_NST128B : PQ_NST128, AK, BK>;
+struct tile_jobs {
+  tile_job j[4];
+};
 template <int WBM, int XBM, int XBK>
-__global__ __launch_bounds__(256) void tile_set_kernel(tile_job w0, tile_job w1, tile_job x) {
+__global__ __launch_bounds__(256) void tile_set_kernel(tile_jobs w, tile_job x) {
   using W = tile_in_set<WBM, PQ_SRC_KS16, PQ_SRC_KS16>;
   using X = tile_in_set<XBM, PQ_SRC_KC16, XBK>;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[W::LDS > X::LDS ? W::LDS : X::LDS];
   __shared__ double red[4];
-  const int b = blockIdx.x, nw = w0.blocks + w1.blocks;
-  if (b >= nw) {                                     // uniform
-    X::run(x, b - nw, smem, red);
-    return;
-  }
-  const bool second = b >= w0.blocks;
-  const tile_job& w = second ? w1 : w0;
-  W::run(w, second ? b - w0.blocks : b, smem, red);
+  int b = blockIdx.x, i = 0;
+  while (i < 4 && b >= w.j[i].blocks) b -= w.j[i++].blocks;    // uniform
+  if (i == 4) X::run(x, b, smem, red);
+  else W::run(w.j[i], b, smem, red);
 }
 
 // What follows dH in the backward of a linear with a dense branch, where all of it takes 64x64 tiles and nothing is split: workgroups of
@@ -879,8 +878,8 @@ __global__ __launch_bounds__(256) void tile64_grads_kernel(tile_job x, pq_phase2
 }
 
 template <int WBM, int XBM, int XBK>
-int launch_set(const tile_job& w0, const tile_job& w1, const tile_job& x, hipStream_t s) {
-  tile_set_kernel<WBM, XBM, XBK><<<w0.blocks + w1.blocks + x.blocks, 256, 0, s>>>(w0, w1, x);
+int launch_set(const tile_jobs& w, const tile_job& x, hipStream_t s) {
+  tile_set_kernel<WBM, XBM, XBK><<<w.j[0].blocks + w.j[1].blocks + w.j[2].blocks + w.j[3].blocks + x.blocks, 256, 0, s>>>(w, x);
   PQ_CHECK_LAUNCH("tile_set_kernel");
   return PQ_OK;
 }
@@ -898,16 +897,20 @@ tile_job job_of(const pq_tile_call* c) {
 
 }  // namespace
 
-bool pq_tile_set_applies(const pq_tile_call* w0, const pq_tile_call* w1, const pq_tile_call& x) {
-  for (const pq_tile_call* w : {w0, w1})
-    if (w && (w->A.kind != PQ_SRC_KS16 || w->B.kind != PQ_SRC_KS16 || w->pl.bn > 128 || w->pl.bm != w0->pl.bm)) return false;
-  return x.A.kind == PQ_SRC_KC16 && (x.B.kind == PQ_SRC_BITS16 || x.B.kind == PQ_SRC_KS16) && x.pl.bn <= 128;
+bool pq_tile_set_applies(const pq_tile_call* w, int nw, const pq_tile_call* x) {
+  if (nw < 1 || nw > 4) return false;
+  for (int i = 0; i < nw; ++i)
+    if (w[i].A.kind != PQ_SRC_KS16 || w[i].B.kind != PQ_SRC_KS16 || w[i].pl.bn > 128 || w[i].pl.bm != w[0].pl.bm) return false;
+  return !x || (x->A.kind == PQ_SRC_KC16 && (x->B.kind == PQ_SRC_BITS16 || x->B.kind == PQ_SRC_KS16) && x->pl.bn <= 128);
 }
 
-int pq_launch_tile_set(const pq_tile_call* w0, const pq_tile_call* w1, const pq_tile_call& x, hipStream_t s) {
-  if (!w0 || !pq_tile_set_applies(w0, w1, x)) return pq_set_error(PQ_ERR_BAD_ARG, "products that cannot share a launch");
-  const tile_job j0 = job_of(w0), j1 = job_of(w1), jx = job_of(&x);
-#define PQ_SET(WBM, XBM, XBK) if (w0->pl.bm == WBM && x.pl.bm == XBM && x.B.kind == XBK) return launch_set<WBM, XBM, XBK>(j0, j1, jx, s)
+int pq_launch_tile_set(const pq_tile_call* w, int nw, const pq_tile_call* x, hipStream_t s) {
+  if (!pq_tile_set_applies(w, nw, x)) return pq_set_error(PQ_ERR_BAD_ARG, "products that cannot share a launch");
+  tile_jobs jw;
+  for (int i = 0; i < 4; ++i) jw.j[i] = job_of(i < nw ? &w[i] : nullptr);
+  const tile_job jx = job_of(x);
+  const int xbm = x ? x->pl.bm : 64, xbk = x ? x->B.kind : PQ_SRC_KS16;
+#define PQ_SET(WBM, XBM, XBK) if (w[0].pl.bm == WBM && xbm == XBM && xbk == XBK) return launch_set<WBM, XBM, XBK>(jw, jx, s)
   PQ_SET(64, 64, PQ_SRC_BITS16); PQ_SET(64, 128, PQ_SRC_BITS16); PQ_SET(128, 64, PQ_SRC_BITS16); PQ_SET(128, 128, PQ_SRC_BITS16);
   PQ_SET(64, 64, PQ_SRC_KS16); PQ_SET(64, 128, PQ_SRC_KS16); PQ_SET(128, 64, PQ_SRC_KS16); PQ_SET(128, 128, PQ_SRC_KS16);
 #undef PQ_SET
