@@ -1937,20 +1937,33 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
   const bool one = M0 > 0 && N0 > 0 && M1 > 0 && N1 > 0 && K > 0 && al(A0) && al(B0) && al(A1) && al(B1) && A0.ld >= M0 && B0.ld >= N0 &&
                    A1.ld >= M1 && B1.ld >= N1 &&
                    (pp.splits == 1 || (sk0.p && sk1.p && ((uintptr_t)sk0.p % 16) == 0 && ((uintptr_t)sk1.p % 16) == 0));
+  bool launched = false;
   if (along) {
-    // where dW takes 64x64 tiles and is not split, those of dB and dA, not split either, end with its own
+    // (dW on 64x64 tiles, not split: those of dB and dA end with its own at the latest)
     pq_tile_call c[3], x;
     const pq_gemm_call &w = along->w, &xc = along->x;
-    const bool w_too = one && !pp.apart && !pp.tn && pq_plain_64(w, along->sk, &c[0]), x_too = w_too && along->has_x && pq_plain_64(xc, along->sk, &x);
+    bool w_too = one && !pp.apart && !pp.tn && pq_plain_64(w, along->sk, &c[0]);
+    if (w_too && pp.splits > 1) {
+      // A split pair joins a dW of more than one workgroup per CU (1724 tokens 1984 -> 736, r = 32, INT8 branch: whole call 107.0 -> 101.0 us) or one
+      // that it leaves at that; below, dW would lose its deep ring to it (3032 tokens 1504 -> 480, r = 16: 110.9 -> 114.4).
+      auto tiles = [](int m, int n) { return (long)((m + 63) / 64) * ((n + 63) / 64); };
+      const long nw = tiles(w.M, w.N);
+      w_too = nw > 256 || nw + pp.splits * (tiles(M0, N0) + tiles(M1, N1)) <= 256;
+    }
+    const bool x_too = w_too && along->has_x && pq_plain_64(xc, along->sk, &x);
     if (along->has_x && !x_too)
       if (int rc = pq_launch_gemm(xc.M, xc.N, xc.K, xc.A, xc.B, xc.epi, s, xc.prof_label, along->sk, nullptr, &along->p2)) return rc;
     if (w_too) {
-      c[1] = pq_tile_call{M0, N0, K, A0, B0, e0, c[0].grp, c[0].pl, nullptr};
-      c[2] = pq_tile_call{M1, N1, K, A1, B1, e1, c[0].grp, c[0].pl, nullptr};
+      if (int rc = check_scratch(pp.ws0, sk0)) return rc;
+      if (int rc = check_scratch(pp.ws1, sk1)) return rc;
+      pq_gemm_plan pl = c[0].pl;
+      pl.splits = pp.splits; pl.kchunk = pp.kchunk;
+      c[1] = pq_tile_call{M0, N0, K, A0, B0, e0, c[0].grp, pl, (float*)sk0.p};
+      c[2] = pq_tile_call{M1, N1, K, A1, B1, e1, c[0].grp, pl, (float*)sk1.p};
       pq_prof_scope prof(w.prof_label, s);
-      return pq_launch_tile_grads(c, x_too ? &x : nullptr, x_too ? &along->p2 : nullptr, s);
-    }
-    if (int rc = pq_launch_gemm(w.M, w.N, w.K, w.A, w.B, w.epi, s, w.prof_label, along->sk)) return rc;
+      if (int rc = pq_launch_tile_grads(c, x_too ? &x : nullptr, x_too ? &along->p2 : nullptr, s)) return rc;
+      launched = true;
+    } else if (int rc = pq_launch_gemm(w.M, w.N, w.K, w.A, w.B, w.epi, s, w.prof_label, along->sk)) return rc;
   }
   if (!one || pp.apart) {
     if (int rc = pq_launch_gemm(M0, N0, K, A0, B0, e0, s, prof_label0, sk0)) return rc;
@@ -1958,7 +1971,7 @@ int pq_launch_gemm_pair_ks16(int K, int M0, int N0, const pq_operand& A0, const 
   }
   if (int rc = check_scratch(pp.ws0, sk0)) return rc;
   if (int rc = check_scratch(pp.ws1, sk1)) return rc;
-  {
+  if (!launched) {
     pq_prof_scope prof(prof_label0, s);
     if (pp.tn) {
       skt_problem q0{(const uint16_t*)A0.p, A0.ld, (const uint16_t*)B0.p, B0.ld, M0, 0, (float*)sk0.p};

@@ -256,7 +256,7 @@ struct pq_tile_call {
   float* part;
 };
 bool pq_tile_set_applies(const pq_tile_call* w, int nw, const pq_tile_call* x);   // (x may be NULL)
-// 64x64 tiles, nothing split: three products of contraction-strided operands and, with x, one of packed signs with a second contraction
+// 64x64 tiles: three products of contraction-strided operands (split ones leave slabs) and, with x, one of packed signs with a second contraction
 int pq_launch_tile_grads(const pq_tile_call (&c)[3], const pq_tile_call* x, const pq_phase2* p2, hipStream_t s);
 int pq_launch_tile_set(const pq_tile_call* w, int nw, const pq_tile_call* x, hipStream_t s);
 // Products that do not depend on each other: up to four weight gradients and, with has_x, at the end one of a contraction-contiguous

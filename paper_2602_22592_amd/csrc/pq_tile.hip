@@ -849,12 +849,12 @@ __global__ __launch_bounds__(256) void tile_set_kernel(tile_jobs w, tile_job x) 
   else W::run(w.j[i], b, smem, red);
 }
 
-// What follows dH in the backward of a linear with a dense branch, where all of it takes 64x64 tiles and nothing is split: workgroups of
-// dX (with X), then of dW, dB and dA (j0, j1, j2), which share a contraction.  Each is one chain of latencies; the branch's gradients
-// alone fill a fraction of the chip (32 to 70 tiles) and were split and added where that paid.  In one launch instead of three or four
+// What follows dH in the backward of a linear with a dense branch, where all of it takes 64x64 tiles and neither dX nor dW is split: workgroups
+// of dX (with X), then of dW, dB and dA (j0, j1, j2; the last two split as they are alone, so that no sum is longer than it was).  Each is one
+// chain of latencies; the branch's gradients alone fill a fraction of the chip (32 to 70 tiles).  In one launch instead of three or four
 // (whole call, forward and backward): 64 tokens 256 -> 256, r = 16, 47.8 -> 37.5 us; 512 tokens 512 -> 512, r = 64, 56.7 -> 43.0; 701 tokens
-// 608 -> 2048, r = 40, 77.4 -> 61.0; 236 tokens 2560 -> 672, r = 160, INT8 branch, 84.4 -> 72.5; without dX, which takes other tiles there: 3032
-// tokens 1504 -> 480, r = 16, 111.0 -> 102.5; 1724 tokens 1984 -> 736, r = 32, INT8 branch, 107.1 -> 99.2.
+// 608 -> 2048, r = 40, 77.4 -> 61.0; 236 tokens 2560 -> 672, r = 160, INT8 branch, 84.4 -> 72.5; without dX, which takes other tiles
+// there: 1724 tokens 1984 -> 736, r = 32, INT8 branch, 107.1 -> 101.0.
 template <int NG, bool X>
 __global__ __launch_bounds__(256) void tile64_grads_kernel(tile_job x, pq_phase2 p2, tile_job j0, tile_job j1, tile_job j2) {
   constexpr int LW = tile64_lds<NG, PQ_SRC_KS16, PQ_SRC_KS16, -1>(), LX = X ? tile64_lds<NG, PQ_SRC_KC16, PQ_SRC_BITS16, PQ_SRC_KS16>() : 0;
@@ -873,8 +873,9 @@ __global__ __launch_bounds__(256) void tile64_grads_kernel(tile_job x, pq_phase2
   const tile_job& j = b < j0.blocks ? j0 : b < n1 ? j1 : j2;   // uniform
   pq_phase2 none;
   none.K2 = 0;
-  tile64_body<NG, false, PQ_SRC_KS16, PQ_SRC_KS16, -1>(j.M, j.N, j.K, j.A, j.B, j.epi, j.nbn, j.tiles, j.kchunk, nullptr, j.grp, none,
-                                                       b < j0.blocks ? b : b < n1 ? b - j0.blocks : b - n1, 0, 0, 1, smem, red);
+  b = b < j0.blocks ? b : b < n1 ? b - j0.blocks : b - n1;
+  tile64_body<NG, false, PQ_SRC_KS16, PQ_SRC_KS16, -1>(j.M, j.N, j.K, j.A, j.B, j.epi, j.nbn, j.tiles, j.kchunk, j.part, j.grp, none, b % j.tiles,
+                                                       b / j.tiles, 0, j.gy, smem, red);
 }
 
 template <int WBM, int XBM, int XBK>
@@ -918,10 +919,10 @@ int pq_launch_tile_set(const pq_tile_call* w, int nw, const pq_tile_call* x, hip
 }
 
 int pq_launch_tile_grads(const pq_tile_call (&c)[3], const pq_tile_call* x, const pq_phase2* p2, hipStream_t s) {
-  auto plain64 = [](const pq_tile_call& q) { return q.pl.bm == 64 && q.pl.splits == 1 && q.grp.mode == 0 && q.M > 0 && q.N > 0; };
+  auto plain64 = [](const pq_tile_call& q) { return q.pl.bm == 64 && q.pl.splits >= 1 && (q.pl.splits == 1 || q.part) && q.grp.mode == 0 && q.M > 0 && q.N > 0; };
   for (const pq_tile_call& q : c)
     if (!plain64(q) || q.A.kind != PQ_SRC_KS16 || q.B.kind != PQ_SRC_KS16) return pq_set_error(PQ_ERR_BAD_ARG, "products that cannot share a launch");
-  if (x && (!p2 || !plain64(*x) || x->A.kind != PQ_SRC_KC16 || x->B.kind != PQ_SRC_BITS16 || p2->A2.kind != PQ_SRC_KC16 || p2->B2.kind != PQ_SRC_KS16))
+  if (x && (!p2 || !plain64(*x) || x->pl.splits != 1 || x->A.kind != PQ_SRC_KC16 || x->B.kind != PQ_SRC_BITS16 || p2->A2.kind != PQ_SRC_KC16 || p2->B2.kind != PQ_SRC_KS16))
     return pq_set_error(PQ_ERR_BAD_ARG, "products that cannot share a launch");
   const tile_job jx = job_of(x), j0 = job_of(&c[0]), j1 = job_of(&c[1]), j2 = job_of(&c[2]);
   const int blocks = jx.blocks + j0.blocks + j1.blocks + j2.blocks;
