@@ -128,11 +128,12 @@ struct cursor {
 };
 
 // The two large contractions of the fp32 backward in fixed point: seven int8 products of one in fp64, a quarter of its time, but five
-// more launches (some 20 us) and 56 bytes of planes per output and 22 of digits per element of dY, written and read, i.e. 56 (1 / d_out +
-// 1 / tokens) + 22 / d_in bytes per product.  Backward against the fp64 products, 49 shapes of 64 to 65536 tokens and widths of 128 to 16384:
+// more launches (some 20 us), 8 bytes of sums per output and 22 of digits per element of dY, written and read.  Measured while an output's seven
+// int32 sums went through memory (56 bytes: the terms in 1 / d_out and 1 / tokens below); the line was not moved when that traffic went.
+// Backward against the fp64 products, 49 shapes of 64 to 65536 tokens and widths of 128 to 16384:
 // with 1 / tokens + 1 / d_out + 0.4 / d_in up to 1 / 320 1.17 x (512 tokens 1024->4096, 65536 512->512 1.19) to 2.77 x (2048 tokens
 // 4096->4096), beyond it 1.14 x (16384 256->512) down to 0.39 x (64 tokens 8192->8192); below tokens * d_in * d_out = 1.2e9 0.55 to 1.1 x.
-// The int32 sums of dW hold tokens * 2^14, those of dX d_out * 2^7.  Calls whose digits and planes would take more than FIXED_MAX_BYTES
+// The int32 sums of dW hold tokens * 2^14, those of dX d_out * 2^7.  Calls whose region would take more than FIXED_MAX_BYTES
 // (14 tokens * d_out + 28 d_in * max(tokens, d_out) bytes: 176 MiB at 2048 tokens 2048x2048, 1.9 GiB at 4096 tokens 4096x11008) keep
 // the fp64 products.
 constexpr size_t FIXED_MAX_BYTES = (size_t)2 << 30;
@@ -664,7 +665,7 @@ static int hp_int8_factor_grads(const void* dY, const void* Xt, int T, int K, in
 // (pq_fixed.hip), whose sums the launches below finish.  What depends on nothing (dW, dH, dB) is one launch, what needs dH
 // (dX with dH A in the same sums, dA) and the two scalar reductions a second one: six products and a reduction in a row
 // left most of the chip idle at every size, and at 64 tokens their starts were most of the time.
-// fx: the region of the digits and planes, or NULL for the fp64 products alone.
+// fx: the region of the digits and their sums, or NULL for the fp64 products alone.
 static int linear_bwd_f32(const pq_linear_desc* d, const lin_layout& L, const void* dY, const void* X, const void* W, const void* hpA,
                           const void* hpB, const char* cx, void* dX, float* dW, float* dhpA, float* dhpB, float* dalpha_dbeta, char* ws, char* fx,
                           hipStream_t s) {
@@ -695,7 +696,7 @@ static int linear_bwd_f32(const pq_linear_desc* d, const lin_layout& L, const vo
     p[n].counts = fx ? (const int*)(fx + L.fx_counts) : nullptr;
     ++n;
   };
-  if (!fx) add_dW();                 // (the longest first: products before sums of planes)
+  if (!fx) add_dW();                 // (the longest first: products before sums of digits)
   if (r > 0) {
     pq_epilogue e = epi_zero();      // dB = alpha * dY^T H
     e.C = dhpB; e.ldc = r; e.scale = d->alpha;

@@ -3,25 +3,26 @@
 //
 // One operand of each is already small integers (signs, codes), so only dY has to be cut up: a row of the left operand (a
 // token of dY, or an output channel over the tokens) is written as fixed-point numbers of 55 bits relative to its largest
-// element, X = rint(x 2^(54 - E)), max |x| < 2^E, and those as seven signed digits of base 256, each a plane of int8 (the
+// element, X = rint(x 2^(54 - E)), max |x| < 2^E, and those as seven signed digits of base 256, each in a byte (the
 // splitting of operands into slices whose products are exact: Ozaki, Ogita, Oishi, Rump, "Error-free transformations of matrix
-// multiplication", 2012).  Seven int8 products with int32 sums are exact; their sum sum_d 256^d acc_d 2^(E - 54) is formed in fp64
-// (pq_ref.hip, the SUM forms).  What is lost is the rounding of an element to 2^(E - 55).  In dX every element of a row enters every
+// multiplication", 2012).  Seven int8 products with int32 sums are exact; their sum sum_d 256^d acc_d 2^(E - 54) is formed in fp64 by
+// the kernel that multiplies them, and the fp64 engine (pq_ref.hip, the SUM forms) adds what belongs to it and rounds.  What is lost is the rounding of an element to 2^(E - 55).  In dX every element of a row enters every
 // sum, and the additions behind the largest one round as much in fp64.  In dW a token whose code is zero stays out of a sum, and the
 // largest element may be such a token's.  The column pass therefore counts the small elements, below 2^(E - 17), the zero ones and,
-// per channel, the zero codes; a sum is taken from the planes only if, with l = tokens - small - zero ones and z the zero codes,
+// per channel, the zero codes; a sum is taken from the digits only if, with l = tokens - small - zero ones and z the zero codes,
 //     8 max(l - z, 0) >= min(small, tokens - z):
 // at least l - z larger elements enter it then and at most eight times as many small ones, so that it is off by at most 2^-28 of
 // sum |x q|, a sixteenth of the rounding to fp32.  A 32x32 tile with another sum in it
 // is formed as the fp64 product it stands for.  One token 1e9 / 1e12 / 1e16 times the others: relative error of the sums that its zero
-// codes leave out 3.2e-8 / 1.9e-5 / 0.2 from the planes, 2.6e-8 now.  Backward of 2048 tokens 2048x2048 (us): 248 with normal data; 218 to
+// codes leave out 3.2e-8 / 1.9e-5 / 0.2 from the digits, 2.6e-8 now.  Backward of 2048 tokens 2048x2048 (us): 248 with normal data; 218 to
 // 249 with 95 % zero codes, half of the tokens masked, token scales of e^+-6 or elements of e^+-10; 538 with one token 1e6 times the others
 // (all tiles fp64).
 // What it is for: the fp64 matrix rate is 78.6 TFLOP/s, the int8 one 5 POP/s nominal and 2 on real data, so seven products cost a
-// quarter of one fp64 product.  2048 tokens, 2048x2048, r = 128 (us): dX 277 -> 74 + 55 (with the rank-128 product and dA), dW 275 -> 77 + 63 (with
-// dB and dH); the passes below 13, 5 and 20, two of them over dY, 4 bytes read and 7 written per element; whole step 718 -> 380.
+// quarter of one fp64 product.  2048 tokens, 2048x2048, r = 128, whole step (us): 718 with every product in fp64, 380 with the digits' int32 sums
+// added up from memory, 333 with the sums formed where they are multiplied; the passes below 13, 5 and 20, two of them over dY, 4 bytes read
+// and 7 written per element.
 // Infinities and NaN have no fixed-point form: their rows get no digits and are marked, and the SUM forms compute a 32x32 tile that
-// a marked row reaches as the fp64 product it stands for.  Step of 2048 tokens 2048x2048 (us): finite 300; one NaN in dY 443; an infinity in X, which marks every
+// a marked row reaches as the fp64 product it stands for.  Step of 2048 tokens 2048x2048 without a branch, int32 sums in memory (us): finite 300; one NaN in dY 443; an infinity in X, which marks every
 // row of dW, 604 (one element after the other: 1115 and 5368; fp64 products alone 600).
 #include <string.h>
 #include <type_traits>

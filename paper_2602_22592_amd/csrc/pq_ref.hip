@@ -561,7 +561,7 @@ int ref_config(int M, int N, int K) {
 
 }  // namespace
 
-// (the SUM forms read and add planes: 32x32 tiles, in the launch of the small products)
+// (the SUM forms read a sum each: 32x32 tiles, in the launch of the small products)
 int pq_ref_red_blocks(int M, int N, int K) { return ref_blocks(K < 0 ? 1 : ref_config(M, N, K), M, N); }
 
 int pq_launch_ref(pq_ref_problem* p, int n, const pq_reduce_job* jobs, int njobs, hipStream_t s, int prof_label) {
