@@ -446,8 +446,12 @@ __global__ __launch_bounds__(256, 1) void fixed_gemm_kernel(fixed_product p0, fi
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
         const int ch = (x >> 1) * 4 + (lane >> 5) * 2 + (x & 1);     // 16-byte chunk of the row's 128 bytes
-        *reinterpret_cast<double2*>(mine + row * 128 + ((ch ^ (row & 7)) << 4)) = o[x];
+        const uint32_t ad = (uint32_t)(size_t)(mine + row * 128 + ((ch ^ (row & 7)) << 4));
+        const i32x4_t w = __builtin_bit_cast(i32x4_t, o[x]);
+        // (asm with two wait states behind it: see the staged epilogue of mfma_gemm_kernel)
+        asm volatile("ds_write_b128 %0, %1\n\ts_nop 1" ::"v"(ad), "v"(w) : "memory");
       }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (int it = 0; it < 4; ++it) {
