@@ -410,6 +410,8 @@ __global__ __launch_bounds__(256, 1) void fixed_gemm_kernel(fixed_product p0, fi
       }
       slot = (slot + 1) & 3;
     }
+    // The operand reads of the next tile have landed before the compiler has registers to place: it takes their outputs as written.
+    F0.wait_all();
     // (an asm MFMA's registers may be read when the matrix pipe has written them: the compiler does not know)
     asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
 #pragma unroll

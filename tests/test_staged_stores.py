@@ -1,5 +1,6 @@
 """What the build made of the kernels that pass their output through LDS, read from the library's own code: a 16-byte LDS store keeps two
-wait states between itself and the next write to the registers it stores."""
+wait states between itself and the next write to the registers it stores, and operand reads that the compiler does not know to be under
+way are waited for before it has registers of its own to place."""
 import os
 import re
 import struct
@@ -82,3 +83,23 @@ def test_registers_outlive_their_store(code, kernel):
                     assert not registers(args[0]) & held, (name, x, y)
                 states += 1
     assert stores
+
+
+def test_operand_reads_land_before_the_output_is_formed(code):
+    """The digit products read the next tile's operands with asm statements ahead of the output's conversion to fp64, which the compiler
+    arranges: a register it copied or spilled there would be one that the read has not yet written."""
+    (name, ins), = [k for k in code.items() if "fixed_gemm_kernel" in k[0]]
+    pending, converted, reads = set(), 0, 0
+    for x in ins:
+        op, args = operands(x)
+        if op == "ds_read_b128":
+            pending |= registers(args[0])
+            reads += 1
+        elif op == "s_waitcnt" and "lgkmcnt(0)" in x:
+            pending = set()
+        elif op == "v_cvt_f64_i32_e32":
+            converted += 1
+            assert not pending, (name, x, sorted(pending))
+        else:
+            assert not pending & set().union(*map(registers, args)), (name, x)
+    assert reads and converted
