@@ -209,8 +209,11 @@ lin_layout make_layout(const pq_linear_desc& d) {
   L.splitk2_bytes = sk2a > sk2b ? sk2a : sk2b;
   L.splitk2 = w.take(L.splitk2_bytes);
   if (routed) {
-    L.hist = w.take((T + pq_router_tokens((int)E) - 1) / pq_router_tokens((int)E) * E * sizeof(int));
-    L.dYp = w.take(S * N * 2); L.rd = w.take(S * 4); L.dHs = w.take(S * re * 2); L.dXs = w.take(S * K * 2);
+    // The router's counts, which the forward alone needs, lie in the backward's dYp: at most E <= 64 bytes a token against 2 k d_out >= 64, so
+    // that they add nothing to what a workspace holds.
+    const size_t rt = pq_router_tokens((int)E), counts = (T + rt - 1) / rt * E * sizeof(int), dyp = S * N * 2;
+    L.hist = L.dYp = w.take(counts > dyp ? counts : dyp);
+    L.rd = w.take(S * 4); L.dHs = w.take(S * re * 2); L.dXs = w.take(S * K * 2);
     L.dlogit = w.take(T * E * 4);
     L.dwr = w.take(pq_dwr_scratch_bytes(d.tokens, d.d_in, d.n_experts));
   }

@@ -111,8 +111,10 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   L.splitk = w.take(sk);
   L.splitk_bytes = sk;
   L.dHd = w.take(T * F * 2); L.dU = w.take(T * F * 2); L.dG = w.take(T * F * 2);
-  L.hist = w.take(E > 1 ? (T + pq_router_tokens((int)E) - 1) / pq_router_tokens((int)E) * E * sizeof(int) : 0);
-  L.dYp = w.take(So * D * 2); L.rd = w.take(So * 4);
+  // (the router's counts, which the forward alone needs, lie in the backward's dYp, see the linear's layout)
+  const size_t rt = pq_router_tokens((int)E), counts = E > 1 ? (T + rt - 1) / rt * E * sizeof(int) : 0, dyp = So * D * 2;
+  L.hist = L.dYp = w.take(counts > dyp ? counts : dyp);
+  L.rd = w.take(So * 4);
   L.da = w.take(S * r * 2); L.du = w.take(2 * S * r * 2); L.dg = L.du + S * r * 2; L.as = w.take(S * r * 2);
   L.dXs = w.take(So * D * 2); L.dlogit = w.take(E > 1 ? T * E * 4 : 0);
   L.dwr = w.take(E > 1 ? pq_dwr_scratch_bytes((int)T, (int)D, (int)E) : 0);

@@ -1,6 +1,7 @@
 """Every split contraction of a library call leaves its slabs inside the section that the call's workspace query reserved for it
 (the launches compare the two and refuse with PQ_ERR_WORKSPACE): whole training and prefill calls, run on the host alone, over
 random sizes of everything the descriptors accept, far beyond the sizes the workloads use."""
+import ctypes
 import math
 import os
 import random
@@ -74,5 +75,29 @@ def test_large_rank_int8_branch():
 def test_random_calls(seed):
     rng = random.Random(seed)
     calls = [draw(rng) for _ in range(500)]
+    for c, r in zip(calls, trace(calls)):
+        assert r["rc"] == 0, (c, r["error"])
+
+
+# bytes that these calls have taken since before the router counted its experts for the ordering of the slots; a workspace allocated once for
+# a model's layers is kept over versions of the library
+LINEAR_BYTES = {(1, 32, 32, 8, 64, 1): 27136, (9, 64, 32, 8, 64, 1): 41472, (105, 5152, 32, 64, 64, 8): 16403712, (1531, 1056, 3104, 24, 4, 2): 30470400,
+                (2100, 64, 96, 8, 16, 3): 4332032}
+FFN_BYTES = {(1, 32, 36, 8, 64, 1, 0): 60928, (64, 256, 512, 128, 1, 1, 0): 837376, (2048, 2048, 5076, 384, 1, 1, 1): 119200768,
+             (300, 512, 1020, 24, 4, 2, 0): 4249856, (35, 64, 164, 32, 64, 8, 1): 850688}
+
+
+def test_routed_calls_take_no_larger_workspace():
+    sizes = {}
+    for T, K, N, r, E, k in LINEAR_BYTES:
+        sizes[T, K, N, r, E, k] = pq.lib().pq_linear_workspace_bytes(ctypes.byref(pq.make_desc(T, K, N, hp_rank=r, n_experts=E, top_k=k)))
+    assert all(n <= LINEAR_BYTES[c] for c, n in sizes.items()), sizes
+    sizes = {}
+    for T, D, F, r, E, k, i8 in FFN_BYTES:
+        sizes[T, D, F, r, E, k, i8] = pq.lib().pq_ffn_workspace_bytes(ctypes.byref(pq.FFNDesc(T, D, F, r, E, k, pq.PQ_BF16, 2.0, 0.2, i8)))
+    assert all(n <= FFN_BYTES[c] for c, n in sizes.items()), sizes
+    calls = [dict(op="linear", tokens=T, d_in=K, d_out=N, hp_rank=r, n_experts=E, top_k=k, workspace_bytes=n)
+             for (T, K, N, r, E, k), n in LINEAR_BYTES.items()]
+    calls += [dict(op="ffn", tokens=T, d_model=D, d_ffn=F, hp_rank=r, n_experts=E, top_k=k, hp_kind=i8) for T, D, F, r, E, k, i8 in FFN_BYTES]
     for c, r in zip(calls, trace(calls)):
         assert r["rc"] == 0, (c, r["error"])
