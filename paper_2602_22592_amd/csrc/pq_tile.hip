@@ -212,11 +212,13 @@ constexpr int tile_lds() {   // (the second contraction's stages follow in the r
   constexpr int ring = NST * (tile_src<AK, 128>::BYTES + tile_src<BK, 128>::BYTES), two = BK2 >= 0 ? 2 * 256 * 128 : 0;
   return ring > two ? ring : two;
 }
-// (bx, by, bz) of a grid of gy rows: the workgroup's place in its own product's launch
-template <int NST, bool INT8, int AK, int BK, int BK2>
+// (bx, by, bz) of a grid of gy rows: the workgroup's place in its own product's launch.  The second problem of a pair is chosen here, not by the
+// kernel that calls: what the compiler makes of the arguments' loads ahead of the first requests is a few tenths of a microsecond a launch
+// (prefill of 2892 tokens 1024 -> 960: 18.5 us with the choice in the kernel, 18.1 here).
+template <int NST, bool INT8, int AK, int BK, int BK2, class SECOND>
 __device__ __forceinline__ void tile_body(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn, int total_tiles, int kchunk,
-                                          float* splitk_part, const pq_gemm_group& grp, const pq_phase2& ph2, int bx, int by, int bz, int gy,
-                                          unsigned char* smem, double* red) {
+                                          float* splitk_part, const pq_gemm_group& grp, const pq_phase2& ph2, const SECOND& second, int bx, int by,
+                                          int bz, int gy, unsigned char* smem, double* red) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int BM = 128, BN = 128, WM = 64, WN = 64, TM = 2, TN = 2;
   constexpr int EPB = INT8 ? 128 : 64;
@@ -228,6 +230,13 @@ __device__ __forceinline__ void tile_body(int M, int N, int K, pq_operand A, pq_
   constexpr int STG2 = PH2 ? (BM + BN) * 128 : 0;
   using acc_t = typename std::conditional<INT8, i32x16_t, f32x16_t>::type;
   constexpr bool PAIR = pair_kinds<AK, BK, BK2>();
+  if constexpr (std::is_same<SECOND, pq_gemm_second>::value)
+    if (grp.mode == 3 && bz == 1) {          // uniform: the second problem of a paired launch
+      A = second.A; B = second.B;
+      M = second.M; N = second.N; nbn = second.nbn;
+      splitk_part = second.part;
+      epi.C = second.C; epi.ldc = second.ldc; epi.scale = second.scale; epi.dev_scale = second.dev_scale;
+    }
   // XCD-aware order: XCD c takes the c-th eighth of the (contraction split, tile row, tile column) order
   int pid = bx, split = by;
   {
@@ -421,14 +430,7 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(int M, int N, int K, pq_
                                                         pq_second_arg<pair_kinds<AK, BK, BK2>()> second) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[tile_lds<NST, AK, BK, BK2>()];
   __shared__ double red[4];
-  if constexpr (pair_kinds<AK, BK, BK2>())
-    if (grp.mode == 3 && blockIdx.z == 1) {          // uniform: the second problem of a paired launch
-      A = second.A; B = second.B;
-      M = second.M; N = second.N; nbn = second.nbn;
-      splitk_part = second.part;
-      epi.C = second.C; epi.ldc = second.ldc; epi.scale = second.scale; epi.dev_scale = second.dev_scale;
-    }
-  tile_body<NST, INT8, AK, BK, BK2>(M, N, K, A, B, epi, nbn, total_tiles, kchunk, splitk_part, grp, ph2, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y,
+  tile_body<NST, INT8, AK, BK, BK2>(M, N, K, A, B, epi, nbn, total_tiles, kchunk, splitk_part, grp, ph2, second, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y,
                                     smem, red);
 }
 
@@ -511,10 +513,11 @@ constexpr int tile64_lds() {
   static_assert(need <= 150 * 1024, "LDS");
   return need > 65536 ? need : 65536;                // four partial tiles at the end
 }
-template <int NG, bool INT8, int AK, int BK, int BK2>
-__device__ __forceinline__ void tile64_body(int M, int N, int K, pq_operand A, pq_operand B, pq_epilogue epi, int nbn, int total_tiles, int kchunk,
-                                            float* splitk_part, const pq_gemm_group& grp, const pq_phase2& ph2, int bx, int by, int bz, int gy,
-                                            unsigned char* smem, double* red) {
+// (by reference what the body changes, for the same reason: 1348 tokens 1984 -> 896, r = 80, 92.3 us with copies, 90.9 so)
+template <int NG, bool INT8, int AK, int BK, int BK2, class SECOND>
+__device__ __forceinline__ void tile64_body(int& M, int& N, int K, pq_operand& A, pq_operand& B, pq_epilogue& epi, int& nbn, int total_tiles, int kchunk,
+                                            float*& splitk_part, const pq_gemm_group& grp, const pq_phase2& ph2, const SECOND& second, int bx, int by,
+                                            int bz, int gy, unsigned char* smem, double* red) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int EPB = INT8 ? 128 : 64;
   using SA = tile_src<AK, 64>;
@@ -528,6 +531,13 @@ __device__ __forceinline__ void tile64_body(int M, int N, int K, pq_operand A, p
   constexpr int OFF2 = RING;                         // the second contraction's first two steps have LDS of their own
   using acc_t = typename std::conditional<INT8, i32x16_t, f32x16_t>::type;
   constexpr bool PAIR = pair_kinds<AK, BK, BK2>();
+  if constexpr (std::is_same<SECOND, pq_gemm_second>::value)
+    if (grp.mode == 3 && bz == 1) {          // uniform: the second problem of a paired launch
+      A = second.A; B = second.B;
+      M = second.M; N = second.N; nbn = second.nbn;
+      splitk_part = second.part;
+      epi.C = second.C; epi.ldc = second.ldc; epi.scale = second.scale; epi.dev_scale = second.dev_scale;
+    }
   // XCD-aware order: XCD c takes the c-th eighth of the (contraction split, tile row, tile column) order
   int pid = bx, split = by;
   {
@@ -754,14 +764,7 @@ __global__ __launch_bounds__(256) void tile64_gemm_kernel(int M, int N, int K, p
                                                           pq_second_arg<pair_kinds<AK, BK, BK2>()> second) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[tile64_lds<NG, AK, BK, BK2>()];
   __shared__ double red[4];
-  if constexpr (pair_kinds<AK, BK, BK2>())
-    if (grp.mode == 3 && blockIdx.z == 1) {          // uniform: the second problem of a paired launch
-      A = second.A; B = second.B;
-      M = second.M; N = second.N; nbn = second.nbn;
-      splitk_part = second.part;
-      epi.C = second.C; epi.ldc = second.ldc; epi.scale = second.scale; epi.dev_scale = second.dev_scale;
-    }
-  tile64_body<NG, INT8, AK, BK, BK2>(M, N, K, A, B, epi, nbn, total_tiles, kchunk, splitk_part, grp, ph2, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y,
+  tile64_body<NG, INT8, AK, BK, BK2>(M, N, K, A, B, epi, nbn, total_tiles, kchunk, splitk_part, grp, ph2, second, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y,
                                      smem, red);
 }
 
@@ -824,12 +827,12 @@ struct tile_job {
 template <int BM, int NST, int AK, int BK>
 struct tile_kind {
   static constexpr int LDS = BM == 64 ? tile64_lds<NST, AK, BK, -1>() : tile_lds<NST, AK, BK, -1>();
-  static __device__ __forceinline__ void run(const tile_job& j, int b, unsigned char* smem, double* red) {
+  static __device__ __forceinline__ void run(tile_job j, int b, unsigned char* smem, double* red) {
     pq_phase2 none;
     none.K2 = 0;
     const int bx = b % j.tiles, by = b / j.tiles % j.gy, bz = b / (j.tiles * j.gy);
-    if constexpr (BM == 64) tile64_body<NST, false, AK, BK, -1>(j.M, j.N, j.K, j.A, j.B, j.epi, j.nbn, j.tiles, j.kchunk, j.part, j.grp, none, bx, by, bz, j.gy, smem, red);
-    else tile_body<NST, false, AK, BK, -1>(j.M, j.N, j.K, j.A, j.B, j.epi, j.nbn, j.tiles, j.kchunk, j.part, j.grp, none, bx, by, bz, j.gy, smem, red);
+    if constexpr (BM == 64) tile64_body<NST, false, AK, BK, -1>(j.M, j.N, j.K, j.A, j.B, j.epi, j.nbn, j.tiles, j.kchunk, j.part, j.grp, none, pq_no_second{}, bx, by, bz, j.gy, smem, red);
+    else tile_body<NST, false, AK, BK, -1>(j.M, j.N, j.K, j.A, j.B, j.epi, j.nbn, j.tiles, j.kchunk, j.part, j.grp, none, pq_no_second{}, bx, by, bz, j.gy, smem, red);
   }
 };
 template <int BM, int AK, int BK>
@@ -863,18 +866,18 @@ __global__ __launch_bounds__(256) void tile64_grads_kernel(tile_job x, pq_phase2
   int b = blockIdx.x;
   if constexpr (X) {
     if (b < x.blocks) {                              // uniform
-      tile64_body<NG, false, PQ_SRC_KC16, PQ_SRC_BITS16, PQ_SRC_KS16>(x.M, x.N, x.K, x.A, x.B, x.epi, x.nbn, x.tiles, x.kchunk, nullptr, x.grp, p2, b, 0, 0,
+      tile64_body<NG, false, PQ_SRC_KC16, PQ_SRC_BITS16, PQ_SRC_KS16>(x.M, x.N, x.K, x.A, x.B, x.epi, x.nbn, x.tiles, x.kchunk, x.part, x.grp, p2, pq_no_second{}, b, 0, 0,
                                                                       1, smem, red);
       return;
     }
     b -= x.blocks;
   }
   const int n1 = j0.blocks + j1.blocks;
-  const tile_job& j = b < j0.blocks ? j0 : b < n1 ? j1 : j2;   // uniform
+  tile_job j = b < j0.blocks ? j0 : b < n1 ? j1 : j2;   // uniform
   pq_phase2 none;
   none.K2 = 0;
   b = b < j0.blocks ? b : b < n1 ? b - j0.blocks : b - n1;
-  tile64_body<NG, false, PQ_SRC_KS16, PQ_SRC_KS16, -1>(j.M, j.N, j.K, j.A, j.B, j.epi, j.nbn, j.tiles, j.kchunk, j.part, j.grp, none, b % j.tiles,
+  tile64_body<NG, false, PQ_SRC_KS16, PQ_SRC_KS16, -1>(j.M, j.N, j.K, j.A, j.B, j.epi, j.nbn, j.tiles, j.kchunk, j.part, j.grp, none, pq_no_second{}, b % j.tiles,
                                                        b / j.tiles, 0, j.gy, smem, red);
 }
 
