@@ -23,6 +23,14 @@ def test_shapes_take_the_form(T, K, N, r, tau):
     assert len(kernels(res, "fixed_rows_kernel")) == 1 and len(kernels(res, "fixed_cols_kernel")) == 1
 
 
+@pytest.mark.parametrize("T,K,N", [(1037, 1056, 1120), (409, 2080, 2080), (2050, 288, 2400), (2048, 2048, 2048), (517, 1568, 1504)])
+def test_both_products_are_one_launch_of_at_most_a_workgroup_per_cu(T, K, N):
+    res = trace([dict(op="linear", tokens=T, d_in=K, d_out=N, io_dtype=0)])[0]
+    assert res["rc"] == 0, res["error"]
+    tiles = (-(-T // 64) + -(-N // 64)) * -(-K // 128)
+    assert [grid for _, grid in kernels(res, "fixed_gemm_kernel")] == [[min(tiles, 256), 1, 1]]
+
+
 # few tokens or narrow layers: the planes' traffic outweighs the products (fp64 backward 157 / 368 / 173 / 170 / 816 us, digits 307 / 943 / 287 / 216 / 820)
 @pytest.mark.parametrize("T,K,N", [(64, 4640, 4096), (64, 8192, 8192), (2048, 8192, 128), (2048, 128, 8192), (65536, 512, 256)])
 def test_shapes_that_digits_would_slow_down_do_not(T, K, N):

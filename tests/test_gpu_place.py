@@ -6,7 +6,8 @@ from launch_trace import kernels, trace
 from test_gpu_tile import test_linear_at_tile_edges as check_linear
 
 # tokens, d_in, d_out, rank, experts, active; workgroups that order the slots (the packing has one)
-CASES = [(2100, 64, 96, 8, 64, 3, 512), (4200, 32, 64, 8, 16, 16, 512), (8300, 32, 32, 8, 8, 2, 512), (300, 32, 64, 8, 5, 5, 76), (3000, 64, 32, 16, 3, 1, 376)]
+CASES = [(2100, 64, 96, 8, 64, 3, 512), (4200, 32, 64, 8, 16, 16, 512), (8300, 32, 32, 8, 8, 2, 512), (300, 32, 64, 8, 5, 5, 76), (3000, 64, 32, 16, 3, 1, 376),
+         (9001, 32, 32, 8, 64, 2, 512)]
 
 
 @pytest.mark.parametrize("T,K,N,r,E,k,groups", CASES)

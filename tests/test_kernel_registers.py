@@ -60,3 +60,22 @@ def test_whole_step_products_keep_nothing_in_scratch(metadata, call):
     assert names, result["launches"]
     spilled = {n: metadata[n][".private_segment_fixed_size"] for n in names if metadata[n][".private_segment_fixed_size"]}
     assert not spilled
+
+
+@pytest.mark.parametrize("call,kernels", [(dict(op="linear", tokens=2048, d_in=2048, d_out=2048, hp_rank=128, io_dtype=0), {"fixed_gemm_kernel"}),
+                                          (dict(op="linear", tokens=1531, d_in=1056, d_out=3104, hp_rank=24, n_experts=4, top_k=2), {"tile_set_kernel"}),
+                                          (dict(op="linear", tokens=393, d_in=5216, d_out=800), {"tile_set_kernel"}),
+                                          (dict(op="ffn", tokens=304, d_model=2368, d_ffn=68, n_experts=8, hp_rank=128, top_k=2), {"tile_set_kernel"}),
+                                          (dict(op="linear", tokens=600, d_in=1056, d_out=1088, hp_rank=264), {"tile64_grads_kernel"}),
+                                          (dict(op="linear", tokens=130, d_in=768, d_out=800, hp_rank=40), {"tile64_grads_kernel"}),
+                                          (dict(op="linear", tokens=1779, d_in=2208, d_out=800, hp_rank=64), {"tile64_grads_kernel"})])
+def test_digit_products_and_shared_launches_keep_nothing_in_scratch(metadata, call, kernels):
+    """... the digit products with 224 accumulators and two sets of operands in 512 registers above all."""
+    result = trace([call])[0]
+    assert result["rc"] == 0, result["error"]
+    for kernel in kernels:
+        names = {n for n in result["symbols"] if kernel in n}
+        assert names, result["launches"]
+        for n in names:
+            m = metadata[n]
+            assert (m[".private_segment_fixed_size"], m[".vgpr_spill_count"]) == (0, 0), n
