@@ -110,7 +110,8 @@ ffn_layout make_layout(const pq_ffn_desc& d) {
   if (8 * S * 2 * r * sizeof(float) > sk) sk = 8 * S * 2 * r * sizeof(float);
   L.splitk = w.take(sk);
   L.splitk_bytes = sk;
-  L.dHd = w.take(T * F * 2); L.dU = w.take(T * F * 2); L.dG = w.take(T * F * 2);
+  // (no gradient of the hidden state where it goes through the gated unit inside its product)
+  L.dHd = w.take(pq_gemm_swiglu_applies(Ti, Fi, Di) ? 0 : T * F * 2); L.dU = w.take(T * F * 2); L.dG = w.take(T * F * 2);
   // (the router's counts, which the forward alone needs, lie in the backward's dYp, see the linear's layout)
   const size_t rt = pq_router_tokens((int)E), counts = E > 1 ? (T + rt - 1) / rt * E * sizeof(int) : 0, dyp = So * D * 2;
   L.hist = L.dYp = w.take(counts > dyp ? counts : dyp);

@@ -1,8 +1,11 @@
 """FFN backward whose hidden-state gradient goes through the gated unit inside the product: rows, columns and contractions that end inside a
 tile or a step, padded hidden widths, one branch and routed ones; against the oracle, with the bar of the other FFN tests."""
+import ctypes
+
 import pytest
 
 from launch_trace import kernels, trace
+from paper_2602_22592_amd import binding as pq
 from paper_2602_22592_amd import workloads as wl
 from test_gpu_ffn import check_ffn
 
@@ -23,6 +26,13 @@ def test_small_tiles_leave_it_apart(T, D, F):
     res = trace([dict(op="ffn", tokens=T, d_model=D, d_ffn=F, hp_rank=8)])[0]
     assert res["rc"] == 0, res["error"]
     assert len(kernels(res, "swiglu_bwd_kernel")) == 1
+
+
+def test_no_memory_for_a_gradient_that_is_not_stored():
+    """The workspace holds dU and dG [T][F], nothing of the size of dHd, and little else (8192 tokens: no split weight gradients)."""
+    T, D, F = 8192, 2048, 5504
+    desc = pq.FFNDesc(T, D, F, 8, 1, 1, pq.PQ_BF16, 2.0, 0.2, pq.PQ_HP_LOWRANK_BF16)
+    assert 2 * (2 * T * F) < pq.lib().pq_ffn_workspace_bytes(ctypes.byref(desc)) < 2.5 * (2 * T * F)
 
 
 @pytest.mark.gpu
