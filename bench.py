@@ -317,9 +317,9 @@ def hp_int8_bench(pq, torch, T=8192, K=2048, N=2048, r=128, steps=100, warmup=20
 
 
 def fp32_io_bench(pq, torch, c, steps=5, warmup=2):
-    """The config-2 step with fp32 activations and gradients: every GEMM except the int8 one runs on the fp64 matrix
-    instructions (the path the tight-tolerance parity tests use).  Reported so that its cost is known; fp64 MFMA peak
-    78.6 TFLOP/s."""
+    """The config-2 step with fp32 activations and gradients, at the precision of fp64 products: those themselves, except the int8 one and
+    the contractions of dX and dW, which are exact int8 products of fixed-point digits (the path the tight-tolerance parity tests use).
+    Reported so that its cost is known; fp64 MFMA peak 78.6 TFLOP/s."""
     T, K, N, r = c["tokens"], c["d_in"], c["d_out"], c["hp_rank"]
     to = lambda x: torch.from_numpy(x).cuda().float()
     X, W, dY, A, B = to(c["X"]), to(c["W"]), to(c["dY"]), to(c["A"]), to(c["B"])
@@ -338,9 +338,9 @@ def fp32_io_bench(pq, torch, c, steps=5, warmup=2):
     big = 2.0 * T * K * N
     return {"workload": "tokens=%d, d_in=%d, d_out=%d, r=%d, fp32 I/O, fwd+bwd" % (T, K, N, r), "ms_per_step": round(ms, 3),
             "tokens_per_s": round(T / (ms * 1e-3), 1),
-            # operations of the one fp64 product over everything a step spends under its label: the int8 product of its digits, the
-            # launch that sums them and what shares it (dX: the rank-r product and dA; dW: dB and dH)
-            **{f"{n}_fp64_equivalent_TFLOPs": round(big / (1e-3 * prof[n][0] / steps) / 1e12, 1) for n in ("gemm_dX", "gemm_dW") if n in prof},
+            # operations of the two fp64 products that the digits stand for, over everything a step spends under the labels of dX and dW: one launch
+            # forms both products, two more finish them together with the rank-r products, dA, dB and dH
+            "dX_dW_fp64_equivalent_TFLOPs": round(2 * big / (1e-3 * sum(prof[n][0] for n in ("gemm_dX", "gemm_dW")) / steps) / 1e12, 1),
             "kernels_us": k_us}
 
 

@@ -492,7 +492,7 @@ int pq_launch_fixed_split(const float* dY, const float* gamma, const int8_t* q, 
 int pq_launch_fixed_products(const int8_t* Drow, const int* rexp, const int8_t* signs, double* SX, const int8_t* Dcol, const int* cexp, const int8_t* qT,
                              double* SW, int T, int N, int K, hipStream_t s) {
   if (T <= 0 || N <= 0 || N % 32 != 0 || K <= 0 || K % 32 != 0) return pq_set_error(PQ_ERR_SHAPE, "digit products: T=%d d_in=%d d_out=%d", T, K, N);
-  pq_prof_scope prof(PQP_GEMM_DX, s);
+  pq_prof_scope prof(PQP_GEMM_DX, s);               // (dW's products too)
   const int nbn = (K + FXN - 1) / FXN;
   const fixed_product x{Drow, signs, rexp, SX, T, K, (N + 63) / 64, nbn}, w{Dcol, qT, cexp, SW, N, K, (T + 63) / 64, nbn};
   const int tx = (T + FXM - 1) / FXM * nbn, tw = (N + FXM - 1) / FXM * nbn, tiles = tx + tw;

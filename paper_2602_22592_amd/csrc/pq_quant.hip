@@ -976,7 +976,7 @@ __global__ __launch_bounds__(256) void pack_place_kernel(const uint16_t* __restr
 int pq_launch_pack_place(const void* W, int N, int K, const double* partials, int nblocks, uint32_t* P, uint32_t* Pt, float* mu_lambda,
                          const pq_place& place, hipStream_t s) {
   if (N % 32 != 0 || K % 32 != 0) return pq_set_error(PQ_ERR_SHAPE, "N=%d and K=%d must be multiples of 32", N, K);
-  pq_prof_scope prof(PQP_PACK, s);
+  pq_prof_scope prof(W ? PQP_PACK : PQP_MOE_ROUTE, s);
   const int gx = (K + 511) / 512, groups = place_groups(place.nblk), subs = place_subs(place.nblk);
   pack_place_kernel<<<groups * subs + (W ? gx * (N / 32) : 0), 256, 0, s>>>((const uint16_t*)W, N, K, partials, nblocks, (uint8_t*)P, Pt, mu_lambda, gx, place,
                                                                           groups, subs);
