@@ -139,7 +139,7 @@ int pq_onebit_acc(const int8_t* Xq, const uint32_t* packed, int32_t T, int32_t K
  * quantised activations and gamma, the hp hidden state, routing decisions); workspace is scratch
  * whose contents need not survive between calls.  Both sizes cover forward and backward.
  * fp32 I/O, latent weights: the workspace of a large call ends with the digits that its backward forms the products of
- * dX and dW from (up to 2 GiB; 14 tokens * d_out + 28 d_in * max(tokens, d_out) bytes).  A workspace without them, i.e. of the size
+ * dX and dW from (up to 2 GiB; about 14 tokens * d_out + 28 d_in * max(tokens, d_out) bytes).  A workspace without them, i.e. of the size
  * that the same descriptor with PQ_W_PACKED asks for, is accepted by both calls; the backward then runs fp64 products
  * (about twice its time). */
 size_t pq_linear_ctx_bytes(const pq_linear_desc* desc);

@@ -127,15 +127,17 @@ struct cursor {
   }
 };
 
-// The two large contractions of the fp32 backward in fixed point: seven int8 products of one in fp64, a quarter of its time, but five
-// more launches (some 20 us), 8 bytes of sums per output and 22 of digits per element of dY, written and read.  Measured while an output's seven
-// int32 sums went through memory (56 bytes: the terms in 1 / d_out and 1 / tokens below); the line was not moved when that traffic went.
-// Backward against the fp64 products, 49 shapes of 64 to 65536 tokens and widths of 128 to 16384:
-// with 1 / tokens + 1 / d_out + 0.4 / d_in up to 1 / 320 1.17 x (512 tokens 1024->4096, 65536 512->512 1.19) to 2.77 x (2048 tokens
-// 4096->4096), beyond it 1.14 x (16384 256->512) down to 0.39 x (64 tokens 8192->8192); below tokens * d_in * d_out = 1.2e9 0.55 to 1.1 x.
-// The int32 sums of dW hold tokens * 2^14, those of dX d_out * 2^7.  Calls whose region would take more than FIXED_MAX_BYTES
-// (14 tokens * d_out + 28 d_in * max(tokens, d_out) bytes: 176 MiB at 2048 tokens 2048x2048, 1.9 GiB at 4096 tokens 4096x11008) keep
-// the fp64 products.
+// The two large contractions of the fp32 backward in fixed point: seven int8 products of one in fp64, a quarter of its time, but four
+// more launches (some 20 us), 8 bytes of sums per output and 22 of digits per element of dY, written and read.  The line was drawn while an
+// output's seven int32 sums went through memory (56 bytes: its terms in 1 / tokens and 1 / d_out) and has not been moved since.
+// Backward against the fp64 products, both as they are now, 40 shapes of 64 to 65536 tokens and widths of 128 to 11008: inside the line 1.11 x
+// (65536 tokens 512->512) to 3.95 x (4096 4096->11008), 2048 tokens 2048x2048 554 / 168 us; outside it 0.52 x (512 512->512, 32768 256->256) to
+// 1.9 x: the digits would be ahead for few tokens through wide layers (256 11008->4096 770 / 405 us, 128 8192->8192 593 / 514) and narrow outputs of
+// few thousand tokens (2048 4096->256 165 / 99), behind for 64 tokens (8192->8192 349 / 503) and many tokens through narrow layers.
+// The int32 sums of dW hold tokens * 2^14, those of dX d_out * 2^7.  Calls whose region would take more than FIXED_MAX_BYTES keep the fp64
+// products.  The region is counted as 14 tokens * d_out + tokens * d_in + 28 d_in * max(tokens, d_out) bytes, what it was with the int32 sums and callers
+// have sized it by: 172 MiB at 2048 tokens 2048x2048 (130 used), 1.8 GiB at 4096 tokens 4096x11008 (1.1 used); the 1.9 GiB that
+// 8192 tokens 4096->11008 would use count as 2.4.
 constexpr size_t FIXED_MAX_BYTES = (size_t)2 << 30;
 bool fixed_applies(int T, int K, int N) {
   return T <= 65536 && N <= 65536 && (double)T * K * N >= 1.2e9 && 1.0 / T + 1.0 / N + 0.4 / K <= 1.0 / 320;
@@ -232,7 +234,7 @@ lin_layout make_layout(const pq_linear_desc& d) {
     L.fx_counts = x.take((2 * N + K) * sizeof(int));
     L.fx_red_b = x.take(sizeof(double) * (size_t)pq_ref_red_blocks(Ni, Ki, -1));
     L.fx_SW = x.take(N * K * sizeof(double)); L.fx_SX = x.take(T * K * sizeof(double));
-    // (the region is never smaller than 14 T N + K T + 28 K max(T, N) bytes, what callers have sized it by)
+    // (never smaller than what callers have sized it by, see FIXED_MAX_BYTES)
     const size_t least = 14 * T * N + K * T + 28 * K * (T > N ? T : N);
     if (x.off < least) x.take(least - x.off);
     if (x.off <= FIXED_MAX_BYTES) {

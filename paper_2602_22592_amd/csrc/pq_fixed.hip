@@ -14,16 +14,16 @@
 // at least l - z larger elements enter it then and at most eight times as many small ones, so that it is off by at most 2^-28 of
 // sum |x q|, a sixteenth of the rounding to fp32.  A 32x32 tile with another sum in it
 // is formed as the fp64 product it stands for.  One token 1e9 / 1e12 / 1e16 times the others: relative error of the sums that its zero
-// codes leave out 3.2e-8 / 1.9e-5 / 0.2 from the digits, 2.6e-8 now.  Backward of 2048 tokens 2048x2048 (us): 248 with normal data; 218 to
-// 249 with 95 % zero codes, half of the tokens masked, token scales of e^+-6 or elements of e^+-10; 538 with one token 1e6 times the others
+// codes leave out 3.2e-8 / 1.9e-5 / 0.2 from the digits, 2.6e-8 now.  Backward of 2048 tokens 2048x2048 (us): 166 with normal data; 154 to
+// 165 with 95 % zero codes, half of the tokens masked, token scales of e^+-6 or elements of e^+-10; 476 with one token 1e6 times the others
 // (all tiles fp64).
 // What it is for: the fp64 matrix rate is 78.6 TFLOP/s, the int8 one 5 POP/s nominal and 2 on real data, so seven products cost a
 // quarter of one fp64 product.  2048 tokens, 2048x2048, r = 128, whole step (us): 718 with every product in fp64, 380 with the digits' int32 sums
-// added up from memory, 333 with the sums formed where they are multiplied; the passes below 13, 5 and 20, two of them over dY, 4 bytes read
+// added up from memory, 326 with the sums formed where they are multiplied; the passes below 13, 5 and 16, two of them over dY, 4 bytes read
 // and 7 written per element.
 // Infinities and NaN have no fixed-point form: their rows get no digits and are marked, and the SUM forms compute a 32x32 tile that
-// a marked row reaches as the fp64 product it stands for.  Step of 2048 tokens 2048x2048 without a branch, int32 sums in memory (us): finite 300; one NaN in dY 443; an infinity in X, which marks every
-// row of dW, 604 (one element after the other: 1115 and 5368; fp64 products alone 600).
+// a marked row reaches as the fp64 product it stands for.  Step of 2048 tokens 2048x2048 without a branch (us): finite 206; one NaN in dY 363; an infinity in X, which marks every
+// row of dW, 515 (one element after the other: 1115 and 5368; fp64 products alone 594).
 #include <string.h>
 #include <type_traits>
 #include "pq_epilogue.h"
