@@ -381,7 +381,9 @@ int pq_glue_gather_rows(const void* table, const int32_t* ids, int32_t T, int32_
  * bracketed by a pair of HIP events on the caller's stream (events are created on demand, so this
  * mode allocates; it is off by default).  pq_prof_count() = number of kernel labels;
  * pq_prof_label(i) = host string naming label i; pq_prof_read(i, &ms, &launches) waits for the
- * recorded events of label i and returns their summed duration in milliseconds and their count;
+ * recorded events of label i and returns their summed duration in milliseconds and their count (a launch that forms
+ * several products counts under one of them: a shared one of dW, dB, dA and dX under gemm_dW, the digit products of an
+ * fp32 backward under gemm_dX);
  * pq_prof_reset() drops all recorded samples. */
 int pq_prof_enable(int on);
 int pq_prof_count(void);
